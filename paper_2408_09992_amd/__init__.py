@@ -14,7 +14,8 @@ __all__ = ["workloads", "pq_subitem_scores", "pq_score_topk", "pq_score_topk_wor
 def __getattr__(name):
     if name in __all__[1:]:
         from . import binding
-        return getattr(binding, name)
+        globals()[name] = found = getattr(binding, name)       # (the next use finds it without coming here)
+        return found
     if name in ("workloads", "binding", "build"):
         import importlib
         return importlib.import_module(f"{__name__}.{name}")

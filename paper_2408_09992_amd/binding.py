@@ -1,5 +1,8 @@
 """Python names for the C ABI in include/pqtopk.h: argument marshalling only.
 
+The scoring calls go through _pqnative.so (csrc/py_native.cpp), which marshals plain arguments in C; arguments it does
+not take come back here, where they are checked one by one and reported.
+
 Every computation happens in the HIP kernels of libpqtopk.so.  Tensors are torch CUDA (ROCm) tensors, used here
 only as device memory; work is enqueued on torch's current stream.  If the library has not been built the import
 of the first entry point raises: there is no CPU fallback.
@@ -20,6 +23,7 @@ PQ_ERR_TOO_LARGE = -7
 PQ_STATIC_SCRATCH_BYTES = 8 << 20
 
 _lib = None
+_native_module = None
 
 
 class PQError(RuntimeError):
@@ -85,6 +89,20 @@ def lib() -> ctypes.CDLL:
     return _lib
 
 
+def _native():
+    """The C fast path of the scoring calls; raises if it was never built."""
+    global _native_module
+    if _native_module is None:
+        lib()
+        try:
+            from . import _pqnative
+        except ImportError as e:
+            raise RuntimeError("_pqnative.so is missing: build it with `python -m paper_2408_09992_amd.build` "
+                               "(there is no fallback path)") from e
+        _native_module = _pqnative
+    return _native_module
+
+
 def pq_strerror(code: int) -> str:
     return lib().pq_strerror(int(code)).decode()
 
@@ -103,6 +121,11 @@ def _stream() -> int:
 
 def pq_subitem_scores(queries: torch.Tensor, centroids: torch.Tensor, out: Optional[torch.Tensor] = None) -> torch.Tensor:
     """Eq. 4: queries [B][d], centroids [m][b][d/m] -> S [B][m][b] (all fp32, on the device)."""
+    r = (_native_module or _native()).subitem_scores(queries, centroids, out)
+    if r.__class__ is int:
+        raise PQError(r, "pq_subitem_scores")
+    if r is not None:
+        return r
     _dev(queries, torch.float32, "queries")
     _dev(centroids, torch.float32, "centroids")
     B, d = queries.shape
@@ -144,6 +167,11 @@ def pq_score_topk(codes: torch.Tensor, S: torch.Tensor, K: int, workspace: Optio
                   out_ids: Optional[torch.Tensor] = None, out_scores: Optional[torch.Tensor] = None
                   ) -> Tuple[torch.Tensor, torch.Tensor]:
     """Algorithm 1 (V = I): codes uint8 [N][m], S fp32 [B][m][b] -> (ids int32 [B][K], scores fp32 [B][K])."""
+    r = (_native_module or _native()).score_topk(codes, S, K, workspace, out_ids, out_scores)
+    if r.__class__ is int:
+        raise PQError(r, "pq_score_topk")
+    if r is not None:
+        return r
     N, B, m, b, workspace, out_ids, out_scores = _topk_args(codes, S, K, workspace, out_ids, out_scores)
     rc = lib().pq_score_topk(codes.data_ptr(), S.data_ptr(), N, B, m, b, K, out_ids.data_ptr(),
                              out_scores.data_ptr(), workspace.data_ptr(), workspace.numel(), _stream())
@@ -179,6 +207,11 @@ def pq_score_topk_u16(codes: torch.Tensor, S: torch.Tensor, K: int, workspace: O
                       ) -> Tuple[torch.Tensor, torch.Tensor]:
     """Algorithm 1 (V = I) over 16-bit sub-ids: codes uint16 [N][m], S fp32 [B][m][b], b <= 65536
     -> (ids int32 [B][K], scores fp32 [B][K])."""
+    r = (_native_module or _native()).score_topk_u16(codes, S, K, workspace, out_ids, out_scores)
+    if r.__class__ is int:
+        raise PQError(r, "pq_score_topk_u16")
+    if r is not None:
+        return r
     N, B, m, b, workspace, out_ids, out_scores = _topk_args(codes, S, K, workspace, out_ids, out_scores, wide=True)
     rc = lib().pq_score_topk_u16(codes.data_ptr(), S.data_ptr(), N, B, m, b, K, out_ids.data_ptr(),
                                  out_scores.data_ptr(), workspace.data_ptr(), workspace.numel(), _stream())
@@ -229,6 +262,11 @@ def pq_score_topk_subset(codes: torch.Tensor, S: torch.Tensor, subset: torch.Ten
                          workspace: Optional[torch.Tensor] = None, out_ids: Optional[torch.Tensor] = None,
                          out_scores: Optional[torch.Tensor] = None) -> Tuple[torch.Tensor, torch.Tensor]:
     """Algorithm 1 with a candidate list V: subset int32 [n] of distinct item ids -> the K best items of the list."""
+    r = (_native_module or _native()).score_topk_subset(codes, S, subset, K, workspace, out_ids, out_scores)
+    if r.__class__ is int:
+        raise PQError(r, "pq_score_topk_subset")
+    if r is not None:
+        return r
     n, N, B, m, b, workspace, out_ids, out_scores = _subset_args(codes, S, subset, K, workspace, out_ids, out_scores)
     rc = lib().pq_score_topk_subset(codes.data_ptr(), S.data_ptr(), subset.data_ptr(), n, N, B, m, b, K,
                                     out_ids.data_ptr(), out_scores.data_ptr(), workspace.data_ptr(),
@@ -403,73 +441,80 @@ def pq_measure_step_stamps(queries: torch.Tensor, centroids: torch.Tensor, codes
     return int(grid[0]), int(grid[1])
 
 
-class _Prepared:
-    """An entry point with its arguments marshalled once; calling the object only enqueues (for tight serving loops).
-    The tensors are kept alive by the object; `stream` is a raw hipStream_t handle (default: torch's current stream at
-    construction)."""
+def _prepared_class():
+    """Base of the Prepared classes: an entry point with its arguments marshalled once; calling the object only enqueues
+    (for tight serving loops).  The tensors are kept alive by the object; `stream` is a raw hipStream_t handle (default:
+    torch's current stream at construction)."""
+    native = _native()
 
-    def _prepare(self, entry: str, keep, result, stream: Optional[int], make_args):
-        self._entry, self._keep, self._result = entry, keep, result
-        self._fn = getattr(lib(), entry)
-        self._args = make_args(ctypes.c_void_p(_stream() if stream is None else stream))
+    class _Prepared(native.Enqueue):
+        def _prepare(self, entry: str, which: int, keep, result, stream: Optional[int], in0, in1, in2=0, n=0, N=0, B=0, d=0, m=0,
+                     b=0, K=0, out0=0, out1=0, ws=0, ws_bytes=0):
+            self._keep = keep
 
-    def __call__(self):
-        rc = self._fn(*self._args)
-        if rc != PQ_OK:
-            raise PQError(rc, self._entry)
-        return self._result
+            def failed(rc):
+                raise PQError(rc, entry)
+
+            self._bind(which, in0, in1, in2, n, N, B, d, m, b, K, out0, out1, ws, ws_bytes, _stream() if stream is None else stream,
+                       result, failed)
+
+    class PreparedSubitemScores(_Prepared):
+        """pq_subitem_scores, marshalled once; returns S."""
+
+        def __init__(self, queries: torch.Tensor, centroids: torch.Tensor, out: Optional[torch.Tensor] = None,
+                     stream: Optional[int] = None):
+            _dev(queries, torch.float32, "queries")
+            _dev(centroids, torch.float32, "centroids")
+            B, d = queries.shape
+            m, b, s = centroids.shape
+            if m * s != d:
+                raise PQError(PQ_ERR_SHAPE, "pq_subitem_scores")
+            self.S = out if out is not None else torch.empty((B, m, b), dtype=torch.float32, device=queries.device)
+            _dev(self.S, torch.float32, "S")
+            self._prepare("pq_subitem_scores", native.SUBITEM, (queries, centroids), self.S, stream, queries.data_ptr(),
+                          centroids.data_ptr(), B=B, d=d, m=m, b=b, out0=self.S.data_ptr())
+
+    class PreparedScoreTopK(_Prepared):
+        """pq_score_topk, marshalled once (workspace and outputs allocated here if not given); returns (ids, scores)."""
+        _ENTRY, _WIDE = "pq_score_topk", False
+
+        def __init__(self, codes: torch.Tensor, S: torch.Tensor, K: int, workspace: Optional[torch.Tensor] = None,
+                     out_ids: Optional[torch.Tensor] = None, out_scores: Optional[torch.Tensor] = None,
+                     stream: Optional[int] = None):
+            N, B, m, b, workspace, out_ids, out_scores = _topk_args(codes, S, K, workspace, out_ids, out_scores, wide=self._WIDE)
+            self.ids, self.scores, self.workspace = out_ids, out_scores, workspace
+            self._prepare(self._ENTRY, native.TOPK_U16 if self._WIDE else native.TOPK, (codes, S), (out_ids, out_scores), stream,
+                          codes.data_ptr(), S.data_ptr(), N=N, B=B, m=m, b=b, K=K, out0=out_ids.data_ptr(),
+                          out1=out_scores.data_ptr(), ws=workspace.data_ptr(), ws_bytes=workspace.numel())
+
+    class PreparedScoreTopKU16(PreparedScoreTopK):
+        """pq_score_topk_u16, marshalled once (same signature, uint16 codes)."""
+        _ENTRY, _WIDE = "pq_score_topk_u16", True
+
+    class PreparedScoreTopKSubset(_Prepared):
+        """pq_score_topk_subset, marshalled once (workspace and outputs allocated here if not given); returns (ids, scores)."""
+
+        def __init__(self, codes: torch.Tensor, S: torch.Tensor, subset: torch.Tensor, K: int,
+                     workspace: Optional[torch.Tensor] = None, stream: Optional[int] = None):
+            n, N, B, m, b, workspace, self.ids, self.scores = _subset_args(codes, S, subset, K, workspace, None, None)
+            self.workspace = workspace
+            self._prepare("pq_score_topk_subset", native.TOPK_SUBSET, (codes, S, subset), (self.ids, self.scores), stream,
+                          codes.data_ptr(), S.data_ptr(), subset.data_ptr(), n=n, N=N, B=B, m=m, b=b, K=K,
+                          out0=self.ids.data_ptr(), out1=self.scores.data_ptr(), ws=workspace.data_ptr(),
+                          ws_bytes=workspace.numel())
+
+    found = {c.__name__: c for c in (PreparedSubitemScores, PreparedScoreTopK, PreparedScoreTopKU16, PreparedScoreTopKSubset)}
+    for c in found.values():
+        c.__qualname__ = c.__name__
+    return found
 
 
-class PreparedSubitemScores(_Prepared):
-    """pq_subitem_scores, marshalled once; returns S."""
-
-    def __init__(self, queries: torch.Tensor, centroids: torch.Tensor, out: Optional[torch.Tensor] = None,
-                 stream: Optional[int] = None):
-        _dev(queries, torch.float32, "queries")
-        _dev(centroids, torch.float32, "centroids")
-        B, d = queries.shape
-        m, b, s = centroids.shape
-        if m * s != d:
-            raise PQError(PQ_ERR_SHAPE, "pq_subitem_scores")
-        self.S = out if out is not None else torch.empty((B, m, b), dtype=torch.float32, device=queries.device)
-        _dev(self.S, torch.float32, "S")
-        c = ctypes
-        self._prepare("pq_subitem_scores", (queries, centroids), self.S, stream, lambda st: (
-            c.c_void_p(queries.data_ptr()), c.c_void_p(centroids.data_ptr()), c.c_void_p(self.S.data_ptr()),
-            c.c_int(B), c.c_int(d), c.c_int(m), c.c_int(b), st))
-
-
-class PreparedScoreTopK(_Prepared):
-    """pq_score_topk, marshalled once (workspace and outputs allocated here if not given); returns (ids, scores)."""
-    _ENTRY, _WIDE = "pq_score_topk", False
-
-    def __init__(self, codes: torch.Tensor, S: torch.Tensor, K: int, workspace: Optional[torch.Tensor] = None,
-                 out_ids: Optional[torch.Tensor] = None, out_scores: Optional[torch.Tensor] = None,
-                 stream: Optional[int] = None):
-        N, B, m, b, workspace, out_ids, out_scores = _topk_args(codes, S, K, workspace, out_ids, out_scores, wide=self._WIDE)
-        self.ids, self.scores, self.workspace = out_ids, out_scores, workspace
-        c = ctypes
-        self._prepare(self._ENTRY, (codes, S), (out_ids, out_scores), stream, lambda st: (
-            c.c_void_p(codes.data_ptr()), c.c_void_p(S.data_ptr()), c.c_longlong(N), c.c_int(B), c.c_int(m),
-            c.c_int(b), c.c_int(K), c.c_void_p(out_ids.data_ptr()), c.c_void_p(out_scores.data_ptr()),
-            c.c_void_p(workspace.data_ptr()), c.c_size_t(workspace.numel()), st))
-
-
-class PreparedScoreTopKU16(PreparedScoreTopK):
-    """pq_score_topk_u16, marshalled once (same signature, uint16 codes)."""
-    _ENTRY, _WIDE = "pq_score_topk_u16", True
-
-
-class PreparedScoreTopKSubset(_Prepared):
-    """pq_score_topk_subset, marshalled once (workspace and outputs allocated here if not given); returns (ids, scores)."""
-
-    def __init__(self, codes: torch.Tensor, S: torch.Tensor, subset: torch.Tensor, K: int,
-                 workspace: Optional[torch.Tensor] = None, stream: Optional[int] = None):
-        n, N, B, m, b, workspace, self.ids, self.scores = _subset_args(codes, S, subset, K, workspace, None, None)
-        self.workspace = workspace
-        c = ctypes
-        self._prepare("pq_score_topk_subset", (codes, S, subset), (self.ids, self.scores), stream, lambda st: (
-            c.c_void_p(codes.data_ptr()), c.c_void_p(S.data_ptr()), c.c_void_p(subset.data_ptr()),
-            c.c_longlong(n), c.c_longlong(N), c.c_int(B), c.c_int(m), c.c_int(b), c.c_int(K),
-            c.c_void_p(self.ids.data_ptr()), c.c_void_p(self.scores.data_ptr()),
-            c.c_void_p(workspace.data_ptr()), c.c_size_t(workspace.numel()), st))
+def __getattr__(name):
+    # (the Prepared classes derive from a type of the native module, which is loaded when the first of them is asked for:
+    # importing this module never needs a built library)
+    if name.startswith("Prepared"):
+        found = _prepared_class()
+        if name in found:
+            globals().update(found)
+            return found[name]
+    raise AttributeError(f"module {__name__!r} has no attribute {name!r}")

@@ -1,4 +1,5 @@
-"""Compile the HIP library (csrc/*.hip and the .hpp parts they include -> libpqtopk.so, in-tree) for gfx950.
+"""Compile the HIP library (csrc/*.hip and the .hpp parts they include -> libpqtopk.so, in-tree) for gfx950, and the
+Python entry points' marshalling (csrc/py_native.cpp, host code against torch's headers -> _pqnative.so).
 
 The translation units are compiled side by side (the scan kernels are large: tens of seconds each) and linked
 into one shared library."""
@@ -7,6 +8,7 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
@@ -17,6 +19,8 @@ SOURCES = sorted(os.path.join(CSRC, f) for f in os.listdir(CSRC) if f.endswith("
 HEADERS = sorted(os.path.join(ROOT, "include", f) for f in os.listdir(os.path.join(ROOT, "include")) if f.endswith(".h")) + \
     sorted(os.path.join(CSRC, f) for f in os.listdir(CSRC) if f.endswith(".hpp"))
 LIB = os.path.join(_HERE, "libpqtopk.so")
+NATIVE_SOURCE = os.path.join(CSRC, "py_native.cpp")
+NATIVE = os.path.join(_HERE, "_pqnative.so")
 
 # -packed-fp32-ops switches the packed FP32 instructions (v_pk_add_f32 and friends) off in the DEVICE code.  hipcc hands
 # -Xclang options to its host pass as well, where the x86 back end answers with one line per function saying that it does
@@ -31,10 +35,10 @@ _HOST_PASS_NOISE = "'-packed-fp32-ops' is not a recognized feature for this targ
 
 
 def is_stale() -> bool:
-    if not os.path.exists(LIB):
+    if not os.path.exists(LIB) or not os.path.exists(NATIVE):
         return True
-    t = os.path.getmtime(LIB)
-    return any(os.path.getmtime(p) > t for p in SOURCES + HEADERS)
+    t = min(os.path.getmtime(LIB), os.path.getmtime(NATIVE))
+    return any(os.path.getmtime(p) > t for p in SOURCES + HEADERS + [NATIVE_SOURCE])
 
 
 def _run(cmd, verbose):
@@ -46,6 +50,18 @@ def _run(cmd, verbose):
         print(out, file=sys.stderr, flush=True)
     if r.returncode != 0:
         raise subprocess.CalledProcessError(r.returncode, cmd)
+
+
+def _build_native(verbose):
+    """_pqnative.so; linked after libpqtopk.so, which it finds beside itself."""
+    import torch
+    root = os.path.dirname(os.path.abspath(torch.__file__))
+    _run([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
+          f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", "-I", os.path.join(ROOT, "include"),
+          "-isystem", sysconfig.get_paths()["include"], "-isystem", os.path.join(root, "include"),
+          "-isystem", os.path.join(root, "include", "torch", "csrc", "api", "include"), "-isystem", "/opt/rocm/include",
+          NATIVE_SOURCE, "-o", NATIVE, "-L", _HERE, "-lpqtopk", "-L", os.path.join(root, "lib"),
+          "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_hip", "-ltorch_python", "-Wl,-rpath,$ORIGIN"], verbose)
 
 
 def build(force: bool = True, verbose: bool = False, jobs: int = 0) -> str:
@@ -68,6 +84,7 @@ def build(force: bool = True, verbose: bool = False, jobs: int = 0) -> str:
     with ThreadPoolExecutor(max_workers=jobs) as pool:
         list(pool.map(compile_one, zip(SOURCES, objs)))
     _run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs], verbose)
+    _build_native(verbose)
     return LIB
 
 
