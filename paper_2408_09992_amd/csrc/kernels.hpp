@@ -18,6 +18,7 @@ namespace pqk {
 #include "scan_short.hpp"
 #include "scan_subset.hpp"
 #include "scan_batched.hpp"
+#include "scan_filter.hpp"
 #include "fold.hpp"
 #ifndef PQ_INSTANCE_TU
 #include "comparison.hpp"   // (kernels that are no templates: defined once, in the translation unit that launches them)
@@ -72,6 +73,22 @@ namespace pqk {
 #define PQ_SUBSET_M(X, M) X(M, 1, kThreads) X(M, 2, kThreads) X(M, 3, kThreads) X(M, 4, kThreads) X(M, 5, kThreads) \
     X(M, 6, kThreads) X(M, 7, kThreads) X(M, 8, kThreads)
 #define PQ_SUBSET_INSTANCES(X) PQ_SUBSET_M(X, 4) PQ_SUBSET_M(X, 8) PQ_SUBSET_M(X, 16)
+// scan_filter_kernel<M, CW, W, W16, SUB, FINE> and filter_prepare_kernel<M, CW, SUB>, by translation unit.  X for scans, Y
+// for the kernels that prepare them
+#define PQ_FILTER_W3(X, M, CW, W16, SUB, FINE) X(M, CW, 1, W16, SUB, FINE) X(M, CW, 2, W16, SUB, FINE) X(M, CW, 4, W16, SUB, FINE)
+#define PQ_FILTER_W8(X, M, CW, SUB) PQ_FILTER_W3(X, M, CW, false, SUB, false) PQ_FILTER_W3(X, M, CW, false, SUB, true)
+#define PQ_FILTER_INSTANCES_A(X, Y) PQ_FILTER_W8(X, 4, 1, false) PQ_FILTER_W8(X, 8, 1, false) Y(4, 1, false) Y(8, 1, false)
+#define PQ_FILTER_INSTANCES_B(X, Y) PQ_FILTER_W8(X, 16, 1, false) PQ_FILTER_W3(X, 16, 1, true, false, false) Y(16, 1, false)
+#define PQ_FILTER_INSTANCES_C(X, Y) \
+    PQ_FILTER_W3(X, 32, 1, true, false, false) X(64, 1, 1, true, false, false) X(64, 1, 2, true, false, false) Y(32, 1, false) Y(64, 1, false)
+#define PQ_FILTER_INSTANCES_SUBSET(X, Y) \
+    PQ_FILTER_W8(X, 4, 1, true) PQ_FILTER_W8(X, 8, 1, true) PQ_FILTER_W8(X, 16, 1, true) PQ_FILTER_W3(X, 16, 1, true, true, false) \
+    Y(4, 1, true) Y(8, 1, true) Y(16, 1, true)
+#define PQ_FILTER_INSTANCES_U16(X, Y) \
+    PQ_FILTER_W8(X, 4, 2, false) PQ_FILTER_W8(X, 8, 2, false) PQ_FILTER_W8(X, 16, 2, false) PQ_FILTER_W3(X, 16, 2, true, false, false) \
+    Y(4, 2, false) Y(8, 2, false) Y(16, 2, false)
+// measurement instances (wall-clock stamps per wave) of those the named batch workloads run
+#define PQ_FILTER_INSTANCES_STAMPED(X) X(8, 1, 4, false, false, true, true) X(16, 1, 4, false, false, false, true)
 // the batched kernel
 #define PQ_TILED_INSTANCES(X) X(8, false) X(16, false) X(8, true) X(16, true)
 
@@ -85,6 +102,12 @@ namespace pqk {
 #define PQ_SHORT16_EXTERN(M, U, NT, ST, CW) extern PQ_SHORT16_DEFINE(M, U, NT, ST, CW)
 #define PQ_SUBSET_DEFINE(M, U, NT) template __global__ void scan_subset_kernel<M, U, NT>(ScanArgs);
 #define PQ_SUBSET_EXTERN(M, U, NT) extern PQ_SUBSET_DEFINE(M, U, NT)
+#define PQ_FILTER_DEFINE(M, CW, W, W16, SUB, FINE) template __global__ void scan_filter_kernel<M, CW, W, W16, SUB, FINE>(FilterArgs);
+#define PQ_FILTER_EXTERN(M, CW, W, W16, SUB, FINE) extern PQ_FILTER_DEFINE(M, CW, W, W16, SUB, FINE)
+#define PQ_FILTER_DEFINE7(M, CW, W, W16, SUB, FINE, ST) template __global__ void scan_filter_kernel<M, CW, W, W16, SUB, FINE, ST>(FilterArgs);
+#define PQ_FILTER_EXTERN7(M, CW, W, W16, SUB, FINE, ST) extern PQ_FILTER_DEFINE7(M, CW, W, W16, SUB, FINE, ST)
+#define PQ_FILTERP_DEFINE(M, CW, SUB) template __global__ void filter_prepare_kernel<M, CW, SUB>(FilterArgs);
+#define PQ_FILTERP_EXTERN(M, CW, SUB) extern PQ_FILTERP_DEFINE(M, CW, SUB)
 #define PQ_TILED_DEFINE(M, ST) template __global__ void scan_topk_tiled_kernel<M, ST>(ScanArgs, int);
 #define PQ_TILED_EXTERN(M, ST) extern PQ_TILED_DEFINE(M, ST)
 
@@ -101,6 +124,12 @@ PQ_SHORT_INSTANCES_C(PQ_SHORT_EXTERN)
 PQ_SUBSET_INSTANCES(PQ_SUBSET_EXTERN)
 PQ_SHORT16_INSTANCES(PQ_SHORT16_EXTERN)
 PQ_TILED_INSTANCES(PQ_TILED_EXTERN)
+PQ_FILTER_INSTANCES_STAMPED(PQ_FILTER_EXTERN7)
+PQ_FILTER_INSTANCES_A(PQ_FILTER_EXTERN, PQ_FILTERP_EXTERN)
+PQ_FILTER_INSTANCES_B(PQ_FILTER_EXTERN, PQ_FILTERP_EXTERN)
+PQ_FILTER_INSTANCES_C(PQ_FILTER_EXTERN, PQ_FILTERP_EXTERN)
+PQ_FILTER_INSTANCES_SUBSET(PQ_FILTER_EXTERN, PQ_FILTERP_EXTERN)
+PQ_FILTER_INSTANCES_U16(PQ_FILTER_EXTERN, PQ_FILTERP_EXTERN)
 #endif
 
 }  // namespace pqk

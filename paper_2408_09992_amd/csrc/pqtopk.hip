@@ -28,6 +28,7 @@
 // that kernels.hpp gathers in namespace pqk; the large scan kernels are compiled in the inst_*.hip translation units
 // and only launched from here.
 #include <hip/hip_runtime.h>
+#include <math.h>
 #include <stdint.h>
 #include <string.h>
 
@@ -95,7 +96,22 @@ struct ScanPlan {
     int short_units; // ... units (code vectors, or items for m = 32, 64) a thread holds
     bool short_subset; // scan_subset_kernel: a candidate list whose share per thread fits its registers, K small
     int subset_vecs;   // ... code vectors' worth of gathered rows a thread holds
+    bool filter;       // filter_prepare_kernel + scan_filter_kernel: a batch scanned by integer upper bounds
+    int f_words;       // ... 32-bit words of a table entry
+    bool f_w16;        // ... 16-bit fields (8-bit otherwise)
+    int f_queries;     // ... queries per workgroup
+    int f_cap;         // ... keys of a query's list
+    bool f_fine;       // ... 16-bit counts beside 8-bit fields
+    bool f_share;      // ... the workgroups of a query share their floors
+    int f_sample;      // ... units of a part's sample
+    int f_rounds;      // ... rounds of a part's sample
+    int f_parts;       // ... parts of the sample
+    int f_best;        // ... scores a part leaves (several parts)
+    long long f_entries;  // ... table entries
 };
+
+// What make_plan() may choose from.
+enum { kNoFilter = 1 };
 
 bool is_vec_m(int m) { return m == 1 || m == 2 || m == 4 || m == 8 || m == 16 || m == 32 || m == 64; }
 
@@ -142,7 +158,10 @@ double tiled_min_lookups(int m, int K) {
 
 // `generic`: plan for the generic kernel whatever m is (candidate-list scans use it: their rows are gathered)
 // `cw`, `b`: bytes per sub-id (1 or 2) and, for two-byte sub-ids, the alphabet size (it sizes the tables in LDS)
-ScanPlan make_plan(long long N, int B, int m, int K, bool generic = false, int cw = 1, int b = kLutStride) {
+size_t workspace_bytes(const ScanPlan& p, int B, int K);
+void plan_filter(ScanPlan& p, long long N, int B, int m, int K, bool subset, int cw, int b);
+
+ScanPlan make_plan(long long N, int B, int m, int K, bool generic = false, int cw = 1, int b = kLutStride, int without = 0) {
     ScanPlan p;
     const int row = m * cw;                                    // bytes of an item's row
     size_t lut_floats = cw == 1 ? (size_t)m * kLutStride : (size_t)m * b;
@@ -306,7 +325,113 @@ ScanPlan make_plan(long long N, int B, int m, int K, bool generic = false, int c
             p.scan_lds = (size_t)m * kLutStride * sizeof(float) + sizeof(SmallSelectLds<kThreads>);
         }
     }
+    p.filter = false;
+    if (!(without & kNoFilter)) {
+        ScanPlan f = p;
+        plan_filter(f, N, B, m, K, generic, cw, b);
+        // (a workspace of at most 32 KB per result and 1 MB: the tables of tens of thousands of queries can be more)
+        if (f.filter && workspace_bytes(f, B, K) <= ((size_t)B * K << 15) + (1u << 20)) p = f;
+    }
     return p;
+}
+
+// LDS reads a CU returns per clock when every lane reads at random: of 4-, 8- and 16-byte words.
+constexpr double kGather4 = 8.7, kGather8 = 8.5, kGather16 = 5.0;
+
+// Lookups (B * N * m) from which a batch is scanned by upper bounds.  Measured on catalogues of 2e4 to 1.3e6 items, batches of
+// 2 to 256 queries: the sample, the tables and one launch more (some 12 us together) are paid back from 7e7 lookups on at
+// K = 10 and m <= 8; longer rows cost more to prepare; a larger K means more items scored exactly.  With more than 256
+// results the lists leave room for half the queries only.  Candidate lists gain earlier: the rows are gathered once per
+// sixteen queries instead of once per query.
+double filter_min_lookups(int m, int K, bool subset) {
+    if (K > 256) return 2.0e9;
+    const double at_small_k = subset ? 2.5e7 : m <= 8 ? 7.0e7 : m == 16 ? 9.0e7 : m == 32 ? 1.3e8 : 2.0e8;
+    return K <= 12 ? at_small_k : at_small_k * (1.0 + K / 130.0);
+}
+
+// Whether a batch is scanned by upper bounds (scan_filter.hpp), and how.
+size_t workspace_bytes(const ScanPlan& p, int B, int K);
+void plan_filter(ScanPlan& p, long long N, int B, int m, int K, bool subset, int cw, int b) {
+    const int force = g_force_general.load(std::memory_order_relaxed);
+    if (force & 8) return;
+    const bool rows = (cw == 1 && !subset) ? (m == 4 || m == 8 || m == 16 || m == 32 || m == 64) : (m == 4 || m == 8 || m == 16);
+    if (!rows || N * m * cw < 16) return;
+    const long long entries = (long long)m * (cw == 1 ? kLutStride : b);
+    if (!(force & 16) && (B < 2 || (double)B * (double)N * m < filter_min_lookups(m, K, subset) || N < 8 * entries ||
+                          N < (K > 128 ? 4000LL : 1000LL) * K))
+        return;
+    if (filter_prepare_lds_bytes(entries, m) > kMaxLdsBytes) return;
+    // Fields: eight bits as long as a score's sum of roundings stays small against its spread.  At m = 16 the bound is loose
+    // by half a standard deviation: twenty times as many items as necessary pass near a high floor, a hundred at larger K.
+    const bool w16 = m >= 32 || (m == 16 && K > 32);
+    const int fields = w16 ? 2 : 4;
+    int cap = next_pow2(2 * K);
+    if (cap < 128) cap = 128;
+    double best_cost = 0.0;
+    int words = 0;
+    for (int w = 4; w >= 1; w >>= 1) {
+        if (m == 64 && w == 4) continue;
+        if (filter_lds_bytes(entries, w, w * fields, cap, false) > kMaxLdsBytes) continue;
+        const long long tiles = (B + w * fields - 1) / (w * fields);
+        // (without the fine counts more is scored exactly, most of all at m = 16: 46 us with 16 queries per workgroup and
+        // without them, 41 us with eight and with them, on 5M items)
+        const bool coarse = !w16 && filter_lds_bytes(entries, w, w * fields, cap, true) > kMaxLdsBytes;
+        const double cost = (coarse ? (m == 16 ? 1.35 : 1.15) : 1.0) * (double)tiles / (w == 4 ? kGather16 : w == 2 ? kGather8 : kGather4);
+        if (words == 0 || cost < best_cost) { words = w; best_cost = cost; }
+    }
+    if (words == 0) return;
+    const int row = m * cw, queries = words * fields;
+    const long long tiles = (B + queries - 1) / queries;
+    const bool by_vector = row <= 16 && !subset;
+    const long long units = by_vector ? N * row / 16 : N;
+    const int vecs = row >= 32 ? row / 16 : 1;
+    const long long per_round = (long long)kFilterThreads * (by_vector ? vecs : vecs * 16 / row);
+    const long long rounds = (units + per_round - 1) / per_round;
+    // Item blocks per tile: one workgroup per CU, or a few one after the other when one filling would leave CUs idle.
+    const double stream_us = (double)N * m / ((words == 4 ? kGather16 : words == 2 ? kGather8 : kGather4) * 2400.0);
+    long long nb = 1;
+    double best_us = 0.0;
+    for (int fill = 1; fill <= 4; ++fill) {
+        long long cand = (long long)kAssumedCUs * fill / tiles;
+        if (cand > rounds) cand = rounds;
+        if (cand < 1) cand = 1;
+        const double per_cu = (double)((tiles * cand + kAssumedCUs - 1) / kAssumedCUs);
+        const double us = per_cu * (stream_us / (double)cand + 8.0);
+        if (fill == 1 || us < best_us) { best_us = us; nb = cand; }
+    }
+    p.filter = true;
+    p.tiled = p.short_scan = p.short_subset = false;
+    p.f_words = words;
+    p.f_w16 = w16;
+    p.f_queries = queries;
+    p.f_cap = cap;
+    p.f_entries = entries;
+    const int sample_units = (row == 8 || row == 16 || row == 32) ? 2 : 1;
+    p.f_sample = kFilterThreads * ((subset && row < 16) ? sample_units * 16 / row : sample_units);
+    // The sample: n items cost n * m lookups of 4 bytes, and (K / n) of the catalogue then passes the first floor and is
+    // scored from device memory, an eighth as fast: least together at about 3.5 sqrt(K N).  Where the workgroups of a query
+    // share their floors those rise fast by themselves.
+    p.f_share = nb > 1 && nb <= 16 && rounds / nb >= 32;
+    const long long items_per_round = (long long)p.f_sample * N / units;
+    long long want = (long long)(3.5 * sqrt((double)K * (double)N)) / items_per_round;
+    if (p.f_share && want > 1) want = 1;
+    if (want > N / 8 / items_per_round) want = N / 8 / items_per_round;
+    if (want < 1) want = 1;
+    long long parts = kAssumedCUs / B;
+    if (parts > 16) parts = 16;
+    if (parts > want) parts = want;
+    if (parts < 1 || 2 * K + 3 * parts > kFilterBest) parts = 1;
+    long long sample_rounds = (want + parts / 2) / parts;
+    if (sample_rounds > 8) sample_rounds = 8;
+    p.f_parts = (int)parts;
+    p.f_rounds = (int)(sample_rounds < 1 ? 1 : sample_rounds);
+    // scores a part leaves: twice its share of the K best and two more, never more than K
+    long long best = (2 * K + parts - 1) / parts + 2;
+    p.f_best = (int)(best < K ? best : K);
+    p.f_fine = !w16 && filter_lds_bytes(entries, words, queries, cap, true) <= kMaxLdsBytes;
+    p.nblk = (int)nb;
+    p.scan_lds = filter_lds_bytes(entries, words, queries, cap, p.f_fine);
+    p.scan_dyn_lds = p.scan_lds - (cw == 1 ? (size_t)entries * words * 4 : 0);   // (one-byte sub-ids: the tables are a static array)
 }
 
 size_t keys_bytes(const ScanPlan& p, int B, int K) {
@@ -317,8 +442,18 @@ size_t keys_bytes(const ScanPlan& p, int B, int K) {
 size_t fold_area_keys(int nblk, int B, int K);
 
 // workspace: [B][nblk][K] keys from the scan | a second, smaller key area for folds that take more than one level
+// | filter scans: the queries' tables of counts | their FilterQuery records | their histograms | the sample's best scores
+size_t fold_area_bytes(const ScanPlan& p, int B, int K) {
+    return (fold_area_keys(p.nblk, B, K) * sizeof(uint64_t) + 255) & ~(size_t)255;
+}
+size_t counts_bytes(const ScanPlan& p, int B) {
+    return p.filter ? ((size_t)B * p.f_entries * sizeof(uint16_t) + 255) & ~(size_t)255 : 0;
+}
+size_t query_bytes(const ScanPlan& p, int B) { return p.filter ? ((size_t)B * sizeof(FilterQuery) + 255) & ~(size_t)255 : 0; }
+size_t hist_bytes(const ScanPlan& p, int B) { return p.filter ? (size_t)B * kFilterBins * sizeof(uint32_t) : 0; }
 size_t workspace_bytes(const ScanPlan& p, int B, int K) {
-    return keys_bytes(p, B, K) + ((fold_area_keys(p.nblk, B, K) * sizeof(uint64_t) + 255) & ~(size_t)255);
+    return keys_bytes(p, B, K) + fold_area_bytes(p, B, K) + counts_bytes(p, B) + query_bytes(p, B) + hist_bytes(p, B) +
+           (p.filter && p.f_parts > 1 ? ((size_t)B * p.f_parts * p.f_best * sizeof(float) + 255) & ~(size_t)255 : 0);
 }
 
 int check_topk_shape(long long N, int B, int m, int b, int K, int cw) {
@@ -500,12 +635,91 @@ hipError_t launch_subset_m(const ScanPlan& p, const ScanArgs& a, int B, hipStrea
     }
 }
 
+template <int M, int CW, bool W16, bool SUB>
+hipError_t launch_filter(const ScanPlan& p, const FilterArgs& a, hipStream_t st) {
+    const size_t prep_lds = filter_prepare_lds_bytes(a.entries, M);
+    hipError_t e = allow_lds(filter_prepare_kernel<M, CW, SUB>, prep_lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((filter_prepare_kernel<M, CW, SUB>), dim3(p.f_parts, a.B), dim3(kFilterThreads), prep_lds, st, a);
+    auto go = [&](auto kernel) {
+        e = allow_lds(kernel, p.scan_dyn_lds);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(kernel, dim3(p.nblk, (a.B + p.f_queries - 1) / p.f_queries), dim3(kFilterThreads), p.scan_dyn_lds, st, a);
+        return hipGetLastError();
+    };
+    if (a.stamps != nullptr) {
+        if constexpr (M == 8 && CW == 1 && !W16 && !SUB) {
+            if (p.f_words == 4 && p.f_fine) return go(scan_filter_kernel<8, 1, 4, false, false, true, true>);
+        }
+        if constexpr (M == 16 && CW == 1 && !W16 && !SUB) {
+            if (p.f_words == 4 && !p.f_fine) return go(scan_filter_kernel<16, 1, 4, false, false, false, true>);
+        }
+        return hipErrorInvalidValue;                         // (pq_measure_step_stamps() has checked)
+    }
+    if constexpr (!W16) {
+        if (p.f_fine) {
+            switch (p.f_words) {
+                case 1: return go(scan_filter_kernel<M, CW, 1, W16, SUB, true>);
+                case 2: return go(scan_filter_kernel<M, CW, 2, W16, SUB, true>);
+                default: return go(scan_filter_kernel<M, CW, 4, W16, SUB, true>);
+            }
+        }
+    }
+    switch (p.f_words) {
+        case 1: return go(scan_filter_kernel<M, CW, 1, W16, SUB, false>);
+        case 2: return go(scan_filter_kernel<M, CW, 2, W16, SUB, false>);
+        default:
+            if constexpr (M < 64) return go(scan_filter_kernel<M, CW, 4, W16, SUB, false>);
+            else return hipErrorInvalidValue;                // (the plan never asks for it)
+    }
+}
+
+hipError_t launch_filter(const ScanPlan& p, const FilterArgs& a, int m, int cw, hipStream_t st) {
+    if (a.subset != nullptr) {
+        if (m == 4) return launch_filter<4, 1, false, true>(p, a, st);
+        if (m == 8) return launch_filter<8, 1, false, true>(p, a, st);
+        return p.f_w16 ? launch_filter<16, 1, true, true>(p, a, st) : launch_filter<16, 1, false, true>(p, a, st);
+    }
+    if (cw == 2) {
+        if (m == 4) return launch_filter<4, 2, false, false>(p, a, st);
+        if (m == 8) return launch_filter<8, 2, false, false>(p, a, st);
+        return p.f_w16 ? launch_filter<16, 2, true, false>(p, a, st) : launch_filter<16, 2, false, false>(p, a, st);
+    }
+    switch (m) {
+        case 4: return launch_filter<4, 1, false, false>(p, a, st);
+        case 8: return launch_filter<8, 1, false, false>(p, a, st);
+        case 16: return p.f_w16 ? launch_filter<16, 1, true, false>(p, a, st) : launch_filter<16, 1, false, false>(p, a, st);
+        case 32: return launch_filter<32, 1, true, false>(p, a, st);
+        default: return launch_filter<64, 1, true, false>(p, a, st);
+    }
+}
+
 // Enqueue the catalogue scan: every workgroup's K best keys land in the workspace.
 // `subset` / `n_items`: candidate list (then N is its length and the plan is a generic one) or nullptr / N
 // `cw`: bytes per sub-id (2: `codes` holds uint16 values)
 int enqueue_scan(const ScanPlan& p, const uint8_t* codes, const float* S, long long N, int B, int m, int b, int K,
                  void* workspace, hipStream_t st, const int* subset = nullptr, long long n_items = 0, int cw = 1,
                  uint64_t* stamps = nullptr) {
+    if (p.filter) {
+        unsigned char* ws = static_cast<unsigned char*>(workspace) + keys_bytes(p, B, K) + fold_area_bytes(p, B, K);
+        FilterArgs f;
+        f.codes = codes; f.S = S; f.N = N; f.b = b; f.K = K; f.B = B; f.cap = p.f_cap;
+        f.subset = subset; f.n_items = (uint32_t)(subset ? n_items : N);
+        f.ws_keys = static_cast<uint64_t*>(workspace);
+        f.counts = reinterpret_cast<uint16_t*>(ws);
+        f.query = reinterpret_cast<FilterQuery*>(ws + counts_bytes(p, B));
+        f.entries = p.f_entries;
+        f.hist = reinterpret_cast<uint32_t*>(ws + counts_bytes(p, B) + query_bytes(p, B));
+        f.best = reinterpret_cast<float*>(ws + counts_bytes(p, B) + query_bytes(p, B) + hist_bytes(p, B));
+        f.sample = p.f_sample;
+        f.rounds = p.f_rounds;
+        f.parts = p.f_parts;
+        f.best_per_part = p.f_best;
+        f.share = p.f_share;
+        f.stamps = stamps;
+        f.spare = p.f_w16 ? 3 : m + 3;
+        return record_hip(launch_filter(p, f, m, cw, st));
+    }
     ScanArgs a;
     a.codes = codes; a.S = S; a.N = N; a.m = m; a.b = b; a.K = K;
     a.subset = subset; a.n_items = (uint32_t)(subset ? n_items : N);
@@ -777,7 +991,8 @@ int pq_score_topk_static(const uint8_t* codes, const float* S, long long N, int 
     if (!codes || !S || !out_ids || !out_scores) return PQ_ERR_NULL;
     int rc = check_topk_shape(N, B, m, b, K, 1);
     if (rc != PQ_OK) return rc;
-    const ScanPlan p = make_plan(N, B, m, K);
+    ScanPlan p = make_plan(N, B, m, K);
+    if (p.filter && workspace_bytes(p, B, K) > kStaticScratchBytes) p = make_plan(N, B, m, K, false, 1, kLutStride, kNoFilter);
     if (p.scan_lds > kMaxLdsBytes || p.fold_lds > kMaxLdsBytes) return PQ_ERR_UNSUPPORTED;
     if (((uintptr_t)codes & 15) || ((uintptr_t)S & 3) || ((uintptr_t)out_ids & 3) || ((uintptr_t)out_scores & 3))
         return PQ_ERR_ALIGN;
@@ -835,7 +1050,7 @@ int pq_score_topk_profile(const uint8_t* codes, const float* S, long long N, int
 }
 
 int pq_measure_force_general(int mask) {
-    return g_force_general.exchange(mask & 7, std::memory_order_relaxed);
+    return g_force_general.exchange(mask & 31, std::memory_order_relaxed);
 }
 
 int pq_measure_step_stamps(const float* queries, const float* centroids, const uint8_t* codes, long long N, int B,
@@ -850,9 +1065,10 @@ int pq_measure_step_stamps(const float* queries, const float* centroids, const u
     if (stamps_bytes < PQ_STAMP_BYTES) return PQ_ERR_WORKSPACE;
     static_assert(PQ_STAMP_SLOTS == kStampSlots, "header and kernels agree on the record size");
     const ScanPlan p = make_plan(N, B, m, K);
-    if (!(p.tiled || m == 8)) return PQ_ERR_UNSUPPORTED;       // (scan kernels with a measurement instance)
-    const int waves = (!p.tiled && p.big) ? kMaxWaves : kWaves;   // (the batched kernel: always kWaves)
-    const long long scan_groups = p.tiled ? (long long)p.nblk * ((B + kQ - 1) / kQ) : (long long)p.nblk * B;
+    if (p.filter ? (p.f_words != 4 || p.f_w16 || !(m == 8 ? p.f_fine : (m == 16 && !p.f_fine))) : !(p.tiled || m == 8))
+        return PQ_ERR_UNSUPPORTED;                             // (scan kernels with a measurement instance)
+    const int waves = p.filter ? kFilterWaves : (!p.tiled && p.big) ? kMaxWaves : kWaves;
+    const long long scan_groups = p.filter ? (long long)p.nblk * ((B + p.f_queries - 1) / p.f_queries) : p.tiled ? (long long)p.nblk * ((B + kQ - 1) / kQ) : (long long)p.nblk * B;
     if (scan_groups * waves > PQ_STAMP_RECORDS || (long long)B * kWaves > PQ_STAMP_RECORDS) return PQ_ERR_UNSUPPORTED;
     if (scan_grid != nullptr) { scan_grid[0] = (int)scan_groups; scan_grid[1] = waves; }
     hipStream_t st = static_cast<hipStream_t>(stream);

@@ -1,0 +1,839 @@
+// Eq. 5 + TopK for batches (filter_prepare_kernel, scan_filter_kernel): a scan of small-integer upper bounds finds the few
+// items that can matter, and only those are scored exactly.
+// Part of kernels.hpp, which includes these parts inside namespace pqk in this order:
+// common.hpp, subitem_scores.hpp, topk_parts.hpp, select_small.hpp, scan_single.hpp, scan_short.hpp, scan_subset.hpp,
+// scan_filter.hpp, fold.hpp, comparison.hpp.
+//
+// What bounds a batch is the LDS: random 16-byte gathers return 5 lane reads per clock and CU whatever they hold.  With
+// fp32 table entries one of them serves four queries; with 8-bit entries it serves sixteen (16-bit: eight), and the four
+// sums in a 32-bit word are made by ONE integer addition.  So:
+//   - a table entry S[k][j] is replaced by a count of steps with base_k + count * step >= S[k][j].  The sum A of an item's
+//     counts bounds its score from above: score <= sum(base) + A * step (+ the rounding of the fp32 chain, which `off`
+//     below includes).  An item whose A is below T = floor((f - off) / step) scores below f: it is out.
+//   - f is a floor of the query's K-th best score.  The first one comes from an exactly scored sample of the catalogue
+//     (K of the sample's items reach it); the scan raises it as it finds better items.
+//   - 8-bit counts are coarse: near a high floor three or four items pass for every one that should.  So the counts exist
+//     in 256ths of a step too (16 bits per entry and query, where LDS has room), and what passes is tried against those
+//     before it is scored: an exact score reads its table values from device memory, one lane per clock and CU.
+//   - what is left is scored exactly, by the same left-to-right fp32 chain as everywhere, and only exact scores enter
+//     lists, floors and results.  Bit for bit the same results as the other kernels, whatever the tables are: bad bounds
+//     (heavy ties, degenerate tables) only mean more exact scoring.
+// A field starts at 128 - T (16-bit fields: 256 times that), so its top bit says A >= T.  Fields never carry into each
+// other: `step` is chosen so that the largest possible sum is at most T_first + 127, T never falls, and T is capped at 128
+// (a lower T is always allowed).
+#pragma once
+
+constexpr int kFilterThreads = kBigThreads;
+constexpr int kFilterWaves = kFilterThreads / kWave;
+constexpr int kFilterBins = 128;                  // histogram of exact scores per query, in units of T
+constexpr int kFilterQueue = 2 * kWave;           // a wave's queue of items to score exactly
+constexpr int kFilterSpan = 127;                  // steps from the first T to the largest possible sum
+constexpr float kFilterT0 = 80.0f;                // where the first T of a query's own sample lies: 48 steps of room to rise
+constexpr float kFilterUp = 0.02f;                // 256ths of a step a count is rounded up by more than it must be, against the
+constexpr float kFilterDown = 0.02f;              // rounding of its own computation; steps T is rounded down by, likewise
+constexpr int kSampleBins = 256;                  // histogram of a sample's scores
+constexpr int kFilterBest = 512;                  // sample scores a query's parts leave at most
+constexpr int kFilterCollect = 1024;              // ... and what a part collects to find its best
+
+struct FilterQuery {                              // one query's bounds, written by filter_prepare_kernel
+    float off, inv;                               // units of a score s: (s - off) * inv
+    int t_first;                                  // T of the first part's own floor
+    int pad;
+};
+
+struct FilterArgs {
+    const uint8_t* codes;
+    const float* S;
+    long long N;                // items scanned: the catalogue, or the candidate list's length
+    int b, K, B;
+    int cap;                    // keys of a query's list (a power of two)
+    const int* subset;          // candidate list or nullptr
+    uint32_t n_items;
+    uint64_t* ws_keys;          // [B][nblk][K]
+    uint16_t* counts;           // [B][entries] table counts in 256ths of a step; entries = M * 256, or M * b for two-byte sub-ids
+    FilterQuery* query;         // [B]
+    uint32_t* hist;             // [B][kFilterBins] exact scores found, by T above the first (cleared by filter_prepare_kernel)
+    float* best;                // [B][parts][best_per_part] scores of sample items (parts > 1)
+    long long entries;
+    int sample;                 // units of a part's sample per round (code vectors, or items of more than 16 bytes; candidates of a list)
+    int rounds;                 // ... and the rounds
+    int parts, best_per_part;
+    int share;                  // the workgroups of a query share their floors
+    uint64_t* stamps;           // STAMP instances only
+    int spare;                  // steps of the span left for rounding: an 8-bit sum rounds up once per split
+};
+
+// Row geometry.  P: bytes of an item's row.  A lane's unit of work is kVecs 16-byte vectors = kItems items.
+template <int M, int CW>
+struct FilterShape {
+    static constexpr int P = M * CW;
+    static constexpr int kVecs = P >= 32 ? P / 16 : 1;
+    static constexpr int kItems = kVecs * 16 / P;
+    static constexpr int kWords = kVecs * 4;
+    static constexpr int kSampleUnits = (P == 8 || P == 16 || P == 32) ? 2 : 1;   // ... of a part's sample per thread (vectors or wide items)
+    static constexpr int kSampleItems = P >= 16 ? kSampleUnits : kSampleUnits * (16 / P);
+    static constexpr int kSampleWords = P >= 16 ? kSampleUnits * P / 4 : kSampleUnits * 4;
+};
+
+template <int M, int CW>
+__device__ __forceinline__ uint32_t filter_sub_id(const uint32_t* w, int item, int k) {
+    constexpr int P = M * CW;
+    const int byte = item * P + k * CW;
+    if constexpr (CW == 2) return (byte & 2) ? (w[byte >> 2] >> 16) : (w[byte >> 2] & 0xFFFFu);
+    else return (w[byte >> 2] >> ((byte & 3) * 8)) & 0xFFu;
+}
+
+// an item's row, as words
+template <int P>
+__device__ __forceinline__ void load_row_words(const uint8_t* codes, uint32_t item, uint32_t* w) {
+    const uint8_t* row = codes + (size_t)item * P;
+    if constexpr (P == 4) {
+        w[0] = *reinterpret_cast<const uint32_t*>(row);
+    } else if constexpr (P == 8) {
+        const uint2 x = *reinterpret_cast<const uint2*>(row);
+        w[0] = x.x; w[1] = x.y;
+    } else {
+#pragma unroll
+        for (int j = 0; j < P / 16; ++j) {
+            const uint4 x = reinterpret_cast<const uint4*>(row)[j];
+            w[4 * j] = x.x; w[4 * j + 1] = x.y; w[4 * j + 2] = x.z; w[4 * j + 3] = x.w;
+        }
+    }
+}
+
+__device__ __forceinline__ float wave_sum_f32(float v) {     // (for bounds and heuristics: any order will do)
+    v += dpp_f32<kDppQuadSwap1>(0.0f, v);
+    v += dpp_f32<kDppQuadSwap2>(0.0f, v);
+    v += dpp_f32<kDppRowHalfMirror>(0.0f, v);
+    v += dpp_f32<kDppRowMirror>(0.0f, v);
+    float sum = 0.0f;
+#pragma unroll
+    for (int row = 0; row < 4; ++row) sum += __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), row * 16));
+    return sum;
+}
+
+__host__ __device__ inline size_t filter_prepare_lds_bytes(long long entries, int m) {
+    return align16((size_t)entries * sizeof(float)) + kSampleBins * sizeof(uint32_t) + align16(sizeof(Ctl)) + (size_t)m * 5 * sizeof(float) +
+           (kFilterCollect + 4) * sizeof(float);
+}
+
+// The sample.  grid = (parts, B).  Every part scores a sample of its own exactly, in rounds of kSampleItems per thread, and,
+// when there are several, leaves its best scores; part 0 also sets the query's step and bases by the floor of its own sample
+// and writes the table of counts.  (The scan takes the K-th best of all parts' scores as the first floor: at least as high
+// as part 0's, so the fields' range holds.)  The more items the sample has, the fewer pass the floor it gives; a batch of
+// few queries would leave most CUs idle with one part each (16 queries x 16 parts x 4096 items cost no more time than
+// 16 x 4096), and a round more costs less than a part more, which loads the tables again.
+// What it costs is latency: the tables' way from memory, then kSampleItems x M lookups per thread and round (4096 items at
+// m = 8: 1.6 us), a histogram of the first round, the counts.
+//   M, CW: splits, bytes per sub-id; SUB: the sample is taken from a candidate list
+template <int M, int CW, bool SUB>
+__global__ __launch_bounds__(kFilterThreads) void filter_prepare_kernel(FilterArgs a) {
+    using Sh = FilterShape<M, CW>;
+    constexpr int NT = kFilterThreads, NW = kFilterWaves, P = Sh::P;
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+    const int q = blockIdx.y, part = blockIdx.x, b = a.b, K = a.K;
+    const int stride = CW == 1 ? kLutStride : b;
+    float* lut = reinterpret_cast<float*>(smem);
+    uint32_t* hist = reinterpret_cast<uint32_t*>(smem + align16((size_t)a.entries * sizeof(float)));
+    Ctl* ctl = reinterpret_cast<Ctl*>(hist + kSampleBins);
+    float* stat = reinterpret_cast<float*>(reinterpret_cast<unsigned char*>(ctl) + align16(sizeof(Ctl)));   // [M][4]: max, min, mean, max |.|; then [M] bases
+    float* found = stat + 5 * M;                              // [kFilterCollect]
+    int* n_found = reinterpret_cast<int*>(found + kFilterCollect);
+    const float* Sq = a.S + (size_t)q * M * b;
+
+    // ---- the sample's rows: units spread evenly over the catalogue (or the list), the parts' and rounds' interleaved
+    constexpr bool kByItem = SUB || P > 16;
+    constexpr int kLoads = SUB ? Sh::kSampleItems : Sh::kSampleUnits;
+    const uint32_t total = (uint32_t)(kByItem ? a.N : (a.N * P) / 16);
+    const uint32_t n_sample = (uint32_t)a.sample < total ? (uint32_t)a.sample : total, every = total / n_sample;
+    auto fetch = [&](int round, uint32_t (&w)[Sh::kSampleWords]) {
+        const uint32_t slices = (uint32_t)(a.parts * a.rounds);
+        const uint32_t shift = (uint32_t)(((uint64_t)every * (uint32_t)(part * a.rounds + round)) / slices);
+#pragma unroll
+        for (int u = 0; u < kLoads; ++u) {
+            uint32_t i = (uint32_t)(u * NT + tid);
+            i = (i < n_sample ? i : n_sample - 1) * every + shift;
+            if constexpr (SUB) {
+                uint32_t item = (uint32_t)a.subset[i];
+                item = item < a.n_items ? item : a.n_items - 1;
+                load_row_words<P>(a.codes, item, &w[u * P / 4]);
+            } else if constexpr (P > 16) {
+                load_row_words<P>(a.codes, i, &w[u * P / 4]);
+            } else {
+                const uint4 x = reinterpret_cast<const uint4*>(a.codes)[i];
+                w[4 * u] = x.x; w[4 * u + 1] = x.y; w[4 * u + 2] = x.z; w[4 * u + 3] = x.w;
+            }
+        }
+    };
+    uint32_t w[Sh::kSampleWords];
+    fetch(0, w);
+
+    // ---- the query's tables to LDS; a wave takes whole splits and finds their extremes on the way
+    for (int k = wave; k < M; k += NW) {
+        float mx = -__builtin_inff(), mn = __builtin_inff(), sum = 0.0f;
+        for (int j0 = 0; j0 < stride; j0 += 4 * kWave) {
+            float v[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int j = j0 + i * kWave + lane;
+                v[i] = j < b ? Sq[(size_t)k * b + j] : 0.0f;
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int j = j0 + i * kWave + lane;
+                if (j < stride) lut[(size_t)k * stride + j] = v[i];
+                if (j < b) { mx = fmaxf(mx, v[i]); mn = fminf(mn, v[i]); sum += v[i]; }
+            }
+        }
+        wave_minmax(mn, mx);
+        sum = wave_sum_f32(sum);
+        if (lane == 0) {
+            stat[4 * k] = mx; stat[4 * k + 1] = mn; stat[4 * k + 2] = sum / (float)b; stat[4 * k + 3] = fmaxf(fabsf(mx), fabsf(mn));
+        }
+    }
+    for (int i = tid; i < kSampleBins; i += NT) hist[i] = 0;
+    if (tid == 0) *n_found = 0;
+    __syncthreads();
+
+    // ---- the first round, scored; a floor that at least K of its items exceed
+    constexpr int kPerLoad = Sh::kSampleItems / kLoads;
+    auto have = [&](int e) { return (uint32_t)((e / kPerLoad) * NT + tid) < n_sample; };
+    auto score = [&](const uint32_t (&w)[Sh::kSampleWords], float (&sc)[Sh::kSampleItems]) {
+#pragma unroll
+        for (int e = 0; e < Sh::kSampleItems; ++e) {
+            float acc = 0.0f;
+#pragma unroll
+            for (int k = 0; k < M; ++k) {
+                const float v = lut[(size_t)k * stride + filter_sub_id<M, CW>(w, e, k)];
+                acc = k == 0 ? v : acc + v;
+            }
+            sc[e] = acc;
+        }
+    };
+    float sc[Sh::kSampleItems];
+    score(w, sc);
+    if (a.rounds > 1) fetch(1, w);
+    float mn = __builtin_inff(), mx = -__builtin_inff();
+#pragma unroll
+    for (int e = 0; e < Sh::kSampleItems; ++e)
+        if (have(e)) { mn = fminf(mn, sc[e]); mx = fmaxf(mx, sc[e]); }
+    float lo, scale;
+    set_range<NW>(mn, mx, ctl, tid, lo, scale, 1.25f);        // (room on top for the scores of later rounds)
+    scale *= (float)kSampleBins / (float)kBins;
+    if (tid == 0) ctl->scale = scale;
+#pragma unroll
+    for (int e = 0; e < Sh::kSampleItems; ++e)
+        if (have(e)) atomicAdd(&hist[bucket_of<kSampleBins>(sc[e], lo, scale)], 1u);
+    __syncthreads();
+    if (tid < kWave) find_cut<kSampleBins>(hist, K, ctl, lane);
+    __syncthreads();
+
+    if (a.parts > 1 || a.rounds > 1) {
+        // scores above the cut (a few more than K), and of further rounds those that exceed it too; any of them will do when
+        // ties make them too many
+        const float cut = ctl->cut;
+        auto collect = [&](int first_round) {
+#pragma unroll
+            for (int e = 0; e < Sh::kSampleItems; ++e) {
+                if (have(e) && sc[e] > cut) {
+                    const int pos = atomicAdd(n_found, 1);
+                    if (pos < kFilterCollect) found[pos] = sc[e];
+                    if (first_round == 0) atomicAdd(&hist[bucket_of<kSampleBins>(sc[e], lo, scale)], 1u);
+                }
+            }
+        };
+        collect(1);
+        for (int round = 1; round < a.rounds; ++round) {
+            score(w, sc);
+            if (round + 1 < a.rounds) fetch(round + 1, w);
+            collect(0);
+        }
+        __syncthreads();
+        if (a.rounds > 1) {
+            if (tid < kWave) find_cut<kSampleBins>(hist, K, ctl, lane);
+            __syncthreads();
+        }
+        if (a.parts > 1) {
+            // this part's best scores, ranked among those above the last cut; fewer than asked for are filled up with -inf
+            const int n = *n_found < kFilterCollect ? *n_found : kFilterCollect, r = a.best_per_part;
+            const float last_cut = ctl->cut;
+            float* out = a.best + ((size_t)q * a.parts + part) * r;
+            int above = 0;
+            for (int t0 = 0; t0 < n; t0 += NT) {              // (n <= NT: one trip)
+                const int t = t0 + tid;
+                const float mine = t < n ? found[t] : -__builtin_inff();
+                if (t < n && mine > last_cut) {
+                    int rank = 0;
+                    for (int u = 0; u < n; ++u) rank += (found[u] > mine || (found[u] == mine && u < t)) ? 1 : 0;
+                    if (rank < r) out[rank] = mine;
+                }
+                above += __syncthreads_count(t < n && mine > last_cut);
+            }
+            for (int t = above + tid; t < r; t += NT) out[t] = -__builtin_inff();
+        }
+        if (part != 0) return;                                // (the same for the whole workgroup)
+    }
+
+    // ---- step and bases (every wave for itself: lane k holds split k)
+    const bool mine = lane < M;
+    const float s_mx = mine ? stat[4 * lane] : 0.0f, s_mn = mine ? stat[4 * lane + 1] : 0.0f, s_mean = mine ? stat[4 * lane + 2] : 0.0f;
+    const float sum_max = wave_sum_f32(s_mx), sum_min = wave_sum_f32(s_mn), sum_abs = wave_sum_f32(mine ? stat[4 * lane + 3] : 0.0f);
+    const float spread = wave_sum_f32(s_mx - s_mean);
+    // what fp32 chains of M additions (scores, sums of bases) can be off by
+    const float slack = 4.0f * (float)(M + 1) * 5.9604645e-8f * sum_abs;
+    const float floor_s = fmaxf(ctl->cut, sum_min - slack);   // (the cut: at least K of the part's items exceed it)
+    float step = (sum_max - floor_s + 2.0f * slack) / (float)(kFilterSpan - a.spare);
+    float inv = 1.0f / step;
+    if (!(step > 0.0f) || !(inv < 1.0e30f) || !(step < 1.0e30f)) { inv = 0.0f; step = 0.0f; }   // degenerate: T stays 0, every item is scored
+    // bases: the further a split's maximum lies above its mean, the more of the range it gets; what lies below the base
+    // counts as the base (loose only for items that will rarely be near a floor)
+    const float lambda = spread > 0.0f ? (sum_max - floor_s + kFilterT0 * step) / spread : 0.0f;
+    const float base = mine ? fmaxf(s_mn, s_mx - lambda * (s_mx - s_mean)) : 0.0f;
+    const float off = wave_sum_f32(base) + slack;
+    if (tid == 0) {
+        int t = inv > 0.0f ? (int)floorf((floor_s - off) * inv - kFilterDown) : 0;
+        t = t < 0 ? 0 : (t > kFilterSpan + 1 ? kFilterSpan + 1 : t);
+        a.query[q] = FilterQuery{off, inv, t, 0};
+    }
+    if (wave == 0 && mine) stat[4 * M + lane] = base;
+    __syncthreads();
+
+    // ---- counts, two entries per thread and store
+    uint32_t* out = reinterpret_cast<uint32_t*>(a.counts + (size_t)q * a.entries);
+    const float inv256 = inv * 256.0f;
+    for (long long i = tid; i * 2 < a.entries; i += NT) {     // (entries is a multiple of 4)
+        uint32_t word = 0;
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+            const uint32_t e = (uint32_t)(i * 2 + c), k = e / (uint32_t)stride;
+            const float x = ceilf((lut[e] - stat[4 * M + k]) * inv256 + kFilterUp);
+            word |= (uint32_t)fminf(fmaxf(x, 0.0f), 65535.0f) << (c * 16);
+        }
+        out[i] = word;
+    }
+    if (tid < kFilterBins) a.hist[(size_t)q * kFilterBins + tid] = 0u;
+}
+
+__host__ __device__ inline size_t filter_state_bytes(int queries) {   // everything but the tables, the lists and the queues
+    return (size_t)queries * (kFilterBins * sizeof(uint32_t) + sizeof(uint64_t) + 2 * sizeof(uint32_t) + sizeof(FilterQuery)) + 64 + 64;
+}
+// `fine`: the 16-bit counts beside the 8-bit tables
+__host__ __device__ inline size_t filter_lds_bytes(long long entries, int words, int queries, int cap, bool fine) {
+    return (size_t)entries * words * 4 + (fine ? (size_t)entries * queries * 2 : 0) + (size_t)queries * cap * sizeof(uint64_t) +
+           (size_t)kFilterWaves * kFilterQueue * sizeof(uint64_t) + align16(filter_state_bytes(queries));
+}
+
+template <int W> struct FilterWord;
+template <> struct FilterWord<1> { typedef uint32_t type; };
+template <> struct FilterWord<2> { typedef uint2 type; };
+template <> struct FilterWord<4> { typedef uint4 type; };
+
+// The scan.  grid = (item blocks, tiles of QT queries).  M, CW, SUB as above; W: 32-bit words of a table entry (1, 2, 4);
+// W16: 16-bit fields.  QT = W * 4 (or 2) queries per workgroup.
+// Dynamic LDS: tables | lists [QT][cap] | queues [waves][kFilterQueue] | hist [QT][kFilterBins] | thr | state words.
+// STAMP: measurement instance that also records wall-clock stamps per wave.
+template <int M, int CW, int W, bool W16, bool SUB, bool FINE, bool STAMP = false>
+__global__ __launch_bounds__(kFilterThreads) void scan_filter_kernel(FilterArgs a) {
+    using Sh = FilterShape<M, CW>;
+    using Word = typename FilterWord<W>::type;
+    constexpr int NT = kFilterThreads, NW = kFilterWaves, P = Sh::P, NI = Sh::kItems;
+    constexpr int F = W16 ? 2 : 4, QT = W * F;                // fields per word, queries per tile
+    static_assert(!(FINE && W16), "16-bit fields are fine already");
+    constexpr uint32_t TOP = W16 ? 0x80008000u : 0x80808080u;
+    static_assert(QT <= kFilterWaves, "the final selection gives each query a wave");
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const int q0 = blockIdx.y * QT, nblk = gridDim.x, blk = blockIdx.x, K = a.K, b = a.b, cap = a.cap;
+    uint64_t* const rec = STAMP ? a.stamps + (((size_t)blockIdx.y * nblk + blk) * NW + wave) * kStampSlots : nullptr;
+    stamp<STAMP>(rec, kStampEntry, lane);
+    const int nq = a.B - q0 < QT ? a.B - q0 : QT;
+    const int stride = CW == 1 ? kLutStride : b;
+    __shared__ __align__(16) uint32_t tab_static[CW == 1 ? M * kLutStride * W : 4];
+    uint32_t* const tab = CW == 1 ? tab_static : reinterpret_cast<uint32_t*>(smem);
+    const uint32_t entries = CW == 1 ? M * kLutStride : (uint32_t)a.entries;
+    unsigned char* const rest = smem + (CW == 1 ? 0 : (size_t)entries * W * 4);
+    uint16_t* const fine = reinterpret_cast<uint16_t*>(rest);
+    uint64_t* const lists = reinterpret_cast<uint64_t*>(rest + (FINE ? (size_t)entries * QT * 2 : 0));
+    uint64_t* const queue = lists + (size_t)QT * cap + (size_t)wave * kFilterQueue;
+    uint32_t* const hist = reinterpret_cast<uint32_t*>(lists + (size_t)QT * cap + (size_t)NW * kFilterQueue);
+    uint64_t* const thr = reinterpret_cast<uint64_t*>(hist + QT * kFilterBins);   // a pruned list's K-th best key
+    uint32_t* const cnt = reinterpret_cast<uint32_t*>(thr + QT);                  // keys in the list (or asked for)
+    uint32_t* const lock = cnt + QT;
+    FilterQuery* const par = reinterpret_cast<FilterQuery*>(lock + QT);
+    uint32_t* const start = reinterpret_cast<uint32_t*>(par + QT);                // [W] the fields' start values: 128 - T, or 256 times that
+    uint32_t* const next_unit = start + 4;
+
+    // ---- units of work: a wave's share (64 lanes x kVecs vectors) of one of this workgroup's rounds
+    const uint32_t total = (uint32_t)((P <= 16 && !SUB) ? (a.N * P) / 16 : a.N);  // whole vectors, or items / candidates
+    constexpr uint32_t kPerLane = (P <= 16 && !SUB) ? Sh::kVecs : NI;             // ... per lane and unit
+    constexpr uint32_t kRound = NT * kPerLane;
+    const uint32_t rounds = (total + kRound - 1) / kRound;
+    const uint32_t my_rounds = (uint32_t)blk < rounds ? (rounds - blk + nblk - 1) / nblk : 0;
+    const uint32_t units = my_rounds * NW;
+    const uint32_t last = total - 1;
+    auto first_of = [&](uint32_t u) -> uint32_t {             // the lane's first element of unit u; the others follow at 64
+        return ((uint32_t)blk + (u / NW) * (uint32_t)nblk) * kRound + (u % NW) * (kWave * kPerLane) + (uint32_t)lane;
+    };
+    auto fetch_ids = [&](uint32_t u, uint32_t (&id)[NI]) {    // candidate lists: the items' ids
+        if constexpr (SUB) {
+            const uint32_t p0 = first_of(u);
+#pragma unroll
+            for (int e = 0; e < NI; ++e) {
+                const uint32_t p = p0 + e * kWave;
+                const uint32_t item = (uint32_t)a.subset[p < last ? p : last];
+                id[e] = item < a.n_items ? item : a.n_items - 1;
+            }
+        }
+    };
+    auto fetch = [&](uint32_t u, const uint32_t (&id)[NI], uint32_t (&w)[Sh::kWords]) {   // branch-free: clamped past the end
+        const uint32_t p0 = first_of(u);
+        if constexpr (SUB) {
+#pragma unroll
+            for (int e = 0; e < NI; ++e) load_row_words<P>(a.codes, id[e], &w[e * P / 4]);
+        } else if constexpr (P > 16) {
+            load_row_words<P>(a.codes, p0 < last ? p0 : last, w);
+        } else {
+#pragma unroll
+            for (int v = 0; v < Sh::kVecs; ++v) {
+                const uint32_t p = p0 + v * kWave;
+                const uint4 x = reinterpret_cast<const uint4*>(a.codes)[p < last ? p : last];
+                w[4 * v] = x.x; w[4 * v + 1] = x.y; w[4 * v + 2] = x.z; w[4 * v + 3] = x.w;
+            }
+        }
+    };
+    // item e of unit u: its id, or -1u past the end
+    auto item_of = [&](uint32_t u, int e, const uint32_t (&id)[NI]) -> uint32_t {
+        const uint32_t p0 = first_of(u);
+        if constexpr (SUB) return p0 + e * kWave <= last ? id[e] : ~0u;
+        else if constexpr (P > 16) return p0 <= last ? p0 : ~0u;
+        else {
+            constexpr int IPV = 16 / P;
+            const uint32_t p = p0 + (e / IPV) * kWave;
+            return p <= last ? p * IPV + e % IPV : ~0u;
+        }
+    };
+
+    // ---- the tile's counts on their way, then the first units' codes (loads return in order, and codes may come from
+    // far away: asked for first, they held the tables up by 5 us on an 80 MB catalogue), then the tables: rows of counts,
+    // one per query, become entries of QT fields (transposed in registers)
+    const uint32_t row_words = entries / 2;                   // two 16-bit counts per word
+    const uint32_t* const rows = reinterpret_cast<const uint32_t*>(a.counts) + (size_t)q0 * row_words;
+    auto fetch_counts = [&](uint32_t i, uint32_t (&in)[QT]) {
+        const uint32_t at = i < row_words ? i : 0u;
+#pragma unroll
+        for (int q = 0; q < QT; ++q) in[q] = rows[(size_t)(q < nq ? q : 0) * row_words + at];
+    };
+    uint32_t first_in[QT];
+    fetch_counts(tid, first_in);
+    FilterQuery my_par = a.query[q0 + (wave < nq ? wave : 0)];   // (a wave per query below)
+    uint32_t wa[Sh::kWords], wb[Sh::kWords], ia[NI], ib[NI], inext[NI];
+    fetch_ids(wave, ia);
+    fetch_ids(NW + wave, ib);
+    fetch(wave, ia, wa);
+    fetch(NW + wave, ib, wb);
+    for (int i = tid; i < QT * cap; i += NT) lists[i] = 0ull;
+    for (int i = tid; i < QT * kFilterBins; i += NT) hist[i] = 0u;
+    {
+        for (uint32_t i = tid; i < row_words; i += NT) {      // entries 2i and 2i + 1 of every query
+            uint32_t in[QT];
+            if (i == (uint32_t)tid) {
+#pragma unroll
+                for (int q = 0; q < QT; ++q) in[q] = first_in[q];
+            } else {
+                fetch_counts(i, in);
+            }
+            if (nq < QT) {
+#pragma unroll
+                for (int q = 0; q < QT; ++q) in[q] = q < nq ? in[q] : 0u;
+            }
+            uint32_t out[2][W];                               // [entry][word of the entry]
+#pragma unroll
+            for (int j = 0; j < W; ++j) {
+                if constexpr (W16) {
+                    out[0][j] = __builtin_amdgcn_perm(in[2 * j + 1], in[2 * j], 0x05040100u);
+                    out[1][j] = __builtin_amdgcn_perm(in[2 * j + 1], in[2 * j], 0x07060302u);
+                } else {
+                    // whole steps, rounded up: the high bytes of (count + 255), without a carry from one half to the other
+                    // (counts stay below 2^16 - 256: the sum of a score's largest ones is at most 255 steps)
+                    const uint32_t r0 = in[4 * j] + 0x00FF00FFu, r1 = in[4 * j + 1] + 0x00FF00FFu;
+                    const uint32_t r2 = in[4 * j + 2] + 0x00FF00FFu, r3 = in[4 * j + 3] + 0x00FF00FFu;
+                    const uint32_t p01 = __builtin_amdgcn_perm(r1, r0, 0x07030501u), p23 = __builtin_amdgcn_perm(r3, r2, 0x07030501u);
+                    out[0][j] = __builtin_amdgcn_perm(p23, p01, 0x05040100u);
+                    out[1][j] = __builtin_amdgcn_perm(p23, p01, 0x07060302u);
+                }
+            }
+#pragma unroll
+            for (int f = 0; f < 2; ++f) {
+                Word x;
+                if constexpr (W == 1) x = out[f][0];
+                else if constexpr (W == 2) x = make_uint2(out[f][0], out[f][1]);
+                else x = make_uint4(out[f][0], out[f][1], out[f][2], out[f][3]);
+                reinterpret_cast<Word*>(tab)[i * 2 + f] = x;
+            }
+            if constexpr (FINE) {
+#pragma unroll
+                for (int q = 0; q < QT; ++q) reinterpret_cast<uint32_t*>(fine)[(size_t)q * row_words + i] = in[q];
+            }
+        }
+    }
+    // (words that other waves write meanwhile: relaxed accesses)
+    auto set_t = [&](int q, int t) {
+        const int s = kFilterSpan + 1 - t;
+        if constexpr (W16) lds_poke(reinterpret_cast<uint16_t*>(start) + q, (uint16_t)(s << 8));
+        else lds_poke(reinterpret_cast<uint8_t*>(start) + q, (uint8_t)s);
+    };
+    auto t_of = [&](int q) -> int {
+        if constexpr (W16) return kFilterSpan + 1 - (int)(lds_peek(reinterpret_cast<uint16_t*>(start) + q) >> 8);
+        else return kFilterSpan + 1 - (int)lds_peek(reinterpret_cast<uint8_t*>(start) + q);
+    };
+    auto units_of_score = [&](float s, const FilterQuery& p) -> int {
+        const float x = floorf((s - p.off) * p.inv - kFilterDown);
+        return (int)fminf(fmaxf(x, 0.0f), (float)(kFilterSpan + 1));
+    };
+    if (tid < QT) { thr[tid] = 0ull; cnt[tid] = 0u; lock[tid] = 0u; }
+    if (tid == 0) *next_unit = 2 * NW;
+    if (wave < QT) {
+        // a wave per query: the first T (queries that do not exist: start 0, counts 0: never at the top bit)
+        const int q = wave;
+        FilterQuery p = q < nq ? my_par : FilterQuery{0.0f, 0.0f, kFilterSpan + 1, 0};
+        if (q < nq && a.parts > 1) {
+            // the K-th best of the parts' scores, to 16 bits of its order-preserving image: K of them reach it
+            const int n = a.parts * a.best_per_part;
+            const float* v = a.best + (size_t)(q0 + q) * n;
+            uint32_t o[kFilterBest / kWave];
+#pragma unroll
+            for (int i = 0; i < kFilterBest / kWave; ++i) o[i] = i * kWave + lane < n ? orderable_bits(v[i * kWave + lane]) : 0u;
+            uint32_t at = 0;
+            for (uint32_t bit = 0x80000000u; bit >= 0x10000u; bit >>= 1) {
+                const uint32_t t = at | bit;
+                int c = 0;
+#pragma unroll
+                for (int i = 0; i < kFilterBest / kWave; ++i)
+                    if (i * kWave < n) c += __popcll(__ballot(o[i] >= t));
+                if (c >= K) at = t;
+            }
+            const float f = float_of_orderable(at);
+            if (p.inv > 0.0f && f == f && f > -__builtin_inff()) {
+                const int t = units_of_score(f, p);
+                p.t_first = t > p.t_first ? t : p.t_first;
+            }
+        }
+        if (lane == 0) {
+            par[q] = p;
+            set_t(q, p.t_first);
+        }
+    }
+    stamp<STAMP>(rec, kStampRequested, lane);
+    __syncthreads();
+    stamp<STAMP>(rec, kStampTables, lane);
+
+    // Floors.  Every exact score that enters a list is counted in its query's histogram, and wave q looks after query q: now
+    // and then it asks for the counters and one unit later reads off the highest T that K of the counted scores reach.
+    // a.share: the histogram is in device memory and counts for all workgroups that serve the query: the K-th best of all
+    // their shares together is a far higher floor than one share's own.  For a few workgroups with long shares (serving:
+    // four per query, K = 100: scan 373 -> 238 us).  Where many workgroups share a query their updates of the same counters
+    // are served one by one, and a wave's loads wait behind its updates: the histogram is the workgroup's own then, in LDS
+    // (256 workgroups, 20 units per wave: 46 us, 64 with a shared one).
+    static_assert(kFilterBins == 2 * kWave, "two counters per lane");
+    const bool looks_after = wave < nq;
+    unsigned long long seen = 0ull;                           // this lane's two counters as asked for
+    int until_look = 1, look_gap = 2;                         // units until the next request; the gap grows by a quarter
+    bool asked = false;
+    auto look = [&]() {
+        if (!looks_after) return;
+        if (asked) {
+            asked = false;
+            const uint32_t h0 = (uint32_t)seen, h1 = (uint32_t)(seen >> 32);
+            const int top = kFilterBins - 1 - 2 * lane;       // lane 0 owns the highest two
+            const uint32_t upto = wave_prefix_sum(h0 + h1);
+            const uint64_t has = __ballot(upto >= (uint32_t)K);
+            if (has != 0) {
+                const int owner = __builtin_ctzll(has);
+                const int bin = __builtin_amdgcn_readlane(upto - h0 >= (uint32_t)K ? top : top - 1, owner);
+                const int t = par[wave].t_first + bin < kFilterSpan + 1 ? par[wave].t_first + bin : kFilterSpan + 1;
+                if (lane == 0 && t > t_of(wave)) set_t(wave, t);
+            }
+        }
+        if (--until_look <= 0) {
+            const int at = kFilterBins - 2 - 2 * lane;
+            if (a.share) seen = __hip_atomic_load(reinterpret_cast<const unsigned long long*>(a.hist + (size_t)(q0 + wave) * kFilterBins + at),
+                                                  __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            else seen = lds_peek(reinterpret_cast<const unsigned long long*>(hist + wave * kFilterBins + at));
+            asked = true;
+            look_gap += (look_gap + 3) >> 2;
+            until_look = look_gap < 16 ? look_gap : 16;
+        }
+    };
+
+    // One wave makes room in query q's full list, which it has locked: keys below the present floor go; if that is not
+    // enough the list is sorted and its K best stay.  Every slot has been handed out, and whoever was handed one writes it
+    // without waiting for anything, so the wait for the last of them ends.
+    auto make_room = [&](int q) {
+        uint64_t* const list = lists + (size_t)q * cap;
+        for (int t = lane; t < cap; t += kWave)
+            while (lds_peek(list + t) == 0ull) __builtin_amdgcn_s_sleep(1);
+        const int tq = t_of(q);
+        const FilterQuery p = par[q];
+        int kept = 0;
+        for (int base = 0; base < cap; base += kWave) {       // in place: a chunk is in registers before its survivors
+            const uint64_t key = list[base + lane];           // are written at or below its start
+            const bool take = units_of_score(score_of_key(key), p) >= tq;
+            const uint64_t mask = __ballot(take);
+            wave_sync();
+            if (take) list[kept + __popcll(mask & ((1ull << lane) - 1ull))] = key;
+            kept += __popcll(mask);
+            wave_sync();
+        }
+        if (kept > cap / 2 && kept > K + K / 4) {
+            const uint64_t kth = sort_wave_list(list, cap, kept, K, lane);
+            kept = K;
+            if (lane == 0) lds_poke(thr + q, kth);
+        }
+        for (int t = kept + lane; t < cap; t += kWave) list[t] = 0ull;
+        wave_sync();
+        if (lane == 0) lds_poke(cnt + q, (uint32_t)kept);
+        wave_sync();
+    };
+
+    // Scores queue entries [n0, n0 + n), n <= 64, exactly, one per lane, and puts what reaches its query's floor into the
+    // query's list.
+    auto process = [&](int n0, int n) {
+        wave_sync();
+        const uint64_t entry = lane < n ? queue[n0 + lane] : 0ull;
+        const int q = (int)(entry >> 32);
+        const uint32_t item = (uint32_t)entry;
+        uint32_t w[P / 4 > 0 ? P / 4 : 1];
+        load_row_words<P>(a.codes, item, w);
+        bool live = lane < n;
+        if constexpr (FINE) {
+            uint32_t sum = 0;
+#pragma unroll
+            for (int k = 0; k < M; ++k) sum += fine[(size_t)q * entries + (uint32_t)k * stride + filter_sub_id<M, CW>(w, 0, k)];
+            live = live && sum >= ((uint32_t)t_of(q) << 8);
+        }
+        const float* Sq = a.S + (size_t)(q0 + q) * M * b;
+        float acc = 0.0f;
+        if (live) {
+#pragma unroll
+        for (int k0 = 0; k0 < M; k0 += 16) {
+            float v[M < 16 ? M : 16];
+#pragma unroll
+            for (int k = k0; k < k0 + (M < 16 ? M : 16); ++k) {
+                const uint32_t g = filter_sub_id<M, CW>(w, 0, k);
+                v[k - k0] = Sq[(size_t)k * b + (g < (uint32_t)b ? g : (uint32_t)b - 1u)];   // (never outside the tables)
+            }
+#pragma unroll
+            for (int k = k0; k < k0 + (M < 16 ? M : 16); ++k) acc = k == 0 ? v[0] : acc + v[k - k0];
+        }
+        }
+        const FilterQuery p = par[q];
+        const int t = units_of_score(acc, p);
+        const uint64_t key = make_key(acc + 0.0f, item);
+        const bool want = live && t >= t_of(q) && key > lds_peek(thr + q);
+        if (want) {
+            int bin = t - p.t_first;
+            bin = bin < 0 ? 0 : (bin > kFilterBins - 1 ? kFilterBins - 1 : bin);
+            if (a.share) (void)__hip_atomic_fetch_add(a.hist + (size_t)(q0 + q) * kFilterBins + bin, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            else atomicAdd(&hist[q * kFilterBins + bin], 1u);
+        }
+        // Who still has a key to place is kept as a mask in scalar registers, never as a flag per lane that goes round the
+        // loop: the compiler then lets lanes that are done skip ahead and parks them outside, and the loop's steps for the
+        // whole wave (lane 0 takes the lock, all lanes tidy the list) run without them.
+        uint64_t left = __ballot(want);
+        while (left != 0) {
+            bool full = false;
+            if ((left >> lane) & 1ull) {
+                const uint32_t pos = atomicAdd(&cnt[q], 1u);
+                full = pos >= (uint32_t)cap;
+                if (!full) lds_poke(lists + (size_t)q * cap + pos, key);
+            }
+            left &= __ballot(full);
+            if (left == 0) break;
+            // a list is full: the wave that gets its lock makes room, the others try again
+            const int qf = __builtin_amdgcn_readlane(q, __builtin_ctzll(left));
+            uint32_t got = 1u;
+            if (lane == 0) got = atomicExch(&lock[qf], 1u);
+            got = (uint32_t)__builtin_amdgcn_readfirstlane((int)got);
+            if (got == 0u) {
+                const uint32_t now = (uint32_t)__builtin_amdgcn_readfirstlane((int)lds_peek(cnt + qf));
+                if (now >= (uint32_t)cap) make_room(qf);
+                wave_sync();
+                if (lane == 0) lds_poke(lock + qf, 0u);
+            } else {
+                __builtin_amdgcn_s_sleep(2);
+            }
+            wave_sync();
+            left &= __ballot(key > lds_peek(thr + q));
+        }
+        wave_sync();
+        // (while much is scored, as in the first units of a long scan, floors move fast: look every time)
+        until_look = 0;
+        look();
+    };
+
+    // ---- stream
+    int queued = 0;                                           // entries in this wave's queue
+    uint32_t s[W];                                            // the fields' start values
+    auto read_start = [&]() {
+        if constexpr (W == 1) s[0] = lds_peek(start);         // (fields other waves may be raising: any value read is a floor)
+        else {
+#pragma unroll
+            for (int j = 0; j < W; j += 2) {
+                const unsigned long long x = lds_peek(reinterpret_cast<const unsigned long long*>(start) + j / 2);
+                s[j] = (uint32_t)x; s[j + 1] = (uint32_t)(x >> 32);
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < W; ++j) s[j] = (uint32_t)__builtin_amdgcn_readfirstlane((int)s[j]);
+    };
+    auto scan_unit = [&](uint32_t u, const uint32_t (&w)[Sh::kWords], const uint32_t (&id)[NI]) {
+        uint32_t sum[NI][W];
+        uint32_t any = 0;
+#pragma unroll
+        for (int e = 0; e < NI; ++e) {
+#pragma unroll
+            for (int j = 0; j < W; ++j) sum[e][j] = s[j];
+#pragma unroll
+            for (int k0 = 0; k0 < M; k0 += 8) {
+                constexpr int STEP = M < 8 ? M : 8;
+                Word v[STEP];
+#pragma unroll
+                for (int k = k0; k < k0 + STEP; ++k) v[k - k0] = reinterpret_cast<const Word*>(tab)[k * stride + filter_sub_id<M, CW>(w, e, k)];
+#pragma unroll
+                for (int k = k0; k < k0 + STEP; ++k) {
+                    if constexpr (W == 1) sum[e][0] += v[k - k0];
+                    else if constexpr (W == 2) { sum[e][0] += v[k - k0].x; sum[e][1] += v[k - k0].y; }
+                    else { sum[e][0] += v[k - k0].x; sum[e][1] += v[k - k0].y; sum[e][2] += v[k - k0].z; sum[e][3] += v[k - k0].w; }
+                }
+            }
+#pragma unroll
+            for (int j = 0; j < W; ++j) any |= sum[e][j];
+        }
+        if (__ballot((any & TOP) != 0u) == 0) return;
+        // hits: per item a mask of the queries whose field has its top bit set (bit f * 8 (or 16) + j: field f of word j)
+        uint32_t hits[NI];
+#pragma unroll
+        for (int e = 0; e < NI; ++e) {
+            hits[e] = 0;
+#pragma unroll
+            for (int j = 0; j < W; ++j) hits[e] |= ((sum[e][j] & TOP) >> (W16 ? 15 : 7)) << j;
+            if (item_of(u, e, id) == ~0u) hits[e] = 0;
+        }
+        for (;;) {
+            uint32_t mask = 0, item = 0;
+            bool taken = false;
+#pragma unroll
+            for (int e = 0; e < NI; ++e) {
+                const bool here = !taken && hits[e] != 0u;
+                mask = here ? hits[e] : mask;
+                item = here ? item_of(u, e, id) : item;
+                hits[e] = here ? hits[e] & (hits[e] - 1u) : hits[e];
+                taken = taken || here;
+                asm volatile("" : "+v"(hits[e]));             // (nothing known about it: no lane skips ahead, see process())
+            }
+            const uint64_t who = __ballot(taken);
+            if (who == 0) break;
+            const int bit = mask != 0u ? __builtin_ctz(mask) : 0;
+            const int q = W16 ? (bit & 15) * 2 + (bit >> 4) : (bit & 7) * 4 + (bit >> 3);
+            if (taken) queue[queued + __popcll(who & ((1ull << lane) - 1ull))] = ((uint64_t)q << 32) | item;
+            queued += __popcll(who);
+            if (queued >= kWave) {
+                queued -= kWave;
+                process(queued, kWave);
+            }
+        }
+    };
+    if (units != 0) {
+        int pending = 0;                                      // lane 0: the counter request in flight
+        auto request = [&]() { if (lane == 0) pending = (int)atomicAdd(next_unit, 1u); };
+        auto requested = [&]() -> uint32_t { return (uint32_t)__builtin_amdgcn_readfirstlane(pending); };
+        uint32_t ua = wave, ub = NW + wave, un = 0;
+        request();
+        un = requested();
+        request();
+        fetch_ids(un, inext);
+        while (ua < units) {                                  // (ua is the oldest; loads past the end are clamped and never scored)
+            look();
+            read_start();
+            scan_unit(ua, wa, ia);
+#pragma unroll
+            for (int e = 0; e < NI; ++e) ia[e] = inext[e];
+            ua = un;
+            fetch(ua, ia, wa);
+            un = requested();
+            request();
+            fetch_ids(un, inext);
+            if (ub < units) {
+                look();
+                scan_unit(ub, wb, ib);
+            }
+#pragma unroll
+            for (int e = 0; e < NI; ++e) ib[e] = inext[e];
+            ub = un;
+            fetch(ub, ib, wb);
+            un = requested();
+            request();
+            fetch_ids(un, inext);
+        }
+    }
+    if constexpr (P < 16 && !SUB) {
+        // the fewer than 16 / P items after the last whole code vector: straight to the queue of one wave of block 0
+        const uint32_t first_left = total * (16 / P), n_left = (uint32_t)a.N - first_left;
+        if (blk == 0 && wave == 0 && n_left != 0) {
+            for (int q = 0; q < nq; ++q) {
+                if ((uint32_t)lane < n_left) queue[queued + lane] = ((uint64_t)q << 32) | (first_left + (uint32_t)lane);
+                queued += (int)n_left;
+                if (queued >= kWave) { queued -= kWave; process(queued, kWave); }
+            }
+        }
+    }
+    stamp<STAMP>(rec, kStampStreamed, lane);
+    if (queued != 0) process(0, queued);
+    stamp<STAMP>(rec, kStampOffered, lane);
+    __syncthreads();
+
+    // ---- a wave per query: keys that reach the final floor, ranked by counting, straight to the workspace
+    if (wave < nq) {
+        const int q = wave;
+        uint64_t* const list = lists + (size_t)q * cap;
+        const int tq = t_of(q);
+        const FilterQuery p = par[q];
+        const int n = (int)cnt[q] < cap ? (int)cnt[q] : cap;
+        int kept = 0;
+        for (int base = 0; base < n; base += kWave) {
+            const uint64_t key = base + lane < n ? list[base + lane] : 0ull;
+            const bool take = key != 0ull && units_of_score(score_of_key(key), p) >= tq;
+            const uint64_t mask = __ballot(take);
+            wave_sync();
+            if (take) list[kept + __popcll(mask & ((1ull << lane) - 1ull))] = key;
+            kept += __popcll(mask);
+            wave_sync();
+        }
+        uint64_t* const out = a.ws_keys + ((size_t)(q0 + q) * nblk + blk) * K;
+        if (kept > 3 * kWave) {                               // (counting costs kept^2 / 64: 192 keys as much as a sort of 256)
+            sort_wave_list(list, cap, kept, K, lane);
+            for (int t = lane; t < K && t < kept; t += kWave) out[t] = list[t];
+            for (int t = kept + lane; t < K; t += kWave) out[t] = 0ull;
+            kept = 0;
+        } else {
+            for (int t = kept + lane; t < K; t += kWave) out[t] = 0ull;
+        }
+        const int n8 = (kept + 7) & ~7;                       // (cap is a multiple of 8)
+        if (kept + lane < n8) list[kept + lane] = 0ull;
+        wave_sync();
+        for (int t = lane; t < kept; t += kWave) {
+            const uint64_t mine = list[t];
+            uint32_t rank = 0;
+            for (int u = 0; u < n8; u += 8) {
+                const ulonglong2 p0 = *reinterpret_cast<const ulonglong2*>(list + u), p1 = *reinterpret_cast<const ulonglong2*>(list + u + 2);
+                const ulonglong2 p2 = *reinterpret_cast<const ulonglong2*>(list + u + 4), p3 = *reinterpret_cast<const ulonglong2*>(list + u + 6);
+                rank += (uint32_t)((p0.x > mine) + (p0.y > mine) + (p1.x > mine) + (p1.y > mine) + (p2.x > mine) + (p2.y > mine) +
+                                   (p3.x > mine) + (p3.y > mine));
+            }
+            if (rank < (uint32_t)K) out[rank] = mine;
+        }
+        stamp<STAMP>(rec, kStampSelected, lane);
+    }
+    stamp<STAMP>(rec, kStampEnd, lane);
+}

@@ -238,6 +238,81 @@ def test_score_topk_batched_kernel_shapes(pq, oracle, N, m, B, K, b):
     assert_same_topk(pq, oracle, G, S, K, "batched")
 
 
+# ---- batches scanned by upper bounds: every geometry of fields and rows, edges of tiles and of the last code vector, K from 1
+# to the longest lists, samples of one and of several parts and rounds; bit 4 keeps small shapes on these kernels
+def _bounds_case(pq, oracle, codes, S, K, subset=None):
+    import torch
+    Gd, Sd = torch.from_numpy(codes).cuda(), torch.from_numpy(S).cuda()
+    prev = pq.pq_measure_force_general(16)
+    try:
+        if subset is not None:
+            ids, sc = pq.pq_score_topk_subset(Gd, Sd, torch.from_numpy(subset).cuda(), K)
+            rid, rsc = oracle.score_topk_subset(codes, S, subset, K)
+        elif codes.dtype == np.uint16:
+            ids, sc = pq.pq_score_topk_u16(Gd, Sd, K)
+            rid, rsc = oracle.score_topk_u16(codes, S, K)
+        else:
+            ids, sc = pq.pq_score_topk(Gd, Sd, K)
+            rid, rsc = oracle.score_topk(codes, S, K)
+        torch.cuda.synchronize()
+    finally:
+        pq.pq_measure_force_general(prev)
+    assert np.array_equal(ids.cpu().numpy(), rid)
+    assert np.array_equal(sc.cpu().numpy().view(np.uint32), rsc.view(np.uint32))
+
+
+@pytest.mark.parametrize("m", [4, 8, 16, 32, 64])
+@pytest.mark.parametrize("N,B,K,b", [(1_027, 1, 1, 256), (20_001, 2, 10, 256), (70_003, 5, 33, 7), (50_002, 17, 100, 256),
+                                     (150_001, 16, 10, 200), (9_000, 3, 512, 256), (400_001, 4, 128, 256)])
+def test_scan_by_upper_bounds(pq, oracle, m, N, B, K, b):
+    rng = np.random.default_rng(m * 1000 + B)
+    codes = rng.integers(0, b, (N, m), dtype=np.uint8)
+    S = rng.standard_normal((B, m, b), dtype=np.float32)
+    _bounds_case(pq, oracle, codes, S, K)
+
+
+@pytest.mark.parametrize("m", [4, 8, 16])
+@pytest.mark.parametrize("B,K", [(2, 10), (9, 100), (20, 1)])
+def test_scan_by_upper_bounds_of_lists_and_wide_ids(pq, oracle, m, B, K):
+    rng = np.random.default_rng(m * 100 + B)
+    N = 90_001
+    S = rng.standard_normal((B, m, 256), dtype=np.float32)
+    codes = rng.integers(0, 256, (N, m), dtype=np.uint8)
+    _bounds_case(pq, oracle, codes, S, K, subset=rng.permutation(N)[:30_011].astype(np.int32))
+    for b in (300, 2048):
+        wide = rng.integers(0, b, (N, m), dtype=np.uint16)
+        _bounds_case(pq, oracle, wide, rng.standard_normal((B, m, b), dtype=np.float32), K)
+
+
+@pytest.mark.parametrize("tables", ["equal", "coarse", "offset", "denormal", "negative", "one_split", "rising"])
+def test_scan_by_upper_bounds_when_the_bounds_say_little(pq, oracle, tables):
+    rng = np.random.default_rng(5)
+    for m, B, K in ((8, 18, 100), (16, 5, 10), (64, 3, 40)):
+        N = 60_001
+        codes = rng.integers(0, 256, (N, m), dtype=np.uint8)
+        S = rng.standard_normal((B, m, 256), dtype=np.float32)
+        if tables == "equal":
+            S[:] = 0.25
+        elif tables == "coarse":
+            S = np.round(S)
+        elif tables == "offset":                               # far from zero, close to each other: the fp32 sums round a lot
+            S = (S * np.float32(1e-3) + np.float32(1e4)).astype(np.float32)
+        elif tables == "denormal":
+            S = (S * np.float32(1e-39)).astype(np.float32)
+        elif tables == "negative":
+            S = -np.abs(S)
+        elif tables == "one_split":
+            S[:, 1:] = 0.0
+        elif tables == "rising":                               # every item beats all before it
+            i = np.arange(N)
+            codes[:] = 0
+            codes[:, 0], codes[:, 1], codes[:, 2] = i >> 16, (i >> 8) & 255, i & 255
+            S[:] = 0.0
+            for k, scale in enumerate((65536.0, 256.0, 1.0)):
+                S[:, k] = np.arange(256, dtype=np.float32) * np.float32(scale)
+        _bounds_case(pq, oracle, codes, np.ascontiguousarray(S, dtype=np.float32), K)
+
+
 @pytest.mark.parametrize("N,m,B,K", [(300_001, 64, 17, 10), (200_003, 64, 40, 100), (150_001, 64, 100, 10), (300_005, 4, 100, 10),
                                      (100_003, 4, 1024, 100), (200_001, 32, 100, 10), (150_007, 5, 100, 10), (120_001, 48, 40, 10),
                                      (100_001, 64, 300, 10)])
