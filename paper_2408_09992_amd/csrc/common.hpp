@@ -20,11 +20,8 @@ constexpr int kRing = 2;                          // rounds of codes a thread ha
 constexpr int kRegisterSelectMinK = 32;           // scans of at most kRing rounds: K from which all scores are selected from registers at once
 constexpr int kSharedFloorMinRounds = 6;          // single-query scan: rounds per workgroup from which the waves share a floor
 constexpr int kSharedFloorMinRoundsLargeK = 3;    // ... for K >= 32
-constexpr int kFoldRegs = 12;                     // keys per thread the fold keeps in registers (6144 per query)
-constexpr int kFoldWideRegs = 13;                 // ... and of the 1024-thread fold (13,312 keys)
 constexpr int kFoldSmallRegs = 6;                 // keys per thread of the small-K fold (3072 per query) ...
 constexpr int kFoldSmallRegsMax = 12;             // ... and of its larger instance (6144)
-constexpr int kChunkKeys = 2048;                  // keys the grid-level fold takes per pass (4 per thread)
 constexpr size_t kMaxLdsBytes = 160 * 1024;       // LDS per workgroup on gfx950
 constexpr int kAssumedCUs = 256;                  // MI355X; only used to size grids and the workspace
 constexpr int kBlocksPerCU = 2;                   // single-query scan workgroups per CU over the whole grid

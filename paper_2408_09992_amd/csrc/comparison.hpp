@@ -10,7 +10,7 @@
 
 // TopK of score rows that already sit in memory: scores float [B][ld], N of them used per row.  grid = (blocks, B).
 // Same lists, keys and final selection as the catalogue scan; a wave's first floor is one that K of its lanes' best
-// scores reach.  Leaves each workgroup's K best keys in the workspace for fold_topk_kernel.
+// scores reach.  Leaves each workgroup's K best keys in the workspace for the fold.
 struct TopkScoresArgs {
     const float* scores;
     long long ld, N;

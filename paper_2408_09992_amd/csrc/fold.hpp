@@ -1,123 +1,162 @@
-// The second launch of every TopK call: the workgroups' lists -> the final sorted K per query (fold_topk_kernel).
+// The last launch of every TopK call: the workgroups' lists -> the final sorted K per query (fold_lists_kernel,
+// fold_small_kernel).
 // Part of kernels.hpp, which includes these parts inside namespace pqk in this order:
 // common.hpp, subitem_scores.hpp, topk_parts.hpp, select_small.hpp, scan_single.hpp, scan_short.hpp, scan_subset.hpp, scan_batched.hpp,
-// fold.hpp, comparison.hpp.
+// scan_filter.hpp, fold.hpp, comparison.hpp.
 #pragma once
 
-// Grid-level fold: one workgroup per query turns the nblk sorted lists of K keys into the final K, sorted.
-// Dynamic LDS: hist | ctl | stage (stage_keys, a power of two >= 2K) | cand | sorted
 struct FoldArgs {
-    const uint64_t* ws_keys;   // [B][nlists][K]: per query, nlists sorted lists of K keys
+    const uint64_t* ws_keys;   // [B][nlists][K]: per query, nlists lists of K keys, sorted best first, zeros at the end
     int nlists, K;
-    int lists_per_group;       // lists one workgroup folds; grid = (ceil(nlists / lists_per_group), B)
-    int stage_keys, candmax;
-    uint64_t* out_keys;        // intermediate level: [B][groups][K] keys; nullptr at the last level, which writes
-    int* out_ids;              // ... the result
+    int chunk, depth, need;    // fold_lists_kernel: see there
+    int* out_ids;              // [B][K]
     float* out_scores;
     uint64_t* stamps;          // STAMP instances only: wall-clock stamps, kStampSlots per wave
 };
 
-__host__ __device__ inline size_t fold_lds_bytes(int stage_keys, int candmax, int K) {
-    return kBins * sizeof(uint32_t) + align16(sizeof(Ctl)) + (size_t)stage_keys * sizeof(uint64_t) +
-           (size_t)candmax * sizeof(uint64_t) + align16((size_t)K * sizeof(uint64_t));
+constexpr int kFoldThreads = 1024;                // a few queries: as many threads as a workgroup has
+constexpr int kFoldThreadsMany = 256;             // many queries: several workgroups per CU
+constexpr int kFoldSlots = 4096;                  // keys read at first: nlists * chunk at most
+constexpr int kFoldLists = 1024;                  // lists per query at most
+constexpr int kFoldCand = 2048;                   // candidates ranked at most; more (heavy ties in few lists) take the slow path
+
+// Dynamic LDS: hist | ctl | stage (kFoldCand keys; first the lists' floor keys and the lists to read on in) | cand | sorted
+__host__ __device__ inline size_t fold_lds_bytes(int K) {
+    return kBins * sizeof(uint32_t) + align16(sizeof(Ctl)) + 2 * (size_t)kFoldCand * sizeof(uint64_t) + align16((size_t)K * sizeof(uint64_t));
 }
 
-// NT threads, REGS keys per thread held in registers: <kThreads, kFoldRegs> is the usual instance; <kBigThreads,
-// kFoldWideRegs> takes a query's lists in one go when they are too many for the first (many workgroups times a
-// larger K at a small batch), instead of a level of several smaller folds.
-template <int NT, int REGS, bool STAMP = false>
-__global__ __launch_bounds__(NT) void fold_topk_kernel(FoldArgs a) {
+// The fold for any K.  grid = (1, B).  The lists are sorted, so few keys decide: `need` lists whose key number `depth` is at
+// least f hold need * depth >= K keys that are.  So the need-th largest of the lists' depth-th keys is a floor of the K-th
+// best, and only keys that reach it are ranked: about 1.3 K of them.  A list's first `chunk` keys are read at once (chunk
+// covers 2.5 times a list's share of the K best and the depth), lists that reach the floor with all of them are read on,
+// chunk after chunk.  One round trip to memory, usually; reading everything instead took two launches for 256 lists of
+// K = 100 (25,600 keys: sixteen folds of sixteen lists, then one: 12 us; this: 4 us).
+template <int NT, bool STAMP = false>
+__global__ __launch_bounds__(NT) void fold_lists_kernel(FoldArgs a) {
+    constexpr int R = kFoldSlots / NT;
     extern __shared__ __align__(16) unsigned char smem[];
-    uint64_t* const rec = STAMP ? a.stamps + (((size_t)blockIdx.y * gridDim.x + blockIdx.x) * (NT / kWave) + threadIdx.x / kWave) * kStampSlots : nullptr;
-    stamp<STAMP>(rec, kStampEntry, threadIdx.x & (kWave - 1));
+    __shared__ int n_cand, n_more[2];
+    __shared__ uint64_t floor_key;
     uint32_t* hist = reinterpret_cast<uint32_t*>(smem);
     Ctl* ctl = reinterpret_cast<Ctl*>(smem + kBins * sizeof(uint32_t));
     uint64_t* stage = reinterpret_cast<uint64_t*>(smem + kBins * sizeof(uint32_t) + align16(sizeof(Ctl)));
-    uint64_t* cand = stage + a.stage_keys;
-    uint64_t* sorted = cand + a.candmax;
-    const int tid = threadIdx.x, q = blockIdx.y, group = blockIdx.x, K = a.K;
-    const int first_list = group * a.lists_per_group;
-    const int my_lists = a.nlists - first_list < a.lists_per_group ? a.nlists - first_list : a.lists_per_group;
-    const uint64_t* all = a.ws_keys + ((size_t)q * a.nlists + first_list) * K;
-    const long long nkeys = (long long)my_lists * K;
-    auto key_at = [&](long long i) { return all[i]; };
-    auto emit = [&](const uint64_t* sorted_keys) {
-        for (int t = tid; t < K; t += NT) {
-            const uint64_t key = sorted_keys[t];
-            if (a.out_keys != nullptr) {
-                a.out_keys[((size_t)q * gridDim.x + group) * K + t] = key;
-            } else {
-                a.out_ids[(size_t)q * K + t] = id_of_key(key);
-                a.out_scores[(size_t)q * K + t] = score_of_key(key);
-            }
-        }
+    uint64_t* cand = stage + kFoldCand;
+    uint64_t* sorted = cand + kFoldCand;
+    uint64_t* heads = stage;                                  // [kFoldLists]
+    int* more[2] = {reinterpret_cast<int*>(stage + kFoldLists), reinterpret_cast<int*>(stage + kFoldLists) + kFoldLists};
+    static_assert(2 * kFoldLists * sizeof(int) <= (kFoldCand - kFoldLists) * sizeof(uint64_t), "room for both lists of lists");
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), q = blockIdx.y, K = a.K, nlists = a.nlists;
+    uint64_t* const rec = STAMP ? a.stamps + ((size_t)q * (NT / kWave) + tid / kWave) * kStampSlots : nullptr;
+    stamp<STAMP>(rec, kStampEntry, lane);
+    const uint64_t* all = a.ws_keys + (size_t)q * nlists * K;
+    const int cshift = 31 - __builtin_clz((uint32_t)a.chunk);   // (a power of two)
+    auto emit = [&](int rank, uint64_t key) {
+        a.out_ids[(size_t)q * K + rank] = id_of_key(key);
+        a.out_scores[(size_t)q * K + rank] = score_of_key(key);
     };
 
-    // score range of all the keys (empty slots of short lists are 0).  The host never gives a workgroup more keys than
-    // its registers hold (nkeys <= NT * REGS: fold_lists_per_group()).
-    const int lane = tid & (kWave - 1);
-    uint64_t keys[REGS];
-    float mn = __builtin_inff(), mx = -__builtin_inff();
+    uint64_t keys[R];
 #pragma unroll
-    for (int r = 0; r < REGS; ++r) {
-        const long long i = (long long)r * NT + tid;
-        keys[r] = (i < nkeys) ? key_at(i) : 0ull;
-        if (keys[r]) { float s = score_of_key(keys[r]); mn = fminf(mn, s); mx = fmaxf(mx, s); }
+    for (int r = 0; r < R; ++r) {
+        const int i = r * NT + tid, list = i >> cshift, pos = i & (a.chunk - 1);
+        keys[r] = (list < nlists && pos < K) ? all[(size_t)list * K + pos] : 0ull;
     }
-    for (int i = tid; i < kBins; i += NT) hist[i] = 0;
+    if (tid == 0) { n_cand = 0; n_more[0] = n_more[1] = 0; floor_key = 1ull; }   // (every key is at least 1)
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const int i = r * NT + tid, list = i >> cshift, pos = i & (a.chunk - 1);
+        if (list < nlists && pos == a.depth - 1) heads[list] = keys[r];
+    }
+    __syncthreads();
     stamp<STAMP>(rec, kStampLoaded, lane);
+
+    // ---- the need-th largest of the lists' depth-th keys: the one that need - 1 others beat (keys are distinct; fewer than
+    // `need` lists that long: no floor)
+    for (int part_of = tid; part_of < nlists * 4; part_of += NT) {   // four lanes per list, each over a quarter of the others
+        const int l = part_of >> 2, part = part_of & 3;
+        const uint64_t mine = heads[l];
+        uint32_t rank = 0;
+        for (int u = part; u < nlists; u += 4) rank += heads[u] > mine;
+        rank += dpp_u32<kDppQuadSwap1>(0u, rank);
+        rank += dpp_u32<kDppQuadSwap2>(0u, rank);
+        if (part == 0 && mine != 0ull && rank == (uint32_t)a.need - 1u) floor_key = mine;
+    }
+    __syncthreads();
+    stamp<STAMP>(rec, kStampCut, lane);
+    const uint64_t f = floor_key;
+
+    // ---- what reaches it
+    auto take = [&](uint64_t key) {
+        const bool in = key >= f;
+        const uint64_t mask = __ballot(in);
+        if (mask == 0) return;
+        int base = 0;
+        if (lane == __builtin_ctzll(mask)) base = atomicAdd(&n_cand, __popcll(mask));
+        base = __builtin_amdgcn_readlane(base, __builtin_ctzll(mask));
+        const int pos = base + __popcll(mask & ((1ull << lane) - 1ull));
+        if (in && pos < kFoldCand) cand[pos] = key;
+    };
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const int i = r * NT + tid, list = i >> cshift, pos = i & (a.chunk - 1);
+        take(keys[r]);
+        if (keys[r] >= f && pos == a.chunk - 1 && a.chunk < K) more[0][atomicAdd(&n_more[0], 1)] = list;
+    }
+    __syncthreads();
+    int n = n_more[0];
+    for (int off = a.chunk, turn = 0; n != 0; off += a.chunk, turn ^= 1) {   // (the same n for the whole workgroup; ends at off >= K)
+        const int slots = (n << cshift);
+        for (int i0 = 0; i0 < slots; i0 += NT) {
+            const int i = i0 + tid, pos = off + (i & (a.chunk - 1));
+            const int list = i < slots ? more[turn][i >> cshift] : 0;
+            const uint64_t key = (i < slots && pos < K) ? all[(size_t)list * K + pos] : 0ull;
+            take(key);
+            if (key >= f && (i & (a.chunk - 1)) == a.chunk - 1 && pos + 1 < K) more[turn ^ 1][atomicAdd(&n_more[turn ^ 1], 1)] = list;
+        }
+        __syncthreads();
+        n = n_more[turn ^ 1];
+        if (tid == 0) n_more[turn] = 0;
+        __syncthreads();
+    }
+    stamp<STAMP>(rec, kStampCollected, lane);
+    const int c = n_cand;
+    if (c <= kFoldCand) {
+        const int c8 = (c + 7) & ~7;
+        if (c + tid < c8) cand[c + tid] = 0ull;
+        __syncthreads();
+        rank_emit<NT>(cand, c, K, tid, emit);
+        stamp<STAMP>(rec, kStampSelected, lane);
+        stamp<STAMP>(rec, kStampEnd, lane);
+        return;
+    }
+
+    // ---- too many (a floor far below the K-th best: lists that share few of the best keys evenly): everything once more,
+    // stage by stage
+    __syncthreads();
+    const long long nkeys = (long long)nlists * K;
+    float mn = __builtin_inff(), mx = -__builtin_inff();
+    for (long long i = tid; i < nkeys; i += NT) {
+        const uint64_t key = all[i];
+        if (key) { const float s = score_of_key(key); mn = fminf(mn, s); mx = fmaxf(mx, s); }
+    }
     float lo, scale;
     set_range<NT / kWave>(mn, mx, ctl, tid, lo, scale);
-
-    {
-        // one pass: histogram, cut, collect the few keys at or above the cut, rank them
-        int bk[REGS];
-#pragma unroll
-        for (int r = 0; r < REGS; ++r) {
-            bk[r] = -1;
-            if (keys[r]) { bk[r] = bucket_of(score_of_key(keys[r]), lo, scale); atomicAdd(&hist[bk[r]], 1u); }
-        }
-        __syncthreads();
-        if (tid < kWave) find_cut(hist, K, ctl, lane);
-        __syncthreads();
-        stamp<STAMP>(rec, kStampCut, lane);
-        const int bstar = ctl->bstar;
-#pragma unroll
-        for (int r = 0; r < REGS; ++r) {
-            if (bk[r] >= bstar) {
-                int pos = atomicAdd(&ctl->ncand, 1);
-                if (pos < a.candmax) cand[pos] = keys[r];
-            }
-        }
-        __syncthreads();
-        stamp<STAMP>(rec, kStampCollected, lane);
-        const int C = ctl->ncand;
-        if (C <= a.candmax) {
-            rank_select<NT>(cand, C, K, sorted, tid);
-            stamp<STAMP>(rec, kStampSelected, lane);
-            emit(sorted);
-            stamp<STAMP>(rec, kStampEnd, lane);
-            return;
-        }
-        // too many keys share the cut bucket (heavy ties): take the staged, sorting path below
-    }
-
-    int keep = 0;                                            // best-so-far keys carried at the front of stage
+    int keep = 0;                                             // best-so-far keys carried at the front of stage
     long long done = 0;
     while (done < nkeys) {
-        long long take = nkeys - done;
-        if (take > a.stage_keys - keep) take = a.stage_keys - keep;
-        for (int t = tid; t < a.stage_keys - keep; t += NT) stage[keep + t] = (t < take) ? key_at(done + t) : 0ull;
+        long long n_in = nkeys - done;
+        if (n_in > kFoldCand - keep) n_in = kFoldCand - keep;
+        for (int t = tid; t < kFoldCand - keep; t += NT) stage[keep + t] = (t < n_in) ? all[done + t] : 0ull;
         __syncthreads();
-        block_select<NT>(stage, a.stage_keys, K, sorted, cand, a.candmax, hist, ctl, tid);
-        done += take;
+        block_select<NT>(stage, kFoldCand, K, sorted, cand, kFoldCand, hist, ctl, tid);
+        done += n_in;
         keep = K;
         if (done < nkeys) {
             for (int t = tid; t < K; t += NT) stage[t] = sorted[t];
             __syncthreads();
         }
     }
-    emit(sorted);
+    for (int t = tid; t < K; t += NT) emit(t, sorted[t]);
 }
 
 // The fold for small K (K <= kSmallKMax) when a query's lists fit R keys per thread (nlists * K <= NT * R): the keys go

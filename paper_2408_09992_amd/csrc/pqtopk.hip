@@ -20,7 +20,7 @@
 //   scan_topk_tiled_kernel<M> (scan_batched.hpp; m = 8 or 16, larger batches; a tile of four queries per workgroup,
 //     tables interleaved as float4 so one 16-byte LDS read serves the four queries and sub-id extraction is shared):
 //     same steps; its floors are workgroup-wide, kept up to date by a running histogram of the candidates' scores.
-//   fold_topk_kernel (fold.hpp; one workgroup per query) reduces the workgroups' lists to the final sorted K.
+//   fold_lists_kernel or fold_small_kernel (fold.hpp; one workgroup per query) reduces the workgroups' lists to the final sorted K.
 // Floors and histograms only ever prune; every decision that picks a winner compares full keys, so the result is
 // exact for any input, including heavy ties (which merely take slower paths).
 //
@@ -86,7 +86,6 @@ struct ScanPlan {
     int nblk;        // item blocks per query
     int cap;         // keys per wave list
     int candmax;     // keys of the candidate array
-    int stage_keys;  // keys the fold stages per pass
     size_t scan_dyn_lds;     // dynamic LDS of the scan launch
     size_t scan_lds;         // dynamic + the static score tables of the vector kernels
     size_t fold_lds;
@@ -184,16 +183,7 @@ ScanPlan make_plan(long long N, int B, int m, int K, bool generic = false, int c
     if (rounds > one_per_cu && rounds <= most) nblk = one_per_cu;
     if (nblk < 1) nblk = 1;
     nblk = xcd_aligned(nblk, B);
-    {
-        // A fold of one launch instead of two levels is worth a slightly coarser grid (K = 53 .. 69 at batch 1: 256
-        // lists of K = 64 take two fold levels, 208 lists one launch: 22.1 -> 19.1 us per call); not a much coarser one
-        // (K = 100 on 133 workgroups instead of 256: 24.7 -> 26.9 us).
-        const long long one_fold = (long long)kBigThreads * kFoldWideRegs / K;   // lists one fold launch takes
-        if (nblk > one_fold && 4 * one_fold >= 3 * nblk) nblk = one_fold;
-    }
     p.nblk = (int)nblk;
-    p.stage_keys = next_pow2(2 * K);
-    if (p.stage_keys < kChunkKeys) p.stage_keys = kChunkKeys;
     p.copies = 1;
     // A long scan for few queries is bound by LDS bank conflicts of the random lookups: with kTableCopies copies of
     // the tables, lanes l and l' collide only if l % kTableCopies == l' % kTableCopies.  Worth its LDS and fill time
@@ -265,7 +255,7 @@ ScanPlan make_plan(long long N, int B, int m, int K, bool generic = false, int c
             p.nblk = (int)nb;
         }
     }
-    p.fold_lds = fold_lds_bytes(p.stage_keys, p.candmax, K);
+    p.fold_lds = fold_lds_bytes(K);
     // Single-query scans (one query per workgroup row) with a small K whose share per thread fits a few registers run
     // the short kernel: scores stay in registers, one selection, a few KB of code.  Its grid is spread as thin as the
     // CUs allow (one workgroup per CU over all queries): a workgroup's time is the lookups of its share plus a fixed
@@ -439,20 +429,14 @@ size_t keys_bytes(const ScanPlan& p, int B, int K) {
     return (bytes + 255) & ~(size_t)255;
 }
 
-size_t fold_area_keys(int nblk, int B, int K);
-
-// workspace: [B][nblk][K] keys from the scan | a second, smaller key area for folds that take more than one level
-// | filter scans: the queries' tables of counts | their FilterQuery records | their histograms | the sample's best scores
-size_t fold_area_bytes(const ScanPlan& p, int B, int K) {
-    return (fold_area_keys(p.nblk, B, K) * sizeof(uint64_t) + 255) & ~(size_t)255;
-}
+// workspace: [B][nblk][K] keys from the scan | filter scans: the queries' tables of counts | their FilterQuery records | their histograms | the sample's best scores
 size_t counts_bytes(const ScanPlan& p, int B) {
     return p.filter ? ((size_t)B * p.f_entries * sizeof(uint16_t) + 255) & ~(size_t)255 : 0;
 }
 size_t query_bytes(const ScanPlan& p, int B) { return p.filter ? ((size_t)B * sizeof(FilterQuery) + 255) & ~(size_t)255 : 0; }
 size_t hist_bytes(const ScanPlan& p, int B) { return p.filter ? (size_t)B * kFilterBins * sizeof(uint32_t) : 0; }
 size_t workspace_bytes(const ScanPlan& p, int B, int K) {
-    return keys_bytes(p, B, K) + fold_area_bytes(p, B, K) + counts_bytes(p, B) + query_bytes(p, B) + hist_bytes(p, B) +
+    return keys_bytes(p, B, K) + counts_bytes(p, B) + query_bytes(p, B) + hist_bytes(p, B) +
            (p.filter && p.f_parts > 1 ? ((size_t)B * p.f_parts * p.f_best * sizeof(float) + 255) & ~(size_t)255 : 0);
 }
 
@@ -701,7 +685,7 @@ int enqueue_scan(const ScanPlan& p, const uint8_t* codes, const float* S, long l
                  void* workspace, hipStream_t st, const int* subset = nullptr, long long n_items = 0, int cw = 1,
                  uint64_t* stamps = nullptr) {
     if (p.filter) {
-        unsigned char* ws = static_cast<unsigned char*>(workspace) + keys_bytes(p, B, K) + fold_area_bytes(p, B, K);
+        unsigned char* ws = static_cast<unsigned char*>(workspace) + keys_bytes(p, B, K);
         FilterArgs f;
         f.codes = codes; f.S = S; f.N = N; f.b = b; f.K = K; f.B = B; f.cap = p.f_cap;
         f.subset = subset; f.n_items = (uint32_t)(subset ? n_items : N);
@@ -796,85 +780,41 @@ int enqueue_scan(const ScanPlan& p, const uint8_t* codes, const float* S, long l
     return record_hip(e);
 }
 
-// Lists one fold workgroup takes at a level with `nlists` lists per query.  All of them when their keys fit the usual
-// fold's registers (kThreads * kFoldRegs keys), or the wide fold's (kBigThreads * kFoldWideRegs keys, `wide` set: one
-// launch of one larger workgroup instead of two levels).  More keys than that are split into groups: several small
-// folds side by side and one more level beat one workgroup that reads everything (256 lists of K = 100: 12 us in two
-// levels, 16-24 us in one workgroup of 1024 threads holding 26 keys each).  A group has about sqrt(nlists) lists, so
-// that both levels are small (256 lists of K = 100: 16 folds of 16 lists, then one of 16, instead of 5 folds of 61
-// lists and one of 5: 14.4 -> 12.2 us), and never more keys than the usual fold's registers hold.
-int fold_lists_per_group(int nlists, int K, bool* wide) {
-    const long long nkeys = (long long)nlists * K;
-    *wide = nkeys > (long long)kThreads * kFoldRegs && nkeys <= (long long)kBigThreads * kFoldWideRegs;
-    if (nkeys <= (long long)kBigThreads * kFoldWideRegs) return nlists;
-    const int fit = kThreads * kFoldRegs / K;
-    int per = 2;
-    while (per * per < nlists) ++per;
-    if (per > fit) per = fit;
-    return per < 2 ? 2 : per;
-}
-
-// Keys of the second key area of the workspace: what the first fold level writes when the lists of a query do not fit
-// one workgroup's registers (later levels alternate between the two areas, each needing less than the one before).
-size_t fold_area_keys(int nblk, int B, int K) {
-    bool wide;
-    const int per = fold_lists_per_group(nblk, K, &wide);
-    if (nblk <= per) return 0;
-    return (size_t)B * ((nblk + per - 1) / per) * K;
-}
-
-// Enqueue the fold of the workspace's lists into the outputs: one launch when a query's lists fit one workgroup's
-// registers, else levels of launches that each fold groups of lists into one list per group.
+// Enqueue the fold of the workspace's lists into the outputs.
 int enqueue_fold(const ScanPlan& p, int B, int K, void* workspace, int* out_ids, float* out_scores, hipStream_t st,
                  uint64_t* stamps = nullptr) {
-    hipError_t e = allow_lds(fold_topk_kernel<kThreads, kFoldRegs>, p.fold_lds);
-    if (e == hipSuccess) e = allow_lds(fold_topk_kernel<kBigThreads, kFoldWideRegs>, p.fold_lds);
-    if (e != hipSuccess) return record_hip(e);
-    uint64_t* area[2] = {static_cast<uint64_t*>(workspace),
-                         reinterpret_cast<uint64_t*>(static_cast<unsigned char*>(workspace) + keys_bytes(p, B, K))};
-    int nlists = p.nblk, src = 0;
-    for (;;) {
-        bool wide;
-        const int per = fold_lists_per_group(nlists, K, &wide);
-        const int groups = nlists <= per ? 1 : (nlists + per - 1) / per;
-        FoldArgs f;
-        f.ws_keys = area[src];
-        f.nlists = nlists; f.K = K; f.lists_per_group = groups == 1 ? nlists : per;
-        f.stage_keys = p.stage_keys; f.candmax = p.candmax;
-        f.out_keys = groups == 1 ? nullptr : area[1 - src];
-        f.out_ids = out_ids; f.out_scores = out_scores;
-        f.stamps = stamps;
-        if (groups == 1 && K <= kSmallKMax && (long long)nlists * K <= (long long)kThreads * kFoldSmallRegsMax &&
-            !(g_force_general.load(std::memory_order_relaxed) & 2)) {
-            // small K, few keys: the lean fold
-            const bool few = (long long)nlists * K <= (long long)kThreads * kFoldSmallRegs;
-            if (stamps != nullptr) {
-                if (few) hipLaunchKernelGGL((fold_small_kernel<kThreads, kFoldSmallRegs, true>), dim3(1, B), dim3(kThreads), 0, st, f);
-                else hipLaunchKernelGGL((fold_small_kernel<kThreads, kFoldSmallRegsMax, true>), dim3(1, B), dim3(kThreads), 0, st, f);
-            } else {
-                if (few) hipLaunchKernelGGL((fold_small_kernel<kThreads, kFoldSmallRegs, false>), dim3(1, B), dim3(kThreads), 0, st, f);
-                else hipLaunchKernelGGL((fold_small_kernel<kThreads, kFoldSmallRegsMax, false>), dim3(1, B), dim3(kThreads), 0, st, f);
-            }
-            return record_hip(hipGetLastError());
+    const int nlists = p.nblk;
+    FoldArgs f;
+    f.ws_keys = static_cast<const uint64_t*>(workspace);
+    f.nlists = nlists; f.K = K;
+    f.chunk = f.depth = f.need = 0;
+    f.out_ids = out_ids; f.out_scores = out_scores;
+    f.stamps = stamps;
+    if (K <= kSmallKMax && (long long)nlists * K <= (long long)kThreads * kFoldSmallRegsMax &&
+        !(g_force_general.load(std::memory_order_relaxed) & 2)) {
+        // small K, few keys: the lean fold
+        const bool few = (long long)nlists * K <= (long long)kThreads * kFoldSmallRegs;
+        if (stamps != nullptr) {
+            if (few) hipLaunchKernelGGL((fold_small_kernel<kThreads, kFoldSmallRegs, true>), dim3(1, B), dim3(kThreads), 0, st, f);
+            else hipLaunchKernelGGL((fold_small_kernel<kThreads, kFoldSmallRegsMax, true>), dim3(1, B), dim3(kThreads), 0, st, f);
+        } else {
+            if (few) hipLaunchKernelGGL((fold_small_kernel<kThreads, kFoldSmallRegs, false>), dim3(1, B), dim3(kThreads), 0, st, f);
+            else hipLaunchKernelGGL((fold_small_kernel<kThreads, kFoldSmallRegsMax, false>), dim3(1, B), dim3(kThreads), 0, st, f);
         }
-        if (stamps != nullptr) {                             // measurement instance: the usual one-launch fold only
-            if (wide || groups != 1) return PQ_ERR_UNSUPPORTED;
-            e = allow_lds(fold_topk_kernel<kThreads, kFoldRegs, true>, p.fold_lds);
-            if (e != hipSuccess) return record_hip(e);
-            hipLaunchKernelGGL((fold_topk_kernel<kThreads, kFoldRegs, true>), dim3(1, B), dim3(kThreads), p.fold_lds, st, f);
-            return record_hip(hipGetLastError());
-        }
-        if (wide)
-            hipLaunchKernelGGL((fold_topk_kernel<kBigThreads, kFoldWideRegs>), dim3(groups, B), dim3(kBigThreads), p.fold_lds,
-                               st, f);
-        else
-            hipLaunchKernelGGL((fold_topk_kernel<kThreads, kFoldRegs>), dim3(groups, B), dim3(kThreads), p.fold_lds, st, f);
-        e = hipGetLastError();
-        if (e != hipSuccess) return record_hip(e);
-        if (groups == 1) return PQ_OK;
-        nlists = groups;
-        src = 1 - src;
+        return record_hip(hipGetLastError());
     }
+    // (see fold_lists_kernel: a chunk holds 2.5 times a list's share of the K best, and the depth at which at most 60 % of
+    // the lists have to reach the floor)
+    f.chunk = 4;
+    while (f.chunk < K && 2LL * f.chunk * nlists < 5LL * K) f.chunk *= 2;
+    f.depth = 1;
+    while (f.depth < f.chunk && f.depth < K && 10LL * ((K + f.depth - 1) / f.depth) > 6LL * nlists) ++f.depth;
+    f.need = (K + f.depth - 1) / f.depth;
+    if (nlists > kFoldLists || (long long)nlists * f.chunk > kFoldSlots) return PQ_ERR_UNSUPPORTED;   // (no plan makes that many)
+    if (stamps != nullptr) hipLaunchKernelGGL((fold_lists_kernel<kFoldThreads, true>), dim3(1, B), dim3(kFoldThreads), p.fold_lds, st, f);
+    else if (B < 64) hipLaunchKernelGGL((fold_lists_kernel<kFoldThreads>), dim3(1, B), dim3(kFoldThreads), p.fold_lds, st, f);
+    else hipLaunchKernelGGL((fold_lists_kernel<kFoldThreadsMany>), dim3(1, B), dim3(kFoldThreadsMany), p.fold_lds, st, f);
+    return record_hip(hipGetLastError());
 }
 
 // Batch from which Eq. 4 runs on the matrix cores.  The scalar kernels are faster below: a wave's chain of d/m matrix
@@ -1069,7 +1009,7 @@ int pq_measure_step_stamps(const float* queries, const float* centroids, const u
         return PQ_ERR_UNSUPPORTED;                             // (scan kernels with a measurement instance)
     const int waves = p.filter ? kFilterWaves : (!p.tiled && p.big) ? kMaxWaves : kWaves;
     const long long scan_groups = p.filter ? (long long)p.nblk * ((B + p.f_queries - 1) / p.f_queries) : p.tiled ? (long long)p.nblk * ((B + kQ - 1) / kQ) : (long long)p.nblk * B;
-    if (scan_groups * waves > PQ_STAMP_RECORDS || (long long)B * kWaves > PQ_STAMP_RECORDS) return PQ_ERR_UNSUPPORTED;
+    if (scan_groups * waves > PQ_STAMP_RECORDS || (long long)B * (kFoldThreads / kWave) > PQ_STAMP_RECORDS) return PQ_ERR_UNSUPPORTED;
     if (scan_grid != nullptr) { scan_grid[0] = (int)scan_groups; scan_grid[1] = waves; }
     hipStream_t st = static_cast<hipStream_t>(stream);
     const size_t section = (size_t)PQ_STAMP_RECORDS * PQ_STAMP_SLOTS;
@@ -1190,11 +1130,9 @@ ScanPlan make_topk_scores_plan(long long N, int B, int K) {
     p.cap = list_capacity(K);
     p.candmax = next_pow2(2 * K);
     if (p.candmax < 512) p.candmax = 512;
-    p.stage_keys = next_pow2(2 * K);
-    if (p.stage_keys < kChunkKeys) p.stage_keys = kChunkKeys;
     p.copies = 1;
     p.scan_dyn_lds = p.scan_lds = scan_lds_bytes(0, p.cap, p.candmax, K, kWaves);
-    p.fold_lds = fold_lds_bytes(p.stage_keys, p.candmax, K);
+    p.fold_lds = fold_lds_bytes(K);
     return p;
 }
 

@@ -238,6 +238,31 @@ def test_score_topk_batched_kernel_shapes(pq, oracle, N, m, B, K, b):
     assert_same_topk(pq, oracle, G, S, K, "batched")
 
 
+@pytest.mark.parametrize("N,B,K", [(1_280_000, 1, 32), (1_280_000, 1, 100), (300_000, 1, 512), (3_000, 1, 512), (1_030, 2, 512),
+                                   (700_001, 5, 33), (40_000, 64, 100), (2_000, 300, 257)])
+def test_fold_of_sorted_lists(pq, oracle, N, B, K):
+    """The one-launch fold of any K: lists from 1 to 256, chunks that end inside the lists, lists that hold all of the best
+    (read on chunk after chunk: the catalogue sorted by score) and floors that say nothing (equal scores)."""
+    rng = np.random.default_rng(N + K)
+    for kind in ("random", "sorted", "coarse"):
+        codes = rng.integers(0, 256, (N, 8), dtype=np.uint8)
+        S = tables(K, B, 8, 256)
+        if kind == "sorted":
+            i = np.arange(N)[::-1]
+            codes[:] = 0
+            codes[:, 0], codes[:, 1], codes[:, 2] = i >> 16, (i >> 8) & 255, i & 255
+            S = np.zeros((B, 8, 256), dtype=np.float32)
+            for k, scale in enumerate((65536.0, 256.0, 1.0)):
+                S[:, k] = np.arange(256, dtype=np.float32) * np.float32(scale)
+        elif kind == "coarse":
+            S = np.round(S).astype(np.float32)
+        prev = pq.pq_measure_force_general(8)
+        try:
+            assert_same_topk(pq, oracle, codes, S, K, f"fold {kind}")
+        finally:
+            pq.pq_measure_force_general(prev)
+
+
 # ---- batches scanned by upper bounds: every geometry of fields and rows, edges of tiles and of the last code vector, K from 1
 # to the longest lists, samples of one and of several parts and rounds; bit 4 keeps small shapes on these kernels
 def _bounds_case(pq, oracle, codes, S, K, subset=None):
