@@ -176,6 +176,32 @@ __device__ void bitonic_sort_desc(uint64_t* a, int n, int tid, int nthr) {
     }
 }
 
+// Bitonic sort of n (a power of two) keys in LDS, descending, by a workgroup of NT threads.  A wave's 64 pairs of a stage lie
+// within 128 consecutive keys when the stage's distance is at most 64: such stages need no workgroup barrier between them
+// (1024 keys: 7 barriers instead of 55).  Ends with a barrier.
+template <int NT>
+__device__ void block_sort_desc(uint64_t* a, int n, int tid) {
+    __syncthreads();
+    for (int k = 2; k <= n; k <<= 1) {
+        for (int j = k >> 1; j > 0; j >>= 1) {
+            for (int t = tid; t < (n >> 1); t += NT) {
+                const int i = ((t & ~(j - 1)) << 1) | (t & (j - 1)), p = i | j;
+                const bool desc = (i & k) == 0;
+                const uint64_t x = a[i], y = a[p];
+                if ((x < y) == desc) { a[i] = y; a[p] = x; }
+            }
+            const int next = j > 1 ? j >> 1 : k;              // distance of the stage that follows (k: of the next k's first)
+            if (j > kWave || next > kWave) __syncthreads(); else wave_sync();
+        }
+    }
+    __syncthreads();
+}
+
+// Keys from which ordering by buckets (with a range) or sorting (without) beats ranking by counting, whose LDS reads take
+// n^2 / 16 clocks in a workgroup of 512.
+constexpr int kRankByCount = 192, kRankBySort = 448;
+__device__ __forceinline__ int pow2_at_least(int n) { return n <= 1 ? 1 : 1 << (32 - __builtin_clz((uint32_t)(n - 1))); }
+
 // Slots of a wave's stamp record (measurement instances of the kernels; wall_clock64() ticks, lane 0 of the wave).
 // A slot a kernel does not pass stays as the caller left it.
 constexpr int kStampSlots = 16;

@@ -121,10 +121,23 @@ __global__ __launch_bounds__(NT) void fold_lists_kernel(FoldArgs a) {
     stamp<STAMP>(rec, kStampCollected, lane);
     const int c = n_cand;
     if (c <= kFoldCand) {
-        const int c8 = (c + 7) & ~7;
-        if (c + tid < c8) cand[c + tid] = 0ull;
-        __syncthreads();
-        rank_emit<NT>(cand, c, K, tid, emit);
+        if (c > kRankByCount) {
+            // by buckets over the candidates' own range
+            float mn = __builtin_inff(), mx = -__builtin_inff(), lo, scale;
+            for (int t = tid; t < c; t += NT) { const float v = score_of_key(cand[t]); mn = fminf(mn, v); mx = fmaxf(mx, v); }
+            set_range<NT / kWave>(mn, mx, ctl, tid, lo, scale);
+            if (!bucket_sort<NT, kFoldCand / NT>(cand, c, lo, scale, hist, tid)) {
+                const int padded = pow2_at_least(c);
+                for (int t = c + tid; t < padded; t += NT) cand[t] = 0ull;
+                block_sort_desc<NT>(cand, padded, tid);
+            }
+            for (int t = tid; t < K; t += NT) emit(t, t < c ? cand[t] : 0ull);
+        } else {
+            const int c8 = (c + 7) & ~7;
+            if (c + tid < c8) cand[c + tid] = 0ull;
+            __syncthreads();
+            rank_emit<NT>(cand, c, K, tid, emit);
+        }
         stamp<STAMP>(rec, kStampSelected, lane);
         stamp<STAMP>(rec, kStampEnd, lane);
         return;

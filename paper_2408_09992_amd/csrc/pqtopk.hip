@@ -84,6 +84,7 @@ struct ScanPlan {
     bool tiled;      // batched kernel: kQ queries per workgroup
     bool big;        // single-query kernel: kBigThreads threads per workgroup, one workgroup per CU
     int nblk;        // item blocks per query
+    bool direct;     // nblk is 1 and the scan writes the result itself
     int cap;         // keys per wave list
     int candmax;     // keys of the candidate array
     size_t scan_dyn_lds;     // dynamic LDS of the scan launch
@@ -155,6 +156,11 @@ double tiled_min_lookups(int m, int K) {
     return K <= 128 ? kTiledMinLookups * (1.0 + K / 400.0) : 5.0e8;
 }
 
+// Units (code vectors; items of 32 bytes and more) per thread up to which one workgroup scans a query's whole catalogue and
+// writes the result: the scan takes up to 3 us longer than spread over the chip, the fold's launch (3 us of host time, 3.7 us
+// from the scan's end to the result) is saved.
+constexpr long long kDirectUnits(int row) { return row <= 16 ? 8 : row == 32 ? 4 : 2; }
+
 // `generic`: plan for the generic kernel whatever m is (candidate-list scans use it: their rows are gathered)
 // `cw`, `b`: bytes per sub-id (1 or 2) and, for two-byte sub-ids, the alphabet size (it sizes the tables in LDS)
 size_t workspace_bytes(const ScanPlan& p, int B, int K);
@@ -181,7 +187,7 @@ ScanPlan make_plan(long long N, int B, int m, int K, bool generic = false, int c
     long long one_per_cu = kAssumedCUs / B;                    // a short scan is spread evenly: one workgroup per CU, which
     if (one_per_cu < 8) one_per_cu = 8;                        // then takes two or three (possibly ragged) rounds
     if (rounds > one_per_cu && rounds <= most) nblk = one_per_cu;
-    if (nblk < 1) nblk = 1;
+    if (nblk < 1 || (rounds <= kRing && N >= K)) nblk = 1;    // (what one workgroup holds in registers: no fold)
     nblk = xcd_aligned(nblk, B);
     p.nblk = (int)nblk;
     p.copies = 1;
@@ -266,7 +272,7 @@ ScanPlan make_plan(long long N, int B, int m, int K, bool generic = false, int c
     const bool short16 = cw == 2 && !p.glut && lut_floats * sizeof(float) + sizeof(SmallSelectLds<kThreads>) <= kMaxLdsBytes;
     if ((cw == 1 || short16) && p.vec && !generic && !p.tiled && K <= kSmallKMax) {
         long long nb = kAssumedCUs / B;
-        if (nb < 1) nb = 1;
+        if (nb < 1 || units <= kDirectUnits(row) * (long long)kThreads) nb = 1;
         const long long thin = (units + kThreads - 1) / kThreads;          // workgroups if every thread held one unit
         if (nb > thin) nb = thin;
         const long long per_slot = (long long)kThreads * nb;               // units one slot of all threads covers
@@ -300,7 +306,7 @@ ScanPlan make_plan(long long N, int B, int m, int K, bool generic = false, int c
     if (generic && cw == 1 && (m == 4 || m == 8 || m == 16) && K <= kSmallKMax &&
         !(g_force_general.load(std::memory_order_relaxed) & 1)) {
         long long nb = kAssumedCUs / B;
-        if (nb < 1) nb = 1;
+        if (nb < 1 || N * m <= kDirectUnits(16) * 16LL * kThreads) nb = 1;
         const long long thin = (N + kThreads - 1) / kThreads;              // workgroups if every thread held one candidate
         if (nb > thin) nb = thin;
         const long long per_thread = (N + kThreads * nb - 1) / (kThreads * nb);
@@ -322,6 +328,7 @@ ScanPlan make_plan(long long N, int B, int m, int K, bool generic = false, int c
         // (a workspace of at most 32 KB per result and 1 MB: the tables of tens of thousands of queries can be more)
         if (f.filter && workspace_bytes(f, B, K) <= ((size_t)B * K << 15) + (1u << 20)) p = f;
     }
+    p.direct = p.nblk == 1;
     return p;
 }
 
@@ -681,8 +688,9 @@ hipError_t launch_filter(const ScanPlan& p, const FilterArgs& a, int m, int cw, 
 // Enqueue the catalogue scan: every workgroup's K best keys land in the workspace.
 // `subset` / `n_items`: candidate list (then N is its length and the plan is a generic one) or nullptr / N
 // `cw`: bytes per sub-id (2: `codes` holds uint16 values)
+// A plan of one item block per query leaves nothing to fold: the scan writes the result.
 int enqueue_scan(const ScanPlan& p, const uint8_t* codes, const float* S, long long N, int B, int m, int b, int K,
-                 void* workspace, hipStream_t st, const int* subset = nullptr, long long n_items = 0, int cw = 1,
+                 void* workspace, int* out_ids, float* out_scores, hipStream_t st, const int* subset = nullptr, long long n_items = 0, int cw = 1,
                  uint64_t* stamps = nullptr) {
     if (p.filter) {
         unsigned char* ws = static_cast<unsigned char*>(workspace) + keys_bytes(p, B, K);
@@ -690,6 +698,7 @@ int enqueue_scan(const ScanPlan& p, const uint8_t* codes, const float* S, long l
         f.codes = codes; f.S = S; f.N = N; f.b = b; f.K = K; f.B = B; f.cap = p.f_cap;
         f.subset = subset; f.n_items = (uint32_t)(subset ? n_items : N);
         f.ws_keys = static_cast<uint64_t*>(workspace);
+        f.out_ids = p.direct ? out_ids : nullptr; f.out_scores = out_scores;
         f.counts = reinterpret_cast<uint16_t*>(ws);
         f.query = reinterpret_cast<FilterQuery*>(ws + counts_bytes(p, B));
         f.entries = p.f_entries;
@@ -715,6 +724,7 @@ int enqueue_scan(const ScanPlan& p, const uint8_t* codes, const float* S, long l
     // floor of long scans keeps them from filling (K = 10: 50M items 79.7 -> 77.5 us, m = 4 at batch 64 57 -> 49 us).
     a.prune_at = (p.tiled && K <= 12) ? 2 * K + 8 : 0;
     a.ws_keys = static_cast<uint64_t*>(workspace);
+    a.out_ids = p.direct ? out_ids : nullptr; a.out_scores = out_scores;
     hipError_t e;
     if (p.short_scan && cw == 2) {
         if (stamps != nullptr) return PQ_ERR_UNSUPPORTED;
@@ -784,6 +794,7 @@ int enqueue_scan(const ScanPlan& p, const uint8_t* codes, const float* S, long l
 int enqueue_fold(const ScanPlan& p, int B, int K, void* workspace, int* out_ids, float* out_scores, hipStream_t st,
                  uint64_t* stamps = nullptr) {
     const int nlists = p.nblk;
+    if (p.direct) return PQ_OK;               // (the scan has written the result)
     FoldArgs f;
     f.ws_keys = static_cast<const uint64_t*>(workspace);
     f.nlists = nlists; f.K = K;
@@ -921,7 +932,7 @@ int pq_score_topk(const uint8_t* codes, const float* S, long long N, int B, int 
     if (rc != PQ_OK) return rc;
     const ScanPlan p = make_plan(N, B, m, K);
     hipStream_t st = static_cast<hipStream_t>(stream);
-    rc = enqueue_scan(p, codes, S, N, B, m, b, K, workspace, st);
+    rc = enqueue_scan(p, codes, S, N, B, m, b, K, workspace, out_ids, out_scores, st);
     if (rc != PQ_OK) return rc;
     return enqueue_fold(p, B, K, workspace, out_ids, out_scores, st);
 }
@@ -941,7 +952,7 @@ int pq_score_topk_static(const uint8_t* codes, const float* S, long long N, int 
     rc = static_scratch(&ws);
     if (rc != PQ_OK) return rc;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    rc = enqueue_scan(p, codes, S, N, B, m, b, K, ws, st);
+    rc = enqueue_scan(p, codes, S, N, B, m, b, K, ws, out_ids, out_scores, st);
     if (rc != PQ_OK) return rc;
     return enqueue_fold(p, B, K, ws, out_ids, out_scores, st);
 }
@@ -964,7 +975,7 @@ int profile_scan(const uint8_t* codes, const float* S, long long N, int B, int m
     if (e != hipSuccess) return record_hip(e);
     e = hipEventCreate(&ev1);
     if (e != hipSuccess) { (void)hipEventDestroy(ev0); return record_hip(e); }
-    auto scan = [&]() { return enqueue_scan(p, codes, S, N, B, m, b, K, workspace, st, nullptr, 0, cw); };
+    auto scan = [&]() { return enqueue_scan(p, codes, S, N, B, m, b, K, workspace, out_ids, out_scores, st, nullptr, 0, cw); };
     rc = scan();                                                            // untimed warm-up launch
     if (rc == PQ_OK) rc = record_hip(hipEventRecord(ev0, st));
     for (int it = 0; it < iters && rc == PQ_OK; ++it) rc = scan();
@@ -1025,7 +1036,7 @@ int pq_measure_step_stamps(const float* queries, const float* centroids, const u
         rc = pq_subitem_scores(queries, centroids, S, B, d, m, b, stream);   // (no measurement instance: section 0 stays empty)
     }
     if (rc != PQ_OK) return rc;
-    rc = enqueue_scan(p, codes, S, N, B, m, b, K, workspace, st, nullptr, 0, 1, stamps + section);
+    rc = enqueue_scan(p, codes, S, N, B, m, b, K, workspace, out_ids, out_scores, st, nullptr, 0, 1, stamps + section);
     if (rc != PQ_OK) return rc;
     return enqueue_fold(p, B, K, workspace, out_ids, out_scores, st, stamps + 2 * section);
 }
@@ -1043,7 +1054,7 @@ int pq_score_topk_u16(const uint16_t* codes, const float* S, long long N, int B,
     if (rc != PQ_OK) return rc;
     const ScanPlan p = make_plan(N, B, m, K, false, 2, b);
     hipStream_t st = static_cast<hipStream_t>(stream);
-    rc = enqueue_scan(p, reinterpret_cast<const uint8_t*>(codes), S, N, B, m, b, K, workspace, st, nullptr, 0, 2);
+    rc = enqueue_scan(p, reinterpret_cast<const uint8_t*>(codes), S, N, B, m, b, K, workspace, out_ids, out_scores, st, nullptr, 0, 2);
     if (rc != PQ_OK) return rc;
     return enqueue_fold(p, B, K, workspace, out_ids, out_scores, st);
 }
@@ -1078,7 +1089,7 @@ int pq_score_topk_subset(const uint8_t* codes, const float* S, const int* subset
         return PQ_ERR_ALIGN;
     if (workspace_bytes_given < workspace_bytes(p, B, K)) return PQ_ERR_WORKSPACE;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    int rc = enqueue_scan(p, codes, S, n_subset, B, m, b, K, workspace, st, subset, N);
+    int rc = enqueue_scan(p, codes, S, n_subset, B, m, b, K, workspace, out_ids, out_scores, st, subset, N);
     if (rc != PQ_OK) return rc;
     return enqueue_fold(p, B, K, workspace, out_ids, out_scores, st);
 }

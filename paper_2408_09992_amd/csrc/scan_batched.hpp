@@ -570,7 +570,7 @@ __global__ __launch_bounds__(kThreads) void scan_topk_tiled_kernel(ScanArgs a, i
     stamp<STAMP>(rec, kStampSelected, lane);
     for (int i = tid; i < nq * K; i += kThreads) {
         const int q = i / K, t = i % K;
-        a.ws_keys[((size_t)(q0 + q) * nblk + blockIdx.x) * K + t] = best[(size_t)q * kpad + t];
+        emit_key(a, q0 + q, nblk, blockIdx.x, t, best[(size_t)q * kpad + t]);
     }
     stamp<STAMP>(rec, kStampEnd, lane);
 }

@@ -50,6 +50,8 @@ struct FilterArgs {
     const int* subset;          // candidate list or nullptr
     uint32_t n_items;
     uint64_t* ws_keys;          // [B][nblk][K]
+    int* out_ids;               // [B][K]: the result, when one workgroup scans everything for a query; nullptr: lists for the fold
+    float* out_scores;
     uint16_t* counts;           // [B][entries] table counts in 256ths of a step; entries = M * 256, or M * b for two-byte sub-ids
     FilterQuery* query;         // [B]
     uint32_t* hist;             // [B][kFilterBins] exact scores found, by T above the first (cleared by filter_prepare_kernel)
@@ -810,14 +812,21 @@ __global__ __launch_bounds__(kFilterThreads) void scan_filter_kernel(FilterArgs 
             kept += __popcll(mask);
             wave_sync();
         }
-        uint64_t* const out = a.ws_keys + ((size_t)(q0 + q) * nblk + blk) * K;
+        auto out = [&](int t, uint64_t key) {
+            if (a.out_ids != nullptr) {
+                a.out_ids[(size_t)(q0 + q) * K + t] = id_of_key(key);
+                a.out_scores[(size_t)(q0 + q) * K + t] = score_of_key(key);
+            } else {
+                a.ws_keys[((size_t)(q0 + q) * nblk + blk) * K + t] = key;
+            }
+        };
         if (kept > 3 * kWave) {                               // (counting costs kept^2 / 64: 192 keys as much as a sort of 256)
             sort_wave_list(list, cap, kept, K, lane);
-            for (int t = lane; t < K && t < kept; t += kWave) out[t] = list[t];
-            for (int t = kept + lane; t < K; t += kWave) out[t] = 0ull;
+            for (int t = lane; t < K && t < kept; t += kWave) out(t, list[t]);
+            for (int t = kept + lane; t < K; t += kWave) out(t, 0ull);
             kept = 0;
         } else {
-            for (int t = kept + lane; t < K; t += kWave) out[t] = 0ull;
+            for (int t = kept + lane; t < K; t += kWave) out(t, 0ull);
         }
         const int n8 = (kept + 7) & ~7;                       // (cap is a multiple of 8)
         if (kept + lane < n8) list[kept + lane] = 0ull;
@@ -831,7 +840,7 @@ __global__ __launch_bounds__(kFilterThreads) void scan_filter_kernel(FilterArgs 
                 rank += (uint32_t)((p0.x > mine) + (p0.y > mine) + (p1.x > mine) + (p1.y > mine) + (p2.x > mine) + (p2.y > mine) +
                                    (p3.x > mine) + (p3.y > mine));
             }
-            if (rank < (uint32_t)K) out[rank] = mine;
+            if (rank < (uint32_t)K) out((int)rank, mine);
         }
         stamp<STAMP>(rec, kStampSelected, lane);
     }

@@ -152,12 +152,11 @@ __global__ __launch_bounds__(NT) void scan_short_kernel(ScanArgs a) {
     }
     stamp<STAMP>(rec, kStampScored, lane);
 
-    // ---- the workgroup's K best, ranked, straight to the workspace
-    uint64_t* const mine_out = a.ws_keys + ((size_t)q * nblk + blk) * K;
+    // ---- the workgroup's K best, ranked, straight to the workspace or the result
     auto id_of = [&](int slot) -> uint32_t {
         if (kTail && slot == R - 1) return total_units * IPV + (uint32_t)lane;
         return (first + (uint32_t)(slot / IPV) * stride) * IPV + (uint32_t)(slot % IPV);
     };
-    select_small_k<NT, R, STAMP>(sc, id_of, K, sel, tid, [&](int rank, uint64_t key) { mine_out[rank] = key; }, rec);
+    select_small_k<NT, R, STAMP>(sc, id_of, K, sel, tid, [&](int rank, uint64_t key) { emit_key(a, q, nblk, blk, rank, key); }, rec);
     stamp<STAMP>(rec, kStampEnd, lane);
 }

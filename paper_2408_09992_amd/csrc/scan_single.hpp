@@ -13,10 +13,23 @@ struct ScanArgs {
     int candmax;         // keys of the exact-selection candidate array
     int prune_at;        // wave list length that triggers a tightening (0: only when full)
     uint64_t* ws_keys;   // [B][nblk][K]
+    int* out_ids;        // [B][K]: the result, when one workgroup per query scans everything; nullptr: lists for the fold
+    float* out_scores;
     const int* subset;   // candidate list V (generic kernel only): unit p stands for item subset[p]; nullptr: V = I
     uint32_t n_items;    // items in the catalogue (bounds the ids read from `subset`)
     uint64_t* stamps;    // STAMP instances only: wall-clock stamps, kStampSlots per wave (slot names: StampSlot)
 };
+
+// Rank t of workgroup blk's K best for query q: to the result when there is no other list to fold it with, else to the
+// workspace.
+__device__ __forceinline__ void emit_key(const ScanArgs& a, int q, int nblk, int blk, int t, uint64_t key) {
+    if (a.out_ids != nullptr) {
+        a.out_ids[(size_t)q * a.K + t] = id_of_key(key);
+        a.out_scores[(size_t)q * a.K + t] = score_of_key(key);
+    } else {
+        a.ws_keys[((size_t)q * nblk + blk) * a.K + t] = key;
+    }
+}
 
 // Items a thread holds per round.  M > 0: an item's row of sub-ids takes M bytes (m sub-ids of one byte, or m / 2 of
 // two bytes) and one 16-byte vector carries 16/M items; M == 0: any row, one item per slot, row loads sized by the
@@ -620,7 +633,8 @@ __global__ __launch_bounds__(NT, 4) void scan_topk_kernel(ScanArgs a) {
         }
         if (!done) {
             if (ncand <= a.candmax) {
-                rank_select<NT>(L.cand, ncand, K, L.sorted, tid);
+                // (K < 32: few candidates; else the histogram's range covers them)
+                rank_select<NT>(L.cand, ncand, K, L.sorted, tid, K < kRegisterSelectMinK ? nullptr : L.hist, ctl->lo, ctl->scale);
                 done = true;
             } else {
                 __syncthreads();                                  // start over with the general path
@@ -733,7 +747,6 @@ __global__ __launch_bounds__(NT, 4) void scan_topk_kernel(ScanArgs a) {
     workgroup_select<NT>(L, ctl, top, K, a.cap, a.candmax, tid, wide_floor && K >= 32, hlo, hscale);
     }
     stamp<STAMP>(rec, kStampSelected, lane);
-    uint64_t* mine_out = a.ws_keys + ((size_t)q * nblk + blockIdx.x) * K;
-    for (int t = tid; t < K; t += NT) mine_out[t] = L.sorted[t];
+    for (int t = tid; t < K; t += NT) emit_key(a, q, nblk, blk, t, L.sorted[t]);
     stamp<STAMP>(rec, kStampEnd, lane);
 }

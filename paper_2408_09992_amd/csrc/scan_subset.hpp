@@ -86,8 +86,7 @@ __global__ __launch_bounds__(NT) void scan_subset_kernel(ScanArgs a) {
         }
     }
 
-    // ---- the workgroup's K best, ranked, straight to the workspace
-    uint64_t* const mine_out = a.ws_keys + ((size_t)q * nblk + blk) * K;
+    // ---- the workgroup's K best, ranked, straight to the workspace or the result
     select_small_k<NT, R>(sc, [&](int slot) -> uint32_t { return item[slot]; }, K, sel, tid,
-                          [&](int rank, uint64_t key) { mine_out[rank] = key; });
+                          [&](int rank, uint64_t key) { emit_key(a, q, nblk, blk, rank, key); });
 }

@@ -273,13 +273,95 @@ __device__ __forceinline__ void wave_rank_select(uint64_t* c, int T, int K, uint
     wave_sync();
 }
 
-// Sorted exact K best of the C candidates in cand[] by counting: the position of a key is the number of candidates
-// that beat it.  cand must have room for C rounded up to a multiple of 8 (the pad is zeroed here; a zero beats
-// nothing).  dst[0..K) is zero-filled where fewer than K exist.  When the workgroup has four threads per candidate,
-// four adjacent lanes share a key and each counts over a quarter of the candidates: the loop is bound by the latency
-// of its LDS reads, so a shorter loop per thread is what makes it faster.
+// Sorts the C keys of cand[] (LDS), best first, by buckets: a histogram over [lo, lo + kBins / scale) gives every bucket its
+// place, and within a bucket (a key or two, when the range fits) a key's place is the number of keys of the bucket that beat
+// it.  C <= R * NT.  False, with the keys in any order, when a bucket holds too many (ties, a range that does not fit).
+template <int NT, int R>
+__device__ bool bucket_sort(uint64_t* cand, int C, float lo, float scale, uint32_t* hist, int tid) {
+    constexpr uint32_t kMost = 64;                            // keys of a bucket at most
+    __shared__ int crowded;
+    __syncthreads();
+    for (int i = tid; i < kBins; i += NT) hist[i] = 0;
+    if (tid == 0) crowded = 0;
+    uint64_t key[R];
+    uint32_t bin[R], at[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) key[r] = r * NT + tid < C ? cand[r * NT + tid] : 0ull;
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        bin[r] = at[r] = 0;
+        if (r * NT + tid < C) {
+            bin[r] = key[r] != 0ull ? (uint32_t)bucket_of(score_of_key(key[r]), lo, scale) : 0u;
+            at[r] = atomicAdd(&hist[bin[r]], 1u);
+            if (at[r] >= kMost) crowded = 1;
+        }
+    }
+    __syncthreads();
+    if (crowded) return false;
+    if (tid < kWave) {                                        // every bucket's first place; the best buckets come first
+        constexpr int per = kBins / kWave;
+        const int first = kBins - per * (tid + 1);            // lane 0 owns the top ones
+        uint32_t c[per], mine = 0;
+#pragma unroll
+        for (int i = 0; i < per; i += 4) {
+            const uint4 v = *reinterpret_cast<const uint4*>(hist + first + i);
+            c[i] = v.x; c[i + 1] = v.y; c[i + 2] = v.z; c[i + 3] = v.w;
+            mine += v.x + v.y + v.z + v.w;
+        }
+        uint32_t before = wave_prefix_sum(mine) - mine;
+#pragma unroll
+        for (int i = per - 1; i >= 0; --i) {                  // (count and place in one word: both are below 2^16)
+            const uint32_t n = c[i];
+            c[i] = (before << 16) | n;
+            before += n;
+        }
+#pragma unroll
+        for (int i = 0; i < per; i += 4) *reinterpret_cast<uint4*>(hist + first + i) = make_uint4(c[i], c[i + 1], c[i + 2], c[i + 3]);
+    }
+    __syncthreads();
+    uint32_t place[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        place[r] = hist[bin[r]];
+        if (r * NT + tid < C) cand[(place[r] >> 16) + at[r]] = key[r];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const uint32_t n = place[r] & 0xFFFFu, first = place[r] >> 16;
+        at[r] = first;
+        if (r * NT + tid < C && n > 1)
+            for (uint32_t u = 0; u < n; ++u) at[r] += cand[first + u] > key[r];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+        if (r * NT + tid < C) cand[at[r]] = key[r];
+    __syncthreads();
+    return true;
+}
+
+// Sorted exact K best of the C candidates in cand[] (distinct, nonzero): by counting (the position of a key is the number of
+// candidates that beat it) while they are few, by buckets when there is a range for them (hist, lo, scale), else by sorting.
+// cand must have room for C rounded up to a multiple of 8 (the pad is zeroed here; a zero beats nothing), and for the next
+// power of two above kRankByCount.  dst[0..K) is zero-filled where fewer than K exist.  When the workgroup has four threads
+// per candidate, four adjacent lanes share a key and each counts over a quarter of the candidates: the loop is bound by the
+// latency of its LDS reads, so a shorter loop per thread is what makes it faster.
 template <int NT = kThreads>
-__device__ void rank_select(uint64_t* cand, int C, int K, uint64_t* dst, int tid) {
+__device__ void rank_select(uint64_t* cand, int C, int K, uint64_t* dst, int tid, uint32_t* hist = nullptr, float lo = 0.0f,
+                            float scale = 0.0f) {
+    constexpr int R = 2048 / NT;
+    if (C > (hist != nullptr ? kRankByCount : kRankBySort)) {
+        if (hist == nullptr || C > R * NT || !bucket_sort<NT, R>(cand, C, lo, scale, hist, tid)) {
+            const int n = pow2_at_least(C);
+            for (int i = C + tid; i < n; i += NT) cand[i] = 0;
+            block_sort_desc<NT>(cand, n, tid);
+        }
+        for (int i = tid; i < K; i += NT) dst[i] = i < C ? cand[i] : 0ull;
+        __syncthreads();
+        return;
+    }
     const int C8 = (C + 7) & ~7;
     for (int i = tid; i < K; i += NT) dst[i] = 0;
     if (tid < C8 - C) cand[C + tid] = 0;
@@ -344,7 +426,7 @@ __device__ void block_select(uint64_t* src, int n, int K, uint64_t* dst, uint64_
     __syncthreads();
     const int C = ctl->ncand;
     if (C <= candmax) {
-        rank_select<NT>(cand, C, K, dst, tid);
+        rank_select<NT>(cand, C, K, dst, tid, hist, lo, scale);
     } else {
         bitonic_sort_desc<true>(src, n, tid, NT);
         for (int i = tid; i < K; i += NT) dst[i] = src[i];
