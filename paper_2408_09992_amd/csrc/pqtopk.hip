@@ -849,16 +849,24 @@ bool launch_subitem_mfma(const float* queries, const float* centroids, float* S,
     return true;
 }
 
+constexpr int kSubBatchMin = 3;            // batch from which the interleaved kernel beats one query after the other
+
 template <int S_ELEMS>
 void launch_subitem(const float* queries, const float* centroids, float* S, int B, int d, int m, int b, hipStream_t st) {
-    if constexpr (S_ELEMS % 4 == 0) {
-        // batches, and any sub-dimension that is a multiple of 4 without an unrolled instance (96, 128, ...): the
-        // interleaved kernel (it needs 16-byte aligned rows of queries and centroids)
-        const bool rows_aligned = (((uintptr_t)queries | (uintptr_t)centroids) & 15) == 0 && d % 4 == 0 && (d / m) % 4 == 0;
-        if ((B >= kSubInterleave || S_ELEMS == 0) && rows_aligned) {
+    const bool rows_aligned = (((uintptr_t)queries | (uintptr_t)centroids) & 15) == 0 && d % 4 == 0 && (d / m) % 4 == 0;
+    if constexpr (S_ELEMS % 4 == 0 && S_ELEMS > 0) {
+        if (B >= kSubBatchMin && rows_aligned) {
+            const int waves = B < kSubBatchTile ? (B + kSubInterleave - 1) / kSubInterleave : kSubBatchTile / kSubInterleave;
             dim3 grid(m * ((b + kSubThreads - 1) / kSubThreads), (B + kSubBatchTile - 1) / kSubBatchTile);
-            hipLaunchKernelGGL(subitem_scores_batched_kernel<S_ELEMS>, grid, dim3(kSubThreads), 0, st, queries, centroids, S,
+            hipLaunchKernelGGL(subitem_scores_batched_kernel<S_ELEMS>, grid, dim3(kSubThreads * waves), 0, st, queries, centroids, S,
                                B, d, m, b);
+            return;
+        }
+    }
+    if constexpr (S_ELEMS == 0) {
+        if (rows_aligned) {
+            dim3 grid(m * ((b + kSubThreads - 1) / kSubThreads), (B + kSubAnyTile - 1) / kSubAnyTile);
+            hipLaunchKernelGGL(subitem_scores_any_kernel<kSubAnyTile>, grid, dim3(kSubThreads), 0, st, queries, centroids, S, B, d, m, b);
             return;
         }
     }
@@ -914,6 +922,7 @@ int pq_subitem_scores(const float* queries, const float* centroids, float* S, in
         case 16: launch_subitem<16>(queries, centroids, S, B, d, m, b, st); break;
         case 32: launch_subitem<32>(queries, centroids, S, B, d, m, b, st); break;
         case 64: launch_subitem<64>(queries, centroids, S, B, d, m, b, st); break;
+        case 128: launch_subitem<128>(queries, centroids, S, B, d, m, b, st); break;
         default: launch_subitem<0>(queries, centroids, S, B, d, m, b, st); break;
     }
     return record_hip(hipGetLastError());

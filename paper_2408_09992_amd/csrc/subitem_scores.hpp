@@ -81,52 +81,102 @@ __global__ __launch_bounds__(kSubThreads) void subitem_scores_kernel(const float
     }
 }
 
-// Eq. 4 for batches.  A workgroup (one wave) serves 64 sub-ids of ONE split and a tile of queries, so the query
-// chunk it multiplies with is the same for all its lanes (read through the scalar cache), and it runs the chains of
-// kSubInterleave queries side by side: the chains are independent, which hides the latency of each chain's
-// dependent multiply-adds.  Per query the arithmetic is the same left-to-right chain from +0 as above.
-constexpr int kSubInterleave = 8;     // queries whose chains run interleaved
-constexpr int kSubBatchTile = 8;      // queries per workgroup
+// Eq. 4 for batches.  A workgroup serves 64 sub-ids of ONE split and up to kSubBatchTile queries, kSubInterleave of them per
+// wave, whose chains run side by side (independent chains hide the latency of each chain's dependent multiply-adds).  Per
+// query the arithmetic is the same left-to-right chain from +0 as above.
+// What bounds it is latency: one round trip to memory, then some 256 multiply-adds per lane.  So everything is asked for at
+// once, in whole cache lines: the 64 sub-item embeddings (consecutive memory) and the queries' chunks go to LDS; a lane's row
+// is read from there (rows padded by 16 bytes: conflict-free), a query's chunk by all lanes at once.  Read straight from
+// memory, row by row, every load of a lane's row touched 64 cache lines, and the queries' chunks came four elements at a time.
+constexpr int kSubInterleave = 4;     // queries whose chains run interleaved in a wave
+constexpr int kSubBatchTile = 16;     // queries per workgroup
 
-template <int S_ELEMS>   // d/m (a multiple of 4) when it is one of the unrolled sizes, else 0: d/m (a multiple of 4) at run time
-__global__ __launch_bounds__(kSubThreads) void subitem_scores_batched_kernel(const float* __restrict__ queries,
-                                                                             const float* __restrict__ centroids,
-                                                                             float* __restrict__ S, int B, int d, int m, int b) {
-    const int s = S_ELEMS ? S_ELEMS : d / m;
+template <int S_ELEMS>   // d/m, a multiple of 4; rows of queries and centroids 16-byte aligned
+__global__ __launch_bounds__(kSubThreads * (kSubBatchTile / kSubInterleave)) void subitem_scores_batched_kernel(
+    const float* __restrict__ queries, const float* __restrict__ centroids, float* __restrict__ S, int B, int d, int m, int b) {
+    constexpr int PPR = S_ELEMS / 4, kRow = S_ELEMS + 4;             // 16-byte pieces per row, floats from row to row in LDS
+    __shared__ __align__(16) float rows[kSubThreads * kRow];
+    __shared__ __align__(16) float phi[kSubBatchTile * S_ELEMS];
+    const int nt = blockDim.x, tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+    const int jblocks = (b + kSubThreads - 1) / kSubThreads;
+    const int k = blockIdx.x / jblocks, j0 = (blockIdx.x % jblocks) * kSubThreads;
+    const int q0 = blockIdx.y * kSubBatchTile;
+    const int nq = B - q0 < kSubBatchTile ? B - q0 : kSubBatchTile;
+    const float4* psi4 = reinterpret_cast<const float4*>(centroids + ((size_t)k * b + j0) * S_ELEMS);
+    const int live_rows = b - j0 < kSubThreads ? b - j0 : kSubThreads;
+#pragma unroll 4
+    for (int p = tid; p < nq * PPR; p += nt)
+        *reinterpret_cast<float4*>(&phi[4 * p]) =
+            *reinterpret_cast<const float4*>(queries + (size_t)(q0 + p / PPR) * d + (size_t)k * S_ELEMS + 4 * (p % PPR));
+#pragma unroll 8
+    for (int p = tid; p < live_rows * PPR; p += nt) *reinterpret_cast<float4*>(&rows[(p / PPR) * kRow + 4 * (p % PPR)]) = psi4[p];
+    __syncthreads();
+    const int first = wave * kSubInterleave;
+    if (first >= nq || lane >= live_rows) return;
+    float acc[kSubInterleave];
+#pragma unroll
+    for (int i = 0; i < kSubInterleave; ++i) acc[i] = 0.0f;
+    const float* mine = &rows[lane * kRow];
+    const float* chunk[kSubInterleave];
+#pragma unroll
+    for (int i = 0; i < kSubInterleave; ++i) chunk[i] = &phi[(first + i < nq ? first + i : nq - 1) * S_ELEMS];   // (past the tile: a repeat, not stored)
+#pragma unroll 4
+    for (int t = 0; t < S_ELEMS; t += 4) {
+        const float4 wv = *reinterpret_cast<const float4*>(mine + t);
+#pragma unroll
+        for (int i = 0; i < kSubInterleave; ++i) {
+            const float4 pv = *reinterpret_cast<const float4*>(chunk[i] + t);
+            acc[i] = __builtin_fmaf(wv.x, pv.x, acc[i]);
+            acc[i] = __builtin_fmaf(wv.y, pv.y, acc[i]);
+            acc[i] = __builtin_fmaf(wv.z, pv.z, acc[i]);
+            acc[i] = __builtin_fmaf(wv.w, pv.w, acc[i]);
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < kSubInterleave; ++i)
+        if (first + i < nq) S[((size_t)(q0 + first + i) * m + k) * b + j0 + lane] = acc[i];
+}
+
+// Eq. 4 for any d/m that is a multiple of 4 without an instance above (96, 192, ...): a wave serves 64 sub-ids of one split and
+// the chains of eight queries, everything read where it lies.
+constexpr int kSubAnyTile = 8;
+template <int kTile>
+__global__ __launch_bounds__(kSubThreads) void subitem_scores_any_kernel(const float* __restrict__ queries,
+                                                                         const float* __restrict__ centroids,
+                                                                         float* __restrict__ S, int B, int d, int m, int b) {
+    const int s = d / m;
     const int jblocks = (b + kSubThreads - 1) / kSubThreads;
     const int k = blockIdx.x / jblocks;                              // the same for the whole workgroup
     const int j = (blockIdx.x % jblocks) * kSubThreads + threadIdx.x;
     const bool live = j < b;
     const int kj = k * b + (live ? j : 0);
     const float4* psi4 = reinterpret_cast<const float4*>(centroids + (size_t)kj * s);
-    const int q0 = blockIdx.y * kSubBatchTile;
-    int q1 = q0 + kSubBatchTile;
+    const int q0 = blockIdx.y * kTile;
+    int q1 = q0 + kTile;
     if (q1 > B) q1 = B;
-    for (int q = q0; q < q1; q += kSubInterleave) {
-        const float4* phi4[kSubInterleave];
-        float acc[kSubInterleave];
+    const float4* phi4[kTile];
+    float acc[kTile];
 #pragma unroll
-        for (int i = 0; i < kSubInterleave; ++i) {
-            const int qi = (q + i < q1) ? q + i : q1 - 1;            // past the tile: a repeat, computed and not stored
-            phi4[i] = reinterpret_cast<const float4*>(queries + (size_t)qi * d + (size_t)k * s);
-            acc[i] = 0.0f;
-        }
-#pragma unroll 4
-        for (int t4 = 0; t4 < s / 4; ++t4) {                         // four elements of every chain per step
-            const float4 wv = psi4[t4];
-#pragma unroll
-            for (int i = 0; i < kSubInterleave; ++i) {
-                const float4 pv = phi4[i][t4];
-                acc[i] = __builtin_fmaf(wv.x, pv.x, acc[i]);
-                acc[i] = __builtin_fmaf(wv.y, pv.y, acc[i]);
-                acc[i] = __builtin_fmaf(wv.z, pv.z, acc[i]);
-                acc[i] = __builtin_fmaf(wv.w, pv.w, acc[i]);
-            }
-        }
-#pragma unroll
-        for (int i = 0; i < kSubInterleave; ++i)
-            if (live && q + i < q1) S[(size_t)(q + i) * m * b + kj] = acc[i];
+    for (int i = 0; i < kTile; ++i) {
+        const int qi = (q0 + i < q1) ? q0 + i : q1 - 1;              // past the tile: a repeat, computed and not stored
+        phi4[i] = reinterpret_cast<const float4*>(queries + (size_t)qi * d + (size_t)k * s);
+        acc[i] = 0.0f;
     }
+#pragma unroll 4
+    for (int t4 = 0; t4 < s / 4; ++t4) {                             // four elements of every chain per step
+        const float4 wv = psi4[t4];
+#pragma unroll
+        for (int i = 0; i < kTile; ++i) {
+            const float4 pv = phi4[i][t4];
+            acc[i] = __builtin_fmaf(wv.x, pv.x, acc[i]);
+            acc[i] = __builtin_fmaf(wv.y, pv.y, acc[i]);
+            acc[i] = __builtin_fmaf(wv.z, pv.z, acc[i]);
+            acc[i] = __builtin_fmaf(wv.w, pv.w, acc[i]);
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < kTile; ++i)
+        if (live && q0 + i < q1) S[(size_t)(q0 + i) * m * b + kj] = acc[i];
 }
 
 // Eq. 4 on the matrix cores, for batches.  Per split, S_k = Phi_k Psi_k^T is a [B x d/m] x [d/m x b] product, and
