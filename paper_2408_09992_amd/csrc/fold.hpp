@@ -178,13 +178,14 @@ __global__ __launch_bounds__(NT) void fold_lists_kernel(FoldArgs a) {
 // latency (a few thousand keys): its time is the two dependent memory round trips it cannot avoid (arguments, keys)
 // plus its instruction count, and this one has a fifth of the general fold's instructions and a sixth of its barriers.
 template <int NT, int R, bool STAMP = false>
-__global__ __launch_bounds__(NT) void fold_small_kernel(FoldArgs a) {
+__global__ __launch_bounds__(NT) void fold_small_kernel(const uint64_t* ws_keys, int* result_ids, float* result_scores, int nlists, int K,
+                                                        uint64_t* stamps) {
     __shared__ SmallSelectLds<NT> sel;
-    const int tid = threadIdx.x, lane = tid & (kWave - 1), q = blockIdx.y, K = a.K;
-    uint64_t* const rec = STAMP ? a.stamps + ((size_t)q * (NT / kWave) + tid / kWave) * kStampSlots : nullptr;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), q = blockIdx.y;
+    uint64_t* const rec = STAMP ? stamps + ((size_t)q * (NT / kWave) + tid / kWave) * kStampSlots : nullptr;
     stamp<STAMP>(rec, kStampEntry, lane);
-    const int nkeys = a.nlists * K;
-    const uint64_t* all = a.ws_keys + (size_t)q * nkeys;
+    const int nkeys = nlists * K;
+    const uint64_t* all = ws_keys + (size_t)q * nkeys;
     uint64_t keys[R];
 #pragma unroll
     for (int r = 0; r < R; ++r) {
@@ -197,8 +198,8 @@ __global__ __launch_bounds__(NT) void fold_small_kernel(FoldArgs a) {
 #pragma unroll
     for (int r = 0; r < R; ++r) sc[r] = keys[r] != 0ull ? score_of_key(keys[r]) : empty_score();
     stamp<STAMP>(rec, kStampLoaded, lane);
-    int* const out_ids = a.out_ids + (size_t)q * K;
-    float* const out_scores = a.out_scores + (size_t)q * K;
+    int* const out_ids = result_ids + (size_t)q * K;
+    float* const out_scores = result_scores + (size_t)q * K;
     select_small_k<NT, R, STAMP>(sc, [&](int slot) -> uint32_t { return (uint32_t)id_of_key(keys[slot]); }, K, sel, tid,
                                  [&](int rank, uint64_t key) {
                                      out_ids[rank] = id_of_key(key);

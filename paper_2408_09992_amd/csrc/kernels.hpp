@@ -96,11 +96,11 @@ namespace pqk {
 #define PQ_SCAN_EXTERN(M, C, NT, CW, GL) extern PQ_SCAN_DEFINE(M, C, NT, CW, GL)
 #define PQ_SCAN_DEFINE6(M, C, NT, CW, GL, ST) template __global__ void scan_topk_kernel<M, C, NT, CW, GL, ST>(ScanArgs);
 #define PQ_SCAN_EXTERN6(M, C, NT, CW, GL, ST) extern PQ_SCAN_DEFINE6(M, C, NT, CW, GL, ST)
-#define PQ_SHORT_DEFINE(M, U, NT, ST) template __global__ void scan_short_kernel<M, U, NT, ST>(ScanArgs);
+#define PQ_SHORT_DEFINE(M, U, NT, ST) template __global__ void scan_short_kernel<M, U, NT, ST>(const uint8_t*, const float*, void*, float*, uint32_t, int, int, uint64_t*);
 #define PQ_SHORT_EXTERN(M, U, NT, ST) extern PQ_SHORT_DEFINE(M, U, NT, ST)
-#define PQ_SHORT16_DEFINE(M, U, NT, ST, CW) template __global__ void scan_short_kernel<M, U, NT, ST, CW>(ScanArgs);
+#define PQ_SHORT16_DEFINE(M, U, NT, ST, CW) template __global__ void scan_short_kernel<M, U, NT, ST, CW>(const uint8_t*, const float*, void*, float*, uint32_t, int, int, uint64_t*);
 #define PQ_SHORT16_EXTERN(M, U, NT, ST, CW) extern PQ_SHORT16_DEFINE(M, U, NT, ST, CW)
-#define PQ_SUBSET_DEFINE(M, U, NT) template __global__ void scan_subset_kernel<M, U, NT>(ScanArgs);
+#define PQ_SUBSET_DEFINE(M, U, NT) template __global__ void scan_subset_kernel<M, U, NT>(const uint8_t*, const int*, const float*, void*, float*, uint32_t, uint32_t, int, int);
 #define PQ_SUBSET_EXTERN(M, U, NT) extern PQ_SUBSET_DEFINE(M, U, NT)
 #define PQ_FILTER_DEFINE(M, CW, W, W16, SUB, FINE) template __global__ void scan_filter_kernel<M, CW, W, W16, SUB, FINE>(FilterArgs);
 #define PQ_FILTER_EXTERN(M, CW, W, W16, SUB, FINE) extern PQ_FILTER_DEFINE(M, CW, W, W16, SUB, FINE)

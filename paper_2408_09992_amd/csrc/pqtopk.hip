@@ -34,6 +34,7 @@
 
 #include <atomic>
 #include <mutex>
+#include <tuple>
 
 #include "pqtopk.h"
 #include "pqtopk_measure.h"
@@ -59,6 +60,7 @@ std::atomic<int> g_force_general{0};
 
 int record_hip(hipError_t e) {
     if (e == hipSuccess) return PQ_OK;
+    (void)hipGetLastError();                                 // (reported here: not a second time by whoever asks next)
     strncpy(g_hip_error, hipGetErrorString(e), sizeof(g_hip_error) - 1);
     g_hip_error[sizeof(g_hip_error) - 1] = 0;
     return PQ_ERR_HIP;
@@ -497,39 +499,52 @@ hipError_t allow_lds(KernelT kernel, size_t bytes) {
     return allow_lds_once(reinterpret_cast<const void*>(kernel), bytes);
 }
 
+// Enqueue a kernel with its arguments.  (hipLaunchKernelGGL passes the configuration through two more runtime calls and the
+// error through a third: 0.15 us of a launch's 3.)
+template <typename... P, typename... A>
+hipError_t launch(void (*kernel)(P...), dim3 grid, int threads, size_t dyn_lds, hipStream_t st, A... args) {
+    std::tuple<P...> values(static_cast<P>(args)...);
+    return std::apply([&](P&... v) {
+        void* ptrs[] = {const_cast<void*>(static_cast<const void*>(&v))...};
+        return hipLaunchKernel(reinterpret_cast<const void*>(kernel), grid, dim3((unsigned)threads), ptrs, dyn_lds, st);
+    }, values);
+}
+
 template <int M, int CW = 1>
 hipError_t launch_scan(const ScanPlan& p, const ScanArgs& a, int B, hipStream_t st) {
     if constexpr (CW == 1 && M >= 1 && M <= 8) {
         if (p.copies == kTableCopies) {
             hipError_t e = allow_lds(scan_topk_kernel<M, kTableCopies, kBigThreads>, p.scan_dyn_lds);
             if (e != hipSuccess) return e;
-            hipLaunchKernelGGL((scan_topk_kernel<M, kTableCopies, kBigThreads>), dim3(p.nblk, B), dim3(kBigThreads),
-                               p.scan_dyn_lds, st, a);
-            return hipGetLastError();
+            return launch(scan_topk_kernel<M, kTableCopies, kBigThreads>, dim3(p.nblk, B), kBigThreads, p.scan_dyn_lds, st, a);
         }
     }
     if constexpr (CW == 2) {
         if (p.glut) {
             hipError_t e = allow_lds(scan_topk_kernel<M, 1, kThreads, 2, true>, p.scan_dyn_lds);
             if (e != hipSuccess) return e;
-            hipLaunchKernelGGL((scan_topk_kernel<M, 1, kThreads, 2, true>), dim3(p.nblk, B), dim3(kThreads), p.scan_dyn_lds,
-                               st, a);
-            return hipGetLastError();
+            return launch(scan_topk_kernel<M, 1, kThreads, 2, true>, dim3(p.nblk, B), kThreads, p.scan_dyn_lds, st, a);
         }
     }
     if constexpr (M == 0 || M == 64 || CW == 2) {
         if (p.big) {
             hipError_t e = allow_lds(scan_topk_kernel<M, 1, kBigThreads, CW>, p.scan_dyn_lds);
             if (e != hipSuccess) return e;
-            hipLaunchKernelGGL((scan_topk_kernel<M, 1, kBigThreads, CW>), dim3(p.nblk, B), dim3(kBigThreads),
-                               p.scan_dyn_lds, st, a);
-            return hipGetLastError();
+            return launch(scan_topk_kernel<M, 1, kBigThreads, CW>, dim3(p.nblk, B), kBigThreads, p.scan_dyn_lds, st, a);
         }
     }
     hipError_t e = allow_lds(scan_topk_kernel<M, 1, kThreads, CW>, p.scan_dyn_lds);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((scan_topk_kernel<M, 1, kThreads, CW>), dim3(p.nblk, B), dim3(kThreads), p.scan_dyn_lds, st, a);
-    return hipGetLastError();
+    return launch(scan_topk_kernel<M, 1, kThreads, CW>, dim3(p.nblk, B), kThreads, p.scan_dyn_lds, st, a);
+}
+
+// Where a lean kernel's K best go: the result's ids (and scores), or the workspace's lists (scores: nullptr).
+void* out_of(const ScanArgs& a) { return a.out_ids != nullptr ? static_cast<void*>(a.out_ids) : static_cast<void*>(a.ws_keys); }
+float* scores_of(const ScanArgs& a) { return a.out_ids != nullptr ? a.out_scores : nullptr; }
+
+template <typename KernelT>
+hipError_t launch_short_args(KernelT kernel, const ScanPlan& p, const ScanArgs& a, int B, hipStream_t st) {
+    return launch(kernel, dim3(p.nblk, B), kThreads, p.scan_dyn_lds, st, a.codes, a.S, out_of(a), scores_of(a), (uint32_t)a.N, a.b, a.K, a.stamps);
 }
 
 template <int M, int U>
@@ -537,12 +552,10 @@ hipError_t launch_short_units(const ScanPlan& p, const ScanArgs& a, int B, hipSt
     if constexpr (U <= short_max_units(M)) {
         if constexpr (M == 8) {
             if (a.stamps != nullptr) {
-                hipLaunchKernelGGL((scan_short_kernel<M, U, kThreads, true>), dim3(p.nblk, B), dim3(kThreads), 0, st, a);
-                return hipGetLastError();
+                return launch_short_args(scan_short_kernel<M, U, kThreads, true>, p, a, B, st);
             }
         }
-        hipLaunchKernelGGL((scan_short_kernel<M, U, kThreads, false>), dim3(p.nblk, B), dim3(kThreads), 0, st, a);
-        return hipGetLastError();
+        return launch_short_args(scan_short_kernel<M, U, kThreads, false>, p, a, B, st);
     } else {
         return hipErrorInvalidValue;                         // (the plan never asks for it)
     }
@@ -582,8 +595,7 @@ hipError_t launch_short16_units(const ScanPlan& p, const ScanArgs& a, int B, hip
     if constexpr (U <= short16_max_units(M)) {
         hipError_t e = allow_lds(scan_short_kernel<M, U, kThreads, false, 2>, p.scan_dyn_lds);
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL((scan_short_kernel<M, U, kThreads, false, 2>), dim3(p.nblk, B), dim3(kThreads), p.scan_dyn_lds, st, a);
-        return hipGetLastError();
+        return launch_short_args(scan_short_kernel<M, U, kThreads, false, 2>, p, a, B, st);
     } else {
         return hipErrorInvalidValue;                         // (the plan never asks for it)
     }
@@ -610,8 +622,7 @@ hipError_t launch_short16_m(const ScanPlan& p, const ScanArgs& a, int B, hipStre
 template <int M>
 hipError_t launch_subset_m(const ScanPlan& p, const ScanArgs& a, int B, hipStream_t st) {
     auto go = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, dim3(p.nblk, B), dim3(kThreads), 0, st, a);
-        return hipGetLastError();
+        return launch(kernel, dim3(p.nblk, B), kThreads, 0, st, a.codes, a.subset, a.S, out_of(a), scores_of(a), (uint32_t)a.N, a.n_items, a.b, a.K);
     };
     switch (p.subset_vecs) {
         case 1: return go(scan_subset_kernel<M, 1, kThreads>);
@@ -631,12 +642,12 @@ hipError_t launch_filter(const ScanPlan& p, const FilterArgs& a, hipStream_t st)
     const size_t prep_lds = filter_prepare_lds_bytes(a.entries, M);
     hipError_t e = allow_lds(filter_prepare_kernel<M, CW, SUB>, prep_lds);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((filter_prepare_kernel<M, CW, SUB>), dim3(p.f_parts, a.B), dim3(kFilterThreads), prep_lds, st, a);
+    e = launch(filter_prepare_kernel<M, CW, SUB>, dim3(p.f_parts, a.B), kFilterThreads, prep_lds, st, a);
+    if (e != hipSuccess) return e;
     auto go = [&](auto kernel) {
         e = allow_lds(kernel, p.scan_dyn_lds);
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(kernel, dim3(p.nblk, (a.B + p.f_queries - 1) / p.f_queries), dim3(kFilterThreads), p.scan_dyn_lds, st, a);
-        return hipGetLastError();
+        return launch(kernel, dim3(p.nblk, (a.B + p.f_queries - 1) / p.f_queries), kFilterThreads, p.scan_dyn_lds, st, a);
     };
     if (a.stamps != nullptr) {
         if constexpr (M == 8 && CW == 1 && !W16 && !SUB) {
@@ -805,14 +816,11 @@ int enqueue_fold(const ScanPlan& p, int B, int K, void* workspace, int* out_ids,
         !(g_force_general.load(std::memory_order_relaxed) & 2)) {
         // small K, few keys: the lean fold
         const bool few = (long long)nlists * K <= (long long)kThreads * kFoldSmallRegs;
-        if (stamps != nullptr) {
-            if (few) hipLaunchKernelGGL((fold_small_kernel<kThreads, kFoldSmallRegs, true>), dim3(1, B), dim3(kThreads), 0, st, f);
-            else hipLaunchKernelGGL((fold_small_kernel<kThreads, kFoldSmallRegsMax, true>), dim3(1, B), dim3(kThreads), 0, st, f);
-        } else {
-            if (few) hipLaunchKernelGGL((fold_small_kernel<kThreads, kFoldSmallRegs, false>), dim3(1, B), dim3(kThreads), 0, st, f);
-            else hipLaunchKernelGGL((fold_small_kernel<kThreads, kFoldSmallRegsMax, false>), dim3(1, B), dim3(kThreads), 0, st, f);
-        }
-        return record_hip(hipGetLastError());
+        auto go = [&](auto kernel) {
+            return record_hip(launch(kernel, dim3(1, B), kThreads, 0, st, f.ws_keys, out_ids, out_scores, nlists, K, stamps));
+        };
+        if (stamps != nullptr) return few ? go(fold_small_kernel<kThreads, kFoldSmallRegs, true>) : go(fold_small_kernel<kThreads, kFoldSmallRegsMax, true>);
+        return few ? go(fold_small_kernel<kThreads, kFoldSmallRegs, false>) : go(fold_small_kernel<kThreads, kFoldSmallRegsMax, false>);
     }
     // (see fold_lists_kernel: a chunk holds 2.5 times a list's share of the K best, and the depth at which at most 60 % of
     // the lists have to reach the floor)
@@ -822,10 +830,9 @@ int enqueue_fold(const ScanPlan& p, int B, int K, void* workspace, int* out_ids,
     while (f.depth < f.chunk && f.depth < K && 10LL * ((K + f.depth - 1) / f.depth) > 6LL * nlists) ++f.depth;
     f.need = (K + f.depth - 1) / f.depth;
     if (nlists > kFoldLists || (long long)nlists * f.chunk > kFoldSlots) return PQ_ERR_UNSUPPORTED;   // (no plan makes that many)
-    if (stamps != nullptr) hipLaunchKernelGGL((fold_lists_kernel<kFoldThreads, true>), dim3(1, B), dim3(kFoldThreads), p.fold_lds, st, f);
-    else if (B < 64) hipLaunchKernelGGL((fold_lists_kernel<kFoldThreads>), dim3(1, B), dim3(kFoldThreads), p.fold_lds, st, f);
-    else hipLaunchKernelGGL((fold_lists_kernel<kFoldThreadsMany>), dim3(1, B), dim3(kFoldThreadsMany), p.fold_lds, st, f);
-    return record_hip(hipGetLastError());
+    if (stamps != nullptr) return record_hip(launch(fold_lists_kernel<kFoldThreads, true>, dim3(1, B), kFoldThreads, p.fold_lds, st, f));
+    if (B < 64) return record_hip(launch(fold_lists_kernel<kFoldThreads>, dim3(1, B), kFoldThreads, p.fold_lds, st, f));
+    return record_hip(launch(fold_lists_kernel<kFoldThreadsMany>, dim3(1, B), kFoldThreadsMany, p.fold_lds, st, f));
 }
 
 // Batch from which Eq. 4 runs on the matrix cores.  The scalar kernels are faster below: a wave's chain of d/m matrix
@@ -852,34 +859,29 @@ bool launch_subitem_mfma(const float* queries, const float* centroids, float* S,
 constexpr int kSubBatchMin = 3;            // batch from which the interleaved kernel beats one query after the other
 
 template <int S_ELEMS>
-void launch_subitem(const float* queries, const float* centroids, float* S, int B, int d, int m, int b, hipStream_t st) {
+hipError_t launch_subitem(const float* queries, const float* centroids, float* S, int B, int d, int m, int b, hipStream_t st) {
     const bool rows_aligned = (((uintptr_t)queries | (uintptr_t)centroids) & 15) == 0 && d % 4 == 0 && (d / m) % 4 == 0;
     if constexpr (S_ELEMS % 4 == 0 && S_ELEMS > 0) {
         if (B >= kSubBatchMin && rows_aligned) {
             const int waves = B < kSubBatchTile ? (B + kSubInterleave - 1) / kSubInterleave : kSubBatchTile / kSubInterleave;
             dim3 grid(m * ((b + kSubThreads - 1) / kSubThreads), (B + kSubBatchTile - 1) / kSubBatchTile);
-            hipLaunchKernelGGL(subitem_scores_batched_kernel<S_ELEMS>, grid, dim3(kSubThreads * waves), 0, st, queries, centroids, S,
-                               B, d, m, b);
-            return;
+            return launch(subitem_scores_batched_kernel<S_ELEMS>, grid, kSubThreads * waves, 0, st, queries, centroids, S, B, d, m, b);
         }
     }
     if constexpr (S_ELEMS == 0) {
         if (rows_aligned) {
             dim3 grid(m * ((b + kSubThreads - 1) / kSubThreads), (B + kSubAnyTile - 1) / kSubAnyTile);
-            hipLaunchKernelGGL(subitem_scores_any_kernel<kSubAnyTile>, grid, dim3(kSubThreads), 0, st, queries, centroids, S, B, d, m, b);
-            return;
+            return launch(subitem_scores_any_kernel<kSubAnyTile>, grid, kSubThreads, 0, st, queries, centroids, S, B, d, m, b);
         }
     }
     dim3 grid((m * b + kSubThreads - 1) / kSubThreads, (B + kSubQueryTile - 1) / kSubQueryTile);
     if constexpr (S_ELEMS != 0 && S_ELEMS % 4 == 0 && S_ELEMS <= 128) {
         // whole waves of 16-byte aligned rows: the wave reads its block of sub-item embeddings piece after piece
         if (((long long)m * b) % kSubThreads == 0 && ((uintptr_t)centroids & 15) == 0) {
-            hipLaunchKernelGGL((subitem_scores_kernel<S_ELEMS, false, true>), grid, dim3(kSubThreads), 0, st, queries, centroids, S,
-                               B, d, m, b, nullptr);
-            return;
+            return launch(subitem_scores_kernel<S_ELEMS, false, true>, grid, kSubThreads, 0, st, queries, centroids, S, B, d, m, b, nullptr);
         }
     }
-    hipLaunchKernelGGL(subitem_scores_kernel<S_ELEMS>, grid, dim3(kSubThreads), 0, st, queries, centroids, S, B, d, m, b);
+    return launch(subitem_scores_kernel<S_ELEMS>, grid, kSubThreads, 0, st, queries, centroids, S, B, d, m, b, nullptr);
 }
 
 // ---- the built-in scratch of pq_score_topk_static(): one array per GPU, held until the process ends
@@ -917,15 +919,14 @@ int pq_subitem_scores(const float* queries, const float* centroids, float* S, in
         launch_subitem_mfma(queries, centroids, S, B, d, m, b, (long long)m * b, st))
         return record_hip(hipGetLastError());
     switch (d / m) {
-        case 4: launch_subitem<4>(queries, centroids, S, B, d, m, b, st); break;
-        case 8: launch_subitem<8>(queries, centroids, S, B, d, m, b, st); break;
-        case 16: launch_subitem<16>(queries, centroids, S, B, d, m, b, st); break;
-        case 32: launch_subitem<32>(queries, centroids, S, B, d, m, b, st); break;
-        case 64: launch_subitem<64>(queries, centroids, S, B, d, m, b, st); break;
-        case 128: launch_subitem<128>(queries, centroids, S, B, d, m, b, st); break;
-        default: launch_subitem<0>(queries, centroids, S, B, d, m, b, st); break;
+        case 4: return record_hip(launch_subitem<4>(queries, centroids, S, B, d, m, b, st));
+        case 8: return record_hip(launch_subitem<8>(queries, centroids, S, B, d, m, b, st));
+        case 16: return record_hip(launch_subitem<16>(queries, centroids, S, B, d, m, b, st));
+        case 32: return record_hip(launch_subitem<32>(queries, centroids, S, B, d, m, b, st));
+        case 64: return record_hip(launch_subitem<64>(queries, centroids, S, B, d, m, b, st));
+        case 128: return record_hip(launch_subitem<128>(queries, centroids, S, B, d, m, b, st));
+        default: return record_hip(launch_subitem<0>(queries, centroids, S, B, d, m, b, st));
     }
-    return record_hip(hipGetLastError());
 }
 
 size_t pq_score_topk_workspace_bytes(long long N, int B, int m, int b, int K) {

@@ -24,8 +24,16 @@ __host__ __device__ constexpr int short16_max_units(int m) { return m == 16 ? 6 
 // microseconds of traffic), and a wave's latency is its instruction count: a kernel of its own, a few KB of code.
 //   M: splits; CW: bytes per sub-id.  An item's row takes P = M * CW bytes (1, 2, 4, 8, 16: 16 / P items per code vector;
 //   32, 64: P / 16 vectors per item).  CW = 2 (M = 4, 8, 16): the query's m x b table lies in dynamic LDS as in memory.
+// The arguments are plain values, not a struct: they fit the scalar registers the hardware loads before a wave starts
+// (amdgpu-kernarg-preload-count), and the kernel's first loads go out without a round trip for their addresses.
 template <int M, int U, int NT, bool STAMP = false, int CW = 1>
-__global__ __launch_bounds__(NT) void scan_short_kernel(ScanArgs a) {
+__global__ __launch_bounds__(NT) void scan_short_kernel(const uint8_t* codes, const float* S, void* out, float* out_scores, uint32_t N,
+                                                        int b, int K, uint64_t* stamps) {
+    ScanArgs a;                                               // (what the shared parts below expect; never in memory)
+    a.codes = codes; a.S = S; a.N = N; a.m = M; a.b = b; a.K = K;
+    // out_scores: with one workgroup per query `out` is the ids of the result; without, the workspace's lists
+    a.ws_keys = static_cast<uint64_t*>(out); a.out_ids = out_scores != nullptr ? static_cast<int*>(out) : nullptr;
+    a.out_scores = out_scores; a.stamps = stamps;
     constexpr int NW = NT / kWave;
     constexpr int P = M * CW;
     constexpr int VPU = Round<P>::kVPU, IPV = Round<P>::kIPV;  // vectors per unit, items per unit
@@ -38,7 +46,7 @@ __global__ __launch_bounds__(NT) void scan_short_kernel(ScanArgs a) {
     float* const lut = CW == 1 ? lut_static : reinterpret_cast<float*>(smem);
     __shared__ SmallSelectLds<NT> sel;
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
-    const int q = blockIdx.y, nblk = gridDim.x, blk = blockIdx.x, K = a.K, b = a.b;
+    const int q = blockIdx.y, nblk = gridDim.x, blk = blockIdx.x;
     uint64_t* const rec = STAMP ? a.stamps + (((size_t)q * nblk + blk) * NW + wave) * kStampSlots : nullptr;
     stamp<STAMP>(rec, kStampEntry, lane);
 

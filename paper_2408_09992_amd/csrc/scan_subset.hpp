@@ -19,7 +19,12 @@ constexpr int kSubsetMaxVecs = 8;
 //   M: bytes of an item's row (4, 8 or 16); U: code vectors' worth of rows per thread (1 .. kSubsetMaxVecs)
 // An id outside [0, n_items) is clamped to n_items - 1 (memory-safe; the result is then unspecified, as documented).
 template <int M, int U, int NT>
-__global__ __launch_bounds__(NT) void scan_subset_kernel(ScanArgs a) {
+__global__ __launch_bounds__(NT) void scan_subset_kernel(const uint8_t* codes, const int* subset, const float* S, void* out,
+                                                         float* out_scores, uint32_t N, uint32_t n_items, int b, int K) {
+    ScanArgs a;                                               // (plain arguments: see scan_short_kernel)
+    a.codes = codes; a.subset = subset; a.S = S; a.N = N; a.n_items = n_items; a.m = M; a.b = b; a.K = K;
+    a.ws_keys = static_cast<uint64_t*>(out); a.out_ids = out_scores != nullptr ? static_cast<int*>(out) : nullptr;
+    a.out_scores = out_scores;
     constexpr int IPV = 16 / M, WPI = M / 4;                   // candidates per code vector, 4-byte words per row
     constexpr int R = U * IPV;
     static_assert(M == 4 || M == 8 || M == 16, "rows of 4, 8 or 16 bytes");
@@ -27,7 +32,7 @@ __global__ __launch_bounds__(NT) void scan_subset_kernel(ScanArgs a) {
     __shared__ __align__(16) float lut[M * kLutStride];
     __shared__ SmallSelectLds<NT> sel;
     const int tid = threadIdx.x;
-    const int q = blockIdx.y, nblk = gridDim.x, blk = blockIdx.x, K = a.K, b = a.b;
+    const int q = blockIdx.y, nblk = gridDim.x, blk = blockIdx.x;
     const uint32_t n = (uint32_t)a.N;                          // candidates in the list
     const uint32_t first = (uint32_t)blk * NT + (uint32_t)tid, stride = (uint32_t)nblk * NT;
 
