@@ -8,7 +8,7 @@
 struct FoldArgs {
     const uint64_t* ws_keys;   // [B][nlists][K]: per query, nlists lists of K keys, sorted best first, zeros at the end
     int nlists, K;
-    int chunk, depth, need;    // fold_lists_kernel: see there
+    int chunk, depth, need, groups, group_mask;   // fold_lists_kernel: see there
     int* out_ids;              // [B][K]
     float* out_scores;
     uint64_t* stamps;          // STAMP instances only: wall-clock stamps, kStampSlots per wave
@@ -20,14 +20,16 @@ constexpr int kFoldSlots = 4096;                  // keys read at first: nlists 
 constexpr int kFoldLists = 1024;                  // lists per query at most
 constexpr int kFoldCand = 2048;                   // candidates ranked at most; more (heavy ties in few lists) take the slow path
 
-// Dynamic LDS: hist | ctl | stage (kFoldCand keys; first the lists' floor keys and the lists to read on in) | cand | sorted
+// Dynamic LDS: hist | ctl | stage (kFoldCand keys; first the groups' floor scores and the lists to read on in) | cand | sorted
 __host__ __device__ inline size_t fold_lds_bytes(int K) {
     return kBins * sizeof(uint32_t) + align16(sizeof(Ctl)) + 2 * (size_t)kFoldCand * sizeof(uint64_t) + align16((size_t)K * sizeof(uint64_t));
 }
 
 // The fold for any K.  grid = (1, B).  The lists are sorted, so few keys decide: `need` lists whose key number `depth` is at
 // least f hold need * depth >= K keys that are.  So the need-th largest of the lists' depth-th keys is a floor of the K-th
-// best, and only keys that reach it are ranked: about 1.3 K of them.  A list's first `chunk` keys are read at once (chunk
+// best, and only keys that reach it are ranked: about 1.3 K of them.  The floor is found by comparing every list's score with
+// every other's, so where far fewer lists are needed than there are, each of `groups` groups of lists puts forward its best
+// only (512 lists of K = 15: 15.2 us for the kernel, with 64 groups 5).  A list's first `chunk` keys are read at once (chunk
 // covers 2.5 times a list's share of the K best and the depth), lists that reach the floor with all of them are read on,
 // chunk after chunk.  One round trip to memory, usually; reading everything instead took two launches for 256 lists of
 // K = 100 (25,600 keys: sixteen folds of sixteen lists, then one: 12 us; this: 4 us).
@@ -36,13 +38,13 @@ __global__ __launch_bounds__(NT) void fold_lists_kernel(FoldArgs a) {
     constexpr int R = kFoldSlots / NT;
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ int n_cand, n_more[2];
-    __shared__ uint64_t floor_key;
+    __shared__ uint32_t floor_score;
     uint32_t* hist = reinterpret_cast<uint32_t*>(smem);
     Ctl* ctl = reinterpret_cast<Ctl*>(smem + kBins * sizeof(uint32_t));
     uint64_t* stage = reinterpret_cast<uint64_t*>(smem + kBins * sizeof(uint32_t) + align16(sizeof(Ctl)));
     uint64_t* cand = stage + kFoldCand;
     uint64_t* sorted = cand + kFoldCand;
-    uint64_t* heads = stage;                                  // [kFoldLists]
+    uint32_t* heads = reinterpret_cast<uint32_t*>(stage);     // [kFoldLists], ordered as the scores they stand for
     int* more[2] = {reinterpret_cast<int*>(stage + kFoldLists), reinterpret_cast<int*>(stage + kFoldLists) + kFoldLists};
     static_assert(2 * kFoldLists * sizeof(int) <= (kFoldCand - kFoldLists) * sizeof(uint64_t), "room for both lists of lists");
     const int tid = threadIdx.x, lane = tid & (kWave - 1), q = blockIdx.y, K = a.K, nlists = a.nlists;
@@ -61,29 +63,34 @@ __global__ __launch_bounds__(NT) void fold_lists_kernel(FoldArgs a) {
         const int i = r * NT + tid, list = i >> cshift, pos = i & (a.chunk - 1);
         keys[r] = (list < nlists && pos < K) ? all[(size_t)list * K + pos] : 0ull;
     }
-    if (tid == 0) { n_cand = 0; n_more[0] = n_more[1] = 0; floor_key = 1ull; }   // (every key is at least 1)
+    if (tid == 0) { n_cand = 0; n_more[0] = n_more[1] = 0; floor_score = 0xFFFFFFFFu; }
+    for (int g = tid; g < a.groups; g += NT) heads[g] = 0u;
+    __syncthreads();                                          // (while the keys are under way)
 #pragma unroll
     for (int r = 0; r < R; ++r) {
         const int i = r * NT + tid, list = i >> cshift, pos = i & (a.chunk - 1);
-        if (list < nlists && pos == a.depth - 1) heads[list] = keys[r];
+        if (list < nlists && pos == a.depth - 1) atomicMax(&heads[list & a.group_mask], (uint32_t)(keys[r] >> 32));
     }
     __syncthreads();
     stamp<STAMP>(rec, kStampLoaded, lane);
 
-    // ---- the need-th largest of the lists' depth-th keys: the one that need - 1 others beat (keys are distinct; fewer than
-    // `need` lists that long: no floor)
-    for (int part_of = tid; part_of < nlists * 4; part_of += NT) {   // four lanes per list, each over a quarter of the others
-        const int l = part_of >> 2, part = part_of & 3;
-        const uint64_t mine = heads[l];
+    // ---- the need-th largest of the groups' scores: the smallest that fewer than `need` others beat (not that many lists so
+    // long: zero, no floor)
+    for (int part_of = tid; part_of < a.groups * 4; part_of += NT) {   // four lanes per group, each over a quarter of the others
+        const int part = part_of & 3;
+        const uint32_t mine = heads[part_of >> 2];
         uint32_t rank = 0;
-        for (int u = part; u < nlists; u += 4) rank += heads[u] > mine;
+        for (int u = part * 4; u < a.groups; u += 16) {
+            const uint4 others = *reinterpret_cast<const uint4*>(heads + u);
+            rank += (others.x > mine) + (others.y > mine) + (others.z > mine) + (others.w > mine);
+        }
         rank += dpp_u32<kDppQuadSwap1>(0u, rank);
         rank += dpp_u32<kDppQuadSwap2>(0u, rank);
-        if (part == 0 && mine != 0ull && rank == (uint32_t)a.need - 1u) floor_key = mine;
+        if (part == 0 && rank < (uint32_t)a.need) atomicMin(&floor_score, mine);
     }
     __syncthreads();
     stamp<STAMP>(rec, kStampCut, lane);
-    const uint64_t f = floor_key;
+    const uint64_t f = floor_score != 0u ? (uint64_t)floor_score << 32 : 1ull;   // (every key is at least 1)
 
     // ---- what reaches it
     auto take = [&](uint64_t key) {

@@ -809,7 +809,7 @@ int enqueue_fold(const ScanPlan& p, int B, int K, void* workspace, int* out_ids,
     FoldArgs f;
     f.ws_keys = static_cast<const uint64_t*>(workspace);
     f.nlists = nlists; f.K = K;
-    f.chunk = f.depth = f.need = 0;
+    f.chunk = f.depth = f.need = f.groups = f.group_mask = 0;
     f.out_ids = out_ids; f.out_scores = out_scores;
     f.stamps = stamps;
     if (K <= kSmallKMax && (long long)nlists * K <= (long long)kThreads * kFoldSmallRegsMax &&
@@ -829,6 +829,14 @@ int enqueue_fold(const ScanPlan& p, int B, int K, void* workspace, int* out_ids,
     f.depth = 1;
     while (f.depth < f.chunk && f.depth < K && 10LL * ((K + f.depth - 1) / f.depth) > 6LL * nlists) ++f.depth;
     f.need = (K + f.depth - 1) / f.depth;
+    // (groups: at least four times as many as have to reach the floor, so that 15 % more keys at most pass it)
+    f.groups = 64;
+    while (f.groups < 4 * f.need) f.groups *= 2;
+    f.group_mask = f.groups - 1;
+    if (f.groups >= nlists) {
+        f.groups = (nlists + 15) & ~15;
+        f.group_mask = kFoldLists - 1;
+    }
     if (nlists > kFoldLists || (long long)nlists * f.chunk > kFoldSlots) return PQ_ERR_UNSUPPORTED;   // (no plan makes that many)
     if (stamps != nullptr) return record_hip(launch(fold_lists_kernel<kFoldThreads, true>, dim3(1, B), kFoldThreads, p.fold_lds, st, f));
     if (B < 64) return record_hip(launch(fold_lists_kernel<kFoldThreads>, dim3(1, B), kFoldThreads, p.fold_lds, st, f));
