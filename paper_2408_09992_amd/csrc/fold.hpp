@@ -30,7 +30,7 @@ __host__ __device__ inline size_t fold_lds_bytes(int K) {
 // best, and only keys that reach it are ranked: about 1.3 K of them.  The floor is found by comparing every list's score with
 // every other's, so where far fewer lists are needed than there are, each of `groups` groups of lists puts forward its best
 // only (512 lists of K = 15: 15.2 us for the kernel, with 64 groups 5).  A list's first `chunk` keys are read at once (chunk
-// covers 2.5 times a list's share of the K best and the depth), lists that reach the floor with all of them are read on,
+// covers a list's share of the K best and what chance adds to it), lists that reach the floor with all of them are read on,
 // chunk after chunk.  One round trip to memory, usually; reading everything instead took two launches for 256 lists of
 // K = 100 (25,600 keys: sixteen folds of sixteen lists, then one: 12 us; this: 4 us).
 template <int NT, bool STAMP = false>
@@ -179,7 +179,7 @@ __global__ __launch_bounds__(NT) void fold_lists_kernel(FoldArgs a) {
     for (int t = tid; t < K; t += NT) emit(t, sorted[t]);
 }
 
-// The fold for small K (K <= kSmallKMax) when a query's lists fit R keys per thread (nlists * K <= NT * R): the keys go
+// The fold for small K (K < kRegisterSelectMinK) when a query's lists fit R keys per thread (nlists * K <= NT * R): the keys go
 // straight from memory to registers and through select_small_k(), the selection the short scan uses: per-wave floors
 // by wave operations, one barrier, ranking by counting.  grid = (1, B).  A kernel of its own because this launch is all
 // latency (a few thousand keys): its time is the two dependent memory round trips it cannot avoid (arguments, keys)

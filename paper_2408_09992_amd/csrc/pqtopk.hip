@@ -264,15 +264,17 @@ ScanPlan make_plan(long long N, int B, int m, int K, bool generic = false, int c
         }
     }
     p.fold_lds = fold_lds_bytes(K);
-    // Single-query scans (one query per workgroup row) with a small K whose share per thread fits a few registers run
+    // Single-query scans (one query per workgroup row) whose share per thread fits a few registers run
     // the short kernel: scores stay in registers, one selection, a few KB of code.  Its grid is spread as thin as the
     // CUs allow (one workgroup per CU over all queries): a workgroup's time is the lookups of its share plus a fixed
     // selection, so the fewer units a thread holds the better, and the small fold takes the 256 lists in its stride.
     p.short_scan = false;
     p.short_units = 0;
+    const size_t select_lds = K <= kSmallKMax ? sizeof(SmallSelectLds<kThreads>) : sizeof(MidSelectLds<kThreads>);
     // (two-byte sub-ids: when the table fits LDS beside the selection's few KB)
-    const bool short16 = cw == 2 && !p.glut && lut_floats * sizeof(float) + sizeof(SmallSelectLds<kThreads>) <= kMaxLdsBytes;
-    if ((cw == 1 || short16) && p.vec && !generic && !p.tiled && K <= kSmallKMax) {
+    const size_t table16 = cw == 2 ? align16((size_t)m * b * sizeof(float)) : 0;
+    const bool short16 = cw == 2 && table16 + select_lds <= kMaxLdsBytes;
+    if ((cw == 1 || short16) && p.vec && !generic && !p.tiled) {
         long long nb = kAssumedCUs / B;
         if (nb < 1 || units <= kDirectUnits(row) * (long long)kThreads) nb = 1;
         const long long thin = (units + kThreads - 1) / kThreads;          // workgroups if every thread held one unit
@@ -295,18 +297,18 @@ ScanPlan make_plan(long long N, int B, int m, int K, bool generic = false, int c
             if (!forced) {
                 p.short_scan = true;
                 p.short_units = (int)slots;
-                p.scan_dyn_lds = cw == 1 ? 0 : lut_floats * sizeof(float);
-                p.scan_lds = lut_floats * sizeof(float) + sizeof(SmallSelectLds<kThreads>);
+                p.glut = false;
+                p.scan_dyn_lds = select_lds + table16;
+                p.scan_lds = select_lds + (cw == 1 ? lut_floats * sizeof(float) : table16);
             }
         }
     }
-    // Candidate lists (the `generic` plans) of rows of 4, 8 or 16 bytes with a small K, short enough for a thread to
+    // Candidate lists (the `generic` plans) of rows of 4, 8 or 16 bytes, short enough for a thread to
     // hold its share: every row of a thread is requested at once and the selection comes straight from registers.
     // Same thin grid as the short scan.
     p.short_subset = false;
     p.subset_vecs = 0;
-    if (generic && cw == 1 && (m == 4 || m == 8 || m == 16) && K <= kSmallKMax &&
-        !(g_force_general.load(std::memory_order_relaxed) & 1)) {
+    if (generic && cw == 1 && (m == 4 || m == 8 || m == 16) && !(g_force_general.load(std::memory_order_relaxed) & 1)) {
         long long nb = kAssumedCUs / B;
         if (nb < 1 || N * m <= kDirectUnits(16) * 16LL * kThreads) nb = 1;
         const long long thin = (N + kThreads - 1) / kThreads;              // workgroups if every thread held one candidate
@@ -319,8 +321,8 @@ ScanPlan make_plan(long long N, int B, int m, int K, bool generic = false, int c
             p.nblk = (int)nb;
             p.copies = 1;
             p.big = false;
-            p.scan_dyn_lds = 0;
-            p.scan_lds = (size_t)m * kLutStride * sizeof(float) + sizeof(SmallSelectLds<kThreads>);
+            p.scan_dyn_lds = select_lds;
+            p.scan_lds = (size_t)m * kLutStride * sizeof(float) + select_lds;
         }
     }
     p.filter = false;
@@ -622,7 +624,7 @@ hipError_t launch_short16_m(const ScanPlan& p, const ScanArgs& a, int B, hipStre
 template <int M>
 hipError_t launch_subset_m(const ScanPlan& p, const ScanArgs& a, int B, hipStream_t st) {
     auto go = [&](auto kernel) {
-        return launch(kernel, dim3(p.nblk, B), kThreads, 0, st, a.codes, a.subset, a.S, out_of(a), scores_of(a), (uint32_t)a.N, a.n_items, a.b, a.K);
+        return launch(kernel, dim3(p.nblk, B), kThreads, p.scan_dyn_lds, st, a.codes, a.subset, a.S, out_of(a), scores_of(a), (uint32_t)a.N, a.n_items, a.b, a.K);
     };
     switch (p.subset_vecs) {
         case 1: return go(scan_subset_kernel<M, 1, kThreads>);
@@ -812,7 +814,7 @@ int enqueue_fold(const ScanPlan& p, int B, int K, void* workspace, int* out_ids,
     f.chunk = f.depth = f.need = f.groups = f.group_mask = 0;
     f.out_ids = out_ids; f.out_scores = out_scores;
     f.stamps = stamps;
-    if (K <= kSmallKMax && (long long)nlists * K <= (long long)kThreads * kFoldSmallRegsMax &&
+    if (K < kRegisterSelectMinK && (long long)nlists * K <= (long long)kThreads * kFoldSmallRegsMax &&
         !(g_force_general.load(std::memory_order_relaxed) & 2)) {
         // small K, few keys: the lean fold
         const bool few = (long long)nlists * K <= (long long)kThreads * kFoldSmallRegs;
@@ -822,10 +824,11 @@ int enqueue_fold(const ScanPlan& p, int B, int K, void* workspace, int* out_ids,
         if (stamps != nullptr) return few ? go(fold_small_kernel<kThreads, kFoldSmallRegs, true>) : go(fold_small_kernel<kThreads, kFoldSmallRegsMax, true>);
         return few ? go(fold_small_kernel<kThreads, kFoldSmallRegs, false>) : go(fold_small_kernel<kThreads, kFoldSmallRegsMax, false>);
     }
-    // (see fold_lists_kernel: a chunk holds 2.5 times a list's share of the K best, and the depth at which at most 60 % of
-    // the lists have to reach the floor)
+    // (see fold_lists_kernel: a chunk holds what a list has of the K best in all but one case of thousands, when they are
+    // spread at random: reading on is another round trip; and the depth at which at most 60 % of the lists have to reach the floor)
+    const double share = (double)K / nlists, most = share + 3.5 * sqrt(share) + 2.0;
     f.chunk = 4;
-    while (f.chunk < K && 2LL * f.chunk * nlists < 5LL * K) f.chunk *= 2;
+    while (f.chunk < K && f.chunk < most && 2LL * f.chunk * nlists <= kFoldSlots) f.chunk *= 2;
     f.depth = 1;
     while (f.depth < f.chunk && f.depth < K && 10LL * ((K + f.depth - 1) / f.depth) > 6LL * nlists) ++f.depth;
     f.need = (K + f.depth - 1) / f.depth;

@@ -1,5 +1,5 @@
 // Eq. 5 + TopK for catalogues short enough that a workgroup's share fits its registers (scan_short_kernel): the scan of
-// every single-query call over up to a few million items with K < 32, the headline workload among them.
+// every single-query call over up to a few million items, the headline workload among them.
 // Part of kernels.hpp, which includes these parts inside namespace pqk in this order:
 // common.hpp, subitem_scores.hpp, topk_parts.hpp, select_small.hpp, scan_single.hpp, scan_short.hpp, scan_subset.hpp, scan_batched.hpp,
 // fold.hpp, comparison.hpp.
@@ -26,8 +26,9 @@ __host__ __device__ constexpr int short16_max_units(int m) { return m == 16 ? 6 
 //   32, 64: P / 16 vectors per item).  CW = 2 (M = 4, 8, 16): the query's m x b table lies in dynamic LDS as in memory.
 // The arguments are plain values, not a struct: they fit the scalar registers the hardware loads before a wave starts
 // (amdgpu-kernarg-preload-count), and the kernel's first loads go out without a round trip for their addresses.
+// (Few units: 64 vector registers are enough, for four workgroups on a CU when many queries each take one.)
 template <int M, int U, int NT, bool STAMP = false, int CW = 1>
-__global__ __launch_bounds__(NT) void scan_short_kernel(const uint8_t* codes, const float* S, void* out, float* out_scores, uint32_t N,
+__global__ __launch_bounds__(NT, M * CW <= 16 && U <= 3 ? 8 : 1) void scan_short_kernel(const uint8_t* codes, const float* S, void* out, float* out_scores, uint32_t N,
                                                         int b, int K, uint64_t* stamps) {
     ScanArgs a;                                               // (what the shared parts below expect; never in memory)
     a.codes = codes; a.S = S; a.N = N; a.m = M; a.b = b; a.K = K;
@@ -44,7 +45,7 @@ __global__ __launch_bounds__(NT) void scan_short_kernel(const uint8_t* codes, co
     __shared__ __align__(16) float lut_static[CW == 1 ? M * kLutStride : 4];
     extern __shared__ __align__(16) unsigned char smem[];
     float* const lut = CW == 1 ? lut_static : reinterpret_cast<float*>(smem);
-    __shared__ SmallSelectLds<NT> sel;
+    unsigned char* const sel = smem + (CW == 1 ? 0 : align16((size_t)M * b * sizeof(float)));   // what the selection needs, for this K
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
     const int q = blockIdx.y, nblk = gridDim.x, blk = blockIdx.x;
     uint64_t* const rec = STAMP ? a.stamps + (((size_t)q * nblk + blk) * NW + wave) * kStampSlots : nullptr;
@@ -108,7 +109,8 @@ __global__ __launch_bounds__(NT) void scan_short_kernel(const uint8_t* codes, co
         for (int i = 0; i < kPer; ++i)
             if (tid + i * NT < M * kLutStride) lut[tid + i * NT] = tv[i];
     }
-    small_select_clear<NT>(sel, tid);
+    if (K <= kSmallKMax) small_select_clear<NT>(*reinterpret_cast<SmallSelectLds<NT>*>(sel), tid);
+    else mid_select_clear<NT>(*reinterpret_cast<MidSelectLds<NT>*>(sel), tid);
     stamp<STAMP>(rec, kStampRequested, lane);
     __syncthreads();
     stamp<STAMP>(rec, kStampTables, lane);
@@ -165,6 +167,8 @@ __global__ __launch_bounds__(NT) void scan_short_kernel(const uint8_t* codes, co
         if (kTail && slot == R - 1) return total_units * IPV + (uint32_t)lane;
         return (first + (uint32_t)(slot / IPV) * stride) * IPV + (uint32_t)(slot % IPV);
     };
-    select_small_k<NT, R, STAMP>(sc, id_of, K, sel, tid, [&](int rank, uint64_t key) { emit_key(a, q, nblk, blk, rank, key); }, rec);
+    auto emit = [&](int rank, uint64_t key) { emit_key(a, q, nblk, blk, rank, key); };
+    if (K <= kSmallKMax) select_small_k<NT, R, STAMP>(sc, id_of, K, *reinterpret_cast<SmallSelectLds<NT>*>(sel), tid, emit, rec);
+    else select_mid_k<NT, R, STAMP>(sc, id_of, K, *reinterpret_cast<MidSelectLds<NT>*>(sel), tid, emit, rec);
     stamp<STAMP>(rec, kStampEnd, lane);
 }

@@ -1,4 +1,4 @@
-// Algorithm 1 with a candidate list V, for lists short enough that a workgroup's share fits its registers and K < 32
+// Algorithm 1 with a candidate list V, for lists short enough that a workgroup's share fits its registers
 // (scan_subset_kernel): lists of up to a couple of million candidates at batch 1.
 // Part of kernels.hpp, which includes these parts inside namespace pqk in this order:
 // common.hpp, subitem_scores.hpp, topk_parts.hpp, select_small.hpp, scan_single.hpp, scan_short.hpp, scan_subset.hpp,
@@ -30,7 +30,7 @@ __global__ __launch_bounds__(NT) void scan_subset_kernel(const uint8_t* codes, c
     static_assert(M == 4 || M == 8 || M == 16, "rows of 4, 8 or 16 bytes");
     static_assert(U >= 1 && U <= kSubsetMaxVecs, "vectors per thread");
     __shared__ __align__(16) float lut[M * kLutStride];
-    __shared__ SmallSelectLds<NT> sel;
+    extern __shared__ __align__(16) unsigned char smem[];     // what the selection needs, for this K
     const int tid = threadIdx.x;
     const int q = blockIdx.y, nblk = gridDim.x, blk = blockIdx.x;
     const uint32_t n = (uint32_t)a.N;                          // candidates in the list
@@ -75,7 +75,8 @@ __global__ __launch_bounds__(NT) void scan_subset_kernel(const uint8_t* codes, c
         for (int i = 0; i < kPer; ++i)
             if (tid + i * NT < M * kLutStride) lut[tid + i * NT] = tv[i];
     }
-    small_select_clear<NT>(sel, tid);
+    if (K <= kSmallKMax) small_select_clear<NT>(*reinterpret_cast<SmallSelectLds<NT>*>(smem), tid);
+    else mid_select_clear<NT>(*reinterpret_cast<MidSelectLds<NT>*>(smem), tid);
     __syncthreads();
 
     // ---- Eq. 5 for every candidate this thread holds
@@ -92,6 +93,8 @@ __global__ __launch_bounds__(NT) void scan_subset_kernel(const uint8_t* codes, c
     }
 
     // ---- the workgroup's K best, ranked, straight to the workspace or the result
-    select_small_k<NT, R>(sc, [&](int slot) -> uint32_t { return item[slot]; }, K, sel, tid,
-                          [&](int rank, uint64_t key) { emit_key(a, q, nblk, blk, rank, key); });
+    auto id_of = [&](int slot) -> uint32_t { return item[slot]; };
+    auto emit = [&](int rank, uint64_t key) { emit_key(a, q, nblk, blk, rank, key); };
+    if (K <= kSmallKMax) select_small_k<NT, R>(sc, id_of, K, *reinterpret_cast<SmallSelectLds<NT>*>(smem), tid, emit);
+    else select_mid_k<NT, R>(sc, id_of, K, *reinterpret_cast<MidSelectLds<NT>*>(smem), tid, emit);
 }

@@ -8,7 +8,7 @@
 // written for few instructions and few LDS round trips, not for throughput.
 #pragma once
 
-constexpr int kSmallKMax = kRegisterSelectMinK - 1;   // K up to which select_small_k() is used (a wave's 64 lanes give its floor)
+constexpr int kSmallKMax = 12;                        // K up to which a workgroup's scan selects by select_small_k() (above, select_mid_k() ranks fewer candidates)
 constexpr int kSmallCand = 512;                       // keys of its candidate array
 constexpr int kSmallFloorSteps = 3;                   // four-way search steps of a wave's floor: a 64th of the lanes' range (5 % more candidates than the exact floor gives)
 
@@ -58,7 +58,7 @@ __device__ __forceinline__ uint64_t wave_max_key(uint64_t k) {
 
 // Sorted exact K best of the n keys in cand[0..n) (LDS; zero up to the next multiple of 8) by counting: a key's position
 // is the number of keys that beat it.  Rank r goes to emit(r, key); ranks from n on (fewer than K keys exist) get 0.
-// With four threads per key each counts over a quarter of the keys (the loop is bound by the latency of its LDS reads).
+// With four or two threads per key each counts over a part of the keys (the loop is bound by the latency of its LDS reads).
 // No barrier inside: the caller's barrier has made cand[] complete.
 template <int NT, typename Emit>
 __device__ __forceinline__ void rank_emit(const uint64_t* cand, int n, int K, int tid, Emit&& emit) {
@@ -71,17 +71,23 @@ __device__ __forceinline__ void rank_emit(const uint64_t* cand, int n, int K, in
         return (uint32_t)((p0.x > mine) + (p0.y > mine) + (p1.x > mine) + (p1.y > mine) + (p2.x > mine) + (p2.y > mine) +
                           (p3.x > mine) + (p3.y > mine));
     };
-    if (n8 * 4 <= NT) {
-        const int t = tid >> 2, part = tid & 3;              // (n8 is a multiple of 8: a wave is all in or all out)
+    auto shared = [&](auto lanes) {                           // (n8 is a multiple of 8: four lanes of a key are all in or all out)
+        constexpr int kLanes = decltype(lanes)::value;
+        const int t = tid / kLanes, part = tid % kLanes;
         if (t < n8) {
             const uint64_t mine = cand[t];
             uint32_t rank = 0;
 #pragma unroll 2
-            for (int u = part * 8; u < n8; u += 32) rank += count8(u, mine);
+            for (int u = part * 8; u < n8; u += kLanes * 8) rank += count8(u, mine);
             rank += dpp_u32<kDppQuadSwap1>(0u, rank);
-            rank += dpp_u32<kDppQuadSwap2>(0u, rank);
+            if constexpr (kLanes == 4) rank += dpp_u32<kDppQuadSwap2>(0u, rank);
             if (part == 0 && mine != 0ull && rank < (uint32_t)K) emit((int)rank, mine);
         }
+    };
+    if (n8 * 4 <= NT) {
+        shared(std::integral_constant<int, 4>());
+    } else if (n8 * 2 <= NT) {
+        shared(std::integral_constant<int, 2>());
     } else {
         for (int t = tid; t < n; t += NT) {
             const uint64_t mine = cand[t];
@@ -93,7 +99,7 @@ __device__ __forceinline__ void rank_emit(const uint64_t* cand, int n, int K, in
     for (int t = n + tid; t < K; t += NT) emit(t, 0ull);
 }
 
-// The workgroup's exact, sorted K best (1 <= K <= kSmallKMax) of the items its threads hold in registers: thread-local
+// The workgroup's exact, sorted K best (1 <= K < kRegisterSelectMinK: a wave's 64 lanes give its floor) of the items its threads hold in registers: thread-local
 // slots i = 0 .. R-1 with score sc[i] (empty_score() where a slot holds nothing) and item id id_of(i).  Rank r goes to
 // emit(r, key) (0 for ranks that do not exist).  L: cleared by small_select_clear() before the caller's last barrier.
 //
@@ -197,4 +203,146 @@ __device__ __forceinline__ void select_small_k(const float (&sc)[R], IdOf&& id_o
         last = top;                                           // (0: no key is smaller, the remaining ranks get 0)
         __syncthreads();
     }
+}
+
+// ---- larger K
+constexpr int kMidCand = 1536;                        // keys of the candidate array
+constexpr int kMidBins = 256;                         // buckets of the histogram of the threads' best scores
+
+template <int NT>
+struct MidSelectLds {
+    uint64_t cand[kMidCand];
+    uint32_t hist[kBins];                             // (kMidBins counters of it, then the buckets of the final order)
+    float wave_min[NT / kWave], wave_max[NT / kWave];
+    int ncand;
+};
+
+// Before the workgroup barrier that precedes select_mid_k().
+template <int NT>
+__device__ __forceinline__ void mid_select_clear(MidSelectLds<NT>& L, int tid) {
+    for (int i = tid; i < kMidBins; i += NT) L.hist[i] = 0u;
+    if (tid == 0) L.ncand = 0;
+}
+
+// As select_small_k(), for K <= 2 * NT.  The floor is one that K of the THREADS' best scores reach
+// (K > NT / 2: of the best of their even and of their odd slots), taken from a histogram of those alone: 512 counts instead
+// of the 11,000 that all scores would be, and for K = 100 only a tenth more candidates than K: three barriers, then the
+// candidates are ordered.  (1.28M items, one user: K = 100 18.4 -> 16.6 us per step, K = 31 18.0 -> 14.9; from K = 13 on it
+// beats the waves' own floors, which let eight times K pass.)
+// More candidates than the array holds (heavy ties): the exact K-th key is found bit by bit first.
+template <int NT, int R, bool STAMP = false, typename IdOf, typename Emit>
+__device__ __forceinline__ void select_mid_k(const float (&sc)[R], IdOf&& id_of, int K, MidSelectLds<NT>& L, int tid, Emit&& emit,
+                                             uint64_t* rec = nullptr) {
+    constexpr int NW = NT / kWave;
+    const int lane = tid & (kWave - 1), wave = tid / kWave;
+    const float ninf = -__builtin_inff();
+    float best = ninf, other = ninf;
+#pragma unroll
+    for (int i = 0; i < R; ++i) {                             // (an empty slot's NaN never wins)
+        if (i % 2 == 0) best = fmaxf(best, sc[i]);
+        else other = fmaxf(other, sc[i]);
+    }
+    const bool both = K > NT / 2;
+    if (!both) { best = fmaxf(best, other); other = ninf; }
+    float mx = fmaxf(best, other), mn = fminf(best > ninf ? best : -ninf, other > ninf ? other : -ninf);
+    wave_minmax(mn, mx);
+    if (lane == 0) { L.wave_min[wave] = mn; L.wave_max[wave] = mx; }
+    __syncthreads();
+    float lo = L.wave_min[0], hi = L.wave_max[0];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) { lo = fminf(lo, L.wave_min[w]); hi = fmaxf(hi, L.wave_max[w]); }
+    float scale = hi > lo ? (float)kMidBins / (hi - lo) : 0.0f;
+    if (!(scale > 0.0f) || scale > 3.0e38f) scale = 0.0f;
+    if (best > ninf) atomicAdd(&L.hist[bucket_of<kMidBins>(best, lo, scale)], 1u);
+    if (both && other > ninf) atomicAdd(&L.hist[bucket_of<kMidBins>(other, lo, scale)], 1u);
+    __syncthreads();
+    const float f = floor_of_hist<kMidBins>(L.hist, K, lo, scale, lane);   // (every wave for itself)
+    int total = 0;
+#pragma unroll
+    for (int i = 0; i < R; ++i) total += __popcll(__ballot(sc[i] >= f));
+    if (total != 0) {
+        int at = 0;
+        if (lane == 0) at = atomicAdd(&L.ncand, total);
+        at = __builtin_amdgcn_readfirstlane(at);
+#pragma unroll
+        for (int i = 0; i < R; ++i) {
+            const uint64_t mask = __ballot(sc[i] >= f);
+            if (mask == 0) continue;
+            const int pos = at + __popcll(mask & ((1ull << lane) - 1ull));
+            if (sc[i] >= f && pos < kMidCand) L.cand[pos] = make_key(sc[i] + 0.0f, id_of(i));
+            at += __popcll(mask);
+        }
+    }
+    stamp<STAMP>(rec, kStampOffered, lane);
+    __syncthreads();
+    int n = L.ncand;
+    if (n > kMidCand) {
+        // the K-th best key: the largest that K keys reach (K keys exist: there are more than kMidCand)
+        uint64_t kth = 0ull;
+        for (int bit = 63; bit >= 0; --bit) {
+            const uint64_t t = kth | (1ull << bit);
+            int reach = 0;
+#pragma unroll
+            for (int i = 0; i < R; ++i) reach += __popcll(__ballot(sc[i] == sc[i] && make_key(sc[i] + 0.0f, id_of(i)) >= t));
+            if (tid == 0) L.hist[bit] = 0u;
+            __syncthreads();
+            if (lane == 0) atomicAdd(&L.hist[bit], (uint32_t)reach);
+            __syncthreads();
+            if (L.hist[bit] >= (uint32_t)K) kth = t;
+        }
+        if (tid == 0) L.ncand = 0;
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < R; ++i) {
+            const uint64_t key = make_key(sc[i] + 0.0f, id_of(i));
+            if (sc[i] == sc[i] && key >= kth) L.cand[atomicAdd(&L.ncand, 1)] = key;
+        }
+        __syncthreads();
+        n = L.ncand;                                          // = K: keys are distinct
+    }
+    if (n <= kRankByCount) {
+        const int n8 = (n + 7) & ~7;
+        if (tid < n8 - n) L.cand[n + tid] = 0ull;
+        __syncthreads();
+        rank_emit<NT>(L.cand, n, K, tid, emit);
+    } else {
+        // by buckets over the candidates' own range (from the floor up, where there is one)
+        lo = f;
+        if (!(f > ninf)) {
+            mn = -ninf;
+            for (int t = tid; t < n; t += NT) mn = fminf(mn, score_of_key(L.cand[t]));
+            mx = mn;
+            wave_minmax(mn, mx);
+            if (lane == 0) L.wave_min[wave] = mn;
+            __syncthreads();
+            lo = L.wave_min[0];
+#pragma unroll
+            for (int w = 1; w < NW; ++w) lo = fminf(lo, L.wave_min[w]);
+        }
+        scale = hi > lo ? (float)kBins / (hi - lo) : 0.0f;
+        if (!(scale > 0.0f) || scale > 3.0e38f) scale = 0.0f;
+        if (!bucket_sort<NT, kMidCand / NT>(L.cand, n, lo, scale, L.hist, tid)) {
+            // (too many in one bucket: by counting, from registers to their places)
+            uint64_t mine[kMidCand / NT];
+            int rank[kMidCand / NT];
+#pragma unroll
+            for (int r = 0; r < kMidCand / NT; ++r) {
+                mine[r] = r * NT + tid < n ? L.cand[r * NT + tid] : 0ull;
+                rank[r] = 0;
+            }
+            for (int u = 0; u < n; ++u) {
+                const uint64_t x = L.cand[u];
+#pragma unroll
+                for (int r = 0; r < kMidCand / NT; ++r) rank[r] += x > mine[r];
+            }
+#pragma unroll
+            for (int r = 0; r < kMidCand / NT; ++r)
+                if (mine[r] != 0ull && rank[r] < K) emit(rank[r], mine[r]);
+            for (int t = n + tid; t < K; t += NT) emit(t, 0ull);
+            stamp<STAMP>(rec, kStampSelected, lane);
+            return;
+        }
+        for (int t = tid; t < K; t += NT) emit(t, t < n ? L.cand[t] : 0ull);
+    }
+    stamp<STAMP>(rec, kStampSelected, lane);
 }

@@ -263,6 +263,28 @@ def test_fold_of_sorted_lists(pq, oracle, N, B, K):
             pq.pq_measure_force_general(prev)
 
 
+@pytest.mark.parametrize("K", [32, 193, 256, 257, 512])
+@pytest.mark.parametrize("kind", ["bytes", "list", "wide"])
+def test_larger_k_straight_from_registers(pq, oracle, K, kind):
+    """Shares held in registers with K >= 32: one workgroup and many, fewer items than K threads, ragged last slots, a floor
+    that says nothing, and ties that fill the candidates."""
+    rng = np.random.default_rng(K)
+    for N, B, m in ((K, 3, 8), (1_537, 2, 4), (30_011, 1, 16), (200_003, 2, 8), (900_001, 1, 8)):
+        for ties in (False, True):
+            b = 256 if kind != "wide" else 300
+            codes = rng.integers(0, b, (N, m)).astype(np.uint16 if kind == "wide" else np.uint8)
+            S = tables(K + N, B, m, b)
+            if ties:
+                S[:] = np.float32(0.5)
+                S[:, 0, :3] = np.float32(0.75)
+            if kind == "bytes":
+                assert_same_topk(pq, oracle, codes, S, K, f"{N} {ties}")
+            elif kind == "wide":
+                assert_same_topk_u16(pq, oracle, codes, S, K, f"{N} {ties}")
+            else:
+                assert_same_subset_topk(pq, oracle, codes, S, rng.permutation(N).astype(np.int32), K, f"{N} {ties}")
+
+
 # ---- batches scanned by upper bounds: every geometry of fields and rows, edges of tiles and of the last code vector, K from 1
 # to the longest lists, samples of one and of several parts and rounds; bit 4 keeps small shapes on these kernels
 def _bounds_case(pq, oracle, codes, S, K, subset=None):
