@@ -48,8 +48,8 @@ namespace pqk {
     X(16, 1, kThreads, 2, true) X(16, 1, kBigThreads, 2, false) X(16, 1, kThreads, 2, false)
 // measurement instances (wall-clock stamps per wave) of the two kernels the named single-query workloads run
 #define PQ_SCAN_INSTANCES_STAMPED(X) X(8, 1, kThreads, 1, false, true) X(8, kTableCopies, kBigThreads, 1, false, true)
-// scan_short_kernel<M, U, NT, STAMP> instances: every number of units per thread up to short_max_units(M), in three
-// translation units; measurement instances for m = 8
+// scan_short_kernel<M, U, NT, STAMP> instances: every number of units per thread up to short_held_units(M) and the
+// larger instances; measurement instances for m = 8
 #define PQ_SHORT_U(X, M, U) X(M, U, kThreads, false)
 #define PQ_SHORT_U4(X, M, U) PQ_SHORT_U(X, M, U) PQ_SHORT_U(X, M, U + 1) PQ_SHORT_U(X, M, U + 2) PQ_SHORT_U(X, M, U + 3)
 #define PQ_SHORT_INSTANCES_A(X) \
@@ -58,6 +58,14 @@ namespace pqk {
     X(8, 6, kThreads, true) X(8, 7, kThreads, true) X(8, 8, kThreads, true) \
     PQ_SHORT_U(X, 1, 1) PQ_SHORT_U(X, 1, 2) PQ_SHORT_U(X, 2, 1) PQ_SHORT_U(X, 2, 2) \
     PQ_SHORT_U4(X, 4, 1) PQ_SHORT_U(X, 4, 5) PQ_SHORT_U(X, 4, 6)
+#define PQ_SHORT_INSTANCES_D(X) \
+    X(8, 9, kThreads, true) X(8, 10, kThreads, true) X(8, 11, kThreads, true) X(8, 12, kThreads, true) \
+    X(8, 16, kThreads, true) X(8, 24, kThreads, true) X(8, 32, kThreads, true) \
+    PQ_SHORT_U(X, 4, 8) PQ_SHORT_U(X, 4, 12) PQ_SHORT_U(X, 4, 16) PQ_SHORT_U(X, 8, 16) PQ_SHORT_U(X, 8, 24) PQ_SHORT_U(X, 8, 32) \
+    PQ_SHORT_U(X, 16, 16) PQ_SHORT_U(X, 16, 24) PQ_SHORT_U(X, 16, 32) PQ_SHORT_U(X, 16, 48)
+#define PQ_SHORT_INSTANCES_E(X) \
+    PQ_SHORT_U(X, 32, 12) PQ_SHORT_U(X, 32, 16) PQ_SHORT_U(X, 32, 24) PQ_SHORT_U(X, 32, 32) \
+    PQ_SHORT_U(X, 64, 8) PQ_SHORT_U(X, 64, 12) PQ_SHORT_U(X, 64, 16) PQ_SHORT_U(X, 64, 24) PQ_SHORT_U(X, 64, 32)
 #define PQ_SHORT_INSTANCES_B(X) \
     PQ_SHORT_U4(X, 16, 1) PQ_SHORT_U4(X, 16, 5) PQ_SHORT_U4(X, 16, 9)
 #define PQ_SHORT_INSTANCES_C(X) \
@@ -69,6 +77,9 @@ namespace pqk {
     PQ_SHORT16_U(X, 4, 7) PQ_SHORT16_U(X, 4, 8) PQ_SHORT16_U(X, 4, 9) PQ_SHORT16_U(X, 4, 10) PQ_SHORT16_U(X, 4, 11) PQ_SHORT16_U(X, 4, 12) \
     PQ_SHORT16_U(X, 8, 1) PQ_SHORT16_U(X, 8, 2) PQ_SHORT16_U(X, 8, 3) PQ_SHORT16_U(X, 8, 4) PQ_SHORT16_U(X, 8, 5) PQ_SHORT16_U(X, 8, 6) \
     PQ_SHORT16_U(X, 8, 7) PQ_SHORT16_U(X, 8, 8) PQ_SHORT16_U(X, 8, 9) PQ_SHORT16_U(X, 8, 10) PQ_SHORT16_U(X, 8, 11) PQ_SHORT16_U(X, 8, 12) \
+    PQ_SHORT16_U(X, 4, 16) PQ_SHORT16_U(X, 4, 24) PQ_SHORT16_U(X, 4, 32) \
+    PQ_SHORT16_U(X, 8, 16) PQ_SHORT16_U(X, 8, 24) PQ_SHORT16_U(X, 8, 32) PQ_SHORT16_U(X, 8, 48) \
+    PQ_SHORT16_U(X, 16, 8) PQ_SHORT16_U(X, 16, 12) PQ_SHORT16_U(X, 16, 16) PQ_SHORT16_U(X, 16, 24) PQ_SHORT16_U(X, 16, 32) \
     PQ_SHORT16_U(X, 16, 1) PQ_SHORT16_U(X, 16, 2) PQ_SHORT16_U(X, 16, 3) PQ_SHORT16_U(X, 16, 4) PQ_SHORT16_U(X, 16, 5) PQ_SHORT16_U(X, 16, 6)
 // scan_subset_kernel<M, U, NT>: rows of 4, 8, 16 bytes, every number of vectors per thread
 #define PQ_SUBSET_M(X, M) X(M, 1, kThreads) X(M, 2, kThreads) X(M, 3, kThreads) X(M, 4, kThreads) X(M, 5, kThreads) \
@@ -122,6 +133,8 @@ PQ_SCAN_INSTANCES_STAMPED(PQ_SCAN_EXTERN6)
 PQ_SHORT_INSTANCES_A(PQ_SHORT_EXTERN)
 PQ_SHORT_INSTANCES_B(PQ_SHORT_EXTERN)
 PQ_SHORT_INSTANCES_C(PQ_SHORT_EXTERN)
+PQ_SHORT_INSTANCES_D(PQ_SHORT_EXTERN)
+PQ_SHORT_INSTANCES_E(PQ_SHORT_EXTERN)
 PQ_SUBSET_INSTANCES(PQ_SUBSET_EXTERN)
 PQ_SHORT16_INSTANCES(PQ_SHORT16_EXTERN)
 PQ_TILED_INSTANCES(PQ_TILED_EXTERN)

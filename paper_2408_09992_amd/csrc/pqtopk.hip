@@ -270,10 +270,10 @@ ScanPlan make_plan(long long N, int B, int m, int K, bool generic = false, int c
     // selection, so the fewer units a thread holds the better, and the small fold takes the 256 lists in its stride.
     p.short_scan = false;
     p.short_units = 0;
-    const size_t select_lds = K <= kSmallKMax ? sizeof(SmallSelectLds<kThreads>) : sizeof(MidSelectLds<kThreads>);
     // (two-byte sub-ids: when the table fits LDS beside the selection's few KB)
     const size_t table16 = cw == 2 ? align16((size_t)m * b * sizeof(float)) : 0;
-    const bool short16 = cw == 2 && table16 + select_lds <= kMaxLdsBytes;
+    auto select_lds = [](bool small) { return small ? sizeof(SmallSelectLds<kThreads>) : sizeof(MidSelectLds<kThreads>); };
+    const bool short16 = cw == 2 && table16 + select_lds(K <= kSmallKMax) <= kMaxLdsBytes;
     if ((cw == 1 || short16) && p.vec && !generic && !p.tiled) {
         long long nb = kAssumedCUs / B;
         if (nb < 1 || units <= kDirectUnits(row) * (long long)kThreads) nb = 1;
@@ -281,7 +281,9 @@ ScanPlan make_plan(long long N, int B, int m, int K, bool generic = false, int c
         if (nb > thin) nb = thin;
         const long long per_slot = (long long)kThreads * nb;               // units one slot of all threads covers
         const long long slots = (units + per_slot - 1) / per_slot;
-        if (slots <= (cw == 1 ? short_max_units(m) : short16_max_units(m))) {
+        const int instance = slots <= 48 ? short_instance((int)slots, cw == 1 ? short_held_units(m) : short16_held_units(m)) : 0;
+        const size_t select = select_lds(short_selects_small(K, instance, row));
+        if (slots <= (cw == 1 ? short_max_units(m) : short16_max_units(m)) && table16 + select <= kMaxLdsBytes) {
             // (one-byte sub-ids: the general kernel takes the same grid when the measurement hook keeps a call off the
             // short one; two-byte sub-ids: its plan stays as it is)
             const bool forced = (g_force_general.load(std::memory_order_relaxed) & 1) != 0;
@@ -298,8 +300,8 @@ ScanPlan make_plan(long long N, int B, int m, int K, bool generic = false, int c
                 p.short_scan = true;
                 p.short_units = (int)slots;
                 p.glut = false;
-                p.scan_dyn_lds = select_lds + table16;
-                p.scan_lds = select_lds + (cw == 1 ? lut_floats * sizeof(float) : table16);
+                p.scan_dyn_lds = select + table16;
+                p.scan_lds = select + (cw == 1 ? lut_floats * sizeof(float) : table16);
             }
         }
     }
@@ -321,8 +323,8 @@ ScanPlan make_plan(long long N, int B, int m, int K, bool generic = false, int c
             p.nblk = (int)nb;
             p.copies = 1;
             p.big = false;
-            p.scan_dyn_lds = select_lds;
-            p.scan_lds = (size_t)m * kLutStride * sizeof(float) + select_lds;
+            p.scan_dyn_lds = select_lds(K <= kSmallKMax);
+            p.scan_lds = (size_t)m * kLutStride * sizeof(float) + p.scan_dyn_lds;
         }
     }
     p.filter = false;
@@ -551,7 +553,7 @@ hipError_t launch_short_args(KernelT kernel, const ScanPlan& p, const ScanArgs& 
 
 template <int M, int U>
 hipError_t launch_short_units(const ScanPlan& p, const ScanArgs& a, int B, hipStream_t st) {
-    if constexpr (U <= short_max_units(M)) {
+    if constexpr (short_has(U, short_held_units(M), short_max_units(M))) {
         if constexpr (M == 8) {
             if (a.stamps != nullptr) {
                 return launch_short_args(scan_short_kernel<M, U, kThreads, true>, p, a, B, st);
@@ -564,7 +566,7 @@ hipError_t launch_short_units(const ScanPlan& p, const ScanArgs& a, int B, hipSt
 }
 template <int M>
 hipError_t launch_short_m(const ScanPlan& p, const ScanArgs& a, int B, hipStream_t st) {
-    switch (p.short_units) {
+    switch (short_instance(p.short_units, short_held_units(M))) {
         case 1: return launch_short_units<M, 1>(p, a, B, st);
         case 2: return launch_short_units<M, 2>(p, a, B, st);
         case 3: return launch_short_units<M, 3>(p, a, B, st);
@@ -577,6 +579,10 @@ hipError_t launch_short_m(const ScanPlan& p, const ScanArgs& a, int B, hipStream
         case 10: return launch_short_units<M, 10>(p, a, B, st);
         case 11: return launch_short_units<M, 11>(p, a, B, st);
         case 12: return launch_short_units<M, 12>(p, a, B, st);
+        case 16: return launch_short_units<M, 16>(p, a, B, st);
+        case 24: return launch_short_units<M, 24>(p, a, B, st);
+        case 32: return launch_short_units<M, 32>(p, a, B, st);
+        case 48: return launch_short_units<M, 48>(p, a, B, st);
         default: return hipErrorInvalidValue;
     }
 }
@@ -594,7 +600,7 @@ hipError_t launch_short(const ScanPlan& p, const ScanArgs& a, int B, int m, hipS
 
 template <int M, int U>
 hipError_t launch_short16_units(const ScanPlan& p, const ScanArgs& a, int B, hipStream_t st) {
-    if constexpr (U <= short16_max_units(M)) {
+    if constexpr (short_has(U, short16_held_units(M), short16_max_units(M))) {
         hipError_t e = allow_lds(scan_short_kernel<M, U, kThreads, false, 2>, p.scan_dyn_lds);
         if (e != hipSuccess) return e;
         return launch_short_args(scan_short_kernel<M, U, kThreads, false, 2>, p, a, B, st);
@@ -604,7 +610,7 @@ hipError_t launch_short16_units(const ScanPlan& p, const ScanArgs& a, int B, hip
 }
 template <int M>
 hipError_t launch_short16_m(const ScanPlan& p, const ScanArgs& a, int B, hipStream_t st) {
-    switch (p.short_units) {
+    switch (short_instance(p.short_units, short16_held_units(M))) {
         case 1: return launch_short16_units<M, 1>(p, a, B, st);
         case 2: return launch_short16_units<M, 2>(p, a, B, st);
         case 3: return launch_short16_units<M, 3>(p, a, B, st);
@@ -617,6 +623,10 @@ hipError_t launch_short16_m(const ScanPlan& p, const ScanArgs& a, int B, hipStre
         case 10: return launch_short16_units<M, 10>(p, a, B, st);
         case 11: return launch_short16_units<M, 11>(p, a, B, st);
         case 12: return launch_short16_units<M, 12>(p, a, B, st);
+        case 16: return launch_short16_units<M, 16>(p, a, B, st);
+        case 24: return launch_short16_units<M, 24>(p, a, B, st);
+        case 32: return launch_short16_units<M, 32>(p, a, B, st);
+        case 48: return launch_short16_units<M, 48>(p, a, B, st);
         default: return hipErrorInvalidValue;
     }
 }

@@ -5,15 +5,29 @@
 // fold.hpp, comparison.hpp.
 #pragma once
 
-// Most units (16-byte code vectors for m <= 16, items for m = 32 and 64) a thread of the short kernel holds: as many as
-// still beat the general kernel (measured at batch 1, K = 10: m = 8, 2.5M items 14.5 -> 12.3 us, at 16 vectors no gain left;
-// m = 16, 1.28M items 14.0 -> 11.6 us; m = 32, 700K items 13.9 -> 11.9 us; m = 64, 500K items 15.6 -> 14.4 us, but
-// eight items of four vectors each no longer fit the registers; m = 4, 3M items 13.3 -> 11.3 us).
-__host__ __device__ constexpr int short_max_units(int m) {
+// Most units (16-byte code vectors for rows of up to 16 bytes, items for longer rows) a thread holds ALL AT ONCE: everything is
+// requested before the tables are even there.
+__host__ __device__ constexpr int short_held_units(int m) {
     return m == 1 ? 2 : m == 2 ? 2 : m == 4 ? 6 : m == 8 ? 12 : m == 16 ? 12 : m == 32 ? 8 : 4;
 }
-// ... with two-byte sub-ids (rows of 8, 16, 32 bytes: m = 4, 8, 16): code vectors, or items of two vectors for m = 16
-__host__ __device__ constexpr int short16_max_units(int m) { return m == 16 ? 6 : 12; }
+__host__ __device__ constexpr int short16_held_units(int m) { return m == 16 ? 6 : 12; }   // two-byte sub-ids (m = 4, 8, 16)
+// Beyond, the scores of up to 64 items per thread stay in registers and only the next units' codes with them: instances of 16, 24,
+// ... units, each for every count down to the next smaller instance's.  Against the general kernel, whose lists, running floors and
+// final merge cost more the more results there are (one user, microseconds per step for K = 10, 100, 512): 5M items at m = 8
+// 24.7, 34.9, 70.8 -> 19.0, 23.1, 28.7; 8.3M at m = 4 21.8, 32.2, 68.4 -> 17.6, 21.9, 28.6; 3.5M at m = 64 55.7, 60.0, 96.1 -> 51.4,
+// 55.2, 60.3.  At 64 items it ends: registers (at m = 8 the general kernel's sixteen copies of the tables are as fast there).
+__host__ __device__ constexpr int short_max_units(int m) { return m <= 2 ? 2 : m == 4 ? 16 : m == 8 ? 32 : m == 16 ? 48 : 32; }
+__host__ __device__ constexpr int short16_max_units(int m) { return m == 4 ? 32 : m == 8 ? 48 : 32; }
+// the instance that takes `units` units per thread (at most short_max_units), and the most the next smaller one takes
+__host__ __device__ constexpr int short_instance(int units, int held) {
+    return units <= held ? units : units <= 8 && held < 8 ? 8 : units <= 12 && held < 12 ? 12 : units <= 16 ? 16 : units <= 24 ? 24 : units <= 32 ? 32 : 48;
+}
+__host__ __device__ constexpr int short_sure_units(int u, int held) {
+    return u <= held ? u - 1 : u == 8 ? held : u == 12 ? (held < 8 ? 8 : held) : u == 16 ? (held > 12 ? held : 12) : u == 24 ? 16 : u == 32 ? 24 : 32;
+}
+
+__host__ __device__ constexpr bool short_selects_small(int K, int u, int row) { return K <= kSmallKMax && u * (row < 16 ? 16 / row : 1) <= 24; }
+__host__ __device__ constexpr bool short_has(int u, int held, int most) { return u <= most && short_instance(u, held) == u; }
 
 // grid = (item blocks, B); one query per workgroup; a thread holds U units of its workgroup's share: unit u of thread t
 // of workgroup g is number (u * blocks + g) * NT + t of the catalogue's units (slot u of all workgroups together is one
@@ -41,6 +55,9 @@ __global__ __launch_bounds__(NT, M * CW <= 16 && U <= 3 ? 8 : 1) void scan_short
     constexpr bool kTail = P < 16 || (CW == 1 && P == 16);     // items after the last whole code vector may exist (a slot is kept for them)
     constexpr int R = U * IPV + (kTail ? 1 : 0);
     static_assert(CW == 1 || CW == 2, "one- or two-byte sub-ids");
+    constexpr int kHeld = CW == 1 ? short_held_units(M) : short16_held_units(M);
+    constexpr int kSure = short_sure_units(U, kHeld);          // slots that lie wholly inside the catalogue
+    constexpr int kRingUnits = U <= kHeld ? U : (VPU >= 4 || U * IPV > 48 ? 4 : 8);   // units whose codes are on their way or here
     static_assert(U >= 1 && U <= (CW == 1 ? short_max_units(M) : short16_max_units(M)), "units per thread");
     __shared__ __align__(16) float lut_static[CW == 1 ? M * kLutStride : 4];
     extern __shared__ __align__(16) unsigned char smem[];
@@ -56,18 +73,21 @@ __global__ __launch_bounds__(NT, M * CW <= 16 && U <= 3 ? 8 : 1) void scan_short
     const uint32_t first = (uint32_t)blk * NT + (uint32_t)tid, stride = (uint32_t)nblk * NT;   // unit u: first + u * stride
 
     // ---- table values requested, then all codes, then the tables go to LDS
-    uint32_t w[U][4 * VPU];
-    auto fetch_codes = [&]() {                                // (branch-free: a unit past the end re-reads the last one)
-        const uint4* base = reinterpret_cast<const uint4*>(a.codes);
+    uint32_t w[kRingUnits][4 * VPU];
+    uint32_t ahead = first;
+    auto fetch = [&](int u) {                                 // (branch-free: a unit past the end re-reads another)
+        const uint32_t at = ahead + (uint32_t)u * stride;
+        const uint4* base = reinterpret_cast<const uint4*>(a.codes) + (size_t)(U <= kHeld ? min(at, last_unit) : u < kSure || at <= last_unit ? at : min(first, last_unit)) * VPU;
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const uint32_t v = min(first + (uint32_t)u * stride, last_unit);
-#pragma unroll
-            for (int j = 0; j < VPU; ++j) {
-                const uint4 x = base[(size_t)v * VPU + j];
-                w[u][4 * j] = x.x; w[u][4 * j + 1] = x.y; w[u][4 * j + 2] = x.z; w[u][4 * j + 3] = x.w;
-            }
+        for (int j = 0; j < VPU; ++j) {
+            const uint4 x = base[j];
+            uint32_t* const to = w[u % kRingUnits] + 4 * j;
+            to[0] = x.x; to[1] = x.y; to[2] = x.z; to[3] = x.w;
         }
+    };
+    auto fetch_codes = [&]() {
+#pragma unroll
+        for (int u = 0; u < kRingUnits; ++u) fetch(u);
     };
     const float* Sq = a.S + (size_t)q * M * b;
     if constexpr (CW == 2) {
@@ -109,7 +129,8 @@ __global__ __launch_bounds__(NT, M * CW <= 16 && U <= 3 ? 8 : 1) void scan_short
         for (int i = 0; i < kPer; ++i)
             if (tid + i * NT < M * kLutStride) lut[tid + i * NT] = tv[i];
     }
-    if (K <= kSmallKMax) small_select_clear<NT>(*reinterpret_cast<SmallSelectLds<NT>*>(sel), tid);
+    const bool small = short_selects_small(K, U, P);
+    if (small) small_select_clear<NT>(*reinterpret_cast<SmallSelectLds<NT>*>(sel), tid);
     else mid_select_clear<NT>(*reinterpret_cast<MidSelectLds<NT>*>(sel), tid);
     stamp<STAMP>(rec, kStampRequested, lane);
     __syncthreads();
@@ -124,17 +145,28 @@ __global__ __launch_bounds__(NT, M * CW <= 16 && U <= 3 ? 8 : 1) void scan_short
     float sc[R];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-        const bool have = u < U - 1 || first + (uint32_t)u * stride < total_units;
+        const bool have = u < kSure || first + (uint32_t)u * stride < total_units;
+        const uint32_t* const x = w[u % kRingUnits];
         float part[IPV];
-        if (u < U - 1 || __ballot(have) != 0) {               // (a wave wholly past the end looks nothing up)
+        if (u < kSure || __ballot(have) != 0) {               // (a wave wholly past the end looks nothing up)
             if constexpr (CW == 2) {
-                if constexpr (P > 16) part[0] = score_wide16<M>(lut, b, w[u]);
-                else score_vector16<M>(lut, b, w[u], part);
-            } else if constexpr (M > 16) part[0] = score_wide<M>(lut, w[u]);
-            else score_vector<M, 1>(lut, w[u], part);
+                if constexpr (P > 16) part[0] = score_wide16<M>(lut, b, x);
+                else score_vector16<M>(lut, b, x, part);
+            } else if constexpr (M > 16) part[0] = score_wide<M>(lut, x);
+            else score_vector<M, 1>(lut, x, part);
         } else {
 #pragma unroll
             for (int e = 0; e < IPV; ++e) part[e] = 0.0f;
+        }
+        if (u + kRingUnits < U) {
+            asm volatile("" : "+v"(ahead) : "v"(part[0]));
+            fetch(u + kRingUnits);
+        }
+        if constexpr (U > kHeld) {
+            // the next unit's lookups wait for this unit's scores, or the compiler moves every unit's loads and lookups to the
+            // front and runs out of registers
+#pragma unroll
+            for (int j = 0; j < 4 * VPU; ++j) asm volatile("" : "+v"(w[(u + 1) % kRingUnits][j]) : "v"(part[0]));
         }
 #pragma unroll
         for (int e = 0; e < IPV; ++e) sc[u * IPV + e] = have ? part[e] : empty_score();
@@ -168,7 +200,7 @@ __global__ __launch_bounds__(NT, M * CW <= 16 && U <= 3 ? 8 : 1) void scan_short
         return (first + (uint32_t)(slot / IPV) * stride) * IPV + (uint32_t)(slot % IPV);
     };
     auto emit = [&](int rank, uint64_t key) { emit_key(a, q, nblk, blk, rank, key); };
-    if (K <= kSmallKMax) select_small_k<NT, R, STAMP>(sc, id_of, K, *reinterpret_cast<SmallSelectLds<NT>*>(sel), tid, emit, rec);
+    if (small) select_small_k<NT, R, STAMP>(sc, id_of, K, *reinterpret_cast<SmallSelectLds<NT>*>(sel), tid, emit, rec);
     else select_mid_k<NT, R, STAMP>(sc, id_of, K, *reinterpret_cast<MidSelectLds<NT>*>(sel), tid, emit, rec);
     stamp<STAMP>(rec, kStampEnd, lane);
 }

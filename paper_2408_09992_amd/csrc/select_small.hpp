@@ -264,12 +264,14 @@ __device__ __forceinline__ void select_mid_k(const float (&sc)[R], IdOf&& id_of,
         int at = 0;
         if (lane == 0) at = atomicAdd(&L.ncand, total);
         at = __builtin_amdgcn_readfirstlane(at);
+        float again = f;                                      // (compared anew: R masks do not fit the scalar registers)
+        asm volatile("" : "+v"(again));
 #pragma unroll
         for (int i = 0; i < R; ++i) {
-            const uint64_t mask = __ballot(sc[i] >= f);
+            const uint64_t mask = __ballot(sc[i] >= again);
             if (mask == 0) continue;
             const int pos = at + __popcll(mask & ((1ull << lane) - 1ull));
-            if (sc[i] >= f && pos < kMidCand) L.cand[pos] = make_key(sc[i] + 0.0f, id_of(i));
+            if (sc[i] >= again && pos < kMidCand) L.cand[pos] = make_key(sc[i] + 0.0f, id_of(i));
             at += __popcll(mask);
         }
     }

@@ -263,6 +263,24 @@ def test_fold_of_sorted_lists(pq, oracle, N, B, K):
             pq.pq_measure_force_general(prev)
 
 
+@pytest.mark.parametrize("m,wide", [(4, False), (8, False), (16, False), (32, False), (64, False), (4, True), (8, True), (16, True)])
+def test_short_scan_with_more_units_than_are_held_at_once(pq, oracle, m, wide):
+    """The larger instances: the edges of each (its last slots empty, ragged, whole), for a query that has the chip to itself's
+    sixteenth (sixteen queries side by side)."""
+    rng = np.random.default_rng(m + wide)
+    row, b = m * (2 if wide else 1), 300 if wide else 256
+    items = max(1, 16 // row)                                  # per unit
+    S = tables(m, 16, m, b)
+    prev = pq.pq_measure_force_general(8)
+    try:
+        for units in (5, 7, 9, 12, 13, 16, 17, 24, 25, 32, 33, 48, 49):
+            N = units * 16 * 512 * items + (-37 if units % 2 else 0) - 8 * 512 * items * (units % 3 == 0)
+            codes = rng.integers(0, b, (N, m)).astype(np.uint16 if wide else np.uint8)
+            (assert_same_topk_u16 if wide else assert_same_topk)(pq, oracle, codes, S, 10 if units % 2 else 40, f"{units} units")
+    finally:
+        pq.pq_measure_force_general(prev)
+
+
 @pytest.mark.parametrize("K", [32, 193, 256, 257, 512])
 @pytest.mark.parametrize("kind", ["bytes", "list", "wide"])
 def test_larger_k_straight_from_registers(pq, oracle, K, kind):
