@@ -341,15 +341,26 @@ ScanPlan make_plan(long long N, int B, int m, int K, bool generic = false, int c
 // LDS reads a CU returns per clock when every lane reads at random: of 4-, 8- and 16-byte words.
 constexpr double kGather4 = 8.7, kGather8 = 8.5, kGather16 = 5.0;
 
-// Lookups (B * N * m) from which a batch is scanned by upper bounds.  Measured on catalogues of 2e4 to 1.3e6 items, batches of
-// 2 to 256 queries: the sample, the tables and one launch more (some 12 us together) are paid back from 7e7 lookups on at
-// K = 10 and m <= 8; longer rows cost more to prepare; a larger K means more items scored exactly.  With more than 256
-// results the lists leave room for half the queries only.  Candidate lists gain earlier: the rows are gathered once per
-// sixteen queries instead of once per query.
-double filter_min_lookups(int m, int K, bool subset) {
-    if (K > 256) return 2.0e9;
-    const double at_small_k = subset ? 2.5e7 : m <= 8 ? 7.0e7 : m == 16 ? 9.0e7 : m == 32 ? 1.3e8 : 2.0e8;
-    return K <= 12 ? at_small_k : at_small_k * (1.0 + K / 130.0);
+// Lookups (B * N * m) from which a batch is scanned by upper bounds.  Measured against the scans side by side on catalogues of
+// 2e4 to 1e7 items, batches of 2 to 300 queries, K from 10 to 500: the sample, the tables and one launch more (some 12 us
+// together) are paid back from 6e7 lookups on at m = 4; longer rows cost more to prepare, the most at m = 64 with many results.
+// Two queries fill half a word's fields; more than 256 make the sample take turns on the CUs, which costs two-byte sub-ids with
+// their larger tables most.  Candidate lists gain earlier: the rows are gathered once per sixteen queries, not once per query.
+double filter_min_lookups(int m, int K, int B, bool subset, int cw) {
+    if (subset) return m <= 8 ? 2.2e7 : 4.5e7;
+    double least = m == 4 ? 6.0e7 : m == 8 ? 6.5e7 : m == 16 ? 1.0e8 : m == 32 ? (K <= 64 ? 1.6e8 : 2.1e8) : K <= 64 ? 2.4e8 : K <= 128 ? 3.2e8 : 4.0e8;
+    if (B == 2) least *= 1.5;
+    if (cw == 2) least *= (m == 16 ? 1.3 : 1.0) * (B > 256 ? 2.5 : 1.0);
+    return least;
+}
+// ... and the items per result: with fewer, a sample that is an eighth of them gives too low a floor, and what passes it is
+// scored exactly (from tables in device memory: two-byte sub-ids' are large).  The more queries there are, the less the scans
+// side by side leave idle.  (m = 16 with sixteen-bit fields, more than 256 queries: against the batched kernel.)
+long long filter_min_items_per_result(int m, int K, int B, bool subset, bool w16, int cw) {
+    if (m == 16 && w16 && B > 256) return subset ? 600 : cw == 2 ? 1000 : 2000;
+    if (subset) return K > 128 ? 350 : 150;
+    if (cw == 2) return 2000;
+    return B <= 256 ? (K > 128 ? 800 : 500) : K > 128 ? 1300 : K > 64 ? 800 : 500;
 }
 
 // Whether a batch is scanned by upper bounds (scan_filter.hpp), and how.
@@ -360,13 +371,14 @@ void plan_filter(ScanPlan& p, long long N, int B, int m, int K, bool subset, int
     const bool rows = (cw == 1 && !subset) ? (m == 4 || m == 8 || m == 16 || m == 32 || m == 64) : (m == 4 || m == 8 || m == 16);
     if (!rows || N * m * cw < 16) return;
     const long long entries = (long long)m * (cw == 1 ? kLutStride : b);
-    if (!(force & 16) && (B < 2 || (double)B * (double)N * m < filter_min_lookups(m, K, subset) || N < 8 * entries ||
-                          N < (K > 128 ? 4000LL : 1000LL) * K))
+    // Fields: eight bits as long as a score's sum of roundings stays small against its spread.  At m = 16 the bound is loose
+    // by half a standard deviation: twenty times as many items as necessary pass near a high floor, a hundred at larger K (and
+    // large tables leave no room for the fine counts that sort them out).
+    const bool w16 = m >= 32 || (m == 16 && (K > 32 || entries > 16 * kLutStride));
+    if (!(force & 16) && (B < 2 || (double)B * (double)N * m < filter_min_lookups(m, K, B, subset, cw) || N < 8 * entries ||
+                          N < filter_min_items_per_result(m, K, B, subset, w16, cw) * K))
         return;
     if (filter_prepare_lds_bytes(entries, m) > kMaxLdsBytes) return;
-    // Fields: eight bits as long as a score's sum of roundings stays small against its spread.  At m = 16 the bound is loose
-    // by half a standard deviation: twenty times as many items as necessary pass near a high floor, a hundred at larger K.
-    const bool w16 = m >= 32 || (m == 16 && K > 32);
     const int fields = w16 ? 2 : 4;
     int cap = next_pow2(2 * K);
     if (cap < 128) cap = 128;
@@ -412,11 +424,11 @@ void plan_filter(ScanPlan& p, long long N, int B, int m, int K, bool subset, int
     const int sample_units = (row == 8 || row == 16 || row == 32) ? 2 : 1;
     p.f_sample = kFilterThreads * ((subset && row < 16) ? sample_units * 16 / row : sample_units);
     // The sample: n items cost n * m lookups of 4 bytes, and (K / n) of the catalogue then passes the first floor and is
-    // scored from device memory, an eighth as fast: least together at about 3.5 sqrt(K N).  Where the workgroups of a query
+    // scored from device memory, an eighth as fast: least together at about 5 sqrt(K N).  Where the workgroups of a query
     // share their floors those rise fast by themselves.
     p.f_share = nb > 1 && nb <= 16 && rounds / nb >= 32;
     const long long items_per_round = (long long)p.f_sample * N / units;
-    long long want = (long long)(3.5 * sqrt((double)K * (double)N)) / items_per_round;
+    long long want = (long long)(5.0 * sqrt((double)K * (double)N)) / items_per_round;
     if (p.f_share && want > 1) want = 1;
     if (want > N / 8 / items_per_round) want = N / 8 / items_per_round;
     if (want < 1) want = 1;

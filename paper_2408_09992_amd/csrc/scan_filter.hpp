@@ -32,8 +32,7 @@ constexpr float kFilterT0 = 80.0f;                // where the first T of a quer
 constexpr float kFilterUp = 0.02f;                // 256ths of a step a count is rounded up by more than it must be, against the
 constexpr float kFilterDown = 0.02f;              // rounding of its own computation; steps T is rounded down by, likewise
 constexpr int kSampleBins = 256;                  // histogram of a sample's scores
-constexpr int kFilterBest = 512;                  // sample scores a query's parts leave at most
-constexpr int kFilterCollect = 1024;              // ... and what a part collects to find its best
+constexpr int kFilterBest = 1280;                 // sample scores a query's parts leave at most
 
 struct FilterQuery {                              // one query's bounds, written by filter_prepare_kernel
     float off, inv;                               // units of a score s: (s - off) * inv
@@ -115,8 +114,8 @@ __device__ __forceinline__ float wave_sum_f32(float v) {     // (for bounds and 
 }
 
 __host__ __device__ inline size_t filter_prepare_lds_bytes(long long entries, int m) {
-    return align16((size_t)entries * sizeof(float)) + kSampleBins * sizeof(uint32_t) + align16(sizeof(Ctl)) + (size_t)m * 5 * sizeof(float) +
-           (kFilterCollect + 4) * sizeof(float);
+    const size_t pieces = (size_t)m * (((size_t)entries / m + 4 * kWave - 1) / (4 * kWave));
+    return align16((size_t)entries * sizeof(float)) + kSampleBins * sizeof(uint32_t) + align16(sizeof(Ctl)) + ((size_t)m + 1 + 3 * pieces) * sizeof(float);
 }
 
 // The sample.  grid = (parts, B).  Every part scores a sample of its own exactly, in rounds of kSampleItems per thread, and,
@@ -126,7 +125,7 @@ __host__ __device__ inline size_t filter_prepare_lds_bytes(long long entries, in
 // few queries would leave most CUs idle with one part each (16 queries x 16 parts x 4096 items cost no more time than
 // 16 x 4096), and a round more costs less than a part more, which loads the tables again.
 // What it costs is latency: the tables' way from memory, then kSampleItems x M lookups per thread and round (4096 items at
-// m = 8: 1.6 us), a histogram of the first round, the counts.
+// m = 8: 1.6 us), a histogram of the threads' best, the counts.
 //   M, CW: splits, bytes per sub-id; SUB: the sample is taken from a candidate list
 template <int M, int CW, bool SUB>
 __global__ __launch_bounds__(kFilterThreads) void filter_prepare_kernel(FilterArgs a) {
@@ -139,9 +138,9 @@ __global__ __launch_bounds__(kFilterThreads) void filter_prepare_kernel(FilterAr
     float* lut = reinterpret_cast<float*>(smem);
     uint32_t* hist = reinterpret_cast<uint32_t*>(smem + align16((size_t)a.entries * sizeof(float)));
     Ctl* ctl = reinterpret_cast<Ctl*>(hist + kSampleBins);
-    float* stat = reinterpret_cast<float*>(reinterpret_cast<unsigned char*>(ctl) + align16(sizeof(Ctl)));   // [M][4]: max, min, mean, max |.|; then [M] bases
-    float* found = stat + 5 * M;                              // [kFilterCollect]
-    int* n_found = reinterpret_cast<int*>(found + kFilterCollect);
+    float* bases = reinterpret_cast<float*>(reinterpret_cast<unsigned char*>(ctl) + align16(sizeof(Ctl)));   // [M]
+    int* n_found = reinterpret_cast<int*>(bases + M);
+    float* piece = reinterpret_cast<float*>(n_found + 1);     // [pieces of the tables][3]: max, min, sum
     const float* Sq = a.S + (size_t)q * M * b;
 
     // ---- the sample's rows: units spread evenly over the catalogue (or the list), the parts' and rounds' interleaved
@@ -169,39 +168,52 @@ __global__ __launch_bounds__(kFilterThreads) void filter_prepare_kernel(FilterAr
         }
     };
     uint32_t w[Sh::kSampleWords];
-    fetch(0, w);
+    fetch(0, w);                                              // (rounds >= 1)
 
-    // ---- the query's tables to LDS; a wave takes whole splits and finds their extremes on the way
-    for (int k = wave; k < M; k += NW) {
+    // ---- the query's tables to LDS, in pieces of 256 entries, their extremes on the way
+    const int pieces = (stride + 4 * kWave - 1) / (4 * kWave);   // per split (one-byte sub-ids: one)
+    auto load_piece = [&](int p, float (&v)[4]) {
+        const int k = CW == 1 ? p : p / pieces, j0 = CW == 1 ? 0 : (p % pieces) * 4 * kWave;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int j = j0 + i * kWave + lane;
+            v[i] = (p < M * pieces && j < b) ? Sq[(size_t)k * b + j] : 0.0f;
+        }
+    };
+    auto keep_piece = [&](int p, const float (&v)[4]) {
+        if (p >= M * pieces) return;
+        const int k = CW == 1 ? p : p / pieces, j0 = CW == 1 ? 0 : (p % pieces) * 4 * kWave;
         float mx = -__builtin_inff(), mn = __builtin_inff(), sum = 0.0f;
-        for (int j0 = 0; j0 < stride; j0 += 4 * kWave) {
-            float v[4];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int j = j0 + i * kWave + lane;
-                v[i] = j < b ? Sq[(size_t)k * b + j] : 0.0f;
-            }
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int j = j0 + i * kWave + lane;
-                if (j < stride) lut[(size_t)k * stride + j] = v[i];
-                if (j < b) { mx = fmaxf(mx, v[i]); mn = fminf(mn, v[i]); sum += v[i]; }
-            }
+        for (int i = 0; i < 4; ++i) {
+            const int j = j0 + i * kWave + lane;
+            if (j < stride) lut[(size_t)k * stride + j] = v[i];
+            if (j < b) { mx = fmaxf(mx, v[i]); mn = fminf(mn, v[i]); sum += v[i]; }
         }
         wave_minmax(mn, mx);
         sum = wave_sum_f32(sum);
-        if (lane == 0) {
-            stat[4 * k] = mx; stat[4 * k + 1] = mn; stat[4 * k + 2] = sum / (float)b; stat[4 * k + 3] = fmaxf(fabsf(mx), fabsf(mn));
-        }
+        if (lane == 0) { piece[3 * p] = mx; piece[3 * p + 1] = mn; piece[3 * p + 2] = sum; }
+    };
+    constexpr int kAhead = CW == 1 ? (M + NW - 1) / NW : 4;   // pieces of a wave on their way together
+    for (int p0 = wave; p0 < M * pieces; p0 += kAhead * NW) {
+        float v[kAhead][4];
+#pragma unroll
+        for (int i = 0; i < kAhead; ++i) load_piece(p0 + i * NW, v[i]);
+#pragma unroll
+        for (int i = 0; i < kAhead; ++i) keep_piece(p0 + i * NW, v[i]);
     }
     for (int i = tid; i < kSampleBins; i += NT) hist[i] = 0;
     if (tid == 0) *n_found = 0;
     __syncthreads();
 
-    // ---- the first round, scored; a floor that at least K of its items exceed
+    // ---- all rounds, scored: a thread keeps its best score (of its even and its odd items, when K is large).  At least K of
+    // these exceed the cut, and hardly more of all scores do: they are a histogram's 1024 counts instead of thousands that
+    // would have to be collected (64 queries, K = 120: 28 us, collecting and ranking, -> 10)
     constexpr int kPerLoad = Sh::kSampleItems / kLoads;
     auto have = [&](int e) { return (uint32_t)((e / kPerLoad) * NT + tid) < n_sample; };
-    auto score = [&](const uint32_t (&w)[Sh::kSampleWords], float (&sc)[Sh::kSampleItems]) {
+    const float ninf = -__builtin_inff();
+    float best[2] = {ninf, ninf};
+    for (int round = 0; round < a.rounds; ++round) {
 #pragma unroll
         for (int e = 0; e < Sh::kSampleItems; ++e) {
             float acc = 0.0f;
@@ -210,81 +222,59 @@ __global__ __launch_bounds__(kFilterThreads) void filter_prepare_kernel(FilterAr
                 const float v = lut[(size_t)k * stride + filter_sub_id<M, CW>(w, e, k)];
                 acc = k == 0 ? v : acc + v;
             }
-            sc[e] = acc;
+            if (have(e)) best[e & 1] = fmaxf(best[e & 1], acc);
         }
-    };
-    float sc[Sh::kSampleItems];
-    score(w, sc);
-    if (a.rounds > 1) fetch(1, w);
-    float mn = __builtin_inff(), mx = -__builtin_inff();
-#pragma unroll
-    for (int e = 0; e < Sh::kSampleItems; ++e)
-        if (have(e)) { mn = fminf(mn, sc[e]); mx = fmaxf(mx, sc[e]); }
+        if (round + 1 < a.rounds) fetch(round + 1, w);
+    }
+    const bool both = K > NT / 4 && Sh::kSampleItems > 1;
+    if (!both) { best[0] = fmaxf(best[0], best[1]); best[1] = ninf; }
+    float mn = fminf(best[0] > ninf ? best[0] : -ninf, best[1] > ninf ? best[1] : -ninf), mx = fmaxf(best[0], best[1]);
     float lo, scale;
-    set_range<NW>(mn, mx, ctl, tid, lo, scale, 1.25f);        // (room on top for the scores of later rounds)
+    set_range<NW>(mn, mx, ctl, tid, lo, scale);
     scale *= (float)kSampleBins / (float)kBins;
     if (tid == 0) ctl->scale = scale;
 #pragma unroll
-    for (int e = 0; e < Sh::kSampleItems; ++e)
-        if (have(e)) atomicAdd(&hist[bucket_of<kSampleBins>(sc[e], lo, scale)], 1u);
+    for (int h = 0; h < 2; ++h)
+        if (best[h] > ninf) atomicAdd(&hist[bucket_of<kSampleBins>(best[h], lo, scale)], 1u);
     __syncthreads();
     if (tid < kWave) find_cut<kSampleBins>(hist, K, ctl, lane);
     __syncthreads();
-
-    if (a.parts > 1 || a.rounds > 1) {
-        // scores above the cut (a few more than K), and of further rounds those that exceed it too; any of them will do when
-        // ties make them too many
-        const float cut = ctl->cut;
-        auto collect = [&](int first_round) {
+    const float cut = ctl->cut;
+    if (a.parts > 1) {
+        // this part's best scores, in any order: those above the cut that so many exceed (more, for want of buckets: as many
+        // as there is room for); fewer than asked for are filled up with -inf
+        const int r = a.best_per_part;
+        float* out = a.best + ((size_t)q * a.parts + part) * r;
+        __syncthreads();
+        if (tid < kWave) find_cut<kSampleBins>(hist, r - r / 8, ctl, lane);
+        __syncthreads();
+        const float part_cut = ctl->cut;
 #pragma unroll
-            for (int e = 0; e < Sh::kSampleItems; ++e) {
-                if (have(e) && sc[e] > cut) {
-                    const int pos = atomicAdd(n_found, 1);
-                    if (pos < kFilterCollect) found[pos] = sc[e];
-                    if (first_round == 0) atomicAdd(&hist[bucket_of<kSampleBins>(sc[e], lo, scale)], 1u);
-                }
+        for (int h = 0; h < 2; ++h) {
+            if (best[h] > part_cut) {
+                const int pos = atomicAdd(n_found, 1);
+                if (pos < r) out[pos] = best[h];
             }
-        };
-        collect(1);
-        for (int round = 1; round < a.rounds; ++round) {
-            score(w, sc);
-            if (round + 1 < a.rounds) fetch(round + 1, w);
-            collect(0);
         }
         __syncthreads();
-        if (a.rounds > 1) {
-            if (tid < kWave) find_cut<kSampleBins>(hist, K, ctl, lane);
-            __syncthreads();
-        }
-        if (a.parts > 1) {
-            // this part's best scores, ranked among those above the last cut; fewer than asked for are filled up with -inf
-            const int n = *n_found < kFilterCollect ? *n_found : kFilterCollect, r = a.best_per_part;
-            const float last_cut = ctl->cut;
-            float* out = a.best + ((size_t)q * a.parts + part) * r;
-            int above = 0;
-            for (int t0 = 0; t0 < n; t0 += NT) {              // (n <= NT: one trip)
-                const int t = t0 + tid;
-                const float mine = t < n ? found[t] : -__builtin_inff();
-                if (t < n && mine > last_cut) {
-                    int rank = 0;
-                    for (int u = 0; u < n; ++u) rank += (found[u] > mine || (found[u] == mine && u < t)) ? 1 : 0;
-                    if (rank < r) out[rank] = mine;
-                }
-                above += __syncthreads_count(t < n && mine > last_cut);
-            }
-            for (int t = above + tid; t < r; t += NT) out[t] = -__builtin_inff();
-        }
+        for (int t = *n_found + tid; t < r; t += NT) out[t] = ninf;
         if (part != 0) return;                                // (the same for the whole workgroup)
     }
 
     // ---- step and bases (every wave for itself: lane k holds split k)
     const bool mine = lane < M;
-    const float s_mx = mine ? stat[4 * lane] : 0.0f, s_mn = mine ? stat[4 * lane + 1] : 0.0f, s_mean = mine ? stat[4 * lane + 2] : 0.0f;
-    const float sum_max = wave_sum_f32(s_mx), sum_min = wave_sum_f32(s_mn), sum_abs = wave_sum_f32(mine ? stat[4 * lane + 3] : 0.0f);
+    float s_mx = -__builtin_inff(), s_mn = __builtin_inff(), s_mean = 0.0f;
+    for (int p = 0; p < pieces && mine; ++p) {
+        const float* x = piece + 3 * (lane * pieces + p);
+        s_mx = fmaxf(s_mx, x[0]); s_mn = fminf(s_mn, x[1]); s_mean += x[2];
+    }
+    if (!mine) s_mx = s_mn = 0.0f;
+    s_mean = s_mean / (float)b;
+    const float sum_max = wave_sum_f32(s_mx), sum_min = wave_sum_f32(s_mn), sum_abs = wave_sum_f32(fmaxf(fabsf(s_mx), fabsf(s_mn)));
     const float spread = wave_sum_f32(s_mx - s_mean);
     // what fp32 chains of M additions (scores, sums of bases) can be off by
     const float slack = 4.0f * (float)(M + 1) * 5.9604645e-8f * sum_abs;
-    const float floor_s = fmaxf(ctl->cut, sum_min - slack);   // (the cut: at least K of the part's items exceed it)
+    const float floor_s = fmaxf(cut, sum_min - slack);        // (at least K of the part's items exceed the cut)
     float step = (sum_max - floor_s + 2.0f * slack) / (float)(kFilterSpan - a.spare);
     float inv = 1.0f / step;
     if (!(step > 0.0f) || !(inv < 1.0e30f) || !(step < 1.0e30f)) { inv = 0.0f; step = 0.0f; }   // degenerate: T stays 0, every item is scored
@@ -298,7 +288,7 @@ __global__ __launch_bounds__(kFilterThreads) void filter_prepare_kernel(FilterAr
         t = t < 0 ? 0 : (t > kFilterSpan + 1 ? kFilterSpan + 1 : t);
         a.query[q] = FilterQuery{off, inv, t, 0};
     }
-    if (wave == 0 && mine) stat[4 * M + lane] = base;
+    if (wave == 0 && mine) bases[lane] = base;
     __syncthreads();
 
     // ---- counts, two entries per thread and store
@@ -309,7 +299,7 @@ __global__ __launch_bounds__(kFilterThreads) void filter_prepare_kernel(FilterAr
 #pragma unroll
         for (int c = 0; c < 2; ++c) {
             const uint32_t e = (uint32_t)(i * 2 + c), k = e / (uint32_t)stride;
-            const float x = ceilf((lut[e] - stat[4 * M + k]) * inv256 + kFilterUp);
+            const float x = ceilf((lut[e] - bases[k]) * inv256 + kFilterUp);
             word |= (uint32_t)fminf(fmaxf(x, 0.0f), 65535.0f) << (c * 16);
         }
         out[i] = word;
@@ -503,18 +493,23 @@ __global__ __launch_bounds__(kFilterThreads) void scan_filter_kernel(FilterArgs 
             // the K-th best of the parts' scores, to 16 bits of its order-preserving image: K of them reach it
             const int n = a.parts * a.best_per_part;
             const float* v = a.best + (size_t)(q0 + q) * n;
-            uint32_t o[kFilterBest / kWave];
-#pragma unroll
-            for (int i = 0; i < kFilterBest / kWave; ++i) o[i] = i * kWave + lane < n ? orderable_bits(v[i * kWave + lane]) : 0u;
             uint32_t at = 0;
-            for (uint32_t bit = 0x80000000u; bit >= 0x10000u; bit >>= 1) {
-                const uint32_t t = at | bit;
-                int c = 0;
+            auto search = [&](auto per_lane) {
+                constexpr int R = decltype(per_lane)::value;
+                uint32_t o[R];
 #pragma unroll
-                for (int i = 0; i < kFilterBest / kWave; ++i)
-                    if (i * kWave < n) c += __popcll(__ballot(o[i] >= t));
-                if (c >= K) at = t;
-            }
+                for (int i = 0; i < R; ++i) o[i] = i * kWave + lane < n ? orderable_bits(v[i * kWave + lane]) : 0u;
+                for (uint32_t bit = 0x80000000u; bit >= 0x10000u; bit >>= 1) {
+                    const uint32_t t = at | bit;
+                    int c = 0;
+#pragma unroll
+                    for (int i = 0; i < R; ++i) c += __popcll(__ballot(o[i] >= t));
+                    if (c >= K) at = t;
+                }
+            };
+            if (n <= kWave) search(std::integral_constant<int, 1>());
+            else if (n <= 4 * kWave) search(std::integral_constant<int, 4>());
+            else search(std::integral_constant<int, kFilterBest / kWave>());
             const float f = float_of_orderable(at);
             if (p.inv > 0.0f && f == f && f > -__builtin_inff()) {
                 const int t = units_of_score(f, p);
