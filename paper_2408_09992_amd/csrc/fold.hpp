@@ -14,8 +14,8 @@ struct FoldArgs {
     uint64_t* stamps;          // STAMP instances only: wall-clock stamps, kStampSlots per wave
 };
 
-constexpr int kFoldThreads = 1024;                // a few queries: as many threads as a workgroup has
-constexpr int kFoldThreadsMany = 256;             // many queries: several workgroups per CU
+constexpr int kFoldThreads = 1024;                // a CU per query: as many threads as a workgroup has (238 queries, K = 440: 8.8 us with 256, 5.7)
+constexpr int kFoldThreadsMany = 256;             // more queries: several workgroups per CU (1024 queries, K = 100: 13.6 us with 1024, 8.3)
 constexpr int kFoldSlots = 4096;                  // keys read at first: nlists * chunk at most
 constexpr int kFoldLists = 1024;                  // lists per query at most
 constexpr int kFoldCand = 2048;                   // candidates ranked at most; more (heavy ties in few lists) take the slow path

@@ -864,7 +864,7 @@ int enqueue_fold(const ScanPlan& p, int B, int K, void* workspace, int* out_ids,
     }
     if (nlists > kFoldLists || (long long)nlists * f.chunk > kFoldSlots) return PQ_ERR_UNSUPPORTED;   // (no plan makes that many)
     if (stamps != nullptr) return record_hip(launch(fold_lists_kernel<kFoldThreads, true>, dim3(1, B), kFoldThreads, p.fold_lds, st, f));
-    if (B < 64) return record_hip(launch(fold_lists_kernel<kFoldThreads>, dim3(1, B), kFoldThreads, p.fold_lds, st, f));
+    if (B <= kAssumedCUs) return record_hip(launch(fold_lists_kernel<kFoldThreads>, dim3(1, B), kFoldThreads, p.fold_lds, st, f));
     return record_hip(launch(fold_lists_kernel<kFoldThreadsMany>, dim3(1, B), kFoldThreadsMany, p.fold_lds, st, f));
 }
 

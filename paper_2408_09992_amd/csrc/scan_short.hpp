@@ -58,6 +58,7 @@ __global__ __launch_bounds__(NT, M * CW <= 16 && U <= 3 ? 8 : 1) void scan_short
     constexpr int kHeld = CW == 1 ? short_held_units(M) : short16_held_units(M);
     constexpr int kSure = short_sure_units(U, kHeld);          // slots that lie wholly inside the catalogue
     constexpr int kRingUnits = U <= kHeld ? U : (VPU >= 4 || U * IPV > 48 ? 4 : 8);   // units whose codes are on their way or here
+    constexpr int kWindow = VPU >= 2 ? 1 : 2;                  // units whose lookups are under way together
     static_assert(U >= 1 && U <= (CW == 1 ? short_max_units(M) : short16_max_units(M)), "units per thread");
     __shared__ __align__(16) float lut_static[CW == 1 ? M * kLutStride : 4];
     extern __shared__ __align__(16) unsigned char smem[];
@@ -166,7 +167,7 @@ __global__ __launch_bounds__(NT, M * CW <= 16 && U <= 3 ? 8 : 1) void scan_short
             // the next unit's lookups wait for this unit's scores, or the compiler moves every unit's loads and lookups to the
             // front and runs out of registers
 #pragma unroll
-            for (int j = 0; j < 4 * VPU; ++j) asm volatile("" : "+v"(w[(u + 1) % kRingUnits][j]) : "v"(part[0]));
+            for (int j = 0; j < 4 * VPU; ++j) asm volatile("" : "+v"(w[(u + kWindow) % kRingUnits][j]) : "v"(part[0]));
         }
 #pragma unroll
         for (int e = 0; e < IPV; ++e) sc[u * IPV + e] = have ? part[e] : empty_score();

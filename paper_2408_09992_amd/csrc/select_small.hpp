@@ -206,7 +206,7 @@ __device__ __forceinline__ void select_small_k(const float (&sc)[R], IdOf&& id_o
 }
 
 // ---- larger K
-constexpr int kMidCand = 1536;                        // keys of the candidate array
+constexpr int kMidCand = 1408;                        // keys of the candidate array
 constexpr int kMidBins = 256;                         // buckets of the histogram of the threads' best scores
 
 template <int NT>
@@ -323,22 +323,22 @@ __device__ __forceinline__ void select_mid_k(const float (&sc)[R], IdOf&& id_of,
         }
         scale = hi > lo ? (float)kBins / (hi - lo) : 0.0f;
         if (!(scale > 0.0f) || scale > 3.0e38f) scale = 0.0f;
-        if (!bucket_sort<NT, kMidCand / NT>(L.cand, n, lo, scale, L.hist, tid)) {
+        if (!bucket_sort<NT, (kMidCand + NT - 1) / NT>(L.cand, n, lo, scale, L.hist, tid)) {
             // (too many in one bucket: by counting, from registers to their places)
-            uint64_t mine[kMidCand / NT];
-            int rank[kMidCand / NT];
+            uint64_t mine[(kMidCand + NT - 1) / NT];
+            int rank[(kMidCand + NT - 1) / NT];
 #pragma unroll
-            for (int r = 0; r < kMidCand / NT; ++r) {
+            for (int r = 0; r < (kMidCand + NT - 1) / NT; ++r) {
                 mine[r] = r * NT + tid < n ? L.cand[r * NT + tid] : 0ull;
                 rank[r] = 0;
             }
             for (int u = 0; u < n; ++u) {
                 const uint64_t x = L.cand[u];
 #pragma unroll
-                for (int r = 0; r < kMidCand / NT; ++r) rank[r] += x > mine[r];
+                for (int r = 0; r < (kMidCand + NT - 1) / NT; ++r) rank[r] += x > mine[r];
             }
 #pragma unroll
-            for (int r = 0; r < kMidCand / NT; ++r)
+            for (int r = 0; r < (kMidCand + NT - 1) / NT; ++r)
                 if (mine[r] != 0ull && rank[r] < K) emit(rank[r], mine[r]);
             for (int t = n + tid; t < K; t += NT) emit(t, 0ull);
             stamp<STAMP>(rec, kStampSelected, lane);
