@@ -678,7 +678,7 @@ hipError_t launch_filter(const ScanPlan& p, const FilterArgs& a, hipStream_t st)
             if (p.f_words == 4 && p.f_fine) return go(scan_filter_kernel<8, 1, 4, false, false, true, true>);
         }
         if constexpr (M == 16 && CW == 1 && !W16 && !SUB) {
-            if (p.f_words == 4 && !p.f_fine) return go(scan_filter_kernel<16, 1, 4, false, false, false, true>);
+            if (p.f_words == 2 && p.f_fine) return go(scan_filter_kernel<16, 1, 2, false, false, true, true>);
         }
         return hipErrorInvalidValue;                         // (pq_measure_step_stamps() has checked)
     }
@@ -687,10 +687,13 @@ hipError_t launch_filter(const ScanPlan& p, const FilterArgs& a, hipStream_t st)
             switch (p.f_words) {
                 case 1: return go(scan_filter_kernel<M, CW, 1, W16, SUB, true>);
                 case 2: return go(scan_filter_kernel<M, CW, 2, W16, SUB, true>);
-                default: return go(scan_filter_kernel<M, CW, 4, W16, SUB, true>);
+                default:
+                    if constexpr (M < 16 || CW == 2) return go(scan_filter_kernel<M, CW, 4, W16, SUB, true>);
             }
         }
     }
+    if constexpr (M == 16 && !W16) return hipErrorInvalidValue;   // (the plan never asks for it)
+    else
     switch (p.f_words) {
         case 1: return go(scan_filter_kernel<M, CW, 1, W16, SUB, false>);
         case 2: return go(scan_filter_kernel<M, CW, 2, W16, SUB, false>);
@@ -1059,7 +1062,7 @@ int pq_measure_step_stamps(const float* queries, const float* centroids, const u
     if (stamps_bytes < PQ_STAMP_BYTES) return PQ_ERR_WORKSPACE;
     static_assert(PQ_STAMP_SLOTS == kStampSlots, "header and kernels agree on the record size");
     const ScanPlan p = make_plan(N, B, m, K);
-    if (p.filter ? (p.f_words != 4 || p.f_w16 || !(m == 8 ? p.f_fine : (m == 16 && !p.f_fine))) : !(p.tiled || m == 8))
+    if (p.filter ? (p.f_w16 || !p.f_fine || !((m == 8 && p.f_words == 4) || (m == 16 && p.f_words == 2))) : !(p.tiled || m == 8))
         return PQ_ERR_UNSUPPORTED;                             // (scan kernels with a measurement instance)
     const int waves = p.filter ? kFilterWaves : (!p.tiled && p.big) ? kMaxWaves : kWaves;
     const long long scan_groups = p.filter ? (long long)p.nblk * ((B + p.f_queries - 1) / p.f_queries) : p.tiled ? (long long)p.nblk * ((B + kQ - 1) / kQ) : (long long)p.nblk * B;

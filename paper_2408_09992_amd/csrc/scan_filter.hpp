@@ -356,16 +356,16 @@ __global__ __launch_bounds__(kFilterThreads) void scan_filter_kernel(FilterArgs 
     uint32_t* const start = reinterpret_cast<uint32_t*>(par + QT);                // [W] the fields' start values: 128 - T, or 256 times that
     uint32_t* const next_unit = start + 4;
 
-    // ---- units of work: a wave's share (64 lanes x kVecs vectors) of one of this workgroup's rounds
+    // ---- units of work: a wave's share (64 lanes x kVecs vectors), the workgroups' interleaved one by one (whole rounds of a
+    // workgroup's waves left some with a twentieth more than others: 5M items at m = 16, 256 workgroups)
     const uint32_t total = (uint32_t)((P <= 16 && !SUB) ? (a.N * P) / 16 : a.N);  // whole vectors, or items / candidates
     constexpr uint32_t kPerLane = (P <= 16 && !SUB) ? Sh::kVecs : NI;             // ... per lane and unit
-    constexpr uint32_t kRound = NT * kPerLane;
-    const uint32_t rounds = (total + kRound - 1) / kRound;
-    const uint32_t my_rounds = (uint32_t)blk < rounds ? (rounds - blk + nblk - 1) / nblk : 0;
-    const uint32_t units = my_rounds * NW;
+    constexpr uint32_t kPerUnit = kWave * kPerLane;
+    const uint32_t all_units = (total + kPerUnit - 1) / kPerUnit;
+    const uint32_t units = (uint32_t)blk < all_units ? (all_units - blk + nblk - 1) / nblk : 0;
     const uint32_t last = total - 1;
     auto first_of = [&](uint32_t u) -> uint32_t {             // the lane's first element of unit u; the others follow at 64
-        return ((uint32_t)blk + (u / NW) * (uint32_t)nblk) * kRound + (u % NW) * (kWave * kPerLane) + (uint32_t)lane;
+        return (u * (uint32_t)nblk + (uint32_t)blk) * kPerUnit + (uint32_t)lane;
     };
     auto fetch_ids = [&](uint32_t u, uint32_t (&id)[NI]) {    // candidate lists: the items' ids
         if constexpr (SUB) {
