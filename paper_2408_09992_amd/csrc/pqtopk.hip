@@ -356,10 +356,13 @@ double filter_min_lookups(int m, int K, int B, bool subset, int cw) {
 // ... and the items per result: with fewer, a sample that is an eighth of them gives too low a floor, and what passes it is
 // scored exactly (from tables in device memory: two-byte sub-ids' are large).  The more queries there are, the less the scans
 // side by side leave idle.  (m = 16 with sixteen-bit fields, more than 256 queries: against the batched kernel.)
-long long filter_min_items_per_result(int m, int K, int B, bool subset, bool w16, int cw) {
+// The catalogue itself has at least eight items per table entry, 3.5 with long rows (m = 64, 100 queries of 60,000 items, K = 10: 87 ->
+// 60 us).
+long long filter_min_items_per_result(long long N, int m, int K, int B, bool subset, bool w16, int cw) {
     if (m == 16 && w16 && B > 256) return subset ? 600 : cw == 2 ? 1000 : 2000;
     if (subset) return K > 128 ? 350 : 150;
     if (cw == 2) return 2000;
+    if (m >= 32) return N < 5LL * m * kLutStride ? 2000 : 1000;
     return B <= 256 ? (K > 128 ? 800 : 500) : K > 128 ? 1300 : K > 64 ? 800 : 500;
 }
 
@@ -375,8 +378,8 @@ void plan_filter(ScanPlan& p, long long N, int B, int m, int K, bool subset, int
     // by half a standard deviation: twenty times as many items as necessary pass near a high floor, a hundred at larger K (and
     // large tables leave no room for the fine counts that sort them out).
     const bool w16 = m >= 32 || (m == 16 && (K > 32 || entries > 16 * kLutStride));
-    if (!(force & 16) && (B < 2 || (double)B * (double)N * m < filter_min_lookups(m, K, B, subset, cw) || N < 8 * entries ||
-                          N < filter_min_items_per_result(m, K, B, subset, w16, cw) * K))
+    if (!(force & 16) && (B < 2 || (double)B * (double)N * m < filter_min_lookups(m, K, B, subset, cw) || 2 * N < (m >= 32 ? 7 : 16) * entries ||
+                          N < filter_min_items_per_result(N, m, K, B, subset, w16, cw) * K))
         return;
     if (filter_prepare_lds_bytes(entries, m) > kMaxLdsBytes) return;
     const int fields = w16 ? 2 : 4;
