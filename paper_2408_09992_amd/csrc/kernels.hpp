@@ -17,6 +17,7 @@ namespace pqk {
 #include "select_small.hpp"
 #include "scan_single.hpp"
 #include "scan_short.hpp"
+#include "scan_long.hpp"
 #include "scan_subset.hpp"
 #include "scan_batched.hpp"
 #include "scan_filter.hpp"
@@ -81,6 +82,9 @@ namespace pqk {
     PQ_SHORT16_U(X, 8, 16) PQ_SHORT16_U(X, 8, 24) PQ_SHORT16_U(X, 8, 32) PQ_SHORT16_U(X, 8, 48) \
     PQ_SHORT16_U(X, 16, 8) PQ_SHORT16_U(X, 16, 12) PQ_SHORT16_U(X, 16, 16) PQ_SHORT16_U(X, 16, 24) PQ_SHORT16_U(X, 16, 32) \
     PQ_SHORT16_U(X, 16, 1) PQ_SHORT16_U(X, 16, 2) PQ_SHORT16_U(X, 16, 3) PQ_SHORT16_U(X, 16, 4) PQ_SHORT16_U(X, 16, 5) PQ_SHORT16_U(X, 16, 6)
+// scan_long_kernel<M, CW, C>
+#define PQ_LONG_INSTANCES(X) \
+    X(4, 1, kTableCopies) X(8, 1, kTableCopies) X(16, 1, 1) X(32, 1, 1) X(64, 1, 1) X(4, 2, 1) X(8, 2, 1) X(16, 2, 1)
 // scan_subset_kernel<M, U, NT>: rows of 4, 8, 16 bytes, every number of vectors per thread
 #define PQ_SUBSET_M(X, M) X(M, 1, kThreads) X(M, 2, kThreads) X(M, 3, kThreads) X(M, 4, kThreads) X(M, 5, kThreads) \
     X(M, 6, kThreads) X(M, 7, kThreads) X(M, 8, kThreads)
@@ -115,6 +119,8 @@ namespace pqk {
 #define PQ_SHORT_EXTERN(M, U, NT, ST) extern PQ_SHORT_DEFINE(M, U, NT, ST)
 #define PQ_SHORT16_DEFINE(M, U, NT, ST, CW) template __global__ void scan_short_kernel<M, U, NT, ST, CW>(const uint8_t*, const float*, void*, float*, uint32_t, int, int, uint64_t*);
 #define PQ_SHORT16_EXTERN(M, U, NT, ST, CW) extern PQ_SHORT16_DEFINE(M, U, NT, ST, CW)
+#define PQ_LONG_DEFINE(M, CW, C) template __global__ void scan_long_kernel<M, CW, C>(const uint8_t*, const float*, void*, float*, uint32_t, int, int);
+#define PQ_LONG_EXTERN(M, CW, C) extern PQ_LONG_DEFINE(M, CW, C)
 #define PQ_SUBSET_DEFINE(M, U, NT) template __global__ void scan_subset_kernel<M, U, NT>(const uint8_t*, const int*, const float*, void*, float*, uint32_t, uint32_t, int, int);
 #define PQ_SUBSET_EXTERN(M, U, NT) extern PQ_SUBSET_DEFINE(M, U, NT)
 #define PQ_FILTER_DEFINE(M, CW, W, W16, SUB, FINE) template __global__ void scan_filter_kernel<M, CW, W, W16, SUB, FINE>(FilterArgs);
@@ -138,6 +144,7 @@ PQ_SHORT_INSTANCES_B(PQ_SHORT_EXTERN)
 PQ_SHORT_INSTANCES_C(PQ_SHORT_EXTERN)
 PQ_SHORT_INSTANCES_D(PQ_SHORT_EXTERN)
 PQ_SHORT_INSTANCES_E(PQ_SHORT_EXTERN)
+PQ_LONG_INSTANCES(PQ_LONG_EXTERN)
 PQ_SUBSET_INSTANCES(PQ_SUBSET_EXTERN)
 PQ_SHORT16_INSTANCES(PQ_SHORT16_EXTERN)
 PQ_TILED_INSTANCES(PQ_TILED_EXTERN)

@@ -96,6 +96,7 @@ struct ScanPlan {
     bool glut;       // two-byte sub-ids: the m x b table does not fit LDS and is read from device memory
     bool short_scan; // scan_short_kernel: every workgroup's share fits its registers, K small
     int short_units; // ... units (code vectors, or items for m = 32, 64) a thread holds
+    bool long_scan;  // scan_long_kernel: one query's catalogue in segments
     bool short_subset; // scan_subset_kernel: a candidate list whose share per thread fits its registers, K small
     int subset_vecs;   // ... code vectors' worth of gathered rows a thread holds
     bool filter;       // filter_prepare_kernel + scan_filter_kernel: a batch scanned by integer upper bounds
@@ -162,6 +163,22 @@ double tiled_min_lookups(int m, int K) {
 // writes the result: the scan takes up to 3 us longer than spread over the chip, the fold's launch (3 us of host time, 3.7 us
 // from the scan's end to the result) is saved.
 constexpr long long kDirectUnits(int row) { return row <= 16 ? 8 : row == 32 ? 4 : 2; }
+
+// Where one query's catalogue is scanned in segments (scan_long_kernel) and not by the general kernel's per-wave lists.  Measured at
+// 5e6 to 5e7 items, K from 3 to 512: with more than 256 results nearly always (1.2 to 3.6 times as fast) and for rows of 8 and 16 bytes of
+// two-byte sub-ids (1.08 to 1.26); otherwise while the first cut, the lists' merge and the sorting of full lists weigh more than the general kernel's
+// twice as many waves.
+bool long_scan_pays(long long N, int m, int K, int cw) {
+    if (cw == 2) return m == 4 ? K <= 256 || N <= 12000000 : m == 8 || (m == 16 && K > 256);
+    switch (m) {
+        case 4: return K > 256 || N <= 17000000;
+        case 8: return K > 256 || N <= 20000000 || (K > 80 && (K <= 128 || N <= 40000000));
+        case 16: return K > 80 || (K >= 32 && N <= 17000000);
+        case 32: return K > 128;
+        case 64: return K > 256;
+        default: return false;
+    }
+}
 
 // `generic`: plan for the generic kernel whatever m is (candidate-list scans use it: their rows are gathered)
 // `cw`, `b`: bytes per sub-id (1 or 2) and, for two-byte sub-ids, the alphabet size (it sizes the tables in LDS)
@@ -305,6 +322,21 @@ ScanPlan make_plan(long long N, int B, int m, int K, bool generic = false, int c
             }
         }
     }
+    // Longer catalogues of a single query are scanned in segments, one workgroup per CU.
+    p.long_scan = false;
+    if (!p.short_scan && p.vec && !generic && !p.tiled && B == 1 && long_scan_pays(N, m, K, cw) &&
+        !(g_force_general.load(std::memory_order_relaxed) & 1)) {
+        const size_t table = cw == 1 ? lut_floats * (m <= 8 ? kTableCopies : 1) * sizeof(float) : table16;
+        if (table + sizeof(LongSelectLds<kLongThreads>) <= kMaxLdsBytes) {
+            p.long_scan = true;
+            p.glut = false;
+            p.nblk = kAssumedCUs;
+            p.copies = cw == 1 && m <= 8 ? kTableCopies : 1;
+            p.big = true;
+            p.scan_dyn_lds = sizeof(LongSelectLds<kLongThreads>) + table16;
+            p.scan_lds = sizeof(LongSelectLds<kLongThreads>) + table;
+        }
+    }
     // Candidate lists (the `generic` plans) of rows of 4, 8 or 16 bytes, short enough for a thread to
     // hold its share: every row of a thread is requested at once and the selection comes straight from registers.
     // Same thin grid as the short scan.
@@ -418,7 +450,7 @@ void plan_filter(ScanPlan& p, long long N, int B, int m, int K, bool subset, int
         if (fill == 1 || us < best_us) { best_us = us; nb = cand; }
     }
     p.filter = true;
-    p.tiled = p.short_scan = p.short_subset = false;
+    p.tiled = p.short_scan = p.short_subset = p.long_scan = false;
     p.f_words = words;
     p.f_w16 = w16;
     p.f_queries = queries;
@@ -613,6 +645,23 @@ hipError_t launch_short(const ScanPlan& p, const ScanArgs& a, int B, int m, hipS
     }
 }
 
+template <int M, int CW, int C>
+hipError_t launch_long_m(const ScanPlan& p, const ScanArgs& a, int B, hipStream_t st) {
+    hipError_t e = allow_lds(scan_long_kernel<M, CW, C>, p.scan_dyn_lds);
+    if (e != hipSuccess) return e;
+    return launch(scan_long_kernel<M, CW, C>, dim3(p.nblk, B), kLongThreads, p.scan_dyn_lds, st, a.codes, a.S, out_of(a), scores_of(a), (uint32_t)a.N, a.b, a.K);
+}
+hipError_t launch_long(const ScanPlan& p, const ScanArgs& a, int B, int m, int cw, hipStream_t st) {
+    if (cw == 2) return m == 4 ? launch_long_m<4, 2, 1>(p, a, B, st) : m == 8 ? launch_long_m<8, 2, 1>(p, a, B, st) : launch_long_m<16, 2, 1>(p, a, B, st);
+    switch (m) {
+        case 4: return launch_long_m<4, 1, kTableCopies>(p, a, B, st);
+        case 8: return launch_long_m<8, 1, kTableCopies>(p, a, B, st);
+        case 16: return launch_long_m<16, 1, 1>(p, a, B, st);
+        case 32: return launch_long_m<32, 1, 1>(p, a, B, st);
+        default: return launch_long_m<64, 1, 1>(p, a, B, st);
+    }
+}
+
 template <int M, int U>
 hipError_t launch_short16_units(const ScanPlan& p, const ScanArgs& a, int B, hipStream_t st) {
     if constexpr (short_has(U, short16_held_units(M), short16_max_units(M))) {
@@ -774,6 +823,10 @@ int enqueue_scan(const ScanPlan& p, const uint8_t* codes, const float* S, long l
     if (p.short_scan) {
         if (stamps != nullptr && m != 8) return PQ_ERR_UNSUPPORTED;
         return record_hip(launch_short(p, a, B, m, st));
+    }
+    if (p.long_scan) {
+        if (stamps != nullptr) return PQ_ERR_UNSUPPORTED;
+        return record_hip(launch_long(p, a, B, m, cw, st));
     }
     if (p.short_subset) {
         if (subset == nullptr || stamps != nullptr) return PQ_ERR_UNSUPPORTED;   // (the plan is only made for candidate lists)

@@ -285,7 +285,11 @@ __device__ __forceinline__ void select_mid_k(const float (&sc)[R], IdOf&& id_of,
             const uint64_t t = kth | (1ull << bit);
             int reach = 0;
 #pragma unroll
-            for (int i = 0; i < R; ++i) reach += __popcll(__ballot(sc[i] == sc[i] && make_key(sc[i] + 0.0f, id_of(i)) >= t));
+            for (int i = 0; i < R; ++i) {
+                float x = sc[i];                              // (made anew in every step: R keys do not fit the registers)
+                asm volatile("" : "+v"(x));
+                reach += __popcll(__ballot(x == x && make_key(x + 0.0f, id_of(i)) >= t));
+            }
             if (tid == 0) L.hist[bit] = 0u;
             __syncthreads();
             if (lane == 0) atomicAdd(&L.hist[bit], (uint32_t)reach);
@@ -296,8 +300,10 @@ __device__ __forceinline__ void select_mid_k(const float (&sc)[R], IdOf&& id_of,
         __syncthreads();
 #pragma unroll
         for (int i = 0; i < R; ++i) {
-            const uint64_t key = make_key(sc[i] + 0.0f, id_of(i));
-            if (sc[i] == sc[i] && key >= kth) L.cand[atomicAdd(&L.ncand, 1)] = key;
+            float x = sc[i];
+            asm volatile("" : "+v"(x));
+            const uint64_t key = make_key(x + 0.0f, id_of(i));
+            if (x == x && key >= kth) L.cand[atomicAdd(&L.ncand, 1)] = key;
         }
         __syncthreads();
         n = L.ncand;                                          // = K: keys are distinct

@@ -281,6 +281,27 @@ def test_short_scan_with_more_units_than_are_held_at_once(pq, oracle, m, wide):
         pq.pq_measure_force_general(prev)
 
 
+@pytest.mark.parametrize("m,wide,N,K", [(4, False, 8_400_003, 40), (8, False, 8_390_001, 1), (8, False, 12_700_001, 512), (16, False, 6_300_001, 100),
+                                        (32, False, 4_200_000, 200), (64, False, 4_194_305, 300), (4, True, 8_400_001, 512),
+                                        (8, True, 6_300_000, 100), (16, True, 4_194_305, 512)])
+def test_single_query_in_segments(pq, oracle, m, wide, N, K):
+    """More items than one set of registers holds: a last segment of a few units, ties and ascending scores that overflow the
+    candidates (all once more with barriers; cutting back; the exact K-th key)."""
+    rng = np.random.default_rng(m + K)
+    b = 300 if wide else 256
+    codes = rng.integers(0, b, (N, m), dtype=np.uint16 if wide else np.uint8)
+    check = assert_same_topk_u16 if wide else assert_same_topk
+    S = tables(m, 1, m, b)
+    check(pq, oracle, codes, S, K, "random")
+    check(pq, oracle, codes, np.round(S).astype(np.float32) * (np.arange(m) < 2)[None, :, None].astype(np.float32), K, "ties")
+    i = np.arange(N)
+    codes[:, 0], codes[:, 1], codes[:, 2] = i >> 16, (i >> 8) & 255, i & 255
+    S[:] = 0.0
+    for k, scale in enumerate((65536.0, 256.0, 1.0)):
+        S[:, k, :256] = np.arange(256, dtype=np.float32) * np.float32(scale)
+    check(pq, oracle, codes, S, K, "rising")
+
+
 @pytest.mark.parametrize("K", [32, 193, 256, 257, 512])
 @pytest.mark.parametrize("kind", ["bytes", "list", "wide"])
 def test_larger_k_straight_from_registers(pq, oracle, K, kind):
