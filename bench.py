@@ -862,7 +862,8 @@ def main():
         # a batch re-uses every code byte B times: the table lookups (4 bytes gathered from LDS per split, item and
         # query), not HBM, bound the scan; reported beside the HBM figure, against what the LDS returns at best on paper
         # (`peak`: 128 bytes per clock and CU) and against what random 16-byte gathers get out of it on this machine,
-        # measured by this run (`measured_peak`; the batched kernel reads four queries' values with one such gather)
+        # measured by this run (`measured_peak`).  Scans by upper bounds read one such gather per sixteen (or eight) queries
+        # and the four bytes of a score only for what passes: they reach more than either
         lds_bytes = 4.0 * m * N * B
         lds_achieved = lds_bytes / (scan_ms * 1e-3) / 1e9
         lds_measured = measured_lds_peak(pq, torch)
@@ -870,7 +871,8 @@ def main():
                              "unit": "GB/s", "frac": lds_achieved / LDS_PEAK_GBS,
                              "measured_peak": lds_measured, "frac_of_measured": lds_achieved / lds_measured,
                              "measured_peak_what": "random 16-byte gathers from a 32 KB LDS table, 16 waves per CU, nothing else (pq_measure_lds_gather)",
-                             "algorithmic_bytes_per_launch": lds_bytes}
+                             "algorithmic_bytes_per_launch": lds_bytes,
+                             "algorithmic_bytes_what": "4 per query, item and split, as summing the scores would read"}
     if not args.no_cpu_baseline:
         out["cpu_baseline"] = cpu_baseline(G, cent, Q, K)
     print(json.dumps(out))

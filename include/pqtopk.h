@@ -78,8 +78,8 @@ size_t pq_score_topk_workspace_bytes(long long N, int B, int m, int b, int K);
  *   out_ids     out  int32 [B][K]     rank r of query q at [q][r]; score descending, id ascending
  *   out_scores  out  float [B][K]     the scores of those items
  *   workspace        scratch of at least pq_score_topk_workspace_bytes(N, B, m, b, K) bytes, 16-byte aligned;
- *                    contents on entry are irrelevant (it receives every workgroup's K best keys, which one or
- *                    more small launches fold into the result); calls sharing a workspace must not overlap in time
+ *                    contents on entry are irrelevant (it receives every workgroup's K best keys, which a small
+ *                    launch folds into the result, and for batches the queries' tables of bounds); calls sharing a workspace must not overlap in time
  * Errors: PQ_ERR_NULL, PQ_ERR_SHAPE, PQ_ERR_UNSUPPORTED (K > PQ_MAX_K, m > PQ_MAX_M, B > PQ_MAX_B, or m and K together
  *         too large for the 160 KB of LDS: m KB of score tables plus about 80*nextpow2(K+64) bytes of candidate
  *         lists; every K <= 512 fits with m <= 64, and m = 128 fits with K <= 64),
@@ -115,8 +115,8 @@ int pq_score_topk_static(const uint8_t* codes, const float* S, long long N, int 
  * The query's whole m x b table is held in LDS when m * b * 4 bytes plus the candidate lists (about 80 *
  * nextpow2(K + 64) bytes) fit 160 KB, e.g. m * b <= 36864 at K = 10 (m = 8: b <= 4608); a larger table is read where
  * it lies, in device memory (it stays in L2; several times slower per lookup, sub-ids clamped to b - 1).  Rows of 8,
- * 16 or 32 bytes (m = 4, 8, 16) are scanned as 16-byte vectors; any other m row by row.  Every query of a batch scans
- * the codebook by itself (no shared pass).  A sub-id >= b makes the result unspecified, but no device memory outside the
+ * 16 or 32 bytes (m = 4, 8, 16) are scanned as 16-byte vectors; any other m row by row.  Larger batches share passes
+ * over these rows; for any other m every query scans the codebook by itself.  A sub-id >= b makes the result unspecified, but no device memory outside the
  * arguments is touched: lookups in device memory are clamped to the table, lookups in LDS stay in LDS.
  * Errors: as pq_score_topk(), with PQ_ERR_SHAPE for b > 65536.
  */

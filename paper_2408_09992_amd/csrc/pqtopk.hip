@@ -7,19 +7,18 @@
 // Total order used everywhere: a 64-bit key  (orderable(score) << 32) | ~id.  A larger key is a better item:
 // higher score first, lower id between equal scores.  Keys of distinct items are distinct, key 0 means "empty".
 //
-// Shape of pq_score_topk(): one scan launch, then a small fold launch.
-//   scan_topk_kernel<M, C, NT> (scan_single.hpp; one query per workgroup; grid = (item blocks, B)):
-//     1. requests its query's table values and its first rounds of codes, then fills the m x b table into LDS
-//        (C copies of it for long scans, so that lanes with different copies never collide on an LDS bank);
-//     2. scores a first round of items into registers and cuts it with a 1024-bucket histogram over the workgroup's
-//        scores: a floor that at least K of them exceed; everything below it is out for good;
-//     3. streams the rest of its share of G against the floor; code loads are branch-free and counted, so the next
-//        round's loads stay in flight; waves take their work units from a counter in LDS; survivors (a handful)
-//        go to small per-wave lists in LDS that are pruned exactly (by key) when they fill, which raises the floor;
-//     4. selects its exact K best and writes them, sorted, to the workspace.
-//   scan_topk_tiled_kernel<M> (scan_batched.hpp; m = 8 or 16, larger batches; a tile of four queries per workgroup,
-//     tables interleaved as float4 so one 16-byte LDS read serves the four queries and sub-id extraction is shared):
-//     same steps; its floors are workgroup-wide, kept up to date by a running histogram of the candidates' scores.
+// Shape of pq_score_topk(): one scan launch, then a small fold launch (none when one workgroup per query does).  The scans, by
+// what they are for:
+//   scan_short_kernel (scan_short.hpp; scan_subset_kernel for candidate lists): a workgroup's share fits its registers as scores, up to
+//     64 per thread: single queries over up to 8M items, batches over small catalogues.  The K best are selected from there.
+//   scan_long_kernel (scan_long.hpp): a single query over more, in segments of registers.
+//   scan_filter_kernel (scan_filter.hpp; filter_prepare_kernel before it takes a sample for the first floors and makes the tables):
+//     batches.  Upper bounds of 8 or 16 bits for up to sixteen queries are summed with one LDS read per sub-id; only what reaches
+//     a query's floor is scored exactly.
+//   scan_topk_tiled_kernel (scan_batched.hpp; m = 8 or 16): large batches over catalogues too small for bounds to pay, four queries per
+//     16-byte LDS read.
+//   scan_topk_kernel (scan_single.hpp): everything else: any row length, tables that do not fit LDS, the longest single-query scans
+//     (sixteen copies of the tables, per-wave lists, floors from a running histogram).
 //   fold_lists_kernel or fold_small_kernel (fold.hpp; one workgroup per query) reduces the workgroups' lists to the final sorted K.
 // Floors and histograms only ever prune; every decision that picks a winner compares full keys, so the result is
 // exact for any input, including heavy ties (which merely take slower paths).
@@ -54,8 +53,8 @@ using namespace pqk;
 
 thread_local char g_hip_error[256] = "no HIP error recorded";
 
-// pq_measure_force_general(): bit 0 keeps calls off scan_short_kernel, bit 1 off fold_small_kernel, bit 2 Eq. 4 off the
-// matrix cores (0: the product's choice)
+// pq_measure_force_general(): bit 0 keeps calls off the short and long scans, bit 1 off fold_small_kernel, bit 2 Eq. 4 off the
+// matrix cores, bit 3 off the scans by upper bounds; bit 4 on them wherever they can (0: the product's choice)
 std::atomic<int> g_force_general{0};
 
 int record_hip(hipError_t e) {
@@ -114,7 +113,7 @@ struct ScanPlan {
 };
 
 // What make_plan() may choose from.
-enum { kNoFilter = 1 };
+enum { kNoFilter = 1, kNoLong = 2 };
 
 bool is_vec_m(int m) { return m == 1 || m == 2 || m == 4 || m == 8 || m == 16 || m == 32 || m == 64; }
 
@@ -324,7 +323,7 @@ ScanPlan make_plan(long long N, int B, int m, int K, bool generic = false, int c
     }
     // Longer catalogues of a single query are scanned in segments, one workgroup per CU.
     p.long_scan = false;
-    if (!p.short_scan && p.vec && !generic && !p.tiled && B == 1 && long_scan_pays(N, m, K, cw) &&
+    if (!(without & kNoLong) && !p.short_scan && p.vec && !generic && !p.tiled && B == 1 && long_scan_pays(N, m, K, cw) &&
         !(g_force_general.load(std::memory_order_relaxed) & 1)) {
         const size_t table = cw == 1 ? lut_floats * (m <= 8 ? kTableCopies : 1) * sizeof(float) : table16;
         if (table + sizeof(LongSelectLds<kLongThreads>) <= kMaxLdsBytes) {
@@ -922,6 +921,8 @@ int enqueue_fold(const ScanPlan& p, int B, int K, void* workspace, int* out_ids,
         f.group_mask = kFoldLists - 1;
     }
     if (nlists > kFoldLists || (long long)nlists * f.chunk > kFoldSlots) return PQ_ERR_UNSUPPORTED;   // (no plan makes that many)
+    if (stamps != nullptr && B > kAssumedCUs)
+        return record_hip(launch(fold_lists_kernel<kFoldThreadsMany, true>, dim3(1, B), kFoldThreadsMany, p.fold_lds, st, f));
     if (stamps != nullptr) return record_hip(launch(fold_lists_kernel<kFoldThreads, true>, dim3(1, B), kFoldThreads, p.fold_lds, st, f));
     if (B <= kAssumedCUs) return record_hip(launch(fold_lists_kernel<kFoldThreads>, dim3(1, B), kFoldThreads, p.fold_lds, st, f));
     return record_hip(launch(fold_lists_kernel<kFoldThreadsMany>, dim3(1, B), kFoldThreadsMany, p.fold_lds, st, f));
@@ -1117,12 +1118,17 @@ int pq_measure_step_stamps(const float* queries, const float* centroids, const u
     if (((uintptr_t)queries & 3) || ((uintptr_t)centroids & 3) || ((uintptr_t)stamps & 7)) return PQ_ERR_ALIGN;
     if (stamps_bytes < PQ_STAMP_BYTES) return PQ_ERR_WORKSPACE;
     static_assert(PQ_STAMP_SLOTS == kStampSlots, "header and kernels agree on the record size");
-    const ScanPlan p = make_plan(N, B, m, K);
-    if (p.filter ? (p.f_w16 || !p.f_fine || !((m == 8 && p.f_words == 4) || (m == 16 && p.f_words == 2))) : !(p.tiled || m == 8))
+    // (the scan in segments has no measurement instance, that by upper bounds those of the named workloads: otherwise the kernels
+    // that would run without them)
+    ScanPlan p = make_plan(N, B, m, K, false, 1, kLutStride, kNoLong);
+    if (p.filter && (p.f_w16 || !p.f_fine || !((m == 8 && p.f_words == 4) || (m == 16 && p.f_words == 2))))
+        p = make_plan(N, B, m, K, false, 1, kLutStride, kNoLong | kNoFilter);
+    if (workspace_bytes_given < workspace_bytes(p, B, K)) return PQ_ERR_WORKSPACE;
+    if (!(p.filter || p.tiled || m == 8))
         return PQ_ERR_UNSUPPORTED;                             // (scan kernels with a measurement instance)
     const int waves = p.filter ? kFilterWaves : (!p.tiled && p.big) ? kMaxWaves : kWaves;
     const long long scan_groups = p.filter ? (long long)p.nblk * ((B + p.f_queries - 1) / p.f_queries) : p.tiled ? (long long)p.nblk * ((B + kQ - 1) / kQ) : (long long)p.nblk * B;
-    if (scan_groups * waves > PQ_STAMP_RECORDS || (long long)B * (kFoldThreads / kWave) > PQ_STAMP_RECORDS) return PQ_ERR_UNSUPPORTED;
+    if (scan_groups * waves > PQ_STAMP_RECORDS || (long long)B * ((B <= kAssumedCUs ? kFoldThreads : kThreads) / kWave) > PQ_STAMP_RECORDS) return PQ_ERR_UNSUPPORTED;
     if (scan_grid != nullptr) { scan_grid[0] = (int)scan_groups; scan_grid[1] = waves; }
     hipStream_t st = static_cast<hipStream_t>(stream);
     const size_t section = (size_t)PQ_STAMP_RECORDS * PQ_STAMP_SLOTS;
