@@ -163,6 +163,17 @@ double tiled_min_lookups(int m, int K) {
 // from the scan's end to the result) is saved.
 constexpr long long kDirectUnits(int row) { return row <= 16 ? 8 : row == 32 ? 4 : 2; }
 
+// Where one workgroup takes all N candidates of a query's list and writes the result itself.  A compute unit gathers about one row
+// per clock, whatever its length, and looks up m entries for it: a candidate costs m + 8 here.  Spread over the chip this passes, but
+// the fold's launch comes on top, and so do the tables that every workgroup loads, the more of the chip B queries fill.  Steps of
+// 15,000 candidates, m = 4, by one workgroup and spread: B = 1 13.9 and 9.8 us (K = 5), 19.1 and 15.1 (K = 500); B = 30 17.7 and 14.5;
+// B = 100, K = 200 21.9 and 22.9.  10,000 candidates: within 5 % of each other at B = 1 and 6, B = 30, K = 40 14.4 and 16.2; 7000 at
+// K = 40: 10.1 and 11.8.  At m = 16 the list that a workgroup holds at most (3500: 10.1 and 11.3) lies below the line.
+bool subset_direct_pays(long long N, int m, int B) {
+    if (N * m > kDirectUnits(16) * 16LL * kThreads) return false;
+    return N * (m + 8) <= (112LL << 10) + 720LL * B;
+}
+
 // Where one query's catalogue is scanned in segments (scan_long_kernel) and not by the general kernel's per-wave lists.  Measured at
 // 5e6 to 5e7 items, K from 3 to 512: with more than 256 results nearly always (1.2 to 3.6 times as fast) and for rows of 8 and 16 bytes of
 // two-byte sub-ids (1.08 to 1.26); otherwise while the first cut, the lists' merge and the sorting of full lists weigh more than the general kernel's
@@ -343,7 +354,7 @@ ScanPlan make_plan(long long N, int B, int m, int K, bool generic = false, int c
     p.subset_vecs = 0;
     if (generic && cw == 1 && (m == 4 || m == 8 || m == 16) && !(g_force_general.load(std::memory_order_relaxed) & 1)) {
         long long nb = kAssumedCUs / B;
-        if (nb < 1 || N * m <= kDirectUnits(16) * 16LL * kThreads) nb = 1;
+        if (nb < 1 || subset_direct_pays(N, m, B)) nb = 1;
         const long long thin = (N + kThreads - 1) / kThreads;              // workgroups if every thread held one candidate
         if (nb > thin) nb = thin;
         const long long per_thread = (N + kThreads * nb - 1) / (kThreads * nb);

@@ -265,8 +265,7 @@ def test_fold_of_sorted_lists(pq, oracle, N, B, K):
 
 @pytest.mark.parametrize("m,wide", [(4, False), (8, False), (16, False), (32, False), (64, False), (4, True), (8, True), (16, True)])
 def test_short_scan_with_more_units_than_are_held_at_once(pq, oracle, m, wide):
-    """The larger instances: the edges of each (its last slots empty, ragged, whole), for a query that has the chip to itself's
-    sixteenth (sixteen queries side by side)."""
+    """The larger instances: the edges of each (its last slots empty, ragged, whole), sixteen queries side by side."""
     rng = np.random.default_rng(m + wide)
     row, b = m * (2 if wide else 1), 300 if wide else 256
     items = max(1, 16 // row)                                  # per unit
@@ -953,6 +952,18 @@ def test_subset_lists_held_in_registers(pq, oracle, m):
     Gs = W.codes_uniform(5000, m, 16, seed=3)                  # a short alphabet and a list of a few candidates
     for n in (1, 2, 31, 513):
         assert_same_subset_topk(pq, oracle, Gs, tables(n, 2, m, 16), W.candidate_list(5000, n, seed=n), min(n, 10), "subset registers tiny")
+
+
+@pytest.mark.parametrize("m", [4, 8, 16])
+@pytest.mark.parametrize("B,K", [(1, 1), (1, 300), (7, 40), (120, 10)])
+def test_subset_by_one_workgroup_or_spread(pq, oracle, m, B, K):
+    """List lengths around the line between one workgroup per query and many, and the most one workgroup holds."""
+    N = 40_000
+    G = W.codes_uniform(N, m, 256, seed=m)
+    S = W.normal_f32(W.stream_key(m, W.STREAM_QUERIES), B * m * 256).reshape(B, m, 256)
+    line = (112 * 1024 + 720 * B) // (m + 8)
+    for n in sorted({line, line + 1, 65_536 // m, 65_536 // m + 1}):
+        assert_same_subset_topk(pq, oracle, G, S, W.candidate_list(N, n, seed=n), K, "subset-line")
 
 
 def test_subset_ties_go_to_the_lower_item_id(pq, oracle):
