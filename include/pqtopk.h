@@ -94,9 +94,10 @@ int pq_score_topk(const uint8_t* codes, const float* S, long long N, int B, int 
  * result; the workgroups' partial top-K lists go to an array built into the library (PQ_STATIC_SCRATCH_BYTES = 8 MiB
  * of device memory per GPU the library runs on, held until the process ends) instead of a caller's workspace.  The
  * call allocates and frees nothing.
- *   - A problem whose pq_score_topk_workspace_bytes() exceeds PQ_STATIC_SCRATCH_BYTES is rejected with
- *     PQ_ERR_TOO_LARGE (nothing enqueued).  Every named workload fits (the largest, B = 1024 with K = 100, needs
- *     less than 2 MiB).
+ *   - A problem whose partial lists exceed PQ_STATIC_SCRATCH_BYTES, on a grid up to a quarter coarser than
+ *     pq_score_topk() would take, is rejected with PQ_ERR_TOO_LARGE (nothing enqueued).  Where only a batch's tables of
+ *     bounds do not fit, the batch is scanned without them.  Whatever pq_score_topk_workspace_bytes() puts at or below
+ *     PQ_STATIC_SCRATCH_BYTES is taken.
  *   - All calls on one GPU share that GPU's array: calls that overlap in time on one GPU (two streams, two
  *     threads) race and give unspecified results; calls on one stream are ordered and safe.  Nothing in the array
  *     has to survive from one call to the next.

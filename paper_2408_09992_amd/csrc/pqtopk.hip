@@ -510,6 +510,17 @@ size_t workspace_bytes(const ScanPlan& p, int B, int K) {
            (p.filter && p.f_parts > 1 ? ((size_t)B * p.f_parts * p.f_best * sizeof(float) + 255) & ~(size_t)255 : 0);
 }
 
+// Lists that do not fit `bytes`: up to a quarter fewer item blocks per query, where the kernel takes any grid.  (The scan gets longer
+// by that much at most; coarser grids are left to the caller, who can pass a workspace.)
+void coarsen_to_fit(ScanPlan& p, int B, int K, size_t bytes) {
+    if (p.filter || p.short_scan || p.long_scan || workspace_bytes(p, B, K) <= bytes) return;
+    const long long most = (long long)(bytes / ((size_t)B * K * sizeof(uint64_t)));
+    if (most >= 1 && 4 * most >= 3LL * p.nblk) {
+        p.nblk = (int)most;
+        p.direct = p.nblk == 1;
+    }
+}
+
 int check_topk_shape(long long N, int B, int m, int b, int K, int cw) {
     if (N < 1 || B < 1 || m < 1 || b < 1 || K < 1 || b > (cw == 1 ? 256 : 65536) || K > N || N >= 2147483648LL)
         return PQ_ERR_SHAPE;
@@ -1058,6 +1069,7 @@ int pq_score_topk_static(const uint8_t* codes, const float* S, long long N, int 
     if (rc != PQ_OK) return rc;
     ScanPlan p = make_plan(N, B, m, K);
     if (p.filter && workspace_bytes(p, B, K) > kStaticScratchBytes) p = make_plan(N, B, m, K, false, 1, kLutStride, kNoFilter);
+    coarsen_to_fit(p, B, K, kStaticScratchBytes);
     if (p.scan_lds > kMaxLdsBytes || p.fold_lds > kMaxLdsBytes) return PQ_ERR_UNSUPPORTED;
     if (((uintptr_t)codes & 15) || ((uintptr_t)S & 3) || ((uintptr_t)out_ids & 3) || ((uintptr_t)out_scores & 3))
         return PQ_ERR_ALIGN;

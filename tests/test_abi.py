@@ -21,6 +21,7 @@ def lib(pqlib_path):
     L.pq_score_topk_workspace_bytes.argtypes = [LL, I, I, I, I]
     L.pq_score_topk_workspace_bytes.restype = SZ
     L.pq_score_topk.argtypes = [P, P, LL, I, I, I, I, P, P, P, SZ, P]
+    L.pq_score_topk_static.argtypes = [P, P, LL, I, I, I, I, P, P, P]
     L.pq_score_topk_profile.argtypes = [P, P, LL, I, I, I, I, P, P, P, SZ, P, I, P]
     L.pq_score_topk_u16_workspace_bytes.argtypes = [LL, I, I, I, I]
     L.pq_score_topk_u16_workspace_bytes.restype = SZ
@@ -278,3 +279,16 @@ def test_workspace_bytes_over_a_grid_of_shapes(lib):
                         assert need16 >= B * K * 8 and need16 % 16 == 0, (N, B, m, K, need16)
                     n_checked += 1
     assert n_checked > 5000
+
+
+@pytest.mark.parametrize("N,B,m,K,taken", [
+    (14_074_490, 71, 24, 488, True), (36_248_764, 65, 12, 361, True),     # a slightly coarser grid than their own: lists just fit
+    (1_280_000, 1024, 8, 100, True), (100_000, 60_000, 8, 512, False), (20_000_000, 2_600, 24, 512, False)])
+def test_static_scratch_takes_grids_a_little_coarser(lib, N, B, m, K, taken):
+    """Which problems fit the built-in scratch is decided on the host, before any HIP call: without a GPU a problem that is taken
+    gets as far as HIP's own error."""
+    import torch
+    if torch.cuda.is_available():
+        pytest.skip("dummy pointers: only where no kernel can run")
+    a = ctypes.c_void_p(0x1000)
+    assert lib.pq_score_topk_static(a, a, N, B, m, 256, K, a, a, None) == (HIP if taken else -7)

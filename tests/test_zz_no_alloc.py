@@ -56,3 +56,17 @@ def test_static_scratch_rejects_what_does_not_fit(pq):
     rc = L.pq_score_topk_static(dummy.data_ptr(), dummy.data_ptr(), N, B, m, b, K, dummy.data_ptr(), dummy.data_ptr(), None)
     assert rc == pq.PQ_ERR_TOO_LARGE
     assert "scratch" in pq.pq_strerror(rc)
+
+
+@pytest.mark.parametrize("N,B,m,K", [(14_074_490, 71, 24, 488)])
+def test_static_scratch_on_a_coarser_grid(pq, N, B, m, K):
+    # (too large for the oracle: against the same call with a workspace, whose grid is the finer one)
+    import torch
+    from paper_2408_09992_amd import workloads as W
+    assert pq.pq_score_topk_workspace_bytes(N, B, m, 256, K) > pq.PQ_STATIC_SCRATCH_BYTES
+    G = W.codes_uniform_device(N, m, 256, 3)
+    S = torch.randn((B, m, 256), device="cuda", generator=torch.Generator(device="cuda").manual_seed(3))
+    ref_ids, ref_sc = pq.pq_score_topk(G, S, K)
+    ids, sc = torch.empty_like(ref_ids), torch.empty_like(ref_sc)
+    pq.pq_score_topk_static(G, S, K, ids, sc)
+    assert torch.equal(ids, ref_ids) and torch.equal(sc.view(torch.int32), ref_sc.view(torch.int32))
