@@ -93,14 +93,19 @@ namespace pqk {
 // for the kernels that prepare them
 #define PQ_FILTER_W3(X, M, CW, W16, SUB, FINE) X(M, CW, 1, W16, SUB, FINE) X(M, CW, 2, W16, SUB, FINE) X(M, CW, 4, W16, SUB, FINE)
 #define PQ_FILTER_W8(X, M, CW, SUB) PQ_FILTER_W3(X, M, CW, false, SUB, false) PQ_FILTER_W3(X, M, CW, false, SUB, true)
-#define PQ_FILTER_INSTANCES_A(X, Y) PQ_FILTER_W8(X, 4, 1, false) PQ_FILTER_W8(X, 8, 1, false) Y(4, 1, false) Y(8, 1, false)
+// (one-byte sub-ids: the fine counts fit beside the 8-bit tables, but for sixteen queries of more than 128 results at m = 8: see
+// filter_may_be_coarse())
+#define PQ_FILTER_W8_BYTES(X, M, SUB) PQ_FILTER_W3(X, M, 1, false, SUB, true)
+#define PQ_FILTER_INSTANCES_A(X, Y) \
+    PQ_FILTER_W8_BYTES(X, 4, false) PQ_FILTER_W8_BYTES(X, 8, false) X(8, 1, 4, false, false, false) Y(4, 1, false) Y(8, 1, false)
 // (m = 16 with eight-bit fields and one-byte sub-ids: always with the fine counts, and then eight queries are the better tile)
 #define PQ_FILTER_INSTANCES_B(X, Y) \
     X(16, 1, 1, false, false, true) X(16, 1, 2, false, false, true) PQ_FILTER_W3(X, 16, 1, true, false, false) Y(16, 1, false)
 #define PQ_FILTER_INSTANCES_C(X, Y) \
     PQ_FILTER_W3(X, 32, 1, true, false, false) X(64, 1, 1, true, false, false) X(64, 1, 2, true, false, false) Y(32, 1, false) Y(64, 1, false)
 #define PQ_FILTER_INSTANCES_SUBSET(X, Y) \
-    PQ_FILTER_W8(X, 4, 1, true) PQ_FILTER_W8(X, 8, 1, true) X(16, 1, 1, false, true, true) X(16, 1, 2, false, true, true) \
+    PQ_FILTER_W8_BYTES(X, 4, true) PQ_FILTER_W8_BYTES(X, 8, true) X(8, 1, 4, false, true, false) \
+    X(16, 1, 1, false, true, true) X(16, 1, 2, false, true, true) \
     PQ_FILTER_W3(X, 16, 1, true, true, false) \
     Y(4, 1, true) Y(8, 1, true) Y(16, 1, true)
 #define PQ_FILTER_INSTANCES_U16(X, Y) \

@@ -734,6 +734,19 @@ hipError_t launch_subset_m(const ScanPlan& p, const ScanArgs& a, int B, hipStrea
     }
 }
 
+// Whether a plan can ask for fields of W words without the fine counts.  16-bit fields: always without (m = 64: four words of tables
+// do not fit).  8-bit fields over one-byte sub-ids: where the counts do not fit for some K, the longest list that a K has being
+// 1024 keys; at m = 16 (K <= 32, lists of 128 keys) plan_filter() takes eight queries with the counts over sixteen without.
+// Two-byte sub-ids: as their alphabet has it, but at m = 16 tables of more than 16 * 256 entries have 16-bit fields.
+constexpr bool filter_may_be_coarse(int M, int CW, int W, bool W16) {
+    if (W16) return M < 64 || W < 4;
+    if (M == 16) return false;
+    if (CW == 2) return true;
+    for (int cap = 128; cap <= 1024; cap *= 2)
+        if (filter_lds_bytes(M * kLutStride, W, W * 4, cap, false) <= kMaxLdsBytes && filter_lds_bytes(M * kLutStride, W, W * 4, cap, true) > kMaxLdsBytes) return true;
+    return false;
+}
+
 template <int M, int CW, bool W16, bool SUB>
 hipError_t launch_filter(const ScanPlan& p, const FilterArgs& a, hipStream_t st) {
     const size_t prep_lds = filter_prepare_lds_bytes(a.entries, M);
@@ -765,15 +778,17 @@ hipError_t launch_filter(const ScanPlan& p, const FilterArgs& a, hipStream_t st)
             }
         }
     }
-    if constexpr (M == 16 && !W16) return hipErrorInvalidValue;   // (the plan never asks for it)
-    else
     switch (p.f_words) {
-        case 1: return go(scan_filter_kernel<M, CW, 1, W16, SUB, false>);
-        case 2: return go(scan_filter_kernel<M, CW, 2, W16, SUB, false>);
+        case 1:
+            if constexpr (filter_may_be_coarse(M, CW, 1, W16)) return go(scan_filter_kernel<M, CW, 1, W16, SUB, false>);
+            break;
+        case 2:
+            if constexpr (filter_may_be_coarse(M, CW, 2, W16)) return go(scan_filter_kernel<M, CW, 2, W16, SUB, false>);
+            break;
         default:
-            if constexpr (M < 64) return go(scan_filter_kernel<M, CW, 4, W16, SUB, false>);
-            else return hipErrorInvalidValue;                // (the plan never asks for it)
+            if constexpr (filter_may_be_coarse(M, CW, 4, W16)) return go(scan_filter_kernel<M, CW, 4, W16, SUB, false>);
     }
+    return hipErrorInvalidValue;                             // (the plan never asks for it)
 }
 
 hipError_t launch_filter(const ScanPlan& p, const FilterArgs& a, int m, int cw, hipStream_t st) {

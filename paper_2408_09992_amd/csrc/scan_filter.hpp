@@ -307,11 +307,11 @@ __global__ __launch_bounds__(kFilterThreads) void filter_prepare_kernel(FilterAr
     if (tid < kFilterBins) a.hist[(size_t)q * kFilterBins + tid] = 0u;
 }
 
-__host__ __device__ inline size_t filter_state_bytes(int queries) {   // everything but the tables, the lists and the queues
+__host__ __device__ constexpr size_t filter_state_bytes(int queries) {   // everything but the tables, the lists and the queues
     return (size_t)queries * (kFilterBins * sizeof(uint32_t) + sizeof(uint64_t) + 2 * sizeof(uint32_t) + sizeof(FilterQuery)) + 64 + 64;
 }
 // `fine`: the 16-bit counts beside the 8-bit tables
-__host__ __device__ inline size_t filter_lds_bytes(long long entries, int words, int queries, int cap, bool fine) {
+__host__ __device__ constexpr size_t filter_lds_bytes(long long entries, int words, int queries, int cap, bool fine) {
     return (size_t)entries * words * 4 + (fine ? (size_t)entries * queries * 2 : 0) + (size_t)queries * cap * sizeof(uint64_t) +
            (size_t)kFilterWaves * kFilterQueue * sizeof(uint64_t) + align16(filter_state_bytes(queries));
 }

@@ -434,7 +434,7 @@ __device__ void block_select(uint64_t* src, int n, int K, uint64_t* dst, uint64_
     }
 }
 
-__host__ __device__ inline size_t align16(size_t x) { return (x + 15) & ~(size_t)15; }
+__host__ __device__ constexpr size_t align16(size_t x) { return (x + 15) & ~(size_t)15; }
 
 // LDS layout of the scan kernel (dynamic): lut | hist | ctl | wave lists | cand | sorted
 struct ScanLds {
