@@ -1,7 +1,8 @@
 """Python names for the C ABI in include/pqtopk.h: argument marshalling only.
 
 The scoring calls go through _pqnative.so (csrc/py_native.cpp), which marshals plain arguments in C; arguments it does
-not take come back here, where they are checked one by one and reported.
+not take come back here, where they are checked one by one and reported.  Where that module cannot be loaded (it is built
+against one torch) everything is marshalled here, some 20 us a step slower, and a warning says so.
 
 Every computation happens in the HIP kernels of libpqtopk.so.  Tensors are torch CUDA (ROCm) tensors, used here
 only as device memory; work is enqueued on torch's current stream.  If the library has not been built the import
@@ -11,6 +12,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import warnings
 from typing import Optional, Tuple
 
 import torch
@@ -89,17 +91,46 @@ def lib() -> ctypes.CDLL:
     return _lib
 
 
+class _Marshalling:
+    """What _pqnative.so offers, through ctypes: the calls are answered with None (the code below marshals them), Enqueue holds an
+    entry point with its arguments."""
+    SUBITEM, TOPK, TOPK_U16, TOPK_SUBSET = 1, 2, 3, 4
+
+    @staticmethod
+    def subitem_scores(*args):
+        return None
+
+    score_topk = score_topk_u16 = score_topk_subset = subitem_scores
+
+    class Enqueue:
+        def _bind(self, which, in0, in1, in2, n, N, B, d, m, b, K, out0, out1, ws, ws_bytes, stream, result, failed):
+            M = _Marshalling
+            if which == M.SUBITEM:
+                self._call, self._args = lib().pq_subitem_scores, (in0, in1, out0, B, d, m, b, stream)
+            elif which == M.TOPK_SUBSET:
+                self._call, self._args = lib().pq_score_topk_subset, (in0, in1, in2, n, N, B, m, b, K, out0, out1, ws, ws_bytes, stream)
+            else:
+                self._call = lib().pq_score_topk_u16 if which == M.TOPK_U16 else lib().pq_score_topk
+                self._args = (in0, in1, N, B, m, b, K, out0, out1, ws, ws_bytes, stream)
+            self._result, self._failed = result, failed
+
+        def __call__(self):
+            rc = self._call(*self._args)
+            return self._result if rc == PQ_OK else self._failed(rc)
+
+
 def _native():
-    """The C fast path of the scoring calls; raises if it was never built."""
+    """The C fast path of the scoring calls, or the same in Python."""
     global _native_module
     if _native_module is None:
         lib()
         try:
             from . import _pqnative
+            _native_module = _pqnative
         except ImportError as e:
-            raise RuntimeError("_pqnative.so is missing: build it with `python -m paper_2408_09992_amd.build` "
-                               "(there is no fallback path)") from e
-        _native_module = _pqnative
+            warnings.warn(f"_pqnative.so cannot be loaded ({e}): calls are marshalled in Python, some 20 us a step slower; build it with "
+                          "`python -m paper_2408_09992_amd.build`", RuntimeWarning, stacklevel=3)
+            _native_module = _Marshalling
     return _native_module
 
 

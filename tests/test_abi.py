@@ -292,3 +292,35 @@ def test_static_scratch_takes_grids_a_little_coarser(lib, N, B, m, K, taken):
         pytest.skip("dummy pointers: only where no kernel can run")
     a = ctypes.c_void_p(0x1000)
     assert lib.pq_score_topk_static(a, a, N, B, m, 256, K, a, a, None) == (HIP if taken else -7)
+
+
+def test_calls_are_marshalled_in_python_without_the_native_module(lib, monkeypatch):
+    """Without _pqnative.so the same entry points are reached through ctypes, and a warning says so."""
+    import sys
+    import paper_2408_09992_amd as package
+    from paper_2408_09992_amd import binding
+    monkeypatch.setattr(binding, "_native_module", None)
+    monkeypatch.setitem(sys.modules, "paper_2408_09992_amd._pqnative", None)      # (importing it raises ImportError)
+    monkeypatch.delattr(package, "_pqnative", raising=False)
+    with pytest.warns(RuntimeWarning, match="marshalled in Python"):
+        native = binding._native()
+    assert native.subitem_scores(1, 2, None) is None and native.score_topk(1, 2, 3, None, None, None) is None
+    # what the host rejects, through both Enqueue types: same codes (null pointers, a K of 0, a batch of 0)
+    monkeypatch.undo()
+    from paper_2408_09992_amd import _pqnative
+    for which, in0, K, B in ((1, 0, 10, 1), (2, 0, 10, 1), (2, 64, 0, 1), (3, 64, 10, 0), (4, 64, 0, 1), (4, 64, 10, 0)):
+        seen = []
+        for module in (_pqnative, binding._Marshalling):
+            e = module.Enqueue()
+            e._bind(which, in0, 64, 64, 1000, 2000, B, 64, 8, 256, K, 64, 64, 64, 1 << 20, 0, "result", lambda rc: ("failed", rc))
+            seen.append(e())
+        assert seen[0] == seen[1] and seen[0][0] == "failed", (which, in0, K, B, seen)
+
+
+def test_stale_when_built_against_another_torch(pqlib_path, tmp_path, monkeypatch):
+    from paper_2408_09992_amd import build
+    assert not build.is_stale()
+    monkeypatch.setattr(build, "_torch_identity", lambda: "torch 0.0, python 0.0\n")
+    assert build.is_stale() and not build._library_is_stale()
+    monkeypatch.setattr(build, "_torch_identity", lambda: "")
+    assert not build.is_stale()                                # (no torch: the library is all there is to build)
