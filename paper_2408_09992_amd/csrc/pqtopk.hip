@@ -110,6 +110,7 @@ struct ScanPlan {
     int f_parts;       // ... parts of the sample
     int f_best;        // ... scores a part leaves (several parts)
     long long f_entries;  // ... table entries
+    int f_batch;       // ... queries scanned together (larger batches in turns, so that the tables of counts stay bounded)
 };
 
 // What make_plan() may choose from.
@@ -373,12 +374,15 @@ ScanPlan make_plan(long long N, int B, int m, int K, bool generic = false, int c
     if (!(without & kNoFilter)) {
         ScanPlan f = p;
         plan_filter(f, N, B, m, K, generic, cw, b);
-        // (a workspace of at most 32 KB per result and 1 MB: the tables of tens of thousands of queries can be more)
-        if (f.filter && workspace_bytes(f, B, K) <= ((size_t)B * K << 15) + (1u << 20)) p = f;
+        if (f.filter) p = f;
     }
     p.direct = p.nblk == 1;
     return p;
 }
+
+// Tables of counts the workspace holds at most: 1024 queries' at m = 64 or over 32768 two-byte entries, 16384 queries' at m = 8.
+// So many fill the chip several times over; a batch larger still takes turns with the same workspace.
+constexpr size_t kFilterTableBytes = 64u << 20;
 
 // LDS reads a CU returns per clock when every lane reads at random: of 4-, 8- and 16-byte words.
 constexpr double kGather4 = 8.7, kGather8 = 8.5, kGather16 = 5.0;
@@ -441,7 +445,9 @@ void plan_filter(ScanPlan& p, long long N, int B, int m, int K, bool subset, int
     }
     if (words == 0) return;
     const int row = m * cw, queries = words * fields;
-    const long long tiles = (B + queries - 1) / queries;
+    const long long together = (long long)(kFilterTableBytes / ((size_t)entries * sizeof(uint16_t))), turns = (B + together - 1) / together;
+    const int batch = turns == 1 ? B : (int)(((B + turns - 1) / turns + 15) & ~15LL);
+    const long long tiles = (batch + queries - 1) / queries;
     const bool by_vector = row <= 16 && !subset;
     const long long units = by_vector ? N * row / 16 : N;
     const int vecs = row >= 32 ? row / 16 : 1;
@@ -466,6 +472,7 @@ void plan_filter(ScanPlan& p, long long N, int B, int m, int K, bool subset, int
     p.f_queries = queries;
     p.f_cap = cap;
     p.f_entries = entries;
+    p.f_batch = batch;
     const int sample_units = (row == 8 || row == 16 || row == 32) ? 2 : 1;
     p.f_sample = kFilterThreads * ((subset && row < 16) ? sample_units * 16 / row : sample_units);
     // The sample: n items cost n * m lookups of 4 bytes, and (K / n) of the catalogue then passes the first floor and is
@@ -477,7 +484,7 @@ void plan_filter(ScanPlan& p, long long N, int B, int m, int K, bool subset, int
     if (p.f_share && want > 1) want = 1;
     if (want > N / 8 / items_per_round) want = N / 8 / items_per_round;
     if (want < 1) want = 1;
-    long long parts = kAssumedCUs / B;
+    long long parts = kAssumedCUs / batch;
     if (parts > 16) parts = 16;
     if (parts > want) parts = want;
     if (parts < 1 || 2 * K + 3 * parts > kFilterBest) parts = 1;
@@ -499,15 +506,14 @@ size_t keys_bytes(const ScanPlan& p, int B, int K) {
     return (bytes + 255) & ~(size_t)255;
 }
 
-// workspace: [B][nblk][K] keys from the scan | filter scans: the queries' tables of counts | their FilterQuery records | their histograms | the sample's best scores
-size_t counts_bytes(const ScanPlan& p, int B) {
-    return p.filter ? ((size_t)B * p.f_entries * sizeof(uint16_t) + 255) & ~(size_t)255 : 0;
-}
-size_t query_bytes(const ScanPlan& p, int B) { return p.filter ? ((size_t)B * sizeof(FilterQuery) + 255) & ~(size_t)255 : 0; }
-size_t hist_bytes(const ScanPlan& p, int B) { return p.filter ? (size_t)B * kFilterBins * sizeof(uint32_t) : 0; }
+// workspace: [B][nblk][K] keys from the scan | filter scans, for the f_batch queries scanned together: tables of counts | FilterQuery
+// records | histograms | the sample's best scores
+size_t counts_bytes(const ScanPlan& p) { return p.filter ? ((size_t)p.f_batch * p.f_entries * sizeof(uint16_t) + 255) & ~(size_t)255 : 0; }
+size_t query_bytes(const ScanPlan& p) { return p.filter ? ((size_t)p.f_batch * sizeof(FilterQuery) + 255) & ~(size_t)255 : 0; }
+size_t hist_bytes(const ScanPlan& p) { return p.filter ? (size_t)p.f_batch * kFilterBins * sizeof(uint32_t) : 0; }
 size_t workspace_bytes(const ScanPlan& p, int B, int K) {
-    return keys_bytes(p, B, K) + counts_bytes(p, B) + query_bytes(p, B) + hist_bytes(p, B) +
-           (p.filter && p.f_parts > 1 ? ((size_t)B * p.f_parts * p.f_best * sizeof(float) + 255) & ~(size_t)255 : 0);
+    return keys_bytes(p, B, K) + counts_bytes(p) + query_bytes(p) + hist_bytes(p) +
+           (p.filter && p.f_parts > 1 ? ((size_t)p.f_batch * p.f_parts * p.f_best * sizeof(float) + 255) & ~(size_t)255 : 0);
 }
 
 // Lists that do not fit `bytes`: up to a quarter fewer item blocks per query, where the kernel takes any grid.  (The scan gets longer
@@ -821,15 +827,13 @@ int enqueue_scan(const ScanPlan& p, const uint8_t* codes, const float* S, long l
     if (p.filter) {
         unsigned char* ws = static_cast<unsigned char*>(workspace) + keys_bytes(p, B, K);
         FilterArgs f;
-        f.codes = codes; f.S = S; f.N = N; f.b = b; f.K = K; f.B = B; f.cap = p.f_cap;
+        f.codes = codes; f.N = N; f.b = b; f.K = K; f.cap = p.f_cap;
         f.subset = subset; f.n_items = (uint32_t)(subset ? n_items : N);
-        f.ws_keys = static_cast<uint64_t*>(workspace);
-        f.out_ids = p.direct ? out_ids : nullptr; f.out_scores = out_scores;
         f.counts = reinterpret_cast<uint16_t*>(ws);
-        f.query = reinterpret_cast<FilterQuery*>(ws + counts_bytes(p, B));
+        f.query = reinterpret_cast<FilterQuery*>(ws + counts_bytes(p));
         f.entries = p.f_entries;
-        f.hist = reinterpret_cast<uint32_t*>(ws + counts_bytes(p, B) + query_bytes(p, B));
-        f.best = reinterpret_cast<float*>(ws + counts_bytes(p, B) + query_bytes(p, B) + hist_bytes(p, B));
+        f.hist = reinterpret_cast<uint32_t*>(ws + counts_bytes(p) + query_bytes(p));
+        f.best = reinterpret_cast<float*>(ws + counts_bytes(p) + query_bytes(p) + hist_bytes(p));
         f.sample = p.f_sample;
         f.rounds = p.f_rounds;
         f.parts = p.f_parts;
@@ -837,7 +841,16 @@ int enqueue_scan(const ScanPlan& p, const uint8_t* codes, const float* S, long l
         f.share = p.f_share;
         f.stamps = stamps;
         f.spare = p.f_w16 ? 3 : m + 3;
-        return record_hip(launch_filter(p, f, m, cw, st));
+        for (int q0 = 0; q0 < B; q0 += p.f_batch) {          // (once, unless the batch is one of thousands)
+            f.B = B - q0 < p.f_batch ? B - q0 : p.f_batch;
+            f.S = S + (size_t)q0 * m * b;
+            f.ws_keys = static_cast<uint64_t*>(workspace) + (size_t)q0 * p.nblk * K;
+            f.out_ids = p.direct ? out_ids + (size_t)q0 * K : nullptr;
+            f.out_scores = out_scores + (size_t)q0 * K;
+            const hipError_t e = launch_filter(p, f, m, cw, st);
+            if (e != hipSuccess) return record_hip(e);
+        }
+        return PQ_OK;
     }
     ScanArgs a;
     a.codes = codes; a.S = S; a.N = N; a.m = m; a.b = b; a.K = K;

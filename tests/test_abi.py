@@ -324,3 +324,17 @@ def test_stale_when_built_against_another_torch(pqlib_path, tmp_path, monkeypatc
     assert build.is_stale() and not build._library_is_stale()
     monkeypatch.setattr(build, "_torch_identity", lambda: "")
     assert not build.is_stale()                                # (no torch: the library is all there is to build)
+
+
+def test_workspace_of_large_batches_is_bounded(lib):
+    """Beside the lists of results: at most 64 MiB of tables and what goes with them, however many queries."""
+    ws, ws16, wsub = lib.pq_score_topk_workspace_bytes, lib.pq_score_topk_u16_workspace_bytes, lib.pq_score_topk_subset_workspace_bytes
+    for m in (4, 8, 16, 32, 64):
+        for B in (1024, 1100, 4096, 30_000, 65_535):
+            for K in (1, 100):
+                lists = 8 * K * B * 16                        # (up to sixteen workgroups per query, at batches of a thousand)
+                most = lists + (64 << 20) + (10 << 20)
+                assert ws(2_000_000, B, m, 256, K) <= most, (m, B, K)
+                if m <= 16:
+                    assert ws16(2_000_000, B, m, 32_768 // m, K) <= most, (m, B, K)
+                    assert wsub(2_000_000, B, m, 256, K) <= most, (m, B, K)

@@ -356,6 +356,12 @@ def test_scan_by_upper_bounds(pq, oracle, m, N, B, K, b):
     _bounds_case(pq, oracle, codes, S, K)
 
 
+@pytest.mark.parametrize("B", [1024, 1025, 2100])              # (1024 queries' tables are what one turn holds at m = 64)
+def test_scan_by_upper_bounds_in_turns(pq, oracle, B):
+    rng = np.random.default_rng(B)
+    _bounds_case(pq, oracle, rng.integers(0, 256, (3_001, 64), dtype=np.uint8), rng.standard_normal((B, 64, 256), dtype=np.float32), 3)
+
+
 @pytest.mark.parametrize("m", [4, 8, 16])
 @pytest.mark.parametrize("B,K", [(2, 10), (9, 100), (20, 1)])
 def test_scan_by_upper_bounds_of_lists_and_wide_ids(pq, oracle, m, B, K):
