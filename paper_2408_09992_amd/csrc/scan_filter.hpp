@@ -16,8 +16,10 @@
 //     in 256ths of a step too (16 bits per entry and query, where LDS has room), and what passes is tried against those
 //     before it is scored: an exact score reads its table values from device memory, one lane per clock and CU.
 //   - what is left is scored exactly, by the same left-to-right fp32 chain as everywhere, and only exact scores enter
-//     lists, floors and results.  Bit for bit the same results as the other kernels, whatever the tables are: bad bounds
-//     (heavy ties, degenerate tables) only mean more exact scoring.
+//     lists, floors and results.  Bit for bit the same results as the other kernels, whatever the tables are.
+// The time does depend on the tables: an item that passes costs as much as a hundred that do not.  Masked entries and queries
+// of zeros (a padded batch) cost nothing extra, see filter_prepare_kernel; tables whose largest entries hardly any item has, or
+// whose scores hardly differ in fp32, let most items through.
 // A field starts at 128 - T (16-bit fields: 256 times that), so its top bit says A >= T.  Fields never carry into each
 // other: `step` is chosen so that the largest possible sum is at most T_first + 127, T never falls, and T is capped at 128
 // (a lower T is always allowed).
@@ -32,12 +34,13 @@ constexpr float kFilterT0 = 80.0f;                // where the first T of a quer
 constexpr float kFilterUp = 0.02f;                // 256ths of a step a count is rounded up by more than it must be, against the
 constexpr float kFilterDown = 0.02f;              // rounding of its own computation; steps T is rounded down by, likewise
 constexpr int kSampleBins = 256;                  // histogram of a sample's scores
+constexpr int kSamplePasses = 8;                  // ... and the times its range is narrowed at most
 constexpr int kFilterBest = 1280;                 // sample scores a query's parts leave at most
 
 struct FilterQuery {                              // one query's bounds, written by filter_prepare_kernel
     float off, inv;                               // units of a score s: (s - off) * inv
     int t_first;                                  // T of the first part's own floor
-    int pad;
+    int flat;                                     // every item scores the same, `off`: the result is the lowest ids
 };
 
 struct FilterArgs {
@@ -118,6 +121,51 @@ __host__ __device__ inline size_t filter_prepare_lds_bytes(long long entries, in
     return align16((size_t)entries * sizeof(float)) + kSampleBins * sizeof(uint32_t) + align16(sizeof(Ctl)) + ((size_t)m + 1 + 3 * pieces) * sizeof(float);
 }
 
+// A cut through the sample's scores by their histogram: `reach` scores (0: there are fewer than asked for) exceed `cut`; the last of
+// those asked for is in `bucket`, with `beyond` in higher ones.
+struct SampleCut {
+    float cut;
+    int reach, beyond, bucket;
+};
+static_assert(kMaxWaves >= 12, "three of them in Ctl::wave_cnt");
+__device__ __forceinline__ SampleCut sample_cut(const Ctl* ctl, int slot) {
+    const int* c = ctl->wave_cnt + 4 * slot;
+    return SampleCut{__int_as_float(c[0]), c[1], c[2], c[3]};
+}
+// one wave; lo and scale as in bucket_of()
+__device__ __forceinline__ void find_sample_cut(const uint32_t* hist, int target, float lo, float scale, Ctl* ctl, int slot, int lane) {
+    static_assert(kSampleBins == 4 * kWave, "four buckets per lane, lane 0 with the highest");
+    const int base = kSampleBins - 4 * (lane + 1);
+    const uint4 v = *reinterpret_cast<const uint4*>(hist + base);
+    const uint32_t upto = wave_prefix_sum(v.x + v.y + v.z + v.w);
+    const uint64_t has = __ballot(upto >= (uint32_t)target);
+    const float ninf = -__builtin_inff();
+    if (has != 0 ? lane == __builtin_ctzll(has) : lane == 0) {
+        SampleCut c = {ninf, 0, 0, 0};
+        if (has != 0) {
+            uint32_t above = upto - (v.x + v.y + v.z + v.w);
+            int i = 3;
+            if (above + v.w < (uint32_t)target) { above += v.w; i = 2; }
+            if (i == 2 && above + v.z < (uint32_t)target) { above += v.z; i = 1; }
+            if (i == 1 && above + v.y < (uint32_t)target) { above += v.y; i = 0; }
+            c.bucket = base + i;
+            c.beyond = (int)above;
+            c.reach = (int)(above + (i == 3 ? v.w : i == 2 ? v.z : i == 1 ? v.y : v.x));
+            // a score of a lower bucket than that: every score of it or a higher one exceeds it
+            c.cut = next_down(lo);                            // (all reach the lowest score)
+            if (c.bucket > 0 && scale > 0.0f) {
+                const float width = 1.0f / scale;
+                float cut = lo + ((float)c.bucket - 0.5f) * width;
+#pragma unroll 1
+                for (int guard = 0; guard < 64 && bucket_of<kSampleBins>(cut, lo, scale) >= c.bucket; ++guard) cut -= width;
+                if (bucket_of<kSampleBins>(cut, lo, scale) < c.bucket) c.cut = fmaxf(cut, c.cut);
+            }
+        }
+        int* out = ctl->wave_cnt + 4 * slot;
+        out[0] = __float_as_int(c.cut); out[1] = c.reach; out[2] = c.beyond; out[3] = c.bucket;
+    }
+}
+
 // The sample.  grid = (parts, B).  Every part scores a sample of its own exactly, in rounds of kSampleItems per thread, and,
 // when there are several, leaves its best scores; part 0 also sets the query's step and bases by the floor of its own sample
 // and writes the table of counts.  (The scan takes the K-th best of all parts' scores as the first floor: at least as high
@@ -127,8 +175,10 @@ __host__ __device__ inline size_t filter_prepare_lds_bytes(long long entries, in
 // What it costs is latency: the tables' way from memory, then kSampleItems x M lookups per thread and round (4096 items at
 // m = 8: 1.6 us), a histogram of the threads' best, the counts.
 //   M, CW: splits, bytes per sub-id; SUB: the sample is taken from a candidate list
+// Two workgroups per CU where the tables leave room (16 of 32 waves each: at most 64 vector and 80 scalar registers; with 88 scalar
+// ones a CU held one workgroup, and 1024 queries at m = 8 took 31 us instead of 21).
 template <int M, int CW, bool SUB>
-__global__ __launch_bounds__(kFilterThreads) void filter_prepare_kernel(FilterArgs a) {
+__global__ __launch_bounds__(kFilterThreads, M <= 16 ? 8 : 4) void filter_prepare_kernel(FilterArgs a) {
     using Sh = FilterShape<M, CW>;
     constexpr int NT = kFilterThreads, NW = kFilterWaves, P = Sh::P;
     extern __shared__ __align__(16) unsigned char smem[];
@@ -150,7 +200,7 @@ __global__ __launch_bounds__(kFilterThreads) void filter_prepare_kernel(FilterAr
     const uint32_t n_sample = (uint32_t)a.sample < total ? (uint32_t)a.sample : total, every = total / n_sample;
     auto fetch = [&](int round, uint32_t (&w)[Sh::kSampleWords]) {
         const uint32_t slices = (uint32_t)(a.parts * a.rounds);
-        const uint32_t shift = (uint32_t)(((uint64_t)every * (uint32_t)(part * a.rounds + round)) / slices);
+        const uint32_t shift = every * (uint32_t)(part * a.rounds + round) / slices;   // (every <= 2^21, or 1; slices <= 128)
 #pragma unroll
         for (int u = 0; u < kLoads; ++u) {
             uint32_t i = (uint32_t)(u * NT + tid);
@@ -214,44 +264,85 @@ __global__ __launch_bounds__(kFilterThreads) void filter_prepare_kernel(FilterAr
     const float ninf = -__builtin_inff();
     float best[2] = {ninf, ninf};
     for (int round = 0; round < a.rounds; ++round) {
+        float acc[Sh::kSampleItems];
 #pragma unroll
         for (int e = 0; e < Sh::kSampleItems; ++e) {
-            float acc = 0.0f;
 #pragma unroll
             for (int k = 0; k < M; ++k) {
                 const float v = lut[(size_t)k * stride + filter_sub_id<M, CW>(w, e, k)];
-                acc = k == 0 ? v : acc + v;
+                acc[e] = k == 0 ? v : acc[e] + v;
             }
-            if (have(e)) best[e & 1] = fmaxf(best[e & 1], acc);
         }
         if (round + 1 < a.rounds) fetch(round + 1, w);
+#pragma unroll
+        for (int e = 0; e < Sh::kSampleItems; ++e) {
+            asm volatile("" : "+v"(acc[e]));                  // (the lookups of all items under way together, whichever count)
+            best[e & 1] = fmaxf(best[e & 1], have(e) ? acc[e] : ninf);
+        }
     }
     const bool both = K > NT / 4 && Sh::kSampleItems > 1;
     if (!both) { best[0] = fmaxf(best[0], best[1]); best[1] = ninf; }
-    float mn = fminf(best[0] > ninf ? best[0] : -ninf, best[1] > ninf ? best[1] : -ninf), mx = fmaxf(best[0], best[1]);
+    // Cuts, from one histogram: several parts leave their best scores, those above the cut that so many exceed; part 0 goes on with
+    // the cut that K exceed.  (Two waves look for them at the same time.)
+    const int r = a.best_per_part;
+    const bool several = a.parts > 1;
     float lo, scale;
-    set_range<NW>(mn, mx, ctl, tid, lo, scale);
+    set_range<NW>(fminf(best[0] > ninf ? best[0] : -ninf, best[1] > ninf ? best[1] : -ninf), fmaxf(best[0], best[1]), ctl, tid, lo, scale);
     scale *= (float)kSampleBins / (float)kBins;
-    if (tid == 0) ctl->scale = scale;
 #pragma unroll
     for (int h = 0; h < 2; ++h)
         if (best[h] > ninf) atomicAdd(&hist[bucket_of<kSampleBins>(best[h], lo, scale)], 1u);
+    // (meanwhile: the splits' extremes, lane k with split k, every wave for itself)
+    const bool mine = lane < M;
+    float s_mx = -__builtin_inff(), s_mn = __builtin_inff(), s_mean = 0.0f;
+    for (int p = 0; p < pieces && mine; ++p) {
+        const float* x = piece + 3 * (lane * pieces + p);
+        s_mx = fmaxf(s_mx, x[0]); s_mn = fminf(s_mn, x[1]); s_mean += x[2];
+    }
+    if (!mine) s_mx = s_mn = 0.0f;
+    s_mean = s_mean / (float)b;
+    const float sum_max = wave_sum_f32(s_mx);
+    const bool flat = __ballot(mine && s_mx != s_mn) == 0;    // every item has the same score (a query of zeros, as batches are padded with)
     __syncthreads();
-    if (tid < kWave) find_cut<kSampleBins>(hist, K, ctl, lane);
+    if (wave < 2) find_sample_cut(hist, wave == 0 ? K : r - r / 8, lo, scale, ctl, wave, lane);
     __syncthreads();
-    const float cut = ctl->cut;
-    if (a.parts > 1) {
-        // this part's best scores, in any order: those above the cut that so many exceed (more, for want of buckets: as many
-        // as there is room for); fewer than asked for are filled up with -inf
-        const int r = a.best_per_part;
+    // A score far from the others (an item with a masked sub-id, at -1e9) stretches the range until the buckets tell nothing apart:
+    // while the one sought shares its bucket with many that are no better, that bucket alone is taken apart again.
+    auto narrowed = [&](SampleCut c, int target) -> float {
+        bool in0 = best[0] > ninf, in1 = best[1] > ninf;
+        float from = lo, per = scale;
+        int left = target;                                    // the left-th best of what is `in` is sought
+#pragma unroll 1
+        for (int pass = 0; pass < kSamplePasses && c.reach - left > target / 2 + kWave && per > 0.0f; ++pass) {
+            left -= c.beyond;
+            in0 = in0 && bucket_of<kSampleBins>(best[0], from, per) == c.bucket;
+            in1 = in1 && bucket_of<kSampleBins>(best[1], from, per) == c.bucket;
+            for (int i = tid; i < kSampleBins; i += NT) hist[i] = 0;   // (added to behind set_range()'s barrier)
+            set_range<NW>(fminf(in0 ? best[0] : -ninf, in1 ? best[1] : -ninf), fmaxf(in0 ? best[0] : ninf, in1 ? best[1] : ninf), ctl, tid, from, per);
+            per *= (float)kSampleBins / (float)kBins;
+            if (in0) atomicAdd(&hist[bucket_of<kSampleBins>(best[0], from, per)], 1u);
+            if (in1) atomicAdd(&hist[bucket_of<kSampleBins>(best[1], from, per)], 1u);
+            __syncthreads();
+            if (wave == 0) find_sample_cut(hist, left, from, per, ctl, 2, lane);
+            __syncthreads();
+            c = sample_cut(ctl, 2);
+        }
+        return c.cut;
+    };
+    const SampleCut first = sample_cut(ctl, 0), own = sample_cut(ctl, 1);
+    float cut = several ? own.cut : first.cut;
+#pragma unroll 1
+    for (int which = several ? 1 : 0;; --which) {
+        const SampleCut c = which == 0 ? first : own;
+        const int target = which == 0 ? K : r - r / 8;
+        cut = c.cut;
+        if (__builtin_expect(c.reach - target > target / 2 + kWave, 0)) cut = narrowed(c, target);
+        if (which == 0) break;
+        // this part's best scores, in any order (more than there is room for: as many as there is); fewer are filled up with -inf
         float* out = a.best + ((size_t)q * a.parts + part) * r;
-        __syncthreads();
-        if (tid < kWave) find_cut<kSampleBins>(hist, r - r / 8, ctl, lane);
-        __syncthreads();
-        const float part_cut = ctl->cut;
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
-            if (best[h] > part_cut) {
+            if (best[h] > cut) {
                 const int pos = atomicAdd(n_found, 1);
                 if (pos < r) out[pos] = best[h];
             }
@@ -262,19 +353,49 @@ __global__ __launch_bounds__(kFilterThreads) void filter_prepare_kernel(FilterAr
     }
 
     // ---- step and bases (every wave for itself: lane k holds split k)
-    const bool mine = lane < M;
-    float s_mx = -__builtin_inff(), s_mn = __builtin_inff(), s_mean = 0.0f;
-    for (int p = 0; p < pieces && mine; ++p) {
-        const float* x = piece + 3 * (lane * pieces + p);
-        s_mx = fmaxf(s_mx, x[0]); s_mn = fminf(s_mn, x[1]); s_mean += x[2];
+    // An item with an entry further than sum_max - cut below its split's largest scores below the cut whatever its others are: all
+    // such entries count as that depth (more than they are: the bounds hold), and for the split's mean as three times as far from the
+    // largest as its other entries (or the splits' on average) are.  Left as they are, one masked sub-id (-1e9) would
+    // set step, bases and slack for all: 1.28M items, 64 queries with one masked sub-id each: 604 us (37 without it), now 36.
+    // Only where a split's entries lie further from its largest than that, or twice as far as the splits' do on average: at m = 4 the
+    // lowest entries of ordinary tables are that deep, and a second pass over the tables is 0.5 us.
+    const float depth = sum_max - cut, deepest = s_mx - depth;
+    float spread = wave_sum_f32(s_mx - s_mean);
+    const bool clamped = __ballot(mine && s_mn < deepest && s_mx - s_mean > fminf(depth, spread * (2.0f / M))) != 0;   // (the same in every wave)
+    if (__builtin_expect(clamped, 0)) {
+        __syncthreads();
+        for (int p = wave; p < M * pieces; p += NW) {
+            const int k = CW == 1 ? p : p / pieces, j0 = CW == 1 ? 0 : (p % pieces) * 4 * kWave;
+            const float least = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(deepest), __builtin_amdgcn_readfirstlane(k)));
+            float sum = 0.0f, n = 0.0f;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int j = j0 + i * kWave + lane;
+                const float x = j < b ? lut[(size_t)k * stride + j] : -__builtin_inff();
+                if (x >= least && j < b) { sum += x; n += 1.0f; }
+            }
+            sum = wave_sum_f32(sum);
+            n = wave_sum_f32(n);
+            if (lane == 0) { piece[3 * p + 1] = n; piece[3 * p + 2] = sum; }
+        }
+        __syncthreads();
+        float sum = 0.0f, n = 0.0f;                           // the entries that count as they are: the largest at least
+        for (int p = 0; p < pieces && mine; ++p) {
+            n += piece[3 * (lane * pieces + p) + 1];
+            sum += piece[3 * (lane * pieces + p) + 2];
+        }
+        const float near = mine ? s_mx - sum / n : 0.0f;
+        const float far = 3.0f * fmaxf(near, wave_sum_f32(near) * (1.0f / M));
+        if (mine) {
+            s_mean = (sum + ((float)b - n) * (s_mx - fminf(far, depth))) / (float)b;
+            s_mn = fmaxf(s_mn, deepest);
+        }
+        spread = wave_sum_f32(s_mx - s_mean);
     }
-    if (!mine) s_mx = s_mn = 0.0f;
-    s_mean = s_mean / (float)b;
-    const float sum_max = wave_sum_f32(s_mx), sum_min = wave_sum_f32(s_mn), sum_abs = wave_sum_f32(fmaxf(fabsf(s_mx), fabsf(s_mn)));
-    const float spread = wave_sum_f32(s_mx - s_mean);
+    const float sum_min = wave_sum_f32(s_mn), sum_abs = wave_sum_f32(fmaxf(fabsf(s_mx), fabsf(s_mn)));
     // what fp32 chains of M additions (scores, sums of bases) can be off by
     const float slack = 4.0f * (float)(M + 1) * 5.9604645e-8f * sum_abs;
-    const float floor_s = fmaxf(cut, sum_min - slack);        // (at least K of the part's items exceed the cut)
+    const float floor_s = clamped ? cut : fmaxf(cut, sum_min - slack);   // (at least K of the part's items exceed the cut)
     float step = (sum_max - floor_s + 2.0f * slack) / (float)(kFilterSpan - a.spare);
     float inv = 1.0f / step;
     if (!(step > 0.0f) || !(inv < 1.0e30f) || !(step < 1.0e30f)) { inv = 0.0f; step = 0.0f; }   // degenerate: T stays 0, every item is scored
@@ -287,19 +408,25 @@ __global__ __launch_bounds__(kFilterThreads) void filter_prepare_kernel(FilterAr
         int t = inv > 0.0f ? (int)floorf((floor_s - off) * inv - kFilterDown) : 0;
         t = t < 0 ? 0 : (t > kFilterSpan + 1 ? kFilterSpan + 1 : t);
         a.query[q] = FilterQuery{off, inv, t, 0};
+        if (__builtin_expect(flat && !SUB, 0)) {                                   // (no bound is reached, and the scan knows the result)
+            float score = lut[0];
+            for (int k = 1; k < M; ++k) score += lut[(size_t)k * stride];
+            a.query[q] = FilterQuery{score, 0.0f, kFilterSpan + 1, 1};
+        }
     }
     if (wave == 0 && mine) bases[lane] = base;
     __syncthreads();
 
     // ---- counts, two entries per thread and store
     uint32_t* out = reinterpret_cast<uint32_t*>(a.counts + (size_t)q * a.entries);
-    const float inv256 = inv * 256.0f;
+    const float inv256 = flat && !SUB ? 0.0f : inv * 256.0f;
+    const float up = flat && !SUB ? 0.0f : kFilterUp;
     for (long long i = tid; i * 2 < a.entries; i += NT) {     // (entries is a multiple of 4)
         uint32_t word = 0;
 #pragma unroll
         for (int c = 0; c < 2; ++c) {
             const uint32_t e = (uint32_t)(i * 2 + c), k = e / (uint32_t)stride;
-            const float x = ceilf((lut[e] - bases[k]) * inv256 + kFilterUp);
+            const float x = ceilf((lut[e] - bases[k]) * inv256 + up);
             word |= (uint32_t)fminf(fmaxf(x, 0.0f), 65535.0f) << (c * 16);
         }
         out[i] = word;
@@ -815,7 +942,9 @@ __global__ __launch_bounds__(kFilterThreads) void scan_filter_kernel(FilterArgs 
                 a.ws_keys[((size_t)(q0 + q) * nblk + blk) * K + t] = key;
             }
         };
-        if (kept > 3 * kWave) {                               // (counting costs kept^2 / 64: 192 keys as much as a sort of 256)
+        if (!SUB && p.flat) {
+            for (int t = lane; t < K; t += kWave) out(t, blk == 0 ? make_key(p.off + 0.0f, (uint32_t)t) : 0ull);
+        } else if (kept > 3 * kWave) {                               // (counting costs kept^2 / 64: 192 keys as much as a sort of 256)
             sort_wave_list(list, cap, kept, K, lane);
             for (int t = lane; t < K && t < kept; t += kWave) out(t, list[t]);
             for (int t = kept + lane; t < K; t += kWave) out(t, 0ull);

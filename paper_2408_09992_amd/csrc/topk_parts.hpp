@@ -118,6 +118,13 @@ __device__ __forceinline__ float next_up(float x) {
     return __uint_as_float(x > 0.0f ? u + 1u : u - 1u);
 }
 
+// Largest float below x (x finite; below the lowest: -inf): `s > next_down(x)` is `s >= x`.
+__device__ __forceinline__ float next_down(float x) {
+    if (x == 0.0f) return __uint_as_float(0x80000001u);
+    const uint32_t u = __float_as_uint(x);
+    return __uint_as_float(x > 0.0f ? u - 1u : u + 1u);
+}
+
 // One wave: the score floor a running histogram allows: at least K counted scores lie in the buckets from b* up, so
 // the K-th best of everything counted exceeds every score of a lower bucket.  -inf if fewer than K are counted or the
 // range is degenerate.  Same value in all lanes; nothing is written.

@@ -404,6 +404,74 @@ def test_scan_by_upper_bounds_when_the_bounds_say_little(pq, oracle, tables):
         _bounds_case(pq, oracle, codes, np.ascontiguousarray(S, dtype=np.float32), K)
 
 
+def _odd_tables(kind, S):
+    """Score tables that are not bell-shaped: masked entries, queries of zeros (a padded batch), single large entries, ..."""
+    B, m, b = S.shape
+    if kind == "zero_queries":
+        S[::3] = 0.0
+    elif kind == "flat_splits":
+        S[1::2] = S[1::2, :, :1]
+    elif kind == "one_masked":
+        S[:, m // 2, 3] = -1e9
+    elif kind == "each_masked":
+        S[:, :, 3] = -1e4
+    elif kind == "lowest":                                     # (the sums of an item with two of them are not finite)
+        S[:, :, 3] = np.finfo(np.float32).min
+    elif kind == "half_masked":
+        S[:, : (m + 1) // 2, : b // 2] = -1e9
+    elif kind == "one_high":
+        S[:, m // 2, 3] = 1e4
+    elif kind == "high_and_masked":
+        S[:, 0, 3], S[:, m - 1, 3] = 1e4, -1e9
+    elif kind == "heavy_tails":
+        S[:] = np.tan(np.pi * (np.random.default_rng(1).random(S.shape, dtype=np.float32) - 0.5)) * np.float32(3.0)
+    elif kind == "far_offset":
+        S += np.float32(1e7)
+    return S
+
+
+@pytest.mark.parametrize("kind", ["zero_queries", "flat_splits", "one_masked", "each_masked", "lowest", "half_masked", "one_high",
+                                  "high_and_masked", "heavy_tails", "far_offset"])
+def test_scan_by_upper_bounds_of_tables_that_are_not_bell_shaped(pq, oracle, kind):
+    rng = np.random.default_rng(11)
+    for m, N, B, K in ((4, 30_003, 7, 10), (8, 60_001, 18, 100), (8, 400_001, 6, 10), (16, 90_001, 5, 10), (16, 50_000, 9, 40), (64, 40_001, 5, 3)):
+        print(f"case {kind} m={m} N={N} B={B} K={K}", flush=True)
+        codes = rng.integers(0, 256, (N, m), dtype=np.uint8)
+        S = _odd_tables(kind, rng.standard_normal((B, m, 256), dtype=np.float32))
+        _bounds_case(pq, oracle, codes, S, K)
+        if m == 8:
+            _bounds_case(pq, oracle, codes, S, K, subset=rng.permutation(N)[: N // 2].astype(np.int32))
+            wide = rng.integers(0, 700, (N, m), dtype=np.uint16)
+            _bounds_case(pq, oracle, wide, _odd_tables(kind, rng.standard_normal((B, m, 700), dtype=np.float32)), K)
+
+
+@pytest.mark.parametrize("kind", ["zero_queries", "one_masked", "each_masked", "lowest"])
+@pytest.mark.parametrize("N,m,B,K", [(1_280_000, 8, 64, 10), (2_000_000, 16, 48, 100)])
+def test_batches_of_masked_and_zero_queries_are_scanned_as_fast_as_others(pq, N, m, B, K, kind):
+    # (bounds that such tables loosen would let nearly every item through: ten times the time; a third of it is allowed here)
+    rng = np.random.default_rng(3)
+    G = W.codes_uniform_device(N, m, 256, 3)
+    S = rng.standard_normal((B, m, 256), dtype=np.float32)
+
+    def best_us(tables):
+        call = pq.PreparedScoreTopK(G, dev(tables), K)
+        times = []
+        for _ in range(8):
+            ev = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+            call()
+            ev[0].record()
+            for _ in range(5):
+                call()
+            ev[1].record()
+            torch.cuda.synchronize()
+            times.append(ev[0].elapsed_time(ev[1]) * 200)
+        return min(times)
+
+    plain = best_us(S)
+    odd = best_us(_odd_tables(kind, S.copy()))
+    assert odd < 3.5 * plain, (plain, odd)
+
+
 @pytest.mark.parametrize("N,m,B,K", [(300_001, 64, 17, 10), (200_003, 64, 40, 100), (150_001, 64, 100, 10), (300_005, 4, 100, 10),
                                      (100_003, 4, 1024, 100), (200_001, 32, 100, 10), (150_007, 5, 100, 10), (120_001, 48, 40, 10),
                                      (100_001, 64, 300, 10)])
