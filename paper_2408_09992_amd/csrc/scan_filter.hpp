@@ -18,8 +18,9 @@
 //   - what is left is scored exactly, by the same left-to-right fp32 chain as everywhere, and only exact scores enter
 //     lists, floors and results.  Bit for bit the same results as the other kernels, whatever the tables are.
 // The time does depend on the tables: an item that passes costs as much as a hundred that do not.  Masked entries and queries
-// of zeros (a padded batch) cost nothing extra, see filter_prepare_kernel; tables whose largest entries hardly any item has, or
-// whose scores hardly differ in fp32, let most items through.
+// of zeros (a padded batch) cost nothing extra, see filter_prepare_kernel; where most items pass all the same (a large entry
+// that hardly any item has, scores that hardly differ in fp32) a query is given up and its share scanned exactly, four queries
+// per LDS read.
 // A field starts at 128 - T (16-bit fields: 256 times that), so its top bit says A >= T.  Fields never carry into each
 // other: `step` is chosen so that the largest possible sum is at most T_first + 127, T never falls, and T is capped at 128
 // (a lower T is always allowed).
@@ -33,14 +34,16 @@ constexpr int kFilterSpan = 127;                  // steps from the first T to t
 constexpr float kFilterT0 = 80.0f;                // where the first T of a query's own sample lies: 48 steps of room to rise
 constexpr float kFilterUp = 0.02f;                // 256ths of a step a count is rounded up by more than it must be, against the
 constexpr float kFilterDown = 0.02f;              // rounding of its own computation; steps T is rounded down by, likewise
+constexpr int kHopeless = 256;
 constexpr int kSampleBins = 256;                  // histogram of a sample's scores
 constexpr int kSamplePasses = 8;                  // ... and the times its range is narrowed at most
 constexpr int kFilterBest = 1280;                 // sample scores a query's parts leave at most
 
 struct FilterQuery {                              // one query's bounds, written by filter_prepare_kernel
     float off, inv;                               // units of a score s: (s - off) * inv
-    int t_first;                                  // T of the first part's own floor
-    int flat;                                     // every item scores the same, `off`: the result is the lowest ids
+    int t_first;                                  // T of the first part's own floor (+ kHopeless: nearly everything passes that)
+    float floor;                                  // a score that K items reach
+    __host__ __device__ bool flat() const { return inv == 0.0f && t_first > kFilterSpan; }   // every item scores the same, `off`: the result is the lowest ids
 };
 
 struct FilterArgs {
@@ -385,7 +388,9 @@ __global__ __launch_bounds__(kFilterThreads, M <= 16 ? 8 : 4) void filter_prepar
             sum += piece[3 * (lane * pieces + p) + 2];
         }
         const float near = mine ? s_mx - sum / n : 0.0f;
-        const float far = 3.0f * fmaxf(near, wave_sum_f32(near) * (1.0f / M));
+        // (... and further where most of a split's entries count so, by what keeps their items from passing in their numbers)
+        const float most = (mine && (float)b > 2.0f * n) ? logf(((float)b - n) / n) : 0.0f;
+        const float far = fmaxf(near, wave_sum_f32(near) * (1.0f / M)) * (3.0f + 0.18f * sqrtf((float)M) * most);
         if (mine) {
             s_mean = (sum + ((float)b - n) * (s_mx - fminf(far, depth))) / (float)b;
             s_mn = fmaxf(s_mn, deepest);
@@ -404,22 +409,30 @@ __global__ __launch_bounds__(kFilterThreads, M <= 16 ? 8 : 4) void filter_prepar
     const float lambda = spread > 0.0f ? (sum_max - floor_s + kFilterT0 * step) / spread : 0.0f;
     const float base = mine ? fmaxf(s_mn, s_mx - lambda * (s_mx - s_mean)) : 0.0f;
     const float off = wave_sum_f32(base) + slack;
-    if (tid == 0) {
-        int t = inv > 0.0f ? (int)floorf((floor_s - off) * inv - kFilterDown) : 0;
-        t = t < 0 ? 0 : (t > kFilterSpan + 1 ? kFilterSpan + 1 : t);
-        a.query[q] = FilterQuery{off, inv, t, 0};
-        if (__builtin_expect(flat && !SUB, 0)) {                                   // (no bound is reached, and the scan knows the result)
-            float score = lut[0];
-            for (int k = 1; k < M; ++k) score += lut[(size_t)k * stride];
-            a.query[q] = FilterQuery{score, 0.0f, kFilterSpan + 1, 1};
+    if (wave == 0) {
+        if (mine) bases[lane] = base;
+        // How much of the sample would pass: scores within the roundings of their counts below the floor.  Where that is more than three
+        // in ten, by the best of n scores of 64 threads, the scan gives the query up unless the parts together know better.
+        // (Floors shared between workgroups rise by themselves, and how far nobody knows yet.)
+        const float near = floor_s - step * (a.spare > 3 ? 0.5f * (float)(M + 1) : 0.5f);   // (a.spare: 8-bit counts are rounded to whole steps)
+        const int n = a.rounds * Sh::kSampleItems, pass = __popcll(__ballot(fmaxf(best[0], best[1]) >= near));
+        const bool hopeless = !(inv > 0.0f) || (a.share == 0 && (float)pass > (float)kWave * (1.0f - exp2f((float)n * -0.5146f)));   // 0.7 ^ n
+        if (lane == 0) {
+            int t = inv > 0.0f ? (int)floorf((floor_s - off) * inv - kFilterDown) : 0;
+            t = t < 0 ? 0 : (t > kFilterSpan + 1 ? kFilterSpan + 1 : t);
+            a.query[q] = FilterQuery{off, inv, hopeless ? t + kHopeless : t, cut};
+            if (__builtin_expect(flat && !SUB, 0)) {          // (no bound is reached, and the scan knows the result)
+                float score = lut[0];
+                for (int k = 1; k < M; ++k) score += lut[(size_t)k * stride];
+                a.query[q] = FilterQuery{score, 0.0f, kFilterSpan + 1, cut};
+            }
         }
     }
-    if (wave == 0 && mine) bases[lane] = base;
     __syncthreads();
 
     // ---- counts, two entries per thread and store
     uint32_t* out = reinterpret_cast<uint32_t*>(a.counts + (size_t)q * a.entries);
-    const float inv256 = flat && !SUB ? 0.0f : inv * 256.0f;
+    const float inv256 = flat && !SUB ? 0.0f : inv * 256.0f;  // (a flat query: nothing passes)
     const float up = flat && !SUB ? 0.0f : kFilterUp;
     for (long long i = tid; i * 2 < a.entries; i += NT) {     // (entries is a multiple of 4)
         uint32_t word = 0;
@@ -482,6 +495,12 @@ __global__ __launch_bounds__(kFilterThreads) void scan_filter_kernel(FilterArgs 
     FilterQuery* const par = reinterpret_cast<FilterQuery*>(lock + QT);
     uint32_t* const start = reinterpret_cast<uint32_t*>(par + QT);                // [W] the fields' start values: 128 - T, or 256 times that
     uint32_t* const next_unit = start + 4;
+    uint32_t* const given_up = next_unit + 1;                                     // queries the bounds are no use for, as bits of a mask of hits
+    uint32_t* const passed = given_up + 1;                                        // [QT] items whose bounds reached the floor; top bit: given up
+
+    // a query's bit in a mask of hits: field f of word j is bit f * 8 (or 16) + j
+    auto bit_of = [](int q) -> int { return W16 ? (q & 1) * 16 + (q >> 1) : (q & 3) * 8 + (q >> 2); };
+    auto query_of = [](int bit) -> int { return W16 ? (bit & 15) * 2 + (bit >> 4) : (bit & 7) * 4 + (bit >> 3); };
 
     // ---- units of work: a wave's share (64 lanes x kVecs vectors), the workgroups' interleaved one by one (whole rounds of a
     // workgroup's waves left some with a twentieth more than others: 5M items at m = 16, 256 workgroups)
@@ -596,6 +615,7 @@ __global__ __launch_bounds__(kFilterThreads) void scan_filter_kernel(FilterArgs 
             }
         }
     }
+    constexpr uint32_t kLost = 0x80000000u;                   // in passed[]
     // (words that other waves write meanwhile: relaxed accesses)
     auto set_t = [&](int q, int t) {
         const int s = kFilterSpan + 1 - t;
@@ -611,11 +631,14 @@ __global__ __launch_bounds__(kFilterThreads) void scan_filter_kernel(FilterArgs 
         return (int)fminf(fmaxf(x, 0.0f), (float)(kFilterSpan + 1));
     };
     if (tid < QT) { thr[tid] = 0ull; cnt[tid] = 0u; lock[tid] = 0u; }
-    if (tid == 0) *next_unit = 2 * NW;
+    if (tid == 0) { *next_unit = 2 * NW; *given_up = 0u; }
+    bool hopeless = false;                                    // this wave's query is given up at once
     if (wave < QT) {
         // a wave per query: the first T (queries that do not exist: start 0, counts 0: never at the top bit)
         const int q = wave;
-        FilterQuery p = q < nq ? my_par : FilterQuery{0.0f, 0.0f, kFilterSpan + 1, 0};
+        FilterQuery p = q < nq ? my_par : FilterQuery{0.0f, 0.0f, kFilterSpan + 1, 0.0f};
+        hopeless = p.t_first >= kHopeless;
+        if (hopeless) p.t_first -= kHopeless;
         if (q < nq && a.parts > 1) {
             // the K-th best of the parts' scores, to 16 bits of its order-preserving image: K of them reach it
             const int n = a.parts * a.best_per_part;
@@ -638,14 +661,17 @@ __global__ __launch_bounds__(kFilterThreads) void scan_filter_kernel(FilterArgs 
             else if (n <= 4 * kWave) search(std::integral_constant<int, 4>());
             else search(std::integral_constant<int, kFilterBest / kWave>());
             const float f = float_of_orderable(at);
-            if (p.inv > 0.0f && f == f && f > -__builtin_inff()) {
-                const int t = units_of_score(f, p);
+            if (f == f && f > -__builtin_inff()) {
+                const int t = p.inv > 0.0f ? units_of_score(f, p) : 0;
+                hopeless = hopeless && t <= p.t_first;
                 p.t_first = t > p.t_first ? t : p.t_first;
+                p.floor = fmaxf(p.floor, f);
             }
         }
         if (lane == 0) {
             par[q] = p;
             set_t(q, p.t_first);
+            passed[q] = 0u;
         }
     }
     stamp<STAMP>(rec, kStampRequested, lane);
@@ -720,9 +746,34 @@ __global__ __launch_bounds__(kFilterThreads) void scan_filter_kernel(FilterArgs 
         wave_sync();
     };
 
+    // Tables whose bounds say little (a large entry that hardly any item has stretches the steps; scores that hardly differ in
+    // fp32; ties) let most items through, and each of them costs what a hundred others do.  A query that has let pass a quarter
+    // of the items so far, and by then so many of the whole share that they have cost about what scanning it exactly
+    // costs (a twelfth; a quarter of wide rows, a twentieth with shared floors), or that the sample has found hopeless, is given up (counted from
+    // where a wave has scored a dozen batches more than it has seen units, so that ordinary tables pay nothing): its counts
+    // go to zero, so that nothing passes any more, and when the others are done its share is scanned again from the start
+    // with exact scores, W queries at a time (below).
+    // 1.28M items, m = 8, 64 queries with such an entry each, K = 10: 121 us instead of 808 (37 without it); 1024, K = 100: 3.1 ms
+    // instead of 9.6.  (Given up at once, shared floors' queries with heavy-tailed tables took 1.3 ms instead of 0.5.)
+    uint32_t calls = 0, units_seen = 0, gone = 0;                // process() calls, units seen; queries given up, as far as this wave has looked
+    const uint32_t give_up_from = units * (kWave * NI) / (M >= 32 ? 4u : a.share ? 20u : 12u);
+    auto give_up = [&](int q) {
+        const uint32_t bit = 1u << bit_of(q);
+        uint32_t before = 0;
+        if (lane == 0) before = atomicOr(given_up, bit);
+        if ((uint32_t)__builtin_amdgcn_readfirstlane((int)before) & bit) return;
+        if (lane == 0) {
+            (void)atomicOr(&passed[q], kLost);
+            set_t(q, kFilterSpan + 1);                        // (as for a query that does not exist; nothing relies on it)
+        }
+        const uint32_t keep = W16 ? ~(0xFFFFu << (q & 1) * 16) : ~(0xFFu << (q & 3) * 8);
+#pragma unroll 1
+        for (uint32_t i = lane; i < entries; i += kWave) atomicAnd(&tab[i * W + q / F], keep);
+    };
+
     // Scores queue entries [n0, n0 + n), n <= 64, exactly, one per lane, and puts what reaches its query's floor into the
-    // query's list.
-    auto process = [&](int n0, int n) {
+    // query's list.  `again`: in a query's second scan.
+    auto process = [&](auto again, int n0, int n) {
         wave_sync();
         const uint64_t entry = lane < n ? queue[n0 + lane] : 0ull;
         const int q = (int)(entry >> 32);
@@ -730,7 +781,22 @@ __global__ __launch_bounds__(kFilterThreads) void scan_filter_kernel(FilterArgs 
         uint32_t w[P / 4 > 0 ? P / 4 : 1];
         load_row_words<P>(a.codes, item, w);
         bool live = lane < n;
-        if constexpr (FINE) {
+        if constexpr (!decltype(again)::value) {
+            if (__builtin_expect(calls++ > units_seen + 12u, 0)) {  // (as long as that is not so, nothing is counted)
+                // (units begun: those handed out less what the waves hold)
+                const uint32_t out = (uint32_t)__builtin_amdgcn_readfirstlane((int)lds_peek(next_unit)), begun = out > 4 * NW ? out - 3 * NW : NW;
+                const uint32_t line = begun * (kWave * NI / 4);
+                uint64_t over = __ballot(live && atomicAdd(&passed[q], 1u) > (line > give_up_from ? line : give_up_from));
+#pragma unroll 1
+                while (over != 0) {
+                    const int qo = __builtin_amdgcn_readlane(q, __builtin_ctzll(over));
+                    over &= ~__ballot(q == qo);
+                    give_up(qo);
+                }
+                gone = (uint32_t)__builtin_amdgcn_readfirstlane((int)lds_peek(given_up));
+            }
+        }
+        if constexpr (FINE && !decltype(again)::value) {
             uint32_t sum = 0;
 #pragma unroll
             for (int k = 0; k < M; ++k) sum += fine[(size_t)q * entries + (uint32_t)k * stride + filter_sub_id<M, CW>(w, 0, k)];
@@ -758,7 +824,9 @@ __global__ __launch_bounds__(kFilterThreads) void scan_filter_kernel(FilterArgs 
         if (want) {
             int bin = t - p.t_first;
             bin = bin < 0 ? 0 : (bin > kFilterBins - 1 ? kFilterBins - 1 : bin);
-            if (a.share) (void)__hip_atomic_fetch_add(a.hist + (size_t)(q0 + q) * kFilterBins + bin, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            // (a shared histogram is not cleared for the second scan: no item may be counted twice)
+            if (decltype(again)::value && a.share) {}
+            else if (a.share) (void)__hip_atomic_fetch_add(a.hist + (size_t)(q0 + q) * kFilterBins + bin, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             else atomicAdd(&hist[q * kFilterBins + bin], 1u);
         }
         // Who still has a key to place is kept as a mask in scalar registers, never as a flag per lane that goes round the
@@ -796,6 +864,8 @@ __global__ __launch_bounds__(kFilterThreads) void scan_filter_kernel(FilterArgs 
         look();
     };
 
+    if (__builtin_expect(__builtin_amdgcn_readfirstlane((int)hopeless) != 0, 0)) give_up(wave);
+
     // ---- stream
     int queued = 0;                                           // entries in this wave's queue
     uint32_t s[W];                                            // the fields' start values
@@ -812,6 +882,7 @@ __global__ __launch_bounds__(kFilterThreads) void scan_filter_kernel(FilterArgs 
         for (int j = 0; j < W; ++j) s[j] = (uint32_t)__builtin_amdgcn_readfirstlane((int)s[j]);
     };
     auto scan_unit = [&](uint32_t u, const uint32_t (&w)[Sh::kWords], const uint32_t (&id)[NI]) {
+        ++units_seen;
         uint32_t sum[NI][W];
         uint32_t any = 0;
 #pragma unroll
@@ -859,12 +930,14 @@ __global__ __launch_bounds__(kFilterThreads) void scan_filter_kernel(FilterArgs 
             const uint64_t who = __ballot(taken);
             if (who == 0) break;
             const int bit = mask != 0u ? __builtin_ctz(mask) : 0;
-            const int q = W16 ? (bit & 15) * 2 + (bit >> 4) : (bit & 7) * 4 + (bit >> 3);
+            const int q = query_of(bit);
             if (taken) queue[queued + __popcll(who & ((1ull << lane) - 1ull))] = ((uint64_t)q << 32) | item;
             queued += __popcll(who);
             if (queued >= kWave) {
                 queued -= kWave;
-                process(queued, kWave);
+                process(std::false_type(), queued, kWave);
+#pragma unroll
+                for (int e = 0; e < NI; ++e) hits[e] &= ~gone;
             }
         }
     };
@@ -907,15 +980,162 @@ __global__ __launch_bounds__(kFilterThreads) void scan_filter_kernel(FilterArgs 
         if (blk == 0 && wave == 0 && n_left != 0) {
             for (int q = 0; q < nq; ++q) {
                 if ((uint32_t)lane < n_left) queue[queued + lane] = ((uint64_t)q << 32) | (first_left + (uint32_t)lane);
-                queued += (int)n_left;
-                if (queued >= kWave) { queued -= kWave; process(queued, kWave); }
+                queued += (int)n_left;                        // (at most 3 of 16 queries beside the 63 that may wait: there is room)
             }
         }
     }
     stamp<STAMP>(rec, kStampStreamed, lane);
-    if (queued != 0) process(0, queued);
+#pragma unroll 1
+    while (queued != 0) {
+        const int n = queued < kWave ? queued : kWave;
+        queued -= n;
+        process(std::false_type(), queued, n);
+    }
     stamp<STAMP>(rec, kStampOffered, lane);
     __syncthreads();
+
+    // ---- the queries that were given up, W at a time: lists, counters and floors as at the start, exact tables in the counts'
+    // place; what exceeds a query's floor and its list's K-th best key goes through the queue like any hit
+    uint32_t todo = (uint32_t)__ballot(lane < QT && (lds_peek(passed + (lane < QT ? lane : 0)) & kLost) != 0u);
+    while (__builtin_expect(todo != 0, 0)) {
+        int qs[W];
+#pragma unroll
+        for (int j = 0; j < W; ++j) {
+            qs[j] = todo != 0 ? __builtin_ctz(todo) : -1;
+            todo &= todo - 1u;
+            const int q = qs[j];
+            if (q < 0) continue;
+            for (int i = tid; i < cap; i += NT) lists[(size_t)q * cap + i] = 0ull;
+            if (tid < kFilterBins) hist[q * kFilterBins + tid] = 0u;
+            if (tid == 0) { thr[q] = 0ull; cnt[q] = 0u; set_t(q, par[q].t_first); }
+        }
+        for (uint32_t i = tid; i < entries; i += NT) {
+            const uint32_t k = i / (uint32_t)stride, g = i - k * (uint32_t)stride;
+#pragma unroll
+            for (int j = 0; j < W; ++j)
+                tab[i * W + j] = qs[j] >= 0 && g < (uint32_t)b ? __float_as_uint(a.S[((size_t)(q0 + qs[j]) * M + k) * b + g]) : 0u;
+        }
+        if (tid == 0) *next_unit = NW;
+        uint32_t u = wave;
+        fetch_ids(u, ia);
+        if constexpr (P <= 16) fetch(u, ia, wa);
+        __syncthreads();
+        queued = 0;
+        bool done = units == 0;
+        while (!done) {
+            // (the next unit's codes on their way while this one is scored)
+            int pending = 0;
+            if (lane == 0) pending = (int)atomicAdd(next_unit, 1u);
+            const uint32_t un = (uint32_t)__builtin_amdgcn_readfirstlane(pending);
+            fetch_ids(un, ib);
+            if constexpr (P <= 16) fetch(un, ib, wb);
+            // scores that matter: above the sample's floor and the list's K-th best
+            float floor[W];
+#pragma unroll
+            for (int j = 0; j < W; ++j) {
+                const int q = qs[j] < 0 ? 0 : qs[j];
+                const uint64_t kth = lds_peek(thr + q);
+                floor[j] = kth != 0ull ? fmaxf(score_of_key(kth), par[q].floor) : par[q].floor;
+                if (qs[j] < 0) floor[j] = __builtin_nanf("");
+            }
+            uint32_t hits[NI];                                // per item bit j: query qs[j]
+            if (u < units) {
+#pragma unroll
+                for (int e = 0; e < NI; ++e) {
+                    float acc[W];
+                    // (four lookups on their way together: few registers, and sixteen waves hide each other's waits)
+                    auto add4 = [&](const uint32_t* row, int base, int k0, bool first) {   // sub-ids base + k0 .. k0 + 3, of which `row` starts with `base`
+                        Word v[4];
+#pragma unroll
+                        for (int k = k0; k < k0 + 4; ++k) v[k - k0] = reinterpret_cast<const Word*>(tab)[(base + k) * stride + filter_sub_id<M, CW>(row, 0, k)];
+#pragma unroll
+                        for (int k = 0; k < 4; ++k) {
+                            float x[W];
+                            if constexpr (W == 1) x[0] = __uint_as_float(v[k]);
+                            else if constexpr (W == 2) { x[0] = __uint_as_float(v[k].x); x[1] = __uint_as_float(v[k].y); }
+                            else { x[0] = __uint_as_float(v[k].x); x[1] = __uint_as_float(v[k].y); x[2] = __uint_as_float(v[k].z); x[3] = __uint_as_float(v[k].w); }
+#pragma unroll
+                            for (int j = 0; j < W; ++j) acc[j] = first && k == 0 ? x[j] : acc[j] + x[j];
+                        }
+                        __builtin_amdgcn_sched_barrier(0);
+                    };
+                    if constexpr (P <= 16) {
+#pragma unroll
+                        for (int k0 = 0; k0 < M; k0 += 4) add4(&wa[e * P / 4], 0, k0, k0 == 0);
+                    } else {                                  // wide rows: piece by piece from memory
+                        const uint32_t at = item_of(u, e, ia);
+                        const uint4* const row = reinterpret_cast<const uint4*>(a.codes + (size_t)(at != ~0u ? at : 0u) * P);
+                        constexpr int kPer = 16 / CW;         // sub-ids of a piece
+#pragma unroll
+                        for (int j = 0; j < W; ++j) acc[j] = -0.0f;   // (-0 + x is x, whatever x)
+#pragma unroll 1
+                        for (int i = 0; i < P / 16; ++i) {
+                            const uint4 x = row[i];
+                            const uint32_t piece_words[4] = {x.x, x.y, x.z, x.w};
+#pragma unroll
+                            for (int k0 = 0; k0 < kPer; k0 += 4) add4(piece_words, i * kPer, k0, false);
+                        }
+                    }
+                    hits[e] = 0;
+#pragma unroll
+                    for (int j = 0; j < W; ++j) hits[e] |= (uint32_t)(acc[j] >= floor[j]) << j;
+                    if (__ballot(hits[e] != 0u) != 0) {
+                        const uint32_t item = item_of(u, e, ia);
+#pragma unroll
+                        for (int j = 0; j < W; ++j)
+                            if (item == ~0u || make_key(acc[j] + 0.0f, item) <= lds_peek(thr + (qs[j] < 0 ? 0 : qs[j]))) hits[e] &= ~(1u << j);
+                    }
+                }
+            } else {
+                done = true;
+#pragma unroll
+                for (int e = 0; e < NI; ++e) hits[e] = 0;
+                if constexpr (P < 16 && !SUB) {               // the items after the last whole code vector (at most 3 of W queries)
+                    const uint32_t first_left = total * (16 / P), n_left = (uint32_t)a.N - first_left;
+                    if (blk == 0 && wave == 0 && n_left != 0) {
+#pragma unroll
+                        for (int j = 0; j < W; ++j) {
+                            if (qs[j] < 0) continue;
+                            if ((uint32_t)lane < n_left) queue[queued + lane] = ((uint64_t)qs[j] << 32) | (first_left + (uint32_t)lane);
+                            queued += (int)n_left;
+                        }
+                    }
+                }
+            }
+            for (;;) {
+                uint32_t mask = 0, item = 0;
+                bool taken = false;
+#pragma unroll
+                for (int e = 0; e < NI; ++e) {
+                    const bool here = !taken && hits[e] != 0u;
+                    mask = here ? hits[e] : mask;
+                    item = here ? item_of(u, e, ia) : item;
+                    hits[e] = here ? hits[e] & (hits[e] - 1u) : hits[e];
+                    taken = taken || here;
+                    asm volatile("" : "+v"(hits[e]));
+                }
+                const uint64_t who = __ballot(taken);
+                if (who == 0 && !(done && queued != 0)) break;
+                int q = 0;
+#pragma unroll
+                for (int j = 0; j < W; ++j) q = (mask & (0u - mask)) == (1u << j) ? qs[j] : q;
+                if (taken) queue[queued + __popcll(who & ((1ull << lane) - 1ull))] = ((uint64_t)q << 32) | item;
+                queued += __popcll(who);
+                if (queued >= kWave || who == 0) {
+                    const int n = queued < kWave ? queued : kWave;
+                    queued -= n;
+                    process(std::true_type(), queued, n);
+                }
+            }
+            look();
+            u = un;
+#pragma unroll
+            for (int e = 0; e < NI; ++e) ia[e] = ib[e];
+#pragma unroll
+            for (int i = 0; i < Sh::kWords; ++i) wa[i] = wb[i];
+        }
+        __syncthreads();
+    }
 
     // ---- a wave per query: keys that reach the final floor, ranked by counting, straight to the workspace
     if (wave < nq) {
@@ -942,7 +1162,7 @@ __global__ __launch_bounds__(kFilterThreads) void scan_filter_kernel(FilterArgs 
                 a.ws_keys[((size_t)(q0 + q) * nblk + blk) * K + t] = key;
             }
         };
-        if (!SUB && p.flat) {
+        if (!SUB && p.flat()) {
             for (int t = lane; t < K; t += kWave) out(t, blk == 0 ? make_key(p.off + 0.0f, (uint32_t)t) : 0ull);
         } else if (kept > 3 * kWave) {                               // (counting costs kept^2 / 64: 192 keys as much as a sort of 256)
             sort_wave_list(list, cap, kept, K, lane);

@@ -445,6 +445,30 @@ def test_scan_by_upper_bounds_of_tables_that_are_not_bell_shaped(pq, oracle, kin
             _bounds_case(pq, oracle, wide, _odd_tables(kind, rng.standard_normal((B, m, 700), dtype=np.float32)), K)
 
 
+@pytest.mark.parametrize("kind", ["rare_high", "denormal", "equal_rows", "mixed"])
+@pytest.mark.parametrize("m,K", [(4, 10), (8, 1), (8, 100), (8, 300), (16, 10), (16, 40), (32, 10), (64, 5)])
+def test_queries_that_the_bounds_are_no_use_for(pq, oracle, m, K, kind):
+    # a large entry that five items have, sums that hardly differ, a catalogue of seven rows: such queries are scanned a second
+    # time, exactly; "mixed" has them beside ordinary ones in a tile (more of them than one pass takes)
+    rng = np.random.default_rng(m + K)
+    N, B = 60_003, 13
+    codes = rng.integers(0, 256, (N, m), dtype=np.uint8)
+    S = rng.standard_normal((B, m, 256), dtype=np.float32)
+    which = slice(None) if kind != "mixed" else [0, 2, 3, 5, 8, 9, 12]
+    if kind == "denormal":
+        S = (S * np.float32(1e-40)).astype(np.float32)
+    elif kind == "equal_rows":
+        codes = np.ascontiguousarray(codes[np.arange(N) % 7])
+    else:
+        codes[codes[:, 1] == 7, 1] = 8
+        codes[[3, 4000, 4001, 33_333, N - 1], 1] = 7
+        S[which, 1, 7] = 1e5
+    _bounds_case(pq, oracle, codes, S, K)
+    if m <= 16:
+        _bounds_case(pq, oracle, codes, S, K, subset=rng.permutation(N)[:N - 5000].astype(np.int32))
+        _bounds_case(pq, oracle, codes.astype(np.uint16), S, K)
+
+
 @pytest.mark.parametrize("kind", ["zero_queries", "one_masked", "each_masked", "lowest"])
 @pytest.mark.parametrize("N,m,B,K", [(1_280_000, 8, 64, 10), (2_000_000, 16, 48, 100)])
 def test_batches_of_masked_and_zero_queries_are_scanned_as_fast_as_others(pq, N, m, B, K, kind):
