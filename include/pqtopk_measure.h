@@ -100,11 +100,37 @@ int pq_measure_sync_variant(int variant, void* scratch, size_t scratch_bytes, vo
  * kernels on shapes the lean ones would serve.  mask bit 0: catalogue scans never take the short kernel (scores in
  * registers, one selection) but the general scan kernel; bit 1: folds never take the small-K fold but the general
  * one; bit 2: Eq. 4 never runs on the matrix cores but in the scalar kernels; bit 3: batches are never scanned by
- * upper bounds but with every score computed; bit 4: they are scanned by upper bounds whatever their size.  0 restores
- * the library's own choice.  Process-wide, takes effect for calls made after it returns (workspace sizes depend on bits
- * 3 and 4).  Returns the previous mask.
+ * upper bounds but with every score computed; bit 4: they are scanned by upper bounds whatever their size; bit 5: a
+ * candidate list is never left to one workgroup per query but for want of more.  0 restores the library's own choice.
+ * Process-wide, takes effect for calls made after it returns (workspace sizes depend on bits 3 to 5).  Returns the
+ * previous mask.
  */
 int pq_measure_force_general(int mask);
+
+/*
+ * How a call would be served: the scan kernel its shape (and the mask above) leads to, and how that is laid out.  Pure host
+ * arithmetic.  kind: PQ_PLAN_BYTES for pq_score_topk(), PQ_PLAN_LIST for pq_score_topk_subset() (N: candidates), PQ_PLAN_WIDE for
+ * pq_score_topk_u16().  `plan` (host) receives PQ_PLAN_FIELDS values.  Errors: PQ_ERR_NULL, PQ_ERR_SHAPE, PQ_ERR_UNSUPPORTED.
+ */
+#define PQ_PLAN_BYTES  0
+#define PQ_PLAN_LIST   1
+#define PQ_PLAN_WIDE   2
+#define PQ_PLAN_KERNEL      0   /* PQ_KERNEL_* */
+#define PQ_PLAN_GROUPS      1   /* workgroups that share a query */
+#define PQ_PLAN_QUERIES     2   /* queries of a workgroup */
+#define PQ_PLAN_FIELD_BITS  3   /* scans by bounds: 8 or 16 */
+#define PQ_PLAN_FINE        4   /* ... counts in 256ths of a step beside 8-bit fields */
+#define PQ_PLAN_SHARED      5   /* ... a query's workgroups share their floors */
+#define PQ_PLAN_PARTS       6   /* ... parts of the sample ... */
+#define PQ_PLAN_ROUNDS      7   /* ... and the rounds of each */
+#define PQ_PLAN_FIELDS      8
+#define PQ_KERNEL_GENERAL     0
+#define PQ_KERNEL_BATCHED     1
+#define PQ_KERNEL_SHORT       2
+#define PQ_KERNEL_LONG        3
+#define PQ_KERNEL_SHORT_LIST  4
+#define PQ_KERNEL_BOUNDS      5
+int pq_measure_plan(long long N, int B, int m, int b, int K, int kind, int* plan);
 
 /*
  * One whole step (pq_subitem_scores, then pq_score_topk's scan and fold launches) with the measurement instances of

@@ -83,6 +83,8 @@ def lib() -> ctypes.CDLL:
         L.pq_measure_sync_variant.restype = I
         L.pq_measure_force_general.argtypes = [I]
         L.pq_measure_force_general.restype = I
+        L.pq_measure_plan.argtypes = [LL, I, I, I, I, I, ctypes.POINTER(I * 8)]
+        L.pq_measure_plan.restype = I
         L.pq_measure_step_stamps.argtypes = [P, P, P, LL, I, I, I, I, I, P, P, P, P, SZ, P, SZ, ctypes.POINTER(I * 2), P]
         L.pq_measure_step_stamps.restype = I
         L.pq_strerror.argtypes = [I]
@@ -447,9 +449,23 @@ def pq_measure_sync_variant(variant: int, scratch: torch.Tensor, iters: int) -> 
 
 def pq_measure_force_general(mask: int) -> int:
     """Bit 0: scans avoid the short kernel; bit 1: folds avoid the small-K fold; bit 2: Eq. 4 avoids the matrix cores;
-    bit 3: batches are not scanned by upper bounds; bit 4: they are, whatever their size (workspace sizes depend on both);
-    0: the library's choice.  Returns the previous mask."""
+    bit 3: batches are not scanned by upper bounds; bit 4: they are, whatever their size; bit 5: candidate lists are spread
+    over workgroups (workspace sizes depend on these three); 0: the library's choice.  Returns the previous mask."""
     return int(lib().pq_measure_force_general(int(mask)))
+
+
+PQ_PLAN_KINDS = {"scan": 0, "subset": 1, "scan16": 2}
+PQ_PLAN_KERNELS = ("general", "batched", "short", "long", "short list", "bounds")
+
+
+def pq_measure_plan(kind: str, N: int, B: int, m: int, b: int, K: int) -> dict:
+    """How a call of that shape is served (no GPU needed): the scan kernel and its layout, see pqtopk_measure.h."""
+    plan = (ctypes.c_int * 8)()
+    rc = lib().pq_measure_plan(N, B, m, b, K, PQ_PLAN_KINDS[kind], ctypes.byref(plan))
+    if rc != PQ_OK:
+        raise PQError(rc, "pq_measure_plan")
+    return dict(zip(("kernel", "groups", "queries", "field_bits", "fine", "shared", "parts", "rounds"),
+                    (PQ_PLAN_KERNELS[plan[0]], *plan[1:])))
 
 
 PQ_STAMP_SLOTS, PQ_STAMP_RECORDS = 16, 8192

@@ -54,7 +54,8 @@ using namespace pqk;
 thread_local char g_hip_error[256] = "no HIP error recorded";
 
 // pq_measure_force_general(): bit 0 keeps calls off the short and long scans, bit 1 off fold_small_kernel, bit 2 Eq. 4 off the
-// matrix cores, bit 3 off the scans by upper bounds; bit 4 on them wherever they can (0: the product's choice)
+// matrix cores, bit 3 off the scans by upper bounds; bit 4 on them wherever they can; bit 5 spreads short candidate lists
+// over the chip (0: the product's choice)
 std::atomic<int> g_force_general{0};
 
 int record_hip(hipError_t e) {
@@ -355,7 +356,7 @@ ScanPlan make_plan(long long N, int B, int m, int K, bool generic = false, int c
     p.subset_vecs = 0;
     if (generic && cw == 1 && (m == 4 || m == 8 || m == 16) && !(g_force_general.load(std::memory_order_relaxed) & 1)) {
         long long nb = kAssumedCUs / B;
-        if (nb < 1 || subset_direct_pays(N, m, B)) nb = 1;
+        if (nb < 1 || (subset_direct_pays(N, m, B) && !(g_force_general.load(std::memory_order_relaxed) & 32))) nb = 1;
         const long long thin = (N + kThreads - 1) / kThreads;              // workgroups if every thread held one candidate
         if (nb > thin) nb = thin;
         const long long per_thread = (N + kThreads * nb - 1) / (kThreads * nb);
@@ -1155,7 +1156,30 @@ int pq_score_topk_profile(const uint8_t* codes, const float* S, long long N, int
 }
 
 int pq_measure_force_general(int mask) {
-    return g_force_general.exchange(mask & 31, std::memory_order_relaxed);
+    return g_force_general.exchange(mask & 63, std::memory_order_relaxed);
+}
+
+int pq_measure_plan(long long N, int B, int m, int b, int K, int kind, int* plan) {
+    if (!plan) return PQ_ERR_NULL;
+    if (kind < PQ_PLAN_BYTES || kind > PQ_PLAN_WIDE) return PQ_ERR_SHAPE;
+    const int cw = kind == PQ_PLAN_WIDE ? 2 : 1;
+    const int rc = check_topk_shape(N, B, m, b, K, cw);
+    if (rc != PQ_OK) return rc;
+    const ScanPlan p = kind == PQ_PLAN_LIST ? make_plan(N, B, m, K, true) : kind == PQ_PLAN_WIDE ? make_plan(N, B, m, K, false, 2, b) : make_plan(N, B, m, K);
+    if (p.scan_lds > kMaxLdsBytes || p.fold_lds > kMaxLdsBytes) return PQ_ERR_UNSUPPORTED;
+    for (int i = 0; i < PQ_PLAN_FIELDS; ++i) plan[i] = 0;
+    plan[PQ_PLAN_KERNEL] = p.filter ? PQ_KERNEL_BOUNDS : p.tiled ? PQ_KERNEL_BATCHED : p.short_scan ? PQ_KERNEL_SHORT : p.long_scan ? PQ_KERNEL_LONG
+                           : p.short_subset ? PQ_KERNEL_SHORT_LIST : PQ_KERNEL_GENERAL;
+    plan[PQ_PLAN_GROUPS] = p.nblk;
+    plan[PQ_PLAN_QUERIES] = p.filter ? p.f_queries : p.tiled ? kQ : 1;
+    if (p.filter) {
+        plan[PQ_PLAN_FIELD_BITS] = p.f_w16 ? 16 : 8;
+        plan[PQ_PLAN_FINE] = p.f_fine;
+        plan[PQ_PLAN_SHARED] = p.f_share;
+        plan[PQ_PLAN_PARTS] = p.f_parts;
+        plan[PQ_PLAN_ROUNDS] = p.f_rounds;
+    }
+    return PQ_OK;
 }
 
 int pq_measure_step_stamps(const float* queries, const float* centroids, const uint8_t* codes, long long N, int B,

@@ -338,3 +338,20 @@ def test_workspace_of_large_batches_is_bounded(lib):
                 if m <= 16:
                     assert ws16(2_000_000, B, m, 32_768 // m, K) <= most, (m, B, K)
                     assert wsub(2_000_000, B, m, 256, K) <= most, (m, B, K)
+
+
+def test_plans_the_gpu_tests_count_on(pqlib_path):
+    """The shapes of the GPU tests lead where those tests say (the planner is host arithmetic)."""
+    from paper_2408_09992_amd import binding
+    from test_parity_gpu import SHARED_FLOORS
+    seen = set()
+    for kind, N, B, m, b, K in SHARED_FLOORS:
+        p = binding.pq_measure_plan(kind, N, B, m, b, K)
+        assert p["kernel"] == "bounds" and p["shared"] == 1 and p["groups"] > 1, (kind, N, B, m, b, K, p)
+        seen.add((kind, m, p["field_bits"], p["fine"]))
+    assert {(k, m) for k, m, _, _ in seen} == {("scan", m) for m in (4, 8, 16, 32, 64)} | {(k, m) for k in ("subset", "scan16") for m in (4, 8, 16)}
+    assert {bits for k, m, bits, _ in seen if m == 16 and k == "scan"} == {8, 16}
+    with pytest.raises(binding.PQError):
+        binding.pq_measure_plan("scan", 10, 1, 8, 256, 11)
+    assert binding.pq_measure_plan("scan", 10_000, 1, 4, 256, 10)["kernel"] == "short"
+    assert binding.pq_measure_plan("scan", 50_000_000, 1, 8, 256, 10)["kernel"] == "general"

@@ -469,6 +469,54 @@ def test_queries_that_the_bounds_are_no_use_for(pq, oracle, m, K, kind):
         _bounds_case(pq, oracle, codes.astype(np.uint16), S, K)
 
 
+# Batches whose workgroups share their floors in device memory (long shares, few workgroups per query): every row geometry
+# and field width of each kind of call.  kind, N (candidates of a list), B, m, b, K
+SHARED_FLOORS = [("scan", 271_046, 1650, 4, 256, 10), ("scan", 137_321, 1650, 8, 256, 100), ("scan", 69_570, 700, 16, 256, 10),
+                 ("scan", 97_743, 550, 16, 256, 40), ("scan", 97_742, 600, 32, 256, 10), ("scan", 97_742, 300, 64, 256, 10),
+                 ("subset", 271_047, 1650, 4, 256, 10), ("subset", 137_321, 1650, 8, 256, 10), ("subset", 69_571, 700, 16, 256, 10),
+                 ("subset", 97_743, 550, 16, 256, 50), ("scan16", 137_323, 1400, 4, 300, 10), ("scan16", 69_573, 1400, 8, 300, 10),
+                 ("scan16", 69_573, 700, 8, 1024, 10), ("scan16", 97_742, 550, 16, 300, 10), ("scan16", 69_570, 700, 16, 256, 10)]
+
+
+@pytest.mark.parametrize("tables", ["bell", "ties", "given_up"])
+@pytest.mark.parametrize("kind,N,B,m,b,K", SHARED_FLOORS)
+def test_floors_shared_between_workgroups(pq, oracle, kind, N, B, m, b, K, tables):
+    # all queries against the kernels that do not scan by bounds, every ninth against the oracle
+    assert pq.pq_measure_plan(kind, N, B, m, b, K)["shared"] == 1
+    rng = np.random.default_rng(N + B)
+    items = N + N // 3 if kind == "subset" else N
+    codes = rng.integers(0, b, (items, m), dtype=np.uint16 if kind == "scan16" else np.uint8)
+    S = rng.standard_normal((B, m, b), dtype=np.float32)
+    if tables == "ties":                                       # some ten thousand items with one score, and equal rows
+        S = np.round(S)
+        codes[items // 2:items // 2 + 5000] = codes[:5000]
+    elif tables == "given_up":                                 # a third of the queries let everything pass, in tiles with others
+        codes[codes[:, 1] == 7, 1] = 8
+        codes[[5, N // 2, N - 1], 1] = 7
+        S[::3, 1, 7] = 1e6
+    V = rng.permutation(items)[:N].astype(np.int32) if kind == "subset" else None
+    Gd, Sd, Vd = dev(codes), dev(S), dev(V) if V is not None else None
+
+    def run():
+        call = {"scan": pq.pq_score_topk, "scan16": pq.pq_score_topk_u16}.get(kind)
+        ids, sc = call(Gd, Sd, K) if call else pq.pq_score_topk_subset(Gd, Sd, Vd, K)
+        return ids.cpu().numpy(), sc.cpu().numpy()
+
+    ids, sc = run()
+    prev = pq.pq_measure_force_general(8)
+    try:
+        want_ids, want_sc = run()
+    finally:
+        pq.pq_measure_force_general(prev)
+    assert np.array_equal(ids, want_ids) and np.array_equal(sc.view(np.uint32), want_sc.view(np.uint32))
+    some = np.ascontiguousarray(S[::9])
+    if kind == "subset":
+        rid, rsc = oracle.score_topk_subset(codes, some, V, K)
+    else:
+        rid, rsc = (oracle.score_topk_u16 if kind == "scan16" else oracle.score_topk)(codes, some, K)
+    assert np.array_equal(ids[::9], rid) and np.array_equal(sc[::9].view(np.uint32), rsc.view(np.uint32))
+
+
 @pytest.mark.parametrize("kind", ["zero_queries", "one_masked", "each_masked", "lowest"])
 @pytest.mark.parametrize("N,m,B,K", [(1_280_000, 8, 64, 10), (2_000_000, 16, 48, 100)])
 def test_batches_of_masked_and_zero_queries_are_scanned_as_fast_as_others(pq, N, m, B, K, kind):
