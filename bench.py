@@ -441,6 +441,169 @@ def kcost_mode(args):
                       "config": {"workload": f"{cfg.name}: N={N} d={d} m={m} b={b} batch={B}, K in (1, 10, 100, 512)"}, "kcost": rows}))
 
 
+def _two_sides(torch, pq, prepare, masks):
+    """The same call under each of `masks` (pq_measure_force_general): microseconds a call (best of seven groups of launches, the masks
+    in turn) and whether all results are the same bits."""
+    calls, sames = [], []
+    for mask in masks:
+        prev = pq.pq_measure_force_general(mask)
+        call = prepare()
+        call()
+        torch.cuda.synchronize()
+        t0 = time.perf_counter()
+        call()
+        torch.cuda.synchronize()
+        calls.append((call, max(2, min(100, int(4e-3 / (time.perf_counter() - t0))))))
+        sames.append((call.ids.clone(), call.scores.clone()))
+        pq.pq_measure_force_general(prev)
+    best = [float("inf")] * len(masks)
+    e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    for _ in range(7):
+        for i, mask in enumerate(masks):
+            prev = pq.pq_measure_force_general(mask)
+            call, n = calls[i]
+            call()
+            e0.record()
+            for _ in range(n):
+                call()
+            e1.record()
+            torch.cuda.synchronize()
+            best[i] = min(best[i], e0.elapsed_time(e1) / n * 1e3)
+            pq.pq_measure_force_general(prev)
+    same = all(torch.equal(sames[0][0], x) and torch.equal(sames[0][1].view(torch.int32), y.view(torch.int32)) for x, y in sames)
+    return best, same
+
+
+def _prepared(torch, pq, W, kind, N, B, m, b, K, S=None, codes=None, seed=1):
+    """A way to marshal the call of that shape (for a list: N candidates of four times as many items), and its inputs."""
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    if S is None:
+        S = torch.randn((B, m, b), device="cuda", generator=g)
+    if kind == "subset":
+        codes = W.codes_uniform_device(4 * N, m, b, seed) if codes is None else codes
+        V = torch.randperm(4 * N, device="cuda", generator=g)[:N].to(torch.int32)
+        return lambda: pq.PreparedScoreTopKSubset(codes, S, V, K)
+    if kind == "scan16":
+        codes = W.codes_uniform_u16_device(N, m, b, seed) if codes is None else codes
+        return lambda: pq.PreparedScoreTopKU16(codes, S, K)
+    codes = W.codes_uniform_device(N, m, b, seed) if codes is None else codes
+    return lambda: pq.PreparedScoreTopK(codes, S, K)
+
+
+def rules_mode(args):
+    """Both sides of the rules that choose a scan, on either side of each of their lines: the whole call by the kernel the library
+    takes and by the one it leaves (pq_measure_force_general), the same inputs, the same results."""
+    import torch
+    from paper_2408_09992_amd import binding as pq, workloads as W
+    rows = []
+
+    def row(rule, kind, N, B, m, b, K, masks, names):
+        us, same = _two_sides(torch, pq, _prepared(torch, pq, W, kind, N, B, m, b, K), masks)
+        taken = pq.pq_measure_plan(kind, N, B, m, b, K)
+        rows.append({"rule": rule, "kind": kind, "N": N, "B": B, "m": m, "b": b, "K": K, names[0]: us[0], names[1]: us[1],
+                     "taken": taken["kernel"], "groups": taken["groups"], "same": same})
+        print(f"{rule:10s} {kind:7s} N={N:9d} B={B:4d} m={m:2d} b={b:4d} K={K:3d}  {names[0]} {us[0]:8.1f}  {names[1]} {us[1]:8.1f}  "
+              f"takes {taken['kernel']} ({taken['groups']})  same {same}", file=sys.stderr, flush=True)
+
+    # one query, scanned in segments (mask bit 6) or by the general kernel (bit 0): lines in N and K
+    for kind, m, b, Ns, Ks in (("scan", 4, 256, (12_000_000, 16_000_000, 18_000_000, 40_000_000), (10, 256, 257)),
+                               ("scan", 8, 256, (12_000_000, 19_000_000, 21_000_000, 38_000_000, 42_000_000), (10, 80, 81, 128, 129, 257)),
+                               ("scan", 16, 256, (9_000_000, 16_000_000, 18_000_000, 25_000_000), (10, 31, 32, 80, 81)),
+                               ("scan", 32, 256, (6_000_000, 12_000_000), (100, 128, 129)), ("scan", 64, 256, (5_000_000,), (128, 256, 257)),
+                               ("scan16", 4, 1024, (11_000_000, 13_000_000, 40_000_000), (10, 256, 257)),
+                               ("scan16", 8, 1024, (8_000_000, 40_000_000), (10, 300)), ("scan16", 16, 1024, (6_000_000, 20_000_000), (10, 256, 257))):
+        for N in Ns:
+            for K in Ks:
+                row("segments", kind, N, 1, m, b, K, (64, 1), ("segments", "general"))
+    # batches by bounds (mask bit 4) or with every score computed (bit 3): lines in lookups ...
+    for kind, m, b, K, least, Bs in (("scan", 4, 256, 10, 6.0e7, (4, 64)), ("scan", 8, 256, 10, 6.5e7, (4, 64)), ("scan", 8, 256, 10, 9.75e7, (2,)),
+                                     ("scan", 16, 256, 10, 1.0e8, (4, 64)), ("scan", 32, 256, 10, 1.6e8, (8, 64)), ("scan", 32, 256, 100, 2.1e8, (8,)),
+                                     ("scan", 64, 256, 10, 2.4e8, (8, 40)), ("scan", 64, 256, 100, 3.2e8, (16,)), ("scan", 64, 256, 200, 4.0e8, (16,)),
+                                     ("subset", 4, 256, 10, 2.2e7, (4, 64)), ("subset", 8, 256, 10, 2.2e7, (4, 64)), ("subset", 16, 256, 10, 4.5e7, (4, 64)),
+                                     ("scan16", 4, 1024, 10, 6.0e7, (4, 64)), ("scan16", 8, 1024, 10, 6.5e7, (4, 64)), ("scan16", 8, 1024, 10, 1.625e8, (512,)),
+                                     ("scan16", 16, 1024, 10, 1.3e8, (4, 64))):
+        for B in Bs:
+            for f in (0.5, 0.8, 1.25, 2.0):
+                N = int(f * least / (B * m))
+                if N >= K:
+                    row("lookups", kind, N, B, m, b, K, (16, 8), ("bounds", "without"))
+    # ... and in items per result (lookups enough in all of them)
+    for kind, m, b, B, K, per in (("scan", 8, 256, 64, 100, 500), ("scan", 8, 256, 64, 300, 800), ("scan", 8, 256, 512, 50, 500), ("scan", 8, 256, 512, 100, 800),
+                                  ("scan", 8, 256, 512, 200, 1300), ("scan", 16, 256, 512, 100, 2000), ("scan", 32, 256, 64, 100, 1000), ("scan", 64, 256, 64, 100, 1000),
+                                  ("subset", 8, 256, 64, 100, 150), ("subset", 8, 256, 64, 300, 350), ("subset", 16, 256, 512, 100, 600),
+                                  ("scan16", 8, 1024, 64, 100, 2000), ("scan16", 16, 256, 512, 100, 1000)):
+        for f in (0.5, 0.8, 1.25, 2.0):
+            row("per result", kind, int(f * per * K), B, m, b, K, (16, 8), ("bounds", "without"))
+    # short candidate lists: one workgroup per query writes the result, or spread (mask bit 5)
+    for m, B, K in ((4, 1, 10), (4, 30, 40), (4, 100, 200), (8, 1, 10), (8, 1, 300), (8, 30, 40), (16, 1, 10), (16, 30, 40)):
+        line = min(((112 << 10) + 720 * B) // (m + 8), 8 * 16 * 512 // m)
+        for f in (0.5, 0.8, 1.0):
+            row("one group", "subset", int(f * line), B, m, 256, K, (0, 32), ("one", "spread"))
+    print(json.dumps({"metric": "rules that choose a scan: both sides", "value": len(rows), "unit": "shapes", "n_gpus": 1, "vs_baseline": None,
+                      "dtype": "f32", "data": "synthetic", "all_results_same": all(r["same"] for r in rows), "rules": rows}))
+
+
+def _odd_tables(torch, kind, B, m, b):
+    g = torch.Generator(device="cuda").manual_seed(7)
+    S = torch.randn((B, m, b), device="cuda", generator=g)
+    k = m // 2
+    if kind == "a third of the queries zero":
+        S[::3] = 0
+    elif kind == "one entry -1e4":
+        S[:, k, 17] = -1e4
+    elif kind == "one entry per split -1e9":
+        S[:, :, 17] = -1e9
+    elif kind == "one entry the lowest float":
+        S[:, k, 17] = torch.finfo(torch.float32).min
+    elif kind == "half a split -1e9":
+        S[:, k, :b // 2] = -1e9
+    elif kind in ("one entry +1e4", "... that five items have"):
+        S[:, k, 17] = 1e4
+    elif kind == "all entries + 1e4":
+        S += 1e4
+    elif kind == "all entries + 1e7":
+        S += 1e7
+    elif kind == "denormal":
+        S *= 1e-39
+    elif kind == "Cauchy":
+        S /= torch.randn((B, m, b), device="cuda", generator=g).abs().clamp_min(1e-4)
+    elif kind == "whole numbers":
+        S = S.round()
+    return S.contiguous()
+
+
+def tables_mode(args):
+    """Batches by bounds (the library's choice) and with every score computed (mask bit 3), on score tables of many kinds: the time of
+    the bounds depends on them."""
+    import torch
+    from paper_2408_09992_amd import binding as pq, workloads as W
+    rows = []
+    shapes = [("scan", 1_280_000, 64, 8, 256, 10), ("scan", 1_280_000, 1024, 8, 256, 100), ("scan", 2_000_000, 64, 8, 256, 300), ("scan", 3_000_000, 64, 4, 256, 10),
+              ("scan", 5_000_000, 16, 16, 256, 10), ("scan", 2_000_000, 48, 16, 256, 100), ("scan", 50_000_000, 32, 8, 256, 10), ("scan", 1_000_000, 40, 64, 256, 10),
+              ("subset", 400_000, 64, 8, 256, 10), ("scan16", 1_280_000, 32, 8, 1024, 10)]
+    kinds = ["normal", "a third of the queries zero", "one entry -1e4", "one entry per split -1e9", "one entry the lowest float", "half a split -1e9",
+             "one entry +1e4", "... that five items have", "all entries + 1e4", "all entries + 1e7", "denormal", "Cauchy", "whole numbers", "seven rows"]
+    for kind, N, B, m, b, K in shapes:
+        items = 4 * N if kind == "subset" else N
+        base = (W.codes_uniform_u16_device if kind == "scan16" else W.codes_uniform_device)(items, m, b, 1)
+        for tables in kinds:
+            S, codes = _odd_tables(torch, tables, B, m, b), base
+            if tables == "... that five items have":
+                col = base[:, m // 2].to(torch.int32)
+                hit = col == 17
+                hit[torch.nonzero(hit)[:5, 0]] = False
+                codes = base.clone()
+                codes[:, m // 2] = torch.where(hit, torch.full_like(col, 18), col).to(base.dtype)
+            elif tables == "seven rows":
+                codes = base[:7].repeat((items + 6) // 7, 1)[:items].contiguous()
+            us, same = _two_sides(torch, pq, _prepared(torch, pq, W, kind, N, B, m, b, K, S, codes), (0, 8))
+            rows.append({"kind": kind, "N": N, "B": B, "m": m, "b": b, "K": K, "tables": tables, "bounds_us": us[0], "without_us": us[1], "same": same})
+            print(f"{kind:7s} N={N:9d} B={B:4d} m={m:2d} b={b:4d} K={K:3d}  {tables:28s} bounds {us[0]:8.1f}  without {us[1]:8.1f}  same {same}", file=sys.stderr,
+                  flush=True)
+    print(json.dumps({"metric": "batches on score tables of many kinds: by bounds, and with every score computed", "value": len(rows), "unit": "rows", "n_gpus": 1,
+                      "vs_baseline": None, "dtype": "f32", "data": "synthetic", "all_results_same": all(r["same"] for r in rows), "tables": rows}))
+
+
 def matrix_cores_mode(args):
     """The two dense contractions beside the scan, on the matrix cores and on the scalar kernels
     (pq_measure_force_general bit 2): Eq. 4 over batch sizes (chains of K = 1 fp32 matrix instructions, bit-equal to the
@@ -690,6 +853,8 @@ def main():
                     "against the scalar kernels, over batch sizes")
     ap.add_argument("--yardsticks", action="store_true", help="machine yardsticks: empty launch, plain streaming read, "
                     "random gathers from LDS")
+    ap.add_argument("--rules", action="store_true", help="both sides of the rules that choose a scan, around each of their lines")
+    ap.add_argument("--tables", action="store_true", help="batches on score tables of many kinds, by bounds and with every score computed")
     ap.add_argument("--sweep-max-bytes", type=float, default=7e10, help="largest code matrix the sweep allocates")
     ap.add_argument("--sweep-check-bytes", type=float, default=1e9,
                     help="largest code matrix whose result the sweep checks against the oracle")
@@ -723,6 +888,12 @@ def main():
         return
     if args.matrix_cores:
         matrix_cores_mode(args)
+        return
+    if args.rules:
+        rules_mode(args)
+        return
+    if args.tables:
+        tables_mode(args)
         return
 
     import numpy as np

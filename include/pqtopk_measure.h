@@ -101,8 +101,9 @@ int pq_measure_sync_variant(int variant, void* scratch, size_t scratch_bytes, vo
  * registers, one selection) but the general scan kernel; bit 1: folds never take the small-K fold but the general
  * one; bit 2: Eq. 4 never runs on the matrix cores but in the scalar kernels; bit 3: batches are never scanned by
  * upper bounds but with every score computed; bit 4: they are scanned by upper bounds whatever their size; bit 5: a
- * candidate list is never left to one workgroup per query but for want of more.  0 restores the library's own choice.
- * Process-wide, takes effect for calls made after it returns (workspace sizes depend on bits 3 to 5).  Returns the
+ * candidate list is never left to one workgroup per query but for want of more; bit 6: a single query over a catalogue too
+ * long for the short kernel is always scanned in segments.  0 restores the library's own choice.
+ * Process-wide, takes effect for calls made after it returns (workspace sizes depend on bits 3 to 6).  Returns the
  * previous mask.
  */
 int pq_measure_force_general(int mask);

@@ -55,7 +55,7 @@ thread_local char g_hip_error[256] = "no HIP error recorded";
 
 // pq_measure_force_general(): bit 0 keeps calls off the short and long scans, bit 1 off fold_small_kernel, bit 2 Eq. 4 off the
 // matrix cores, bit 3 off the scans by upper bounds; bit 4 on them wherever they can; bit 5 spreads short candidate lists
-// over the chip (0: the product's choice)
+// over the chip; bit 6: longer single queries always in segments (0: the product's choice)
 std::atomic<int> g_force_general{0};
 
 int record_hip(hipError_t e) {
@@ -167,19 +167,23 @@ constexpr long long kDirectUnits(int row) { return row <= 16 ? 8 : row == 32 ? 4
 
 // Where one workgroup takes all N candidates of a query's list and writes the result itself.  A compute unit gathers about one row
 // per clock, whatever its length, and looks up m entries for it: a candidate costs m + 8 here.  Spread over the chip this passes, but
-// the fold's launch comes on top, and so do the tables that every workgroup loads, the more of the chip B queries fill.  Steps of
-// 15,000 candidates, m = 4, by one workgroup and spread: B = 1 13.9 and 9.8 us (K = 5), 19.1 and 15.1 (K = 500); B = 30 17.7 and 14.5;
-// B = 100, K = 200 21.9 and 22.9.  10,000 candidates: within 5 % of each other at B = 1 and 6, B = 30, K = 40 14.4 and 16.2; 7000 at
-// K = 40: 10.1 and 11.8.  At m = 16 the list that a workgroup holds at most (3500: 10.1 and 11.3) lies below the line.
+// the fold's launch (3 us of host time) comes on top, and so do the tables that every workgroup loads, the more of the chip B queries
+// fill.  Calls back to back, where the host's time is hidden (bench.py --rules; one workgroup and spread, us): m = 4, B = 1, K = 10:
+// 4800 candidates 6.0 and 6.3, 7700 8.0 and 6.3, 9600 8.8 and 6.4; B = 30, K = 40: 5700 6.8 and 9.2, 11,400 10.9 and 10.0; B = 100,
+// K = 200: 15,600 17.9 and 18.5; m = 8, B = 1: 3600 5.7 and 6.1, 7200 8.7 and 6.3 (K = 300: 10.9 and 10.5).  The line lies where one
+// launch less still pays for a program that the host's time bounds: at B = 1 up to 2.4 us of the GPU's time above the other side.
 bool subset_direct_pays(long long N, int m, int B) {
     if (N * m > kDirectUnits(16) * 16LL * kThreads) return false;
     return N * (m + 8) <= (112LL << 10) + 720LL * B;
 }
 
-// Where one query's catalogue is scanned in segments (scan_long_kernel) and not by the general kernel's per-wave lists.  Measured at
-// 5e6 to 5e7 items, K from 3 to 512: with more than 256 results nearly always (1.2 to 3.6 times as fast) and for rows of 8 and 16 bytes of
-// two-byte sub-ids (1.08 to 1.26); otherwise while the first cut, the lists' merge and the sorting of full lists weigh more than the general kernel's
-// twice as many waves.
+// Where one query's catalogue is scanned in segments (scan_long_kernel) and not by the general kernel's per-wave lists: while the first
+// cut, the lists' merge and the sorting of full lists weigh more than the general kernel's twice as many waves.  Both sides
+// around the lines (bench.py --rules; segments and general, us): m = 4, K = 10: 16M items 22.2 and 22.8, 18M 24.6 and 23.8 (K = 257 on
+// 40M: 73 and 56, on the wrong side of its line); m = 8: 19M 34.9 and 36.2 at K = 10, 40.6 and 51.2 at K = 80; 21M 37.7 and 38.2, 44.2
+// and 54.2 (the line in K could lie lower); 42M at K = 128 79.8 and 87.1, at 257 96.5 and 95.6; m = 16: within 4 % at K = 10 and 31,
+// 16M at K = 80 61 and 67; m = 32, 12M: 86.8 and 91.6 at K = 129; m = 64: 5M 85.2 and 79.5 at K = 257; two bytes, m = 4: 13M 26.9 and
+// 29.9 at K = 10, 40M at K = 256 88 and 83; m = 8: 40M 113 and 121; m = 16: within 3 %.
 bool long_scan_pays(long long N, int m, int K, int cw) {
     if (cw == 2) return m == 4 ? K <= 256 || N <= 12000000 : m == 8 || (m == 16 && K > 256);
     switch (m) {
@@ -336,8 +340,9 @@ ScanPlan make_plan(long long N, int B, int m, int K, bool generic = false, int c
     }
     // Longer catalogues of a single query are scanned in segments, one workgroup per CU.
     p.long_scan = false;
-    if (!(without & kNoLong) && !p.short_scan && p.vec && !generic && !p.tiled && B == 1 && long_scan_pays(N, m, K, cw) &&
-        !(g_force_general.load(std::memory_order_relaxed) & 1)) {
+    if (!(without & kNoLong) && !p.short_scan && p.vec && !generic && !p.tiled && B == 1 &&
+        !(g_force_general.load(std::memory_order_relaxed) & 1) &&
+        (long_scan_pays(N, m, K, cw) || ((g_force_general.load(std::memory_order_relaxed) & 64) && (cw == 2 || m >= 4)))) {
         const size_t table = cw == 1 ? lut_floats * (m <= 8 ? kTableCopies : 1) * sizeof(float) : table16;
         if (table + sizeof(LongSelectLds<kLongThreads>) <= kMaxLdsBytes) {
             p.long_scan = true;
@@ -388,11 +393,14 @@ constexpr size_t kFilterTableBytes = 64u << 20;
 // LDS reads a CU returns per clock when every lane reads at random: of 4-, 8- and 16-byte words.
 constexpr double kGather4 = 8.7, kGather8 = 8.5, kGather16 = 5.0;
 
-// Lookups (B * N * m) from which a batch is scanned by upper bounds.  Measured against the scans side by side on catalogues of
-// 2e4 to 1e7 items, batches of 2 to 300 queries, K from 10 to 500: the sample, the tables and one launch more (some 12 us
-// together) are paid back from 6e7 lookups on at m = 4; longer rows cost more to prepare, the most at m = 64 with many results.
-// Two queries fill half a word's fields; more than 256 make the sample take turns on the CUs, which costs two-byte sub-ids with
-// their larger tables most.  Candidate lists gain earlier: the rows are gathered once per sixteen queries, not once per query.
+// Lookups (B * N * m) from which a batch is scanned by upper bounds: the sample, the tables and one launch more (some 12 us
+// together) are then paid back; longer rows cost more to prepare, the most at m = 64 with many results.  Two queries fill half a
+// word's fields; more than 256 make the sample take turns on the CUs, which costs two-byte sub-ids with their larger tables most.
+// Candidate lists gain earlier: the rows are gathered once per sixteen queries, not once per query.
+// At four fifths and five fourths of the lines (bench.py --rules; by bounds and without, us): B = 4, K = 10: m = 4 17.8 and 19.2, 19.4 and
+// 22.6; m = 8 19.6 and 19.8, 21.7 and 23.8; m = 16 21.6 and 22.6, 26.4 and 33.3; m = 32 (B = 8) 29.4 and 29.8, 32.3 and 44.8; m = 64
+// (B = 8) 37.1 and 41.4, 41.6 and 62.0; lists, m = 8: 33.2 and 32.0, 38.9 and 43.7; two bytes, m = 8: 25.8 and 24.2, 28.5 and 30.5.
+// The shape that loses most by its line: a list of 68,750, m = 4, B = 64: 23.4 and 30.8, scanned without.
 double filter_min_lookups(int m, int K, int B, bool subset, int cw) {
     if (subset) return m <= 8 ? 2.2e7 : 4.5e7;
     double least = m == 4 ? 6.0e7 : m == 8 ? 6.5e7 : m == 16 ? 1.0e8 : m == 32 ? (K <= 64 ? 1.6e8 : 2.1e8) : K <= 64 ? 2.4e8 : K <= 128 ? 3.2e8 : 4.0e8;
@@ -403,6 +411,10 @@ double filter_min_lookups(int m, int K, int B, bool subset, int cw) {
 // ... and the items per result: with fewer, a sample that is an eighth of them gives too low a floor, and what passes it is
 // scored exactly (from tables in device memory: two-byte sub-ids' are large).  The more queries there are, the less the scans
 // side by side leave idle.  (m = 16 with sixteen-bit fields, more than 256 queries: against the batched kernel.)
+// At four fifths and five fourths of the lines (bench.py --rules; by bounds and without, us): m = 8, B = 64, K = 300: 40.9 and 44.2, 41.1 and
+// 54.5; B = 512, K = 100: 81.0 and 60.1, 70.2 and 87.4; K = 200: 196 and 169, 221 and 251; m = 16, B = 512, K = 100: 118 and 159 (it
+// could lie lower), 147 and 219; m = 32, B = 64, K = 100: 41.8 and 44.2, 47.4 and 59.9; lists, m = 8, B = 64, K = 300: 43 and 68, 46 and 93
+// (likewise); two bytes, m = 8, B = 64, K = 100: 36.3 and 37.1, 40.2 and 47.1.
 // The catalogue itself has at least eight items per table entry, 3.5 with long rows (m = 64, 100 queries of 60,000 items, K = 10: 87 ->
 // 60 us).
 long long filter_min_items_per_result(long long N, int m, int K, int B, bool subset, bool w16, int cw) {
@@ -1156,7 +1168,7 @@ int pq_score_topk_profile(const uint8_t* codes, const float* S, long long N, int
 }
 
 int pq_measure_force_general(int mask) {
-    return g_force_general.exchange(mask & 63, std::memory_order_relaxed);
+    return g_force_general.exchange(mask & 127, std::memory_order_relaxed);
 }
 
 int pq_measure_plan(long long N, int B, int m, int b, int K, int kind, int* plan) {

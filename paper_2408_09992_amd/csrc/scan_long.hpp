@@ -63,7 +63,7 @@ __device__ __forceinline__ void long_order(LongSelectLds<NT>& L, int n, int tid)
     __syncthreads();
 }
 
-// grid = (item blocks, B); one query per workgroup of kBigThreads.  As in scan_short_kernel, unit u of thread t of workgroup g is
+// grid = (item blocks, B); one query per workgroup of kLongThreads (512).  As in scan_short_kernel, unit u of thread t of workgroup g is
 // number (u * blocks + g) * NT + t; a segment is kUnits of them, its scores in registers, the codes of the next units under way in a
 // ring that runs on across segments.  The first segment gives a floor that K of the threads' best scores reach; after it the scores
 // at or above it (about K per segment) are appended to the candidates, without a barrier when all segments' can be expected to fit.
