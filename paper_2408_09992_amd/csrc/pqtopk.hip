@@ -31,6 +31,7 @@
 #include <stdint.h>
 #include <string.h>
 
+#include <algorithm>
 #include <atomic>
 #include <mutex>
 #include <tuple>
@@ -380,7 +381,9 @@ ScanPlan make_plan(long long N, int B, int m, int K, bool generic = false, int c
     if (!(without & kNoFilter)) {
         ScanPlan f = p;
         plan_filter(f, N, B, m, K, generic, cw, b);
-        if (f.filter) p = f;
+        // (the whole batch's tables at most 32 KB per result and 1 MB: a single result of each query is not worth larger ones)
+        const size_t others = f.filter ? (size_t)(B - f.f_batch) * ((size_t)f.f_entries * sizeof(uint16_t) + sizeof(FilterQuery) + kFilterBins * sizeof(uint32_t)) : 0;
+        if (f.filter && workspace_bytes(f, B, K) + others <= ((size_t)B * K << 15) + (1u << 20)) p = f;
     }
     p.direct = p.nblk == 1;
     return p;
@@ -459,7 +462,7 @@ void plan_filter(ScanPlan& p, long long N, int B, int m, int K, bool subset, int
     if (words == 0) return;
     const int row = m * cw, queries = words * fields;
     const long long together = (long long)(kFilterTableBytes / ((size_t)entries * sizeof(uint16_t))), turns = (B + together - 1) / together;
-    const int batch = turns == 1 ? B : (int)(((B + turns - 1) / turns + 15) & ~15LL);
+    const int batch = turns == 1 ? B : (int)std::min<long long>(((B + turns - 1) / turns + 15) & ~15LL, B);
     const long long tiles = (batch + queries - 1) / queries;
     const bool by_vector = row <= 16 && !subset;
     const long long units = by_vector ? N * row / 16 : N;
