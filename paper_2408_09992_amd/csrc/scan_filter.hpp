@@ -755,7 +755,7 @@ __global__ __launch_bounds__(kFilterThreads) void scan_filter_kernel(FilterArgs 
     // with exact scores, W queries at a time (below).
     // 1.28M items, m = 8, 64 queries with such an entry each, K = 10: 121 us instead of 808 (37 without it); 1024, K = 100: 3.1 ms
     // instead of 9.6.  (Given up at once, shared floors' queries with heavy-tailed tables took 1.3 ms instead of 0.5.)
-    uint32_t calls = 0, units_seen = 0, gone = 0;                // process() calls, units seen; queries given up, as far as this wave has looked
+    uint32_t batches = 0, units_seen = 0, gone = 0;           // batches scored, units seen; queries given up, as far as this wave has looked
     const uint32_t give_up_from = units * (kWave * NI) / (M >= 32 ? 4u : a.share ? 20u : 12u);
     auto give_up = [&](int q) {
         const uint32_t bit = 1u << bit_of(q);
@@ -771,6 +771,22 @@ __global__ __launch_bounds__(kFilterThreads) void scan_filter_kernel(FilterArgs 
         for (uint32_t i = lane; i < entries; i += kWave) atomicAnd(&tab[i * W + q / F], keep);
     };
 
+    auto count_passed = [&](int n0) {                         // queue entries [n0, n0 + 64), which have been scored
+        const int q = (int)(queue[n0 + lane] >> 32);
+        // (units begun: those handed out less what the waves hold)
+        const uint32_t out = (uint32_t)__builtin_amdgcn_readfirstlane((int)lds_peek(next_unit)), begun = out > 4 * NW ? out - 3 * NW : NW;
+        const uint32_t line = begun * (kWave * NI / 4);
+        uint64_t over = __ballot(atomicAdd(&passed[q], 1u) > (line > give_up_from ? line : give_up_from));
+#pragma unroll 1
+        while (over != 0) {
+            const int qo = __builtin_amdgcn_readlane(q, __builtin_ctzll(over));
+            over &= ~__ballot(q == qo);
+            give_up(qo);
+        }
+        wave_sync();
+        gone = (uint32_t)__builtin_amdgcn_readfirstlane((int)lds_peek(given_up));
+    };
+
     // Scores queue entries [n0, n0 + n), n <= 64, exactly, one per lane, and puts what reaches its query's floor into the
     // query's list.  `again`: in a query's second scan.
     auto process = [&](auto again, int n0, int n) {
@@ -781,21 +797,6 @@ __global__ __launch_bounds__(kFilterThreads) void scan_filter_kernel(FilterArgs 
         uint32_t w[P / 4 > 0 ? P / 4 : 1];
         load_row_words<P>(a.codes, item, w);
         bool live = lane < n;
-        if constexpr (!decltype(again)::value) {
-            if (__builtin_expect(calls++ > units_seen + 12u, 0)) {  // (as long as that is not so, nothing is counted)
-                // (units begun: those handed out less what the waves hold)
-                const uint32_t out = (uint32_t)__builtin_amdgcn_readfirstlane((int)lds_peek(next_unit)), begun = out > 4 * NW ? out - 3 * NW : NW;
-                const uint32_t line = begun * (kWave * NI / 4);
-                uint64_t over = __ballot(live && atomicAdd(&passed[q], 1u) > (line > give_up_from ? line : give_up_from));
-#pragma unroll 1
-                while (over != 0) {
-                    const int qo = __builtin_amdgcn_readlane(q, __builtin_ctzll(over));
-                    over &= ~__ballot(q == qo);
-                    give_up(qo);
-                }
-                gone = (uint32_t)__builtin_amdgcn_readfirstlane((int)lds_peek(given_up));
-            }
-        }
         if constexpr (FINE && !decltype(again)::value) {
             uint32_t sum = 0;
 #pragma unroll
@@ -936,8 +937,11 @@ __global__ __launch_bounds__(kFilterThreads) void scan_filter_kernel(FilterArgs 
             if (queued >= kWave) {
                 queued -= kWave;
                 process(std::false_type(), queued, kWave);
+                if (__builtin_expect(++batches > units_seen + 12u, 0)) {   // (as long as that is not so, nothing is counted)
+                    count_passed(queued);
 #pragma unroll
-                for (int e = 0; e < NI; ++e) hits[e] &= ~gone;
+                    for (int e = 0; e < NI; ++e) hits[e] &= ~gone;
+                }
             }
         }
     };
