@@ -749,11 +749,12 @@ __global__ __launch_bounds__(kFilterThreads) void scan_filter_kernel(FilterArgs 
     // Tables whose bounds say little (a large entry that hardly any item has stretches the steps; scores that hardly differ in
     // fp32; ties) let most items through, and each of them costs what a hundred others do.  A query that has let pass a quarter
     // of the items so far, and by then so many of the whole share that they have cost about what scanning it exactly
-    // costs (a twelfth; a quarter of wide rows, a twentieth with shared floors), or that the sample has found hopeless, is given up (counted from
+    // costs (a twelfth; a quarter of wide rows, a twentieth with shared floors; half that while its floor has not risen), or that
+    // the sample has found hopeless, is given up (counted from
     // where a wave has scored a dozen batches more than it has seen units, so that ordinary tables pay nothing): its counts
     // go to zero, so that nothing passes any more, and when the others are done its share is scanned again from the start
     // with exact scores, W queries at a time (below).
-    // 1.28M items, m = 8, 64 queries with such an entry each, K = 10: 121 us instead of 808 (37 without it); 1024, K = 100: 3.1 ms
+    // 1.28M items, m = 8, 64 queries with such an entry each, K = 10: 117 us instead of 808 (37 without it); 1024, K = 100: 2.5 ms
     // instead of 9.6.  (Given up at once, shared floors' queries with heavy-tailed tables took 1.3 ms instead of 0.5.)
     uint32_t batches = 0, units_seen = 0, gone = 0;           // batches scored, units seen; queries given up, as far as this wave has looked
     const uint32_t give_up_from = units * (kWave * NI) / (M >= 32 ? 4u : a.share ? 20u : 12u);
@@ -776,7 +777,9 @@ __global__ __launch_bounds__(kFilterThreads) void scan_filter_kernel(FilterArgs 
         // (units begun: those handed out less what the waves hold)
         const uint32_t out = (uint32_t)__builtin_amdgcn_readfirstlane((int)lds_peek(next_unit)), begun = out > 4 * NW ? out - 3 * NW : NW;
         const uint32_t line = begun * (kWave * NI / 4);
-        uint64_t over = __ballot(atomicAdd(&passed[q], 1u) > (line > give_up_from ? line : give_up_from));
+        // (a floor that has not risen by a step yet is less likely to)
+        const uint32_t from = t_of(q) == par[q].t_first ? give_up_from / 2 : give_up_from;
+        uint64_t over = __ballot(atomicAdd(&passed[q], 1u) > (line > from ? line : from));
 #pragma unroll 1
         while (over != 0) {
             const int qo = __builtin_amdgcn_readlane(q, __builtin_ctzll(over));
@@ -1024,6 +1027,9 @@ __global__ __launch_bounds__(kFilterThreads) void scan_filter_kernel(FilterArgs 
         fetch_ids(u, ia);
         if constexpr (P <= 16) fetch(u, ia, wa);
         __syncthreads();
+        float first_floor[W];
+#pragma unroll
+        for (int j = 0; j < W; ++j) first_floor[j] = par[qs[j] < 0 ? 0 : qs[j]].floor;
         queued = 0;
         bool done = units == 0;
         while (!done) {
@@ -1033,27 +1039,25 @@ __global__ __launch_bounds__(kFilterThreads) void scan_filter_kernel(FilterArgs 
             const uint32_t un = (uint32_t)__builtin_amdgcn_readfirstlane(pending);
             fetch_ids(un, ib);
             if constexpr (P <= 16) fetch(un, ib, wb);
-            // scores that matter: above the sample's floor and the list's K-th best
+            // scores that matter: above the sample's floor and the list's K-th best (none yet: key 0, whose score is a NaN and loses)
             float floor[W];
 #pragma unroll
-            for (int j = 0; j < W; ++j) {
-                const int q = qs[j] < 0 ? 0 : qs[j];
-                const uint64_t kth = lds_peek(thr + q);
-                floor[j] = kth != 0ull ? fmaxf(score_of_key(kth), par[q].floor) : par[q].floor;
-                if (qs[j] < 0) floor[j] = __builtin_nanf("");
-            }
+            for (int j = 0; j < W; ++j) floor[j] = score_of_key(lds_peek(thr + (qs[j] < 0 ? 0 : qs[j])));
+#pragma unroll
+            for (int j = 0; j < W; ++j) floor[j] = qs[j] < 0 ? __builtin_nanf("") : fmaxf(floor[j], first_floor[j]);
             uint32_t hits[NI];                                // per item bit j: query qs[j]
             if (u < units) {
 #pragma unroll
                 for (int e = 0; e < NI; ++e) {
                     float acc[W];
-                    // (four lookups on their way together: few registers, and sixteen waves hide each other's waits)
-                    auto add4 = [&](const uint32_t* row, int base, int k0, bool first) {   // sub-ids base + k0 .. k0 + 3, of which `row` starts with `base`
-                        Word v[4];
+                    // (a few lookups on their way together: few registers, and sixteen waves hide each other's waits)
+                    constexpr int kTogether = P <= 16 && M >= 8 ? 8 : 4;
+                    auto add = [&](const uint32_t* row, int base, int k0, bool first) {   // sub-ids base + k0 .., of which `row` starts with `base`
+                        Word v[kTogether];
 #pragma unroll
-                        for (int k = k0; k < k0 + 4; ++k) v[k - k0] = reinterpret_cast<const Word*>(tab)[(base + k) * stride + filter_sub_id<M, CW>(row, 0, k)];
+                        for (int k = k0; k < k0 + kTogether; ++k) v[k - k0] = reinterpret_cast<const Word*>(tab)[(base + k) * stride + filter_sub_id<M, CW>(row, 0, k)];
 #pragma unroll
-                        for (int k = 0; k < 4; ++k) {
+                        for (int k = 0; k < kTogether; ++k) {
                             float x[W];
                             if constexpr (W == 1) x[0] = __uint_as_float(v[k]);
                             else if constexpr (W == 2) { x[0] = __uint_as_float(v[k].x); x[1] = __uint_as_float(v[k].y); }
@@ -1065,7 +1069,7 @@ __global__ __launch_bounds__(kFilterThreads) void scan_filter_kernel(FilterArgs 
                     };
                     if constexpr (P <= 16) {
 #pragma unroll
-                        for (int k0 = 0; k0 < M; k0 += 4) add4(&wa[e * P / 4], 0, k0, k0 == 0);
+                        for (int k0 = 0; k0 < M; k0 += kTogether) add(&wa[e * P / 4], 0, k0, k0 == 0);
                     } else {                                  // wide rows: piece by piece from memory
                         const uint32_t at = item_of(u, e, ia);
                         const uint4* const row = reinterpret_cast<const uint4*>(a.codes + (size_t)(at != ~0u ? at : 0u) * P);
@@ -1077,7 +1081,7 @@ __global__ __launch_bounds__(kFilterThreads) void scan_filter_kernel(FilterArgs 
                             const uint4 x = row[i];
                             const uint32_t piece_words[4] = {x.x, x.y, x.z, x.w};
 #pragma unroll
-                            for (int k0 = 0; k0 < kPer; k0 += 4) add4(piece_words, i * kPer, k0, false);
+                            for (int k0 = 0; k0 < kPer; k0 += kTogether) add(piece_words, i * kPer, k0, false);
                         }
                     }
                     hits[e] = 0;
