@@ -102,8 +102,9 @@ int pq_measure_sync_variant(int variant, void* scratch, size_t scratch_bytes, vo
  * one; bit 2: Eq. 4 never runs on the matrix cores but in the scalar kernels; bit 3: batches are never scanned by
  * upper bounds but with every score computed; bit 4: they are scanned by upper bounds whatever their size; bit 5: a
  * candidate list is never left to one workgroup per query but for want of more; bit 6: a single query over a catalogue too
- * long for the short kernel is always scanned in segments.  0 restores the library's own choice.
- * Process-wide, takes effect for calls made after it returns (workspace sizes depend on bits 3 to 6).  Returns the
+ * long for the short kernel is always scanned in segments; bit 7: batches scanned by upper bounds are by pairs of lanes wherever
+ * these fit.  0 restores the library's own choice.
+ * Process-wide, takes effect for calls made after it returns (workspace sizes depend on bits 3 to 7).  Returns the
  * previous mask.
  */
 int pq_measure_force_general(int mask);
@@ -120,7 +121,7 @@ int pq_measure_force_general(int mask);
 #define PQ_PLAN_GROUPS      1   /* workgroups that share a query */
 #define PQ_PLAN_QUERIES     2   /* queries of a workgroup */
 #define PQ_PLAN_FIELD_BITS  3   /* scans by bounds: 8 or 16 */
-#define PQ_PLAN_FINE        4   /* ... counts in 256ths of a step beside 8-bit fields */
+#define PQ_PLAN_FINE        4   /* ... finer counts beside 8-bit fields: none, 0 */
 #define PQ_PLAN_SHARED      5   /* ... a query's workgroups share their floors */
 #define PQ_PLAN_PARTS       6   /* ... parts of the sample ... */
 #define PQ_PLAN_ROUNDS      7   /* ... and the rounds of each */

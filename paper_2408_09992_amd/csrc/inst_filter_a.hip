@@ -3,5 +3,4 @@
 #include "kernels.hpp"
 namespace pqk {
 PQ_FILTER_INSTANCES_A(PQ_FILTER_DEFINE, PQ_FILTERP_DEFINE)
-PQ_FILTER_INSTANCES_STAMPED(PQ_FILTER_DEFINE7)
 }

@@ -89,30 +89,26 @@ namespace pqk {
 #define PQ_SUBSET_M(X, M) X(M, 1, kThreads) X(M, 2, kThreads) X(M, 3, kThreads) X(M, 4, kThreads) X(M, 5, kThreads) \
     X(M, 6, kThreads) X(M, 7, kThreads) X(M, 8, kThreads)
 #define PQ_SUBSET_INSTANCES(X) PQ_SUBSET_M(X, 4) PQ_SUBSET_M(X, 8) PQ_SUBSET_M(X, 16)
-// scan_filter_kernel<M, CW, W, W16, SUB, FINE> and filter_prepare_kernel<M, CW, SUB>, by translation unit.  X for scans, Y
+// scan_filter_kernel<M, CW, W, W16, SUB, G, SHARE> and filter_prepare_kernel<M, CW, SUB, NT>, by translation unit.  X for scans, Y
 // for the kernels that prepare them
-#define PQ_FILTER_W3(X, M, CW, W16, SUB, FINE) X(M, CW, 1, W16, SUB, FINE) X(M, CW, 2, W16, SUB, FINE) X(M, CW, 4, W16, SUB, FINE)
-#define PQ_FILTER_W8(X, M, CW, SUB) PQ_FILTER_W3(X, M, CW, false, SUB, false) PQ_FILTER_W3(X, M, CW, false, SUB, true)
-// (one-byte sub-ids: the fine counts fit beside the 8-bit tables, but for sixteen queries of more than 128 results at m = 8: see
-// filter_may_be_coarse())
-#define PQ_FILTER_W8_BYTES(X, M, SUB) PQ_FILTER_W3(X, M, 1, false, SUB, true)
-#define PQ_FILTER_INSTANCES_A(X, Y) \
-    PQ_FILTER_W8_BYTES(X, 4, false) PQ_FILTER_W8_BYTES(X, 8, false) X(8, 1, 4, false, false, false) Y(4, 1, false) Y(8, 1, false)
-// (m = 16 with eight-bit fields and one-byte sub-ids: always with the fine counts, and then eight queries are the better tile)
-#define PQ_FILTER_INSTANCES_B(X, Y) \
-    X(16, 1, 1, false, false, true) X(16, 1, 2, false, false, true) PQ_FILTER_W3(X, 16, 1, true, false, false) Y(16, 1, false)
+#define PQ_FILTER_BOTH(X, M, CW, W, W16, SUB, G) X(M, CW, W, W16, SUB, G, false) X(M, CW, W, W16, SUB, G, true)
+#define PQ_FILTER_W(X, M, CW, SUB) X(M, CW, 1, false, SUB, 1, false) X(M, CW, 2, false, SUB, 1, false) \
+    PQ_FILTER_BOTH(X, M, CW, 4, false, SUB, 1) PQ_FILTER_BOTH(X, M, CW, 4, false, SUB, 2)
+#define PQ_FILTER_INSTANCES_A(X, Y) PQ_FILTER_W(X, 4, 1, false) Y(4, 1, false)
+#define PQ_FILTER_INSTANCES_A8(X, Y) PQ_FILTER_W(X, 8, 1, false) Y(8, 1, false)
+#define PQ_FILTER_INSTANCES_B(X, Y) PQ_FILTER_W(X, 16, 1, false) PQ_FILTER_BOTH(X, 16, 1, 4, true, false, 1) Y(16, 1, false)
+// (64 splits: 16-bit fields always, and room for four queries)
 #define PQ_FILTER_INSTANCES_C(X, Y) \
-    PQ_FILTER_W3(X, 32, 1, true, false, false) X(64, 1, 1, true, false, false) X(64, 1, 2, true, false, false) Y(32, 1, false) Y(64, 1, false)
-#define PQ_FILTER_INSTANCES_SUBSET(X, Y) \
-    PQ_FILTER_W8_BYTES(X, 4, true) PQ_FILTER_W8_BYTES(X, 8, true) X(8, 1, 4, false, true, false) \
-    X(16, 1, 1, false, true, true) X(16, 1, 2, false, true, true) \
-    PQ_FILTER_W3(X, 16, 1, true, true, false) \
-    Y(4, 1, true) Y(8, 1, true) Y(16, 1, true)
-#define PQ_FILTER_INSTANCES_U16(X, Y) \
-    PQ_FILTER_W8(X, 4, 2, false) PQ_FILTER_W8(X, 8, 2, false) PQ_FILTER_W3(X, 16, 2, false, false, true) PQ_FILTER_W3(X, 16, 2, true, false, false) \
-    Y(4, 2, false) Y(8, 2, false) Y(16, 2, false)
+    X(32, 1, 1, false, false, 1, false) PQ_FILTER_BOTH(X, 32, 1, 2, false, false, 1) PQ_FILTER_BOTH(X, 32, 1, 4, false, false, 1) \
+    PQ_FILTER_BOTH(X, 32, 1, 2, true, false, 1) PQ_FILTER_BOTH(X, 32, 1, 4, true, false, 1) \
+    X(64, 1, 1, true, false, 1, false) PQ_FILTER_BOTH(X, 64, 1, 2, true, false, 1) Y(32, 1, false) Y(64, 1, false)
+#define PQ_FILTER_INSTANCES_SUBSET(X, Y) PQ_FILTER_W(X, 4, 1, true) PQ_FILTER_W(X, 8, 1, true) Y(4, 1, true) Y(8, 1, true)
+#define PQ_FILTER_INSTANCES_SUBSET16(X, Y) PQ_FILTER_W(X, 16, 1, true) PQ_FILTER_BOTH(X, 16, 1, 4, true, true, 1) Y(16, 1, true)
+#define PQ_FILTER_INSTANCES_U16(X, Y) PQ_FILTER_W(X, 4, 2, false) PQ_FILTER_W(X, 8, 2, false) Y(4, 2, false) Y(8, 2, false)
+#define PQ_FILTER_INSTANCES_U16_16(X, Y) PQ_FILTER_W(X, 16, 2, false) Y(16, 2, false)
 // measurement instances (wall-clock stamps per wave) of those the named batch workloads run
-#define PQ_FILTER_INSTANCES_STAMPED(X) X(8, 1, 4, false, false, true, true) X(16, 1, 2, false, false, true, true)
+#define PQ_FILTER_STAMPED(X, M, G) X(M, 1, 4, false, false, G, false, true) X(M, 1, 4, false, false, G, true, true)
+#define PQ_FILTER_INSTANCES_STAMPED(X) PQ_FILTER_STAMPED(X, 8, 1) PQ_FILTER_STAMPED(X, 8, 2) PQ_FILTER_STAMPED(X, 16, 1)
 // the batched kernel
 #define PQ_TILED_INSTANCES(X) X(8, false) X(16, false) X(8, true) X(16, true)
 
@@ -128,12 +124,14 @@ namespace pqk {
 #define PQ_LONG_EXTERN(M, CW, C) extern PQ_LONG_DEFINE(M, CW, C)
 #define PQ_SUBSET_DEFINE(M, U, NT) template __global__ void scan_subset_kernel<M, U, NT>(const uint8_t*, const int*, const float*, void*, float*, uint32_t, uint32_t, int, int);
 #define PQ_SUBSET_EXTERN(M, U, NT) extern PQ_SUBSET_DEFINE(M, U, NT)
-#define PQ_FILTER_DEFINE(M, CW, W, W16, SUB, FINE) template __global__ void scan_filter_kernel<M, CW, W, W16, SUB, FINE>(FilterArgs);
-#define PQ_FILTER_EXTERN(M, CW, W, W16, SUB, FINE) extern PQ_FILTER_DEFINE(M, CW, W, W16, SUB, FINE)
-#define PQ_FILTER_DEFINE7(M, CW, W, W16, SUB, FINE, ST) template __global__ void scan_filter_kernel<M, CW, W, W16, SUB, FINE, ST>(FilterArgs);
-#define PQ_FILTER_EXTERN7(M, CW, W, W16, SUB, FINE, ST) extern PQ_FILTER_DEFINE7(M, CW, W, W16, SUB, FINE, ST)
-#define PQ_FILTERP_DEFINE(M, CW, SUB) template __global__ void filter_prepare_kernel<M, CW, SUB>(FilterArgs);
-#define PQ_FILTERP_EXTERN(M, CW, SUB) extern PQ_FILTERP_DEFINE(M, CW, SUB)
+#define PQ_FILTER_DEFINE(M, CW, W, W16, SUB, G, SH) template __global__ void scan_filter_kernel<M, CW, W, W16, SUB, G, SH>(FilterArgs);
+#define PQ_FILTER_EXTERN(M, CW, W, W16, SUB, G, SH) extern PQ_FILTER_DEFINE(M, CW, W, W16, SUB, G, SH)
+#define PQ_FILTER_DEFINE8(M, CW, W, W16, SUB, G, SH, ST) template __global__ void scan_filter_kernel<M, CW, W, W16, SUB, G, SH, ST>(FilterArgs);
+#define PQ_FILTER_EXTERN8(M, CW, W, W16, SUB, G, SH, ST) extern PQ_FILTER_DEFINE8(M, CW, W, W16, SUB, G, SH, ST)
+#define PQ_FILTERP_DEFINE(M, CW, SUB) template __global__ void filter_prepare_kernel<M, CW, SUB, kFilterThreads>(FilterArgs); \
+    template __global__ void filter_prepare_kernel<M, CW, SUB, kThreads>(FilterArgs);
+#define PQ_FILTERP_EXTERN(M, CW, SUB) extern template __global__ void filter_prepare_kernel<M, CW, SUB, kFilterThreads>(FilterArgs); \
+    extern template __global__ void filter_prepare_kernel<M, CW, SUB, kThreads>(FilterArgs);
 #define PQ_TILED_DEFINE(M, ST) template __global__ void scan_topk_tiled_kernel<M, ST>(ScanArgs, int);
 #define PQ_TILED_EXTERN(M, ST) extern PQ_TILED_DEFINE(M, ST)
 
@@ -153,12 +151,15 @@ PQ_LONG_INSTANCES(PQ_LONG_EXTERN)
 PQ_SUBSET_INSTANCES(PQ_SUBSET_EXTERN)
 PQ_SHORT16_INSTANCES(PQ_SHORT16_EXTERN)
 PQ_TILED_INSTANCES(PQ_TILED_EXTERN)
-PQ_FILTER_INSTANCES_STAMPED(PQ_FILTER_EXTERN7)
+PQ_FILTER_INSTANCES_STAMPED(PQ_FILTER_EXTERN8)
 PQ_FILTER_INSTANCES_A(PQ_FILTER_EXTERN, PQ_FILTERP_EXTERN)
+PQ_FILTER_INSTANCES_A8(PQ_FILTER_EXTERN, PQ_FILTERP_EXTERN)
 PQ_FILTER_INSTANCES_B(PQ_FILTER_EXTERN, PQ_FILTERP_EXTERN)
 PQ_FILTER_INSTANCES_C(PQ_FILTER_EXTERN, PQ_FILTERP_EXTERN)
 PQ_FILTER_INSTANCES_SUBSET(PQ_FILTER_EXTERN, PQ_FILTERP_EXTERN)
 PQ_FILTER_INSTANCES_U16(PQ_FILTER_EXTERN, PQ_FILTERP_EXTERN)
+PQ_FILTER_INSTANCES_U16_16(PQ_FILTER_EXTERN, PQ_FILTERP_EXTERN)
+PQ_FILTER_INSTANCES_SUBSET16(PQ_FILTER_EXTERN, PQ_FILTERP_EXTERN)
 #endif
 
 }  // namespace pqk

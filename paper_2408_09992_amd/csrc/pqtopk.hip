@@ -105,8 +105,12 @@ struct ScanPlan {
     bool f_w16;        // ... 16-bit fields (8-bit otherwise)
     int f_queries;     // ... queries per workgroup
     int f_cap;         // ... keys of a query's list
-    bool f_fine;       // ... 16-bit counts beside 8-bit fields
+    int f_lanes;       // ... lanes that share an item (1 or 2)
+    size_t f_pitch;    // ... bytes of a query's counts that go to LDS
+    int f_far;         // ... splits whose counts stay in device memory
+    int f_stride;      // ... table entries of a split
     bool f_share;      // ... the workgroups of a query share their floors
+    int f_prepare;     // ... threads of a workgroup that takes a part of the sample
     int f_sample;      // ... units of a part's sample
     int f_rounds;      // ... rounds of a part's sample
     int f_parts;       // ... parts of the sample
@@ -395,6 +399,9 @@ constexpr size_t kFilterTableBytes = 64u << 20;
 
 // LDS reads a CU returns per clock when every lane reads at random: of 4-, 8- and 16-byte words.
 constexpr double kGather4 = 8.7, kGather8 = 8.5, kGather16 = 5.0;
+// ... and of 16-byte words with an eighth of the splits read from device memory, and by pairs of lanes that read a row of 32 bytes together,
+// a quarter of the splits from device memory.
+constexpr double kGather16Far = 5.7, kGatherPairs = 7.4;
 
 // Lookups (B * N * m) from which a batch is scanned by upper bounds: the sample, the tables and one launch more (some 12 us
 // together) are then paid back; longer rows cost more to prepare, the most at m = 64 with many results.  Two queries fill half a
@@ -436,49 +443,74 @@ void plan_filter(ScanPlan& p, long long N, int B, int m, int K, bool subset, int
     const bool rows = (cw == 1 && !subset) ? (m == 4 || m == 8 || m == 16 || m == 32 || m == 64) : (m == 4 || m == 8 || m == 16);
     if (!rows || N * m * cw < 16) return;
     const long long entries = (long long)m * (cw == 1 ? kLutStride : b);
-    // Fields: eight bits as long as a score's sum of roundings stays small against its spread.  At m = 16 the bound is loose
-    // by half a standard deviation: twenty times as many items as necessary pass near a high floor, a hundred at larger K (and
-    // large tables leave no room for the fine counts that sort them out).
-    const bool w16 = m >= 32 || (m == 16 && (K > 32 || entries > 16 * kLutStride));
+    // Fields: eight bits, or sixteen, which halve the queries of an LDS read but let hardly anything pass that should not: at m = 64, and
+    // with few items per result, where more is scored than the reads save.  Calls of 16 bits and 8 (us): m = 32, K = 20: 48 queries, 300,000
+    // items 44.3 and 47.7, 600,000 65.5 and 59.9; 200 queries 125 and 181, 202 and 231; K = 10, 600,000 195 and 170; K = 100, 600,000: 224
+    // and 268; m = 16, K = 100: 200 queries, 300,000 items 85 and 132, 600,000 123 and 157, 300 queries, 600,000 196 and 203; 100 queries,
+    // 600,000 (8) 74; lists, m = 16, K = 100: 200 queries, 200,000 candidates 94 and 144, 1M 223 and 241; 64 queries, 1M 96 and 90.
+    bool w16 = m == 64;
+    if (m == 32) w16 = N < (long long)K * (K > 64 ? 10000 : B > 150 ? 40000 : 13000);
+    if (m == 16 && cw == 1) w16 = subset ? K > 32 || (B > 256 && N < 20000LL * K) : K > 32 && B > 128 && N < 8000LL * K;
     if (!(force & 16) && (B < 2 || (double)B * (double)N * m < filter_min_lookups(m, K, B, subset, cw) || 2 * N < (m >= 32 ? 7 : 16) * entries ||
                           N < filter_min_items_per_result(N, m, K, B, subset, w16, cw) * K))
         return;
     if (filter_prepare_lds_bytes(entries, m) > kMaxLdsBytes) return;
-    const int fields = w16 ? 2 : 4;
-    int cap = next_pow2(2 * K);
-    if (cap < 128) cap = 128;
-    double best_cost = 0.0;
-    int words = 0;
-    for (int w = 4; w >= 1; w >>= 1) {
-        if (m == 64 && w == 4) continue;
-        if (filter_lds_bytes(entries, w, w * fields, cap, false) > kMaxLdsBytes) continue;
+    const int fields = w16 ? 2 : 4, stride = (int)(entries / m);
+    int cap = K <= 16 ? 64 : next_pow2(2 * K);
+    if (K > 16 && cap < 128) cap = 128;
+    // Words of a lane's table entry, lanes that share an item: what reads least of the LDS's time.
+    // Pairs of lanes read a third more per clock, but a workgroup has twice the queries to prepare, to look after and to select for, and reads
+    // of device memory come in the way of the exact scores': for long scans of few results, where floors are not shared the longest.
+    // Calls by single lanes and by pairs (us; m = 8, K = 10): 32 queries, 3M items 36.4 and 37.8, 8M 62.9 and 57.2, 20M 124 and 99; 64 queries, 1M
+    // 31.2 and 34.3, 3M 53.9 and 51.2, 8M 108 and 88; 200, 1M 66 and 62, 8M 298 and 246; 500, 1M 112 and 123, 3M 269 and 260; K = 100:
+    // 32 queries, 8M 75 and 75, 20M 144 and 126; 200, 3M 154 and 220.  m = 4: 64 queries, 8M 66 and 64, 20M 126 and 120; 500, 3M 160 and 145.
+    // m = 16: 32, 3M 56.5 and 54.6, 8M 111 and 97; 200, 1M 105 and 114.  Lists: m = 4, 500 queries, 200,000 candidates 77 and 64, 1M 178 and 130.
+    const double pair_lookups = B > 128 && !(m == 8 && B <= 256) ? 5.5e9 : (m == 4 ? 2.0e9 : 1.4e9) * (K > 32 ? 1.5 : 1.0);
+    const bool pairs = subset ? m == 4 && B >= 400 && N >= 150000 : (double)B * (double)N * m >= pair_lookups && (K <= 32 || B <= 128);
+    double best_cost = 0.0, rate = 0.0;
+    int words = 0, lanes = 1;
+    for (int w = 8; w >= (w16 && m == 16 ? 4 : w16 && m == 32 ? 2 : 1); w >>= 1) {   // (8: four words for each of two lanes)
+        const int l = w == 8 ? 2 : 1, each = w == 8 ? 4 : w;
+        if (l == 2 && (w16 || !(pairs || (force & 128)))) continue;
+        if ((m >= 32 && l == 2) || (m == 64 && each == 4)) continue;
+        if (filter_lds_bytes(m, stride, each, w16, l, cap) > kMaxLdsBytes) continue;
         const long long tiles = (B + w * fields - 1) / (w * fields);
-        // (without the fine counts more is scored exactly, most of all at m = 16: 46 us with 16 queries per workgroup and
-        // without them, 41 us with eight and with them, on 5M items)
-        const bool coarse = !w16 && filter_lds_bytes(entries, w, w * fields, cap, true) > kMaxLdsBytes;
-        const double cost = (coarse ? (m == 16 ? 1.35 : 1.15) : 1.0) * (double)tiles / (w == 4 ? kGather16 : w == 2 ? kGather8 : kGather4);
-        if (words == 0 || cost < best_cost) { words = w; best_cost = cost; }
+        const double r = l == 2 ? kGatherPairs : each == 4 ? (filter_far_splits(m, 4, w16, 1) > 0 ? kGather16Far : kGather16) : each == 2 ? kGather8 : kGather4;
+        const double cost = (double)tiles * l / r;
+        if (words == 0 || cost < best_cost) { words = each; lanes = l; best_cost = cost; rate = r; }
+        if (l == 2 && (force & 128)) break;
     }
     if (words == 0) return;
-    const int row = m * cw, queries = words * fields;
+    const int row = m * cw, queries = words * fields * lanes;
     const long long together = (long long)(kFilterTableBytes / ((size_t)entries * sizeof(uint16_t))), turns = (B + together - 1) / together;
-    const int batch = turns == 1 ? B : (int)std::min<long long>(((B + turns - 1) / turns + 15) & ~15LL, B);
+    const int batch = turns == 1 ? B : (int)std::min<long long>(((B + turns - 1) / turns + 31) & ~31LL, B);
     const long long tiles = (batch + queries - 1) / queries;
     const bool by_vector = row <= 16 && !subset;
     const long long units = by_vector ? N * row / 16 : N;
     const int vecs = row >= 32 ? row / 16 : 1;
-    const long long per_round = (long long)kFilterThreads * (by_vector ? vecs : vecs * 16 / row);
+    const long long per_round = (long long)kFilterThreads / lanes * (by_vector ? vecs : vecs * 16 / row);
     const long long rounds = (units + per_round - 1) / per_round;
     // Item blocks per tile: one workgroup per CU, or a few one after the other when one filling would leave CUs idle.
-    const double stream_us = (double)N * m / ((words == 4 ? kGather16 : words == 2 ? kGather8 : kGather4) * 2400.0);
+    const double stream_us = (double)N * m * lanes / (rate * 2400.0);
+    // Workgroups of a query share their floors where they are few and their shares long, a round being a unit of every wave (fewer words:
+    // batches of a few queries).  K = 100, not shared and shared (us): m = 4, 200 queries, 8M items 236 and 179; m = 8, 3M 193 and 154; m = 16,
+    // 3M 427 (16-bit fields) and 275.
+    auto shares = [&](long long blocks) {
+        return blocks > 1 && ((blocks <= 16 && rounds / blocks >= 12) || (blocks <= 32 && rounds / blocks >= 32)) && (words == 4 || m >= 32);
+    };
     long long nb = 1;
     double best_us = 0.0;
-    for (int fill = 1; fill <= 4; ++fill) {
-        long long cand = (long long)kAssumedCUs * fill / tiles;
+    for (int fill = 1; fill <= 5; ++fill) {
+        long long cand = fill <= 4 ? (long long)kAssumedCUs * fill / tiles : 16;
+        if (fill == 5 && (kAssumedCUs / tiles < cand || !shares(cand))) break;   // (fewer, which share their floors)
         if (cand > rounds) cand = rounds;
         if (cand < 1) cand = 1;
+        // (rows of a list: with a multiple of 8 blocks, block x of every tile runs on XCD x % 8, whose L2 the tiles share:
+        // 200 queries, 1M of 4M items, m = 8, K = 10: 234 us with 19 blocks, 109 with 16)
+        if (subset && (cand & 7) * (N >= 150000 ? 2 : 5) <= cand) cand = cand < 8 ? cand : cand & ~7LL;
         const double per_cu = (double)((tiles * cand + kAssumedCUs - 1) / kAssumedCUs);
-        const double us = per_cu * (stream_us / (double)cand + 8.0);
+        // (workgroups that share their floors score less)
+        const double us = per_cu * (stream_us / (double)cand * (shares(cand) ? 1.0 : 1.2) + 8.0);
         if (fill == 1 || us < best_us) { best_us = us; nb = cand; }
     }
     p.filter = true;
@@ -490,14 +522,16 @@ void plan_filter(ScanPlan& p, long long N, int B, int m, int K, bool subset, int
     p.f_entries = entries;
     p.f_batch = batch;
     const int sample_units = (row == 8 || row == 16 || row == 32) ? 2 : 1;
-    p.f_sample = kFilterThreads * ((subset && row < 16) ? sample_units * 16 / row : sample_units);
+    p.f_prepare = batch >= 2 * kAssumedCUs && 4 * filter_prepare_lds_bytes(entries, m) <= kMaxLdsBytes ? kThreads : kFilterThreads;
+    p.f_sample = p.f_prepare * ((subset && row < 16) ? sample_units * 16 / row : sample_units);
     // The sample: n items cost n * m lookups of 4 bytes, and (K / n) of the catalogue then passes the first floor and is
     // scored from device memory, an eighth as fast: least together at about 5 sqrt(K N).  Where the workgroups of a query
     // share their floors those rise fast by themselves.
-    p.f_share = nb > 1 && nb <= 16 && rounds / nb >= 32;
+    p.f_share = shares(nb);
     const long long items_per_round = (long long)p.f_sample * N / units;
     long long want = (long long)(5.0 * sqrt((double)K * (double)N)) / items_per_round;
-    if (p.f_share && want > 1) want = 1;
+    const long long most_rounds = (nb > 16 ? 4 : K <= 32 ? 1 : m == 4 ? 4 : m == 8 ? 2 : 1) * (kFilterThreads / p.f_prepare);
+    if (p.f_share && want > most_rounds) want = most_rounds;
     if (want > N / 8 / items_per_round) want = N / 8 / items_per_round;
     if (want < 1) want = 1;
     long long parts = kAssumedCUs / batch;
@@ -505,16 +539,20 @@ void plan_filter(ScanPlan& p, long long N, int B, int m, int K, bool subset, int
     if (parts > want) parts = want;
     if (parts < 1 || 2 * K + 3 * parts > kFilterBest) parts = 1;
     long long sample_rounds = (want + parts / 2) / parts;
-    if (sample_rounds > 8) sample_rounds = 8;
+    if (sample_rounds > 8 * (kFilterThreads / p.f_prepare)) sample_rounds = 8 * (kFilterThreads / p.f_prepare);
     p.f_parts = (int)parts;
     p.f_rounds = (int)(sample_rounds < 1 ? 1 : sample_rounds);
     // scores a part leaves: twice its share of the K best and two more, never more than K
     long long best = (2 * K + parts - 1) / parts + 2;
     p.f_best = (int)(best < K ? best : K);
-    p.f_fine = !w16 && filter_lds_bytes(entries, words, queries, cap, true) <= kMaxLdsBytes;
+    p.f_lanes = lanes;
+    p.f_stride = stride;
+    p.f_far = filter_far_splits(m, words, w16, lanes);
+    p.f_pitch = align16((size_t)(m - p.f_far) * stride * (w16 ? sizeof(uint16_t) : sizeof(uint8_t)));
     p.nblk = (int)nb;
-    p.scan_lds = filter_lds_bytes(entries, words, queries, cap, p.f_fine);
-    p.scan_dyn_lds = p.scan_lds - (cw == 1 ? (size_t)entries * words * 4 : 0);   // (one-byte sub-ids: the tables are a static array)
+    p.scan_lds = filter_lds_bytes(m, stride, words, w16, lanes, cap);
+    // (one-byte sub-ids: the tables are a static array)
+    p.scan_dyn_lds = p.scan_lds - (cw == 2 ? 0 : filter_table_bytes(m, stride, words, w16, lanes));
 }
 
 size_t keys_bytes(const ScanPlan& p, int B, int K) {
@@ -523,12 +561,15 @@ size_t keys_bytes(const ScanPlan& p, int B, int K) {
 }
 
 // workspace: [B][nblk][K] keys from the scan | filter scans, for the f_batch queries scanned together: tables of counts | FilterQuery
-// records | histograms | the sample's best scores
-size_t counts_bytes(const ScanPlan& p) { return p.filter ? ((size_t)p.f_batch * p.f_entries * sizeof(uint16_t) + 255) & ~(size_t)255 : 0; }
+// records | histograms | the rows that stay in device memory | the sample's best scores
+size_t counts_bytes(const ScanPlan& p) { return p.filter ? ((size_t)p.f_batch * p.f_pitch + 255) & ~(size_t)255 : 0; }
+size_t far_bytes(const ScanPlan& p) {
+    return p.filter ? ((size_t)((p.f_batch + p.f_queries - 1) / p.f_queries) * p.f_far * (size_t)p.f_stride * p.f_queries + 255) & ~(size_t)255 : 0;
+}
 size_t query_bytes(const ScanPlan& p) { return p.filter ? ((size_t)p.f_batch * sizeof(FilterQuery) + 255) & ~(size_t)255 : 0; }
 size_t hist_bytes(const ScanPlan& p) { return p.filter ? (size_t)p.f_batch * kFilterBins * sizeof(uint32_t) : 0; }
 size_t workspace_bytes(const ScanPlan& p, int B, int K) {
-    return keys_bytes(p, B, K) + counts_bytes(p) + query_bytes(p) + hist_bytes(p) +
+    return keys_bytes(p, B, K) + counts_bytes(p) + query_bytes(p) + hist_bytes(p) + far_bytes(p) +
            (p.filter && p.f_parts > 1 ? ((size_t)p.f_batch * p.f_parts * p.f_best * sizeof(float) + 255) & ~(size_t)255 : 0);
 }
 
@@ -756,25 +797,16 @@ hipError_t launch_subset_m(const ScanPlan& p, const ScanArgs& a, int B, hipStrea
     }
 }
 
-// Whether a plan can ask for fields of W words without the fine counts.  16-bit fields: always without (m = 64: four words of tables
-// do not fit).  8-bit fields over one-byte sub-ids: where the counts do not fit for some K, the longest list that a K has being
-// 1024 keys; at m = 16 (K <= 32, lists of 128 keys) plan_filter() takes eight queries with the counts over sixteen without.
-// Two-byte sub-ids: as their alphabet has it, but at m = 16 tables of more than 16 * 256 entries have 16-bit fields.
-constexpr bool filter_may_be_coarse(int M, int CW, int W, bool W16) {
-    if (W16) return M < 64 || W < 4;
-    if (M == 16) return false;
-    if (CW == 2) return true;
-    for (int cap = 128; cap <= 1024; cap *= 2)
-        if (filter_lds_bytes(M * kLutStride, W, W * 4, cap, false) <= kMaxLdsBytes && filter_lds_bytes(M * kLutStride, W, W * 4, cap, true) > kMaxLdsBytes) return true;
-    return false;
-}
-
-template <int M, int CW, bool W16, bool SUB>
+template <int M, int CW, bool SUB>
 hipError_t launch_filter(const ScanPlan& p, const FilterArgs& a, hipStream_t st) {
     const size_t prep_lds = filter_prepare_lds_bytes(a.entries, M);
-    hipError_t e = allow_lds(filter_prepare_kernel<M, CW, SUB>, prep_lds);
-    if (e != hipSuccess) return e;
-    e = launch(filter_prepare_kernel<M, CW, SUB>, dim3(p.f_parts, a.B), kFilterThreads, prep_lds, st, a);
+    hipError_t e = hipSuccess;
+    auto prepare = [&](auto kernel) {
+        e = allow_lds(kernel, prep_lds);
+        if (e == hipSuccess) e = launch(kernel, dim3(p.f_parts, a.B), p.f_prepare, prep_lds, st, a);
+    };
+    if (p.f_prepare == kThreads) prepare(filter_prepare_kernel<M, CW, SUB, kThreads>);
+    else prepare(filter_prepare_kernel<M, CW, SUB, kFilterThreads>);
     if (e != hipSuccess) return e;
     auto go = [&](auto kernel) {
         e = allow_lds(kernel, p.scan_dyn_lds);
@@ -782,54 +814,47 @@ hipError_t launch_filter(const ScanPlan& p, const FilterArgs& a, hipStream_t st)
         return launch(kernel, dim3(p.nblk, (a.B + p.f_queries - 1) / p.f_queries), kFilterThreads, p.scan_dyn_lds, st, a);
     };
     if (a.stamps != nullptr) {
-        if constexpr (M == 8 && CW == 1 && !W16 && !SUB) {
-            if (p.f_words == 4 && p.f_fine) return go(scan_filter_kernel<8, 1, 4, false, false, true, true>);
+        if constexpr ((M == 8 || M == 16) && CW == 1 && !SUB) {
+            if (p.f_words == 4 && p.f_lanes == 1 && !p.f_w16)
+                return p.f_share ? go(scan_filter_kernel<M, 1, 4, false, false, 1, true, true>) : go(scan_filter_kernel<M, 1, 4, false, false, 1, false, true>);
         }
-        if constexpr (M == 16 && CW == 1 && !W16 && !SUB) {
-            if (p.f_words == 2 && p.f_fine) return go(scan_filter_kernel<16, 1, 2, false, false, true, true>);
+        if constexpr (M == 8 && CW == 1 && !SUB) {
+            if (p.f_words == 4 && p.f_lanes == 2)
+                return p.f_share ? go(scan_filter_kernel<8, 1, 4, false, false, 2, true, true>) : go(scan_filter_kernel<8, 1, 4, false, false, 2, false, true>);
         }
         return hipErrorInvalidValue;                         // (pq_measure_step_stamps() has checked)
     }
-    if constexpr (!W16) {
-        if (p.f_fine) {
-            switch (p.f_words) {
-                case 1: return go(scan_filter_kernel<M, CW, 1, W16, SUB, true>);
-                case 2: return go(scan_filter_kernel<M, CW, 2, W16, SUB, true>);
-                default:
-                    if constexpr (M < 16 || CW == 2) return go(scan_filter_kernel<M, CW, 4, W16, SUB, true>);
-            }
-        }
+    if constexpr ((M == 16 || M == 32) && CW == 1) {
+        if (p.f_w16 && p.f_words == 4) return p.f_share ? go(scan_filter_kernel<M, 1, 4, true, SUB, 1, true>) : go(scan_filter_kernel<M, 1, 4, true, SUB, 1, false>);
     }
-    switch (p.f_words) {
-        case 1:
-            if constexpr (filter_may_be_coarse(M, CW, 1, W16)) return go(scan_filter_kernel<M, CW, 1, W16, SUB, false>);
-            break;
+    if constexpr (M == 32) {
+        if (p.f_w16) return p.f_share ? go(scan_filter_kernel<32, 1, 2, true, false, 1, true>) : go(scan_filter_kernel<32, 1, 2, true, false, 1, false>);
+    }
+    switch (p.f_words * p.f_lanes) {
+        case 1: return go(scan_filter_kernel<M, CW, 1, M == 64, SUB, 1, false>);
         case 2:
-            if constexpr (filter_may_be_coarse(M, CW, 2, W16)) return go(scan_filter_kernel<M, CW, 2, W16, SUB, false>);
+            if constexpr (M >= 32) {
+                if (p.f_share) return go(scan_filter_kernel<M, CW, 2, M == 64, SUB, 1, true>);
+            }
+            return go(scan_filter_kernel<M, CW, 2, M == 64, SUB, 1, false>);
+        case 4:
+            if constexpr (M < 64) return p.f_share ? go(scan_filter_kernel<M, CW, 4, false, SUB, 1, true>) : go(scan_filter_kernel<M, CW, 4, false, SUB, 1, false>);
             break;
         default:
-            if constexpr (filter_may_be_coarse(M, CW, 4, W16)) return go(scan_filter_kernel<M, CW, 4, W16, SUB, false>);
+            if constexpr (M <= 16) return p.f_share ? go(scan_filter_kernel<M, CW, 4, false, SUB, 2, true>) : go(scan_filter_kernel<M, CW, 4, false, SUB, 2, false>);
     }
     return hipErrorInvalidValue;                             // (the plan never asks for it)
 }
 
 hipError_t launch_filter(const ScanPlan& p, const FilterArgs& a, int m, int cw, hipStream_t st) {
-    if (a.subset != nullptr) {
-        if (m == 4) return launch_filter<4, 1, false, true>(p, a, st);
-        if (m == 8) return launch_filter<8, 1, false, true>(p, a, st);
-        return p.f_w16 ? launch_filter<16, 1, true, true>(p, a, st) : launch_filter<16, 1, false, true>(p, a, st);
-    }
-    if (cw == 2) {
-        if (m == 4) return launch_filter<4, 2, false, false>(p, a, st);
-        if (m == 8) return launch_filter<8, 2, false, false>(p, a, st);
-        return p.f_w16 ? launch_filter<16, 2, true, false>(p, a, st) : launch_filter<16, 2, false, false>(p, a, st);
-    }
+    if (a.subset != nullptr) return m == 4 ? launch_filter<4, 1, true>(p, a, st) : m == 8 ? launch_filter<8, 1, true>(p, a, st) : launch_filter<16, 1, true>(p, a, st);
+    if (cw == 2) return m == 4 ? launch_filter<4, 2, false>(p, a, st) : m == 8 ? launch_filter<8, 2, false>(p, a, st) : launch_filter<16, 2, false>(p, a, st);
     switch (m) {
-        case 4: return launch_filter<4, 1, false, false>(p, a, st);
-        case 8: return launch_filter<8, 1, false, false>(p, a, st);
-        case 16: return p.f_w16 ? launch_filter<16, 1, true, false>(p, a, st) : launch_filter<16, 1, false, false>(p, a, st);
-        case 32: return launch_filter<32, 1, true, false>(p, a, st);
-        default: return launch_filter<64, 1, true, false>(p, a, st);
+        case 4: return launch_filter<4, 1, false>(p, a, st);
+        case 8: return launch_filter<8, 1, false>(p, a, st);
+        case 16: return launch_filter<16, 1, false>(p, a, st);
+        case 32: return launch_filter<32, 1, false>(p, a, st);
+        default: return launch_filter<64, 1, false>(p, a, st);
     }
 }
 
@@ -845,18 +870,22 @@ int enqueue_scan(const ScanPlan& p, const uint8_t* codes, const float* S, long l
         FilterArgs f;
         f.codes = codes; f.N = N; f.b = b; f.K = K; f.cap = p.f_cap;
         f.subset = subset; f.n_items = (uint32_t)(subset ? n_items : N);
-        f.counts = reinterpret_cast<uint16_t*>(ws);
+        f.counts = ws;
         f.query = reinterpret_cast<FilterQuery*>(ws + counts_bytes(p));
         f.entries = p.f_entries;
         f.hist = reinterpret_cast<uint32_t*>(ws + counts_bytes(p) + query_bytes(p));
-        f.best = reinterpret_cast<float*>(ws + counts_bytes(p) + query_bytes(p) + hist_bytes(p));
+        f.pitch = (uint32_t)p.f_pitch;
+        f.far = ws + counts_bytes(p) + query_bytes(p) + hist_bytes(p);
+        f.far_splits = p.f_far;
+        f.tile = p.f_queries;
+        f.wide = p.f_w16;
+        f.best = reinterpret_cast<float*>(ws + counts_bytes(p) + query_bytes(p) + hist_bytes(p) + far_bytes(p));
         f.sample = p.f_sample;
         f.rounds = p.f_rounds;
         f.parts = p.f_parts;
         f.best_per_part = p.f_best;
         f.share = p.f_share;
         f.stamps = stamps;
-        f.spare = p.f_w16 ? 3 : m + 3;
         for (int q0 = 0; q0 < B; q0 += p.f_batch) {          // (once, unless the batch is one of thousands)
             f.B = B - q0 < p.f_batch ? B - q0 : p.f_batch;
             f.S = S + (size_t)q0 * m * b;
@@ -1171,7 +1200,7 @@ int pq_score_topk_profile(const uint8_t* codes, const float* S, long long N, int
 }
 
 int pq_measure_force_general(int mask) {
-    return g_force_general.exchange(mask & 127, std::memory_order_relaxed);
+    return g_force_general.exchange(mask & 255, std::memory_order_relaxed);
 }
 
 int pq_measure_plan(long long N, int B, int m, int b, int K, int kind, int* plan) {
@@ -1189,7 +1218,6 @@ int pq_measure_plan(long long N, int B, int m, int b, int K, int kind, int* plan
     plan[PQ_PLAN_QUERIES] = p.filter ? p.f_queries : p.tiled ? kQ : 1;
     if (p.filter) {
         plan[PQ_PLAN_FIELD_BITS] = p.f_w16 ? 16 : 8;
-        plan[PQ_PLAN_FINE] = p.f_fine;
         plan[PQ_PLAN_SHARED] = p.f_share;
         plan[PQ_PLAN_PARTS] = p.f_parts;
         plan[PQ_PLAN_ROUNDS] = p.f_rounds;
@@ -1211,7 +1239,7 @@ int pq_measure_step_stamps(const float* queries, const float* centroids, const u
     // (the scan in segments has no measurement instance, that by upper bounds those of the named workloads: otherwise the kernels
     // that would run without them)
     ScanPlan p = make_plan(N, B, m, K, false, 1, kLutStride, kNoLong);
-    if (p.filter && (p.f_w16 || !p.f_fine || !((m == 8 && p.f_words == 4) || (m == 16 && p.f_words == 2))))
+    if (p.filter && (p.f_w16 || p.f_words != 4 || !(m == 8 || (m == 16 && p.f_lanes == 1))))
         p = make_plan(N, B, m, K, false, 1, kLutStride, kNoLong | kNoFilter);
     if (workspace_bytes_given < workspace_bytes(p, B, K)) return PQ_ERR_WORKSPACE;
     if (!(p.filter || p.tiled || m == 8))

@@ -6,34 +6,42 @@
 //
 // What bounds a batch is the LDS: random 16-byte gathers return 5 lane reads per clock and CU whatever they hold.  With
 // fp32 table entries one of them serves four queries; with 8-bit entries it serves sixteen (16-bit: eight), and the four
-// sums in a 32-bit word are made by ONE integer addition.  So:
+// sums in a 32-bit word are made by ONE integer addition.  Two lanes that read a row of 32 bytes together, for 32 queries, get 5.9 reads each,
+// and a quarter of the rows comes from device memory, through the L1, beside the LDS's: 7.4 together.  So:
 //   - a table entry S[k][j] is replaced by a count of steps with base_k + count * step >= S[k][j].  The sum A of an item's
 //     counts bounds its score from above: score <= sum(base) + A * step (+ the rounding of the fp32 chain, which `off`
 //     below includes).  An item whose A is below T = floor((f - off) / step) scores below f: it is out.
 //   - f is a floor of the query's K-th best score.  The first one comes from an exactly scored sample of the catalogue
 //     (K of the sample's items reach it); the scan raises it as it finds better items.
-//   - 8-bit counts are coarse: near a high floor three or four items pass for every one that should.  So the counts exist
-//     in 256ths of a step too (16 bits per entry and query, where LDS has room), and what passes is tried against those
-//     before it is scored: an exact score reads its table values from device memory, one lane per clock and CU.
+//   - one 8-bit sum over a row is coarse: every count is rounded up.  So a sum is over four splits, whose counts are of an M / 4 th of a
+//     step then, and sums are averaged, four fields by one v_lerp_u8: the bound is rounded up by two of some hundred steps whatever M
+//     is.  Two items pass for every one that should, three or four at m = 16 and 32; at m = 64, and where there are few items per result,
+//     16-bit fields are the better ones (one sum).  An exact score reads its table values from device memory, one lane per clock and CU.
 //   - what is left is scored exactly, by the same left-to-right fp32 chain as everywhere, and only exact scores enter
 //     lists, floors and results.  Bit for bit the same results as the other kernels, whatever the tables are.
 // The time does depend on the tables: an item that passes costs as much as a hundred that do not.  Masked entries and queries
 // of zeros (a padded batch) cost nothing extra, see filter_prepare_kernel; where most items pass all the same (a large entry
 // that hardly any item has, scores that hardly differ in fp32) a query is given up and its share scanned exactly, four queries
 // per LDS read.
-// A field starts at 128 - T (16-bit fields: 256 times that), so its top bit says A >= T.  Fields never carry into each
+// A sum starts at 128 - T (16-bit fields: 256 times that), so the top bit of their average says A >= T.  Fields never carry into each
 // other: `step` is chosen so that the largest possible sum is at most T_first + 127, T never falls, and T is capped at 128
 // (a lower T is always allowed).
+// 50M items, m = 8, 32 queries: scan 280 us with one sum of whole steps and 16-bit counts in LDS to sort out what passed, 208 now; 20M, m = 16, 32
+// queries, K = 10 and 100: whole calls 258 -> 198 and 470 -> 260; 3M, m = 32, 200 queries: 800 -> 432.
 #pragma once
 
 constexpr int kFilterThreads = kBigThreads;
 constexpr int kFilterWaves = kFilterThreads / kWave;
 constexpr int kFilterBins = 128;                  // histogram of exact scores per query, in units of T
-constexpr int kFilterQueue = 2 * kWave;           // a wave's queue of items to score exactly
+constexpr int kFilterQueue = 3 * kWave / 2;       // a wave's queue of items to score exactly
 constexpr int kFilterSpan = 127;                  // steps from the first T to the largest possible sum
-constexpr float kFilterT0 = 80.0f;                // where the first T of a query's own sample lies: 48 steps of room to rise
-constexpr float kFilterUp = 0.02f;                // 256ths of a step a count is rounded up by more than it must be, against the
-constexpr float kFilterDown = 0.02f;              // rounding of its own computation; steps T is rounded down by, likewise
+// Steps from the first floor to the largest possible sum (a sum's counts and T are rounded), and where the first T of a query's own sample lies:
+// the rest up to 128 is what it can rise by, and what lies further below it is looser.  Short rows have the floor near the largest sum.
+__host__ __device__ constexpr float filter_room(int m) { return m == 4 ? 80.0f : m == 8 ? 90.0f : 110.0f; }
+__host__ __device__ constexpr float filter_t0(int m) { return m == 4 ? 82.0f : m == 8 ? 98.0f : 100.0f; }
+constexpr float kFilterUp = 2.5e-4f;              // steps an 8-bit count is rounded up by more than it must be, against the
+constexpr float kFilterUp16 = 0.02f;              // rounding of its own computation; 256ths of one a 16-bit count is
+constexpr float kFilterDown = 0.02f;              // steps T is rounded down by, likewise
 constexpr int kHopeless = 256;
 constexpr int kSampleBins = 256;                  // histogram of a sample's scores
 constexpr int kSamplePasses = 8;                  // ... and the times its range is narrowed at most
@@ -57,17 +65,20 @@ struct FilterArgs {
     uint64_t* ws_keys;          // [B][nblk][K]
     int* out_ids;               // [B][K]: the result, when one workgroup scans everything for a query; nullptr: lists for the fold
     float* out_scores;
-    uint16_t* counts;           // [B][entries] table counts in 256ths of a step; entries = M * 256, or M * b for two-byte sub-ids
+    uint8_t* counts;            // [B][pitch] a query's counts of the splits that are looked up in LDS: bytes, or 16-bit words
+    uint8_t* far;               // [tile][splits][stride][queries of a tile] counts of the others, a row per sub-id; nullptr: none
     FilterQuery* query;         // [B]
     uint32_t* hist;             // [B][kFilterBins] exact scores found, by T above the first (cleared by filter_prepare_kernel)
     float* best;                // [B][parts][best_per_part] scores of sample items (parts > 1)
-    long long entries;
+    long long entries;          // of a query's tables: M * 256, or M * b for two-byte sub-ids
+    uint32_t pitch;
+    int far_splits, tile;       // splits looked up in device memory (the last ones), queries of a workgroup
+    int wide;                   // 16-bit counts
     int sample;                 // units of a part's sample per round (code vectors, or items of more than 16 bytes; candidates of a list)
     int rounds;                 // ... and the rounds
     int parts, best_per_part;
     int share;                  // the workgroups of a query share their floors
     uint64_t* stamps;           // STAMP instances only
-    int spare;                  // steps of the span left for rounding: an 8-bit sum rounds up once per split
 };
 
 // Row geometry.  P: bytes of an item's row.  A lane's unit of work is kVecs 16-byte vectors = kItems items.
@@ -81,6 +92,19 @@ struct FilterShape {
     static constexpr int kSampleItems = P >= 16 ? kSampleUnits : kSampleUnits * (16 / P);
     static constexpr int kSampleWords = P >= 16 ? kSampleUnits * P / 4 : kSampleUnits * 4;
 };
+
+// 8-bit sums hold the counts of four splits each: in the whole, as many sums of a step's M / 4 th parts as M / 4 are averaged, so that the bound of
+// an item is rounded up by two of 118 steps on average whatever M is (one sum over all splits: by M / 2).
+// Which sum a split belongs to: splits of neighbouring places go to different sums, forth and back, so that sums stay alike
+// where splits differ in their spread.
+__host__ __device__ constexpr int filter_sums(int m) { return m / 4; }
+__host__ __device__ constexpr int filter_members(int m) { return m / filter_sums(m); }
+__host__ __device__ constexpr int filter_member(int m, int sum, int i) { return i * filter_sums(m) + (i & 1 ? filter_sums(m) - 1 - sum : sum); }
+
+// Splits whose tables stay in device memory, so that the L1's way to the lanes works beside the LDS's.  G lanes share an item.
+__host__ __device__ constexpr int filter_far_splits(int m, int words, bool w16, int lanes) {
+    return w16 || words < 4 ? 0 : lanes == 2 ? (m == 4 ? 0 : m == 8 ? 2 : 3) : m == 32 ? 4 : 0;
+}
 
 template <int M, int CW>
 __device__ __forceinline__ uint32_t filter_sub_id(const uint32_t* w, int item, int k) {
@@ -180,10 +204,12 @@ __device__ __forceinline__ void find_sample_cut(const uint32_t* hist, int target
 //   M, CW: splits, bytes per sub-id; SUB: the sample is taken from a candidate list
 // Two workgroups per CU where the tables leave room (16 of 32 waves each: at most 64 vector and 80 scalar registers; with 88 scalar
 // ones a CU held one workgroup, and 1024 queries at m = 8 took 31 us instead of 21).
-template <int M, int CW, bool SUB>
-__global__ __launch_bounds__(kFilterThreads, M <= 16 ? 8 : 4) void filter_prepare_kernel(FilterArgs a) {
+// NT: threads.  512 where the queries alone are several workgroups per CU: four at a time then, and one's barriers pass in the others' work
+// (1000 queries of 300,000 items at m = 8, K = 10: 95 -> 90 us a step).
+template <int M, int CW, bool SUB, int NT>
+__global__ __launch_bounds__(NT, M <= 16 ? 8 : 4) void filter_prepare_kernel(FilterArgs a) {
     using Sh = FilterShape<M, CW>;
-    constexpr int NT = kFilterThreads, NW = kFilterWaves, P = Sh::P;
+    constexpr int NW = NT / kWave, P = Sh::P;
     extern __shared__ __align__(16) unsigned char smem[];
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
     const int q = blockIdx.y, part = blockIdx.x, b = a.b, K = a.K;
@@ -401,25 +427,66 @@ __global__ __launch_bounds__(kFilterThreads, M <= 16 ? 8 : 4) void filter_prepar
     // what fp32 chains of M additions (scores, sums of bases) can be off by
     const float slack = 4.0f * (float)(M + 1) * 5.9604645e-8f * sum_abs;
     const float floor_s = clamped ? cut : fmaxf(cut, sum_min - slack);   // (at least K of the part's items exceed the cut)
-    float step = (sum_max - floor_s + 2.0f * slack) / (float)(kFilterSpan - a.spare);
-    float inv = 1.0f / step;
-    if (!(step > 0.0f) || !(inv < 1.0e30f) || !(step < 1.0e30f)) { inv = 0.0f; step = 0.0f; }   // degenerate: T stays 0, every item is scored
+    const float range = sum_max - floor_s + 2.0f * slack;
     // bases: the further a split's maximum lies above its mean, the more of the range it gets; what lies below the base
     // counts as the base (loose only for items that will rarely be near a floor)
-    const float lambda = spread > 0.0f ? (sum_max - floor_s + kFilterT0 * step) / spread : 0.0f;
-    const float base = mine ? fmaxf(s_mn, s_mx - lambda * (s_mx - s_mean)) : 0.0f;
-    const float off = wave_sum_f32(base) + slack;
+    float step, inv, base, off, t_floor;
+    auto place = [&](float room) {
+        step = range / room;
+        inv = 1.0f / step;
+        if (!(step > 0.0f) || !(inv < 1.0e30f) || !(step < 1.0e30f)) { inv = 0.0f; step = 0.0f; }   // degenerate: T stays 0, every item is scored
+        const float lambda = spread > 0.0f ? (sum_max - floor_s + filter_t0(M) * step) / spread : 0.0f;
+        base = mine ? fmaxf(s_mn, s_mx - lambda * (s_mx - s_mean)) : 0.0f;
+        off = wave_sum_f32(base) + slack;
+    };
+    auto first_t = [&]() {
+        const float t = inv > 0.0f ? floorf((floor_s - off) * inv - kFilterDown) : 0.0f;
+        t_floor = fminf(fmaxf(t, 0.0f), (float)(kFilterSpan + 1));
+    };
+    constexpr int NA = filter_sums(M);
+    if (M >= 16 && a.wide) {
+        place((float)(kFilterSpan - 3));
+        first_t();
+    } else {
+        // A sum starts at 128 - T and must not run over: its four largest counts together are at most 127 + T.  The sum whose
+        // splits spread most decides; the counts are nearly linear in the range's and T's steps.
+        auto largest_sum = [&]() -> float {
+            const float own = mine ? s_mx - base : 0.0f;
+            float sum = 0.0f, least = 0.0f;
+#pragma unroll
+            for (int i = 0; i < filter_members(M); ++i) sum += __shfl(own, filter_member(M, lane & (NA - 1), i));
+            wave_minmax(least, sum);
+            return sum * inv * (float)NA + (float)filter_members(M) * (1.0f + 4.0f * kFilterUp);   // (counts rounded up)
+        };
+        float room = filter_room(M);
+        place(room);
+        first_t();
+        float counts = largest_sum();
+#pragma unroll 1
+        for (int pass = 0; pass < 3 && counts > (float)kFilterSpan + t_floor; ++pass) {
+            const float per = (counts - (float)filter_members(M)) / (room + filter_t0(M));
+            room = fmaxf(((float)kFilterSpan - 5.0f + t_floor) / per - filter_t0(M), 8.0f);
+            place(room);
+            first_t();
+            counts = largest_sum();
+        }
+        if (counts > (float)kFilterSpan + t_floor) {          // (splits that differ widely: these bases, a step with which a sum fits whatever T is)
+            step *= counts / (float)(kFilterSpan - 5);
+            inv = 1.0f / step;
+            if (!(step < 1.0e30f)) { inv = 0.0f; step = 0.0f; }
+            first_t();
+        }
+    }
     if (wave == 0) {
         if (mine) bases[lane] = base;
         // How much of the sample would pass: scores within the roundings of their counts below the floor.  Where that is more than three
         // in ten, by the best of n scores of 64 threads, the scan gives the query up unless the parts together know better.
         // (Floors shared between workgroups rise by themselves, and how far nobody knows yet.)
-        const float near = floor_s - step * (a.spare > 3 ? 0.5f * (float)(M + 1) : 0.5f);   // (a.spare: 8-bit counts are rounded to whole steps)
+        const float near = floor_s - step * (a.wide ? 0.5f : 2.5f);
         const int n = a.rounds * Sh::kSampleItems, pass = __popcll(__ballot(fmaxf(best[0], best[1]) >= near));
         const bool hopeless = !(inv > 0.0f) || (a.share == 0 && (float)pass > (float)kWave * (1.0f - exp2f((float)n * -0.5146f)));   // 0.7 ^ n
         if (lane == 0) {
-            int t = inv > 0.0f ? (int)floorf((floor_s - off) * inv - kFilterDown) : 0;
-            t = t < 0 ? 0 : (t > kFilterSpan + 1 ? kFilterSpan + 1 : t);
+            const int t = (int)t_floor;
             a.query[q] = FilterQuery{off, inv, hopeless ? t + kHopeless : t, cut};
             if (__builtin_expect(flat && !SUB, 0)) {          // (no bound is reached, and the scan knows the result)
                 float score = lut[0];
@@ -430,29 +497,57 @@ __global__ __launch_bounds__(kFilterThreads, M <= 16 ? 8 : 4) void filter_prepar
     }
     __syncthreads();
 
-    // ---- counts, two entries per thread and store
-    uint32_t* out = reinterpret_cast<uint32_t*>(a.counts + (size_t)q * a.entries);
-    const float inv256 = flat && !SUB ? 0.0f : inv * 256.0f;  // (a flat query: nothing passes)
-    const float up = flat && !SUB ? 0.0f : kFilterUp;
-    for (long long i = tid; i * 2 < a.entries; i += NT) {     // (entries is a multiple of 4)
+    if (tid < kFilterBins) a.hist[(size_t)q * kFilterBins + tid] = 0u;
+    const bool nothing = flat && !SUB;                        // (a flat query: nothing passes)
+    uint32_t* const out = reinterpret_cast<uint32_t*>(a.counts + (size_t)q * a.pitch);
+    if (M >= 16 && a.wide) {
+        // ---- 16-bit counts, 256ths of a step, two entries per thread and store
+        const float inv256 = nothing ? 0.0f : inv * 256.0f, up = nothing ? 0.0f : kFilterUp16;
+        for (long long i = tid; i * 2 < a.entries; i += NT) { // (entries is a multiple of 16)
+            uint32_t word = 0;
+#pragma unroll
+            for (int c = 0; c < 2; ++c) {
+                const uint32_t e = (uint32_t)(i * 2 + c), k = e / (uint32_t)stride;
+                const float x = ceilf((lut[e] - bases[k]) * inv256 + up);
+                word |= (uint32_t)fminf(fmaxf(x, 0.0f), 65535.0f) << (c * 16);
+            }
+            out[i] = word;
+        }
+        return;
+    }
+    // ---- 8-bit counts, M / 4 ths of a step: rows of the splits in LDS, four entries per thread and store (a pitch is a multiple of 16);
+    // of the others a byte of the tile's rows each.  (A tile's workgroups write bytes of the same lines, each its own.)
+    const float per = nothing ? 0.0f : inv * (float)NA, up = nothing ? 0.0f : kFilterUp;
+    auto count_of = [&](uint32_t e) -> uint32_t {
+        const float x = ceilf((lut[e] - bases[e / (uint32_t)stride]) * per + up);
+        return (uint32_t)fminf(fmaxf(x, 0.0f), 255.0f);
+    };
+    const uint32_t here = (uint32_t)(M - a.far_splits) * (uint32_t)stride, there = (uint32_t)a.far_splits * (uint32_t)stride;
+    for (uint32_t i = tid; i * 4 < here; i += NT) {
         uint32_t word = 0;
 #pragma unroll
-        for (int c = 0; c < 2; ++c) {
-            const uint32_t e = (uint32_t)(i * 2 + c), k = e / (uint32_t)stride;
-            const float x = ceilf((lut[e] - bases[k]) * inv256 + up);
-            word |= (uint32_t)fminf(fmaxf(x, 0.0f), 65535.0f) << (c * 16);
-        }
+        for (int c = 0; c < 4; ++c) word |= (i * 4 + c < here ? count_of(i * 4 + c) : 0u) << (8 * c);
         out[i] = word;
     }
-    if (tid < kFilterBins) a.hist[(size_t)q * kFilterBins + tid] = 0u;
+    uint8_t* const row = a.far + (size_t)(q / a.tile) * there * a.tile + q % a.tile;
+    const int pad = q == a.B - 1 ? a.tile - 1 - q % a.tile : 0;   // (queries that do not exist count nothing)
+    for (uint32_t i = tid; i < there; i += NT) {
+        uint8_t* const at = row + (size_t)i * a.tile;
+        at[0] = (uint8_t)count_of(here + i);
+        for (int c = 1; c <= pad; ++c) at[c] = 0;
+    }
 }
 
 __host__ __device__ constexpr size_t filter_state_bytes(int queries) {   // everything but the tables, the lists and the queues
-    return (size_t)queries * (kFilterBins * sizeof(uint32_t) + sizeof(uint64_t) + 2 * sizeof(uint32_t) + sizeof(FilterQuery)) + 64 + 64;
+    return (size_t)queries * (kFilterBins * sizeof(uint32_t) + sizeof(uint64_t) + 3 * sizeof(uint32_t) + sizeof(FilterQuery)) + 64;
 }
-// `fine`: the 16-bit counts beside the 8-bit tables
-__host__ __device__ constexpr size_t filter_lds_bytes(long long entries, int words, int queries, int cap, bool fine) {
-    return (size_t)entries * words * 4 + (fine ? (size_t)entries * queries * 2 : 0) + (size_t)queries * cap * sizeof(uint64_t) +
+// `lanes`: that share an item; `stride`: table entries of a split
+__host__ __device__ constexpr size_t filter_table_bytes(int m, long long stride, int words, bool w16, int lanes) {
+    return (size_t)(m - filter_far_splits(m, words, w16, lanes)) * stride * words * 4 * lanes;
+}
+__host__ __device__ constexpr size_t filter_lds_bytes(int m, long long stride, int words, bool w16, int lanes, int cap) {
+    const int queries = words * (w16 ? 2 : 4) * lanes;
+    return align16(filter_table_bytes(m, stride, words, w16, lanes)) + (size_t)queries * cap * sizeof(uint64_t) +
            (size_t)kFilterWaves * kFilterQueue * sizeof(uint64_t) + align16(filter_state_bytes(queries));
 }
 
@@ -461,64 +556,70 @@ template <> struct FilterWord<1> { typedef uint32_t type; };
 template <> struct FilterWord<2> { typedef uint2 type; };
 template <> struct FilterWord<4> { typedef uint4 type; };
 
-// The scan.  grid = (item blocks, tiles of QT queries).  M, CW, SUB as above; W: 32-bit words of a table entry (1, 2, 4);
-// W16: 16-bit fields.  QT = W * 4 (or 2) queries per workgroup.
-// Dynamic LDS: tables | lists [QT][cap] | queues [waves][kFilterQueue] | hist [QT][kFilterBins] | thr | state words.
+// The scan.  grid = (item blocks, tiles of QT queries).  M, CW, SUB as above; W: 32-bit words of a lane's table entry (1, 2, 4);
+// W16: 16-bit fields.  G lanes (1 or 2) share an item, each with W * 4 (or 2) of the QT queries.
+// Dynamic LDS: tables (two-byte sub-ids) | lists [QT][cap] | queues [waves][kFilterQueue] | hist [QT][kFilterBins] | thr | state words.
+// SHARE: the workgroups of a query share their floors (a choice at run time would make the loop wait for all of a wave's loads).
 // STAMP: measurement instance that also records wall-clock stamps per wave.
-template <int M, int CW, int W, bool W16, bool SUB, bool FINE, bool STAMP = false>
+template <int M, int CW, int W, bool W16, bool SUB, int G, bool SHARE, bool STAMP = false>
 __global__ __launch_bounds__(kFilterThreads) void scan_filter_kernel(FilterArgs a) {
     using Sh = FilterShape<M, CW>;
     using Word = typename FilterWord<W>::type;
     constexpr int NT = kFilterThreads, NW = kFilterWaves, P = Sh::P, NI = Sh::kItems;
-    constexpr int F = W16 ? 2 : 4, QT = W * F;                // fields per word, queries per tile
-    static_assert(!(FINE && W16), "16-bit fields are fine already");
+    constexpr int F = W16 ? 2 : 4, QL = W * F, QT = QL * G;   // fields per word, queries per lane and per tile
+    constexpr int PER = kWave / G;                            // items a wave looks up side by side
+    constexpr int V = filter_far_splits(M, W, W16, G);        // splits looked up in device memory, the last ones
+    constexpr int NA = W16 ? 1 : filter_sums(M);              // sums of a field
+    constexpr int QW = (QT + NW - 1) / NW;                    // queries that a wave looks after
+    constexpr int EW = (M - V) * G >= M ? W : W / 2;          // queries of a second scan: exact tables in the counts' place
+    constexpr int D = G == 2 ? 4 : 2;               // units whose codes a wave holds or has asked for
+    constexpr bool AHEAD = V > 0 && Sh::kWords == 4 && NI * V * W <= 16;   // reads of device memory are under way a unit ahead
     constexpr uint32_t TOP = W16 ? 0x80008000u : 0x80808080u;
-    static_assert(QT <= kFilterWaves, "the final selection gives each query a wave");
+    static_assert(W16 ? (M >= 16 && G == 1) : (G == 1 || (G == 2 && W == 4 && QT == 32)), "16-bit fields, or pairs of lanes");
     extern __shared__ __align__(16) unsigned char smem[];
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid / kWave);
-    const int q0 = blockIdx.y * QT, nblk = gridDim.x, blk = blockIdx.x, K = a.K, b = a.b, cap = a.cap;
-    uint64_t* const rec = STAMP ? a.stamps + (((size_t)blockIdx.y * nblk + blk) * NW + wave) * kStampSlots : nullptr;
+    const int half = G == 1 ? 0 : lane & 1, slot = lane / G;  // this lane's part of a row, its place among the wave's items
+    const int nblk = gridDim.x, tile = blockIdx.y, blk = blockIdx.x, q0 = tile * QT, K = a.K, b = a.b, cap = a.cap;
+    uint64_t* const rec = STAMP ? a.stamps + (((size_t)tile * nblk + blk) * NW + wave) * kStampSlots : nullptr;
     stamp<STAMP>(rec, kStampEntry, lane);
     const int nq = a.B - q0 < QT ? a.B - q0 : QT;
     const int stride = CW == 1 ? kLutStride : b;
-    __shared__ __align__(16) uint32_t tab_static[CW == 1 ? M * kLutStride * W : 4];
+    __shared__ __align__(16) uint32_t tab_static[CW == 1 ? (M - V) * kLutStride * W * G : 4];
     uint32_t* const tab = CW == 1 ? tab_static : reinterpret_cast<uint32_t*>(smem);
-    const uint32_t entries = CW == 1 ? M * kLutStride : (uint32_t)a.entries;
-    unsigned char* const rest = smem + (CW == 1 ? 0 : (size_t)entries * W * 4);
-    uint16_t* const fine = reinterpret_cast<uint16_t*>(rest);
-    uint64_t* const lists = reinterpret_cast<uint64_t*>(rest + (FINE ? (size_t)entries * QT * 2 : 0));
+    const uint32_t here = (uint32_t)((M - V) * stride);       // entries of a query in LDS
+    uint64_t* const lists = reinterpret_cast<uint64_t*>(smem + (CW == 1 ? 0 : align16((size_t)here * W * G * 4)));
     uint64_t* const queue = lists + (size_t)QT * cap + (size_t)wave * kFilterQueue;
     uint32_t* const hist = reinterpret_cast<uint32_t*>(lists + (size_t)QT * cap + (size_t)NW * kFilterQueue);
     uint64_t* const thr = reinterpret_cast<uint64_t*>(hist + QT * kFilterBins);   // a pruned list's K-th best key
     uint32_t* const cnt = reinterpret_cast<uint32_t*>(thr + QT);                  // keys in the list (or asked for)
     uint32_t* const lock = cnt + QT;
     FilterQuery* const par = reinterpret_cast<FilterQuery*>(lock + QT);
-    uint32_t* const start = reinterpret_cast<uint32_t*>(par + QT);                // [W] the fields' start values: 128 - T, or 256 times that
-    uint32_t* const next_unit = start + 4;
+    uint32_t* const start = reinterpret_cast<uint32_t*>(par + QT);                // [G][W] the fields' start values: 128 - T, or 256 times that
+    uint32_t* const next_unit = start + 8;
     uint32_t* const given_up = next_unit + 1;                                     // queries the bounds are no use for, as bits of a mask of hits
     uint32_t* const passed = given_up + 1;                                        // [QT] items whose bounds reached the floor; top bit: given up
 
-    // a query's bit in a mask of hits: field f of word j is bit f * 8 (or 16) + j
+    // a query's bit in a mask of hits: field f of word j is bit f * 8 (or 16) + j; the second lane's words follow the first's
     auto bit_of = [](int q) -> int { return W16 ? (q & 1) * 16 + (q >> 1) : (q & 3) * 8 + (q >> 2); };
     auto query_of = [](int bit) -> int { return W16 ? (bit & 15) * 2 + (bit >> 4) : (bit & 7) * 4 + (bit >> 3); };
 
-    // ---- units of work: a wave's share (64 lanes x kVecs vectors), the workgroups' interleaved one by one (whole rounds of a
+    // ---- units of work: a wave's share (PER x kVecs vectors), the workgroups' interleaved one by one (whole rounds of a
     // workgroup's waves left some with a twentieth more than others: 5M items at m = 16, 256 workgroups)
     const uint32_t total = (uint32_t)((P <= 16 && !SUB) ? (a.N * P) / 16 : a.N);  // whole vectors, or items / candidates
     constexpr uint32_t kPerLane = (P <= 16 && !SUB) ? Sh::kVecs : NI;             // ... per lane and unit
-    constexpr uint32_t kPerUnit = kWave * kPerLane;
+    constexpr uint32_t kPerUnit = PER * kPerLane;
     const uint32_t all_units = (total + kPerUnit - 1) / kPerUnit;
     const uint32_t units = (uint32_t)blk < all_units ? (all_units - blk + nblk - 1) / nblk : 0;
     const uint32_t last = total - 1;
-    auto first_of = [&](uint32_t u) -> uint32_t {             // the lane's first element of unit u; the others follow at 64
-        return (u * (uint32_t)nblk + (uint32_t)blk) * kPerUnit + (uint32_t)lane;
+    auto first_of = [&](uint32_t u) -> uint32_t {             // the lane's first element of unit u; the others follow at PER
+        return (u * (uint32_t)nblk + (uint32_t)blk) * kPerUnit + (uint32_t)slot;
     };
     auto fetch_ids = [&](uint32_t u, uint32_t (&id)[NI]) {    // candidate lists: the items' ids
         if constexpr (SUB) {
             const uint32_t p0 = first_of(u);
 #pragma unroll
             for (int e = 0; e < NI; ++e) {
-                const uint32_t p = p0 + e * kWave;
+                const uint32_t p = p0 + e * PER;
                 const uint32_t item = (uint32_t)a.subset[p < last ? p : last];
                 id[e] = item < a.n_items ? item : a.n_items - 1;
             }
@@ -529,90 +630,113 @@ __global__ __launch_bounds__(kFilterThreads) void scan_filter_kernel(FilterArgs 
         if constexpr (SUB) {
 #pragma unroll
             for (int e = 0; e < NI; ++e) load_row_words<P>(a.codes, id[e], &w[e * P / 4]);
-        } else if constexpr (P > 16) {
-            load_row_words<P>(a.codes, p0 < last ? p0 : last, w);
         } else {
+            constexpr int kEach = P > 16 ? P / 16 : 1;        // vectors that follow each other
 #pragma unroll
-            for (int v = 0; v < Sh::kVecs; ++v) {
-                const uint32_t p = p0 + v * kWave;
-                const uint4 x = reinterpret_cast<const uint4*>(a.codes)[p < last ? p : last];
-                w[4 * v] = x.x; w[4 * v + 1] = x.y; w[4 * v + 2] = x.z; w[4 * v + 3] = x.w;
+            for (int v = 0; v < Sh::kVecs / kEach; ++v) {
+                const uint32_t p = p0 + v * PER;
+                const uint4* const at = reinterpret_cast<const uint4*>(a.codes) + (size_t)(p < last ? p : last) * kEach;
+#pragma unroll
+                for (int i = 0; i < kEach; ++i) {
+                    const uint4 x = at[i];
+                    uint32_t* const o = &w[4 * (v * kEach + i)];
+                    o[0] = x.x; o[1] = x.y; o[2] = x.z; o[3] = x.w;
+                }
             }
         }
     };
-    // item e of unit u: its id, or -1u past the end
-    auto item_of = [&](uint32_t u, int e, const uint32_t (&id)[NI]) -> uint32_t {
+    // element e of unit u: the item (or its place in the list), or -1u past the end
+    auto element_of = [&](uint32_t u, int e) -> uint32_t {
         const uint32_t p0 = first_of(u);
-        if constexpr (SUB) return p0 + e * kWave <= last ? id[e] : ~0u;
-        else if constexpr (P > 16) return p0 <= last ? p0 : ~0u;
-        else {
+        if constexpr (SUB || P > 16) {
+            const uint32_t p = p0 + e * PER;
+            return p <= last ? p : ~0u;
+        } else {
             constexpr int IPV = 16 / P;
-            const uint32_t p = p0 + (e / IPV) * kWave;
+            const uint32_t p = p0 + (e / IPV) * PER;
             return p <= last ? p * IPV + e % IPV : ~0u;
+        }
+    };
+    auto item_at = [&](uint32_t element) -> uint32_t {
+        if constexpr (SUB) {
+            const uint32_t item = (uint32_t)a.subset[element];
+            return item < a.n_items ? item : a.n_items - 1;
+        } else {
+            return element;
         }
     };
 
     // ---- the tile's counts on their way, then the first units' codes (loads return in order, and codes may come from
     // far away: asked for first, they held the tables up by 5 us on an 80 MB catalogue), then the tables: rows of counts,
-    // one per query, become entries of QT fields (transposed in registers)
-    const uint32_t row_words = entries / 2;                   // two 16-bit counts per word
-    const uint32_t* const rows = reinterpret_cast<const uint32_t*>(a.counts) + (size_t)q0 * row_words;
-    auto fetch_counts = [&](uint32_t i, uint32_t (&in)[QT]) {
-        const uint32_t at = i < row_words ? i : 0u;
+    // one per query, become entries of QL fields per lane (transposed in registers, N entries of one lane's queries at a time)
+    constexpr int N_ = W16 ? 2 : 4;                           // counts of a 32-bit word
+    const uint32_t pieces = (here + N_ - 1) / N_ * G;         // (rows are padded to whole words)
+    const uint32_t* const rows = reinterpret_cast<const uint32_t*>(a.counts + (size_t)q0 * a.pitch);
+    auto fetch_counts = [&](uint32_t i, uint32_t (&in)[QL]) {
+        const uint32_t at = i < pieces ? i / G : 0u;
+        const int first = (int)(i % G) * QL;
 #pragma unroll
-        for (int q = 0; q < QT; ++q) in[q] = rows[(size_t)(q < nq ? q : 0) * row_words + at];
+        for (int q = 0; q < QL; ++q) in[q] = rows[(size_t)(first + q < nq ? first + q : 0) * (a.pitch / 4) + at];
     };
-    uint32_t first_in[QT];
+    uint32_t first_in[QL];
     fetch_counts(tid, first_in);
-    FilterQuery my_par = a.query[q0 + (wave < nq ? wave : 0)];   // (a wave per query below)
-    uint32_t wa[Sh::kWords], wb[Sh::kWords], ia[NI], ib[NI], inext[NI];
-    fetch_ids(wave, ia);
-    fetch_ids(NW + wave, ib);
-    fetch(wave, ia, wa);
-    fetch(NW + wave, ib, wb);
+    FilterQuery my_par[QW];                                   // (a wave per query below, or two queries)
+#pragma unroll
+    for (int i = 0; i < QW; ++i) my_par[i] = a.query[q0 + (wave + i * NW < nq ? wave + i * NW : 0)];
+    // (several parts: their best scores, where a few registers hold them)
+    constexpr int kFew = 4;
+    const int n_best = a.parts * a.best_per_part;
+    float my_best[QW][kFew];
+#pragma unroll
+    for (int i = 0; i < QW; ++i)
+#pragma unroll
+        for (int j = 0; j < kFew; ++j)
+            my_best[i][j] = a.parts > 1 && j * kWave + lane < n_best ? a.best[(size_t)(q0 + (wave + i * NW < nq ? wave + i * NW : 0)) * n_best + j * kWave + lane] : -__builtin_inff();
+    uint32_t w[D][Sh::kWords], unit[D], inext[NI];            // slot i: a unit's codes
+#pragma unroll
+    for (int i = 0; i < D - 1; ++i) {
+        unit[i] = (uint32_t)(i * NW + wave);
+        fetch_ids(unit[i], inext);
+        fetch(unit[i], inext, w[i]);
+    }
     for (int i = tid; i < QT * cap; i += NT) lists[i] = 0ull;
     for (int i = tid; i < QT * kFilterBins; i += NT) hist[i] = 0u;
-    {
-        for (uint32_t i = tid; i < row_words; i += NT) {      // entries 2i and 2i + 1 of every query
-            uint32_t in[QT];
-            if (i == (uint32_t)tid) {
+    for (uint32_t i = tid; i < pieces; i += NT) {             // entries N_ * (i / G) .. of the queries of lane i % G
+        uint32_t in[QL];
+        if (i == (uint32_t)tid) {
 #pragma unroll
-                for (int q = 0; q < QT; ++q) in[q] = first_in[q];
-            } else {
-                fetch_counts(i, in);
-            }
-            if (nq < QT) {
+            for (int q = 0; q < QL; ++q) in[q] = first_in[q];
+        } else {
+            fetch_counts(i, in);
+        }
+        const int first = (int)(i % G) * QL;
+        if (nq < QT) {
 #pragma unroll
-                for (int q = 0; q < QT; ++q) in[q] = q < nq ? in[q] : 0u;
-            }
-            uint32_t out[2][W];                               // [entry][word of the entry]
+            for (int q = 0; q < QL; ++q) in[q] = first + q < nq ? in[q] : 0u;
+        }
+        uint32_t out[N_][W];                                  // [entry][word of the entry]
 #pragma unroll
-            for (int j = 0; j < W; ++j) {
-                if constexpr (W16) {
-                    out[0][j] = __builtin_amdgcn_perm(in[2 * j + 1], in[2 * j], 0x05040100u);
-                    out[1][j] = __builtin_amdgcn_perm(in[2 * j + 1], in[2 * j], 0x07060302u);
-                } else {
-                    // whole steps, rounded up: the high bytes of (count + 255), without a carry from one half to the other
-                    // (counts stay below 2^16 - 256: the sum of a score's largest ones is at most 255 steps)
-                    const uint32_t r0 = in[4 * j] + 0x00FF00FFu, r1 = in[4 * j + 1] + 0x00FF00FFu;
-                    const uint32_t r2 = in[4 * j + 2] + 0x00FF00FFu, r3 = in[4 * j + 3] + 0x00FF00FFu;
-                    const uint32_t p01 = __builtin_amdgcn_perm(r1, r0, 0x07030501u), p23 = __builtin_amdgcn_perm(r3, r2, 0x07030501u);
-                    out[0][j] = __builtin_amdgcn_perm(p23, p01, 0x05040100u);
-                    out[1][j] = __builtin_amdgcn_perm(p23, p01, 0x07060302u);
-                }
+        for (int j = 0; j < W; ++j) {
+            if constexpr (W16) {
+                out[0][j] = __builtin_amdgcn_perm(in[2 * j + 1], in[2 * j], 0x05040100u);
+                out[1][j] = __builtin_amdgcn_perm(in[2 * j + 1], in[2 * j], 0x07060302u);
+            } else {                                          // four by four bytes
+                const uint32_t a01 = __builtin_amdgcn_perm(in[4 * j + 1], in[4 * j], 0x05010400u), b01 = __builtin_amdgcn_perm(in[4 * j + 1], in[4 * j], 0x07030602u);
+                const uint32_t a23 = __builtin_amdgcn_perm(in[4 * j + 3], in[4 * j + 2], 0x05010400u), b23 = __builtin_amdgcn_perm(in[4 * j + 3], in[4 * j + 2], 0x07030602u);
+                out[0][j] = __builtin_amdgcn_perm(a23, a01, 0x05040100u);
+                out[1][j] = __builtin_amdgcn_perm(a23, a01, 0x07060302u);
+                out[2][j] = __builtin_amdgcn_perm(b23, b01, 0x05040100u);
+                out[3][j] = __builtin_amdgcn_perm(b23, b01, 0x07060302u);
             }
+        }
 #pragma unroll
-            for (int f = 0; f < 2; ++f) {
-                Word x;
-                if constexpr (W == 1) x = out[f][0];
-                else if constexpr (W == 2) x = make_uint2(out[f][0], out[f][1]);
-                else x = make_uint4(out[f][0], out[f][1], out[f][2], out[f][3]);
-                reinterpret_cast<Word*>(tab)[i * 2 + f] = x;
-            }
-            if constexpr (FINE) {
-#pragma unroll
-                for (int q = 0; q < QT; ++q) reinterpret_cast<uint32_t*>(fine)[(size_t)q * row_words + i] = in[q];
-            }
+        for (int c = 0; c < N_; ++c) {
+            Word x;
+            if constexpr (W == 1) x = out[c][0];
+            else if constexpr (W == 2) x = make_uint2(out[c][0], out[c][1]);
+            else x = make_uint4(out[c][0], out[c][1], out[c][2], out[c][3]);
+            const uint32_t e = i / G * N_ + c;
+            if (CW == 1 || e < here) reinterpret_cast<Word*>(tab)[e * G + i % G] = x;
         }
     }
     constexpr uint32_t kLost = 0x80000000u;                   // in passed[]
@@ -631,24 +755,26 @@ __global__ __launch_bounds__(kFilterThreads) void scan_filter_kernel(FilterArgs 
         return (int)fminf(fmaxf(x, 0.0f), (float)(kFilterSpan + 1));
     };
     if (tid < QT) { thr[tid] = 0ull; cnt[tid] = 0u; lock[tid] = 0u; }
-    if (tid == 0) { *next_unit = 2 * NW; *given_up = 0u; }
-    bool hopeless = false;                                    // this wave's query is given up at once
-    if (wave < QT) {
+    if (tid == 0) { *next_unit = (D - 1) * NW; *given_up = 0u; }
+    uint32_t all_hopeless = 0;                                // bit i: this wave's query wave + i * NW is given up at once
+#pragma unroll
+    for (int i_own = 0; i_own < QW; ++i_own) {
+        if (wave + i_own * NW >= QT) break;
         // a wave per query: the first T (queries that do not exist: start 0, counts 0: never at the top bit)
-        const int q = wave;
-        FilterQuery p = q < nq ? my_par : FilterQuery{0.0f, 0.0f, kFilterSpan + 1, 0.0f};
-        hopeless = p.t_first >= kHopeless;
+        const int q = wave + i_own * NW;
+        FilterQuery p = q < nq ? my_par[i_own] : FilterQuery{0.0f, 0.0f, kFilterSpan + 1, 0.0f};
+        bool hopeless = p.t_first >= kHopeless;
         if (hopeless) p.t_first -= kHopeless;
         if (q < nq && a.parts > 1) {
             // the K-th best of the parts' scores, to 16 bits of its order-preserving image: K of them reach it
-            const int n = a.parts * a.best_per_part;
+            const int n = n_best;
             const float* v = a.best + (size_t)(q0 + q) * n;
             uint32_t at = 0;
             auto search = [&](auto per_lane) {
                 constexpr int R = decltype(per_lane)::value;
                 uint32_t o[R];
 #pragma unroll
-                for (int i = 0; i < R; ++i) o[i] = i * kWave + lane < n ? orderable_bits(v[i * kWave + lane]) : 0u;
+                for (int i = 0; i < R; ++i) o[i] = i * kWave + lane < n ? orderable_bits(R <= kFew ? my_best[i_own][i < kFew ? i : 0] : v[i * kWave + lane]) : 0u;
                 for (uint32_t bit = 0x80000000u; bit >= 0x10000u; bit >>= 1) {
                     const uint32_t t = at | bit;
                     int c = 0;
@@ -673,6 +799,7 @@ __global__ __launch_bounds__(kFilterThreads) void scan_filter_kernel(FilterArgs 
             set_t(q, p.t_first);
             passed[q] = 0u;
         }
+        all_hopeless |= (uint32_t)hopeless << i_own;
     }
     stamp<STAMP>(rec, kStampRequested, lane);
     __syncthreads();
@@ -680,39 +807,48 @@ __global__ __launch_bounds__(kFilterThreads) void scan_filter_kernel(FilterArgs 
 
     // Floors.  Every exact score that enters a list is counted in its query's histogram, and wave q looks after query q: now
     // and then it asks for the counters and one unit later reads off the highest T that K of the counted scores reach.
-    // a.share: the histogram is in device memory and counts for all workgroups that serve the query: the K-th best of all
+    // SHARE: the histogram is in device memory and counts for all workgroups that serve the query: the K-th best of all
     // their shares together is a far higher floor than one share's own.  For a few workgroups with long shares (serving:
     // four per query, K = 100: scan 373 -> 238 us).  Where many workgroups share a query their updates of the same counters
     // are served one by one, and a wave's loads wait behind its updates: the histogram is the workgroup's own then, in LDS
     // (256 workgroups, 20 units per wave: 46 us, 64 with a shared one).
     static_assert(kFilterBins == 2 * kWave, "two counters per lane");
-    const bool looks_after = wave < nq;
-    unsigned long long seen = 0ull;                           // this lane's two counters as asked for
-    int until_look = 1, look_gap = 2;                         // units until the next request; the gap grows by a quarter
+    unsigned long long seen[QW] = {};                         // this lane's two counters of a query as asked for
+    int until_look = 1, look_gap = 2;                         // groups of units until the next request; the gap grows by a quarter
     bool asked = false;
     auto look = [&]() {
-        if (!looks_after) return;
+        if (wave >= nq) return;
         if (asked) {
             asked = false;
-            const uint32_t h0 = (uint32_t)seen, h1 = (uint32_t)(seen >> 32);
-            const int top = kFilterBins - 1 - 2 * lane;       // lane 0 owns the highest two
-            const uint32_t upto = wave_prefix_sum(h0 + h1);
-            const uint64_t has = __ballot(upto >= (uint32_t)K);
-            if (has != 0) {
-                const int owner = __builtin_ctzll(has);
-                const int bin = __builtin_amdgcn_readlane(upto - h0 >= (uint32_t)K ? top : top - 1, owner);
-                const int t = par[wave].t_first + bin < kFilterSpan + 1 ? par[wave].t_first + bin : kFilterSpan + 1;
-                if (lane == 0 && t > t_of(wave)) set_t(wave, t);
+#pragma unroll
+            for (int i = 0; i < QW; ++i) {
+                const int q = wave + i * NW;
+                if (i > 0 && q >= nq) break;
+                const uint32_t h0 = (uint32_t)seen[i], h1 = (uint32_t)(seen[i] >> 32);
+                const int top = kFilterBins - 1 - 2 * lane;   // lane 0 owns the highest two
+                const uint32_t upto = wave_prefix_sum(h0 + h1);
+                const uint64_t has = __ballot(upto >= (uint32_t)K);
+                if (has != 0) {
+                    const int owner = __builtin_ctzll(has);
+                    const int bin = __builtin_amdgcn_readlane(upto - h0 >= (uint32_t)K ? top : top - 1, owner);
+                    const int t = par[q].t_first + bin < kFilterSpan + 1 ? par[q].t_first + bin : kFilterSpan + 1;
+                    if (lane == 0 && t > t_of(q)) set_t(q, t);
+                }
             }
         }
         if (--until_look <= 0) {
             const int at = kFilterBins - 2 - 2 * lane;
-            if (a.share) seen = __hip_atomic_load(reinterpret_cast<const unsigned long long*>(a.hist + (size_t)(q0 + wave) * kFilterBins + at),
-                                                  __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            else seen = lds_peek(reinterpret_cast<const unsigned long long*>(hist + wave * kFilterBins + at));
+#pragma unroll
+            for (int i = 0; i < QW; ++i) {
+                const int q = wave + i * NW;
+                if (i > 0 && q >= nq) break;
+                if constexpr (SHARE) seen[i] = __hip_atomic_load(reinterpret_cast<const unsigned long long*>(a.hist + (size_t)(q0 + q) * kFilterBins + at),
+                                                         __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                else seen[i] = lds_peek(reinterpret_cast<const unsigned long long*>(hist + q * kFilterBins + at));
+            }
             asked = true;
             look_gap += (look_gap + 3) >> 2;
-            until_look = look_gap < 16 ? look_gap : 16;
+            until_look = look_gap < 16 / D ? look_gap : 16 / D;
         }
     };
 
@@ -757,7 +893,7 @@ __global__ __launch_bounds__(kFilterThreads) void scan_filter_kernel(FilterArgs 
     // 1.28M items, m = 8, 64 queries with such an entry each, K = 10: 117 us instead of 808 (37 without it); 1024, K = 100: 2.5 ms
     // instead of 9.6.  (Given up at once, shared floors' queries with heavy-tailed tables took 1.3 ms instead of 0.5.)
     uint32_t batches = 0, units_seen = 0, gone = 0;           // batches scored, units seen; queries given up, as far as this wave has looked
-    const uint32_t give_up_from = units * (kWave * NI) / (M >= 32 ? 4u : a.share ? 20u : 12u);
+    const uint32_t give_up_from = units * (PER * NI) / (M >= 32 ? 4u : SHARE ? 20u : 12u);
     auto give_up = [&](int q) {
         const uint32_t bit = 1u << bit_of(q);
         uint32_t before = 0;
@@ -769,14 +905,14 @@ __global__ __launch_bounds__(kFilterThreads) void scan_filter_kernel(FilterArgs 
         }
         const uint32_t keep = W16 ? ~(0xFFFFu << (q & 1) * 16) : ~(0xFFu << (q & 3) * 8);
 #pragma unroll 1
-        for (uint32_t i = lane; i < entries; i += kWave) atomicAnd(&tab[i * W + q / F], keep);
+        for (uint32_t i = lane; i < here; i += kWave) atomicAnd(&tab[i * (W * G) + q / F], keep);
     };
 
     auto count_passed = [&](int n0) {                         // queue entries [n0, n0 + 64), which have been scored
         const int q = (int)(queue[n0 + lane] >> 32);
         // (units begun: those handed out less what the waves hold)
-        const uint32_t out = (uint32_t)__builtin_amdgcn_readfirstlane((int)lds_peek(next_unit)), begun = out > 4 * NW ? out - 3 * NW : NW;
-        const uint32_t line = begun * (kWave * NI / 4);
+        const uint32_t out = (uint32_t)__builtin_amdgcn_readfirstlane((int)lds_peek(next_unit)), begun = out > (D + 2) * NW ? out - (D + 1) * NW : NW;
+        const uint32_t line = begun * (PER * NI / 4);
         // (a floor that has not risen by a step yet is less likely to)
         const uint32_t from = t_of(q) == par[q].t_first ? give_up_from / 2 : give_up_from;
         uint64_t over = __ballot(atomicAdd(&passed[q], 1u) > (line > from ? line : from));
@@ -791,35 +927,29 @@ __global__ __launch_bounds__(kFilterThreads) void scan_filter_kernel(FilterArgs 
     };
 
     // Scores queue entries [n0, n0 + n), n <= 64, exactly, one per lane, and puts what reaches its query's floor into the
-    // query's list.  `again`: in a query's second scan.
+    // query's list.
+    constexpr int kAsked = M < 16 ? M : 16;                   // table values under way together
+    // `again`: in a query's second scan
     auto process = [&](auto again, int n0, int n) {
         wave_sync();
-        const uint64_t entry = lane < n ? queue[n0 + lane] : 0ull;
+        const bool live = lane < n;
+        const uint64_t entry = live ? queue[n0 + lane] : 0ull;
         const int q = (int)(entry >> 32);
-        const uint32_t item = (uint32_t)entry;
-        uint32_t w[P / 4 > 0 ? P / 4 : 1];
-        load_row_words<P>(a.codes, item, w);
-        bool live = lane < n;
-        if constexpr (FINE && !decltype(again)::value) {
-            uint32_t sum = 0;
-#pragma unroll
-            for (int k = 0; k < M; ++k) sum += fine[(size_t)q * entries + (uint32_t)k * stride + filter_sub_id<M, CW>(w, 0, k)];
-            live = live && sum >= ((uint32_t)t_of(q) << 8);
-        }
+        const uint32_t item = item_at((uint32_t)entry);
+        uint32_t row[P / 4];
+        load_row_words<P>(a.codes, item, row);
         const float* Sq = a.S + (size_t)(q0 + q) * M * b;
         float acc = 0.0f;
-        if (live) {
 #pragma unroll
-        for (int k0 = 0; k0 < M; k0 += 16) {
-            float v[M < 16 ? M : 16];
+        for (int k0 = 0; k0 < M; k0 += kAsked) {
+            float v[kAsked];
 #pragma unroll
-            for (int k = k0; k < k0 + (M < 16 ? M : 16); ++k) {
-                const uint32_t g = filter_sub_id<M, CW>(w, 0, k);
-                v[k - k0] = Sq[(size_t)k * b + (g < (uint32_t)b ? g : (uint32_t)b - 1u)];   // (never outside the tables)
+            for (int k = 0; k < kAsked; ++k) {
+                const uint32_t g = filter_sub_id<M, CW>(row, 0, k0 + k);
+                v[k] = Sq[(size_t)(k0 + k) * b + (g < (uint32_t)b ? g : (uint32_t)b - 1u)];   // (never outside the tables)
             }
 #pragma unroll
-            for (int k = k0; k < k0 + (M < 16 ? M : 16); ++k) acc = k == 0 ? v[0] : acc + v[k - k0];
-        }
+            for (int k = 0; k < kAsked; ++k) acc = k0 + k == 0 ? v[0] : acc + v[k];
         }
         const FilterQuery p = par[q];
         const int t = units_of_score(acc, p);
@@ -829,8 +959,8 @@ __global__ __launch_bounds__(kFilterThreads) void scan_filter_kernel(FilterArgs 
             int bin = t - p.t_first;
             bin = bin < 0 ? 0 : (bin > kFilterBins - 1 ? kFilterBins - 1 : bin);
             // (a shared histogram is not cleared for the second scan: no item may be counted twice)
-            if (decltype(again)::value && a.share) {}
-            else if (a.share) (void)__hip_atomic_fetch_add(a.hist + (size_t)(q0 + q) * kFilterBins + bin, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (decltype(again)::value && SHARE) {}
+            else if (SHARE) (void)__hip_atomic_fetch_add(a.hist + (size_t)(q0 + q) * kFilterBins + bin, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             else atomicAdd(&hist[q * kFilterBins + bin], 1u);
         }
         // Who still has a key to place is kept as a mask in scalar registers, never as a flag per lane that goes round the
@@ -868,7 +998,11 @@ __global__ __launch_bounds__(kFilterThreads) void scan_filter_kernel(FilterArgs 
         look();
     };
 
-    if (__builtin_expect(__builtin_amdgcn_readfirstlane((int)hopeless) != 0, 0)) give_up(wave);
+    if (__builtin_expect(__builtin_amdgcn_readfirstlane((int)all_hopeless) != 0, 0)) {
+#pragma unroll 1
+        for (int i = 0; i < QW; ++i)
+            if ((__builtin_amdgcn_readfirstlane((int)all_hopeless) >> i) & 1) give_up(wave + i * NW);
+    }
 
     // ---- stream
     int queued = 0;                                           // entries in this wave's queue
@@ -878,116 +1012,194 @@ __global__ __launch_bounds__(kFilterThreads) void scan_filter_kernel(FilterArgs 
         else {
 #pragma unroll
             for (int j = 0; j < W; j += 2) {
-                const unsigned long long x = lds_peek(reinterpret_cast<const unsigned long long*>(start) + j / 2);
+                const unsigned long long x = lds_peek(reinterpret_cast<const unsigned long long*>(start) + (half * W + j) / 2);
                 s[j] = (uint32_t)x; s[j + 1] = (uint32_t)(x >> 32);
             }
         }
+        if constexpr (G == 1) {
 #pragma unroll
-        for (int j = 0; j < W; ++j) s[j] = (uint32_t)__builtin_amdgcn_readfirstlane((int)s[j]);
+            for (int j = 0; j < W; ++j) s[j] = (uint32_t)__builtin_amdgcn_readfirstlane((int)s[j]);
+        }
     };
-    auto scan_unit = [&](uint32_t u, const uint32_t (&w)[Sh::kWords], const uint32_t (&id)[NI]) {
-        ++units_seen;
+    // where a lane's part of a sub-id's row begins (pairs, one-byte sub-ids: one dot product of bytes, 32 g + 16 half)
+    auto row_at = [&](const uint32_t* w, int e, int k) -> uint32_t {
+        if constexpr (G == 2 && CW == 1) {
+            const int byte = e * P + k;
+            return __builtin_amdgcn_udot4(w[byte >> 2], (uint32_t)QT << ((byte & 3) * 8), (uint32_t)(half * QL), false);
+        } else {
+            return filter_sub_id<M, CW>(w, e, k) * (W * G * 4) + (uint32_t)(half * W * 4);
+        }
+    };
+    const uint8_t* const far = V == 0 ? nullptr : a.far + (size_t)tile * ((size_t)V * stride * QT);
+    auto fetch_far = [&](const uint32_t* w, Word (&x)[NI][V > 0 ? V : 1]) {
+#pragma unroll
+        for (int e = 0; e < NI; ++e)
+#pragma unroll
+            for (int v = 0; v < V; ++v) x[e][v] = *reinterpret_cast<const Word*>(far + (size_t)v * stride * QT + row_at(w, e, M - V + v));
+    };
+    auto add_word = [](uint32_t (&sum)[W], const Word& x) {
+        if constexpr (W == 1) sum[0] += x;
+        else if constexpr (W == 2) { sum[0] += x.x; sum[1] += x.y; }
+        else { sum[0] += x.x; sum[1] += x.y; sum[2] += x.z; sum[3] += x.w; }
+    };
+    // a unit's hits: per item a mask of the queries whose field has its top bit set
+    auto scan_unit = [&](uint32_t u, const uint32_t (&w)[Sh::kWords], const Word (&x)[NI][V > 0 ? V : 1], uint32_t (&hits)[NI]) {
         uint32_t sum[NI][W];
         uint32_t any = 0;
 #pragma unroll
         for (int e = 0; e < NI; ++e) {
+            auto entry = [&](int k) -> Word {
+                return *reinterpret_cast<const Word*>(reinterpret_cast<const uint8_t*>(tab) + (size_t)k * stride * (W * G * 4) + row_at(w, e, k));
+            };
+            if constexpr (NA == 1) {
 #pragma unroll
-            for (int j = 0; j < W; ++j) sum[e][j] = s[j];
-#pragma unroll
-            for (int k0 = 0; k0 < M; k0 += 8) {
+                for (int j = 0; j < W; ++j) sum[e][j] = s[j];
                 constexpr int STEP = M < 8 ? M : 8;
-                Word v[STEP];
 #pragma unroll
-                for (int k = k0; k < k0 + STEP; ++k) v[k - k0] = reinterpret_cast<const Word*>(tab)[k * stride + filter_sub_id<M, CW>(w, e, k)];
+                for (int k0 = 0; k0 < M; k0 += STEP) {
+                    Word v[STEP];
 #pragma unroll
-                for (int k = k0; k < k0 + STEP; ++k) {
-                    if constexpr (W == 1) sum[e][0] += v[k - k0];
-                    else if constexpr (W == 2) { sum[e][0] += v[k - k0].x; sum[e][1] += v[k - k0].y; }
-                    else { sum[e][0] += v[k - k0].x; sum[e][1] += v[k - k0].y; sum[e][2] += v[k - k0].z; sum[e][3] += v[k - k0].w; }
+                    for (int k = k0; k < k0 + STEP; ++k) v[k - k0] = k < M - V ? entry(k) : x[e][k < M - V ? 0 : k - (M - V)];
+#pragma unroll
+                    for (int k = 0; k < STEP; ++k) add_word(sum[e], v[k]);
+                }
+            } else {
+                // sums of four, averaged two by two: rounded up, but the last: it reaches 128 where all sums' total reaches NA * 128
+                uint32_t level[6][W];
+#pragma unroll
+                for (int g0 = 0; g0 < NA; g0 += 2) {
+                    Word v[2][filter_members(M)];
+#pragma unroll
+                    for (int g = 0; g < 2; ++g)
+#pragma unroll
+                        for (int i = 0; i < filter_members(M); ++i) {
+                            const int k = filter_member(M, g0 + g, i);
+                            v[g][i] = k < M - V ? entry(k) : x[e][k < M - V ? 0 : k - (M - V)];
+                        }
+                    uint32_t two[2][W];
+#pragma unroll
+                    for (int g = 0; g < 2; ++g) {
+#pragma unroll
+                        for (int j = 0; j < W; ++j) two[g][j] = s[j];
+#pragma unroll
+                        for (int i = 0; i < filter_members(M); ++i) add_word(two[g], v[g][i]);
+                    }
+                    // pairs of finished averages become one of the next level
+#pragma unroll
+                    for (int j = 0; j < W; ++j) {
+                        uint32_t avg = __builtin_amdgcn_lerp(two[0][j], two[1][j], NA == 2 ? 0u : 0x01010101u);
+#pragma unroll
+                        for (int l = 1; (1 << l) < NA; ++l) {
+                            if (((g0 >> l) & 1) == 0) { level[l][j] = avg; break; }
+                            avg = __builtin_amdgcn_lerp(level[l][j], avg, (2 << l) == NA ? 0u : 0x01010101u);
+                        }
+                        if (g0 + 2 == NA) sum[e][j] = avg;
+                    }
                 }
             }
 #pragma unroll
             for (int j = 0; j < W; ++j) any |= sum[e][j];
         }
-        if (__ballot((any & TOP) != 0u) == 0) return;
-        // hits: per item a mask of the queries whose field has its top bit set (bit f * 8 (or 16) + j: field f of word j)
-        uint32_t hits[NI];
+        const bool some = __ballot((any & TOP) != 0u) != 0;
 #pragma unroll
-        for (int e = 0; e < NI; ++e) {
-            hits[e] = 0;
-#pragma unroll
-            for (int j = 0; j < W; ++j) hits[e] |= ((sum[e][j] & TOP) >> (W16 ? 15 : 7)) << j;
-            if (item_of(u, e, id) == ~0u) hits[e] = 0;
-        }
-        for (;;) {
-            uint32_t mask = 0, item = 0;
-            bool taken = false;
+        for (int e = 0; e < NI; ++e) hits[e] = 0;
+        if (some) {
 #pragma unroll
             for (int e = 0; e < NI; ++e) {
-                const bool here = !taken && hits[e] != 0u;
-                mask = here ? hits[e] : mask;
-                item = here ? item_of(u, e, id) : item;
-                hits[e] = here ? hits[e] & (hits[e] - 1u) : hits[e];
-                taken = taken || here;
-                asm volatile("" : "+v"(hits[e]));             // (nothing known about it: no lane skips ahead, see process())
-            }
-            const uint64_t who = __ballot(taken);
-            if (who == 0) break;
-            const int bit = mask != 0u ? __builtin_ctz(mask) : 0;
-            const int q = query_of(bit);
-            if (taken) queue[queued + __popcll(who & ((1ull << lane) - 1ull))] = ((uint64_t)q << 32) | item;
-            queued += __popcll(who);
-            if (queued >= kWave) {
-                queued -= kWave;
-                process(std::false_type(), queued, kWave);
-                if (__builtin_expect(++batches > units_seen + 12u, 0)) {   // (as long as that is not so, nothing is counted)
-                    count_passed(queued);
 #pragma unroll
-                    for (int e = 0; e < NI; ++e) hits[e] &= ~gone;
-                }
+                for (int j = 0; j < W; ++j) hits[e] |= ((sum[e][j] & TOP) >> (W16 ? 15 : 7)) << j;
+                hits[e] <<= half * W;
+                if (V > 0) hits[e] &= ~gone;                  // (rows in device memory are not cleared when a query is given up)
+                if (element_of(u, e) == ~0u) hits[e] = 0;
             }
         }
+        return some;
     };
     if (units != 0) {
+        // Groups of D units: looked up one after the other, their hits queued together.  A unit's codes are asked for D - 1 units
+        // ahead, its rows in device memory one.
         int pending = 0;                                      // lane 0: the counter request in flight
-        auto request = [&]() { if (lane == 0) pending = (int)atomicAdd(next_unit, 1u); };
+        // (an increment that the compiler's combining of lanes' additions leaves alone: that waits for the answer at once)
+        auto request = [&]() { if (lane == 0) pending = (int)__builtin_amdgcn_atomic_inc32(next_unit, ~0u, __ATOMIC_RELAXED, "workgroup"); };
         auto requested = [&]() -> uint32_t { return (uint32_t)__builtin_amdgcn_readfirstlane(pending); };
-        uint32_t ua = wave, ub = NW + wave, un = 0;
         request();
-        un = requested();
+        uint32_t un = requested();
         request();
         fetch_ids(un, inext);
-        while (ua < units) {                                  // (ua is the oldest; loads past the end are clamped and never scored)
+        Word x[AHEAD ? 2 : 1][NI][V > 0 ? V : 1];
+        if constexpr (AHEAD) fetch_far(w[0], x[0]);
+        while (unit[0] < units) {                             // (slot 0 holds the oldest; loads past the end are clamped and never count)
             look();
             read_start();
-            scan_unit(ua, wa, ia);
+            uint32_t hits[D][NI], in_group[D];
+            bool some = false;
 #pragma unroll
-            for (int e = 0; e < NI; ++e) ia[e] = inext[e];
-            ua = un;
-            fetch(ua, ia, wa);
-            un = requested();
-            request();
-            fetch_ids(un, inext);
-            if (ub < units) {
-                look();
-                scan_unit(ub, wb, ib);
+            for (int i = 0; i < D; ++i) {
+                constexpr int kAt[2] = {0, AHEAD ? 1 : 0};
+                if constexpr (AHEAD) fetch_far(w[(i + 1) % D], x[kAt[(i + 1) & 1]]);
+                else if constexpr (V > 0) fetch_far(w[i], x[0]);
+                const int into = (i + D - 1) % D;
+                unit[into] = un;
+                fetch(un, inext, w[into]);
+                un = requested();
+                request();
+                fetch_ids(un, inext);
+                in_group[i] = unit[i];
+                if (unit[i] < units) {
+                    some = scan_unit(unit[i], w[i], x[kAt[i & 1]], hits[i]) || some;
+                } else {
+#pragma unroll
+                    for (int e = 0; e < NI; ++e) hits[i][e] = 0;
+                }
             }
+            units_seen += D;
+            if (some) {
+                // into the queue, every lane's hits in its turn: ranks from a prefix sum, and as many at a time as there is room for
+                uint32_t mine = 0;
 #pragma unroll
-            for (int e = 0; e < NI; ++e) ib[e] = inext[e];
-            ub = un;
-            fetch(ub, ib, wb);
-            un = requested();
-            request();
-            fetch_ids(un, inext);
+                for (int i = 0; i < D; ++i)
+#pragma unroll
+                    for (int e = 0; e < NI; ++e) mine += __popc(hits[i][e]);
+                const uint32_t upto = wave_prefix_sum(mine);
+                const uint32_t all = (uint32_t)__builtin_amdgcn_readlane((int)upto, kWave - 1);
+                uint32_t rank = upto - mine, queued_to = 0;   // this lane's next hit; hits queued so far
+                while (queued_to < all) {
+                    const uint32_t room = (uint32_t)(kFilterQueue - queued), limit = queued_to + room < all ? queued_to + room : all;
+                    uint64_t* const at = queue + queued - (int)queued_to;
+#pragma unroll
+                    for (int i = 0; i < D; ++i)
+#pragma unroll
+                        for (int e = 0; e < NI; ++e) {
+                            while (hits[i][e] != 0u && rank < limit) {
+                                const int q = query_of(__builtin_ctz(hits[i][e]));
+                                at[rank] = ((uint64_t)q << 32) | element_of(in_group[i], e);
+                                hits[i][e] &= hits[i][e] - 1u;
+                                ++rank;
+                            }
+                        }
+                    queued += (int)(limit - queued_to);
+                    queued_to = limit;
+                    while (queued >= kWave) {
+                        queued -= kWave;
+                        process(std::false_type(), queued, kWave);
+                        if (__builtin_expect(++batches > units_seen + 12u, 0)) count_passed(queued);   // (as long as that is not so, nothing is counted)
+                    }
+                }
+            }
         }
     }
     if constexpr (P < 16 && !SUB) {
         // the fewer than 16 / P items after the last whole code vector: straight to the queue of one wave of block 0
         const uint32_t first_left = total * (16 / P), n_left = (uint32_t)a.N - first_left;
         if (blk == 0 && wave == 0 && n_left != 0) {
+#pragma unroll 1
             for (int q = 0; q < nq; ++q) {
                 if ((uint32_t)lane < n_left) queue[queued + lane] = ((uint64_t)q << 32) | (first_left + (uint32_t)lane);
-                queued += (int)n_left;                        // (at most 3 of 16 queries beside the 63 that may wait: there is room)
+                queued += (int)n_left;
+                if (queued >= kWave) {
+                    queued -= kWave;
+                    process(std::false_type(), queued, kWave);
+                }
             }
         }
     }
@@ -1001,13 +1213,13 @@ __global__ __launch_bounds__(kFilterThreads) void scan_filter_kernel(FilterArgs 
     stamp<STAMP>(rec, kStampOffered, lane);
     __syncthreads();
 
-    // ---- the queries that were given up, W at a time: lists, counters and floors as at the start, exact tables in the counts'
+    // ---- the queries that were given up, EW at a time: lists, counters and floors as at the start, exact tables in the counts'
     // place; what exceeds a query's floor and its list's K-th best key goes through the queue like any hit
     uint32_t todo = (uint32_t)__ballot(lane < QT && (lds_peek(passed + (lane < QT ? lane : 0)) & kLost) != 0u);
     while (__builtin_expect(todo != 0, 0)) {
-        int qs[W];
+        int qs[EW];
 #pragma unroll
-        for (int j = 0; j < W; ++j) {
+        for (int j = 0; j < EW; ++j) {
             qs[j] = todo != 0 ? __builtin_ctz(todo) : -1;
             todo &= todo - 1u;
             const int q = qs[j];
@@ -1016,20 +1228,21 @@ __global__ __launch_bounds__(kFilterThreads) void scan_filter_kernel(FilterArgs 
             if (tid < kFilterBins) hist[q * kFilterBins + tid] = 0u;
             if (tid == 0) { thr[q] = 0ull; cnt[q] = 0u; set_t(q, par[q].t_first); }
         }
-        for (uint32_t i = tid; i < entries; i += NT) {
+        for (uint32_t i = tid; i < (uint32_t)(M * stride); i += NT) {
             const uint32_t k = i / (uint32_t)stride, g = i - k * (uint32_t)stride;
 #pragma unroll
-            for (int j = 0; j < W; ++j)
-                tab[i * W + j] = qs[j] >= 0 && g < (uint32_t)b ? __float_as_uint(a.S[((size_t)(q0 + qs[j]) * M + k) * b + g]) : 0u;
+            for (int j = 0; j < EW; ++j)
+                tab[i * EW + j] = qs[j] >= 0 && g < (uint32_t)b ? __float_as_uint(a.S[((size_t)(q0 + qs[j]) * M + k) * b + g]) : 0u;
         }
         if (tid == 0) *next_unit = NW;
         uint32_t u = wave;
-        fetch_ids(u, ia);
-        if constexpr (P <= 16) fetch(u, ia, wa);
+        uint32_t wa[Sh::kWords], wb[Sh::kWords];
+        fetch_ids(u, inext);
+        if constexpr (P <= 16) fetch(u, inext, wa);
         __syncthreads();
-        float first_floor[W];
+        float first_floor[EW];
 #pragma unroll
-        for (int j = 0; j < W; ++j) first_floor[j] = par[qs[j] < 0 ? 0 : qs[j]].floor;
+        for (int j = 0; j < EW; ++j) first_floor[j] = par[qs[j] < 0 ? 0 : qs[j]].floor;
         queued = 0;
         bool done = units == 0;
         while (!done) {
@@ -1037,45 +1250,59 @@ __global__ __launch_bounds__(kFilterThreads) void scan_filter_kernel(FilterArgs 
             int pending = 0;
             if (lane == 0) pending = (int)atomicAdd(next_unit, 1u);
             const uint32_t un = (uint32_t)__builtin_amdgcn_readfirstlane(pending);
-            fetch_ids(un, ib);
-            if constexpr (P <= 16) fetch(un, ib, wb);
+            fetch_ids(un, inext);
+            if constexpr (P <= 16) fetch(un, inext, wb);
             // scores that matter: above the sample's floor and the list's K-th best (none yet: key 0, whose score is a NaN and loses)
-            float floor[W];
+            float floor[EW];
 #pragma unroll
-            for (int j = 0; j < W; ++j) floor[j] = score_of_key(lds_peek(thr + (qs[j] < 0 ? 0 : qs[j])));
+            for (int j = 0; j < EW; ++j) floor[j] = score_of_key(lds_peek(thr + (qs[j] < 0 ? 0 : qs[j])));
 #pragma unroll
-            for (int j = 0; j < W; ++j) floor[j] = qs[j] < 0 ? __builtin_nanf("") : fmaxf(floor[j], first_floor[j]);
-            uint32_t hits[NI];                                // per item bit j: query qs[j]
+            for (int j = 0; j < EW; ++j) floor[j] = qs[j] < 0 ? __builtin_nanf("") : fmaxf(floor[j], first_floor[j]);
+            // (pairs: a lane takes every other of the pair's items)
+            constexpr int NL = NI % G == 0 ? NI / G : 1;      // items of a lane
+            auto own_element = [&](int e) -> uint32_t {
+                if constexpr (NI % G != 0) return half == 0 ? element_of(u, e) : ~0u;   // (an item for two lanes: the first one's)
+                else return element_of(u, e * G + half);
+            };
+            uint32_t own[NL * (P / 4)];                     // their rows (rows of up to 16 bytes)
+            if constexpr (P <= 16) {
+#pragma unroll
+                for (int e = 0; e < NL; ++e)
+#pragma unroll
+                    for (int j = 0; j < P / 4; ++j) own[e * (P / 4) + j] = NI % G != 0 || half == 0 ? wa[e * G * (P / 4) + j] : wa[(NI % G != 0 ? 0 : e * G + G - 1) * (P / 4) + j];
+            }
+            uint32_t hits[NL];                                // per item bit j: query qs[j]
             if (u < units) {
 #pragma unroll
-                for (int e = 0; e < NI; ++e) {
-                    float acc[W];
+                for (int e = 0; e < NL; ++e) {
+                    float acc[EW];
                     // (a few lookups on their way together: few registers, and sixteen waves hide each other's waits)
                     constexpr int kTogether = P <= 16 && M >= 8 ? 8 : 4;
                     auto add = [&](const uint32_t* row, int base, int k0, bool first) {   // sub-ids base + k0 .., of which `row` starts with `base`
-                        Word v[kTogether];
+                        using Exact = typename FilterWord<EW>::type;
+                        Exact v[kTogether];
 #pragma unroll
-                        for (int k = k0; k < k0 + kTogether; ++k) v[k - k0] = reinterpret_cast<const Word*>(tab)[(base + k) * stride + filter_sub_id<M, CW>(row, 0, k)];
+                        for (int k = k0; k < k0 + kTogether; ++k) v[k - k0] = reinterpret_cast<const Exact*>(tab)[(base + k) * stride + filter_sub_id<M, CW>(row, 0, k)];
 #pragma unroll
                         for (int k = 0; k < kTogether; ++k) {
-                            float x[W];
-                            if constexpr (W == 1) x[0] = __uint_as_float(v[k]);
-                            else if constexpr (W == 2) { x[0] = __uint_as_float(v[k].x); x[1] = __uint_as_float(v[k].y); }
+                            float x[EW];
+                            if constexpr (EW == 1) x[0] = __uint_as_float(v[k]);
+                            else if constexpr (EW == 2) { x[0] = __uint_as_float(v[k].x); x[1] = __uint_as_float(v[k].y); }
                             else { x[0] = __uint_as_float(v[k].x); x[1] = __uint_as_float(v[k].y); x[2] = __uint_as_float(v[k].z); x[3] = __uint_as_float(v[k].w); }
 #pragma unroll
-                            for (int j = 0; j < W; ++j) acc[j] = first && k == 0 ? x[j] : acc[j] + x[j];
+                            for (int j = 0; j < EW; ++j) acc[j] = first && k == 0 ? x[j] : acc[j] + x[j];
                         }
                         __builtin_amdgcn_sched_barrier(0);
                     };
                     if constexpr (P <= 16) {
 #pragma unroll
-                        for (int k0 = 0; k0 < M; k0 += kTogether) add(&wa[e * P / 4], 0, k0, k0 == 0);
+                        for (int k0 = 0; k0 < M; k0 += kTogether) add(&own[e * P / 4], 0, k0, k0 == 0);
                     } else {                                  // wide rows: piece by piece from memory
-                        const uint32_t at = item_of(u, e, ia);
-                        const uint4* const row = reinterpret_cast<const uint4*>(a.codes + (size_t)(at != ~0u ? at : 0u) * P);
+                        const uint32_t at = own_element(e);
+                        const uint4* const row = reinterpret_cast<const uint4*>(a.codes + (size_t)item_at(at != ~0u ? at : 0u) * P);
                         constexpr int kPer = 16 / CW;         // sub-ids of a piece
 #pragma unroll
-                        for (int j = 0; j < W; ++j) acc[j] = -0.0f;   // (-0 + x is x, whatever x)
+                        for (int j = 0; j < EW; ++j) acc[j] = -0.0f;   // (-0 + x is x, whatever x)
 #pragma unroll 1
                         for (int i = 0; i < P / 16; ++i) {
                             const uint4 x = row[i];
@@ -1086,23 +1313,23 @@ __global__ __launch_bounds__(kFilterThreads) void scan_filter_kernel(FilterArgs 
                     }
                     hits[e] = 0;
 #pragma unroll
-                    for (int j = 0; j < W; ++j) hits[e] |= (uint32_t)(acc[j] >= floor[j]) << j;
+                    for (int j = 0; j < EW; ++j) hits[e] |= (uint32_t)(acc[j] >= floor[j]) << j;
                     if (__ballot(hits[e] != 0u) != 0) {
-                        const uint32_t item = item_of(u, e, ia);
+                        const uint32_t at = own_element(e), item = at != ~0u ? item_at(at) : ~0u;
 #pragma unroll
-                        for (int j = 0; j < W; ++j)
+                        for (int j = 0; j < EW; ++j)
                             if (item == ~0u || make_key(acc[j] + 0.0f, item) <= lds_peek(thr + (qs[j] < 0 ? 0 : qs[j]))) hits[e] &= ~(1u << j);
                     }
                 }
             } else {
                 done = true;
 #pragma unroll
-                for (int e = 0; e < NI; ++e) hits[e] = 0;
-                if constexpr (P < 16 && !SUB) {               // the items after the last whole code vector (at most 3 of W queries)
+                for (int e = 0; e < NL; ++e) hits[e] = 0;
+                if constexpr (P < 16 && !SUB) {               // the items after the last whole code vector (at most 3 of EW queries)
                     const uint32_t first_left = total * (16 / P), n_left = (uint32_t)a.N - first_left;
                     if (blk == 0 && wave == 0 && n_left != 0) {
 #pragma unroll
-                        for (int j = 0; j < W; ++j) {
+                        for (int j = 0; j < EW; ++j) {
                             if (qs[j] < 0) continue;
                             if ((uint32_t)lane < n_left) queue[queued + lane] = ((uint64_t)qs[j] << 32) | (first_left + (uint32_t)lane);
                             queued += (int)n_left;
@@ -1111,25 +1338,30 @@ __global__ __launch_bounds__(kFilterThreads) void scan_filter_kernel(FilterArgs 
                 }
             }
             for (;;) {
-                uint32_t mask = 0, item = 0;
+                uint32_t mask = 0, item = 0, left = 0;
+#pragma unroll
+                for (int e = 0; e < NL; ++e) left |= hits[e];
+                const uint64_t who = __ballot(left != 0u);
+                if (who == 0 && !(done && queued != 0)) break;
+                const bool full = queued + __popcll(who) > kFilterQueue;
+                if (!full) {
                 bool taken = false;
 #pragma unroll
-                for (int e = 0; e < NI; ++e) {
+                for (int e = 0; e < NL; ++e) {
                     const bool here = !taken && hits[e] != 0u;
                     mask = here ? hits[e] : mask;
-                    item = here ? item_of(u, e, ia) : item;
+                    item = here ? own_element(e) : item;
                     hits[e] = here ? hits[e] & (hits[e] - 1u) : hits[e];
                     taken = taken || here;
                     asm volatile("" : "+v"(hits[e]));
                 }
-                const uint64_t who = __ballot(taken);
-                if (who == 0 && !(done && queued != 0)) break;
                 int q = 0;
 #pragma unroll
-                for (int j = 0; j < W; ++j) q = (mask & (0u - mask)) == (1u << j) ? qs[j] : q;
+                for (int j = 0; j < EW; ++j) q = (mask & (0u - mask)) == (1u << j) ? qs[j] : q;
                 if (taken) queue[queued + __popcll(who & ((1ull << lane) - 1ull))] = ((uint64_t)q << 32) | item;
                 queued += __popcll(who);
-                if (queued >= kWave || who == 0) {
+                }
+                if (full || queued >= kWave || who == 0) {
                     const int n = queued < kWave ? queued : kWave;
                     queued -= n;
                     process(std::true_type(), queued, n);
@@ -1138,16 +1370,14 @@ __global__ __launch_bounds__(kFilterThreads) void scan_filter_kernel(FilterArgs 
             look();
             u = un;
 #pragma unroll
-            for (int e = 0; e < NI; ++e) ia[e] = ib[e];
-#pragma unroll
             for (int i = 0; i < Sh::kWords; ++i) wa[i] = wb[i];
         }
         __syncthreads();
     }
 
     // ---- a wave per query: keys that reach the final floor, ranked by counting, straight to the workspace
-    if (wave < nq) {
-        const int q = wave;
+#pragma unroll 1
+    for (int q = wave; q < nq; q += NW) {
         uint64_t* const list = lists + (size_t)q * cap;
         const int tq = t_of(q);
         const FilterQuery p = par[q];
@@ -1194,7 +1424,7 @@ __global__ __launch_bounds__(kFilterThreads) void scan_filter_kernel(FilterArgs 
             }
             if (rank < (uint32_t)K) out((int)rank, mine);
         }
-        stamp<STAMP>(rec, kStampSelected, lane);
     }
+    if (wave < nq) stamp<STAMP>(rec, kStampSelected, lane);
     stamp<STAMP>(rec, kStampEnd, lane);
 }

@@ -325,10 +325,10 @@ def test_larger_k_straight_from_registers(pq, oracle, K, kind):
 
 # ---- batches scanned by upper bounds: every geometry of fields and rows, edges of tiles and of the last code vector, K from 1
 # to the longest lists, samples of one and of several parts and rounds; bit 4 keeps small shapes on these kernels
-def _bounds_case(pq, oracle, codes, S, K, subset=None):
+def _bounds_case(pq, oracle, codes, S, K, subset=None, mask=16):
     import torch
     Gd, Sd = torch.from_numpy(codes).cuda(), torch.from_numpy(S).cuda()
-    prev = pq.pq_measure_force_general(16)
+    prev = pq.pq_measure_force_general(mask)
     try:
         if subset is not None:
             ids, sc = pq.pq_score_topk_subset(Gd, Sd, torch.from_numpy(subset).cuda(), K)
@@ -402,6 +402,35 @@ def test_scan_by_upper_bounds_when_the_bounds_say_little(pq, oracle, tables):
             for k, scale in enumerate((65536.0, 256.0, 1.0)):
                 S[:, k] = np.arange(256, dtype=np.float32) * np.float32(scale)
         _bounds_case(pq, oracle, codes, np.ascontiguousarray(S, dtype=np.float32), K)
+
+
+# Pairs of lanes (bit 7: wherever they fit): whole and ragged tiles of 32, the edges of a pair's units, rows looked up in device memory,
+# what is queued when most items pass, and queries given up
+@pytest.mark.parametrize("tables", ["bell", "coarse", "unlike_splits", "rare_high"])
+@pytest.mark.parametrize("m", [4, 8, 16])
+@pytest.mark.parametrize("N,B,K", [(4_099, 33, 1), (20_001, 31, 10), (33_334, 70, 16), (9_000, 5, 32), (16_001, 40, 100)])
+def test_scan_by_upper_bounds_in_pairs_of_lanes(pq, oracle, m, N, B, K, tables):
+    rng = np.random.default_rng(m * 1000 + B + K)
+    codes = rng.integers(0, 256, (N, m), dtype=np.uint8)
+    S = rng.standard_normal((B, m, 256), dtype=np.float32)
+    if tables == "coarse":
+        S = np.round(S)
+    elif tables == "unlike_splits":                            # (the largest sum decides about the step)
+        S *= np.float32(2.0) ** -np.arange(m, dtype=np.float32)[None, :, None]
+    elif tables == "rare_high":
+        codes[codes[:, 1] == 7, 1] = 8
+        codes[[3, N // 2, N - 1], 1] = 7
+        S[::2, 1, 7] = 1e5
+    if m < 16 or K <= 16:
+        prev = pq.pq_measure_force_general(16 | 128)
+        try:
+            assert pq.pq_measure_plan("scan", N, B, m, 256, K)["queries"] == 32
+        finally:
+            pq.pq_measure_force_general(prev)
+    _bounds_case(pq, oracle, codes, S, K, mask=16 | 128)
+    _bounds_case(pq, oracle, codes, S, K, subset=rng.permutation(N)[:N - 1500].astype(np.int32), mask=16 | 128)
+    wide = (codes.astype(np.uint16) * 257 // 256)              # (sub-ids of two bytes, tables of an odd length)
+    _bounds_case(pq, oracle, wide, rng.standard_normal((B, m, 259), dtype=np.float32), K, mask=16 | 128)
 
 
 def _odd_tables(kind, S):
