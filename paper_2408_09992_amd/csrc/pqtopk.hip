@@ -343,16 +343,20 @@ ScanPlan make_plan(long long N, int B, int m, int K, bool generic = false, int c
             }
         }
     }
-    // Longer catalogues of a single query are scanned in segments, one workgroup per CU.
+    // Longer catalogues of a single query are scanned in segments, one workgroup per CU.  So are any queries whose tables of two-byte
+    // sub-ids fit LDS beside one candidate array but not beside a list per wave: the general kernel looks them up in device memory
+    // then, one lane per clock and CU (K = 512: one query, m = 4, b = 8192, 29M items 370 us, in segments 74; m = 8, b = 4096, 64 queries of
+    // 300,000 items 521 and 74, 400 of 100,000 1103 and 154; K = 120: m = 16, b = 2048, one query, 8M 274 and 53; 400 of 100,000 2166 and 217).
     p.long_scan = false;
-    if (!(without & kNoLong) && !p.short_scan && p.vec && !generic && !p.tiled && B == 1 &&
+    if (!(without & kNoLong) && !p.short_scan && p.vec && !generic && !p.tiled && (B == 1 || p.glut) &&
         !(g_force_general.load(std::memory_order_relaxed) & 1) &&
-        (long_scan_pays(N, m, K, cw) || ((g_force_general.load(std::memory_order_relaxed) & 64) && (cw == 2 || m >= 4)))) {
+        (p.glut || long_scan_pays(N, m, K, cw) || ((g_force_general.load(std::memory_order_relaxed) & 64) && (cw == 2 || m >= 4)))) {
         const size_t table = cw == 1 ? lut_floats * (m <= 8 ? kTableCopies : 1) * sizeof(float) : table16;
         if (table + sizeof(LongSelectLds<kLongThreads>) <= kMaxLdsBytes) {
+            const long long per_segment = (long long)kLongThreads * (row <= 16 ? kLongScores * row / 16 : kLongScores);
             p.long_scan = true;
             p.glut = false;
-            p.nblk = kAssumedCUs;
+            p.nblk = B == 1 ? kAssumedCUs : (int)blocks_for_many_queries(kAssumedCUs, B, (units + per_segment - 1) / per_segment, lookups);
             p.copies = cw == 1 && m <= 8 ? kTableCopies : 1;
             p.big = true;
             p.scan_dyn_lds = sizeof(LongSelectLds<kLongThreads>) + table16;
