@@ -179,7 +179,7 @@ __global__ __launch_bounds__(NT) void fold_lists_kernel(FoldArgs a) {
     for (int t = tid; t < K; t += NT) emit(t, sorted[t]);
 }
 
-// The fold for small K (K < kRegisterSelectMinK) when a query's lists fit R keys per thread (nlists * K <= NT * R): the keys go
+// The fold for small K and few keys (nlists * K <= NT * R; the host's rule is fold_small_pays()): the keys go
 // straight from memory to registers and through select_small_k(), the selection the short scan uses: per-wave floors
 // by wave operations, one barrier, ranking by counting.  grid = (1, B).  A kernel of its own because this launch is all
 // latency (a few thousand keys): its time is the two dependent memory round trips it cannot avoid (arguments, keys)

@@ -982,6 +982,16 @@ int enqueue_scan(const ScanPlan& p, const uint8_t* codes, const float* S, long l
     return record_hip(e);
 }
 
+// Which fold takes `nlists` lists of K keys.  fold_small_kernel's waves let K keys or more pass each, which it ranks by counting:
+// right for few of them; fold_lists_kernel lets 1.3 K pass.  Steps without Eq. 4 (us; fold_small and fold_lists), one user,
+// 256 lists: K = 5 8.5 and 8.8, 10 8.9 and 9.3, 11 9.5 and 9.2, 12 10.1 and 9.5, 13 10.1 and 9.1, 16 18.2 and 9.3, 24 16.0 and 9.8;
+// 128 lists, two users: K = 12 12.4 and 12.3, 16 15.6 and 11.6; 20 lists: K = 13 6.5 and 6.6, 16 6.6 and 6.6, 20 7.1 and 6.7, 31 9.4
+// and 7.3; 34 lists: K = 13 6.6 and 6.9, 16 7.2 and 6.9; 13 lists of 31, 300 users: 107.8 and 108.2; 4 lists of 30, 64 users: 12.8 and 13.4.
+bool fold_small_pays(int nlists, int K) {
+    const long long keys = (long long)nlists * K;
+    return keys <= (K <= 10 ? kThreads * kFoldSmallRegsMax : K <= 12 ? 2048 : K < kRegisterSelectMinK ? 448 : 0);
+}
+
 // Enqueue the fold of the workspace's lists into the outputs.
 int enqueue_fold(const ScanPlan& p, int B, int K, void* workspace, int* out_ids, float* out_scores, hipStream_t st,
                  uint64_t* stamps = nullptr) {
@@ -993,9 +1003,7 @@ int enqueue_fold(const ScanPlan& p, int B, int K, void* workspace, int* out_ids,
     f.chunk = f.depth = f.need = f.groups = f.group_mask = 0;
     f.out_ids = out_ids; f.out_scores = out_scores;
     f.stamps = stamps;
-    if (K < kRegisterSelectMinK && (long long)nlists * K <= (long long)kThreads * kFoldSmallRegsMax &&
-        !(g_force_general.load(std::memory_order_relaxed) & 2)) {
-        // small K, few keys: the lean fold
+    if (fold_small_pays(nlists, K) && !(g_force_general.load(std::memory_order_relaxed) & 2)) {
         const bool few = (long long)nlists * K <= (long long)kThreads * kFoldSmallRegs;
         auto go = [&](auto kernel) {
             return record_hip(launch(kernel, dim3(1, B), kThreads, 0, st, f.ws_keys, out_ids, out_scores, nlists, K, stamps));

@@ -785,6 +785,21 @@ def test_small_fold_many_lists(pq, oracle):
         assert_same_topk(pq, oracle, G, tables(N % 89, B, 8, 256), K, "small fold")
 
 
+@pytest.mark.parametrize("N,B,K", [(1_280_000, 1, 10), (1_280_000, 1, 11), (174_080, 1, 12), (175_104, 1, 12), (1_280_000, 1, 16), (28_000, 1, 16),
+                                   (30_000, 1, 16), (14_000, 1, 31), (16_000, 1, 31), (40_000, 64, 31), (1_280_000, 2, 24)])
+def test_fold_on_either_side_of_its_line(pq, oracle, N, B, K):
+    # lists times K on either side of where the small fold ends (K = 11 and 12: 2048 keys, from 13 on 448): random scores, the best
+    # items all in one list, and equal scores across the lists
+    for kind in ("random", "sorted", "coarse"):
+        G = W.codes_uniform(N, 8, 256, seed=K)
+        S = tables(N % 89 + K, B, 8, 256)
+        if kind == "sorted":
+            G = G[np.argsort(sum(S[0, k][G[:, k]] for k in range(8)))[::-1]].copy()
+        elif kind == "coarse":
+            S = np.round(S).astype(np.float32)
+        assert_same_topk(pq, oracle, G, S, K, f"fold {kind}")
+
+
 def test_coarse_tables_many_ties(pq, oracle):
     G = W.codes_uniform(300_000, 4, 16, seed=3)
     S = (np.round(W.normal_f32(W.stream_key(3, W.STREAM_QUERIES), 2 * 4 * 16) * 2) / 2).astype(np.float32)
