@@ -450,12 +450,13 @@ def pq_measure_sync_variant(variant: int, scratch: torch.Tensor, iters: int) -> 
 def pq_measure_force_general(mask: int) -> int:
     """Bit 0: scans avoid the short kernel; bit 1: folds avoid the small-K fold; bit 2: Eq. 4 avoids the matrix cores;
     bit 3: batches are not scanned by upper bounds; bit 4: they are, whatever their size; bit 5: candidate lists are spread
-    over workgroups; bit 6: longer single queries are scanned in segments (workspace sizes depend on these four); 0: the library's choice.  Returns the previous mask."""
+    over workgroups; bit 6: longer single queries are scanned in segments (workspace sizes depend on these four); bit 7: scans by bounds run by pairs of lanes wherever these fit; bit 8: batches take two queries
+    per workgroup wherever that fits; 0: the library's choice.  Returns the previous mask."""
     return int(lib().pq_measure_force_general(int(mask)))
 
 
 PQ_PLAN_KINDS = {"scan": 0, "subset": 1, "scan16": 2}
-PQ_PLAN_KERNELS = ("general", "batched", "short", "long", "short list", "bounds")
+PQ_PLAN_KERNELS = ("general", "batched", "short", "long", "short list", "bounds", "pairs")
 
 
 def pq_measure_plan(kind: str, N: int, B: int, m: int, b: int, K: int) -> dict:

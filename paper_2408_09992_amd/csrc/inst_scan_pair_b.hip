@@ -1,0 +1,6 @@
+// Instantiates the catalogue-scan kernels that take two queries per workgroup (see the instance lists in kernels.hpp).
+#define PQ_INSTANCE_TU
+#include "kernels.hpp"
+namespace pqk {
+PQ_PAIR_INSTANCES_B(PQ_PAIR_DEFINE)
+}

@@ -17,6 +17,7 @@ namespace pqk {
 #include "select_small.hpp"
 #include "scan_single.hpp"
 #include "scan_short.hpp"
+#include "scan_pair.hpp"
 #include "scan_long.hpp"
 #include "scan_subset.hpp"
 #include "scan_batched.hpp"
@@ -73,6 +74,22 @@ namespace pqk {
     PQ_SHORT_U4(X, 32, 1) PQ_SHORT_U4(X, 32, 5) PQ_SHORT_U4(X, 64, 1)
 // scan_short_kernel<M, U, NT, false, 2>: two-byte sub-ids, m = 4, 8 (up to 12 code vectors per thread), 16 (up to 6 items)
 #define PQ_SHORT16_U(X, M, U) X(M, U, kThreads, false, 2)
+// scan_pair_kernel<M, U, NT, CW>: every number of units up to pair_held_units() and the larger instances, up to pair_max_units()
+#define PQ_PAIR_U(X, M, U, CW) X(M, U, kThreads, CW)
+#define PQ_PAIR_U4(X, M, U, CW) PQ_PAIR_U(X, M, U, CW) PQ_PAIR_U(X, M, U + 1, CW) PQ_PAIR_U(X, M, U + 2, CW) PQ_PAIR_U(X, M, U + 3, CW)
+#define PQ_PAIR_20(X, M, CW) PQ_PAIR_U(X, M, 12, CW) PQ_PAIR_U(X, M, 16, CW) PQ_PAIR_U(X, M, 20, CW)
+#define PQ_PAIR_40(X, M, CW) PQ_PAIR_20(X, M, CW) PQ_PAIR_U(X, M, 24, CW) PQ_PAIR_U(X, M, 32, CW) PQ_PAIR_U(X, M, 40, CW)
+#define PQ_PAIR_INSTANCES_A(X) \
+    PQ_PAIR_U4(X, 4, 1, 1) PQ_PAIR_U4(X, 4, 5, 1) \
+    PQ_PAIR_U4(X, 8, 1, 1) PQ_PAIR_U4(X, 8, 5, 1) PQ_PAIR_20(X, 8, 1) \
+    PQ_PAIR_U4(X, 16, 1, 1) PQ_PAIR_U4(X, 16, 5, 1) PQ_PAIR_40(X, 16, 1)
+#define PQ_PAIR_INSTANCES_B(X) \
+    PQ_PAIR_U4(X, 32, 1, 1) PQ_PAIR_U(X, 32, 8, 1) PQ_PAIR_40(X, 32, 1) \
+    PQ_PAIR_U(X, 64, 1, 1) PQ_PAIR_U(X, 64, 2, 1) PQ_PAIR_U(X, 64, 4, 1) PQ_PAIR_U(X, 64, 8, 1) PQ_PAIR_20(X, 64, 1) PQ_PAIR_U(X, 64, 24, 1)
+#define PQ_PAIR_INSTANCES_C(X) \
+    PQ_PAIR_U4(X, 4, 1, 2) PQ_PAIR_U4(X, 4, 5, 2) PQ_PAIR_20(X, 4, 2) \
+    PQ_PAIR_U4(X, 8, 1, 2) PQ_PAIR_U4(X, 8, 5, 2) PQ_PAIR_40(X, 8, 2) \
+    PQ_PAIR_U4(X, 16, 1, 2) PQ_PAIR_U(X, 16, 8, 2) PQ_PAIR_40(X, 16, 2)
 #define PQ_SHORT16_INSTANCES(X) \
     PQ_SHORT16_U(X, 4, 1) PQ_SHORT16_U(X, 4, 2) PQ_SHORT16_U(X, 4, 3) PQ_SHORT16_U(X, 4, 4) PQ_SHORT16_U(X, 4, 5) PQ_SHORT16_U(X, 4, 6) \
     PQ_SHORT16_U(X, 4, 7) PQ_SHORT16_U(X, 4, 8) PQ_SHORT16_U(X, 4, 9) PQ_SHORT16_U(X, 4, 10) PQ_SHORT16_U(X, 4, 11) PQ_SHORT16_U(X, 4, 12) \
@@ -119,6 +136,8 @@ namespace pqk {
 #define PQ_SHORT_DEFINE(M, U, NT, ST) template __global__ void scan_short_kernel<M, U, NT, ST>(const uint8_t*, const float*, void*, float*, uint32_t, int, int, uint64_t*);
 #define PQ_SHORT_EXTERN(M, U, NT, ST) extern PQ_SHORT_DEFINE(M, U, NT, ST)
 #define PQ_SHORT16_DEFINE(M, U, NT, ST, CW) template __global__ void scan_short_kernel<M, U, NT, ST, CW>(const uint8_t*, const float*, void*, float*, uint32_t, int, int, uint64_t*);
+#define PQ_PAIR_DEFINE(M, U, NT, CW) template __global__ void scan_pair_kernel<M, U, NT, CW>(const uint8_t*, const float*, void*, float*, uint32_t, int, int, int);
+#define PQ_PAIR_EXTERN(M, U, NT, CW) extern PQ_PAIR_DEFINE(M, U, NT, CW)
 #define PQ_SHORT16_EXTERN(M, U, NT, ST, CW) extern PQ_SHORT16_DEFINE(M, U, NT, ST, CW)
 #define PQ_LONG_DEFINE(M, CW, C) template __global__ void scan_long_kernel<M, CW, C>(const uint8_t*, const float*, void*, float*, uint32_t, int, int);
 #define PQ_LONG_EXTERN(M, CW, C) extern PQ_LONG_DEFINE(M, CW, C)
@@ -150,6 +169,9 @@ PQ_SHORT_INSTANCES_E(PQ_SHORT_EXTERN)
 PQ_LONG_INSTANCES(PQ_LONG_EXTERN)
 PQ_SUBSET_INSTANCES(PQ_SUBSET_EXTERN)
 PQ_SHORT16_INSTANCES(PQ_SHORT16_EXTERN)
+PQ_PAIR_INSTANCES_A(PQ_PAIR_EXTERN)
+PQ_PAIR_INSTANCES_B(PQ_PAIR_EXTERN)
+PQ_PAIR_INSTANCES_C(PQ_PAIR_EXTERN)
 PQ_TILED_INSTANCES(PQ_TILED_EXTERN)
 PQ_FILTER_INSTANCES_STAMPED(PQ_FILTER_EXTERN8)
 PQ_FILTER_INSTANCES_A(PQ_FILTER_EXTERN, PQ_FILTERP_EXTERN)

@@ -11,6 +11,7 @@
 // what they are for:
 //   scan_short_kernel (scan_short.hpp; scan_subset_kernel for candidate lists): a workgroup's share fits its registers as scores, up to
 //     64 per thread: single queries over up to 8M items, batches over small catalogues.  The K best are selected from there.
+//   scan_pair_kernel (scan_pair.hpp): the same for two queries per workgroup: a few queries, or many over small catalogues.
 //   scan_long_kernel (scan_long.hpp): a single query over more, in segments of registers.
 //   scan_filter_kernel (scan_filter.hpp; filter_prepare_kernel before it takes a sample for the first floors and makes the tables):
 //     batches.  Upper bounds of 8 or 16 bits for up to sixteen queries are summed with one LDS read per sub-id; only what reaches
@@ -98,6 +99,7 @@ struct ScanPlan {
     bool short_scan; // scan_short_kernel: every workgroup's share fits its registers, K small
     int short_units; // ... units (code vectors, or items for m = 32, 64) a thread holds
     bool long_scan;  // scan_long_kernel: one query's catalogue in segments
+    bool pair_scan;  // scan_pair_kernel: as the short scan, two queries per workgroup (short_units: what a thread holds)
     bool short_subset; // scan_subset_kernel: a candidate list whose share per thread fits its registers, K small
     int subset_vecs;   // ... code vectors' worth of gathered rows a thread holds
     bool filter;       // filter_prepare_kernel + scan_filter_kernel: a batch scanned by integer upper bounds
@@ -120,7 +122,7 @@ struct ScanPlan {
 };
 
 // What make_plan() may choose from.
-enum { kNoFilter = 1, kNoLong = 2 };
+enum { kNoFilter = 1, kNoLong = 2, kNoPair = 4 };
 
 bool is_vec_m(int m) { return m == 1 || m == 2 || m == 4 || m == 8 || m == 16 || m == 32 || m == 64; }
 
@@ -199,6 +201,32 @@ bool long_scan_pays(long long N, int m, int K, int cw) {
         case 64: return K > 256;
         default: return false;
     }
+}
+
+// Where two queries per workgroup (scan_pair_kernel) beat one: half the lookups, for a second selection (and twice the lists), which
+// costs the more the more results there are.  Around the lines (us, without Eq. 4; one and two): m = 8, 1.28M items, 2 queries (20M
+// lookups): K = 12 12.6 and 11.4, K = 48 13.0 and 13.9; 4 queries (41M): K = 48 17.1 and 16.2, 64 17.6 and 16.9, 100 19.1 and 20.2;
+// m = 16, 300,000, 12 (58M): K = 100 22.4 and 20.7; m = 4, 1M, 6 (24M): K = 12 12.8 and 13.9; 236,127, 34 (32M): K = 59 21.6 and 17.2;
+// m = 64, 400,000, 4 (102M): K = 400 31.7 and 28.3, 83,912, 15 (81M): K = 152 27.4 and 30.8.  A single workgroup per query leaves no lists
+// to fold: with 22,906 items, m = 8, 170 queries 13.0 and 11.7, 14,183 10.2 and 12.8 (m = 64: 3400 14.5 and 16.5).  The general kernel
+// is the slower one wherever shares fit (m = 8, 37,863, 170, K = 23: 20.4 and 15.2; two bytes, 42,619, 357, K = 434: 237 and 69), but for
+// many results of more queries than compute units, over more blocks than one (m = 16, 28,254, 455, K = 157: 53.6 and 62.0).
+constexpr double kPairLookupsPerUs = 20000.0;         // a CU's
+bool pair_pays(const ScanPlan& p, long long N, int B, int m, int K) {
+    double least = 2.0e7;
+    if (p.short_scan) {
+        if (p.nblk == 1 && B <= kAssumedCUs && N * m < (m >= 32 ? 300000 : 160000)) return false;
+        least = K <= 12 ? (m >= 32 ? 3.0e7 : 2.0e7) : K <= 32 ? 3.0e7 : K <= 64 ? 4.0e7 : m >= 32 ? 1.0e8 : 6.0e7;
+        if (m == 4) least *= 1.5;
+    }
+    return (double)B * (double)N * m >= least;
+}
+double filter_min_lookups(int m, int K, int B, bool subset, int cw);
+// ... and beat the scan by bounds, which has its sample and tables to make first: m = 8, 200,000 items, 44 queries (71M lookups) 21.6 and 17.9,
+// 45,066, 226 (81M) 20.5 and 18.0, 420,542, 50 (168M) 37.8 and 65.3; m = 16, 64,130, 110 (113M) 24.9 and 21.3, 43,359, 620 (430M) 78.7 and 70.6,
+// 85,925, 175 (241M) 37.0 and 42.7; m = 64, 61,190, 78 (305M) 55.8 and 43.4; m = 4, 2.6M, 7 (73M) 17.0 and 20.5.
+bool pair_beats_bounds(long long N, int B, int m, int K, int cw) {
+    return m > 4 && ((double)B * (double)N * m < 1.35 * filter_min_lookups(m, K, B, false, cw) || N < (m == 8 ? 24000 : 48000));
 }
 
 // `generic`: plan for the generic kernel whatever m is (candidate-list scans use it: their rows are gathered)
@@ -385,8 +413,38 @@ ScanPlan make_plan(long long N, int B, int m, int K, bool generic = false, int c
             p.scan_lds = (size_t)m * kLutStride * sizeof(float) + p.scan_dyn_lds;
         }
     }
+    // A few queries over catalogues that fit registers: two queries per workgroup.
+    p.pair_scan = false;
+    const int forced = g_force_general.load(std::memory_order_relaxed);
+    if (!(without & kNoPair) && B >= 2 && m >= 4 && p.vec && !generic && !(forced & 1) &&
+        ((forced & 256) || pair_pays(p, N, B, m, K))) {
+        const long long pairs = (B + 1) / 2, per = (long long)kThreads * pair_max_units(row);
+        const long long least = (units + per - 1) / per, thin = (units + kThreads - 1) / kThreads;
+        const size_t lds = pair_table_bytes(m, b, cw) + 2 * sizeof(MidSelectLds<kThreads>);
+        if (least <= kAssumedCUs && lds <= kMaxLdsBytes) {
+            // as many workgroups as fill the chip once to four times: a workgroup's share takes 5 us beside its lookups, lists 3 us to fold
+            long long nb = 0;
+            double best_us = 0.0;
+            for (int fill = 0; fill <= 4; ++fill) {
+                long long c = fill == 0 ? least : (long long)kAssumedCUs * fill / pairs;
+                c = c < least ? least : c > thin ? thin : c > kAssumedCUs ? kAssumedCUs : c;
+                const double us = (double)((pairs * c + kAssumedCUs - 1) / kAssumedCUs) * (5.0 + lookups / (double)c / kPairLookupsPerUs) + (c > 1 ? 3.0 : 0.0);
+                if (nb == 0 || us < best_us) { best_us = us; nb = c; }
+            }
+            p.pair_scan = (forced & 256) || K <= 128 || B <= kAssumedCUs || nb <= cw;
+            if (p.pair_scan) {
+                p.tiled = p.short_scan = p.long_scan = false;
+                p.glut = false;
+                p.nblk = (int)nb;
+                p.copies = 1;
+                p.big = false;
+                p.short_units = (int)((units + kThreads * nb - 1) / (kThreads * nb));
+                p.scan_dyn_lds = p.scan_lds = lds;
+            }
+        }
+    }
     p.filter = false;
-    if (!(without & kNoFilter)) {
+    if (!(without & kNoFilter) && !(p.pair_scan && !(forced & (16 | 128)) && ((forced & 256) || pair_beats_bounds(N, B, m, K, cw)))) {
         ScanPlan f = p;
         plan_filter(f, N, B, m, K, generic, cw, b);
         // (the whole batch's tables at most 32 KB per result and 1 MB: a single result of each query is not worth larger ones)
@@ -518,7 +576,7 @@ void plan_filter(ScanPlan& p, long long N, int B, int m, int K, bool subset, int
         if (fill == 1 || us < best_us) { best_us = us; nb = cand; }
     }
     p.filter = true;
-    p.tiled = p.short_scan = p.short_subset = p.long_scan = false;
+    p.tiled = p.short_scan = p.pair_scan = p.short_subset = p.long_scan = false;
     p.f_words = words;
     p.f_w16 = w16;
     p.f_queries = queries;
@@ -580,7 +638,7 @@ size_t workspace_bytes(const ScanPlan& p, int B, int K) {
 // Lists that do not fit `bytes`: up to a quarter fewer item blocks per query, where the kernel takes any grid.  (The scan gets longer
 // by that much at most; coarser grids are left to the caller, who can pass a workspace.)
 void coarsen_to_fit(ScanPlan& p, int B, int K, size_t bytes) {
-    if (p.filter || p.short_scan || p.long_scan || workspace_bytes(p, B, K) <= bytes) return;
+    if (p.filter || p.short_scan || p.pair_scan || p.long_scan || workspace_bytes(p, B, K) <= bytes) return;
     const long long most = (long long)(bytes / ((size_t)B * K * sizeof(uint64_t)));
     if (most >= 1 && 4 * most >= 3LL * p.nblk) {
         p.nblk = (int)most;
@@ -783,6 +841,47 @@ hipError_t launch_short16_m(const ScanPlan& p, const ScanArgs& a, int B, hipStre
     }
 }
 
+template <int M, int U, int CW>
+hipError_t launch_pair_units(const ScanPlan& p, const ScanArgs& a, int B, hipStream_t st) {
+    if constexpr (pair_has(U, M * CW)) {
+        hipError_t e = allow_lds(scan_pair_kernel<M, U, kThreads, CW>, p.scan_dyn_lds);
+        if (e != hipSuccess) return e;
+        return launch(scan_pair_kernel<M, U, kThreads, CW>, dim3(p.nblk, (B + 1) / 2), kThreads, p.scan_dyn_lds, st, a.codes, a.S, out_of(a), scores_of(a), (uint32_t)a.N, a.b, B, a.K);
+    } else {
+        return hipErrorInvalidValue;                         // (the plan never asks for it)
+    }
+}
+template <int M, int CW>
+hipError_t launch_pair_m(const ScanPlan& p, const ScanArgs& a, int B, hipStream_t st) {
+    switch (pair_instance(p.short_units, pair_held_units(M * CW))) {
+        case 1: return launch_pair_units<M, 1, CW>(p, a, B, st);
+        case 2: return launch_pair_units<M, 2, CW>(p, a, B, st);
+        case 3: return launch_pair_units<M, 3, CW>(p, a, B, st);
+        case 4: return launch_pair_units<M, 4, CW>(p, a, B, st);
+        case 5: return launch_pair_units<M, 5, CW>(p, a, B, st);
+        case 6: return launch_pair_units<M, 6, CW>(p, a, B, st);
+        case 7: return launch_pair_units<M, 7, CW>(p, a, B, st);
+        case 8: return launch_pair_units<M, 8, CW>(p, a, B, st);
+        case 12: return launch_pair_units<M, 12, CW>(p, a, B, st);
+        case 16: return launch_pair_units<M, 16, CW>(p, a, B, st);
+        case 20: return launch_pair_units<M, 20, CW>(p, a, B, st);
+        case 24: return launch_pair_units<M, 24, CW>(p, a, B, st);
+        case 32: return launch_pair_units<M, 32, CW>(p, a, B, st);
+        case 40: return launch_pair_units<M, 40, CW>(p, a, B, st);
+        default: return hipErrorInvalidValue;
+    }
+}
+hipError_t launch_pair(const ScanPlan& p, const ScanArgs& a, int B, int m, int cw, hipStream_t st) {
+    if (cw == 2) return m == 4 ? launch_pair_m<4, 2>(p, a, B, st) : m == 8 ? launch_pair_m<8, 2>(p, a, B, st) : launch_pair_m<16, 2>(p, a, B, st);
+    switch (m) {
+        case 4: return launch_pair_m<4, 1>(p, a, B, st);
+        case 8: return launch_pair_m<8, 1>(p, a, B, st);
+        case 16: return launch_pair_m<16, 1>(p, a, B, st);
+        case 32: return launch_pair_m<32, 1>(p, a, B, st);
+        default: return launch_pair_m<64, 1>(p, a, B, st);
+    }
+}
+
 template <int M>
 hipError_t launch_subset_m(const ScanPlan& p, const ScanArgs& a, int B, hipStream_t st) {
     auto go = [&](auto kernel) {
@@ -921,6 +1020,10 @@ int enqueue_scan(const ScanPlan& p, const uint8_t* codes, const float* S, long l
     if (p.short_scan) {
         if (stamps != nullptr && m != 8) return PQ_ERR_UNSUPPORTED;
         return record_hip(launch_short(p, a, B, m, st));
+    }
+    if (p.pair_scan) {
+        if (stamps != nullptr) return PQ_ERR_UNSUPPORTED;
+        return record_hip(launch_pair(p, a, B, m, cw, st));
     }
     if (p.long_scan) {
         if (stamps != nullptr) return PQ_ERR_UNSUPPORTED;
@@ -1153,7 +1256,10 @@ int pq_score_topk_static(const uint8_t* codes, const float* S, long long N, int 
     int rc = check_topk_shape(N, B, m, b, K, 1);
     if (rc != PQ_OK) return rc;
     ScanPlan p = make_plan(N, B, m, K);
-    if (p.filter && workspace_bytes(p, B, K) > kStaticScratchBytes) p = make_plan(N, B, m, K, false, 1, kLutStride, kNoFilter);
+    for (int without = 0; (p.pair_scan || p.filter) && workspace_bytes(p, B, K) > kStaticScratchBytes;) {
+        without |= p.pair_scan ? kNoPair : kNoFilter;
+        p = make_plan(N, B, m, K, false, 1, kLutStride, without);
+    }
     coarsen_to_fit(p, B, K, kStaticScratchBytes);
     if (p.scan_lds > kMaxLdsBytes || p.fold_lds > kMaxLdsBytes) return PQ_ERR_UNSUPPORTED;
     if (((uintptr_t)codes & 15) || ((uintptr_t)S & 3) || ((uintptr_t)out_ids & 3) || ((uintptr_t)out_scores & 3))
@@ -1212,7 +1318,7 @@ int pq_score_topk_profile(const uint8_t* codes, const float* S, long long N, int
 }
 
 int pq_measure_force_general(int mask) {
-    return g_force_general.exchange(mask & 255, std::memory_order_relaxed);
+    return g_force_general.exchange(mask & 511, std::memory_order_relaxed);
 }
 
 int pq_measure_plan(long long N, int B, int m, int b, int K, int kind, int* plan) {
@@ -1224,10 +1330,10 @@ int pq_measure_plan(long long N, int B, int m, int b, int K, int kind, int* plan
     const ScanPlan p = kind == PQ_PLAN_LIST ? make_plan(N, B, m, K, true) : kind == PQ_PLAN_WIDE ? make_plan(N, B, m, K, false, 2, b) : make_plan(N, B, m, K);
     if (p.scan_lds > kMaxLdsBytes || p.fold_lds > kMaxLdsBytes) return PQ_ERR_UNSUPPORTED;
     for (int i = 0; i < PQ_PLAN_FIELDS; ++i) plan[i] = 0;
-    plan[PQ_PLAN_KERNEL] = p.filter ? PQ_KERNEL_BOUNDS : p.tiled ? PQ_KERNEL_BATCHED : p.short_scan ? PQ_KERNEL_SHORT : p.long_scan ? PQ_KERNEL_LONG
+    plan[PQ_PLAN_KERNEL] = p.filter ? PQ_KERNEL_BOUNDS : p.pair_scan ? PQ_KERNEL_PAIRS : p.tiled ? PQ_KERNEL_BATCHED : p.short_scan ? PQ_KERNEL_SHORT : p.long_scan ? PQ_KERNEL_LONG
                            : p.short_subset ? PQ_KERNEL_SHORT_LIST : PQ_KERNEL_GENERAL;
     plan[PQ_PLAN_GROUPS] = p.nblk;
-    plan[PQ_PLAN_QUERIES] = p.filter ? p.f_queries : p.tiled ? kQ : 1;
+    plan[PQ_PLAN_QUERIES] = p.filter ? p.f_queries : p.tiled ? kQ : p.pair_scan ? 2 : 1;
     if (p.filter) {
         plan[PQ_PLAN_FIELD_BITS] = p.f_w16 ? 16 : 8;
         plan[PQ_PLAN_SHARED] = p.f_share;
@@ -1250,9 +1356,9 @@ int pq_measure_step_stamps(const float* queries, const float* centroids, const u
     static_assert(PQ_STAMP_SLOTS == kStampSlots, "header and kernels agree on the record size");
     // (the scan in segments has no measurement instance, that by upper bounds those of the named workloads: otherwise the kernels
     // that would run without them)
-    ScanPlan p = make_plan(N, B, m, K, false, 1, kLutStride, kNoLong);
+    ScanPlan p = make_plan(N, B, m, K, false, 1, kLutStride, kNoLong | kNoPair);
     if (p.filter && (p.f_w16 || p.f_words != 4 || !(m == 8 || (m == 16 && p.f_lanes == 1))))
-        p = make_plan(N, B, m, K, false, 1, kLutStride, kNoLong | kNoFilter);
+        p = make_plan(N, B, m, K, false, 1, kLutStride, kNoLong | kNoPair | kNoFilter);
     if (workspace_bytes_given < workspace_bytes(p, B, K)) return PQ_ERR_WORKSPACE;
     if (!(p.filter || p.tiled || m == 8))
         return PQ_ERR_UNSUPPORTED;                             // (scan kernels with a measurement instance)

@@ -1,7 +1,7 @@
 // Eq. 5 + TopK for batches (filter_prepare_kernel, scan_filter_kernel): a scan of small-integer upper bounds finds the few
 // items that can matter, and only those are scored exactly.
 // Part of kernels.hpp, which includes these parts inside namespace pqk in this order:
-// common.hpp, subitem_scores.hpp, topk_parts.hpp, select_small.hpp, scan_single.hpp, scan_short.hpp, scan_long.hpp, scan_subset.hpp,
+// common.hpp, subitem_scores.hpp, topk_parts.hpp, select_small.hpp, scan_single.hpp, scan_short.hpp, scan_pair.hpp, scan_long.hpp, scan_subset.hpp,
 // scan_batched.hpp, scan_filter.hpp, fold.hpp, comparison.hpp.
 //
 // What bounds a batch is the LDS: random 16-byte gathers return 5 lane reads per clock and CU whatever they hold.  With

@@ -1,6 +1,6 @@
 // TopK for small K straight from registers: the selection shared by the short catalogue scan and the small fold.
 // Part of kernels.hpp, which includes these parts inside namespace pqk in this order:
-// common.hpp, subitem_scores.hpp, topk_parts.hpp, select_small.hpp, scan_single.hpp, scan_short.hpp, scan_long.hpp, scan_subset.hpp,
+// common.hpp, subitem_scores.hpp, topk_parts.hpp, select_small.hpp, scan_single.hpp, scan_short.hpp, scan_pair.hpp, scan_long.hpp, scan_subset.hpp,
 // scan_batched.hpp, scan_filter.hpp, fold.hpp, comparison.hpp.
 //
 // These kernels run for a few microseconds with two to four waves per SIMD, so a wave's time is its instruction count
@@ -230,10 +230,11 @@ __device__ __forceinline__ void mid_select_clear(MidSelectLds<NT>& L, int tid) {
 // candidates are ordered.  (1.28M items, one user: K = 100 18.4 -> 16.6 us per step, K = 31 18.0 -> 14.9; from K = 13 on it
 // beats the waves' own floors, which let eight times K pass.)
 // More candidates than the array holds (heavy ties): the exact K-th key is found bit by bit first.
-template <int NT, int R, bool STAMP = false, typename IdOf, typename Emit>
-__device__ __forceinline__ void select_mid_k(const float (&sc)[R], IdOf&& id_of, int K, MidSelectLds<NT>& L, int tid, Emit&& emit,
-                                             uint64_t* rec = nullptr) {
-    constexpr int NW = NT / kWave;
+// Between its barriers: mid_range() the threads' best scores and their range, mid_count() the histogram, mid_collect() the
+// candidates, mid_order() (with barriers of its own) the candidates in order.
+struct MidBest { float best, other, lo, hi, scale; };
+template <int NT, int R>
+__device__ __forceinline__ MidBest mid_range(const float (&sc)[R], int K, MidSelectLds<NT>& L, int tid) {
     const int lane = tid & (kWave - 1), wave = tid / kWave;
     const float ninf = -__builtin_inff();
     float best = ninf, other = ninf;
@@ -247,16 +248,25 @@ __device__ __forceinline__ void select_mid_k(const float (&sc)[R], IdOf&& id_of,
     float mx = fmaxf(best, other), mn = fminf(best > ninf ? best : -ninf, other > ninf ? other : -ninf);
     wave_minmax(mn, mx);
     if (lane == 0) { L.wave_min[wave] = mn; L.wave_max[wave] = mx; }
-    __syncthreads();
-    float lo = L.wave_min[0], hi = L.wave_max[0];
+    return {best, other, 0.0f, 0.0f, 0.0f};
+}
+template <int NT>
+__device__ __forceinline__ void mid_count(MidBest& t, int K, MidSelectLds<NT>& L) {
+    constexpr int NW = NT / kWave;
+    const float ninf = -__builtin_inff();
+    t.lo = L.wave_min[0]; t.hi = L.wave_max[0];
 #pragma unroll
-    for (int w = 1; w < NW; ++w) { lo = fminf(lo, L.wave_min[w]); hi = fmaxf(hi, L.wave_max[w]); }
-    float scale = hi > lo ? (float)kMidBins / (hi - lo) : 0.0f;
-    if (!(scale > 0.0f) || scale > 3.0e38f) scale = 0.0f;
-    if (best > ninf) atomicAdd(&L.hist[bucket_of<kMidBins>(best, lo, scale)], 1u);
-    if (both && other > ninf) atomicAdd(&L.hist[bucket_of<kMidBins>(other, lo, scale)], 1u);
-    __syncthreads();
-    const float f = floor_of_hist<kMidBins>(L.hist, K, lo, scale, lane);   // (every wave for itself)
+    for (int w = 1; w < NW; ++w) { t.lo = fminf(t.lo, L.wave_min[w]); t.hi = fmaxf(t.hi, L.wave_max[w]); }
+    t.scale = t.hi > t.lo ? (float)kMidBins / (t.hi - t.lo) : 0.0f;
+    if (!(t.scale > 0.0f) || t.scale > 3.0e38f) t.scale = 0.0f;
+    if (t.best > ninf) atomicAdd(&L.hist[bucket_of<kMidBins>(t.best, t.lo, t.scale)], 1u);
+    if (K > NT / 2 && t.other > ninf) atomicAdd(&L.hist[bucket_of<kMidBins>(t.other, t.lo, t.scale)], 1u);
+}
+// returns the floor
+template <int NT, int R, typename IdOf>
+__device__ __forceinline__ float mid_collect(const float (&sc)[R], IdOf&& id_of, const MidBest& t, int K, MidSelectLds<NT>& L, int tid) {
+    const int lane = tid & (kWave - 1);
+    const float f = floor_of_hist<kMidBins>(L.hist, K, t.lo, t.scale, lane);   // (every wave for itself)
     int total = 0;
 #pragma unroll
     for (int i = 0; i < R; ++i) total += __popcll(__ballot(sc[i] >= f));
@@ -275,8 +285,13 @@ __device__ __forceinline__ void select_mid_k(const float (&sc)[R], IdOf&& id_of,
             at += __popcll(mask);
         }
     }
-    stamp<STAMP>(rec, kStampOffered, lane);
-    __syncthreads();
+    return f;
+}
+template <int NT, int R, typename IdOf, typename Emit>
+__device__ __forceinline__ void mid_order(const float (&sc)[R], IdOf&& id_of, float f, float hi, int K, MidSelectLds<NT>& L, int tid, Emit&& emit) {
+    constexpr int NW = NT / kWave;
+    const int lane = tid & (kWave - 1), wave = tid / kWave;
+    const float ninf = -__builtin_inff();
     int n = L.ncand;
     if (n > kMidCand) {
         // the K-th best key: the largest that K keys reach (K keys exist: there are more than kMidCand)
@@ -315,11 +330,11 @@ __device__ __forceinline__ void select_mid_k(const float (&sc)[R], IdOf&& id_of,
         rank_emit<NT>(L.cand, n, K, tid, emit);
     } else {
         // by buckets over the candidates' own range (from the floor up, where there is one)
-        lo = f;
+        float lo = f;
         if (!(f > ninf)) {
-            mn = -ninf;
+            float mn = -ninf;
             for (int t = tid; t < n; t += NT) mn = fminf(mn, score_of_key(L.cand[t]));
-            mx = mn;
+            float mx = mn;
             wave_minmax(mn, mx);
             if (lane == 0) L.wave_min[wave] = mn;
             __syncthreads();
@@ -327,7 +342,7 @@ __device__ __forceinline__ void select_mid_k(const float (&sc)[R], IdOf&& id_of,
 #pragma unroll
             for (int w = 1; w < NW; ++w) lo = fminf(lo, L.wave_min[w]);
         }
-        scale = hi > lo ? (float)kBins / (hi - lo) : 0.0f;
+        float scale = hi > lo ? (float)kBins / (hi - lo) : 0.0f;
         if (!(scale > 0.0f) || scale > 3.0e38f) scale = 0.0f;
         if (!bucket_sort<NT, (kMidCand + NT - 1) / NT>(L.cand, n, lo, scale, L.hist, tid)) {
             // (too many in one bucket: by counting, from registers to their places)
@@ -347,10 +362,47 @@ __device__ __forceinline__ void select_mid_k(const float (&sc)[R], IdOf&& id_of,
             for (int r = 0; r < (kMidCand + NT - 1) / NT; ++r)
                 if (mine[r] != 0ull && rank[r] < K) emit(rank[r], mine[r]);
             for (int t = n + tid; t < K; t += NT) emit(t, 0ull);
-            stamp<STAMP>(rec, kStampSelected, lane);
             return;
         }
         for (int t = tid; t < K; t += NT) emit(t, t < n ? L.cand[t] : 0ull);
     }
+}
+template <int NT, int R, bool STAMP = false, typename IdOf, typename Emit>
+__device__ __forceinline__ void select_mid_k(const float (&sc)[R], IdOf&& id_of, int K, MidSelectLds<NT>& L, int tid, Emit&& emit,
+                                             uint64_t* rec = nullptr) {
+    const int lane = tid & (kWave - 1);
+    MidBest t = mid_range<NT>(sc, K, L, tid);
+    __syncthreads();
+    mid_count<NT>(t, K, L);
+    __syncthreads();
+    const float f = mid_collect<NT>(sc, id_of, t, K, L, tid);
+    stamp<STAMP>(rec, kStampOffered, lane);
+    __syncthreads();
+    mid_order<NT>(sc, id_of, f, t.hi, K, L, tid, emit);
     stamp<STAMP>(rec, kStampSelected, lane);
+}
+// The same for two queries' scores of the same items, with one set of barriers up to the candidates; few candidates are ranked by
+// half of the threads for each query.  (For K <= 12 too: the waves' own floors of select_small_k() let twice the candidates through,
+// more than its array holds: 1.28M items, two-byte sub-ids, four queries: 20.9 us per step, with this 14.9.)  emit(h, rank, key): of query h.
+template <int NT, int R, typename IdOf, typename Emit>
+__device__ __forceinline__ void select_mid_k_pair(const float (&sc)[2][R], IdOf&& id_of, int K, MidSelectLds<NT> (&L)[2], int tid, Emit&& emit) {
+    MidBest t[2] = {mid_range<NT>(sc[0], K, L[0], tid), mid_range<NT>(sc[1], K, L[1], tid)};
+    __syncthreads();
+    mid_count<NT>(t[0], K, L[0]);
+    mid_count<NT>(t[1], K, L[1]);
+    __syncthreads();
+    const float f0 = mid_collect<NT>(sc[0], id_of, t[0], K, L[0], tid);
+    const float f1 = mid_collect<NT>(sc[1], id_of, t[1], K, L[1], tid);
+    __syncthreads();
+    const int n0 = L[0].ncand, n1 = L[1].ncand;
+    if (n0 <= kRankByCount && n1 <= kRankByCount) {
+        const int h = __builtin_amdgcn_readfirstlane(tid >= NT / 2 ? 1 : 0), me = tid - h * (NT / 2);
+        const int n = h != 0 ? n1 : n0, n8 = (n + 7) & ~7;
+        if (me < n8 - n) L[h].cand[n + me] = 0ull;
+        __syncthreads();
+        rank_emit<NT / 2>(L[h].cand, n, K, me, [&](int rank, uint64_t key) { emit(h, rank, key); });
+        return;
+    }
+    mid_order<NT>(sc[0], id_of, f0, t[0].hi, K, L[0], tid, [&](int rank, uint64_t key) { emit(0, rank, key); });
+    mid_order<NT>(sc[1], id_of, f1, t[1].hi, K, L[1], tid, [&](int rank, uint64_t key) { emit(1, rank, key); });
 }

@@ -775,6 +775,63 @@ def test_short_scans_side_by_side(pq, oracle, B):
         assert_same_topk(pq, oracle, G, tables(N + B, B, m, 256), K, "short side by side")
 
 
+@pytest.mark.parametrize("m,wide,units", [(4, 0, (1, 5, 8)), (8, 0, (1, 3, 8, 9, 20)), (16, 0, (2, 7, 16, 33, 40)), (32, 0, (1, 4, 5, 24, 40)), (64, 0, (1, 2, 3, 17, 24)),
+                                          (4, 1, (2, 8, 13, 20)), (8, 1, (1, 6, 20, 32, 40)), (16, 1, (4, 5, 21, 40))])
+def test_two_queries_per_workgroup_every_share(pq, oracle, m, wide, units):
+    # one workgroup per pair of 511 queries (the last one alone), shares on either side of the kernel's instances, the last of them
+    # ragged; few and many results
+    B, b = 511, 300 if wide else 256
+    some = [0, 1, 2, 255, 509, 510]
+    for u in units:
+        for K in (7, 100):
+            N = max((u * 512 - 37) * 16 // (m * (2 if wide else 1)) if m * (2 if wide else 1) <= 16 else u * 512 - 37, K) + 1
+            G = (W.codes_uniform_u16 if wide else W.codes_uniform)(N, m, b, seed=u)
+            S = tables(u + K, B, m, b)
+            prev = pq.pq_measure_force_general(256)
+            try:
+                assert pq.pq_measure_plan("scan16" if wide else "scan", N, B, m, b, K)["kernel"] == "pairs"
+                print(f"case pairs m={m} wide={wide} units={u} N={N} K={K}", flush=True)
+                ids, sc = (pq.pq_score_topk_u16 if wide else pq.pq_score_topk)(dev(G), dev(S), K)
+            finally:
+                pq.pq_measure_force_general(prev)
+            rid, rsc = (oracle.score_topk_u16 if wide else oracle.score_topk)(G, S[some], K)
+            assert np.array_equal(ids.cpu().numpy()[some], rid)
+            assert np.array_equal(sc.cpu().numpy()[some].view(np.uint32), rsc.view(np.uint32))
+
+
+@pytest.mark.parametrize("kind", ["random", "coarse", "equal", "infinite", "short alphabet", "misaligned"])
+@pytest.mark.parametrize("N,m,b,B,K", [(40_001, 8, 256, 3, 10), (3_003, 4, 256, 2, 512), (50_000, 16, 256, 5, 200), (9_001, 64, 256, 2, 64), (20_003, 4, 701, 6, 257),
+                                       (30_001, 8, 1024, 4, 12), (17, 4, 300, 7, 17), (5_000, 32, 256, 2, 1)])
+def test_two_queries_per_workgroup_spread(pq, oracle, kind, N, m, b, B, K):
+    # pairs over many workgroups: heavy ties (more candidates than the array holds: the K-th key is found bit by bit, for each query by
+    # itself), masked entries, rows of fewer than 256 sub-ids, tables at a 4-byte boundary, items after the last whole code vector
+    import torch
+    wide = b > 256
+    if kind == "short alphabet":
+        b = 77 if not wide else b - 1
+    G = (W.codes_uniform_u16 if wide else W.codes_uniform)(N, m, b, seed=N)
+    S = tables(N + K, B, m, b)
+    if kind == "coarse":
+        S = np.round(S).astype(np.float32)
+    elif kind == "equal":
+        S[1:] = 0.25                                           # (one ordinary query beside one of ties)
+    elif kind == "infinite":
+        S[:, 0, ::3] = -np.inf
+    buf = torch.empty(S.size + 1, dtype=torch.float32, device="cuda")
+    off = 1 if kind == "misaligned" else 0
+    Sd = buf[off:off + S.size].copy_(torch.from_numpy(S.reshape(-1))).view(S.shape)
+    prev = pq.pq_measure_force_general(256)
+    try:
+        assert pq.pq_measure_plan("scan16" if wide else "scan", N, B, m, b, K)["kernel"] == "pairs"
+        print(f"case pairs {kind} N={N} m={m} b={b} B={B} K={K}", flush=True)
+        ids, sc = (pq.pq_score_topk_u16 if wide else pq.pq_score_topk)(dev(G), Sd, K)
+    finally:
+        pq.pq_measure_force_general(prev)
+    rid, rsc = (oracle.score_topk_u16 if wide else oracle.score_topk)(G, S, K)
+    assert np.array_equal(ids.cpu().numpy(), rid)
+    assert np.array_equal(sc.cpu().numpy().view(np.uint32), rsc.view(np.uint32))
+
+
 def test_small_fold_many_lists(pq, oracle):
     # the small-K fold with both of its instances: up to 3072 and up to 6144 keys per query (256 lists of K = 10, 24; with
     # K = 28, 31 the 256 lists go to the general fold: a third instance of 16 keys per thread was slower than it),
