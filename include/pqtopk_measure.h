@@ -122,7 +122,7 @@ int pq_measure_force_general(int mask);
 #define PQ_PLAN_GROUPS      1   /* workgroups that share a query */
 #define PQ_PLAN_QUERIES     2   /* queries of a workgroup */
 #define PQ_PLAN_FIELD_BITS  3   /* scans by bounds: 8 or 16 */
-#define PQ_PLAN_FINE        4   /* ... finer counts beside 8-bit fields: none, 0 */
+#define PQ_PLAN_FINE        4   /* ... 16-bit counts beside 8-bit fields */
 #define PQ_PLAN_SHARED      5   /* ... a query's workgroups share their floors */
 #define PQ_PLAN_PARTS       6   /* ... parts of the sample ... */
 #define PQ_PLAN_ROUNDS      7   /* ... and the rounds of each */

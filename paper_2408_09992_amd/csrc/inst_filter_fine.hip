@@ -1,0 +1,6 @@
+// Instantiates one group of the batches' filter kernels (see the instance lists in kernels.hpp).
+#define PQ_INSTANCE_TU
+#include "kernels.hpp"
+namespace pqk {
+PQ_FILTER_INSTANCES_FINE(PQ_FILTER_DEFINE9)
+}

@@ -126,6 +126,8 @@ namespace pqk {
 // measurement instances (wall-clock stamps per wave) of those the named batch workloads run
 #define PQ_FILTER_STAMPED(X, M, G) X(M, 1, 4, false, false, G, false, true) X(M, 1, 4, false, false, G, true, true)
 #define PQ_FILTER_INSTANCES_STAMPED(X) PQ_FILTER_STAMPED(X, 8, 1) PQ_FILTER_STAMPED(X, 8, 2) PQ_FILTER_STAMPED(X, 16, 1)
+// ... and those with 16-bit counts beside the bytes
+#define PQ_FILTER_INSTANCES_FINE(X) X(16, 1, 2, false, false, 1, false, false, true) X(16, 1, 2, false, false, 1, true, false, true)
 // the batched kernel
 #define PQ_TILED_INSTANCES(X) X(8, false) X(16, false) X(8, true) X(16, true)
 
@@ -147,6 +149,8 @@ namespace pqk {
 #define PQ_FILTER_EXTERN(M, CW, W, W16, SUB, G, SH) extern PQ_FILTER_DEFINE(M, CW, W, W16, SUB, G, SH)
 #define PQ_FILTER_DEFINE8(M, CW, W, W16, SUB, G, SH, ST) template __global__ void scan_filter_kernel<M, CW, W, W16, SUB, G, SH, ST>(FilterArgs);
 #define PQ_FILTER_EXTERN8(M, CW, W, W16, SUB, G, SH, ST) extern PQ_FILTER_DEFINE8(M, CW, W, W16, SUB, G, SH, ST)
+#define PQ_FILTER_DEFINE9(M, CW, W, W16, SUB, G, SH, ST, FI) template __global__ void scan_filter_kernel<M, CW, W, W16, SUB, G, SH, ST, FI>(FilterArgs);
+#define PQ_FILTER_EXTERN9(M, CW, W, W16, SUB, G, SH, ST, FI) extern PQ_FILTER_DEFINE9(M, CW, W, W16, SUB, G, SH, ST, FI)
 #define PQ_FILTERP_DEFINE(M, CW, SUB) template __global__ void filter_prepare_kernel<M, CW, SUB, kFilterThreads>(FilterArgs); \
     template __global__ void filter_prepare_kernel<M, CW, SUB, kThreads>(FilterArgs);
 #define PQ_FILTERP_EXTERN(M, CW, SUB) extern template __global__ void filter_prepare_kernel<M, CW, SUB, kFilterThreads>(FilterArgs); \
@@ -174,6 +178,7 @@ PQ_PAIR_INSTANCES_B(PQ_PAIR_EXTERN)
 PQ_PAIR_INSTANCES_C(PQ_PAIR_EXTERN)
 PQ_TILED_INSTANCES(PQ_TILED_EXTERN)
 PQ_FILTER_INSTANCES_STAMPED(PQ_FILTER_EXTERN8)
+PQ_FILTER_INSTANCES_FINE(PQ_FILTER_EXTERN9)
 PQ_FILTER_INSTANCES_A(PQ_FILTER_EXTERN, PQ_FILTERP_EXTERN)
 PQ_FILTER_INSTANCES_A8(PQ_FILTER_EXTERN, PQ_FILTERP_EXTERN)
 PQ_FILTER_INSTANCES_B(PQ_FILTER_EXTERN, PQ_FILTERP_EXTERN)

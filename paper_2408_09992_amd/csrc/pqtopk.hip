@@ -105,6 +105,7 @@ struct ScanPlan {
     bool filter;       // filter_prepare_kernel + scan_filter_kernel: a batch scanned by integer upper bounds
     int f_words;       // ... 32-bit words of a table entry
     bool f_w16;        // ... 16-bit fields (8-bit otherwise)
+    bool f_fine;       // ... 16-bit counts beside 8-bit fields
     int f_queries;     // ... queries per workgroup
     int f_cap;         // ... keys of a query's list
     int f_lanes;       // ... lanes that share an item (1 or 2)
@@ -431,7 +432,7 @@ ScanPlan make_plan(long long N, int B, int m, int K, bool generic = false, int c
                 const double us = (double)((pairs * c + kAssumedCUs - 1) / kAssumedCUs) * (5.0 + lookups / (double)c / kPairLookupsPerUs) + (c > 1 ? 3.0 : 0.0);
                 if (nb == 0 || us < best_us) { best_us = us; nb = c; }
             }
-            p.pair_scan = (forced & 256) || K <= 128 || B <= kAssumedCUs || nb <= cw;
+            p.pair_scan = (forced & 256) || B <= kAssumedCUs || nb <= cw || K <= (m <= 16 && B > 2 * kAssumedCUs && nb > 2 ? 16 : 128);
             if (p.pair_scan) {
                 p.tiled = p.short_scan = p.long_scan = false;
                 p.glut = false;
@@ -497,6 +498,17 @@ long long filter_min_items_per_result(long long N, int m, int K, int B, bool sub
     return B <= 256 ? (K > 128 ? 800 : 500) : K > 128 ? 1300 : K > 64 ? 800 : 500;
 }
 
+// Where 16-bit counts lie in LDS beside the bytes (m = 16; eight queries to a workgroup instead of sixteen): where many items are scored
+// exactly for each that is streamed.  Calls with sixteen queries and bytes alone (K > 32: or 16-bit fields, or by pairs) and with eight and
+// both (us): 500 queries, 100,000 items, K = 2 62 and 64, 6 83 and 61, 24 127 and 71, 60 144 and 89; 250,000, K = 12 128 and 110; 260
+// queries, 50,000, K = 24 46 and 48, 200,000 92 and 65, 600,000, K = 6 95 and 97, 12 106 and 101, 60 169 and 116; 130, 600,000, K = 60 96 and 78,
+// 250,000 62 and 60; 90, 3M, K = 100 180 and 152, 1M, K = 20 67 and 80, 40 75 and 74; 40, 1M, K = 100 53 and 54.  Small catalogues of enough
+// items per result stay with 16-bit fields: 500, 100,000, K = 40 78 and 73, 200 queries 47 and 49.
+bool filter_fine_pays(long long N, int m, int K, int B, bool subset, int cw) {
+    return m == 16 && cw == 1 && !subset && K >= 5 && K <= 256 && N < 80000LL * K && !(K > 32 && N >= 2000LL * K && N < 150000) &&
+           (B >= 400 || (N >= 150000 && (B >= 200 || (B > 80 && K > 32))));
+}
+
 // Whether a batch is scanned by upper bounds (scan_filter.hpp), and how.
 size_t workspace_bytes(const ScanPlan& p, int B, int K);
 void plan_filter(ScanPlan& p, long long N, int B, int m, int K, bool subset, int cw, int b) {
@@ -513,13 +525,18 @@ void plan_filter(ScanPlan& p, long long N, int B, int m, int K, bool subset, int
     bool w16 = m == 64;
     if (m == 32) w16 = N < (long long)K * (K > 64 ? 10000 : B > 150 ? 40000 : 13000);
     if (m == 16 && cw == 1) w16 = subset ? K > 32 || (B > 256 && N < 20000LL * K) : K > 32 && B > 128 && N < 8000LL * K;
+    const bool fine = filter_fine_pays(N, m, K, B, subset, cw);
+    if (fine) w16 = false;
     if (!(force & 16) && (B < 2 || (double)B * (double)N * m < filter_min_lookups(m, K, B, subset, cw) || 2 * N < (m >= 32 ? 7 : 16) * entries ||
-                          N < filter_min_items_per_result(N, m, K, B, subset, w16, cw) * K))
+                          N < (fine ? (B > 700 ? 1000 : 450) : filter_min_items_per_result(N, m, K, B, subset, w16, cw)) * K))
         return;
     if (filter_prepare_lds_bytes(entries, m) > kMaxLdsBytes) return;
-    const int fields = w16 ? 2 : 4, stride = (int)(entries / m);
-    int cap = K <= 16 ? 64 : next_pow2(2 * K);
-    if (K > 16 && cap < 128) cap = 128;
+    const int stride = (int)(entries / m);
+    const int fields = w16 ? 2 : 4;
+    // Keys of a query's list: twice K, 128 at least (64 for K = 12: full lists are tidied so often that half a million items, m = 4, 300 queries
+    // take 45 us, with 128 43), but where that does not fit and K is small.
+    const int roomy = 2 * K < 128 ? 128 : next_pow2(2 * K);
+    int cap = roomy;
     // Words of a lane's table entry, lanes that share an item: what reads least of the LDS's time.
     // Pairs of lanes read a third more per clock, but a workgroup has twice the queries to prepare, to look after and to select for, and reads
     // of device memory come in the way of the exact scores': for long scans of few results, where floors are not shared the longest.
@@ -533,13 +550,15 @@ void plan_filter(ScanPlan& p, long long N, int B, int m, int K, bool subset, int
     int words = 0, lanes = 1;
     for (int w = 8; w >= (w16 && m == 16 ? 4 : w16 && m == 32 ? 2 : 1); w >>= 1) {   // (8: four words for each of two lanes)
         const int l = w == 8 ? 2 : 1, each = w == 8 ? 4 : w;
+        if (fine && w != 2) continue;
         if (l == 2 && (w16 || !(pairs || (force & 128)))) continue;
         if ((m >= 32 && l == 2) || (m == 64 && each == 4)) continue;
-        if (filter_lds_bytes(m, stride, each, w16, l, cap) > kMaxLdsBytes) continue;
+        const int c = K <= 16 && filter_lds_bytes(m, stride, each, w16, l, roomy, fine) > kMaxLdsBytes ? 64 : roomy;
+        if (filter_lds_bytes(m, stride, each, w16, l, c, fine) > kMaxLdsBytes) continue;
         const long long tiles = (B + w * fields - 1) / (w * fields);
         const double r = l == 2 ? kGatherPairs : each == 4 ? (filter_far_splits(m, 4, w16, 1) > 0 ? kGather16Far : kGather16) : each == 2 ? kGather8 : kGather4;
         const double cost = (double)tiles * l / r;
-        if (words == 0 || cost < best_cost) { words = each; lanes = l; best_cost = cost; rate = r; }
+        if (words == 0 || cost < best_cost) { words = each; lanes = l; cap = c; best_cost = cost; rate = r; }
         if (l == 2 && (force & 128)) break;
     }
     if (words == 0) return;
@@ -558,7 +577,7 @@ void plan_filter(ScanPlan& p, long long N, int B, int m, int K, bool subset, int
     // batches of a few queries).  K = 100, not shared and shared (us): m = 4, 200 queries, 8M items 236 and 179; m = 8, 3M 193 and 154; m = 16,
     // 3M 427 (16-bit fields) and 275.
     auto shares = [&](long long blocks) {
-        return blocks > 1 && ((blocks <= 16 && rounds / blocks >= 12) || (blocks <= 32 && rounds / blocks >= 32)) && (words == 4 || m >= 32);
+        return blocks > 1 && ((blocks <= 16 && rounds / blocks >= 12) || (blocks <= 32 && rounds / blocks >= 32)) && (words == 4 || m >= 32 || fine);
     };
     long long nb = 1;
     double best_us = 0.0;
@@ -587,11 +606,12 @@ void plan_filter(ScanPlan& p, long long N, int B, int m, int K, bool subset, int
     p.f_prepare = batch >= 2 * kAssumedCUs && 4 * filter_prepare_lds_bytes(entries, m) <= kMaxLdsBytes ? kThreads : kFilterThreads;
     p.f_sample = p.f_prepare * ((subset && row < 16) ? sample_units * 16 / row : sample_units);
     // The sample: n items cost n * m lookups of 4 bytes, and (K / n) of the catalogue then passes the first floor and is
-    // scored from device memory, an eighth as fast: least together at about 5 sqrt(K N).  Where the workgroups of a query
-    // share their floors those rise fast by themselves.
+    // scored from device memory, an eighth as fast: least together at about 5 sqrt(K N), for few results of many queries 8 (300 queries,
+    // 200,000 items, m = 4, K = 12 41 and 29 us; 478, 115,861, m = 8, K = 11 48 and 42; 300, 300,000, K = 26 52 and 56).  Where the workgroups
+    // of a query share their floors those rise fast by themselves.
     p.f_share = shares(nb);
     const long long items_per_round = (long long)p.f_sample * N / units;
-    long long want = (long long)(5.0 * sqrt((double)K * (double)N)) / items_per_round;
+    long long want = (long long)((K <= 16 && B > 128 && !subset && !p.f_share ? 8.0 : 5.0) * sqrt((double)K * (double)N)) / items_per_round;
     const long long most_rounds = (nb > 16 ? 4 : K <= 32 ? 1 : m == 4 ? 4 : m == 8 ? 2 : 1) * (kFilterThreads / p.f_prepare);
     if (p.f_share && want > most_rounds) want = most_rounds;
     if (want > N / 8 / items_per_round) want = N / 8 / items_per_round;
@@ -612,7 +632,8 @@ void plan_filter(ScanPlan& p, long long N, int B, int m, int K, bool subset, int
     p.f_far = filter_far_splits(m, words, w16, lanes);
     p.f_pitch = align16((size_t)(m - p.f_far) * stride * (w16 ? sizeof(uint16_t) : sizeof(uint8_t)));
     p.nblk = (int)nb;
-    p.scan_lds = filter_lds_bytes(m, stride, words, w16, lanes, cap);
+    p.f_fine = fine;
+    p.scan_lds = filter_lds_bytes(m, stride, words, w16, lanes, cap, fine);
     // (one-byte sub-ids: the tables are a static array)
     p.scan_dyn_lds = p.scan_lds - (cw == 2 ? 0 : filter_table_bytes(m, stride, words, w16, lanes));
 }
@@ -630,8 +651,9 @@ size_t far_bytes(const ScanPlan& p) {
 }
 size_t query_bytes(const ScanPlan& p) { return p.filter ? ((size_t)p.f_batch * sizeof(FilterQuery) + 255) & ~(size_t)255 : 0; }
 size_t hist_bytes(const ScanPlan& p) { return p.filter ? (size_t)p.f_batch * kFilterBins * sizeof(uint32_t) : 0; }
+size_t fine_bytes(const ScanPlan& p) { return p.filter && p.f_fine ? (size_t)p.f_batch * p.f_entries * sizeof(uint16_t) : 0; }
 size_t workspace_bytes(const ScanPlan& p, int B, int K) {
-    return keys_bytes(p, B, K) + counts_bytes(p) + query_bytes(p) + hist_bytes(p) + far_bytes(p) +
+    return keys_bytes(p, B, K) + counts_bytes(p) + query_bytes(p) + hist_bytes(p) + far_bytes(p) + fine_bytes(p) +
            (p.filter && p.f_parts > 1 ? ((size_t)p.f_batch * p.f_parts * p.f_best * sizeof(float) + 255) & ~(size_t)255 : 0);
 }
 
@@ -927,6 +949,9 @@ hipError_t launch_filter(const ScanPlan& p, const FilterArgs& a, hipStream_t st)
         }
         return hipErrorInvalidValue;                         // (pq_measure_step_stamps() has checked)
     }
+    if constexpr (M == 16 && CW == 1 && !SUB) {
+        if (p.f_fine) return p.f_share ? go(scan_filter_kernel<16, 1, 2, false, false, 1, true, false, true>) : go(scan_filter_kernel<16, 1, 2, false, false, 1, false, false, true>);
+    }
     if constexpr ((M == 16 || M == 32) && CW == 1) {
         if (p.f_w16 && p.f_words == 4) return p.f_share ? go(scan_filter_kernel<M, 1, 4, true, SUB, 1, true>) : go(scan_filter_kernel<M, 1, 4, true, SUB, 1, false>);
     }
@@ -982,7 +1007,8 @@ int enqueue_scan(const ScanPlan& p, const uint8_t* codes, const float* S, long l
         f.far_splits = p.f_far;
         f.tile = p.f_queries;
         f.wide = p.f_w16;
-        f.best = reinterpret_cast<float*>(ws + counts_bytes(p) + query_bytes(p) + hist_bytes(p) + far_bytes(p));
+        f.fine = p.f_fine ? reinterpret_cast<uint16_t*>(ws + counts_bytes(p) + query_bytes(p) + hist_bytes(p) + far_bytes(p)) : nullptr;
+        f.best = reinterpret_cast<float*>(ws + counts_bytes(p) + query_bytes(p) + hist_bytes(p) + far_bytes(p) + fine_bytes(p));
         f.sample = p.f_sample;
         f.rounds = p.f_rounds;
         f.parts = p.f_parts;
@@ -1336,6 +1362,7 @@ int pq_measure_plan(long long N, int B, int m, int b, int K, int kind, int* plan
     plan[PQ_PLAN_QUERIES] = p.filter ? p.f_queries : p.tiled ? kQ : p.pair_scan ? 2 : 1;
     if (p.filter) {
         plan[PQ_PLAN_FIELD_BITS] = p.f_w16 ? 16 : 8;
+        plan[PQ_PLAN_FINE] = p.f_fine;
         plan[PQ_PLAN_SHARED] = p.f_share;
         plan[PQ_PLAN_PARTS] = p.f_parts;
         plan[PQ_PLAN_ROUNDS] = p.f_rounds;
@@ -1357,7 +1384,7 @@ int pq_measure_step_stamps(const float* queries, const float* centroids, const u
     // (the scan in segments has no measurement instance, that by upper bounds those of the named workloads: otherwise the kernels
     // that would run without them)
     ScanPlan p = make_plan(N, B, m, K, false, 1, kLutStride, kNoLong | kNoPair);
-    if (p.filter && (p.f_w16 || p.f_words != 4 || !(m == 8 || (m == 16 && p.f_lanes == 1))))
+    if (p.filter && (p.f_w16 || p.f_fine || p.f_words != 4 || !(m == 8 || (m == 16 && p.f_lanes == 1))))
         p = make_plan(N, B, m, K, false, 1, kLutStride, kNoLong | kNoPair | kNoFilter);
     if (workspace_bytes_given < workspace_bytes(p, B, K)) return PQ_ERR_WORKSPACE;
     if (!(p.filter || p.tiled || m == 8))

@@ -71,6 +71,7 @@ struct FilterArgs {
     uint32_t* hist;             // [B][kFilterBins] exact scores found, by T above the first (cleared by filter_prepare_kernel)
     float* best;                // [B][parts][best_per_part] scores of sample items (parts > 1)
     long long entries;          // of a query's tables: M * 256, or M * b for two-byte sub-ids
+    uint16_t* fine;             // [B][entries] 256ths of a step beside the bytes; nullptr: none
     uint32_t pitch;
     int far_splits, tile;       // splits looked up in device memory (the last ones), queries of a workgroup
     int wide;                   // 16-bit counts
@@ -522,6 +523,21 @@ __global__ __launch_bounds__(NT, M <= 16 ? 8 : 4) void filter_prepare_kernel(Fil
         const float x = ceilf((lut[e] - bases[e / (uint32_t)stride]) * per + up);
         return (uint32_t)fminf(fmaxf(x, 0.0f), 255.0f);
     };
+    if constexpr (M == 16 && CW == 1 && !SUB) {
+        if (a.fine != nullptr) {                              // (two entries per thread and store)
+            uint32_t* const fine = reinterpret_cast<uint32_t*>(a.fine + (size_t)q * a.entries);
+            const float inv256 = nothing ? 0.0f : inv * 256.0f, up16 = nothing ? 0.0f : kFilterUp16;
+            for (uint32_t i = tid; i * 2 < (uint32_t)a.entries; i += NT) {
+                uint32_t word = 0;
+#pragma unroll
+                for (int c = 0; c < 2; ++c) {
+                    const float x = ceilf((lut[i * 2 + c] - bases[(i * 2 + c) / (uint32_t)stride]) * inv256 + up16);
+                    word |= (uint32_t)fminf(fmaxf(x, 0.0f), 65535.0f) << (c * 16);
+                }
+                fine[i] = word;
+            }
+        }
+    }
     const uint32_t here = (uint32_t)(M - a.far_splits) * (uint32_t)stride, there = (uint32_t)a.far_splits * (uint32_t)stride;
     for (uint32_t i = tid; i * 4 < here; i += NT) {
         uint32_t word = 0;
@@ -545,9 +561,10 @@ __host__ __device__ constexpr size_t filter_state_bytes(int queries) {   // ever
 __host__ __device__ constexpr size_t filter_table_bytes(int m, long long stride, int words, bool w16, int lanes) {
     return (size_t)(m - filter_far_splits(m, words, w16, lanes)) * stride * words * 4 * lanes;
 }
-__host__ __device__ constexpr size_t filter_lds_bytes(int m, long long stride, int words, bool w16, int lanes, int cap) {
+// `fine`: 16-bit counts beside the bytes
+__host__ __device__ constexpr size_t filter_lds_bytes(int m, long long stride, int words, bool w16, int lanes, int cap, bool fine = false) {
     const int queries = words * (w16 ? 2 : 4) * lanes;
-    return align16(filter_table_bytes(m, stride, words, w16, lanes)) + (size_t)queries * cap * sizeof(uint64_t) +
+    return align16(filter_table_bytes(m, stride, words, w16, lanes)) + (fine ? (size_t)m * stride * queries * sizeof(uint16_t) : 0) + (size_t)queries * cap * sizeof(uint64_t) +
            (size_t)kFilterWaves * kFilterQueue * sizeof(uint64_t) + align16(filter_state_bytes(queries));
 }
 
@@ -561,7 +578,10 @@ template <> struct FilterWord<4> { typedef uint4 type; };
 // Dynamic LDS: tables (two-byte sub-ids) | lists [QT][cap] | queues [waves][kFilterQueue] | hist [QT][kFilterBins] | thr | state words.
 // SHARE: the workgroups of a query share their floors (a choice at run time would make the loop wait for all of a wave's loads).
 // STAMP: measurement instance that also records wall-clock stamps per wave.
-template <int M, int CW, int W, bool W16, bool SUB, int G, bool SHARE, bool STAMP = false>
+// FINE: 16-bit counts in LDS beside the bytes (one-byte sub-ids): what the bytes let pass is looked up there, nine 2-byte lanes per clock,
+// before it is scored exactly, one lane per clock: of three or four that pass at m = 16, one is left.  Half the queries per LDS read pay
+// for it, see filter_fine_pays() (100,000 items, 520 queries, K = 60: scan and selection 144 -> 89 us).
+template <int M, int CW, int W, bool W16, bool SUB, int G, bool SHARE, bool STAMP = false, bool FINE = false>
 __global__ __launch_bounds__(kFilterThreads) void scan_filter_kernel(FilterArgs a) {
     using Sh = FilterShape<M, CW>;
     using Word = typename FilterWord<W>::type;
@@ -576,6 +596,7 @@ __global__ __launch_bounds__(kFilterThreads) void scan_filter_kernel(FilterArgs 
     constexpr bool AHEAD = V > 0 && Sh::kWords == 4 && NI * V * W <= 16;   // reads of device memory are under way a unit ahead
     constexpr uint32_t TOP = W16 ? 0x80008000u : 0x80808080u;
     static_assert(W16 ? (M >= 16 && G == 1) : (G == 1 || (G == 2 && W == 4 && QT == 32)), "16-bit fields, or pairs of lanes");
+    static_assert(!FINE || (!W16 && G == 1 && CW == 1 && V == 0), "fine counts: beside bytes");
     extern __shared__ __align__(16) unsigned char smem[];
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid / kWave);
     const int half = G == 1 ? 0 : lane & 1, slot = lane / G;  // this lane's part of a row, its place among the wave's items
@@ -587,7 +608,8 @@ __global__ __launch_bounds__(kFilterThreads) void scan_filter_kernel(FilterArgs 
     __shared__ __align__(16) uint32_t tab_static[CW == 1 ? (M - V) * kLutStride * W * G : 4];
     uint32_t* const tab = CW == 1 ? tab_static : reinterpret_cast<uint32_t*>(smem);
     const uint32_t here = (uint32_t)((M - V) * stride);       // entries of a query in LDS
-    uint64_t* const lists = reinterpret_cast<uint64_t*>(smem + (CW == 1 ? 0 : align16((size_t)here * W * G * 4)));
+    uint16_t* const fine = reinterpret_cast<uint16_t*>(smem);                     // FINE: [QT][M * 256]
+    uint64_t* const lists = reinterpret_cast<uint64_t*>(smem + (CW == 1 ? (FINE ? (size_t)QT * M * kLutStride * sizeof(uint16_t) : 0) : align16((size_t)here * W * G * 4)));
     uint64_t* const queue = lists + (size_t)QT * cap + (size_t)wave * kFilterQueue;
     uint32_t* const hist = reinterpret_cast<uint32_t*>(lists + (size_t)QT * cap + (size_t)NW * kFilterQueue);
     uint64_t* const thr = reinterpret_cast<uint64_t*>(hist + QT * kFilterBins);   // a pruned list's K-th best key
@@ -680,6 +702,16 @@ __global__ __launch_bounds__(kFilterThreads) void scan_filter_kernel(FilterArgs 
     };
     uint32_t first_in[QL];
     fetch_counts(tid, first_in);
+    constexpr int kFineRow = M * kLutStride / 8, kFineVecs = FINE ? QT * kFineRow / NT : 1;   // 16-byte pieces of a query's fine counts, of a thread
+    uint4 fine_in[kFineVecs];
+    if constexpr (FINE) {
+        static_assert(QT * kFineRow % NT == 0, "whole pieces");
+#pragma unroll
+        for (int i = 0; i < kFineVecs; ++i) {
+            const int at = i * NT + tid, q = at / kFineRow;
+            fine_in[i] = reinterpret_cast<const uint4*>(a.fine)[(size_t)(q0 + (q < nq ? q : 0)) * kFineRow + at % kFineRow];
+        }
+    }
     FilterQuery my_par[QW];                                   // (a wave per query below, or two queries)
 #pragma unroll
     for (int i = 0; i < QW; ++i) my_par[i] = a.query[q0 + (wave + i * NW < nq ? wave + i * NW : 0)];
@@ -701,6 +733,10 @@ __global__ __launch_bounds__(kFilterThreads) void scan_filter_kernel(FilterArgs 
     }
     for (int i = tid; i < QT * cap; i += NT) lists[i] = 0ull;
     for (int i = tid; i < QT * kFilterBins; i += NT) hist[i] = 0u;
+    if constexpr (FINE) {
+#pragma unroll
+        for (int i = 0; i < kFineVecs; ++i) reinterpret_cast<uint4*>(fine)[i * NT + tid] = fine_in[i];
+    }
     for (uint32_t i = tid; i < pieces; i += NT) {             // entries N_ * (i / G) .. of the queries of lane i % G
         uint32_t in[QL];
         if (i == (uint32_t)tid) {
@@ -932,14 +968,21 @@ __global__ __launch_bounds__(kFilterThreads) void scan_filter_kernel(FilterArgs 
     // `again`: in a query's second scan
     auto process = [&](auto again, int n0, int n) {
         wave_sync();
-        const bool live = lane < n;
+        bool live = lane < n;
         const uint64_t entry = live ? queue[n0 + lane] : 0ull;
         const int q = (int)(entry >> 32);
         const uint32_t item = item_at((uint32_t)entry);
         uint32_t row[P / 4];
         load_row_words<P>(a.codes, item, row);
+        if constexpr (FINE && !decltype(again)::value) {
+            uint32_t sum = 0;
+#pragma unroll
+            for (int k = 0; k < M; ++k) sum += fine[(uint32_t)(q * M + k) * kLutStride + filter_sub_id<M, CW>(row, 0, k)];
+            live = live && sum >= (uint32_t)t_of(q) << 8;
+        }
         const float* Sq = a.S + (size_t)(q0 + q) * M * b;
         float acc = 0.0f;
+        auto score = [&]() {
 #pragma unroll
         for (int k0 = 0; k0 < M; k0 += kAsked) {
             float v[kAsked];
@@ -951,6 +994,8 @@ __global__ __launch_bounds__(kFilterThreads) void scan_filter_kernel(FilterArgs 
 #pragma unroll
             for (int k = 0; k < kAsked; ++k) acc = k0 + k == 0 ? v[0] : acc + v[k];
         }
+        };
+        if (!FINE || live) score();
         const FilterQuery p = par[q];
         const int t = units_of_score(acc, p);
         const uint64_t key = make_key(acc + 0.0f, item);

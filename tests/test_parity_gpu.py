@@ -775,6 +775,30 @@ def test_short_scans_side_by_side(pq, oracle, B):
         assert_same_topk(pq, oracle, G, tables(N + B, B, m, 256), K, "short side by side")
 
 
+@pytest.mark.parametrize("N,B,K", [(50_001, 401, 5), (116_003, 405, 256), (150_000, 200, 30), (151_001, 83, 33), (60_000, 420, 128)])
+@pytest.mark.parametrize("kind", ["bell", "coarse", "masked", "one large entry", "equal"])
+def test_sixteen_bit_counts_beside_bytes(pq, oracle, kind, N, B, K):
+    # m = 16, eight queries to a workgroup (the last ones of a batch that is no multiple), floors shared and not: what the bytes let pass is
+    # looked up in 16-bit counts first.  Ties, masked entries, a query given up for one large entry, and one whose items all score the same
+    some = sorted({0, 1, B // 2, B - 2, B - 1})
+    assert pq.pq_measure_plan("scan", N, B, 16, 256, K)["fine"] == 1
+    G = W.codes_uniform(N, 16, 256, seed=K)
+    S = tables(N % 89 + K, B, 16, 256)
+    if kind == "coarse":
+        S = np.round(S).astype(np.float32)
+    elif kind == "masked":
+        S[:, 3, ::2] = np.finfo(np.float32).min
+    elif kind == "one large entry":
+        S[::2, 5, 7] = 1e4
+    elif kind == "equal":
+        S[1:] = 0.5
+    print(f"case fine {kind} N={N} B={B} K={K}", flush=True)
+    ids, sc = pq.pq_score_topk(dev(G), dev(S), K)
+    rid, rsc = oracle.score_topk(G, S[some], K)
+    assert np.array_equal(ids.cpu().numpy()[some], rid)
+    assert np.array_equal(sc.cpu().numpy()[some].view(np.uint32), rsc.view(np.uint32))
+
+
 @pytest.mark.parametrize("m,wide,units", [(4, 0, (1, 5, 8)), (8, 0, (1, 3, 8, 9, 20)), (16, 0, (2, 7, 16, 33, 40)), (32, 0, (1, 4, 5, 24, 40)), (64, 0, (1, 2, 3, 17, 24)),
                                           (4, 1, (2, 8, 13, 20)), (8, 1, (1, 6, 20, 32, 40)), (16, 1, (4, 5, 21, 40))])
 def test_two_queries_per_workgroup_every_share(pq, oracle, m, wide, units):
