@@ -456,7 +456,7 @@ def pq_measure_force_general(mask: int) -> int:
 
 
 PQ_PLAN_KINDS = {"scan": 0, "subset": 1, "scan16": 2}
-PQ_PLAN_KERNELS = ("general", "batched", "short", "long", "short list", "bounds", "pairs")
+PQ_PLAN_KERNELS = ("general", "batched", "short", "long", "short list", "bounds", "pairs", "list pairs")
 
 
 def pq_measure_plan(kind: str, N: int, B: int, m: int, b: int, K: int) -> dict:

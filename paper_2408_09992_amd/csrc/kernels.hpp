@@ -105,6 +105,9 @@ namespace pqk {
 // scan_subset_kernel<M, U, NT>: rows of 4, 8, 16 bytes, every number of vectors per thread
 #define PQ_SUBSET_M(X, M) X(M, 1, kThreads) X(M, 2, kThreads) X(M, 3, kThreads) X(M, 4, kThreads) X(M, 5, kThreads) \
     X(M, 6, kThreads) X(M, 7, kThreads) X(M, 8, kThreads)
+#define PQ_SUBSETP_M(X, M) X(M, 1, kThreads) X(M, 2, kThreads) X(M, 3, kThreads) X(M, 4, kThreads) X(M, 6, kThreads) X(M, 8, kThreads)
+#define PQ_SUBSETP_INSTANCES(X) PQ_SUBSETP_M(X, 4) PQ_SUBSETP_M(X, 8) PQ_SUBSETP_M(X, 16) X(8, 12, kThreads) X(8, 16, kThreads) \
+    X(16, 12, kThreads) X(16, 16, kThreads) X(16, 24, kThreads)
 #define PQ_SUBSET_INSTANCES(X) PQ_SUBSET_M(X, 4) PQ_SUBSET_M(X, 8) PQ_SUBSET_M(X, 16)
 // scan_filter_kernel<M, CW, W, W16, SUB, G, SHARE> and filter_prepare_kernel<M, CW, SUB, NT>, by translation unit.  X for scans, Y
 // for the kernels that prepare them
@@ -145,6 +148,8 @@ namespace pqk {
 #define PQ_LONG_EXTERN(M, CW, C) extern PQ_LONG_DEFINE(M, CW, C)
 #define PQ_SUBSET_DEFINE(M, U, NT) template __global__ void scan_subset_kernel<M, U, NT>(const uint8_t*, const int*, const float*, void*, float*, uint32_t, uint32_t, int, int);
 #define PQ_SUBSET_EXTERN(M, U, NT) extern PQ_SUBSET_DEFINE(M, U, NT)
+#define PQ_SUBSETP_DEFINE(M, U, NT) template __global__ void scan_subset_pair_kernel<M, U, NT>(const uint8_t*, const int*, const float*, void*, float*, uint32_t, uint32_t, int, int, int);
+#define PQ_SUBSETP_EXTERN(M, U, NT) extern PQ_SUBSETP_DEFINE(M, U, NT)
 #define PQ_FILTER_DEFINE(M, CW, W, W16, SUB, G, SH) template __global__ void scan_filter_kernel<M, CW, W, W16, SUB, G, SH>(FilterArgs);
 #define PQ_FILTER_EXTERN(M, CW, W, W16, SUB, G, SH) extern PQ_FILTER_DEFINE(M, CW, W, W16, SUB, G, SH)
 #define PQ_FILTER_DEFINE8(M, CW, W, W16, SUB, G, SH, ST) template __global__ void scan_filter_kernel<M, CW, W, W16, SUB, G, SH, ST>(FilterArgs);
@@ -172,6 +177,7 @@ PQ_SHORT_INSTANCES_D(PQ_SHORT_EXTERN)
 PQ_SHORT_INSTANCES_E(PQ_SHORT_EXTERN)
 PQ_LONG_INSTANCES(PQ_LONG_EXTERN)
 PQ_SUBSET_INSTANCES(PQ_SUBSET_EXTERN)
+PQ_SUBSETP_INSTANCES(PQ_SUBSETP_EXTERN)
 PQ_SHORT16_INSTANCES(PQ_SHORT16_EXTERN)
 PQ_PAIR_INSTANCES_A(PQ_PAIR_EXTERN)
 PQ_PAIR_INSTANCES_B(PQ_PAIR_EXTERN)

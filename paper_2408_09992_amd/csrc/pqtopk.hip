@@ -101,6 +101,7 @@ struct ScanPlan {
     bool long_scan;  // scan_long_kernel: one query's catalogue in segments
     bool pair_scan;  // scan_pair_kernel: as the short scan, two queries per workgroup (short_units: what a thread holds)
     bool short_subset; // scan_subset_kernel: a candidate list whose share per thread fits its registers, K small
+    bool subset_pair;  // scan_subset_pair_kernel: the same, two queries per workgroup
     int subset_vecs;   // ... code vectors' worth of gathered rows a thread holds
     bool filter;       // filter_prepare_kernel + scan_filter_kernel: a batch scanned by integer upper bounds
     int f_words;       // ... 32-bit words of a table entry
@@ -226,8 +227,19 @@ double filter_min_lookups(int m, int K, int B, bool subset, int cw);
 // ... and beat the scan by bounds, which has its sample and tables to make first: m = 8, 200,000 items, 44 queries (71M lookups) 21.6 and 17.9,
 // 45,066, 226 (81M) 20.5 and 18.0, 420,542, 50 (168M) 37.8 and 65.3; m = 16, 64,130, 110 (113M) 24.9 and 21.3, 43,359, 620 (430M) 78.7 and 70.6,
 // 85,925, 175 (241M) 37.0 and 42.7; m = 64, 61,190, 78 (305M) 55.8 and 43.4; m = 4, 2.6M, 7 (73M) 17.0 and 20.5.
-bool pair_beats_bounds(long long N, int B, int m, int K, int cw) {
-    return m > 4 && ((double)B * (double)N * m < 1.35 * filter_min_lookups(m, K, B, false, cw) || N < (m == 8 ? 24000 : 48000));
+// Lists: m = 8, 17,851 candidates, 158 queries (23M lookups) 22.7 and 16.1, 100,000, 100 (80M) 25.7 and 42.3.
+bool pair_beats_bounds(long long N, int B, int m, int K, bool subset, int cw) {
+    const double all = (double)B * (double)N * m, least = filter_min_lookups(m, K, B, subset, cw);
+    if (subset) return all < 1.3 * least;
+    return m > 4 && (all < 1.35 * least || N < (m == 8 ? 24000 : 48000));
+}
+// Candidate lists by two queries per workgroup (scan_subset_pair_kernel; us, without): instead of the general kernel, m = 8: 11,583 candidates, 172
+// queries, K = 48 32.6 and 16.8; 100,000, 30, K = 300 48.1 and 23.8; m = 16: 17,825, 162 29.7 and 19.6, 76,492, 296, K = 422 198 and 169, 5086,
+// 146 (12M lookups) 17.2 and 21.0; m = 4: 159,107, 30 35.2 and 20.6, 32,174, 786, K = 150 146 and 125.  Instead of one query per workgroup,
+// m = 4: 77,144, 35 20.5 and 16.2, 12,846, 230 18.7 and 17.2, 99,700, 12 (5M) 13.7 and 13.4; m = 8: 148,492, 7 13.8 and 13.2, 20,032, 68, K = 137
+// 19.5 and 21.8.
+bool subset_pair_pays(const ScanPlan& p, long long N, int B, int m) {
+    return !(p.short_subset && m > 4) && (double)B * (double)N * m >= (p.short_subset ? 1.0e7 : 1.5e7);
 }
 
 // `generic`: plan for the generic kernel whatever m is (candidate-list scans use it: their rows are gathered)
@@ -444,8 +456,29 @@ ScanPlan make_plan(long long N, int B, int m, int K, bool generic = false, int c
             }
         }
     }
+    p.subset_pair = false;
+    if (B >= 2 && generic && cw == 1 && (m == 4 || m == 8 || m == 16) && !(forced & 1) && ((forced & 256) || subset_pair_pays(p, N, B, m))) {
+        const long long pairs = (B + 1) / 2, per = (long long)kThreads * subset_pair_max(m) * 16 / m;
+        const long long least = (N + per - 1) / per, thin = (N + kThreads - 1) / kThreads;
+        long long nb = kAssumedCUs / pairs;
+        // (twice as many workgroups as compute units where their shares are long: 42,189 candidates, m = 8, 134 queries 37.2 and 30.6 us,
+        // 17,825, m = 16, 162 21.6 and 19.6, 24,629, 67 17.9 and 19.0)
+        if (N * (m + 8) >= 120000 * (nb < 1 ? 1 : nb)) nb = 2 * kAssumedCUs / pairs;
+        nb = nb < least ? least : nb > thin ? thin : nb;
+        if (nb < 1) nb = 1;
+        if (least <= kAssumedCUs) {
+            p.subset_pair = true;
+            p.short_subset = false;
+            p.subset_vecs = (int)(((N + kThreads * nb - 1) / (kThreads * nb) * m + 15) / 16);
+            p.nblk = (int)nb;
+            p.copies = 1;
+            p.big = false;
+            p.scan_dyn_lds = p.scan_lds = pair_table_bytes(m, b, 1) + 2 * sizeof(MidSelectLds<kThreads>);
+        }
+    }
     p.filter = false;
-    if (!(without & kNoFilter) && !(p.pair_scan && !(forced & (16 | 128)) && ((forced & 256) || pair_beats_bounds(N, B, m, K, cw)))) {
+    const bool pair_first = (p.pair_scan || p.subset_pair) && !(forced & (16 | 128)) && ((forced & 256) || pair_beats_bounds(N, B, m, K, p.subset_pair, cw));
+    if (!(without & kNoFilter) && !pair_first) {
         ScanPlan f = p;
         plan_filter(f, N, B, m, K, generic, cw, b);
         // (the whole batch's tables at most 32 KB per result and 1 MB: a single result of each query is not worth larger ones)
@@ -595,7 +628,7 @@ void plan_filter(ScanPlan& p, long long N, int B, int m, int K, bool subset, int
         if (fill == 1 || us < best_us) { best_us = us; nb = cand; }
     }
     p.filter = true;
-    p.tiled = p.short_scan = p.pair_scan = p.short_subset = p.long_scan = false;
+    p.tiled = p.short_scan = p.pair_scan = p.short_subset = p.subset_pair = p.long_scan = false;
     p.f_words = words;
     p.f_w16 = w16;
     p.f_queries = queries;
@@ -986,6 +1019,31 @@ hipError_t launch_filter(const ScanPlan& p, const FilterArgs& a, int m, int cw, 
     }
 }
 
+template <int M, int U>
+hipError_t launch_subset_pair_units(const ScanPlan& p, const ScanArgs& a, int B, hipStream_t st) {
+    if constexpr (subset_pair_has(M, U)) {
+        hipError_t e = allow_lds(scan_subset_pair_kernel<M, U, kThreads>, p.scan_dyn_lds);
+        if (e != hipSuccess) return e;
+        return launch(scan_subset_pair_kernel<M, U, kThreads>, dim3(p.nblk, (B + 1) / 2), kThreads, p.scan_dyn_lds, st, a.codes, a.subset, a.S, out_of(a), scores_of(a), (uint32_t)a.N, a.n_items, a.b, B, a.K);
+    } else {
+        return hipErrorInvalidValue;                         // (the plan never asks for it)
+    }
+}
+template <int M>
+hipError_t launch_subset_pair_m(const ScanPlan& p, const ScanArgs& a, int B, hipStream_t st) {
+    switch (subset_pair_instance(p.subset_vecs)) {
+        case 1: return launch_subset_pair_units<M, 1>(p, a, B, st);
+        case 2: return launch_subset_pair_units<M, 2>(p, a, B, st);
+        case 3: return launch_subset_pair_units<M, 3>(p, a, B, st);
+        case 4: return launch_subset_pair_units<M, 4>(p, a, B, st);
+        case 6: return launch_subset_pair_units<M, 6>(p, a, B, st);
+        case 8: return launch_subset_pair_units<M, 8>(p, a, B, st);
+        case 12: return launch_subset_pair_units<M, 12>(p, a, B, st);
+        case 16: return launch_subset_pair_units<M, 16>(p, a, B, st);
+        default: return launch_subset_pair_units<M, 24>(p, a, B, st);
+    }
+}
+
 // Enqueue the catalogue scan: every workgroup's K best keys land in the workspace.
 // `subset` / `n_items`: candidate list (then N is its length and the plan is a generic one) or nullptr / N
 // `cw`: bytes per sub-id (2: `codes` holds uint16 values)
@@ -1054,6 +1112,10 @@ int enqueue_scan(const ScanPlan& p, const uint8_t* codes, const float* S, long l
     if (p.long_scan) {
         if (stamps != nullptr) return PQ_ERR_UNSUPPORTED;
         return record_hip(launch_long(p, a, B, m, cw, st));
+    }
+    if (p.subset_pair) {
+        if (subset == nullptr || stamps != nullptr) return PQ_ERR_UNSUPPORTED;   // (the plan is only made for candidate lists)
+        return record_hip(m == 4 ? launch_subset_pair_m<4>(p, a, B, st) : m == 8 ? launch_subset_pair_m<8>(p, a, B, st) : launch_subset_pair_m<16>(p, a, B, st));
     }
     if (p.short_subset) {
         if (subset == nullptr || stamps != nullptr) return PQ_ERR_UNSUPPORTED;   // (the plan is only made for candidate lists)
@@ -1357,9 +1419,9 @@ int pq_measure_plan(long long N, int B, int m, int b, int K, int kind, int* plan
     if (p.scan_lds > kMaxLdsBytes || p.fold_lds > kMaxLdsBytes) return PQ_ERR_UNSUPPORTED;
     for (int i = 0; i < PQ_PLAN_FIELDS; ++i) plan[i] = 0;
     plan[PQ_PLAN_KERNEL] = p.filter ? PQ_KERNEL_BOUNDS : p.pair_scan ? PQ_KERNEL_PAIRS : p.tiled ? PQ_KERNEL_BATCHED : p.short_scan ? PQ_KERNEL_SHORT : p.long_scan ? PQ_KERNEL_LONG
-                           : p.short_subset ? PQ_KERNEL_SHORT_LIST : PQ_KERNEL_GENERAL;
+                           : p.short_subset ? PQ_KERNEL_SHORT_LIST : p.subset_pair ? PQ_KERNEL_LIST_PAIRS : PQ_KERNEL_GENERAL;
     plan[PQ_PLAN_GROUPS] = p.nblk;
-    plan[PQ_PLAN_QUERIES] = p.filter ? p.f_queries : p.tiled ? kQ : p.pair_scan ? 2 : 1;
+    plan[PQ_PLAN_QUERIES] = p.filter ? p.f_queries : p.tiled ? kQ : p.pair_scan || p.subset_pair ? 2 : 1;
     if (p.filter) {
         plan[PQ_PLAN_FIELD_BITS] = p.f_w16 ? 16 : 8;
         plan[PQ_PLAN_FINE] = p.f_fine;

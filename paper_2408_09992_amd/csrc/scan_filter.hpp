@@ -115,24 +115,6 @@ __device__ __forceinline__ uint32_t filter_sub_id(const uint32_t* w, int item, i
     else return (w[byte >> 2] >> ((byte & 3) * 8)) & 0xFFu;
 }
 
-// an item's row, as words
-template <int P>
-__device__ __forceinline__ void load_row_words(const uint8_t* codes, uint32_t item, uint32_t* w) {
-    const uint8_t* row = codes + (size_t)item * P;
-    if constexpr (P == 4) {
-        w[0] = *reinterpret_cast<const uint32_t*>(row);
-    } else if constexpr (P == 8) {
-        const uint2 x = *reinterpret_cast<const uint2*>(row);
-        w[0] = x.x; w[1] = x.y;
-    } else {
-#pragma unroll
-        for (int j = 0; j < P / 16; ++j) {
-            const uint4 x = reinterpret_cast<const uint4*>(row)[j];
-            w[4 * j] = x.x; w[4 * j + 1] = x.y; w[4 * j + 2] = x.z; w[4 * j + 3] = x.w;
-        }
-    }
-}
-
 __device__ __forceinline__ float wave_sum_f32(float v) {     // (for bounds and heuristics: any order will do)
     v += dpp_f32<kDppQuadSwap1>(0.0f, v);
     v += dpp_f32<kDppQuadSwap2>(0.0f, v);

@@ -54,6 +54,40 @@ __device__ __forceinline__ void pair_scores(const float2* lut, int stride, uint3
     }
 }
 
+// The tables of queries q0 and q0 + 1 (`two`; else q0 once more) to LDS, interleaved: two entries of each at a time when size and address
+// allow.
+template <int M, int CW, int NT>
+__device__ __forceinline__ void pair_tables(float2* lut, const float* S, int q0, bool two, int b, int tid) {
+    const float* S0 = S + (size_t)q0 * M * b;
+    const float* S1 = two ? S0 + (size_t)M * b : S0;
+    const int total = M * b;
+    if ((CW == 2 || b == kLutStride) && (total & 1) == 0 && ((uintptr_t)S & 7) == 0) {
+        constexpr int kBatch = CW == 2 || M * kLutStride / 2 > 4 * NT ? 4 : (M * kLutStride / 2 + NT - 1) / NT;   // (requested together, before the first store)
+        const float2* src0 = reinterpret_cast<const float2*>(S0);
+        const float2* src1 = reinterpret_cast<const float2*>(S1);
+        const int pieces = total >> 1;
+        for (int e0 = tid; e0 < pieces; e0 += kBatch * NT) {
+            float2 x[kBatch], y[kBatch];
+#pragma unroll
+            for (int i = 0; i < kBatch; ++i) { const int e = min(e0 + i * NT, pieces - 1); x[i] = src0[e]; y[i] = src1[e]; }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int i = 0; i < kBatch; ++i)
+                if (e0 + i * NT < pieces) reinterpret_cast<float4*>(lut)[e0 + i * NT] = make_float4(x[i].x, y[i].x, x[i].y, y[i].y);
+        }
+    } else if constexpr (CW == 2) {
+#pragma unroll 4
+        for (int e = tid; e < total; e += NT) lut[e] = make_float2(S0[e], S1[e]);
+    } else {
+        // fewer than 256 sub-ids per split, or an odd address: element by element, rows padded with zeros
+#pragma unroll 4
+        for (int e = tid; e < M * kLutStride; e += NT) {
+            const int k = e / kLutStride, j = e % kLutStride;
+            lut[e] = j < b ? make_float2(S0[k * b + j], S1[k * b + j]) : make_float2(0.0f, 0.0f);
+        }
+    }
+}
+
 // grid = (item blocks, (B + 1) / 2); queries 2y and 2y + 1 per workgroup, their tables' entries side by side in LDS (dynamic): one
 // 8-byte read gives both queries' values, at the rate of a 4-byte one.  The share, its requests and the sums are scan_short_kernel's,
 // over a grid of twice the blocks per query; the selection shares its barriers (select_mid_k_pair).  An odd batch's last query is scored
@@ -102,35 +136,7 @@ __global__ __launch_bounds__(NT, 1) void scan_pair_kernel(const uint8_t* codes, 
 #pragma unroll
     for (int u = 0; u < kRing; ++u) fetch(u);
 
-    // ---- both queries' tables, interleaved: two entries of each at a time when size and address allow
-    const float* S0 = a.S + (size_t)q0 * M * b;
-    const float* S1 = two ? S0 + (size_t)M * b : S0;
-    const int total = M * b;
-    if ((CW == 2 || b == kLutStride) && (total & 1) == 0 && ((uintptr_t)a.S & 7) == 0) {
-        constexpr int kBatch = CW == 2 || M * kLutStride / 2 > 4 * NT ? 4 : (M * kLutStride / 2 + NT - 1) / NT;   // (requested together, before the first store)
-        const float2* src0 = reinterpret_cast<const float2*>(S0);
-        const float2* src1 = reinterpret_cast<const float2*>(S1);
-        const int pieces = total >> 1;
-        for (int e0 = tid; e0 < pieces; e0 += kBatch * NT) {
-            float2 x[kBatch], y[kBatch];
-#pragma unroll
-            for (int i = 0; i < kBatch; ++i) { const int e = min(e0 + i * NT, pieces - 1); x[i] = src0[e]; y[i] = src1[e]; }
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int i = 0; i < kBatch; ++i)
-                if (e0 + i * NT < pieces) reinterpret_cast<float4*>(lut)[e0 + i * NT] = make_float4(x[i].x, y[i].x, x[i].y, y[i].y);
-        }
-    } else if constexpr (CW == 2) {
-#pragma unroll 4
-        for (int e = tid; e < total; e += NT) lut[e] = make_float2(S0[e], S1[e]);
-    } else {
-        // fewer than 256 sub-ids per split, or an odd address: element by element, rows padded with zeros
-#pragma unroll 4
-        for (int e = tid; e < M * kLutStride; e += NT) {
-            const int k = e / kLutStride, j = e % kLutStride;
-            lut[e] = j < b ? make_float2(S0[k * b + j], S1[k * b + j]) : make_float2(0.0f, 0.0f);
-        }
-    }
+    pair_tables<M, CW, NT>(lut, a.S, q0, two, b, tid);
     auto& select = *reinterpret_cast<MidSelectLds<NT>(*)[2]>(sel);
     mid_select_clear<NT>(select[0], tid);
     mid_select_clear<NT>(select[1], tid);

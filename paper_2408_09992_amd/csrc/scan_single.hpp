@@ -31,6 +31,24 @@ __device__ __forceinline__ void emit_key(const ScanArgs& a, int q, int nblk, int
     }
 }
 
+// an item's row, as words
+template <int P>
+__device__ __forceinline__ void load_row_words(const uint8_t* codes, uint32_t item, uint32_t* w) {
+    const uint8_t* row = codes + (size_t)item * P;
+    if constexpr (P == 4) {
+        w[0] = *reinterpret_cast<const uint32_t*>(row);
+    } else if constexpr (P == 8) {
+        const uint2 x = *reinterpret_cast<const uint2*>(row);
+        w[0] = x.x; w[1] = x.y;
+    } else {
+#pragma unroll
+        for (int j = 0; j < P / 16; ++j) {
+            const uint4 x = reinterpret_cast<const uint4*>(row)[j];
+            w[4 * j] = x.x; w[4 * j + 1] = x.y; w[4 * j + 2] = x.z; w[4 * j + 3] = x.w;
+        }
+    }
+}
+
 // Items a thread holds per round.  M > 0: an item's row of sub-ids takes M bytes (m sub-ids of one byte, or m / 2 of
 // two bytes) and one 16-byte vector carries 16/M items; M == 0: any row, one item per slot, row loads sized by the
 // row's alignment.

@@ -98,3 +98,73 @@ __global__ __launch_bounds__(NT) void scan_subset_kernel(const uint8_t* codes, c
     if (K <= kSmallKMax) select_small_k<NT, R>(sc, id_of, K, *reinterpret_cast<SmallSelectLds<NT>*>(smem), tid, emit);
     else select_mid_k<NT, R>(sc, id_of, K, *reinterpret_cast<MidSelectLds<NT>*>(smem), tid, emit);
 }
+
+// Most code vectors' worth of gathered rows a thread of the kernel below holds: up to 64 scores, of two queries each candidate.
+__host__ __device__ constexpr int subset_pair_max(int m) { return m == 4 ? 8 : m == 8 ? 16 : 24; }
+// its instances: 1, 2, 3, 4, 6, 8, 12, 16, 24
+__host__ __device__ constexpr int subset_pair_instance(int vecs) {
+    return vecs <= 4 ? vecs : vecs <= 6 ? 6 : vecs <= 8 ? 8 : vecs <= 12 ? 12 : vecs <= 16 ? 16 : 24;
+}
+__host__ __device__ constexpr bool subset_pair_has(int m, int u) { return u <= subset_pair_max(m) && subset_pair_instance(u) == u; }
+
+// Candidate lists for several queries: as scan_subset_kernel, two queries per workgroup (grid.y = (B + 1) / 2), their tables' entries side
+// by side in LDS as in scan_pair_kernel.  What bounds a list is the gathering of its rows, about one per clock and CU, and then the
+// lookups: both are done once for two queries here.
+template <int M, int U, int NT>
+__global__ __launch_bounds__(NT, 1) void scan_subset_pair_kernel(const uint8_t* codes, const int* subset, const float* S, void* out, float* out_scores,
+                                                                 uint32_t N, uint32_t n_items, int b, int B, int K) {
+    ScanArgs a;                                               // (plain arguments: see scan_short_kernel)
+    a.codes = codes; a.subset = subset; a.S = S; a.N = N; a.n_items = n_items; a.m = M; a.b = b; a.K = K;
+    a.ws_keys = static_cast<uint64_t*>(out); a.out_ids = out_scores != nullptr ? static_cast<int*>(out) : nullptr;
+    a.out_scores = out_scores;
+    constexpr int IPV = 16 / M, R = U * IPV;                   // candidates per code vector, per thread
+    static_assert(subset_pair_has(M, U), "vectors per thread");
+    extern __shared__ __align__(16) unsigned char smem[];
+    float2* const lut = reinterpret_cast<float2*>(smem);
+    auto& select = *reinterpret_cast<MidSelectLds<NT>(*)[2]>(smem + pair_table_bytes(M, b, 1));
+    const int tid = threadIdx.x;
+    const int q0 = blockIdx.y * 2, nblk = gridDim.x, blk = blockIdx.x;
+    const bool two = q0 + 1 < B;
+    const uint32_t n = (uint32_t)a.N;                          // candidates in the list
+    const uint32_t first = (uint32_t)blk * NT + (uint32_t)tid, stride = (uint32_t)nblk * NT;
+
+    // ---- the ids (coalesced), then the rows they name
+    uint32_t item[R], w[U][4];
+#pragma unroll
+    for (int s = 0; s < R; ++s) {
+        const uint32_t pos = first + (uint32_t)s * stride;
+        item[s] = (uint32_t)a.subset[pos < n ? pos : n - 1];  // (past the end: a re-read, never scored)
+    }
+#pragma unroll
+    for (int s = 0; s < R; ++s) {
+        item[s] = item[s] < a.n_items ? item[s] : a.n_items - 1;
+        load_row_words<M>(a.codes, item[s], &w[s / IPV][s % IPV * (M / 4)]);
+    }
+    pair_tables<M, 1, NT>(lut, a.S, q0, two, b, tid);
+    mid_select_clear<NT>(select[0], tid);
+    mid_select_clear<NT>(select[1], tid);
+    __syncthreads();
+
+    // ---- Eq. 5 for every candidate this thread holds
+    float sc[2][R];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        float p0[IPV], p1[IPV];
+        pair_scores<M, 1, kLutStride>(lut, b, w[u], p0, p1);
+#pragma unroll
+        for (int e = 0; e < IPV; ++e) {
+            asm volatile("" : "+v"(p0[e]), "+v"(p1[e]));      // (as in scan_pair_kernel: two vectors' lookups under way together)
+            const bool have = first + (uint32_t)(u * IPV + e) * stride < n;
+            sc[0][u * IPV + e] = have ? p0[e] : empty_score();
+            sc[1][u * IPV + e] = have ? p1[e] : empty_score();
+        }
+        if (u + 2 < U) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) asm volatile("" : "+v"(w[u + 2][j]));
+        }
+    }
+    auto emit = [&](int h, int rank, uint64_t key) {
+        if (h == 0 || two) emit_key(a, q0 + h, nblk, blk, rank, key);
+    };
+    select_mid_k_pair<NT>(sc, [&](int slot) -> uint32_t { return item[slot]; }, K, select, tid, emit);
+}

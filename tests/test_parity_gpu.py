@@ -856,6 +856,36 @@ def test_two_queries_per_workgroup_spread(pq, oracle, kind, N, m, b, B, K):
     assert np.array_equal(sc.cpu().numpy().view(np.uint32), rsc.view(np.uint32))
 
 
+@pytest.mark.parametrize("m", [4, 8, 16])
+@pytest.mark.parametrize("n,B,K", [(1, 2, 1), (511, 3, 40), (513, 511, 7), (6_000, 509, 300), (16_384, 512, 12), (16_385, 511, 12), (70_001, 5, 512), (33_000, 4, 1)])
+def test_list_pairs(pq, oracle, m, n, B, K):
+    # candidate lists, two queries per workgroup: one workgroup and many, shares on either side of the instances' (12,288 candidates for
+    # m = 16, 16,384 for the others, at most), ties, short alphabets, a table at a 4-byte boundary
+    import torch
+    some = sorted({0, 1, B // 2, B - 2, B - 1})
+    N = n + n // 2 + 3
+    for kind in ("random", "coarse", "short alphabet", "misaligned"):
+        b = 99 if kind == "short alphabet" else 256
+        G = W.codes_uniform(N, m, b, seed=n)
+        V = np.random.default_rng(n + K).permutation(N)[:n].astype(np.int32)
+        S = tables(n % 89 + K, B, m, b)
+        if kind == "coarse":
+            S = np.round(S).astype(np.float32)
+        off = 1 if kind == "misaligned" else 0
+        buf = torch.empty(S.size + 1, dtype=torch.float32, device="cuda")
+        Sd = buf[off:off + S.size].copy_(torch.from_numpy(S.reshape(-1))).view(S.shape)
+        prev = pq.pq_measure_force_general(256)
+        try:
+            assert pq.pq_measure_plan("subset", n, B, m, b, K)["kernel"] == "list pairs"
+            print(f"case list pairs {kind} n={n} m={m} b={b} B={B} K={K}", flush=True)
+            ids, sc = pq.pq_score_topk_subset(dev(G), Sd, dev(V), K)
+        finally:
+            pq.pq_measure_force_general(prev)
+        rid, rsc = oracle.score_topk_subset(G, S[some], V, K)
+        assert np.array_equal(ids.cpu().numpy()[some], rid)
+        assert np.array_equal(sc.cpu().numpy()[some].view(np.uint32), rsc.view(np.uint32))
+
+
 def test_small_fold_many_lists(pq, oracle):
     # the small-K fold with both of its instances: up to 3072 and up to 6144 keys per query (256 lists of K = 10, 24; with
     # K = 28, 31 the 256 lists go to the general fold: a third instance of 16 keys per thread was slower than it),
