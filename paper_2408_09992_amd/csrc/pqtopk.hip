@@ -352,7 +352,7 @@ ScanPlan make_plan(long long N, int B, int m, int K, bool generic = false, int c
     // (two-byte sub-ids: when the table fits LDS beside the selection's few KB)
     const size_t table16 = cw == 2 ? align16((size_t)m * b * sizeof(float)) : 0;
     auto select_lds = [](bool small) { return small ? sizeof(SmallSelectLds<kThreads>) : sizeof(MidSelectLds<kThreads>); };
-    const bool short16 = cw == 2 && table16 + select_lds(K <= kSmallKMax) <= kMaxLdsBytes;
+    const bool short16 = cw == 2 && table16 + select_lds(K <= small_k_max(row)) <= kMaxLdsBytes;
     if ((cw == 1 || short16) && p.vec && !generic && !p.tiled) {
         long long nb = kAssumedCUs / B;
         if (nb < 1 || units <= kDirectUnits(row) * (long long)kThreads) nb = 1;
@@ -422,7 +422,7 @@ ScanPlan make_plan(long long N, int B, int m, int K, bool generic = false, int c
             p.nblk = (int)nb;
             p.copies = 1;
             p.big = false;
-            p.scan_dyn_lds = select_lds(K <= kSmallKMax);
+            p.scan_dyn_lds = select_lds(K <= small_k_max(m));
             p.scan_lds = (size_t)m * kLutStride * sizeof(float) + p.scan_dyn_lds;
         }
     }

@@ -26,7 +26,7 @@ __host__ __device__ constexpr int short_sure_units(int u, int held) {
     return u <= held ? u - 1 : u == 8 ? held : u == 12 ? (held < 8 ? 8 : held) : u == 16 ? (held > 12 ? held : 12) : u == 24 ? 16 : u == 32 ? 24 : 32;
 }
 
-__host__ __device__ constexpr bool short_selects_small(int K, int u, int row) { return K <= kSmallKMax && u * (row < 16 ? 16 / row : 1) <= 24; }
+__host__ __device__ constexpr bool short_selects_small(int K, int u, int row) { return K <= small_k_max(row) && u * (row < 16 ? 16 / row : 1) <= 24; }
 __host__ __device__ constexpr bool short_has(int u, int held, int most) { return u <= most && short_instance(u, held) == u; }
 
 // grid = (item blocks, B); one query per workgroup; a thread holds U units of its workgroup's share: unit u of thread t

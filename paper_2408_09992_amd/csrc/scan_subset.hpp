@@ -75,7 +75,7 @@ __global__ __launch_bounds__(NT) void scan_subset_kernel(const uint8_t* codes, c
         for (int i = 0; i < kPer; ++i)
             if (tid + i * NT < M * kLutStride) lut[tid + i * NT] = tv[i];
     }
-    if (K <= kSmallKMax) small_select_clear<NT>(*reinterpret_cast<SmallSelectLds<NT>*>(smem), tid);
+    if (K <= small_k_max(M)) small_select_clear<NT>(*reinterpret_cast<SmallSelectLds<NT>*>(smem), tid);
     else mid_select_clear<NT>(*reinterpret_cast<MidSelectLds<NT>*>(smem), tid);
     __syncthreads();
 
@@ -95,7 +95,7 @@ __global__ __launch_bounds__(NT) void scan_subset_kernel(const uint8_t* codes, c
     // ---- the workgroup's K best, ranked, straight to the workspace or the result
     auto id_of = [&](int slot) -> uint32_t { return item[slot]; };
     auto emit = [&](int rank, uint64_t key) { emit_key(a, q, nblk, blk, rank, key); };
-    if (K <= kSmallKMax) select_small_k<NT, R>(sc, id_of, K, *reinterpret_cast<SmallSelectLds<NT>*>(smem), tid, emit);
+    if (K <= small_k_max(M)) select_small_k<NT, R>(sc, id_of, K, *reinterpret_cast<SmallSelectLds<NT>*>(smem), tid, emit);
     else select_mid_k<NT, R>(sc, id_of, K, *reinterpret_cast<MidSelectLds<NT>*>(smem), tid, emit);
 }
 

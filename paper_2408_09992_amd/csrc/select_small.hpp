@@ -8,7 +8,11 @@
 // written for few instructions and few LDS round trips, not for throughput.
 #pragma once
 
-constexpr int kSmallKMax = 12;                        // K up to which a workgroup's scan selects by select_small_k() (above, select_mid_k() ranks fewer candidates)
+// K up to which a workgroup's scan selects by select_small_k(); above, select_mid_k(), with two barriers more, ranks fewer candidates, the
+// more so the more scores a thread holds.  `row`: bytes of an item's row.  One user's steps without Eq. 4 (us; small and mid): m = 4,
+// 10,000 items, K = 2 4.5 and 5.4, 5 5.2 and 5.4, 10 6.3 and 5.5; 1M, K = 2 7.0 and 7.0, 5 7.7 and 7.4, 10 8.1 and 7.6; m = 8, 1.28M, K = 5 8.6 and
+// 8.7, 10 9.0 and 8.9, 12 9.5 and 9.2, 8000, K = 10 6.0 and 6.8; m = 16, 600,000, K = 12 9.6 and 9.0; m = 32, 500,000, K = 12 10.2 and 10.3.
+__host__ __device__ constexpr int small_k_max(int row) { return row == 4 ? 3 : row <= 16 ? 10 : 12; }
 constexpr int kSmallCand = 512;                       // keys of its candidate array
 constexpr int kSmallFloorSteps = 3;                   // four-way search steps of a wave's floor: a 64th of the lanes' range (5 % more candidates than the exact floor gives)
 
