@@ -112,7 +112,7 @@ namespace pqk {
 // scan_filter_kernel<M, CW, W, W16, SUB, G, SHARE> and filter_prepare_kernel<M, CW, SUB, NT>, by translation unit.  X for scans, Y
 // for the kernels that prepare them
 #define PQ_FILTER_BOTH(X, M, CW, W, W16, SUB, G) X(M, CW, W, W16, SUB, G, false) X(M, CW, W, W16, SUB, G, true)
-#define PQ_FILTER_W(X, M, CW, SUB) X(M, CW, 1, false, SUB, 1, false) X(M, CW, 2, false, SUB, 1, false) \
+#define PQ_FILTER_W(X, M, CW, SUB) X(M, CW, 1, false, SUB, 1, false) PQ_FILTER_BOTH(X, M, CW, 2, false, SUB, 1) \
     PQ_FILTER_BOTH(X, M, CW, 4, false, SUB, 1) PQ_FILTER_BOTH(X, M, CW, 4, false, SUB, 2)
 #define PQ_FILTER_INSTANCES_A(X, Y) PQ_FILTER_W(X, 4, 1, false) Y(4, 1, false)
 #define PQ_FILTER_INSTANCES_A8(X, Y) PQ_FILTER_W(X, 8, 1, false) Y(8, 1, false)

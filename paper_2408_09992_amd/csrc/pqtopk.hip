@@ -579,6 +579,18 @@ void plan_filter(ScanPlan& p, long long N, int B, int m, int K, bool subset, int
     // m = 16: 32, 3M 56.5 and 54.6, 8M 111 and 97; 200, 1M 105 and 114.  Lists: m = 4, 500 queries, 200,000 candidates 77 and 64, 1M 178 and 130.
     const double pair_lookups = B > 128 && !(m == 8 && B <= 256) ? 5.5e9 : (m == 4 ? 2.0e9 : 1.4e9) * (K > 32 ? 1.5 : 1.0);
     const bool pairs = subset ? m == 4 && B >= 400 && N >= 150000 : (double)B * (double)N * m >= pair_lookups && (K <= 32 || B <= 128);
+    // Eight queries to a workgroup instead of sixteen: half as many workgroups share a query, and below some number they share its floors, where
+    // much is scored exactly and the streaming that doubles is not the most of it.  Calls with sixteen and eight (us): m = 8, K = 200: 130
+    // queries, 1M items (floors not shared, shared) 154 and 77, 300,000 (neither) 53 and 65; 300, 300,000 147 and 78; K = 60: 200 queries, 1M
+    // 84 and 71, 130, 3M 114 and 107; 300, 500,000 (both shared) 75 and 68, 2M 147 and 166; K = 100, 600, 500,000 125 and 118, 1.28M 227 and 228;
+    // m = 4, 130 queries, 3M, K = 100 138 and 88 (with shared floors already 16 are better); two bytes, m = 8, 260 queries, 300,000, K = 20 87 and 75.
+    auto few_share = [&](int each, int least) {
+        const long long blocks = kAssumedCUs / ((B + each - 1) / each), rounds = N * m * cw / (16LL * kFilterThreads);
+        return blocks > 1 && ((blocks <= 16 && rounds / blocks >= least) || (blocks <= 32 && rounds / blocks >= 32));
+    };
+    const double scanned = (double)B * (double)N;
+    const bool eight = !subset && !w16 && !(force & 128) && (m == 4 || m == 8) && few_share(8, 14) && K >= (m == 8 && cw == 2 ? 10 : 50) &&
+                       (!few_share(16, 12) || (m == 8 && scanned <= (cw == 2 ? 3.5e8 : K > 128 ? 6.0e8 : K >= 90 ? 4.0e8 : 2.2e8)));
     double best_cost = 0.0, rate = 0.0;
     int words = 0, lanes = 1;
     for (int w = 8; w >= (w16 && m == 16 ? 4 : w16 && m == 32 ? 2 : 1); w >>= 1) {   // (8: four words for each of two lanes)
@@ -588,6 +600,7 @@ void plan_filter(ScanPlan& p, long long N, int B, int m, int K, bool subset, int
         if ((m >= 32 && l == 2) || (m == 64 && each == 4)) continue;
         const int c = K <= 16 && filter_lds_bytes(m, stride, each, w16, l, roomy, fine) > kMaxLdsBytes ? 64 : roomy;
         if (filter_lds_bytes(m, stride, each, w16, l, c, fine) > kMaxLdsBytes) continue;
+        if (w > 2 && eight) continue;
         const long long tiles = (B + w * fields - 1) / (w * fields);
         const double r = l == 2 ? kGatherPairs : each == 4 ? (filter_far_splits(m, 4, w16, 1) > 0 ? kGather16Far : kGather16) : each == 2 ? kGather8 : kGather4;
         const double cost = (double)tiles * l / r;
@@ -610,13 +623,13 @@ void plan_filter(ScanPlan& p, long long N, int B, int m, int K, bool subset, int
     // batches of a few queries).  K = 100, not shared and shared (us): m = 4, 200 queries, 8M items 236 and 179; m = 8, 3M 193 and 154; m = 16,
     // 3M 427 (16-bit fields) and 275.
     auto shares = [&](long long blocks) {
-        return blocks > 1 && ((blocks <= 16 && rounds / blocks >= 12) || (blocks <= 32 && rounds / blocks >= 32)) && (words == 4 || m >= 32 || fine);
+        return blocks > 1 && ((blocks <= 16 && rounds / blocks >= 12) || (blocks <= 32 && rounds / blocks >= 32)) && words > 1;
     };
     long long nb = 1;
     double best_us = 0.0;
     for (int fill = 1; fill <= 5; ++fill) {
         long long cand = fill <= 4 ? (long long)kAssumedCUs * fill / tiles : 16;
-        if (fill == 5 && (kAssumedCUs / tiles < cand || !shares(cand))) break;   // (fewer, which share their floors)
+        if (fill == 5 && (kAssumedCUs / tiles < cand || !shares(cand) || rounds / cand < 20)) break;   // (fewer, which share their floors)
         if (cand > rounds) cand = rounds;
         if (cand < 1) cand = 1;
         // (rows of a list: with a multiple of 8 blocks, block x of every tile runs on XCD x % 8, whose L2 the tiles share:
@@ -994,9 +1007,7 @@ hipError_t launch_filter(const ScanPlan& p, const FilterArgs& a, hipStream_t st)
     switch (p.f_words * p.f_lanes) {
         case 1: return go(scan_filter_kernel<M, CW, 1, M == 64, SUB, 1, false>);
         case 2:
-            if constexpr (M >= 32) {
-                if (p.f_share) return go(scan_filter_kernel<M, CW, 2, M == 64, SUB, 1, true>);
-            }
+            if (p.f_share) return go(scan_filter_kernel<M, CW, 2, M == 64, SUB, 1, true>);
             return go(scan_filter_kernel<M, CW, 2, M == 64, SUB, 1, false>);
         case 4:
             if constexpr (M < 64) return p.f_share ? go(scan_filter_kernel<M, CW, 4, false, SUB, 1, true>) : go(scan_filter_kernel<M, CW, 4, false, SUB, 1, false>);
