@@ -226,12 +226,12 @@ bool pair_pays(const ScanPlan& p, long long N, int B, int m, int K) {
 double filter_min_lookups(int m, int K, int B, bool subset, int cw);
 // ... and beat the scan by bounds, which has its sample and tables to make first: m = 8, 200,000 items, 44 queries (71M lookups) 21.6 and 17.9,
 // 45,066, 226 (81M) 20.5 and 18.0, 420,542, 50 (168M) 37.8 and 65.3; m = 16, 64,130, 110 (113M) 24.9 and 21.3, 43,359, 620 (430M) 78.7 and 70.6,
-// 85,925, 175 (241M) 37.0 and 42.7; m = 64, 61,190, 78 (305M) 55.8 and 43.4; m = 4, 2.6M, 7 (73M) 17.0 and 20.5.
+// 85,925, 175 (241M) 37.0 and 42.7; m = 8, 28,000, 512, K = 50 63.9 and 31.6, K = 10 26.0 and 26.3, 36,000, 900, K = 50 80.5 and 64.9, 48,000 79.2 and 85.3; m = 64, 61,190, 78 (305M) 55.8 and 43.4; m = 4, 2.6M, 7 (73M) 17.0 and 20.5.
 // Lists: m = 8, 17,851 candidates, 158 queries (23M lookups) 22.7 and 16.1, 100,000, 100 (80M) 25.7 and 42.3.
 bool pair_beats_bounds(long long N, int B, int m, int K, bool subset, int cw) {
     const double all = (double)B * (double)N * m, least = filter_min_lookups(m, K, B, subset, cw);
     if (subset) return all < 1.3 * least;
-    return m > 4 && (all < 1.35 * least || N < (m == 8 ? 24000 : 48000));
+    return m > 4 && (all < 1.35 * least || N < (m > 8 ? 48000 : K >= 32 ? 40000 : 24000));
 }
 // Candidate lists by two queries per workgroup (scan_subset_pair_kernel; us, without): instead of the general kernel, m = 8: 11,583 candidates, 172
 // queries, K = 48 32.6 and 16.8; 100,000, 30, K = 300 48.1 and 23.8; m = 16: 17,825, 162 29.7 and 19.6, 76,492, 296, K = 422 198 and 169, 5086,
@@ -499,6 +499,12 @@ constexpr double kGather4 = 8.7, kGather8 = 8.5, kGather16 = 5.0;
 // a quarter of the splits from device memory.
 constexpr double kGather16Far = 5.7, kGatherPairs = 7.4;
 
+// Whether the workgroups of a query, `each` queries to one, share its floors: few of them, `least` rounds of codes each (see shares() below).
+bool few_share(long long N, int B, int row, int each, int least) {
+    const long long blocks = kAssumedCUs / ((B + each - 1) / each), rounds = N * row / (16LL * kFilterThreads);
+    return blocks > 1 && ((blocks <= 16 && rounds / blocks >= least) || (blocks <= 32 && rounds / blocks >= 32));
+}
+
 // Lookups (B * N * m) from which a batch is scanned by upper bounds: the sample, the tables and one launch more (some 12 us
 // together) are then paid back; longer rows cost more to prepare, the most at m = 64 with many results.  Two queries fill half a
 // word's fields; more than 256 make the sample take turns on the CUs, which costs two-byte sub-ids with their larger tables most.
@@ -528,7 +534,11 @@ long long filter_min_items_per_result(long long N, int m, int K, int B, bool sub
     if (subset) return K > 128 ? 350 : 150;
     if (cw == 2) return 2000;
     if (m >= 32) return N < 5LL * m * kLutStride ? 2000 : 1000;
-    return B <= 256 ? (K > 128 ? 800 : 500) : K > 128 ? 1300 : K > 64 ? 800 : 500;
+    // (K > 128, more than 256 queries, with eight queries to a workgroup and shared floors and without bounds: m = 8, 512, 150,000 items, K = 250 94 and
+    // 130, 900, 90,000, K = 150 103 and 155; m = 4, 900, 150,000, K = 250 109 and 168; floors not shared: m = 8, 300, 150,000, K = 250 147 and 115, K = 150
+    // 78 and 107; m = 4, 512, 187,500, K = 150 99 and 87)
+    if (B > 256 && K > 128) return m <= 8 && few_share(N, B, m, 8, 14) ? 600 : m == 8 ? 1000 : 1300;
+    return B <= 256 ? (K > 128 ? 800 : 500) : K > 64 ? 800 : 500;
 }
 
 // Where 16-bit counts lie in LDS beside the bytes (m = 16; eight queries to a workgroup instead of sixteen): where many items are scored
@@ -584,13 +594,10 @@ void plan_filter(ScanPlan& p, long long N, int B, int m, int K, bool subset, int
     // queries, 1M items (floors not shared, shared) 154 and 77, 300,000 (neither) 53 and 65; 300, 300,000 147 and 78; K = 60: 200 queries, 1M
     // 84 and 71, 130, 3M 114 and 107; 300, 500,000 (both shared) 75 and 68, 2M 147 and 166; K = 100, 600, 500,000 125 and 118, 1.28M 227 and 228;
     // m = 4, 130 queries, 3M, K = 100 138 and 88 (with shared floors already 16 are better); two bytes, m = 8, 260 queries, 300,000, K = 20 87 and 75.
-    auto few_share = [&](int each, int least) {
-        const long long blocks = kAssumedCUs / ((B + each - 1) / each), rounds = N * m * cw / (16LL * kFilterThreads);
-        return blocks > 1 && ((blocks <= 16 && rounds / blocks >= least) || (blocks <= 32 && rounds / blocks >= 32));
-    };
     const double scanned = (double)B * (double)N;
-    const bool eight = !subset && !w16 && !(force & 128) && (m == 4 || m == 8) && few_share(8, 14) && K >= (m == 8 && cw == 2 ? 10 : 50) &&
-                       (!few_share(16, 12) || (m == 8 && scanned <= (cw == 2 ? 3.5e8 : K > 128 ? 6.0e8 : K >= 90 ? 4.0e8 : 2.2e8)));
+    const int row_bytes = m * cw;
+    const bool eight = !subset && !w16 && !(force & 128) && (m == 4 || m == 8) && few_share(N, B, row_bytes, 8, 14) && K >= (m == 8 && cw == 2 ? 10 : 50) &&
+                       (!few_share(N, B, row_bytes, 16, 12) || (m == 8 && scanned <= (cw == 2 ? 3.5e8 : K > 128 ? 6.0e8 : K >= 90 ? 4.0e8 : 2.2e8)));
     double best_cost = 0.0, rate = 0.0;
     int words = 0, lanes = 1;
     for (int w = 8; w >= (w16 && m == 16 ? 4 : w16 && m == 32 ? 2 : 1); w >>= 1) {   // (8: four words for each of two lanes)
