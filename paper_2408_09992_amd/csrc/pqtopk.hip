@@ -14,7 +14,7 @@
 //   scan_pair_kernel (scan_pair.hpp): the same for two queries per workgroup: a few queries, or many over small catalogues.
 //   scan_long_kernel (scan_long.hpp): a single query over more, in segments of registers.
 //   scan_filter_kernel (scan_filter.hpp; filter_prepare_kernel before it takes a sample for the first floors and makes the tables):
-//     batches.  Upper bounds of 8 or 16 bits for up to sixteen queries are summed with one LDS read per sub-id; only what reaches
+//     batches.  Upper bounds of 8 or 16 bits for up to 32 queries are summed with one LDS read per sub-id; only what reaches
 //     a query's floor is scored exactly.
 //   scan_topk_tiled_kernel (scan_batched.hpp; m = 8 or 16): large batches over catalogues too small for bounds to pay, four queries per
 //     16-byte LDS read.
@@ -227,11 +227,17 @@ double filter_min_lookups(int m, int K, int B, bool subset, int cw);
 // ... and beat the scan by bounds, which has its sample and tables to make first: m = 8, 200,000 items, 44 queries (71M lookups) 21.6 and 17.9,
 // 45,066, 226 (81M) 20.5 and 18.0, 420,542, 50 (168M) 37.8 and 65.3; m = 16, 64,130, 110 (113M) 24.9 and 21.3, 43,359, 620 (430M) 78.7 and 70.6,
 // 85,925, 175 (241M) 37.0 and 42.7; m = 8, 28,000, 512, K = 50 63.9 and 31.6, K = 10 26.0 and 26.3, 36,000, 900, K = 50 80.5 and 64.9, 48,000 79.2 and 85.3; m = 64, 61,190, 78 (305M) 55.8 and 43.4; m = 4, 2.6M, 7 (73M) 17.0 and 20.5.
-// Lists: m = 8, 17,851 candidates, 158 queries (23M lookups) 22.7 and 16.1, 100,000, 100 (80M) 25.7 and 42.3.
+// Lists: m = 8, 17,851 candidates, 158 queries (23M lookups) 22.7 and 16.1, 100,000, 100 (80M) 25.7 and 42.3; m = 16, 597,501, 5 (48M) 36.3 and 45.8.
 bool pair_beats_bounds(long long N, int B, int m, int K, bool subset, int cw) {
     const double all = (double)B * (double)N * m, least = filter_min_lookups(m, K, B, subset, cw);
-    if (subset) return all < 1.3 * least;
+    if (subset) return N < 100000 && all < 1.3 * least;
     return m > 4 && (all < 1.35 * least || N < (m > 8 ? 48000 : K >= 32 ? 40000 : 24000));
+}
+// Workgroups whose last round would leave more than a quarter of the compute units' time idle (10,045 candidates, m = 16, 538 queries: 269
+// workgroups 54.4 us, by the general kernel 40.0; 17,113, 531: 532 69.7 and 58.2; 16,000, 700: 700 42.2 and 57.1).
+bool last_round_empty(long long groups) {
+    const long long rounds = (groups + kAssumedCUs - 1) / kAssumedCUs;
+    return rounds > 1 && 4 * groups < 3 * rounds * kAssumedCUs;
 }
 // Candidate lists by two queries per workgroup (scan_subset_pair_kernel; us, without): instead of the general kernel, m = 8: 11,583 candidates, 172
 // queries, K = 48 32.6 and 16.8; 100,000, 30, K = 300 48.1 and 23.8; m = 16: 17,825, 162 29.7 and 19.6, 76,492, 296, K = 422 198 and 169, 5086,
@@ -445,6 +451,10 @@ ScanPlan make_plan(long long N, int B, int m, int K, bool generic = false, int c
                 if (nb == 0 || us < best_us) { best_us = us; nb = c; }
             }
             p.pair_scan = (forced & 256) || B <= kAssumedCUs || nb <= cw || K <= (m <= 16 && B > 2 * kAssumedCUs && nb > 2 ? 16 : 128);
+            // (one workgroup to a compute unit: 718 queries of 4500 items, two bytes, m = 16, b = 619 17.1 us without, 19.6)
+            if (!(forced & 256) && p.short_scan && 2 * lds > kMaxLdsBytes && last_round_empty(pairs * nb)) p.pair_scan = false;
+            // (rows of 4 bytes, lists to fold: 3M items, 5 queries, K = 80 28.4 us without, 31.2)
+            if (!(forced & 256) && m == 4 && K > 64 && nb > 128) p.pair_scan = false;
             if (p.pair_scan) {
                 p.tiled = p.short_scan = p.long_scan = false;
                 p.glut = false;
@@ -466,7 +476,7 @@ ScanPlan make_plan(long long N, int B, int m, int K, bool generic = false, int c
         if (N * (m + 8) >= 120000 * (nb < 1 ? 1 : nb)) nb = 2 * kAssumedCUs / pairs;
         nb = nb < least ? least : nb > thin ? thin : nb;
         if (nb < 1) nb = 1;
-        if (least <= kAssumedCUs) {
+        if (least <= kAssumedCUs && ((forced & 256) || !last_round_empty(pairs * nb))) {
             p.subset_pair = true;
             p.short_subset = false;
             p.subset_vecs = (int)(((N + kThreads * nb - 1) / (kThreads * nb) * m + 15) / 16);
@@ -628,9 +638,9 @@ void plan_filter(ScanPlan& p, long long N, int B, int m, int K, bool subset, int
     const double stream_us = (double)N * m * lanes / (rate * 2400.0);
     // Workgroups of a query share their floors where they are few and their shares long, a round being a unit of every wave (fewer words:
     // batches of a few queries).  K = 100, not shared and shared (us): m = 4, 200 queries, 8M items 236 and 179; m = 8, 3M 193 and 154; m = 16,
-    // 3M 427 (16-bit fields) and 275.
+    // 3M 427 (16-bit fields) and 275; K = 3, m = 4, 373 queries, 731,549 items 47.4 and 52.3.
     auto shares = [&](long long blocks) {
-        return blocks > 1 && ((blocks <= 16 && rounds / blocks >= 12) || (blocks <= 32 && rounds / blocks >= 32)) && words > 1;
+        return blocks > 1 && ((blocks <= 16 && rounds / blocks >= (K <= 4 ? 30 : 12)) || (blocks <= 32 && rounds / blocks >= 32)) && words > 1;
     };
     long long nb = 1;
     double best_us = 0.0;

@@ -304,7 +304,7 @@ def test_single_query_in_segments(pq, oracle, m, wide, N, K):
 # ... several of them, and any number of results, where two-byte sub-ids' tables leave no room for lists per wave: one to many
 # workgroups per query, tables up to the largest that fit
 @pytest.mark.parametrize("N,m,b,B,K", [(6_400_003, 4, 7297, 2, 421), (300_001, 8, 4096, 64, 250), (150_003, 4, 8300, 200, 120), (60_001, 16, 2048, 300, 512),
-                                       (2_000_001, 16, 2047, 3, 512), (6_600_007, 16, 2080, 1, 100), (200_005, 8, 1500, 130, 512)])
+                                       (2_000_001, 16, 2047, 3, 512), (6_600_007, 16, 2080, 1, 100), (200_005, 8, 2200, 130, 512)])
 def test_queries_in_segments_beside_tables_that_fill_lds(pq, oracle, N, m, b, B, K):
     assert pq.pq_measure_plan("scan16", N, B, m, b, K)["kernel"] == "long"
     rng = np.random.default_rng(N)
