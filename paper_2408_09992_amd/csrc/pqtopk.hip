@@ -227,10 +227,12 @@ double filter_min_lookups(int m, int K, int B, bool subset, int cw);
 // ... and beat the scan by bounds, which has its sample and tables to make first: m = 8, 200,000 items, 44 queries (71M lookups) 21.6 and 17.9,
 // 45,066, 226 (81M) 20.5 and 18.0, 420,542, 50 (168M) 37.8 and 65.3; m = 16, 64,130, 110 (113M) 24.9 and 21.3, 43,359, 620 (430M) 78.7 and 70.6,
 // 85,925, 175 (241M) 37.0 and 42.7; m = 8, 28,000, 512, K = 50 63.9 and 31.6, K = 10 26.0 and 26.3, 36,000, 900, K = 50 80.5 and 64.9, 48,000 79.2 and 85.3; m = 64, 61,190, 78 (305M) 55.8 and 43.4; m = 4, 2.6M, 7 (73M) 17.0 and 20.5.
-// Lists: m = 8, 17,851 candidates, 158 queries (23M lookups) 22.7 and 16.1, 100,000, 100 (80M) 25.7 and 42.3; m = 16, 597,501, 5 (48M) 36.3 and 45.8.
+// Lists: the rows that are gathered, once per pair and at most, against once per sixteen queries. By bounds and by pairs: m = 8, 17,851 candidates, 158
+// queries 22.7 and 16.1, 100,000, 100 25.7 and 42.3, 900,000, 4 38 and 26, 6 39 and 53, 2M, 2 60 and 46, 4 60 and 82; m = 4, 900,000, 4 36 and 23, 2M, 4 55 and 73;
+// m = 16, 400,000, 4 28 and 18, 6 28 and 31, 900,000, 4 37 and 42, 2M, 2 58 and 49.
 bool pair_beats_bounds(long long N, int B, int m, int K, bool subset, int cw) {
     const double all = (double)B * (double)N * m, least = filter_min_lookups(m, K, B, subset, cw);
-    if (subset) return N < 100000 && all < 1.3 * least;
+    if (subset) return N * ((B + 1) / 2) <= (m == 16 && B > 2 ? 1000000 : 2100000);
     return m > 4 && (all < 1.35 * least || N < (m > 8 ? 48000 : K >= 32 ? 40000 : 24000));
 }
 // Workgroups whose last round would leave more than a quarter of the compute units' time idle (10,045 candidates, m = 16, 538 queries: 269
