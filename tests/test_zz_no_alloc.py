@@ -70,3 +70,18 @@ def test_static_scratch_on_a_coarser_grid(pq, N, B, m, K):
     ids, sc = torch.empty_like(ref_ids), torch.empty_like(ref_sc)
     pq.pq_score_topk_static(G, S, K, ids, sc)
     assert torch.equal(ids, ref_ids) and torch.equal(sc.view(torch.int32), ref_sc.view(torch.int32))
+
+
+@pytest.mark.parametrize("N,B,m,K", [(200_000, 256, 8, 512), (210_000, 255, 8, 500)])
+def test_static_scratch_without_pairs_of_queries(pq, N, B, m, K):
+    # two queries per workgroup leave more lists than the static scratch holds: the call runs without them, with the same results
+    import torch
+    from paper_2408_09992_amd import workloads as W
+    assert pq.pq_measure_plan("scan", N, B, m, 256, K)["kernel"] == "pairs"
+    assert pq.pq_score_topk_workspace_bytes(N, B, m, 256, K) > pq.PQ_STATIC_SCRATCH_BYTES
+    G = W.codes_uniform_device(N, m, 256, 3)
+    S = torch.randn((B, m, 256), device="cuda", generator=torch.Generator(device="cuda").manual_seed(3))
+    ref_ids, ref_sc = pq.pq_score_topk(G, S, K)
+    ids, sc = torch.empty_like(ref_ids), torch.empty_like(ref_sc)
+    pq.pq_score_topk_static(G, S, K, ids, sc)
+    assert torch.equal(ids, ref_ids) and torch.equal(sc.view(torch.int32), ref_sc.view(torch.int32))
