@@ -107,6 +107,13 @@ __host__ __device__ constexpr int filter_far_splits(int m, int words, bool w16, 
     return w16 || words < 4 ? 0 : lanes == 2 ? (m == 4 ? 0 : m == 8 ? 2 : 3) : m == 32 ? 4 : 0;
 }
 
+// Byte of a tile's rows in device memory ([splits][stride][queries]) where the part from query `first` on of sub-id `id`'s row begins, in the
+// v-th of these splits.  A sub-id beyond the alphabet (two bytes hold more than there are rows) reads its last row: the rows lie in the
+// caller's workspace, and no sub-id leads out of them.
+__host__ __device__ constexpr uint32_t filter_far_at(uint32_t v, uint32_t id, uint32_t stride, uint32_t queries, uint32_t first) {
+    return (v * stride + (id < stride ? id : stride - 1u)) * queries + first;
+}
+
 template <int M, int CW>
 __device__ __forceinline__ uint32_t filter_sub_id(const uint32_t* w, int item, int k) {
     constexpr int P = M * CW;
@@ -1062,7 +1069,12 @@ __global__ __launch_bounds__(kFilterThreads) void scan_filter_kernel(FilterArgs 
 #pragma unroll
         for (int e = 0; e < NI; ++e)
 #pragma unroll
-            for (int v = 0; v < V; ++v) x[e][v] = *reinterpret_cast<const Word*>(far + (size_t)v * stride * QT + row_at(w, e, M - V + v));
+            for (int v = 0; v < V; ++v) {
+                // (one-byte sub-ids: a row for each of 256, and the address as in LDS)
+                const size_t at = CW == 1 ? (size_t)v * stride * QT + row_at(w, e, M - V + v)
+                                          : filter_far_at((uint32_t)v, filter_sub_id<M, CW>(w, e, M - V + v), (uint32_t)stride, QT, (uint32_t)(half * QL));
+                x[e][v] = *reinterpret_cast<const Word*>(far + at);
+            }
     };
     auto add_word = [](uint32_t (&sum)[W], const Word& x) {
         if constexpr (W == 1) sum[0] += x;
