@@ -588,7 +588,7 @@ __global__ __launch_bounds__(kFilterThreads) void scan_filter_kernel(FilterArgs 
     static_assert(!FINE || (!W16 && G == 1 && CW == 1 && V == 0), "fine counts: beside bytes");
     extern __shared__ __align__(16) unsigned char smem[];
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid / kWave);
-    const int half = G == 1 ? 0 : lane & 1, slot = lane / G;  // this lane's part of a row, its place among the wave's items
+    const int half = G == 1 ? 0 : lane & 1;                   // this lane's part of a row
     const int nblk = gridDim.x, tile = blockIdx.y, blk = blockIdx.x, q0 = tile * QT, K = a.K, b = a.b, cap = a.cap;
     uint64_t* const rec = STAMP ? a.stamps + (((size_t)tile * nblk + blk) * NW + wave) * kStampSlots : nullptr;
     stamp<STAMP>(rec, kStampEntry, lane);
@@ -618,26 +618,32 @@ __global__ __launch_bounds__(kFilterThreads) void scan_filter_kernel(FilterArgs 
     // workgroup's waves left some with a twentieth more than others: 5M items at m = 16, 256 workgroups)
     const uint32_t total = (uint32_t)((P <= 16 && !SUB) ? (a.N * P) / 16 : a.N);  // whole vectors, or items / candidates
     constexpr uint32_t kPerLane = (P <= 16 && !SUB) ? Sh::kVecs : NI;             // ... per lane and unit
-    constexpr uint32_t kPerUnit = PER * kPerLane;
-    const uint32_t all_units = (total + kPerUnit - 1) / kPerUnit;
-    const uint32_t units = (uint32_t)blk < all_units ? (all_units - blk + nblk - 1) / nblk : 0;
-    const uint32_t last = total - 1;
-    auto first_of = [&](uint32_t u) -> uint32_t {             // the lane's first element of unit u; the others follow at PER
-        return (u * (uint32_t)nblk + (uint32_t)blk) * kPerUnit + (uint32_t)slot;
+    // (`beside`: items side by side, PER as long as G lanes share one, or a whole wave's)
+    constexpr std::integral_constant<int, PER> kShared = {};
+    constexpr std::integral_constant<int, kWave> kOwn = {};
+    auto share_of = [&](auto beside) -> uint32_t {            // this workgroup's units
+        constexpr uint32_t kPerUnit = decltype(beside)::value * kPerLane;
+        const uint32_t all = (total + kPerUnit - 1) / kPerUnit;
+        return (uint32_t)blk < all ? (all - blk + nblk - 1) / nblk : 0;
     };
-    auto fetch_ids = [&](uint32_t u, uint32_t (&id)[NI]) {    // candidate lists: the items' ids
+    const uint32_t units = share_of(kShared);
+    const uint32_t last = total - 1;
+    auto first_of = [&](auto beside, uint32_t u) -> uint32_t {   // the lane's first element of unit u; the others follow at `beside`
+        return (u * (uint32_t)nblk + (uint32_t)blk) * (decltype(beside)::value * kPerLane) + (uint32_t)(decltype(beside)::value == kWave ? lane : lane / G);
+    };
+    auto fetch_ids = [&](auto beside, uint32_t u, uint32_t (&id)[NI]) {   // candidate lists: the items' ids
         if constexpr (SUB) {
-            const uint32_t p0 = first_of(u);
+            const uint32_t p0 = first_of(beside, u);
 #pragma unroll
             for (int e = 0; e < NI; ++e) {
-                const uint32_t p = p0 + e * PER;
+                const uint32_t p = p0 + e * decltype(beside)::value;
                 const uint32_t item = (uint32_t)a.subset[p < last ? p : last];
                 id[e] = item < a.n_items ? item : a.n_items - 1;
             }
         }
     };
-    auto fetch = [&](uint32_t u, const uint32_t (&id)[NI], uint32_t (&w)[Sh::kWords]) {   // branch-free: clamped past the end
-        const uint32_t p0 = first_of(u);
+    auto fetch = [&](auto beside, uint32_t u, const uint32_t (&id)[NI], uint32_t (&w)[Sh::kWords]) {   // branch-free: clamped past the end
+        const uint32_t p0 = first_of(beside, u);
         if constexpr (SUB) {
 #pragma unroll
             for (int e = 0; e < NI; ++e) load_row_words<P>(a.codes, id[e], &w[e * P / 4]);
@@ -645,7 +651,7 @@ __global__ __launch_bounds__(kFilterThreads) void scan_filter_kernel(FilterArgs 
             constexpr int kEach = P > 16 ? P / 16 : 1;        // vectors that follow each other
 #pragma unroll
             for (int v = 0; v < Sh::kVecs / kEach; ++v) {
-                const uint32_t p = p0 + v * PER;
+                const uint32_t p = p0 + v * decltype(beside)::value;
                 const uint4* const at = reinterpret_cast<const uint4*>(a.codes) + (size_t)(p < last ? p : last) * kEach;
 #pragma unroll
                 for (int i = 0; i < kEach; ++i) {
@@ -657,14 +663,14 @@ __global__ __launch_bounds__(kFilterThreads) void scan_filter_kernel(FilterArgs 
         }
     };
     // element e of unit u: the item (or its place in the list), or -1u past the end
-    auto element_of = [&](uint32_t u, int e) -> uint32_t {
-        const uint32_t p0 = first_of(u);
+    auto element_of = [&](auto beside, uint32_t u, int e) -> uint32_t {
+        const uint32_t p0 = first_of(beside, u);
         if constexpr (SUB || P > 16) {
-            const uint32_t p = p0 + e * PER;
+            const uint32_t p = p0 + e * decltype(beside)::value;
             return p <= last ? p : ~0u;
         } else {
             constexpr int IPV = 16 / P;
-            const uint32_t p = p0 + (e / IPV) * PER;
+            const uint32_t p = p0 + (e / IPV) * decltype(beside)::value;
             return p <= last ? p * IPV + e % IPV : ~0u;
         }
     };
@@ -717,8 +723,8 @@ __global__ __launch_bounds__(kFilterThreads) void scan_filter_kernel(FilterArgs 
 #pragma unroll
     for (int i = 0; i < D - 1; ++i) {
         unit[i] = (uint32_t)(i * NW + wave);
-        fetch_ids(unit[i], inext);
-        fetch(unit[i], inext, w[i]);
+        fetch_ids(kShared, unit[i], inext);
+        fetch(kShared, unit[i], inext, w[i]);
     }
     for (int i = tid; i < QT * cap; i += NT) lists[i] = 0ull;
     for (int i = tid; i < QT * kFilterBins; i += NT) hist[i] = 0u;
@@ -1149,7 +1155,7 @@ __global__ __launch_bounds__(kFilterThreads) void scan_filter_kernel(FilterArgs 
                 for (int j = 0; j < W; ++j) hits[e] |= ((sum[e][j] & TOP) >> (W16 ? 15 : 7)) << j;
                 hits[e] <<= half * W;
                 if (V > 0) hits[e] &= ~gone;                  // (rows in device memory are not cleared when a query is given up)
-                if (element_of(u, e) == ~0u) hits[e] = 0;
+                if (element_of(kShared, u, e) == ~0u) hits[e] = 0;
             }
         }
         return some;
@@ -1164,7 +1170,7 @@ __global__ __launch_bounds__(kFilterThreads) void scan_filter_kernel(FilterArgs 
         request();
         uint32_t un = requested();
         request();
-        fetch_ids(un, inext);
+        fetch_ids(kShared, un, inext);
         Word x[AHEAD ? 2 : 1][NI][V > 0 ? V : 1];
         if constexpr (AHEAD) fetch_far(w[0], x[0]);
         while (unit[0] < units) {                             // (slot 0 holds the oldest; loads past the end are clamped and never count)
@@ -1179,10 +1185,10 @@ __global__ __launch_bounds__(kFilterThreads) void scan_filter_kernel(FilterArgs 
                 else if constexpr (V > 0) fetch_far(w[i], x[0]);
                 const int into = (i + D - 1) % D;
                 unit[into] = un;
-                fetch(un, inext, w[into]);
+                fetch(kShared, un, inext, w[into]);
                 un = requested();
                 request();
-                fetch_ids(un, inext);
+                fetch_ids(kShared, un, inext);
                 in_group[i] = unit[i];
                 if (unit[i] < units) {
                     some = scan_unit(unit[i], w[i], x[kAt[i & 1]], hits[i]) || some;
@@ -1211,7 +1217,7 @@ __global__ __launch_bounds__(kFilterThreads) void scan_filter_kernel(FilterArgs 
                         for (int e = 0; e < NI; ++e) {
                             while (hits[i][e] != 0u && rank < limit) {
                                 const int q = query_of(__builtin_ctz(hits[i][e]));
-                                at[rank] = ((uint64_t)q << 32) | element_of(in_group[i], e);
+                                at[rank] = ((uint64_t)q << 32) | element_of(kShared, in_group[i], e);
                                 hits[i][e] &= hits[i][e] - 1u;
                                 ++rank;
                             }
@@ -1253,7 +1259,9 @@ __global__ __launch_bounds__(kFilterThreads) void scan_filter_kernel(FilterArgs 
     __syncthreads();
 
     // ---- the queries that were given up, EW at a time: lists, counters and floors as at the start, exact tables in the counts'
-    // place; what exceeds a query's floor and its list's K-th best key goes through the queue like any hit
+    // place, an item per lane; what exceeds a query's floor and its list's K-th best key goes through the queue like any hit
+    // (with a pair of lanes to an item, both loading its codes: 50M items, m = 8, 32 queries, an entry that five items have: 2009 us, now 1416)
+    const uint32_t units_again = share_of(kOwn);
     uint32_t todo = (uint32_t)__ballot(lane < QT && (lds_peek(passed + (lane < QT ? lane : 0)) & kLost) != 0u);
     while (__builtin_expect(todo != 0, 0)) {
         int qs[EW];
@@ -1276,44 +1284,31 @@ __global__ __launch_bounds__(kFilterThreads) void scan_filter_kernel(FilterArgs 
         if (tid == 0) *next_unit = NW;
         uint32_t u = wave;
         uint32_t wa[Sh::kWords], wb[Sh::kWords];
-        fetch_ids(u, inext);
-        if constexpr (P <= 16) fetch(u, inext, wa);
+        fetch_ids(kOwn, u, inext);
+        if constexpr (P <= 16) fetch(kOwn, u, inext, wa);
         __syncthreads();
         float first_floor[EW];
 #pragma unroll
         for (int j = 0; j < EW; ++j) first_floor[j] = par[qs[j] < 0 ? 0 : qs[j]].floor;
         queued = 0;
-        bool done = units == 0;
+        bool done = units_again == 0;
         while (!done) {
             // (the next unit's codes on their way while this one is scored)
             int pending = 0;
             if (lane == 0) pending = (int)atomicAdd(next_unit, 1u);
             const uint32_t un = (uint32_t)__builtin_amdgcn_readfirstlane(pending);
-            fetch_ids(un, inext);
-            if constexpr (P <= 16) fetch(un, inext, wb);
+            fetch_ids(kOwn, un, inext);
+            if constexpr (P <= 16) fetch(kOwn, un, inext, wb);
             // scores that matter: above the sample's floor and the list's K-th best (none yet: key 0, whose score is a NaN and loses)
             float floor[EW];
 #pragma unroll
             for (int j = 0; j < EW; ++j) floor[j] = score_of_key(lds_peek(thr + (qs[j] < 0 ? 0 : qs[j])));
 #pragma unroll
             for (int j = 0; j < EW; ++j) floor[j] = qs[j] < 0 ? __builtin_nanf("") : fmaxf(floor[j], first_floor[j]);
-            // (pairs: a lane takes every other of the pair's items)
-            constexpr int NL = NI % G == 0 ? NI / G : 1;      // items of a lane
-            auto own_element = [&](int e) -> uint32_t {
-                if constexpr (NI % G != 0) return half == 0 ? element_of(u, e) : ~0u;   // (an item for two lanes: the first one's)
-                else return element_of(u, e * G + half);
-            };
-            uint32_t own[NL * (P / 4)];                     // their rows (rows of up to 16 bytes)
-            if constexpr (P <= 16) {
+            uint32_t hits[NI];                                // per item bit j: query qs[j]
+            if (u < units_again) {
 #pragma unroll
-                for (int e = 0; e < NL; ++e)
-#pragma unroll
-                    for (int j = 0; j < P / 4; ++j) own[e * (P / 4) + j] = NI % G != 0 || half == 0 ? wa[e * G * (P / 4) + j] : wa[(NI % G != 0 ? 0 : e * G + G - 1) * (P / 4) + j];
-            }
-            uint32_t hits[NL];                                // per item bit j: query qs[j]
-            if (u < units) {
-#pragma unroll
-                for (int e = 0; e < NL; ++e) {
+                for (int e = 0; e < NI; ++e) {
                     float acc[EW];
                     // (a few lookups on their way together: few registers, and sixteen waves hide each other's waits)
                     constexpr int kTogether = P <= 16 && M >= 8 ? 8 : 4;
@@ -1335,9 +1330,9 @@ __global__ __launch_bounds__(kFilterThreads) void scan_filter_kernel(FilterArgs 
                     };
                     if constexpr (P <= 16) {
 #pragma unroll
-                        for (int k0 = 0; k0 < M; k0 += kTogether) add(&own[e * P / 4], 0, k0, k0 == 0);
+                        for (int k0 = 0; k0 < M; k0 += kTogether) add(&wa[e * P / 4], 0, k0, k0 == 0);
                     } else {                                  // wide rows: piece by piece from memory
-                        const uint32_t at = own_element(e);
+                        const uint32_t at = element_of(kOwn, u, e);
                         const uint4* const row = reinterpret_cast<const uint4*>(a.codes + (size_t)item_at(at != ~0u ? at : 0u) * P);
                         constexpr int kPer = 16 / CW;         // sub-ids of a piece
 #pragma unroll
@@ -1354,7 +1349,7 @@ __global__ __launch_bounds__(kFilterThreads) void scan_filter_kernel(FilterArgs 
 #pragma unroll
                     for (int j = 0; j < EW; ++j) hits[e] |= (uint32_t)(acc[j] >= floor[j]) << j;
                     if (__ballot(hits[e] != 0u) != 0) {
-                        const uint32_t at = own_element(e), item = at != ~0u ? item_at(at) : ~0u;
+                        const uint32_t at = element_of(kOwn, u, e), item = at != ~0u ? item_at(at) : ~0u;
 #pragma unroll
                         for (int j = 0; j < EW; ++j)
                             if (item == ~0u || make_key(acc[j] + 0.0f, item) <= lds_peek(thr + (qs[j] < 0 ? 0 : qs[j]))) hits[e] &= ~(1u << j);
@@ -1363,7 +1358,7 @@ __global__ __launch_bounds__(kFilterThreads) void scan_filter_kernel(FilterArgs 
             } else {
                 done = true;
 #pragma unroll
-                for (int e = 0; e < NL; ++e) hits[e] = 0;
+                for (int e = 0; e < NI; ++e) hits[e] = 0;
                 if constexpr (P < 16 && !SUB) {               // the items after the last whole code vector (at most 3 of EW queries)
                     const uint32_t first_left = total * (16 / P), n_left = (uint32_t)a.N - first_left;
                     if (blk == 0 && wave == 0 && n_left != 0) {
@@ -1379,17 +1374,17 @@ __global__ __launch_bounds__(kFilterThreads) void scan_filter_kernel(FilterArgs 
             for (;;) {
                 uint32_t mask = 0, item = 0, left = 0;
 #pragma unroll
-                for (int e = 0; e < NL; ++e) left |= hits[e];
+                for (int e = 0; e < NI; ++e) left |= hits[e];
                 const uint64_t who = __ballot(left != 0u);
                 if (who == 0 && !(done && queued != 0)) break;
                 const bool full = queued + __popcll(who) > kFilterQueue;
                 if (!full) {
                 bool taken = false;
 #pragma unroll
-                for (int e = 0; e < NL; ++e) {
+                for (int e = 0; e < NI; ++e) {
                     const bool here = !taken && hits[e] != 0u;
                     mask = here ? hits[e] : mask;
-                    item = here ? own_element(e) : item;
+                    item = here ? element_of(kOwn, u, e) : item;
                     hits[e] = here ? hits[e] & (hits[e] - 1u) : hits[e];
                     taken = taken || here;
                     asm volatile("" : "+v"(hits[e]));

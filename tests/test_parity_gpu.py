@@ -447,6 +447,33 @@ def test_scan_by_upper_bounds_in_pairs_of_lanes(pq, oracle, m, N, B, K, tables):
     _bounds_case(pq, oracle, wide, rng.standard_normal((B, m, 259), dtype=np.float32), K, mask=16 | 128)
 
 
+@pytest.mark.parametrize("tables", ["rare_high", "equal_rows"])
+@pytest.mark.parametrize("m", [4, 8, 16])
+def test_second_scan_after_pairs_of_lanes(pq, oracle, m, tables):
+    # queries given up where two lanes share an item are scanned again with an item per lane: several units for a wave, a ragged
+    # last one, more such queries than one pass takes, an odd one beside whole tiles
+    rng = np.random.default_rng(m)
+    N, B, K = 300_007, 33, 10
+    codes = rng.integers(0, 256, (N, m), dtype=np.uint8)
+    S = rng.standard_normal((B, m, 256), dtype=np.float32)
+    if tables == "equal_rows":
+        codes = np.ascontiguousarray(codes[np.arange(N) % 7])
+    else:
+        codes[codes[:, 1] == 7, 1] = 8
+        codes[[3, 4000, 4001, 33_333, N - 1], 1] = 7
+        S[[0, 2, 3, 5, 8, 9, 12, 32], 1, 7] = 1e5
+    mask = 16 | 128
+    prev = pq.pq_measure_force_general(mask)
+    try:
+        assert pq.pq_measure_plan("scan", N, B, m, 256, K)["queries"] == 32
+    finally:
+        pq.pq_measure_force_general(prev)
+    _bounds_case(pq, oracle, codes, S, K, mask=mask)
+    if m == 4:
+        _bounds_case(pq, oracle, codes, S, K, subset=rng.permutation(N)[:N - 777].astype(np.int32), mask=mask)
+    _bounds_case(pq, oracle, codes.astype(np.uint16), S, K, mask=mask)
+
+
 def _odd_tables(kind, S):
     """Score tables that are not bell-shaped: masked entries, queries of zeros (a padded batch), single large entries, ..."""
     B, m, b = S.shape
