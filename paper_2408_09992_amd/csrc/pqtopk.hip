@@ -646,9 +646,8 @@ void plan_filter(ScanPlan& p, long long N, int B, int m, int K, bool subset, int
     };
     long long nb = 1;
     double best_us = 0.0;
-    for (int fill = 1; fill <= 5; ++fill) {
-        long long cand = fill <= 4 ? (long long)kAssumedCUs * fill / tiles : 16;
-        if (fill == 5 && (kAssumedCUs / tiles < cand || !shares(cand) || rounds / cand < 20)) break;   // (fewer, which share their floors)
+    for (int fill = 1; fill <= 4; ++fill) {
+        long long cand = (long long)kAssumedCUs * fill / tiles;
         if (cand > rounds) cand = rounds;
         if (cand < 1) cand = 1;
         // (rows of a list: with a multiple of 8 blocks, block x of every tile runs on XCD x % 8, whose L2 the tiles share:
