@@ -114,6 +114,7 @@ struct ScanPlan {
     int f_far;         // ... splits whose counts stay in device memory
     int f_stride;      // ... table entries of a split
     bool f_share;      // ... the workgroups of a query share their floors
+    bool f_patient;    // ... which rise so far that the sample gives no query up
     int f_prepare;     // ... threads of a workgroup that takes a part of the sample
     int f_sample;      // ... units of a part's sample
     int f_rounds;      // ... rounds of a part's sample
@@ -641,8 +642,13 @@ void plan_filter(ScanPlan& p, long long N, int B, int m, int K, bool subset, int
     // Workgroups of a query share their floors where they are few and their shares long, a round being a unit of every wave (fewer words:
     // batches of a few queries).  K = 100, not shared and shared (us): m = 4, 200 queries, 8M items 236 and 179; m = 8, 3M 193 and 154; m = 16,
     // 3M 427 (16-bit fields) and 275; K = 3, m = 4, 373 queries, 731,549 items 47.4 and 52.3.
+    // More than sixteen update one histogram too often for few results, and at m = 64, where 16-bit fields let little pass, for some more: m = 64, 40
+    // queries, 1M items, K = 5 143 and 161, 10 147 and 162, 50 229 (1.5M) and 215; 32, 1.5M, K = 5 159 and 182; 56, 2M, K = 20 367 and 342; m = 4, 130,
+    // 4M, K = 3 71.3 and 73.5, 200, K = 10 106 and 94; m = 8, 250, 1.5M, K = 1 69 and 79, 3 75 and 80; m = 16, 180, 700,000, K = 1 71 and 78, 130, 1.5M, K = 3
+    // 105 and 101; m = 32, 180, 1.5M, K = 3 235 and 221.  m = 64, shares of few rounds: 64 queries, 200,000 items (12 rounds), K = 10 69 and 87, K = 100 93
+    // and 116, 450,000 (27) 149 and 153; 100, 300,000 (29) 212 and 192.
     auto shares = [&](long long blocks) {
-        return blocks > 1 && ((blocks <= 16 && rounds / blocks >= (K <= 4 ? 30 : 12)) || (blocks <= 32 && rounds / blocks >= 32)) && words > 1;
+        return blocks > 1 && ((blocks <= 16 && rounds / blocks >= (K <= 4 ? 30 : m == 64 ? 28 : 12)) || (blocks <= 32 && rounds / blocks >= 32 && K > (m <= 8 ? 4 : m <= 32 ? 2 : 16))) && words > 1;
     };
     long long nb = 1;
     double best_us = 0.0;
@@ -674,6 +680,11 @@ void plan_filter(ScanPlan& p, long long N, int B, int m, int K, bool subset, int
     // 200,000 items, m = 4, K = 12 41 and 29 us; 478, 115,861, m = 8, K = 11 48 and 42; 300, 300,000, K = 26 52 and 56).  Where the workgroups
     // of a query share their floors those rise fast by themselves.
     p.f_share = shares(nb);
+    // The sample gives a query up of which more than three in ten items would pass its floor.  Floors that few workgroups share over long shares rise far above
+    // the sample's, and the scan finds out by itself (given up at once, 1024 queries of heavy-tailed tables, m = 8, took 1.3 ms instead of 0.5); those of short
+    // shares, or of more workgroups, rise less.  An entry that five items have, left to the scan and given up at once (us): m = 64, 60 queries, 3M items, K = 100
+    // 4977 and 2272; m = 8, 200, 4M, K = 100 2559 and 988, 300, 500,000, K = 10 919 and 218; m = 4, 500, 300,000, K = 100 841 and 245.
+    p.f_patient = p.f_share && nb <= 16 && rounds / nb >= 32;
     const long long items_per_round = (long long)p.f_sample * N / units;
     long long want = (long long)((K <= 16 && B > 128 && !subset && !p.f_share ? 8.0 : 5.0) * sqrt((double)K * (double)N)) / items_per_round;
     const long long most_rounds = (nb > 16 ? 4 : K <= 32 ? 1 : m == 4 ? 4 : m == 8 ? 2 : 1) * (kFilterThreads / p.f_prepare);
@@ -1100,7 +1111,7 @@ int enqueue_scan(const ScanPlan& p, const uint8_t* codes, const float* S, long l
         f.rounds = p.f_rounds;
         f.parts = p.f_parts;
         f.best_per_part = p.f_best;
-        f.share = p.f_share;
+        f.patient = p.f_patient;
         f.stamps = stamps;
         for (int q0 = 0; q0 < B; q0 += p.f_batch) {          // (once, unless the batch is one of thousands)
             f.B = B - q0 < p.f_batch ? B - q0 : p.f_batch;

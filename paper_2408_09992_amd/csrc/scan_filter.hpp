@@ -78,7 +78,7 @@ struct FilterArgs {
     int sample;                 // units of a part's sample per round (code vectors, or items of more than 16 bytes; candidates of a list)
     int rounds;                 // ... and the rounds
     int parts, best_per_part;
-    int share;                  // the workgroups of a query share their floors
+    int patient;                // floors shared between workgroups rise so far that the sample gives no query up
     uint64_t* stamps;           // STAMP instances only
 };
 
@@ -471,10 +471,10 @@ __global__ __launch_bounds__(NT, M <= 16 ? 8 : 4) void filter_prepare_kernel(Fil
         if (mine) bases[lane] = base;
         // How much of the sample would pass: scores within the roundings of their counts below the floor.  Where that is more than three
         // in ten, by the best of n scores of 64 threads, the scan gives the query up unless the parts together know better.
-        // (Floors shared between workgroups rise by themselves, and how far nobody knows yet.)
+        // (Floors that few workgroups share over long shares rise by themselves, and how far nobody knows yet.)
         const float near = floor_s - step * (a.wide ? 0.5f : 2.5f);
         const int n = a.rounds * Sh::kSampleItems, pass = __popcll(__ballot(fmaxf(best[0], best[1]) >= near));
-        const bool hopeless = !(inv > 0.0f) || (a.share == 0 && (float)pass > (float)kWave * (1.0f - exp2f((float)n * -0.5146f)));   // 0.7 ^ n
+        const bool hopeless = !(inv > 0.0f) || (a.patient == 0 && (float)pass > (float)kWave * (1.0f - exp2f((float)n * -0.5146f)));   // 0.7 ^ n
         if (lane == 0) {
             const int t = (int)t_floor;
             a.query[q] = FilterQuery{off, inv, hopeless ? t + kHopeless : t, cut};
