@@ -112,20 +112,21 @@ namespace pqk {
 // scan_filter_kernel<M, CW, W, W16, SUB, G, SHARE> and filter_prepare_kernel<M, CW, SUB, NT>, by translation unit.  X for scans, Y
 // for the kernels that prepare them
 #define PQ_FILTER_BOTH(X, M, CW, W, W16, SUB, G) X(M, CW, W, W16, SUB, G, false) X(M, CW, W, W16, SUB, G, true)
-#define PQ_FILTER_W(X, M, CW, SUB) X(M, CW, 1, false, SUB, 1, false) PQ_FILTER_BOTH(X, M, CW, 2, false, SUB, 1) \
-    PQ_FILTER_BOTH(X, M, CW, 4, false, SUB, 1) PQ_FILTER_BOTH(X, M, CW, 4, false, SUB, 2)
-#define PQ_FILTER_INSTANCES_A(X, Y) PQ_FILTER_W(X, 4, 1, false) Y(4, 1, false)
-#define PQ_FILTER_INSTANCES_A8(X, Y) PQ_FILTER_W(X, 8, 1, false) Y(8, 1, false)
-#define PQ_FILTER_INSTANCES_B(X, Y) PQ_FILTER_W(X, 16, 1, false) PQ_FILTER_BOTH(X, 16, 1, 4, true, false, 1) Y(16, 1, false)
+#define PQ_FILTER_W(X, M, CW, SUB) X(M, CW, 1, false, SUB, 1, false) PQ_FILTER_BOTH(X, M, CW, 2, false, SUB, 1) PQ_FILTER_BOTH(X, M, CW, 4, false, SUB, 1)
+#define PQ_FILTER_G(X, M, CW, SUB) PQ_FILTER_W(X, M, CW, SUB) PQ_FILTER_BOTH(X, M, CW, 4, false, SUB, 2)
+#define PQ_FILTER_INSTANCES_A(X, Y) PQ_FILTER_G(X, 4, 1, false) Y(4, 1, false)
+#define PQ_FILTER_INSTANCES_A8(X, Y) PQ_FILTER_G(X, 8, 1, false) Y(8, 1, false)
+#define PQ_FILTER_INSTANCES_B(X, Y) PQ_FILTER_G(X, 16, 1, false) PQ_FILTER_BOTH(X, 16, 1, 4, true, false, 1) Y(16, 1, false)
 // (64 splits: 16-bit fields always, and room for four queries)
 #define PQ_FILTER_INSTANCES_C(X, Y) \
     X(32, 1, 1, false, false, 1, false) PQ_FILTER_BOTH(X, 32, 1, 2, false, false, 1) PQ_FILTER_BOTH(X, 32, 1, 4, false, false, 1) \
     PQ_FILTER_BOTH(X, 32, 1, 2, true, false, 1) PQ_FILTER_BOTH(X, 32, 1, 4, true, false, 1) \
     X(64, 1, 1, true, false, 1, false) PQ_FILTER_BOTH(X, 64, 1, 2, true, false, 1) Y(32, 1, false) Y(64, 1, false)
-#define PQ_FILTER_INSTANCES_SUBSET(X, Y) PQ_FILTER_W(X, 4, 1, true) PQ_FILTER_W(X, 8, 1, true) Y(4, 1, true) Y(8, 1, true)
-#define PQ_FILTER_INSTANCES_SUBSET16(X, Y) PQ_FILTER_W(X, 16, 1, true) PQ_FILTER_BOTH(X, 16, 1, 4, true, true, 1) Y(16, 1, true)
-#define PQ_FILTER_INSTANCES_U16(X, Y) PQ_FILTER_W(X, 4, 2, false) PQ_FILTER_W(X, 8, 2, false) Y(4, 2, false) Y(8, 2, false)
-#define PQ_FILTER_INSTANCES_U16_16(X, Y) PQ_FILTER_W(X, 16, 2, false) Y(16, 2, false)
+// (lists: pairs of lanes at m = 4 alone; m = 16: eight queries of bytes are a workgroup's where there are no more, over too short shares to share floors)
+#define PQ_FILTER_INSTANCES_SUBSET(X, Y) PQ_FILTER_G(X, 4, 1, true) PQ_FILTER_W(X, 8, 1, true) Y(4, 1, true) Y(8, 1, true)
+#define PQ_FILTER_INSTANCES_SUBSET16(X, Y) X(16, 1, 1, false, true, 1, false) X(16, 1, 2, false, true, 1, false) PQ_FILTER_BOTH(X, 16, 1, 4, false, true, 1) PQ_FILTER_BOTH(X, 16, 1, 4, true, true, 1) Y(16, 1, true)
+#define PQ_FILTER_INSTANCES_U16(X, Y) PQ_FILTER_G(X, 4, 2, false) PQ_FILTER_G(X, 8, 2, false) Y(4, 2, false) Y(8, 2, false)
+#define PQ_FILTER_INSTANCES_U16_16(X, Y) PQ_FILTER_G(X, 16, 2, false) Y(16, 2, false)
 // measurement instances (wall-clock stamps per wave) of those the named batch workloads run
 #define PQ_FILTER_STAMPED(X, M, G) X(M, 1, 4, false, false, G, false, true) X(M, 1, 4, false, false, G, true, true)
 #define PQ_FILTER_INSTANCES_STAMPED(X) PQ_FILTER_STAMPED(X, 8, 1) PQ_FILTER_STAMPED(X, 8, 2) PQ_FILTER_STAMPED(X, 16, 1)

@@ -616,7 +616,7 @@ void plan_filter(ScanPlan& p, long long N, int B, int m, int K, bool subset, int
     for (int w = 8; w >= (w16 && m == 16 ? 4 : w16 && m == 32 ? 2 : 1); w >>= 1) {   // (8: four words for each of two lanes)
         const int l = w == 8 ? 2 : 1, each = w == 8 ? 4 : w;
         if (fine && w != 2) continue;
-        if (l == 2 && (w16 || !(pairs || (force & 128)))) continue;
+        if (l == 2 && (w16 || (subset && m != 4) || !(pairs || (force & 128)))) continue;
         if ((m >= 32 && l == 2) || (m == 64 && each == 4)) continue;
         const int c = K <= 16 && filter_lds_bytes(m, stride, each, w16, l, roomy, fine) > kMaxLdsBytes ? 64 : roomy;
         if (filter_lds_bytes(m, stride, each, w16, l, c, fine) > kMaxLdsBytes) continue;
@@ -1036,13 +1036,14 @@ hipError_t launch_filter(const ScanPlan& p, const FilterArgs& a, hipStream_t st)
     switch (p.f_words * p.f_lanes) {
         case 1: return go(scan_filter_kernel<M, CW, 1, M == 64, SUB, 1, false>);
         case 2:
-            if (p.f_share) return go(scan_filter_kernel<M, CW, 2, M == 64, SUB, 1, true>);
+            if constexpr (!(SUB && M == 16))
+                if (p.f_share) return go(scan_filter_kernel<M, CW, 2, M == 64, SUB, 1, true>);
             return go(scan_filter_kernel<M, CW, 2, M == 64, SUB, 1, false>);
         case 4:
             if constexpr (M < 64) return p.f_share ? go(scan_filter_kernel<M, CW, 4, false, SUB, 1, true>) : go(scan_filter_kernel<M, CW, 4, false, SUB, 1, false>);
             break;
         default:
-            if constexpr (M <= 16) return p.f_share ? go(scan_filter_kernel<M, CW, 4, false, SUB, 2, true>) : go(scan_filter_kernel<M, CW, 4, false, SUB, 2, false>);
+            if constexpr (M <= 16 && !(SUB && M != 4)) return p.f_share ? go(scan_filter_kernel<M, CW, 4, false, SUB, 2, true>) : go(scan_filter_kernel<M, CW, 4, false, SUB, 2, false>);
     }
     return hipErrorInvalidValue;                             // (the plan never asks for it)
 }
