@@ -513,18 +513,23 @@ __global__ __launch_bounds__(NT, M <= 16 ? 8 : 4) void filter_prepare_kernel(Fil
         return (uint32_t)fminf(fmaxf(x, 0.0f), 255.0f);
     };
     if constexpr (M == 16 && CW == 1 && !SUB) {
-        if (a.fine != nullptr) {                              // (two entries per thread and store)
-            uint32_t* const fine = reinterpret_cast<uint32_t*>(a.fine + (size_t)q * a.entries);
+        if (a.fine != nullptr) {                              // (and 16-bit counts beside them, from the same read of the table)
+            uint2* const fine = reinterpret_cast<uint2*>(a.fine + (size_t)q * a.entries);
             const float inv256 = nothing ? 0.0f : inv * 256.0f, up16 = nothing ? 0.0f : kFilterUp16;
-            for (uint32_t i = tid; i * 2 < (uint32_t)a.entries; i += NT) {
-                uint32_t word = 0;
+            for (uint32_t i = tid; i * 4 < (uint32_t)a.entries; i += NT) {
+                const float4 x = reinterpret_cast<const float4*>(lut)[i];
+                const float base_k = bases[i * 4 / kLutStride], v[4] = {x.x, x.y, x.z, x.w};
+                uint32_t word = 0, words[2] = {0, 0};
 #pragma unroll
-                for (int c = 0; c < 2; ++c) {
-                    const float x = ceilf((lut[i * 2 + c] - bases[(i * 2 + c) / (uint32_t)stride]) * inv256 + up16);
-                    word |= (uint32_t)fminf(fmaxf(x, 0.0f), 65535.0f) << (c * 16);
+                for (int c = 0; c < 4; ++c) {
+                    const float over = v[c] - base_k;
+                    word |= (uint32_t)fminf(fmaxf(ceilf(over * per + up), 0.0f), 255.0f) << (8 * c);
+                    words[c / 2] |= (uint32_t)fminf(fmaxf(ceilf(over * inv256 + up16), 0.0f), 65535.0f) << (16 * (c & 1));
                 }
-                fine[i] = word;
+                out[i] = word;
+                fine[i] = make_uint2(words[0], words[1]);
             }
+            return;                                           // (all splits are looked up in LDS)
         }
     }
     const uint32_t here = (uint32_t)(M - a.far_splits) * (uint32_t)stride, there = (uint32_t)a.far_splits * (uint32_t)stride;
@@ -698,13 +703,14 @@ __global__ __launch_bounds__(kFilterThreads) void scan_filter_kernel(FilterArgs 
     uint32_t first_in[QL];
     fetch_counts(tid, first_in);
     constexpr int kFineRow = M * kLutStride / 8, kFineVecs = FINE ? QT * kFineRow / NT : 1;   // 16-byte pieces of a query's fine counts, of a thread
-    uint4 fine_in[kFineVecs];
+    uint32_t fine_in[kFineVecs][4];                           // (words: an array of uint4 stays in scratch memory)
     if constexpr (FINE) {
         static_assert(QT * kFineRow % NT == 0, "whole pieces");
 #pragma unroll
         for (int i = 0; i < kFineVecs; ++i) {
             const int at = i * NT + tid, q = at / kFineRow;
-            fine_in[i] = reinterpret_cast<const uint4*>(a.fine)[(size_t)(q0 + (q < nq ? q : 0)) * kFineRow + at % kFineRow];
+            const uint4 x = reinterpret_cast<const uint4*>(a.fine)[(size_t)(q0 + (q < nq ? q : 0)) * kFineRow + at % kFineRow];
+            fine_in[i][0] = x.x; fine_in[i][1] = x.y; fine_in[i][2] = x.z; fine_in[i][3] = x.w;
         }
     }
     FilterQuery my_par[QW];                                   // (a wave per query below, or two queries)
@@ -730,7 +736,7 @@ __global__ __launch_bounds__(kFilterThreads) void scan_filter_kernel(FilterArgs 
     for (int i = tid; i < QT * kFilterBins; i += NT) hist[i] = 0u;
     if constexpr (FINE) {
 #pragma unroll
-        for (int i = 0; i < kFineVecs; ++i) reinterpret_cast<uint4*>(fine)[i * NT + tid] = fine_in[i];
+        for (int i = 0; i < kFineVecs; ++i) reinterpret_cast<uint4*>(fine)[i * NT + tid] = make_uint4(fine_in[i][0], fine_in[i][1], fine_in[i][2], fine_in[i][3]);
     }
     for (uint32_t i = tid; i < pieces; i += NT) {             // entries N_ * (i / G) .. of the queries of lane i % G
         uint32_t in[QL];
