@@ -554,15 +554,25 @@ long long filter_min_items_per_result(long long N, int m, int K, int B, bool sub
     return B <= 256 ? (K > 128 ? 800 : 500) : K > 64 ? 800 : 500;
 }
 
+// Lookups (B * N * m) from which a batch is scanned by pairs of lanes (see plan_filter()).
+double filter_pair_lookups(int m, int K, int B) {
+    return B > 128 && !(m == 8 && B <= 256) ? 5.5e9 : (m == 4 ? 2.0e9 : 1.4e9) * (K > 32 ? 1.5 : 1.0);
+}
+
 // Where 16-bit counts lie in LDS beside the bytes (m = 16; eight queries to a workgroup instead of sixteen): where many items are scored
-// exactly for each that is streamed.  Calls with sixteen queries and bytes alone (K > 32: or 16-bit fields, or by pairs) and with eight and
-// both (us): 500 queries, 100,000 items, K = 2 62 and 64, 6 83 and 61, 24 127 and 71, 60 144 and 89; 250,000, K = 12 128 and 110; 260
-// queries, 50,000, K = 24 46 and 48, 200,000 92 and 65, 600,000, K = 6 95 and 97, 12 106 and 101, 60 169 and 116; 130, 600,000, K = 60 96 and 78,
-// 250,000 62 and 60; 90, 3M, K = 100 180 and 152, 1M, K = 20 67 and 80, 40 75 and 74; 40, 1M, K = 100 53 and 54.  Small catalogues of enough
-// items per result stay with 16-bit fields: 500, 100,000, K = 40 78 and 73, 200 queries 47 and 49.
+// exactly for each that is streamed, which is so the more queries and results and the fewer items there are.  Calls with sixteen queries and bytes alone (K > 32: or
+// 16-bit fields, or by pairs) and with eight and both, as their ratio, at 50,000, 150,000, 350,000, 700,000 and 2M items: 1000 queries, K = 2 1.00 1.05 1.03 0.88
+// 0.74, K = 6 1.44 1.22 1.34 1.06 0.82, K = 20 1.89 1.58 1.32 1.16 1.01; 400 queries, K = 2 0.95 0.96 1.03 0.99 0.85, K = 4 1.02 1.04 1.10 1.03 0.83, K = 20 1.23 1.70 1.46 1.29
+// 1.07; 220 queries, K = 6 0.94 0.88 1.09 1.00 0.89, K = 20 1.00 1.03 1.09 1.03 0.98; 130 queries, K = 6 1.00 0.98 0.98 1.13 1.05, K = 20 1.00 1.03 1.05 1.08 1.04; 100
+// queries, K = 20 1.01 1.03 1.03 0.98 1.08, K = 40 0.99 1.07 1.05 1.05 1.07.  (Many items: sixteen or, by pairs of lanes, 32 queries to a workgroup.)  With few items per
+// result, floors that are not shared and lists to fold other kernels are ahead: 400 queries, 60,000 items, K = 60 55 us by pairs of queries, 81 with counts.
 bool filter_fine_pays(long long N, int m, int K, int B, bool subset, int cw) {
-    return m == 16 && cw == 1 && !subset && K >= 5 && K <= 256 && N < 80000LL * K && !(K > 32 && N >= 2000LL * K && N < 150000) &&
-           (B >= 400 || (N >= 150000 && (B >= 200 || (B > 80 && K > 32))));
+    if (m != 16 || cw != 1 || subset || K > 256 || K < (B > 700 ? 2 : B >= 400 ? 4 : 5)) return false;
+    if (N >= 100000LL * K && (double)B * (double)N * m >= 0.6 * filter_pair_lookups(m, K, B)) return false;
+    if (N < 2000LL * K && !few_share(N, B, m, 8, 12)) return false;
+    if (B >= 400) return true;
+    if (K <= 10) return B >= 250 ? N >= 140000 : B >= 130 && (double)B * (double)N >= 4.6e7;
+    return N >= (B >= 250 ? 60000 : 100000) && B >= (K <= 32 ? 130 : 81);
 }
 
 // Whether a batch is scanned by upper bounds (scan_filter.hpp), and how.
@@ -600,8 +610,7 @@ void plan_filter(ScanPlan& p, long long N, int B, int m, int K, bool subset, int
     // 31.2 and 34.3, 3M 53.9 and 51.2, 8M 108 and 88; 200, 1M 66 and 62, 8M 298 and 246; 500, 1M 112 and 123, 3M 269 and 260; K = 100:
     // 32 queries, 8M 75 and 75, 20M 144 and 126; 200, 3M 154 and 220.  m = 4: 64 queries, 8M 66 and 64, 20M 126 and 120; 500, 3M 160 and 145.
     // m = 16: 32, 3M 56.5 and 54.6, 8M 111 and 97; 200, 1M 105 and 114.  Lists: m = 4, 500 queries, 200,000 candidates 77 and 64, 1M 178 and 130.
-    const double pair_lookups = B > 128 && !(m == 8 && B <= 256) ? 5.5e9 : (m == 4 ? 2.0e9 : 1.4e9) * (K > 32 ? 1.5 : 1.0);
-    const bool pairs = subset ? m == 4 && B >= 400 && N >= 150000 : (double)B * (double)N * m >= pair_lookups && (K <= 32 || B <= 128);
+    const bool pairs = subset ? m == 4 && B >= 400 && N >= 150000 : (double)B * (double)N * m >= filter_pair_lookups(m, K, B) && (K <= 32 || B <= 128);
     // Eight queries to a workgroup instead of sixteen: half as many workgroups share a query, and below some number they share its floors, where
     // much is scored exactly and the streaming that doubles is not the most of it.  Calls with sixteen and eight (us): m = 8, K = 200: 130
     // queries, 1M items (floors not shared, shared) 154 and 77, 300,000 (neither) 53 and 65; 300, 300,000 147 and 78; K = 60: 200 queries, 1M
@@ -644,11 +653,11 @@ void plan_filter(ScanPlan& p, long long N, int B, int m, int K, bool subset, int
     // 3M 427 (16-bit fields) and 275; K = 3, m = 4, 373 queries, 731,549 items 47.4 and 52.3.
     // More than sixteen update one histogram too often for few results, and at m = 64, where 16-bit fields let little pass, for some more: m = 64, 40
     // queries, 1M items, K = 5 143 and 161, 10 147 and 162, 50 229 (1.5M) and 215; 32, 1.5M, K = 5 159 and 182; 56, 2M, K = 20 367 and 342; m = 4, 130,
-    // 4M, K = 3 71.3 and 73.5, 200, K = 10 106 and 94; m = 8, 250, 1.5M, K = 1 69 and 79, 3 75 and 80; m = 16, 180, 700,000, K = 1 71 and 78, 130, 1.5M, K = 3
-    // 105 and 101; m = 32, 180, 1.5M, K = 3 235 and 221.  m = 64, shares of few rounds: 64 queries, 200,000 items (12 rounds), K = 10 69 and 87, K = 100 93
+    // 4M, K = 3 71.3 and 73.5, 200, K = 10 106 and 94; m = 8, 250, 1.5M, K = 1 69 and 79, 3 75 and 80; m = 16, 180, 700,000, K = 1 71 and 78, 220, 700,000, K = 2
+    // 83 and 79; m = 32, 180, 1.5M, K = 3 235 and 221.  m = 64, shares of few rounds: 64 queries, 200,000 items (12 rounds), K = 10 69 and 87, K = 100 93
     // and 116, 450,000 (27) 149 and 153; 100, 300,000 (29) 212 and 192.
     auto shares = [&](long long blocks) {
-        return blocks > 1 && ((blocks <= 16 && rounds / blocks >= (K <= 4 ? 30 : m == 64 ? 28 : 12)) || (blocks <= 32 && rounds / blocks >= 32 && K > (m <= 8 ? 4 : m <= 32 ? 2 : 16))) && words > 1;
+        return blocks > 1 && ((blocks <= 16 && rounds / blocks >= (K <= 4 ? 30 : m == 64 ? 28 : 12)) || (blocks <= 32 && rounds / blocks >= 32 && K > (m <= 8 ? 4 : m <= 32 ? 1 : 16))) && words > 1;
     };
     long long nb = 1;
     double best_us = 0.0;

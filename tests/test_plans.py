@@ -25,3 +25,11 @@ def test_floors_are_shared_where_that_pays(plan, N, B, m, K, shared):
     # m = 64, 1M items, 40 queries, K = 10: 162 us with shared floors, 147 without; 200,000, 64 queries 87 and 69
     p = plan("scan", N, B, m, 256, K)
     assert p["kernel"] == "bounds" and p["shared"] == shared
+
+
+@pytest.mark.parametrize("N,B,K,fine", [(120_000, 1000, 3, 1), (120_000, 260, 12, 1), (120_000, 400, 60, 1), (500_000, 200, 6, 1), (1_500_000, 130, 12, 1), (500_000, 1000, 6, 1),
+                                        (60_000, 400, 60, 0), (1_500_000, 400, 6, 0), (250_000, 130, 12, 0), (120_000, 260, 3, 0), (1_000_000, 300, 6, 0)])
+def test_sixteen_bit_counts_where_they_pay(plan, N, B, K, fine):
+    # m = 16.  120,000 items, 260 queries, K = 12: 53 us without them, 48 with; 60,000, 400, K = 60: 81 with, by pairs of queries 55
+    p = plan("scan", N, B, 16, 256, K)
+    assert p["fine"] == fine
