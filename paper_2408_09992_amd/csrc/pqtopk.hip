@@ -571,8 +571,9 @@ bool filter_fine_pays(long long N, int m, int K, int B, bool subset, int cw) {
     if (N >= 100000LL * K && (double)B * (double)N * m >= 0.6 * filter_pair_lookups(m, K, B)) return false;
     if (N < 2000LL * K && !few_share(N, B, m, 8, 12)) return false;
     if (B >= 400) return true;
-    if (K <= 10) return B >= 250 ? N >= 140000 : B >= 130 && (double)B * (double)N >= 4.6e7;
-    return N >= (B >= 250 ? 60000 : 100000) && B >= (K <= 32 ? 130 : 81);
+    if (B >= 250) return N >= (K <= 10 ? 140000 : 60000);
+    if (K <= 16) return B >= 130 && (double)B * (double)N >= 4.6e7;   // (130 queries, 250,000 items, K = 12: 43.9 without, 49.6 with)
+    return N >= 100000 && B >= (K <= 32 ? 130 : 81);
 }
 
 // Whether a batch is scanned by upper bounds (scan_filter.hpp), and how.
