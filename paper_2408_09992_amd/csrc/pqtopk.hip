@@ -639,7 +639,7 @@ void plan_filter(ScanPlan& p, long long N, int B, int m, int K, bool subset, int
     }
     if (words == 0) return;
     const int row = m * cw, queries = words * fields * lanes;
-    const long long together = (long long)(kFilterTableBytes / ((size_t)entries * sizeof(uint16_t))), turns = (B + together - 1) / together;
+    const long long together = (long long)(kFilterTableBytes / ((size_t)entries * (fine ? 3 : 2))), turns = (B + together - 1) / together;
     const int batch = turns == 1 ? B : (int)std::min<long long>(((B + turns - 1) / turns + 31) & ~31LL, B);
     const long long tiles = (batch + queries - 1) / queries;
     const bool by_vector = row <= 16 && !subset;

@@ -340,6 +340,17 @@ def test_workspace_of_large_batches_is_bounded(lib):
                     assert wsub(2_000_000, B, m, 256, K) <= most, (m, B, K)
 
 
+def test_workspace_of_large_batches_with_two_kinds_of_counts_is_bounded(lib):
+    """... with 16-bit counts beside the bytes too: they are tables as well."""
+    from paper_2408_09992_amd import binding
+    ws, wsub = lib.pq_score_topk_workspace_bytes, lib.pq_score_topk_subset_workspace_bytes
+    for B in (5461, 8192, 16_384, 30_000, 65_535):
+        for N, K in ((200_000, 50), (500_000, 100), (1_000_000, 100)):
+            for call, kind, m in ((ws, "scan", 16), (wsub, "subset", 8)):
+                lists = 8 * K * B * binding.pq_measure_plan(kind, N, B, m, 256, K)["groups"]
+                assert call(N, B, m, 256, K) <= lists + (64 << 20) + (10 << 20), (kind, B, N, K)
+
+
 def test_plans_the_gpu_tests_count_on(pqlib_path):
     """The shapes of the GPU tests lead where those tests say (the planner is host arithmetic)."""
     from paper_2408_09992_amd import binding
