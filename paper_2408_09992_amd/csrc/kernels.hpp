@@ -131,7 +131,7 @@ namespace pqk {
 #define PQ_FILTER_STAMPED(X, M, G) X(M, 1, 4, false, false, G, false, true) X(M, 1, 4, false, false, G, true, true)
 #define PQ_FILTER_INSTANCES_STAMPED(X) PQ_FILTER_STAMPED(X, 8, 1) PQ_FILTER_STAMPED(X, 8, 2) PQ_FILTER_STAMPED(X, 16, 1)
 // ... and those with 16-bit counts beside the bytes
-#define PQ_FILTER_INSTANCES_FINE(X) X(16, 1, 2, false, false, 1, false, false, true) X(16, 1, 2, false, false, 1, true, false, true)
+#define PQ_FILTER_INSTANCES_FINE(X) X(16, 1, 2, false, false, 1, false, false, true) X(16, 1, 2, false, false, 1, true, false, true) X(8, 1, 4, false, true, 1, true, false, true)
 // the batched kernel
 #define PQ_TILED_INSTANCES(X) X(8, false) X(16, false) X(8, true) X(16, true)
 

@@ -639,7 +639,9 @@ void plan_filter(ScanPlan& p, long long N, int B, int m, int K, bool subset, int
     }
     if (words == 0) return;
     const int row = m * cw, queries = words * fields * lanes;
-    const long long together = (long long)(kFilterTableBytes / ((size_t)entries * (fine ? 3 : 2))), turns = (B + together - 1) / together;
+    // (lists of m = 8 whose floors are shared have 16-bit counts beside the bytes, see below)
+    const bool fine_list = subset && m == 8 && words == 4 && filter_lds_bytes(m, stride, words, w16, lanes, cap, true) <= kMaxLdsBytes;
+    const long long together = (long long)(kFilterTableBytes / ((size_t)entries * (fine || fine_list ? 3 : 2))), turns = (B + together - 1) / together;
     const int batch = turns == 1 ? B : (int)std::min<long long>(((B + turns - 1) / turns + 31) & ~31LL, B);
     const long long tiles = (batch + queries - 1) / queries;
     const bool by_vector = row <= 16 && !subset;
@@ -717,8 +719,11 @@ void plan_filter(ScanPlan& p, long long N, int B, int m, int K, bool subset, int
     p.f_far = filter_far_splits(m, words, w16, lanes);
     p.f_pitch = align16((size_t)(m - p.f_far) * stride * (w16 ? sizeof(uint16_t) : sizeof(uint8_t)));
     p.nblk = (int)nb;
-    p.f_fine = fine;
-    p.scan_lds = filter_lds_bytes(m, stride, words, w16, lanes, cap, fine);
+    // Lists: what an item costs that passes is its row from another place in memory.  m = 8, floors shared, without 16-bit counts and with (us): 200,000 candidates, 500
+    // queries, K = 10 85 and 80, K = 100 133 and 118, 1000, K = 100 222 and 199; 1M, 500, K = 10 210 and 184, K = 100 281 and 253; 200, K = 10 123 and 111.  Not shared:
+    // 64, 200,000 28.6 and 35.0, 1M, K = 10 51 and 57.
+    p.f_fine = fine || (fine_list && p.f_share);
+    p.scan_lds = filter_lds_bytes(m, stride, words, w16, lanes, cap, p.f_fine);
     // (one-byte sub-ids: the tables are a static array)
     p.scan_dyn_lds = p.scan_lds - (cw == 2 ? 0 : filter_table_bytes(m, stride, words, w16, lanes));
 }
@@ -1036,6 +1041,9 @@ hipError_t launch_filter(const ScanPlan& p, const FilterArgs& a, hipStream_t st)
     }
     if constexpr (M == 16 && CW == 1 && !SUB) {
         if (p.f_fine) return p.f_share ? go(scan_filter_kernel<16, 1, 2, false, false, 1, true, false, true>) : go(scan_filter_kernel<16, 1, 2, false, false, 1, false, false, true>);
+    }
+    if constexpr (M == 8 && CW == 1 && SUB) {
+        if (p.f_fine) return go(scan_filter_kernel<8, 1, 4, false, true, 1, true, false, true>);
     }
     if constexpr ((M == 16 || M == 32) && CW == 1) {
         if (p.f_w16 && p.f_words == 4) return p.f_share ? go(scan_filter_kernel<M, 1, 4, true, SUB, 1, true>) : go(scan_filter_kernel<M, 1, 4, true, SUB, 1, false>);

@@ -512,7 +512,7 @@ __global__ __launch_bounds__(NT, M <= 16 ? 8 : 4) void filter_prepare_kernel(Fil
         const float x = ceilf((lut[e] - bases[e / (uint32_t)stride]) * per + up);
         return (uint32_t)fminf(fmaxf(x, 0.0f), 255.0f);
     };
-    if constexpr (M == 16 && CW == 1 && !SUB) {
+    if constexpr (CW == 1 && (SUB ? M == 8 : M == 16)) {
         if (a.fine != nullptr) {                              // (and 16-bit counts beside them, from the same read of the table)
             uint2* const fine = reinterpret_cast<uint2*>(a.fine + (size_t)q * a.entries);
             const float inv256 = nothing ? 0.0f : inv * 256.0f, up16 = nothing ? 0.0f : kFilterUp16;
