@@ -121,7 +121,7 @@ namespace pqk {
 #define PQ_FILTER_INSTANCES_C(X, Y) \
     X(32, 1, 1, false, false, 1, false) PQ_FILTER_BOTH(X, 32, 1, 2, false, false, 1) PQ_FILTER_BOTH(X, 32, 1, 4, false, false, 1) \
     PQ_FILTER_BOTH(X, 32, 1, 2, true, false, 1) PQ_FILTER_BOTH(X, 32, 1, 4, true, false, 1) \
-    X(64, 1, 1, true, false, 1, false) PQ_FILTER_BOTH(X, 64, 1, 2, true, false, 1) Y(32, 1, false) Y(64, 1, false)
+    PQ_FILTER_BOTH(X, 64, 1, 1, true, false, 1) PQ_FILTER_BOTH(X, 64, 1, 2, true, false, 1) Y(32, 1, false) Y(64, 1, false)
 // (lists: pairs of lanes at m = 4 alone; m = 16: eight queries of bytes are a workgroup's where there are no more, over too short shares to share floors)
 #define PQ_FILTER_INSTANCES_SUBSET(X, Y) PQ_FILTER_G(X, 4, 1, true) PQ_FILTER_W(X, 8, 1, true) Y(4, 1, true) Y(8, 1, true)
 #define PQ_FILTER_INSTANCES_SUBSET16(X, Y) X(16, 1, 1, false, true, 1, false) X(16, 1, 2, false, true, 1, false) PQ_FILTER_BOTH(X, 16, 1, 4, false, true, 1) PQ_FILTER_BOTH(X, 16, 1, 4, true, true, 1) Y(16, 1, true)

@@ -40,3 +40,10 @@ def test_lists_have_sixteen_bit_counts_where_floors_are_shared(plan, n, B, K, fi
     # m = 8.  1M candidates, 500 queries, K = 10: 210 us without, 184 with; not shared, 64 queries: 51 and 57
     p = plan("subset", n, B, 8, 256, K)
     assert p["fine"] == p["shared"] == fine
+
+
+@pytest.mark.parametrize("N,B,K", [(600_000, 141, 500), (1_100_000, 300, 294)])
+def test_floors_are_shared_by_two_queries_of_64_splits_too(plan, N, B, K):
+    # 600,000 items, 141 queries, K = 500: 1258 us without, 731 with
+    p = plan("scan", N, B, 64, 256, K)
+    assert p["kernel"] == "bounds" and p["queries"] == 2 and p["shared"] == 1
