@@ -651,6 +651,7 @@ void plan_filter(ScanPlan& p, long long N, int B, int m, int K, bool subset, int
     const long long rounds = (units + per_round - 1) / per_round;
     // Item blocks per tile: one workgroup per CU, or a few one after the other when one filling would leave CUs idle.
     const double stream_us = (double)N * m * lanes / (rate * 2400.0);
+    const double gather_us = subset && m == 4 ? (double)N / 2400.0 : 0.0;   // (a row per clock, longer than four lookups take)
     // Workgroups of a query share their floors where they are few and their shares long, a round being a unit of every wave (one word:
     // batches of a few queries, but at m = 64, whose tables leave room for no more beside many results).  K = 100, not shared and shared (us): m = 4, 200 queries, 8M items 236 and 179; m = 8, 3M 193 and 154; m = 16,
     // 3M 427 (16-bit fields) and 275; K = 3, m = 4, 373 queries, 731,549 items 47.4 and 52.3.
@@ -672,8 +673,12 @@ void plan_filter(ScanPlan& p, long long N, int B, int m, int K, bool subset, int
         // 200 queries, 1M of 4M items, m = 8, K = 10: 234 us with 19 blocks, 109 with 16)
         if (subset && (cand & 7) * (N >= 150000 ? 2 : 5) <= cand) cand = cand < 8 ? cand : cand & ~7LL;
         const double per_cu = (double)((tiles * cand + kAssumedCUs - 1) / kAssumedCUs);
-        // (workgroups that share their floors score less)
-        const double us = per_cu * (stream_us / (double)cand * (shares(cand) ? 1.0 : 1.2) + 8.0);
+        // (workgroups that share their floors, or scan everything for their queries, score less.  In a list an item that is scored exactly costs its row from
+        // another place in memory too, the more items the more results: with and without this term, 1M candidates, 300 queries, m = 8 (8 workgroups per query that share, 24
+        // that do not), K = 10 151 and 178 us, K = 100 199 and 331, K = 200 292 and 526; 3M, 305, m = 4, K = 200 666 and 971; m = 16, 180, K = 100 220 and 342)
+        const bool alike = cand == 1 || shares(cand);
+        const double list_us = subset ? (alike ? 0.15 : 0.75) * K * queries / 16.0 : 0.0;
+        const double us = per_cu * ((stream_us + gather_us) / (double)cand * (alike ? 1.0 : 1.2) + 8.0 + list_us);
         if (fill == 1 || us < best_us) { best_us = us; nb = cand; }
     }
     p.filter = true;

@@ -47,3 +47,13 @@ def test_floors_are_shared_by_two_queries_of_64_splits_too(plan, N, B, K):
     # 600,000 items, 141 queries, K = 500: 1258 us without, 731 with
     p = plan("scan", N, B, 64, 256, K)
     assert p["kernel"] == "bounds" and p["queries"] == 2 and p["shared"] == 1
+
+
+@pytest.mark.parametrize("kind,N,B,m,K,groups", [("subset", 1_000_000, 300, 8, 100, 8), ("subset", 3_000_000, 305, 4, 200, 8), ("subset", 1_000_000, 180, 16, 100, 8),
+                                                 ("subset", 1_000_000, 200, 8, 10, 16), ("scan", 142_000, 1013, 64, 82, 1), ("scan", 400_000, 1013, 64, 82, 1)])
+def test_workgroups_that_share_floors_or_scan_everything_score_less(plan, kind, N, B, m, K, groups):
+    # lists of 1M candidates, 300 queries, m = 8, K = 100: 331 us with 24 workgroups per query that do not share, 199 with 8 that do; 142,000 items of
+    # 64 splits, 1013 queries, K = 82: 797 with two per query, 654 with one
+    p = plan(kind, N, B, m, 256, K)
+    assert p["kernel"] == "bounds" and p["groups"] == groups
+    assert p["shared"] == (groups > 1)
