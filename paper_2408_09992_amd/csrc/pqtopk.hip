@@ -704,7 +704,11 @@ void plan_filter(ScanPlan& p, long long N, int B, int m, int K, bool subset, int
     p.f_patient = p.f_share && nb <= 16 && rounds / nb >= 32;
     const long long items_per_round = (long long)p.f_sample * N / units;
     long long want = (long long)((K <= 16 && B > 128 && !subset && !p.f_share ? 8.0 : 5.0) * sqrt((double)K * (double)N)) / items_per_round;
-    const long long most_rounds = (nb > 16 ? 4 : K <= 32 ? 1 : m == 4 ? 4 : m == 8 ? 2 : 1) * (kFilterThreads / p.f_prepare);
+    // (... but at m = 32, where an exact score costs most, not within so short a time, if the catalogue is worth the sample: one round and four, 500,000 items, 480 queries,
+    // K = 10 428 and 301, 800,000, 900, K = 20 1169 and 928, K = 30 (16-bit fields) 1139 and 1087; 200,000, 70, K = 100 66 and 80.  m = 16 with bytes alone, one and two: 900,
+    // 500,000, K = 5 231 and 212)
+    const long long few_rounds = K <= 32 ? (m == 16 && !fine && !w16 && !subset ? 2 : 1) : m == 4 ? 4 : m == 8 ? 2 : 1;
+    const long long most_rounds = (nb > 16 ? 4 : m == 32 ? std::min<long long>(4, 1 + N / 170000) : few_rounds) * (kFilterThreads / p.f_prepare);
     if (p.f_share && want > most_rounds) want = most_rounds;
     if (want > N / 8 / items_per_round) want = N / 8 / items_per_round;
     if (want < 1) want = 1;

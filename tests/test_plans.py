@@ -57,3 +57,10 @@ def test_workgroups_that_share_floors_or_scan_everything_score_less(plan, kind, 
     p = plan(kind, N, B, m, 256, K)
     assert p["kernel"] == "bounds" and p["groups"] == groups
     assert p["shared"] == (groups > 1)
+
+
+@pytest.mark.parametrize("N,B,m,K,rounds", [(800_000, 300, 32, 10, 4), (1_500_000, 300, 32, 20, 4), (100_000, 400, 32, 10, 1), (500_000, 480, 16, 3, 2), (500_000, 480, 8, 10, 1)])
+def test_samples_before_shared_floors(plan, N, B, m, K, rounds):
+    # m = 32, 800,000 items, 300 queries, K = 10: 355 us with one round, 277 with four
+    p = plan("scan", N, B, m, 256, K)
+    assert p["kernel"] == "bounds" and p["shared"] == 1 and p["fine"] == 0 and p["rounds"] == rounds
