@@ -231,16 +231,22 @@ double filter_min_lookups(int m, int K, int B, bool subset, int cw);
 // Lists: the rows that are gathered, once per pair and at most, against once per sixteen queries. By bounds and by pairs: m = 8, 17,851 candidates, 158
 // queries 22.7 and 16.1, 100,000, 100 25.7 and 42.3, 900,000, 4 38 and 26, 6 39 and 53, 2M, 2 60 and 46, 4 60 and 82; m = 4, 900,000, 4 36 and 23, 2M, 4 55 and 73;
 // m = 16, 400,000, 4 28 and 18, 6 28 and 31, 900,000, 4 37 and 42, 2M, 2 58 and 49.
-bool pair_beats_bounds(long long N, int B, int m, int K, bool subset, int cw) {
+// Few results: m = 16 with more than 24 vectors to a thread (`held`; one workgroup to a compute unit), 40,000 items, 450 queries, K = 5 41.1 and 45.2, 650 49.5 and 67.1, 800,
+// K = 16 60.4 and 87.7, 35,000, 600, K = 2 41.5 and 59.5, K = 20 71.1 and 62.0; m = 32, 30,000, 530, K = 2 70.5 and 84.8, 800, K = 5 96 and 119, 450, K = 5 66.8 and 60.8, 650,
+// K = 10 94.6 and 88.6, 40,000, 800, K = 10 114 and 149.
+bool pair_beats_bounds(long long N, int B, int m, int K, bool subset, int cw, int held) {
     const double all = (double)B * (double)N * m, least = filter_min_lookups(m, K, B, subset, cw);
     if (subset) return N * ((B + 1) / 2) <= (m == 16 && B > 2 ? 1000000 : 2100000);
+    if (cw == 1 && m == 16 && B > kAssumedCUs && held > 24 && K <= (N >= 38000 ? 20 : 4) && N >= 33000) return false;
+    if (cw == 1 && m == 32 && B > 2 * kAssumedCUs && K <= 10 && N >= (K <= 5 ? 26000 : 36000)) return false;
     return m > 4 && (all < 1.35 * least || N < (m > 8 ? 48000 : K >= 32 ? 40000 : 24000));
 }
 // Workgroups whose last round would leave more than a quarter of the compute units' time idle (10,045 candidates, m = 16, 538 queries: 269
 // workgroups 54.4 us, by the general kernel 40.0; 17,113, 531: 532 69.7 and 58.2; 16,000, 700: 700 42.2 and 57.1).
-bool last_round_empty(long long groups) {
+// (`idle`: per cent.)  Rows of 16 bytes, at 16,000 candidates and more, from an eighth on: 17,780, 652, K = 1 (15 %) 66.9 and 57.4.
+bool last_round_empty(long long groups, int idle = 25) {
     const long long rounds = (groups + kAssumedCUs - 1) / kAssumedCUs;
-    return rounds > 1 && 4 * groups < 3 * rounds * kAssumedCUs;
+    return rounds > 1 && 100 * groups < (100 - idle) * rounds * kAssumedCUs;
 }
 // Candidate lists by two queries per workgroup (scan_subset_pair_kernel; us, without): instead of the general kernel, m = 8: 11,583 candidates, 172
 // queries, K = 48 32.6 and 16.8; 100,000, 30, K = 300 48.1 and 23.8; m = 16: 17,825, 162 29.7 and 19.6, 76,492, 296, K = 422 198 and 169, 5086,
@@ -453,7 +459,19 @@ ScanPlan make_plan(long long N, int B, int m, int K, bool generic = false, int c
                 const double us = (double)((pairs * c + kAssumedCUs - 1) / kAssumedCUs) * (5.0 + lookups / (double)c / kPairLookupsPerUs) + (c > 1 ? 3.0 : 0.0);
                 if (nb == 0 || us < best_us) { best_us = us; nb = c; }
             }
-            p.pair_scan = (forced & 256) || B <= kAssumedCUs || nb <= cw || K <= (m <= 16 && B > 2 * kAssumedCUs && nb > 2 ? 16 : 128);
+            const bool alone = p.short_scan && p.nblk == 1;   // otherwise: one workgroup per query, without lists
+            p.pair_scan = B <= kAssumedCUs || nb <= cw || K <= (m <= 16 && B > 2 * kAssumedCUs && nb > 2 ? 16 : 128);
+            // More than 512 queries take several rounds of workgroups.  Pairs and without (us): a workgroup each, the last round far from full, m = 8, 17,000 items, K = 150, 600
+            // queries 46.5 and 39.0, 900 (full) 47.4 and 51.9; m = 16, 9000, K = 150, 720 37.3 and 27.1; m = 8, 5000, K = 2, 600 9.4 and 8.6; m = 32, 5000, K = 150, 900 45.9 and
+            // 36.3, 12,000, 650, K = 100 65.2 and 55.8.  m = 16 from 25 vectors to a thread on, one workgroup to a compute unit, in four rounds: 30,000 items, 800, K = 10 70.7 and
+            // 57.1, K = 100 90.6 and 77.1 (22,000, two to a compute unit 42.8 and 46.0)
+            const long long held = (units + kThreads * nb - 1) / (kThreads * nb);
+            if (B > 2 * kAssumedCUs) {
+                if (alone && nb == 1 && last_round_empty(pairs) && (K > 128 || (K <= 10 && N * m < 60000))) p.pair_scan = false;
+                if (alone && m == 32 && K > (nb == 1 ? 128 : 64)) p.pair_scan = false;
+                if (cw == 1 && m == 16 && held > 24 && pairs * nb > 3 * kAssumedCUs) p.pair_scan = false;
+            }
+            p.pair_scan = p.pair_scan || (forced & 256);
             // (one workgroup to a compute unit: 718 queries of 4500 items, two bytes, m = 16, b = 619 17.1 us without, 19.6)
             if (!(forced & 256) && p.short_scan && 2 * lds > kMaxLdsBytes && last_round_empty(pairs * nb)) p.pair_scan = false;
             // (rows of 4 bytes, lists to fold: 3M items, 5 queries, K = 80 28.4 us without, 31.2)
@@ -479,7 +497,7 @@ ScanPlan make_plan(long long N, int B, int m, int K, bool generic = false, int c
         if (N * (m + 8) >= 120000 * (nb < 1 ? 1 : nb)) nb = 2 * kAssumedCUs / pairs;
         nb = nb < least ? least : nb > thin ? thin : nb;
         if (nb < 1) nb = 1;
-        if (least <= kAssumedCUs && ((forced & 256) || !last_round_empty(pairs * nb))) {
+        if (least <= kAssumedCUs && ((forced & 256) || !last_round_empty(pairs * nb, m == 16 && N >= 16000 ? 12 : 25))) {
             p.subset_pair = true;
             p.short_subset = false;
             p.subset_vecs = (int)(((N + kThreads * nb - 1) / (kThreads * nb) * m + 15) / 16);
@@ -490,7 +508,7 @@ ScanPlan make_plan(long long N, int B, int m, int K, bool generic = false, int c
         }
     }
     p.filter = false;
-    const bool pair_first = (p.pair_scan || p.subset_pair) && !(forced & (16 | 128)) && ((forced & 256) || pair_beats_bounds(N, B, m, K, p.subset_pair, cw));
+    const bool pair_first = (p.pair_scan || p.subset_pair) && !(forced & (16 | 128)) && ((forced & 256) || pair_beats_bounds(N, B, m, K, p.subset_pair, cw, p.short_units));
     if (!(without & kNoFilter) && !pair_first) {
         ScanPlan f = p;
         plan_filter(f, N, B, m, K, generic, cw, b);

@@ -64,3 +64,12 @@ def test_samples_before_shared_floors(plan, N, B, m, K, rounds):
     # m = 32, 800,000 items, 300 queries, K = 10: 355 us with one round, 277 with four
     p = plan("scan", N, B, m, 256, K)
     assert p["kernel"] == "bounds" and p["shared"] == 1 and p["fine"] == 0 and p["rounds"] == rounds
+
+
+@pytest.mark.parametrize("kind,N,B,m,K,pairs", [
+    ("scan", 17_000, 600, 8, 150, 0), ("scan", 17_000, 900, 8, 150, 1), ("scan", 9000, 720, 16, 150, 0), ("scan", 5000, 600, 8, 2, 0), ("scan", 12_000, 650, 32, 100, 0),
+    ("scan", 30_000, 800, 16, 100, 0), ("scan", 22_000, 800, 16, 10, 1), ("scan", 22_000, 530, 16, 100, 1), ("scan", 40_000, 450, 16, 5, 0), ("scan", 35_000, 600, 16, 2, 0),
+    ("scan", 35_000, 600, 16, 20, 1), ("scan", 40_000, 800, 32, 10, 0), ("scan", 30_000, 450, 32, 5, 1), ("subset", 17_780, 652, 16, 1, 0), ("subset", 17_825, 162, 16, 10, 1)])
+def test_two_queries_per_workgroup_where_that_pays(plan, kind, N, B, m, K, pairs):
+    # m = 16, 40,000 items, 800 queries, K = 10: 86.8 us by pairs, 56 by bounds; 9000, 720, K = 150 37 and 27 by one workgroup per query
+    assert (plan(kind, N, B, m, 256, K)["kernel"] in ("pairs", "list pairs")) == bool(pairs)
