@@ -354,12 +354,29 @@ def test_workspace_of_large_batches_with_two_kinds_of_counts_is_bounded(lib):
 def test_plans_the_gpu_tests_count_on(pqlib_path):
     """The shapes of the GPU tests lead where those tests say (the planner is host arithmetic)."""
     from paper_2408_09992_amd import binding
-    from test_parity_gpu import SHARED_FLOORS
-    seen = set()
+    from test_parity_gpu import MORE_INSTANCES, SHARED_FLOORS
+    seen, instances = set(), set()
     for kind, N, B, m, b, K in SHARED_FLOORS:
         p = binding.pq_measure_plan(kind, N, B, m, b, K)
         assert p["kernel"] == "bounds" and p["shared"] == 1 and p["groups"] > 1, (kind, N, B, m, b, K, p)
         seen.add((kind, m, p["field_bits"], p["fine"]))
+        instances.add((kind, m, p["queries"], p["field_bits"], p["fine"]))
+    for kind, N, B, m, b, K, mask, queries, bits, shared in MORE_INSTANCES:
+        binding.pq_measure_force_general(mask)
+        try:
+            p = binding.pq_measure_plan(kind, N, B, m, b, K)
+        finally:
+            binding.pq_measure_force_general(0)
+        assert (p["kernel"], p["queries"], p["field_bits"], p["shared"]) == ("bounds", queries, bits, shared), (kind, N, B, m, b, K, p)
+        if shared:
+            instances.add((kind, m, queries, bits, p["fine"]))
+    # (sharing floors is a template parameter: every pair of it and the rest that is compiled)
+    queries = {("scan", 4): (8, 16, 32), ("scan", 8): (8, 16, 32), ("scan", 16): (8, 16, 32), ("scan", 32): (8, 16), ("scan", 64): (), ("subset", 4): (8, 16, 32),
+               ("subset", 8): (8, 16), ("subset", 16): (16,), ("scan16", 4): (8, 16, 32), ("scan16", 8): (8, 16, 32), ("scan16", 16): (8, 16, 32)}
+    want = {(k, m, q, 8, 0) for (k, m), each in queries.items() for q in each}
+    want |= {("scan", 16, 8, 8, 1), ("subset", 8, 16, 8, 1)}
+    want |= {("scan", 16, 8, 16, 0), ("scan", 32, 8, 16, 0), ("scan", 32, 4, 16, 0), ("scan", 64, 4, 16, 0), ("scan", 64, 2, 16, 0), ("subset", 16, 8, 16, 0)}
+    assert instances == want, instances ^ want
     assert {(k, m) for k, m, _, _ in seen} == {("scan", m) for m in (4, 8, 16, 32, 64)} | {(k, m) for k in ("subset", "scan16") for m in (4, 8, 16)}
     assert {bits for k, m, bits, _ in seen if m == 16 and k == "scan"} == {8, 16}
     with pytest.raises(binding.PQError):

@@ -370,7 +370,7 @@ def test_scan_by_upper_bounds(pq, oracle, m, N, B, K, b):
     _bounds_case(pq, oracle, codes, S, K)
 
 
-@pytest.mark.parametrize("B", [1024, 1025, 2100])              # (1024 queries' tables are what one turn holds at m = 64)
+@pytest.mark.parametrize("B", [2048, 2049, 4100])              # (2048 queries' tables are what one turn holds at m = 64)
 def test_scan_by_upper_bounds_in_turns(pq, oracle, B):
     rng = np.random.default_rng(B)
     _bounds_case(pq, oracle, rng.integers(0, 256, (3_001, 64), dtype=np.uint8), rng.standard_normal((B, 64, 256), dtype=np.float32), 3)
@@ -504,7 +504,7 @@ def _odd_tables(kind, S):
                                   "high_and_masked", "heavy_tails", "far_offset"])
 def test_scan_by_upper_bounds_of_tables_that_are_not_bell_shaped(pq, oracle, kind):
     rng = np.random.default_rng(11)
-    for m, N, B, K in ((4, 30_003, 7, 10), (8, 60_001, 18, 100), (8, 400_001, 6, 10), (16, 90_001, 5, 10), (16, 50_000, 9, 40), (64, 40_001, 5, 3)):
+    for m, N, B, K in ((4, 30_003, 7, 10), (8, 60_001, 18, 100), (8, 400_001, 6, 10), (16, 90_001, 5, 10), (16, 50_000, 9, 40), (32, 150_001, 3, 10), (32, 60_001, 18, 3), (64, 40_001, 5, 3)):
         print(f"case {kind} m={m} N={N} B={B} K={K}", flush=True)
         codes = rng.integers(0, 256, (N, m), dtype=np.uint8)
         S = _odd_tables(kind, rng.standard_normal((B, m, 256), dtype=np.float32))
@@ -516,10 +516,11 @@ def test_scan_by_upper_bounds_of_tables_that_are_not_bell_shaped(pq, oracle, kin
 
 
 @pytest.mark.parametrize("kind", ["rare_high", "denormal", "equal_rows", "mixed"])
-@pytest.mark.parametrize("m,K", [(4, 10), (8, 1), (8, 100), (8, 300), (16, 10), (16, 40), (32, 10), (64, 5)])
+@pytest.mark.parametrize("m,K", [(4, 10), (8, 1), (8, 100), (8, 300), (16, 10), (16, 40), (32, 3), (32, 10), (64, 5)])
 def test_queries_that_the_bounds_are_no_use_for(pq, oracle, m, K, kind):
     # a large entry that five items have, sums that hardly differ, a catalogue of seven rows: such queries are scanned a second
     # time, exactly; "mixed" has them beside ordinary ones in a tile (more of them than one pass takes)
+    # (m = 32: with three results in bytes, whose tables leave four splits in device memory, with ten in 16 bits)
     rng = np.random.default_rng(m + K)
     N, B = 60_003, 13
     codes = rng.integers(0, 256, (N, m), dtype=np.uint8)
@@ -551,8 +552,12 @@ SHARED_FLOORS = [("scan", 271_046, 1650, 4, 256, 10), ("scan", 137_321, 1650, 8,
 @pytest.mark.parametrize("tables", ["bell", "ties", "given_up"])
 @pytest.mark.parametrize("kind,N,B,m,b,K", SHARED_FLOORS)
 def test_floors_shared_between_workgroups(pq, oracle, kind, N, B, m, b, K, tables):
-    # all queries against the kernels that do not scan by bounds, every ninth against the oracle
     assert pq.pq_measure_plan(kind, N, B, m, b, K)["shared"] == 1
+    _large_batch_case(pq, oracle, kind, N, B, m, b, K, tables)
+
+
+def _large_batch_case(pq, oracle, kind, N, B, m, b, K, tables, mask=0):
+    # all queries against the kernels that do not scan by bounds, every ninth against the oracle
     rng = np.random.default_rng(N + B)
     items = N + N // 3 if kind == "subset" else N
     codes = rng.integers(0, b, (items, m), dtype=np.uint16 if kind == "scan16" else np.uint8)
@@ -572,7 +577,11 @@ def test_floors_shared_between_workgroups(pq, oracle, kind, N, B, m, b, K, table
         ids, sc = call(Gd, Sd, K) if call else pq.pq_score_topk_subset(Gd, Sd, Vd, K)
         return ids.cpu().numpy(), sc.cpu().numpy()
 
-    ids, sc = run()
+    before = pq.pq_measure_force_general(mask)
+    try:
+        ids, sc = run()
+    finally:
+        pq.pq_measure_force_general(before)
     prev = pq.pq_measure_force_general(8)
     try:
         want_ids, want_sc = run()
@@ -585,6 +594,32 @@ def test_floors_shared_between_workgroups(pq, oracle, kind, N, B, m, b, K, table
     else:
         rid, rsc = (oracle.score_topk_u16 if kind == "scan16" else oracle.score_topk)(codes, some, K)
     assert np.array_equal(ids[::9], rid) and np.array_equal(sc[::9].view(np.uint32), rsc.view(np.uint32))
+
+
+# Every instance of the scan by bounds that batches reach beyond those above: how many queries a workgroup takes, the width of the fields, whether
+# workgroups share floors.  The mask keeps a shape on pairs of lanes (16 | 128), or on bounds (16).  kind, N, B, m, b, K, mask, queries, field bits, shared
+MORE_INSTANCES = [("scan", 116_559, 700, 4, 256, 150, 0, 8, 8, 1), ("scan", 102_643, 1639, 4, 256, 17, 144, 32, 8, 1), ("scan", 89_267, 530, 8, 256, 100, 0, 8, 8, 1),
+                  ("scan", 49_733, 1701, 8, 256, 100, 144, 32, 8, 1), ("scan", 245_754, 122, 16, 256, 300, 0, 8, 8, 1), ("scan", 49_584, 180, 16, 256, 40, 0, 8, 16, 0),
+                  ("scan", 33_868, 1367, 16, 256, 17, 0, 16, 8, 1), ("scan", 80_787, 1456, 16, 256, 1, 144, 32, 8, 1), ("scan", 111_981, 107, 32, 256, 100, 0, 4, 16, 1),
+                  ("scan", 150_001, 3, 32, 256, 10, 16, 4, 8, 0), ("scan", 150_001, 7, 32, 256, 10, 16, 8, 8, 0), ("scan", 1_012_270, 65, 32, 256, 100, 0, 8, 8, 1),
+                  ("scan", 50_522, 139, 32, 256, 3, 0, 16, 8, 0), ("scan", 205_001, 260, 32, 256, 5, 0, 16, 8, 1), ("scan", 301_275, 48, 64, 256, 300, 0, 2, 16, 1),
+                  ("scan16", 215_005, 262, 4, 700, 100, 0, 8, 8, 1), ("scan16", 49_299, 1768, 4, 700, 17, 144, 32, 8, 1), ("scan16", 25_487, 1678, 8, 300, 100, 144, 32, 8, 1),
+                  ("scan16", 106_277, 232, 16, 700, 10, 0, 8, 8, 1), ("scan16", 32_281, 1435, 16, 257, 10, 144, 32, 8, 1), ("subset", 415_600, 131, 4, 256, 400, 0, 8, 8, 1),
+                  ("subset", 398_141, 257, 4, 256, 17, 0, 16, 8, 1), ("subset", 194_850, 137, 8, 256, 300, 0, 8, 8, 1), ("subset", 201_753, 273, 8, 256, 150, 0, 16, 8, 1),
+                  ("subset", 212_279, 162, 16, 256, 10, 0, 16, 8, 1)]
+
+
+@pytest.mark.parametrize("kind,N,B,m,b,K,mask,queries,bits,shared", MORE_INSTANCES)
+def test_every_other_instance_of_the_scan_by_bounds(pq, oracle, kind, N, B, m, b, K, mask, queries, bits, shared):
+    prev = pq.pq_measure_force_general(mask)
+    try:
+        p = pq.pq_measure_plan(kind, N, B, m, b, K)
+    finally:
+        pq.pq_measure_force_general(prev)
+    assert (p["kernel"], p["queries"], p["field_bits"], p["shared"]) == ("bounds", queries, bits, shared)
+    for tables in ("bell", "ties", "given_up"):
+        print(f"{tables}", flush=True)
+        _large_batch_case(pq, oracle, kind, N, B, m, b, K, tables, mask)
 
 
 @pytest.mark.parametrize("kind", ["zero_queries", "one_masked", "each_masked", "lowest"])
@@ -914,13 +949,20 @@ def test_list_pairs(pq, oracle, m, n, B, K):
 
 
 def test_small_fold_many_lists(pq, oracle):
-    # the small-K fold with both of its instances: up to 3072 and up to 6144 keys per query (256 lists of K = 10, 24; with
-    # K = 28, 31 the 256 lists go to the general fold: a third instance of 16 keys per thread was slower than it),
-    # a batch of queries folded side by side, and lists with empty slots (fewer than K items in a workgroup's share)
-    for N, B, K in ((1_280_000, 1, 24), (2_000_003, 2, 12), (1_280_001, 2, 31), (300, 1, 10), (70_000, 5, 31),
-                    (1_280_000, 1, 31), (1_280_003, 1, 28)):
+    # the small-K fold with both of its instances, up to 3072 keys per query and up to 6144 (512 lists: pairs of queries over two million
+    # candidates), and lists with empty slots (the last workgroup's share has fewer than K items)
+    for N, K in ((2_000_000, 6), (2_000_000, 7), (2_000_000, 10), (1_999_363, 10)):
+        assert pq.pq_measure_plan("subset", N, 2, 8, 256, K)["groups"] == 512
+        G = W.codes_uniform(N, 8, 256, seed=K)
+        assert_same_subset_topk(pq, oracle, G, tables(N % 89, 2, 8, 256), np.random.default_rng(K).permutation(N).astype(np.int32), K, "small fold, lists")
+    for N, B, K, lists in ((1_280_000, 1, 10, 256), (102_404, 1, 10, 101), (70_002, 2, 10, 69), (102_404, 1, 12, 101)):
+        assert pq.pq_measure_plan("scan", N, B, 8, 256, K)["groups"] == lists
         G = W.codes_uniform(N, 8, 256, seed=N % 97)
         assert_same_topk(pq, oracle, G, tables(N % 89, B, 8, 256), K, "small fold")
+    # ... and neighbours that the general fold takes: more results, more keys than 2048 at K = 12
+    for N, B, K in ((1_280_000, 1, 24), (2_000_003, 2, 12), (1_280_001, 2, 31), (70_000, 5, 31), (1_280_000, 1, 31), (1_280_003, 1, 28)):
+        G = W.codes_uniform(N, 8, 256, seed=N % 97)
+        assert_same_topk(pq, oracle, G, tables(N % 89, B, 8, 256), K, "general fold")
 
 
 @pytest.mark.parametrize("N,B,K", [(1_280_000, 1, 10), (1_280_000, 1, 11), (174_080, 1, 12), (175_104, 1, 12), (1_280_000, 1, 16), (28_000, 1, 16),
