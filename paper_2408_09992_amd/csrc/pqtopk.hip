@@ -243,7 +243,8 @@ bool pair_beats_bounds(long long N, int B, int m, int K, bool subset, int cw, in
 }
 // Workgroups whose last round would leave more than a quarter of the compute units' time idle (10,045 candidates, m = 16, 538 queries: 269
 // workgroups 54.4 us, by the general kernel 40.0; 17,113, 531: 532 69.7 and 58.2; 16,000, 700: 700 42.2 and 57.1).
-// (`idle`: per cent.)  Rows of 16 bytes, at 16,000 candidates and more, from an eighth on: 17,780, 652, K = 1 (15 %) 66.9 and 57.4.
+// (`idle`: per cent.)  More than 512 queries with rows of 16 bytes, at 16,000 candidates and more, from an eighth on: 17,780, 652, K = 1 (15 %) 66.9 and 57.4
+// (59,869, 262, K = 118, as much idle, 105 and 127).
 bool last_round_empty(long long groups, int idle = 25) {
     const long long rounds = (groups + kAssumedCUs - 1) / kAssumedCUs;
     return rounds > 1 && 100 * groups < (100 - idle) * rounds * kAssumedCUs;
@@ -497,7 +498,7 @@ ScanPlan make_plan(long long N, int B, int m, int K, bool generic = false, int c
         if (N * (m + 8) >= 120000 * (nb < 1 ? 1 : nb)) nb = 2 * kAssumedCUs / pairs;
         nb = nb < least ? least : nb > thin ? thin : nb;
         if (nb < 1) nb = 1;
-        if (least <= kAssumedCUs && ((forced & 256) || !last_round_empty(pairs * nb, m == 16 && N >= 16000 ? 12 : 25))) {
+        if (least <= kAssumedCUs && ((forced & 256) || !last_round_empty(pairs * nb, m == 16 && N >= 16000 && B > 2 * kAssumedCUs ? 12 : 25))) {
             p.subset_pair = true;
             p.short_subset = false;
             p.subset_vecs = (int)(((N + kThreads * nb - 1) / (kThreads * nb) * m + 15) / 16);

@@ -73,3 +73,8 @@ def test_samples_before_shared_floors(plan, N, B, m, K, rounds):
 def test_two_queries_per_workgroup_where_that_pays(plan, kind, N, B, m, K, pairs):
     # m = 16, 40,000 items, 800 queries, K = 10: 86.8 us by pairs, 56 by bounds; 9000, 720, K = 150 37 and 27 by one workgroup per query
     assert (plan(kind, N, B, m, 256, K)["kernel"] in ("pairs", "list pairs")) == bool(pairs)
+
+
+def test_lists_that_fill_their_last_round_well_enough(plan):
+    # 59,869 candidates, 262 queries, m = 16, K = 118: 105 us by pairs, 127 by one query per workgroup
+    assert plan("subset", 59_869, 262, 16, 256, 118)["kernel"] == "list pairs"
