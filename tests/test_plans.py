@@ -19,7 +19,7 @@ def test_bounds_keep_the_compute_units_filled(plan, N, B, m, K):
 
 
 @pytest.mark.parametrize("N,B,m,K,shared", [
-    (1_000_000, 40, 64, 10, 0), (1_500_000, 32, 64, 5, 0), (2_000_000, 56, 64, 20, 1), (1_500_000, 250, 8, 1, 0), (4_000_000, 130, 4, 3, 0), (4_000_000, 200, 4, 10, 1),
+    (1_000_000, 40, 64, 10, 0), (1_500_000, 32, 64, 5, 0), (2_000_000, 56, 64, 20, 1), (1_509_979, 52, 64, 9, 1), (1_500_000, 250, 8, 1, 0), (4_000_000, 130, 4, 3, 0), (4_000_000, 200, 4, 10, 1),
     (700_000, 180, 16, 1, 0), (1_500_000, 130, 16, 10, 1), (200_000, 64, 64, 10, 0), (450_000, 64, 64, 100, 0), (300_000, 100, 64, 100, 1), (450_000, 160, 64, 1, 1)])
 def test_floors_are_shared_where_that_pays(plan, N, B, m, K, shared):
     # m = 64, 1M items, 40 queries, K = 10: 162 us with shared floors, 147 without; 200,000, 64 queries 87 and 69
