@@ -672,7 +672,8 @@ void plan_filter(ScanPlan& p, long long N, int B, int m, int K, bool subset, int
     const double stream_us = (double)N * m * lanes / (rate * 2400.0);
     const double gather_us = subset && m == 4 ? (double)N / 2400.0 : 0.0;   // (a row per clock, longer than four lookups take)
     // Workgroups of a query share their floors where they are few and their shares long, a round being a unit of every wave (one word:
-    // batches of a few queries, but at m = 64, whose tables leave room for no more beside many results).  K = 100, not shared and shared (us): m = 4, 200 queries, 8M items 236 and 179; m = 8, 3M 193 and 154; m = 16,
+    // batches of a few queries, but at m = 64 and with large alphabets, whose tables leave room for no more beside many results: two bytes, m = 4, b = 6000, 140 queries, 1M
+    // items, K = 131 141 and 98).  K = 100, not shared and shared (us): m = 4, 200 queries, 8M items 236 and 179; m = 8, 3M 193 and 154; m = 16,
     // 3M 427 (16-bit fields) and 275; K = 3, m = 4, 373 queries, 731,549 items 47.4 and 52.3.
     // More than sixteen update one histogram too often for few results, and at m = 64, where 16-bit fields let little pass, for some more: m = 64, 40
     // queries, 1M items, K = 5 143 and 161, 10 147 and 162, 50 229 (1.5M) and 215; 32, 1.5M, K = 5 159 and 182; 56, 2M, K = 20 367 and 342, 52, 1.5M (77 rounds), K = 9 265 and 256; m = 4, 130,
@@ -680,7 +681,7 @@ void plan_filter(ScanPlan& p, long long N, int B, int m, int K, bool subset, int
     // 83 and 79; m = 32, 180, 1.5M, K = 3 235 and 221.  m = 64, shares of few rounds: 64 queries, 200,000 items (12 rounds), K = 10 69 and 87, K = 100 93
     // and 116, 450,000 (27) 149 and 153; 100, 300,000 (29) 212 and 192.
     auto shares = [&](long long blocks) {
-        return blocks > 1 && ((blocks <= 16 && rounds / blocks >= (K <= 4 ? 30 : m == 64 ? 28 : 12)) || (blocks <= 32 && rounds / blocks >= 32 && K > (m <= 8 ? 4 : m <= 32 ? 1 : rounds / blocks < 60 ? 16 : 8))) && (words > 1 || m == 64);
+        return blocks > 1 && ((blocks <= 16 && rounds / blocks >= (K <= 4 ? 30 : m == 64 ? 28 : 12)) || (blocks <= 32 && rounds / blocks >= 32 && K > (m <= 8 ? 4 : m <= 32 ? 1 : rounds / blocks < 60 ? 16 : 8))) && (words > 1 || m == 64 || cw == 2);
     };
     long long nb = 1;
     double best_us = 0.0;
@@ -1081,8 +1082,8 @@ hipError_t launch_filter(const ScanPlan& p, const FilterArgs& a, hipStream_t st)
     }
     switch (p.f_words * p.f_lanes) {
         case 1:
-            if constexpr (M == 64)
-                if (p.f_share) return go(scan_filter_kernel<64, 1, 1, true, false, 1, true>);
+            if constexpr (M == 64 || CW == 2)
+                if (p.f_share) return go(scan_filter_kernel<M, CW, 1, M == 64, false, 1, true>);
             return go(scan_filter_kernel<M, CW, 1, M == 64, SUB, 1, false>);
         case 2:
             if constexpr (!(SUB && M == 16))

@@ -372,7 +372,7 @@ def test_plans_the_gpu_tests_count_on(pqlib_path):
             instances.add((kind, m, queries, bits, p["fine"]))
     # (sharing floors is a template parameter: every pair of it and the rest that is compiled)
     queries = {("scan", 4): (8, 16, 32), ("scan", 8): (8, 16, 32), ("scan", 16): (8, 16, 32), ("scan", 32): (8, 16), ("scan", 64): (), ("subset", 4): (8, 16, 32),
-               ("subset", 8): (8, 16), ("subset", 16): (16,), ("scan16", 4): (8, 16, 32), ("scan16", 8): (8, 16, 32), ("scan16", 16): (8, 16, 32)}
+               ("subset", 8): (8, 16), ("subset", 16): (16,), ("scan16", 4): (4, 8, 16, 32), ("scan16", 8): (4, 8, 16, 32), ("scan16", 16): (4, 8, 16, 32)}
     want = {(k, m, q, 8, 0) for (k, m), each in queries.items() for q in each}
     want |= {("scan", 16, 8, 8, 1), ("subset", 8, 16, 8, 1)}
     want |= {("scan", 16, 8, 16, 0), ("scan", 32, 8, 16, 0), ("scan", 32, 4, 16, 0), ("scan", 64, 4, 16, 0), ("scan", 64, 2, 16, 0), ("subset", 16, 8, 16, 0)}

@@ -604,7 +604,8 @@ MORE_INSTANCES = [("scan", 116_559, 700, 4, 256, 150, 0, 8, 8, 1), ("scan", 102_
                   ("scan", 150_001, 3, 32, 256, 10, 16, 4, 8, 0), ("scan", 150_001, 7, 32, 256, 10, 16, 8, 8, 0), ("scan", 1_012_270, 65, 32, 256, 100, 0, 8, 8, 1),
                   ("scan", 50_522, 139, 32, 256, 3, 0, 16, 8, 0), ("scan", 205_001, 260, 32, 256, 5, 0, 16, 8, 1), ("scan", 301_275, 48, 64, 256, 300, 0, 2, 16, 1),
                   ("scan16", 215_005, 262, 4, 700, 100, 0, 8, 8, 1), ("scan16", 49_299, 1768, 4, 700, 17, 144, 32, 8, 1), ("scan16", 25_487, 1678, 8, 300, 100, 144, 32, 8, 1),
-                  ("scan16", 106_277, 232, 16, 700, 10, 0, 8, 8, 1), ("scan16", 32_281, 1435, 16, 257, 10, 144, 32, 8, 1), ("subset", 415_600, 131, 4, 256, 400, 0, 8, 8, 1),
+                  ("scan16", 106_277, 232, 16, 700, 10, 0, 8, 8, 1), ("scan16", 32_281, 1435, 16, 257, 10, 144, 32, 8, 1), ("scan16", 294_461, 77, 4, 6000, 131, 0, 4, 8, 1),
+                  ("scan16", 198_689, 61, 8, 3000, 20, 0, 4, 8, 1), ("scan16", 195_847, 61, 16, 1500, 40, 0, 4, 8, 1), ("subset", 415_600, 131, 4, 256, 400, 0, 8, 8, 1),
                   ("subset", 398_141, 257, 4, 256, 17, 0, 16, 8, 1), ("subset", 194_850, 137, 8, 256, 300, 0, 8, 8, 1), ("subset", 201_753, 273, 8, 256, 150, 0, 16, 8, 1),
                   ("subset", 212_279, 162, 16, 256, 10, 0, 16, 8, 1)]
 

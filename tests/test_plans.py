@@ -78,3 +78,10 @@ def test_two_queries_per_workgroup_where_that_pays(plan, kind, N, B, m, K, pairs
 def test_lists_that_fill_their_last_round_well_enough(plan):
     # 59,869 candidates, 262 queries, m = 16, K = 118: 105 us by pairs, 127 by one query per workgroup
     assert plan("subset", 59_869, 262, 16, 256, 118)["kernel"] == "list pairs"
+
+
+@pytest.mark.parametrize("N,B,m,b,K", [(1_000_000, 140, 4, 6000, 131), (1_000_000, 270, 16, 1500, 250)])
+def test_floors_are_shared_beside_large_alphabets(plan, N, B, m, b, K):
+    # four queries to a workgroup.  m = 16, b = 1500, 270 queries of 1M items, K = 250: 1359 us without shared floors, 837 with
+    p = plan("scan16", N, B, m, b, K)
+    assert p["kernel"] == "bounds" and p["queries"] == 4 and p["shared"] == 1
