@@ -472,6 +472,13 @@ ScanPlan make_plan(long long N, int B, int m, int K, bool generic = false, int c
                 if (alone && m == 32 && K > (nb == 1 ? 128 : 64)) p.pair_scan = false;
                 if (cw == 1 && m == 16 && held > 24 && pairs * nb > 3 * kAssumedCUs) p.pair_scan = false;
             }
+            // Two bytes, more than one round of workgroups, instead of the general kernel: m = 4, 35,673 items, 358 queries, K = 146 49.2 and 34.2; 75,948, 152, K = 135 39.8 and 34.5; m = 8,
+            // 25,444, 439, K = 152 56.4 and 38.5; 350,142, 250, K = 196 (nine rounds) 203 and 153, 416,818, 253, K = 292 (eleven) 245 and 200 (136,065, 75, K = 265, two, 39.7 and 41.6);
+            // m = 4, 66,572, 426, K = 4 (four) 49.7 and 37.2, 46,702, 483, K = 6 (three) 38.4 and 29.7
+            if (cw == 2 && !p.short_scan && !p.long_scan && !p.glut && pairs * nb > kAssumedCUs) {
+                if (K > 100 && (K <= 200 || pairs * nb > 4 * kAssumedCUs)) p.pair_scan = false;
+                if (m == 4 && K <= 32 && pairs * nb > 2 * kAssumedCUs) p.pair_scan = false;
+            }
             p.pair_scan = p.pair_scan || (forced & 256);
             // (one workgroup to a compute unit: 718 queries of 4500 items, two bytes, m = 16, b = 619 17.1 us without, 19.6)
             if (!(forced & 256) && p.short_scan && 2 * lds > kMaxLdsBytes && last_round_empty(pairs * nb)) p.pair_scan = false;

@@ -85,3 +85,10 @@ def test_floors_are_shared_beside_large_alphabets(plan, N, B, m, b, K):
     # four queries to a workgroup.  m = 16, b = 1500, 270 queries of 1M items, K = 250: 1359 us without shared floors, 837 with
     p = plan("scan16", N, B, m, b, K)
     assert p["kernel"] == "bounds" and p["queries"] == 4 and p["shared"] == 1
+
+
+@pytest.mark.parametrize("N,B,m,b,K,pairs", [(35_673, 358, 4, 665, 146, 0), (25_444, 439, 8, 1492, 152, 0), (416_818, 253, 8, 604, 292, 0), (66_572, 426, 4, 1772, 4, 0),
+                                             (136_065, 75, 8, 1444, 265, 1), (24_905, 467, 8, 588, 26, 1), (187_157, 157, 16, 296, 98, 1), (83_203, 172, 4, 1089, 6, 1)])
+def test_two_queries_per_workgroup_with_two_byte_sub_ids(plan, N, B, m, b, K, pairs):
+    # m = 8, b = 1492, 25,444 items, 439 queries, K = 152: 56 us by pairs, 38 without
+    assert (plan("scan16", N, B, m, b, K)["kernel"] == "pairs") == bool(pairs)
