@@ -126,7 +126,8 @@ namespace pqk {
 #define PQ_FILTER_INSTANCES_SUBSET(X, Y) PQ_FILTER_G(X, 4, 1, true) PQ_FILTER_W(X, 8, 1, true) Y(4, 1, true) Y(8, 1, true)
 #define PQ_FILTER_INSTANCES_SUBSET16(X, Y) X(16, 1, 1, false, true, 1, false) X(16, 1, 2, false, true, 1, false) PQ_FILTER_BOTH(X, 16, 1, 4, false, true, 1) PQ_FILTER_BOTH(X, 16, 1, 4, true, true, 1) Y(16, 1, true)
 #define PQ_FILTER_INSTANCES_U16(X, Y) PQ_FILTER_G(X, 4, 2, false) PQ_FILTER_G(X, 8, 2, false) X(4, 2, 1, false, false, 1, true) X(8, 2, 1, false, false, 1, true) Y(4, 2, false) Y(8, 2, false)
-#define PQ_FILTER_INSTANCES_U16_16(X, Y) PQ_FILTER_G(X, 16, 2, false) X(16, 2, 1, false, false, 1, true) Y(16, 2, false)
+#define PQ_FILTER_INSTANCES_U16_16(X, Y) PQ_FILTER_G(X, 16, 2, false) X(16, 2, 1, false, false, 1, true) \
+    PQ_FILTER_BOTH(X, 16, 2, 1, true, false, 1) PQ_FILTER_BOTH(X, 16, 2, 2, true, false, 1) PQ_FILTER_BOTH(X, 16, 2, 4, true, false, 1) Y(16, 2, false)
 // measurement instances (wall-clock stamps per wave) of those the named batch workloads run
 #define PQ_FILTER_STAMPED(X, M, G) X(M, 1, 4, false, false, G, false, true) X(M, 1, 4, false, false, G, true, true)
 #define PQ_FILTER_INSTANCES_STAMPED(X) PQ_FILTER_STAMPED(X, 8, 1) PQ_FILTER_STAMPED(X, 8, 2) PQ_FILTER_STAMPED(X, 16, 1)

@@ -562,6 +562,8 @@ double filter_min_lookups(int m, int K, int B, bool subset, int cw) {
 // ... and the items per result: with fewer, a sample that is an eighth of them gives too low a floor, and what passes it is
 // scored exactly (from tables in device memory: two-byte sub-ids' are large).  The more queries there are, the less the scans
 // side by side leave idle.  (m = 16 with sixteen-bit fields, more than 256 queries: against the batched kernel.)
+// Two bytes, m = 16 (by bounds and without, us; 16 bits): 390 queries of 350,000 items, b = 300, K = 200 203 and 472, 580 of 63,000, K = 39 89 and 143; 8 bits, b = 1900:
+// 900 of 350,000, K = 200 810 and 1342, 390 668 and 599.
 // At four fifths and five fourths of the lines (bench.py --rules; by bounds and without, us): m = 8, B = 64, K = 300: 40.9 and 44.2, 41.1 and
 // 54.5; B = 512, K = 100: 81.0 and 60.1, 70.2 and 87.4; K = 200: 196 and 169, 221 and 251; m = 16, B = 512, K = 100: 118 and 159 (it
 // could lie lower), 147 and 219; m = 32, B = 64, K = 100: 41.8 and 44.2, 47.4 and 59.9; lists, m = 8, B = 64, K = 300: 43 and 68, 46 and 93
@@ -571,7 +573,7 @@ double filter_min_lookups(int m, int K, int B, bool subset, int cw) {
 long long filter_min_items_per_result(long long N, int m, int K, int B, bool subset, bool w16, int cw) {
     if (m == 16 && w16 && B > 256) return subset ? 600 : cw == 2 ? 1000 : 2000;
     if (subset) return K > 128 ? 350 : 150;
-    if (cw == 2) return 2000;
+    if (cw == 2) return m == 16 && B > 512 ? 1000 : 2000;
     if (m >= 32) return N < 5LL * m * kLutStride ? 2000 : 1000;
     // (K > 128, more than 256 queries, with eight queries to a workgroup and shared floors and without bounds: m = 8, 512, 150,000 items, K = 250 94 and
     // 130, 900, 90,000, K = 150 103 and 155; m = 4, 900, 150,000, K = 250 109 and 168; floors not shared: m = 8, 300, 150,000, K = 250 147 and 115, K = 150
@@ -618,6 +620,23 @@ void plan_filter(ScanPlan& p, long long N, int B, int m, int K, bool subset, int
     bool w16 = m == 64;
     if (m == 32) w16 = N < (long long)K * (K > 64 ? 10000 : B > 150 ? 40000 : 13000);
     if (m == 16 && cw == 1) w16 = subset ? K > 32 || (B > 256 && N < 20000LL * K) : K > 32 && B > 128 && N < 8000LL * K;
+    // Two bytes, m = 16, more than 32 results (23 from 257 queries on, 17 from 601): with eight or four queries of 16 bits, up to a line of items per result, which lies lower where workgroups of 8 bits have no more
+    // queries and where there are few queries; with two, for 65 to 256 queries of many results or where no four of 8 bits have room.  Calls of 16 bits and 8 (us): b = 300,
+    // 350,000 items: 170 queries, K = 40 86 and 84, K = 100 98 and 122, 390, K = 40 148 and 182, K = 100 171 and 306, 900, K = 40 353 and 285, K = 100 409 and 469; 1M, 390, K = 40
+    // 314 and 265, K = 100 336 and 399; 63,000, 600, K = 31 95 and 118, 56,000, 940, K = 19 107 and 142; eight queries of either, 1M, 900, K = 400
+    // 1168 and 1324, 550,000, 490, K = 149 278 and 261; four and eight, 2.6M, 250, K = 409 590 and 489; four, b = 1000, 1M, 390, K = 200 588 and 717; 128 queries, 320,000, K = 67 72 and 65; b = 1000
+    // (four), 1M, 170, K = 100 273 and 289, 900, K = 100 974 and 1444, 40, K = 100 94 and 77; b = 1900 (two), 1M, 170, K = 200 414 and 520, 390, K = 100 925 and 704, 900, K = 400
+    // 2331 and in segments 3648.
+    if (m == 16 && cw == 2 && K > (B > 600 ? 17 : B > 256 ? 23 : 32) && 2 * K <= 1024) {
+        auto queries = [&](bool wide) {
+            for (int w = 4; w >= 1; w >>= 1)
+                if (filter_lds_bytes(m, entries / m, w, wide, 1, K <= 64 ? 128 : next_pow2(2 * K)) <= kMaxLdsBytes) return w * (wide ? 2 : 4);
+            return 0;
+        };
+        const int of16 = queries(true), of8 = queries(false);
+        const long long line = B <= 128 ? 4000 : of16 == of8 ? (of16 == 8 ? 2800 : 5500) : K > 256 ? 3500 : B > 600 && K < 64 ? 7000 : 10500;
+        w16 = !of8 || (N < line * K && (of16 >= 4 || (B > 64 && B <= 256 && K >= 100)));
+    }
     const bool fine = filter_fine_pays(N, m, K, B, subset, cw);
     if (fine) w16 = false;
     if (!(force & 16) && (B < 2 || (double)B * (double)N * m < filter_min_lookups(m, K, B, subset, cw) || 2 * N < (m >= 32 ? 7 : 16) * entries ||
@@ -649,7 +668,7 @@ void plan_filter(ScanPlan& p, long long N, int B, int m, int K, bool subset, int
                        (!few_share(N, B, row_bytes, 16, 12) || (m == 8 && scanned <= (cw == 2 ? 3.5e8 : K > 128 ? 6.0e8 : K >= 90 ? 4.0e8 : 2.2e8)));
     double best_cost = 0.0, rate = 0.0;
     int words = 0, lanes = 1;
-    for (int w = 8; w >= (w16 && m == 16 ? 4 : w16 && m == 32 ? 2 : 1); w >>= 1) {   // (8: four words for each of two lanes)
+    for (int w = 8; w >= (w16 && m == 16 && cw == 1 ? 4 : w16 && m == 32 ? 2 : 1); w >>= 1) {   // (8: four words for each of two lanes)
         const int l = w == 8 ? 2 : 1, each = w == 8 ? 4 : w;
         if (fine && w != 2) continue;
         if (l == 2 && (w16 || (subset && m != 4) || !(pairs || (force & 128)))) continue;
@@ -770,7 +789,7 @@ size_t keys_bytes(const ScanPlan& p, int B, int K) {
 }
 
 // workspace: [B][nblk][K] keys from the scan | filter scans, for the f_batch queries scanned together: tables of counts | FilterQuery
-// records | histograms | the rows that stay in device memory | the sample's best scores
+// records | histograms | the rows that stay in device memory | 16-bit counts beside the bytes | the sample's best scores
 size_t counts_bytes(const ScanPlan& p) { return p.filter ? ((size_t)p.f_batch * p.f_pitch + 255) & ~(size_t)255 : 0; }
 size_t far_bytes(const ScanPlan& p) {
     return p.filter ? ((size_t)((p.f_batch + p.f_queries - 1) / p.f_queries) * p.f_far * (size_t)p.f_stride * p.f_queries + 255) & ~(size_t)255 : 0;
@@ -1083,6 +1102,15 @@ hipError_t launch_filter(const ScanPlan& p, const FilterArgs& a, hipStream_t st)
     }
     if constexpr ((M == 16 || M == 32) && CW == 1) {
         if (p.f_w16 && p.f_words == 4) return p.f_share ? go(scan_filter_kernel<M, 1, 4, true, SUB, 1, true>) : go(scan_filter_kernel<M, 1, 4, true, SUB, 1, false>);
+    }
+    if constexpr (M == 16 && CW == 2) {
+        if (p.f_w16) {
+            switch (p.f_words) {
+                case 1: return p.f_share ? go(scan_filter_kernel<16, 2, 1, true, false, 1, true>) : go(scan_filter_kernel<16, 2, 1, true, false, 1, false>);
+                case 2: return p.f_share ? go(scan_filter_kernel<16, 2, 2, true, false, 1, true>) : go(scan_filter_kernel<16, 2, 2, true, false, 1, false>);
+                default: return p.f_share ? go(scan_filter_kernel<16, 2, 4, true, false, 1, true>) : go(scan_filter_kernel<16, 2, 4, true, false, 1, false>);
+            }
+        }
     }
     if constexpr (M == 32) {
         if (p.f_w16) return p.f_share ? go(scan_filter_kernel<32, 1, 2, true, false, 1, true>) : go(scan_filter_kernel<32, 1, 2, true, false, 1, false>);

@@ -376,6 +376,7 @@ def test_plans_the_gpu_tests_count_on(pqlib_path):
     want = {(k, m, q, 8, 0) for (k, m), each in queries.items() for q in each}
     want |= {("scan", 16, 8, 8, 1), ("subset", 8, 16, 8, 1)}
     want |= {("scan", 16, 8, 16, 0), ("scan", 32, 8, 16, 0), ("scan", 32, 4, 16, 0), ("scan", 64, 4, 16, 0), ("scan", 64, 2, 16, 0), ("subset", 16, 8, 16, 0)}
+    want |= {("scan16", 16, q, 16, 0) for q in (2, 4, 8)}
     assert instances == want, instances ^ want
     assert {(k, m) for k, m, _, _ in seen} == {("scan", m) for m in (4, 8, 16, 32, 64)} | {(k, m) for k in ("subset", "scan16") for m in (4, 8, 16)}
     assert {bits for k, m, bits, _ in seen if m == 16 and k == "scan"} == {8, 16}

@@ -607,7 +607,9 @@ MORE_INSTANCES = [("scan", 116_559, 700, 4, 256, 150, 0, 8, 8, 1), ("scan", 102_
                   ("scan16", 106_277, 232, 16, 700, 10, 0, 8, 8, 1), ("scan16", 32_281, 1435, 16, 257, 10, 144, 32, 8, 1), ("scan16", 294_461, 77, 4, 6000, 131, 0, 4, 8, 1),
                   ("scan16", 198_689, 61, 8, 3000, 20, 0, 4, 8, 1), ("scan16", 195_847, 61, 16, 1500, 40, 0, 4, 8, 1), ("subset", 415_600, 131, 4, 256, 400, 0, 8, 8, 1),
                   ("subset", 398_141, 257, 4, 256, 17, 0, 16, 8, 1), ("subset", 194_850, 137, 8, 256, 300, 0, 8, 8, 1), ("subset", 201_753, 273, 8, 256, 150, 0, 16, 8, 1),
-                  ("subset", 212_279, 162, 16, 256, 10, 0, 16, 8, 1)]
+                  ("subset", 212_279, 162, 16, 256, 10, 0, 16, 8, 1), ("scan16", 806_718, 20, 16, 1900, 400, 0, 2, 16, 0), ("scan16", 251_345, 66, 16, 1900, 100, 0, 2, 16, 1),
+                  ("scan16", 389_382, 25, 16, 700, 131, 0, 4, 16, 0), ("scan16", 110_893, 101, 16, 700, 40, 0, 4, 16, 1), ("scan16", 392_274, 25, 16, 300, 131, 0, 8, 16, 0),
+                  ("scan16", 97_407, 225, 16, 300, 40, 0, 8, 16, 1)]
 
 
 @pytest.mark.parametrize("kind,N,B,m,b,K,mask,queries,bits,shared", MORE_INSTANCES)

@@ -92,3 +92,11 @@ def test_floors_are_shared_beside_large_alphabets(plan, N, B, m, b, K):
 def test_two_queries_per_workgroup_with_two_byte_sub_ids(plan, N, B, m, b, K, pairs):
     # m = 8, b = 1492, 25,444 items, 439 queries, K = 152: 56 us by pairs, 38 without
     assert (plan("scan16", N, B, m, b, K)["kernel"] == "pairs") == bool(pairs)
+
+
+@pytest.mark.parametrize("N,B,b,K,bits", [(321_782, 389, 300, 200, 16), (347_633, 170, 700, 171, 16), (350_000, 900, 1000, 100, 16), (928_212, 648, 304, 158, 8), (3_791_894, 128, 312, 413, 8), (1_000_000, 40, 1000, 100, 8),
+                                          (1_000_000, 900, 300, 40, 8), (63_334, 598, 300, 31, 16), (55_795, 942, 300, 19, 16), (2_555_679, 252, 1000, 409, 8), (350_000, 390, 300, 10, 8), (1_000_000, 390, 1900, 200, 8), (1_000_000, 900, 1900, 400, 16)])
+def test_sixteen_bit_fields_for_many_results_of_two_byte_sub_ids(plan, N, B, b, K, bits):
+    # (bytes let so many items pass there that 321,782 items with 389 queries took the general kernel: 437 us and 193)
+    p = plan("scan16", N, B, 16, b, K)
+    assert (p["kernel"], p["field_bits"]) == ("bounds", bits)
