@@ -68,9 +68,10 @@ int pq_subitem_scores(const float* queries, const float* centroids, float* S,
  * Bytes of device workspace pq_score_topk() needs for this problem.  Pure host arithmetic, no HIP call.
  * Returns 0 for arguments pq_score_topk() would reject.
  * What it holds: 8 * K bytes per query and workgroup that scans for it (512 workgroups at most for a single query, one for
- * batches of thousands); for batches that are scanned by bounds also 512 * m bytes of tables (2 * m * b with 16-bit sub-ids) and
- * half a kilobyte per query, for as many queries as 64 MiB of tables serve (1024 at m = 64, 16384 at m = 8): larger batches take
- * turns with them.
+ * batches of thousands); for batches that are scanned by bounds also 256 * m to 768 * m bytes of tables (with 16-bit sub-ids m * b or
+ * 2 * m * b)
+ * and half a kilobyte per query, for at most as many queries as 64 MiB of tables serve (2048 at m = 64; at m = 8 16384, lists
+ * 10922): larger batches take turns with them.
  */
 size_t pq_score_topk_workspace_bytes(long long N, int B, int m, int b, int K);
 

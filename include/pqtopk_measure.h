@@ -103,7 +103,7 @@ int pq_measure_sync_variant(int variant, void* scratch, size_t scratch_bytes, vo
  * upper bounds but with every score computed; bit 4: they are scanned by upper bounds whatever their size; bit 5: a
  * candidate list is never left to one workgroup per query but for want of more; bit 6: a single query over a catalogue too
  * long for the short kernel is always scanned in segments; bit 7: batches scanned by upper bounds are by pairs of lanes wherever
- * these fit; bit 8: a batch takes the short kernels for two queries per workgroup wherever they fit (bit 0 keeps
+ * these fit (lists: m = 4); bit 8: a batch takes the short kernels for two queries per workgroup wherever they fit (bit 0 keeps
  * it off these too).
  * 0 restores the library's own choice.
  * Process-wide, takes effect for calls made after it returns (workspace sizes depend on bits 0 and 3 to 8).  Returns the

@@ -55,9 +55,10 @@ using namespace pqk;
 
 thread_local char g_hip_error[256] = "no HIP error recorded";
 
-// pq_measure_force_general(): bit 0 keeps calls off the short and long scans, bit 1 off fold_small_kernel, bit 2 Eq. 4 off the
-// matrix cores, bit 3 off the scans by upper bounds; bit 4 on them wherever they can; bit 5 spreads short candidate lists
-// over the chip; bit 6: longer single queries always in segments (0: the product's choice)
+// pq_measure_force_general(): bit 0 keeps calls off the short and long scans and off those by pairs of queries, bit 1 off fold_small_kernel, bit 2
+// Eq. 4 off the matrix cores, bit 3 off the scans by upper bounds; bit 4 on them wherever they can; bit 5 spreads short candidate lists
+// over the chip; bit 6: longer single queries always in segments; bit 7: scans by upper bounds by pairs of lanes wherever these fit; bit 8: batches by
+// pairs of queries wherever these fit (0: the product's choice)
 std::atomic<int> g_force_general{0};
 
 int record_hip(hipError_t e) {

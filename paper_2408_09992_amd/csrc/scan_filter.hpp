@@ -19,7 +19,7 @@
 //     16-bit fields are the better ones (one sum).  An exact score reads its table values from device memory, one lane per clock and CU.
 //   - what is left is scored exactly, by the same left-to-right fp32 chain as everywhere, and only exact scores enter
 //     lists, floors and results.  Bit for bit the same results as the other kernels, whatever the tables are.
-// The time does depend on the tables: an item that passes costs as much as a hundred that do not.  Masked entries and queries
+// The time does depend on the tables: an item that passes costs as much as a hundred that do not.  Masked entries and, but in lists, queries
 // of zeros (a padded batch) cost nothing extra, see filter_prepare_kernel; where most items pass all the same (a large entry
 // that hardly any item has, scores that hardly differ in fp32) a query is given up and its share scanned exactly, four queries
 // per LDS read.
@@ -574,7 +574,7 @@ template <> struct FilterWord<4> { typedef uint4 type; };
 // STAMP: measurement instance that also records wall-clock stamps per wave.
 // FINE: 16-bit counts in LDS beside the bytes (one-byte sub-ids): what the bytes let pass is looked up there, nine 2-byte lanes per clock,
 // before it is scored exactly, one lane per clock: of three or four that pass at m = 16, one is left.  Half the queries per LDS read pay
-// for it, see filter_fine_pays() (100,000 items, 520 queries, K = 60: scan and selection 144 -> 89 us).
+// for it there, see filter_fine_pays() (120,000 items, 400 queries, K = 60: a call 84 -> 74 us); lists of m = 8 have room for sixteen.
 template <int M, int CW, int W, bool W16, bool SUB, int G, bool SHARE, bool STAMP = false, bool FINE = false>
 __global__ __launch_bounds__(kFilterThreads) void scan_filter_kernel(FilterArgs a) {
     using Sh = FilterShape<M, CW>;

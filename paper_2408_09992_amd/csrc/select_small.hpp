@@ -231,8 +231,8 @@ __device__ __forceinline__ void mid_select_clear(MidSelectLds<NT>& L, int tid) {
 // As select_small_k(), for K <= 2 * NT.  The floor is one that K of the THREADS' best scores reach
 // (K > NT / 2: of the best of their even and of their odd slots), taken from a histogram of those alone: 512 counts instead
 // of the 11,000 that all scores would be, and for K = 100 only a tenth more candidates than K: three barriers, then the
-// candidates are ordered.  (1.28M items, one user: K = 100 18.4 -> 16.6 us per step, K = 31 18.0 -> 14.9; from K = 13 on it
-// beats the waves' own floors, which let eight times K pass.)
+// candidates are ordered.  (1.28M items, one user: K = 100 18.4 -> 16.6 us per step, K = 31 18.0 -> 14.9; where it beats
+// the waves' own floors, which let eight times K pass: small_k_max().)
 // More candidates than the array holds (heavy ties): the exact K-th key is found bit by bit first.
 // Between its barriers: mid_range() the threads' best scores and their range, mid_count() the histogram, mid_collect() the
 // candidates, mid_order() (with barriers of its own) the candidates in order.
