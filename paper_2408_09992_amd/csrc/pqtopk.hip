@@ -744,11 +744,6 @@ void plan_filter(ScanPlan& p, long long N, int B, int m, int K, bool subset, int
     // 200,000 items, m = 4, K = 12 41 and 29 us; 478, 115,861, m = 8, K = 11 48 and 42; 300, 300,000, K = 26 52 and 56).  Where the workgroups
     // of a query share their floors those rise fast by themselves.
     p.f_share = shares(nb);
-    // The sample gives a query up of which more than three in ten items would pass its floor.  Floors that few workgroups share over long shares rise far above
-    // the sample's, and the scan finds out by itself (given up at once, 1024 queries of heavy-tailed tables, m = 8, took 1.3 ms instead of 0.5); those of short
-    // shares, or of more workgroups, rise less.  An entry that five items have, left to the scan and given up at once (us): m = 64, 60 queries, 3M items, K = 100
-    // 4977 and 2272; m = 8, 200, 4M, K = 100 2559 and 988, 300, 500,000, K = 10 919 and 218; m = 4, 500, 300,000, K = 100 841 and 245.
-    p.f_patient = p.f_share && nb <= 16 && rounds / nb >= 32;
     const long long items_per_round = (long long)p.f_sample * N / units;
     long long want = (long long)((K <= 16 && B > 128 && !subset && !p.f_share ? 8.0 : 5.0) * sqrt((double)K * (double)N)) / items_per_round;
     // (... but at m = 32, where an exact score costs most, not within so short a time, if the catalogue is worth the sample: one round and four, 500,000 items, 480 queries,
@@ -767,6 +762,14 @@ void plan_filter(ScanPlan& p, long long N, int B, int m, int K, bool subset, int
     if (sample_rounds > 8 * (kFilterThreads / p.f_prepare)) sample_rounds = 8 * (kFilterThreads / p.f_prepare);
     p.f_parts = (int)parts;
     p.f_rounds = (int)(sample_rounds < 1 ? 1 : sample_rounds);
+    // The sample gives a query up of which more than three in ten items would pass its floor.  Floors that few workgroups share over long shares rise far above
+    // the sample's, and the scan finds out by itself (given up at once, 1024 queries of heavy-tailed tables, m = 8, took 1.3 ms instead of 0.5); those of short
+    // shares, or of more workgroups, rise less.  An entry that five items have, left to the scan and given up at once (us): m = 64, 60 queries, 3M items, K = 100
+    // 4977 and 2272; m = 8, 200, 4M, K = 100 2559 and 988, 300, 500,000, K = 10 919 and 218; m = 4, 500, 300,000, K = 100 841 and 245.  But a sample of few items per
+    // result has a floor that lets a part of that through, which bounds of bytes multiply (one round of 1024 at m = 16): 126 ordinary queries given up, 480,000 items,
+    // m = 16, K = 500 1860 and 157 left to the scan, 300,000, K = 300 322 and 113, a list of 300,000, K = 500 622 and 146.
+    const double sampled = (double)items_per_round * (double)(parts * p.f_rounds);
+    p.f_patient = p.f_share && ((nb <= 16 && rounds / nb >= 32) || (double)K * (w16 ? 8.0 : m >= 16 ? 32.0 : 16.0) > sampled);
     // scores a part leaves: twice its share of the K best and two more, never more than K
     long long best = (2 * K + parts - 1) / parts + 2;
     p.f_best = (int)(best < K ? best : K);

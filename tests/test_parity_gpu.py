@@ -652,6 +652,39 @@ def test_batches_of_masked_and_zero_queries_are_scanned_as_fast_as_others(pq, N,
     assert odd < 3.5 * plain, (plain, odd)
 
 
+@pytest.mark.parametrize("kind,N,m,B,K", [("scan", 480_000, 16, 126, 500), ("scan", 300_000, 16, 126, 300), ("subset", 300_000, 16, 126, 500)])
+def test_samples_of_few_items_per_result_give_no_query_up(pq, kind, N, m, B, K):
+    # (floors shared by sixteen workgroups over short shares; a query that is given up is scanned again with exact tables: 1860, 322 and 622 us, and
+    # 157, 113 and 146 by bounds alone)
+    rng = np.random.default_rng(5)
+    codes = W.codes_uniform_device(4 * N if kind == "subset" else N, m, 256, 5)
+    S = dev(rng.standard_normal((B, m, 256), dtype=np.float32))
+    V = torch.randperm(4 * N, device="cuda")[:N].to(torch.int32) if kind == "subset" else None
+
+    def best_us(mask):
+        prev = pq.pq_measure_force_general(mask)
+        try:
+            call = pq.PreparedScoreTopKSubset(codes, S, V, K) if kind == "subset" else pq.PreparedScoreTopK(codes, S, K)
+            times = []
+            for _ in range(6):
+                ev = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+                call()
+                ev[0].record()
+                for _ in range(5):
+                    call()
+                ev[1].record()
+                torch.cuda.synchronize()
+                times.append(ev[0].elapsed_time(ev[1]) * 200)
+            return min(times)
+        finally:
+            pq.pq_measure_force_general(prev)
+
+    assert pq.pq_measure_plan(kind, N, B, m, 256, K)["kernel"] == "bounds"
+    bounds, without = best_us(0), best_us(8)
+    print(f"{bounds:.1f} {without:.1f}", flush=True)
+    assert bounds < 1.3 * without, (bounds, without)
+
+
 @pytest.mark.parametrize("N,m,B,K", [(300_001, 64, 17, 10), (200_003, 64, 40, 100), (150_001, 64, 100, 10), (300_005, 4, 100, 10),
                                      (100_003, 4, 1024, 100), (200_001, 32, 100, 10), (150_007, 5, 100, 10), (120_001, 48, 40, 10),
                                      (100_001, 64, 300, 10)])
