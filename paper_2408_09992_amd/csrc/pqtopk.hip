@@ -480,6 +480,19 @@ ScanPlan make_plan(long long N, int B, int m, int K, bool generic = false, int c
                 if (K > 100 && (K <= 200 || pairs * nb > 4 * kAssumedCUs)) p.pair_scan = false;
                 if (m == 4 && K <= 32 && pairs * nb > 2 * kAssumedCUs) p.pair_scan = false;
             }
+            // m = 4, instead of the general kernel with one or two workgroups per query, where lists are long (pairs and without, us): K = 130, 250 queries, 33,000 items 29.8 and 18.4, 90,000 54.2
+            // and 28.9, 170, 60,000 30.3 and 23.3, 90, 90,000 29.4 and 25.9; K = 100, 250, 43,000 25.5 and 19.5, 430, 60,000 58.4 and 43.5, 340, whose last round is two thirds
+            // empty, 43,000 29.5 and 36.9; K = 70, 250, 43,000 20.6 and 18.7, 170, 33,000 (even); K = 182, 158, 68,000 24.1 and 25.7; two bytes: K = 100, 430, 90,000 81.5 and
+            // 55.6, K = 40, 430, 43,000 36.4 and 31.8, 340 31.1 and 36.0
+            if (m == 4 && p.nblk <= 2 && !p.short_scan && !p.long_scan && !p.glut) {
+                const int last = B % kAssumedCUs;
+                const bool idle = B > kAssumedCUs && last > 0 && last <= kAssumedCUs * 2 / 5;
+                if (p.nblk == 2 ? K > 110 && K <= 150 : K > (B > 200 && B <= kAssumedCUs ? 64 : 80) && !(idle && cw == 1 && N < 50000) && !(K > 150 && B <= 200 && N < 80000)) p.pair_scan = false;
+                if (cw == 2 && K > 32 && pairs * nb > 2 * kAssumedCUs && !idle) p.pair_scan = false;
+            }
+            // ... and of the short one: 29,000, 832, K = 81 52.8 and 43.1, 24,000, 1000, K = 100 44.6 and 39.4, K = 70 36.1 and 37.2; a workgroup each, 15,000, 1016, K = 22 18.7
+            // and 17.0, 10,000, 787, K = 2 10.5 and 11.8
+            if (m == 4 && p.short_scan && B > 2 * kAssumedCUs && (nb > 1 ? K > 75 : B > 3 * kAssumedCUs && N >= 14000 && K >= 20)) p.pair_scan = false;
             p.pair_scan = p.pair_scan || (forced & 256);
             // (one workgroup to a compute unit: 718 queries of 4500 items, two bytes, m = 16, b = 619 17.1 us without, 19.6)
             if (!(forced & 256) && p.short_scan && 2 * lds > kMaxLdsBytes && last_round_empty(pairs * nb)) p.pair_scan = false;

@@ -69,9 +69,11 @@ def test_samples_before_shared_floors(plan, N, B, m, K, rounds):
 @pytest.mark.parametrize("kind,N,B,m,K,pairs", [
     ("scan", 17_000, 600, 8, 150, 0), ("scan", 17_000, 900, 8, 150, 1), ("scan", 9000, 720, 16, 150, 0), ("scan", 5000, 600, 8, 2, 0), ("scan", 12_000, 650, 32, 100, 0),
     ("scan", 30_000, 800, 16, 100, 0), ("scan", 22_000, 800, 16, 10, 1), ("scan", 22_000, 530, 16, 100, 1), ("scan", 40_000, 450, 16, 5, 0), ("scan", 35_000, 600, 16, 2, 0),
-    ("scan", 35_000, 600, 16, 20, 1), ("scan", 40_000, 800, 32, 10, 0), ("scan", 30_000, 450, 32, 5, 1), ("subset", 17_780, 652, 16, 1, 0), ("subset", 17_825, 162, 16, 10, 1)])
+    ("scan", 35_000, 600, 16, 20, 1), ("scan", 40_000, 800, 32, 10, 0), ("scan", 30_000, 450, 32, 5, 1), ("subset", 17_780, 652, 16, 1, 0), ("subset", 17_825, 162, 16, 10, 1),
+    ("scan", 90_000, 250, 4, 130, 0), ("scan", 60_000, 430, 4, 100, 0), ("scan", 43_000, 340, 4, 100, 1), ("scan", 68_000, 158, 4, 182, 1), ("scan", 24_000, 1000, 4, 100, 0),
+    ("scan", 16_000, 1000, 4, 40, 0), ("scan", 33_000, 170, 4, 40, 1)])
 def test_two_queries_per_workgroup_where_that_pays(plan, kind, N, B, m, K, pairs):
-    # m = 16, 40,000 items, 800 queries, K = 10: 86.8 us by pairs, 56 by bounds; 9000, 720, K = 150 37 and 27 by one workgroup per query
+    # m = 16, 40,000 items, 800 queries, K = 10: 86.8 us by pairs, 56 by bounds; 9000, 720, K = 150 37 and 27 by one workgroup per query; m = 4, 90,000, 250, K = 130 54 and 29
     assert (plan(kind, N, B, m, 256, K)["kernel"] in ("pairs", "list pairs")) == bool(pairs)
 
 
@@ -88,7 +90,8 @@ def test_floors_are_shared_beside_large_alphabets(plan, N, B, m, b, K):
 
 
 @pytest.mark.parametrize("N,B,m,b,K,pairs", [(35_673, 358, 4, 665, 146, 0), (25_444, 439, 8, 1492, 152, 0), (416_818, 253, 8, 604, 292, 0), (66_572, 426, 4, 1772, 4, 0),
-                                             (136_065, 75, 8, 1444, 265, 1), (24_905, 467, 8, 588, 26, 1), (187_157, 157, 16, 296, 98, 1), (83_203, 172, 4, 1089, 6, 1)])
+                                             (136_065, 75, 8, 1444, 265, 1), (24_905, 467, 8, 588, 26, 1), (187_157, 157, 16, 296, 98, 1), (83_203, 172, 4, 1089, 6, 1),
+                                             (90_000, 430, 4, 300, 100, 0), (43_000, 430, 4, 300, 40, 0), (43_000, 340, 4, 300, 40, 1)])
 def test_two_queries_per_workgroup_with_two_byte_sub_ids(plan, N, B, m, b, K, pairs):
     # m = 8, b = 1492, 25,444 items, 439 queries, K = 152: 56 us by pairs, 38 without
     assert (plan("scan16", N, B, m, b, K)["kernel"] == "pairs") == bool(pairs)
