@@ -593,7 +593,8 @@ long long filter_min_items_per_result(long long N, int m, int K, int B, bool sub
     // 130, 900, 90,000, K = 150 103 and 155; m = 4, 900, 150,000, K = 250 109 and 168; floors not shared: m = 8, 300, 150,000, K = 250 147 and 115, K = 150
     // 78 and 107; m = 4, 512, 187,500, K = 150 99 and 87)
     if (B > 256 && K > 128) return m <= 8 && few_share(N, B, m, 8, 14) ? 600 : m == 8 ? 1000 : 1300;
-    return B <= 256 ? (K > 128 ? 800 : 500) : K > 64 ? 800 : 500;
+    // (m = 4 over 512 queries: 1000, 24,000 items, K = 40 63.2 and 37.3, 800, 32,500, K = 58 73 and 62; 33,000, K = 40 42.9 and 62)
+    return B <= 256 ? (K > 128 ? 800 : 500) : K > (m == 4 && B > 512 ? 31 : 64) ? 800 : 500;
 }
 
 // Lookups (B * N * m) from which a batch is scanned by pairs of lanes (see plan_filter()).

@@ -103,3 +103,9 @@ def test_sixteen_bit_fields_for_many_results_of_two_byte_sub_ids(plan, N, B, b, 
     # (bytes let so many items pass there that 321,782 items with 389 queries took the general kernel: 437 us and 193)
     p = plan("scan16", N, B, 16, b, K)
     assert (p["kernel"], p["field_bits"]) == ("bounds", bits)
+
+
+@pytest.mark.parametrize("N,B,K,bounds", [(24_000, 1000, 40, 0), (32_500, 800, 58, 0), (33_000, 830, 40, 1), (24_000, 830, 20, 1)])
+def test_rows_of_four_bytes_with_few_items_per_result(plan, N, B, K, bounds):
+    # 24,000 items, 1000 queries, K = 40: 63 us by bounds, 37 by the short kernel
+    assert (plan("scan", N, B, 4, 256, K)["kernel"] == "bounds") == bool(bounds)
