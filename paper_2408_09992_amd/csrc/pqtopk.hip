@@ -721,8 +721,10 @@ void plan_filter(ScanPlan& p, long long N, int B, int m, int K, bool subset, int
     // 4M, K = 3 71.3 and 73.5, 200, K = 10 106 and 94; m = 8, 250, 1.5M, K = 1 69 and 79, 3 75 and 80; m = 16, 180, 700,000, K = 1 71 and 78, 220, 700,000, K = 2
     // 83 and 79; m = 32, 180, 1.5M, K = 3 235 and 221.  m = 64, shares of few rounds: 64 queries, 200,000 items (12 rounds), K = 10 69 and 87, K = 100 93
     // and 116, 450,000 (27) 149 and 153; 100, 300,000 (29) 212 and 192.
+    // Two bytes, K = 6: m = 8, b = 1500, 60, 2M (61 rounds) 57 and 72, 100, 1M (51) 58 and 67, 2M (102) 84 and 86, 4M (205) 130 and 126; m = 4, b = 4000, 60, 4M (61) 66 and 77;
+    // K = 20: 60, 2M 66 and 69, 100, 2M 100 and 92.
     auto shares = [&](long long blocks) {
-        return blocks > 1 && ((blocks <= 16 && rounds / blocks >= (K <= 4 ? 30 : m == 64 ? 28 : 12)) || (blocks <= 32 && rounds / blocks >= 32 && K > (m <= 8 ? 4 : m <= 32 ? 1 : rounds / blocks < 60 ? 16 : 8))) && (words > 1 || m == 64 || cw == 2);
+        return blocks > 1 && ((blocks <= 16 && rounds / blocks >= (K <= 4 ? 30 : m == 64 ? 28 : 12)) || (blocks <= 32 && rounds / blocks >= 32 && K > (cw == 2 && rounds / blocks < 110 ? 12 : m <= 8 ? 4 : m <= 32 ? 1 : rounds / blocks < 60 ? 16 : 8))) && (words > 1 || m == 64 || cw == 2);
     };
     long long nb = 1;
     double best_us = 0.0;

@@ -109,3 +109,11 @@ def test_sixteen_bit_fields_for_many_results_of_two_byte_sub_ids(plan, N, B, b, 
 def test_rows_of_four_bytes_with_few_items_per_result(plan, N, B, K, bounds):
     # 24,000 items, 1000 queries, K = 40: 63 us by bounds, 37 by the short kernel
     assert (plan("scan", N, B, 4, 256, K)["kernel"] == "bounds") == bool(bounds)
+
+
+@pytest.mark.parametrize("N,B,m,b,K,shared", [(2_000_000, 60, 8, 1500, 6, 0), (4_000_000, 100, 8, 1500, 6, 1), (2_000_000, 60, 8, 1500, 150, 1), (1_000_000, 100, 8, 1500, 6, 0),
+                                              (1_000_000, 100, 8, 1500, 60, 1), (4_000_000, 60, 4, 4000, 6, 0)])
+def test_two_byte_sub_ids_share_floors_between_many_workgroups(plan, N, B, m, b, K, shared):
+    # (more than sixteen workgroups per query.)  m = 8, b = 1500, 60 queries of 2M items, K = 6: 57 us without shared floors, 72 with; K = 150 111 and 103
+    p = plan("scan16", N, B, m, b, K)
+    assert p["kernel"] == "bounds" and p["groups"] > 16 and p["shared"] == shared
