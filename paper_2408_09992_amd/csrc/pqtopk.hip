@@ -735,6 +735,9 @@ void plan_filter(ScanPlan& p, long long N, int B, int m, int K, bool subset, int
         // (rows of a list: with a multiple of 8 blocks, block x of every tile runs on XCD x % 8, whose L2 the tiles share:
         // 200 queries, 1M of 4M items, m = 8, K = 10: 234 us with 19 blocks, 109 with 16)
         if (subset && (cand & 7) * (N >= 150000 ? 2 : 5) <= cand) cand = cand < 8 ? cand : cand & ~7LL;
+        // (seventeen to twenty, whose floors are not shared, or sixteen, whose are: many results.  m = 4, two bytes, 110 queries, 1.1M items, K = 250 111 and 79; one byte,
+        // 2M, K = 400 163 and 88; fewer results, m = 8, 212, 650,000, K = 30 58 and 65, m = 4, 205, 1.7M, K = 30 64 and 71, m = 16, 98, 260,000, K = 100 51 and 60)
+        if (!subset && m <= 16 && K > (m <= 8 ? 128 : 256) && cand > 16 && cand <= 20 && !shares(cand) && shares(16)) cand = 16;
         const double per_cu = (double)((tiles * cand + kAssumedCUs - 1) / kAssumedCUs);
         // (workgroups that share their floors, or scan everything for their queries, score less.  In a list an item that is scored exactly costs its row from
         // another place in memory too, the more items the more results: with and without this term, 1M candidates, 300 queries, m = 8 (8 workgroups per query that share, 24

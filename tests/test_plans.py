@@ -117,3 +117,11 @@ def test_two_byte_sub_ids_share_floors_between_many_workgroups(plan, N, B, m, b,
     # (more than sixteen workgroups per query.)  m = 8, b = 1500, 60 queries of 2M items, K = 6: 57 us without shared floors, 72 with; K = 150 111 and 103
     p = plan("scan16", N, B, m, b, K)
     assert p["kernel"] == "bounds" and p["groups"] > 16 and p["shared"] == shared
+
+
+@pytest.mark.parametrize("kind,N,B,m,b,K,groups", [("scan", 2_000_000, 110, 4, 256, 400, 16), ("scan16", 1_000_000, 110, 4, 1500, 250, 16), ("scan", 600_000, 100, 8, 256, 300, 16),
+                                                   ("scan", 480_000, 110, 16, 256, 450, 16), ("scan", 650_000, 212, 8, 256, 30, 18), ("scan", 260_000, 98, 16, 256, 100, 19)])
+def test_many_results_take_sixteen_workgroups_that_share_floors(plan, kind, N, B, m, b, K, groups):
+    # m = 4, 2M items, 110 queries, K = 400: 163 us by eighteen workgroups that do not, 88 by sixteen
+    p = plan(kind, N, B, m, b, K)
+    assert (p["kernel"], p["groups"], p["shared"]) == ("bounds", groups, int(groups == 16))
