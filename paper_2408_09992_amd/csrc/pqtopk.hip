@@ -723,8 +723,18 @@ void plan_filter(ScanPlan& p, long long N, int B, int m, int K, bool subset, int
     // and 116, 450,000 (27) 149 and 153; 100, 300,000 (29) 212 and 192.
     // Two bytes, K = 6: m = 8, b = 1500, 60, 2M (61 rounds) 57 and 72, 100, 1M (51) 58 and 67, 2M (102) 84 and 86, 4M (205) 130 and 126; m = 4, b = 4000, 60, 4M (61) 66 and 77;
     // K = 20: 60, 2M 66 and 69, 100, 2M 100 and 92.
+    // ... but by five workgroups: 170, 140,000 (27), K = 10 141 and 144, K = 120 292 and 208; 190, 110,000 (21), K = 60 197 and 192.  One word, two bytes: m = 4, b = 6000, 130, 340,000 (24),
+    // K = 13 51 and 60, K = 30 72 and 62, 700,000 (49), K = 4 59 and 75, 300 (114), K = 4 119 and 107; by seventeen, m = 8, b = 3000, 60, 700,000, K = 30 62 and 76, K = 60 74 and 75,
+    // m = 16, b = 1600, K = 60 107 and 112.
+    const bool narrow = cw == 2 && words == 1;
     auto shares = [&](long long blocks) {
-        return blocks > 1 && ((blocks <= 16 && rounds / blocks >= (K <= 4 ? 30 : m == 64 ? 28 : 12)) || (blocks <= 32 && rounds / blocks >= 32 && K > (cw == 2 && rounds / blocks < 110 ? 12 : m <= 8 ? 4 : m <= 32 ? 1 : rounds / blocks < 60 ? 16 : 8))) && (words > 1 || m == 64 || cw == 2);
+        if (blocks <= 1 || blocks > 32 || !(words > 1 || m == 64 || cw == 2)) return false;
+        const long long each = rounds / blocks;
+        if (blocks > 16) {
+            const int few = cw == 2 && each < 110 ? (narrow ? 64 : 12) : m <= 8 ? 4 : m <= 32 ? 1 : each < 60 ? 16 : 8;
+            return each >= 32 && K > few;
+        }
+        return each >= (K <= 4 ? (narrow ? 100 : 30) : m == 64 ? (blocks <= 6 ? 20 : 28) : narrow && K <= 16 ? 28 : 12);
     };
     long long nb = 1;
     double best_us = 0.0;

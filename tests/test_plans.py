@@ -125,3 +125,12 @@ def test_many_results_take_sixteen_workgroups_that_share_floors(plan, kind, N, B
     # m = 4, 2M items, 110 queries, K = 400: 163 us by eighteen workgroups that do not, 88 by sixteen
     p = plan(kind, N, B, m, b, K)
     assert (p["kernel"], p["groups"], p["shared"]) == ("bounds", groups, int(groups == 16))
+
+
+@pytest.mark.parametrize("kind,N,B,m,b,K,shared", [("scan", 140_000, 169, 64, 256, 120, 1), ("scan", 70_000, 169, 64, 256, 30, 0), ("scan", 140_000, 125, 64, 256, 60, 0),
+                                                   ("scan16", 340_000, 129, 4, 6000, 13, 0), ("scan16", 340_000, 129, 4, 6000, 30, 1), ("scan16", 700_000, 129, 4, 6000, 4, 0),
+                                                   ("scan16", 700_000, 300, 4, 6000, 4, 1), ("scan16", 700_000, 60, 8, 3000, 30, 0), ("scan16", 700_000, 60, 8, 3000, 100, 1)])
+def test_queries_of_one_word_share_floors_where_that_pays(plan, kind, N, B, m, b, K, shared):
+    # m = 64, 170 queries of 140,000 items, K = 120: 292 us without shared floors, 208 with; m = 4, b = 6000, 129 of 700,000, K = 4 59 and 75
+    p = plan(kind, N, B, m, b, K)
+    assert p["kernel"] == "bounds" and p["shared"] == shared
