@@ -1413,9 +1413,19 @@ hipError_t launch_subitem(const float* queries, const float* centroids, float* S
     const bool rows_aligned = (((uintptr_t)queries | (uintptr_t)centroids) & 15) == 0 && d % 4 == 0 && (d / m) % 4 == 0;
     if constexpr (S_ELEMS % 4 == 0 && S_ELEMS > 0) {
         if (B >= kSubBatchMin && rows_aligned) {
-            const int waves = B < kSubBatchTile ? (B + kSubInterleave - 1) / kSubInterleave : kSubBatchTile / kSubInterleave;
-            dim3 grid(m * ((b + kSubThreads - 1) / kSubThreads), (B + kSubBatchTile - 1) / kSubBatchTile);
-            return launch(subitem_scores_batched_kernel<S_ELEMS>, grid, kSubThreads * waves, 0, st, queries, centroids, S, B, d, m, b);
+            // One or two chains to a wave while that leaves a workgroup at most to a compute unit: four make each wave's time in LDS longer, and one
+            // workgroup's chunks are fewer to read.  Calls with four chains and with what this takes (d = 512, b = 256, us): m = 8, 16 queries 3.16 and
+            // 2.43, 32 3.17 and 2.49, 64 (two) 3.26 and 2.81; m = 16, 16 2.41 and 2.30; m = 4, 60 4.88 and 3.33.
+            const long long blocks = (long long)m * ((b + kSubThreads - 1) / kSubThreads);
+            auto fits = [&](int each) { return blocks * ((B + kSubBatchWaves * each - 1) / (kSubBatchWaves * each)) <= kAssumedCUs; };
+            auto go = [&](auto each) {
+                constexpr int I = decltype(each)::value;
+                const dim3 grid((unsigned)blocks, (B + kSubBatchWaves * I - 1) / (kSubBatchWaves * I));
+                return launch(subitem_scores_batched_kernel<S_ELEMS, I>, grid, kSubBatchThreads, 0, st, queries, centroids, S, B, d, m, b);
+            };
+            if (B <= kSubBatchWaves || fits(1)) return go(std::integral_constant<int, 1>());
+            if (B <= 2 * kSubBatchWaves || fits(2)) return go(std::integral_constant<int, 2>());
+            return go(std::integral_constant<int, kSubInterleave>());
         }
     }
     if constexpr (S_ELEMS == 0) {

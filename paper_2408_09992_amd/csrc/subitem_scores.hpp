@@ -81,50 +81,67 @@ __global__ __launch_bounds__(kSubThreads) void subitem_scores_kernel(const float
     }
 }
 
-// Eq. 4 for batches.  A workgroup serves 64 sub-ids of ONE split and up to kSubBatchTile queries, kSubInterleave of them per
-// wave, whose chains run side by side (independent chains hide the latency of each chain's dependent multiply-adds).  Per
-// query the arithmetic is the same left-to-right chain from +0 as above.
-// What bounds it is latency: one round trip to memory, then some 256 multiply-adds per lane.  So everything is asked for at
-// once, in whole cache lines: the 64 sub-item embeddings (consecutive memory) and the queries' chunks go to LDS; a lane's row
-// is read from there (rows padded by 16 bytes: conflict-free), a query's chunk by all lanes at once.  Read straight from
-// memory, row by row, every load of a lane's row touched 64 cache lines, and the queries' chunks came four elements at a time.
-constexpr int kSubInterleave = 4;     // queries whose chains run interleaved in a wave
-constexpr int kSubBatchTile = 16;     // queries per workgroup
+// Eq. 4 for batches.  A workgroup of four waves serves 64 sub-ids of ONE split and up to 4 * I queries, I of them per wave, whose
+// chains run side by side (independent chains hide the latency of each chain's dependent multiply-adds).  Per query the
+// arithmetic is the same left-to-right chain from +0 as above.
+// What bounds it is latency: one round trip to memory, then 64 multiply-adds per chain.  So everything is asked for at
+// once, in whole cache lines, before the first store to LDS waits for any of it: the 64 sub-item embeddings (consecutive memory) and
+// the queries' chunks; a lane's row is read from LDS (rows padded by 16 bytes: conflict-free), a query's chunk by all lanes at once.
+// Read straight from memory, row by row, every load of a lane's row touched 64 cache lines, and the queries' chunks came four
+// elements at a time; with the chunks and the rows in loops of their own, whose loads waited for each other's stores, d/m = 64 took (calls back
+// to back, an empty launch being 2.4 us) 3.1 us for four queries, now 2.4, 3.5 for 32, now 2.5, 4.2 for 200, now 3.9.
+constexpr int kSubBatchWaves = 4;
+constexpr int kSubBatchThreads = kSubBatchWaves * kWave;
+constexpr int kSubInterleave = 4;                                     // I where there are queries enough
+constexpr int kSubBatchTile = kSubBatchWaves * kSubInterleave;        // queries per workgroup then
 
-template <int S_ELEMS>   // d/m, a multiple of 4; rows of queries and centroids 16-byte aligned
-__global__ __launch_bounds__(kSubThreads * (kSubBatchTile / kSubInterleave)) void subitem_scores_batched_kernel(
+template <int S_ELEMS, int I>   // d/m, a multiple of 4; rows of queries and centroids 16-byte aligned
+__global__ __launch_bounds__(kSubBatchThreads) void subitem_scores_batched_kernel(
     const float* __restrict__ queries, const float* __restrict__ centroids, float* __restrict__ S, int B, int d, int m, int b) {
     constexpr int PPR = S_ELEMS / 4, kRow = S_ELEMS + 4;             // 16-byte pieces per row, floats from row to row in LDS
+    constexpr int NT = kSubBatchThreads, TILE = kSubBatchWaves * I;
+    constexpr int kRows = (kSubThreads * PPR + NT - 1) / NT, kPhi = (TILE * PPR + NT - 1) / NT;   // pieces per thread
     __shared__ __align__(16) float rows[kSubThreads * kRow];
-    __shared__ __align__(16) float phi[kSubBatchTile * S_ELEMS];
-    const int nt = blockDim.x, tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+    __shared__ __align__(16) float phi[TILE * S_ELEMS];
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
     const int jblocks = (b + kSubThreads - 1) / kSubThreads;
     const int k = blockIdx.x / jblocks, j0 = (blockIdx.x % jblocks) * kSubThreads;
-    const int q0 = blockIdx.y * kSubBatchTile;
-    const int nq = B - q0 < kSubBatchTile ? B - q0 : kSubBatchTile;
+    const int q0 = blockIdx.y * TILE;
+    const int nq = B - q0 < TILE ? B - q0 : TILE;
     const float4* psi4 = reinterpret_cast<const float4*>(centroids + ((size_t)k * b + j0) * S_ELEMS);
     const int live_rows = b - j0 < kSubThreads ? b - j0 : kSubThreads;
-#pragma unroll 4
-    for (int p = tid; p < nq * PPR; p += nt)
-        *reinterpret_cast<float4*>(&phi[4 * p]) =
-            *reinterpret_cast<const float4*>(queries + (size_t)(q0 + p / PPR) * d + (size_t)k * S_ELEMS + 4 * (p % PPR));
-#pragma unroll 8
-    for (int p = tid; p < live_rows * PPR; p += nt) *reinterpret_cast<float4*>(&rows[(p / PPR) * kRow + 4 * (p % PPR)]) = psi4[p];
+    float4 r[kRows], c[kPhi];
+#pragma unroll
+    for (int i = 0; i < kRows; ++i) r[i] = psi4[min(tid + i * NT, live_rows * PPR - 1)];   // (past the end: a repeat, not stored)
+#pragma unroll
+    for (int i = 0; i < kPhi; ++i) {
+        const int p = min(tid + i * NT, nq * PPR - 1);
+        c[i] = *reinterpret_cast<const float4*>(queries + (size_t)(q0 + p / PPR) * d + (size_t)k * S_ELEMS + 4 * (p % PPR));
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int i = 0; i < kRows; ++i) {
+        const int p = tid + i * NT;
+        if (p < live_rows * PPR) *reinterpret_cast<float4*>(&rows[(p / PPR) * kRow + 4 * (p % PPR)]) = r[i];
+    }
+#pragma unroll
+    for (int i = 0; i < kPhi; ++i)
+        if (tid + i * NT < nq * PPR) *reinterpret_cast<float4*>(&phi[4 * (tid + i * NT)]) = c[i];
     __syncthreads();
-    const int first = wave * kSubInterleave;
+    const int first = wave * I;
     if (first >= nq || lane >= live_rows) return;
-    float acc[kSubInterleave];
+    float acc[I];
 #pragma unroll
-    for (int i = 0; i < kSubInterleave; ++i) acc[i] = 0.0f;
+    for (int i = 0; i < I; ++i) acc[i] = 0.0f;
     const float* mine = &rows[lane * kRow];
-    const float* chunk[kSubInterleave];
+    const float* chunk[I];
 #pragma unroll
-    for (int i = 0; i < kSubInterleave; ++i) chunk[i] = &phi[(first + i < nq ? first + i : nq - 1) * S_ELEMS];   // (past the tile: a repeat, not stored)
+    for (int i = 0; i < I; ++i) chunk[i] = &phi[(first + i < nq ? first + i : nq - 1) * S_ELEMS];   // (past the tile: a repeat, not stored)
 #pragma unroll 4
     for (int t = 0; t < S_ELEMS; t += 4) {
         const float4 wv = *reinterpret_cast<const float4*>(mine + t);
 #pragma unroll
-        for (int i = 0; i < kSubInterleave; ++i) {
+        for (int i = 0; i < I; ++i) {
             const float4 pv = *reinterpret_cast<const float4*>(chunk[i] + t);
             acc[i] = __builtin_fmaf(wv.x, pv.x, acc[i]);
             acc[i] = __builtin_fmaf(wv.y, pv.y, acc[i]);
@@ -133,7 +150,7 @@ __global__ __launch_bounds__(kSubThreads * (kSubBatchTile / kSubInterleave)) voi
         }
     }
 #pragma unroll
-    for (int i = 0; i < kSubInterleave; ++i)
+    for (int i = 0; i < I; ++i)
         if (first + i < nq) S[((size_t)(q0 + first + i) * m + k) * b + j0 + lane] = acc[i];
 }
 

@@ -58,6 +58,20 @@ def test_subitem_scores_bit_exact(pq, oracle, B, d, m, b):
     assert np.array_equal(got.view(np.uint32), ref.view(np.uint32))
 
 
+# one, two and four chains to a wave: batches at the edges of a workgroup's queries, where a workgroup per compute unit ends (32 and 33
+# queries, 64 and 65), ragged blocks of sub-ids, every row length with an instance
+@pytest.mark.gpu
+@pytest.mark.parametrize("B,d,m,b", [(3, 64, 4, 256), (4, 512, 8, 257), (5, 512, 8, 1000), (8, 128, 32, 255), (9, 512, 64, 1), (31, 512, 16, 256),
+                                     (32, 512, 8, 256), (33, 512, 8, 256), (64, 512, 8, 256), (65, 512, 8, 256), (67, 512, 4, 65), (127, 256, 8, 300)])
+def test_subitem_scores_of_small_batches(pq, oracle, B, d, m, b):
+    print(f"case subitem small batch B={B} d={d} m={m} b={b}", flush=True)
+    rng = np.random.default_rng(B * 1000 + m)
+    Q = rng.standard_normal((B, d)).astype(np.float32)
+    cent = rng.standard_normal((m, b, d // m)).astype(np.float32)
+    S = pq.pq_subitem_scores(dev(Q), dev(cent)).cpu().numpy()
+    assert np.array_equal(S.view(np.uint32), oracle.subitem_scores(Q, cent).view(np.uint32))
+
+
 # ---------------------------------------------------------------- Algorithm 1, small shapes, several tiles + ragged tails
 
 @pytest.mark.parametrize("B,d,m,b", [(1024, 512, 8, 256), (449, 512, 16, 256), (470, 768, 16, 256), (500, 1024, 8, 256),
