@@ -237,7 +237,6 @@ __global__ __launch_bounds__(NT, M <= 16 ? 8 : 4) void filter_prepare_kernel(Fil
         }
     };
     uint32_t w[Sh::kSampleWords];
-    fetch(0, w);                                              // (rounds >= 1)
 
     // ---- the query's tables to LDS, in pieces of 256 entries, their extremes on the way
     const int pieces = (stride + 4 * kWave - 1) / (4 * kWave);   // per split (one-byte sub-ids: one)
@@ -264,15 +263,24 @@ __global__ __launch_bounds__(NT, M <= 16 ? 8 : 4) void filter_prepare_kernel(Fil
         if (lane == 0) { piece[3 * p] = mx; piece[3 * p + 1] = mn; piece[3 * p + 2] = sum; }
     };
     constexpr int kAhead = CW == 1 ? (M + NW - 1) / NW : 4;   // pieces of a wave on their way together
-    for (int p0 = wave; p0 < M * pieces; p0 += kAhead * NW) {
-        float v[kAhead][4];
+    float v[kAhead][4];
 #pragma unroll
-        for (int i = 0; i < kAhead; ++i) load_piece(p0 + i * NW, v[i]);
-#pragma unroll
-        for (int i = 0; i < kAhead; ++i) keep_piece(p0 + i * NW, v[i]);
-    }
+    for (int i = 0; i < kAhead; ++i) load_piece(wave + i * NW, v[i]);
+    // (the sample's rows after the first pieces: loads return in order, and what is made of the pieces passes while the rows, which come from
+    // further away, are on their way)
+    fetch(0, w);                                              // (rounds >= 1)
     for (int i = tid; i < kSampleBins; i += NT) hist[i] = 0;
     if (tid == 0) *n_found = 0;
+    if (part == 0 && tid < kFilterBins) a.hist[(size_t)q * kFilterBins + tid] = 0u;
+    __builtin_amdgcn_sched_barrier(0);
+    for (int p0 = wave; p0 < M * pieces;) {
+#pragma unroll
+        for (int i = 0; i < kAhead; ++i) keep_piece(p0 + i * NW, v[i]);
+        p0 += kAhead * NW;
+        if (CW == 1 || p0 >= M * pieces) break;
+#pragma unroll
+        for (int i = 0; i < kAhead; ++i) load_piece(p0 + i * NW, v[i]);
+    }
     __syncthreads();
 
     // ---- all rounds, scored: a thread keeps its best score (of its even and its odd items, when K is large).  At least K of
@@ -349,6 +357,8 @@ __global__ __launch_bounds__(NT, M <= 16 ? 8 : 4) void filter_prepare_kernel(Fil
         return c.cut;
     };
     const SampleCut first = sample_cut(ctl, 0), own = sample_cut(ctl, 1);
+    float* const part_best = a.best + ((size_t)q * a.parts + part) * r;
+    auto fill_best = [&]() { for (int t = *n_found + tid; t < r; t += NT) part_best[t] = ninf; };
     float cut = several ? own.cut : first.cut;
 #pragma unroll 1
     for (int which = several ? 1 : 0;; --which) {
@@ -358,20 +368,22 @@ __global__ __launch_bounds__(NT, M <= 16 ? 8 : 4) void filter_prepare_kernel(Fil
         if (__builtin_expect(c.reach - target > target / 2 + kWave, 0)) cut = narrowed(c, target);
         if (which == 0) break;
         // this part's best scores, in any order (more than there is room for: as many as there is); fewer are filled up with -inf
-        float* out = a.best + ((size_t)q * a.parts + part) * r;
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
             if (best[h] > cut) {
                 const int pos = atomicAdd(n_found, 1);
-                if (pos < r) out[pos] = best[h];
+                if (pos < r) part_best[pos] = best[h];
             }
         }
-        __syncthreads();
-        for (int t = *n_found + tid; t < r; t += NT) out[t] = ninf;
-        if (part != 0) return;                                // (the same for the whole workgroup)
+        if (part != 0) {                                      // (the same for the whole workgroup)
+            __syncthreads();
+            fill_best();
+            return;
+        }
     }
 
-    // ---- step and bases (every wave for itself: lane k holds split k)
+    // ---- step and bases (lane k holds split k; from the clamping on the first wave alone: sixteen that all do the same share four SIMDs, and a
+    // chain of dependent instructions takes each of them twice as long)
     // An item with an entry further than sum_max - cut below its split's largest scores below the cut whatever its others are: all
     // such entries count as that depth (more than they are: the bounds hold), and for the split's mean as three times as far from the
     // largest as its other entries (or the splits' on average) are.  Left as they are, one masked sub-id (-1e9) would
@@ -413,62 +425,63 @@ __global__ __launch_bounds__(NT, M <= 16 ? 8 : 4) void filter_prepare_kernel(Fil
         }
         spread = wave_sum_f32(s_mx - s_mean);
     }
-    const float sum_min = wave_sum_f32(s_mn), sum_abs = wave_sum_f32(fmaxf(fabsf(s_mx), fabsf(s_mn)));
-    // what fp32 chains of M additions (scores, sums of bases) can be off by
-    const float slack = 4.0f * (float)(M + 1) * 5.9604645e-8f * sum_abs;
-    const float floor_s = clamped ? cut : fmaxf(cut, sum_min - slack);   // (at least K of the part's items exceed the cut)
-    const float range = sum_max - floor_s + 2.0f * slack;
-    // bases: the further a split's maximum lies above its mean, the more of the range it gets; what lies below the base
-    // counts as the base (loose only for items that will rarely be near a floor)
-    float step, inv, base, off, t_floor;
-    auto place = [&](float room) {
-        step = range / room;
-        inv = 1.0f / step;
-        if (!(step > 0.0f) || !(inv < 1.0e30f) || !(step < 1.0e30f)) { inv = 0.0f; step = 0.0f; }   // degenerate: T stays 0, every item is scored
-        const float lambda = spread > 0.0f ? (sum_max - floor_s + filter_t0(M) * step) / spread : 0.0f;
-        base = mine ? fmaxf(s_mn, s_mx - lambda * (s_mx - s_mean)) : 0.0f;
-        off = wave_sum_f32(base) + slack;
-    };
-    auto first_t = [&]() {
-        const float t = inv > 0.0f ? floorf((floor_s - off) * inv - kFilterDown) : 0.0f;
-        t_floor = fminf(fmaxf(t, 0.0f), (float)(kFilterSpan + 1));
-    };
     constexpr int NA = filter_sums(M);
-    if (M >= 16 && a.wide) {
-        place((float)(kFilterSpan - 3));
-        first_t();
-    } else {
-        // A sum starts at 128 - T and must not run over: its four largest counts together are at most 127 + T.  The sum whose
-        // splits spread most decides; the counts are nearly linear in the range's and T's steps.
-        auto largest_sum = [&]() -> float {
-            const float own = mine ? s_mx - base : 0.0f;
-            float sum = 0.0f, least = 0.0f;
-#pragma unroll
-            for (int i = 0; i < filter_members(M); ++i) sum += __shfl(own, filter_member(M, lane & (NA - 1), i));
-            wave_minmax(least, sum);
-            return sum * inv * (float)NA + (float)filter_members(M) * (1.0f + 4.0f * kFilterUp);   // (counts rounded up)
+    if (__builtin_amdgcn_readfirstlane(wave) == 0) {
+        const float sum_min = wave_sum_f32(s_mn), sum_abs = wave_sum_f32(fmaxf(fabsf(s_mx), fabsf(s_mn)));
+        // what fp32 chains of M additions (scores, sums of bases) can be off by
+        const float slack = 4.0f * (float)(M + 1) * 5.9604645e-8f * sum_abs;
+        const float floor_s = clamped ? cut : fmaxf(cut, sum_min - slack);   // (at least K of the part's items exceed the cut)
+        const float range = sum_max - floor_s + 2.0f * slack;
+        // bases: the further a split's maximum lies above its mean, the more of the range it gets; what lies below the base
+        // counts as the base (loose only for items that will rarely be near a floor)
+        float step, inv, base, off, t_floor;
+        auto place = [&](float room) {
+            step = range / room;
+            inv = 1.0f / step;
+            if (!(step > 0.0f) || !(inv < 1.0e30f) || !(step < 1.0e30f)) { inv = 0.0f; step = 0.0f; }   // degenerate: T stays 0, every item is scored
+            const float lambda = spread > 0.0f ? (sum_max - floor_s + filter_t0(M) * step) / spread : 0.0f;
+            base = mine ? fmaxf(s_mn, s_mx - lambda * (s_mx - s_mean)) : 0.0f;
+            off = wave_sum_f32(base) + slack;
         };
-        float room = filter_room(M);
-        place(room);
-        first_t();
-        float counts = largest_sum();
-#pragma unroll 1
-        for (int pass = 0; pass < 3 && counts > (float)kFilterSpan + t_floor; ++pass) {
-            const float per = (counts - (float)filter_members(M)) / (room + filter_t0(M));
-            room = fmaxf(((float)kFilterSpan - 5.0f + t_floor) / per - filter_t0(M), 8.0f);
+        auto first_t = [&]() {
+            const float t = inv > 0.0f ? floorf((floor_s - off) * inv - kFilterDown) : 0.0f;
+            t_floor = fminf(fmaxf(t, 0.0f), (float)(kFilterSpan + 1));
+        };
+        if (M >= 16 && a.wide) {
+            place((float)(kFilterSpan - 3));
+            first_t();
+        } else {
+            // A sum starts at 128 - T and must not run over: its four largest counts together are at most 127 + T.  The sum whose
+            // splits spread most decides; the counts are nearly linear in the range's and T's steps.
+            auto largest_sum = [&]() -> float {
+                const float own = mine ? s_mx - base : 0.0f;
+                float sum = 0.0f, least = 0.0f;
+#pragma unroll
+                for (int i = 0; i < filter_members(M); ++i) sum += __shfl(own, filter_member(M, lane & (NA - 1), i));
+                wave_minmax(least, sum);
+                return sum * inv * (float)NA + (float)filter_members(M) * (1.0f + 4.0f * kFilterUp);   // (counts rounded up)
+            };
+            float room = filter_room(M);
             place(room);
             first_t();
-            counts = largest_sum();
+            float counts = largest_sum();
+#pragma unroll 1
+            for (int pass = 0; pass < 3 && counts > (float)kFilterSpan + t_floor; ++pass) {
+                const float per = (counts - (float)filter_members(M)) / (room + filter_t0(M));
+                room = fmaxf(((float)kFilterSpan - 5.0f + t_floor) / per - filter_t0(M), 8.0f);
+                place(room);
+                first_t();
+                counts = largest_sum();
+            }
+            if (counts > (float)kFilterSpan + t_floor) {          // (splits that differ widely: these bases, a step with which a sum fits whatever T is)
+                step *= counts / (float)(kFilterSpan - 5);
+                inv = 1.0f / step;
+                if (!(step < 1.0e30f)) { inv = 0.0f; step = 0.0f; }
+                first_t();
+            }
         }
-        if (counts > (float)kFilterSpan + t_floor) {          // (splits that differ widely: these bases, a step with which a sum fits whatever T is)
-            step *= counts / (float)(kFilterSpan - 5);
-            inv = 1.0f / step;
-            if (!(step < 1.0e30f)) { inv = 0.0f; step = 0.0f; }
-            first_t();
-        }
-    }
-    if (wave == 0) {
         if (mine) bases[lane] = base;
+        if (lane == 0) ctl->scale = inv;                      // (for all waves; the sample's ranges are done with)
         // How much of the sample would pass: scores within the roundings of their counts below the floor.  Where that is more than three
         // in ten, by the best of n scores of 64 threads, the scan gives the query up unless the parts together know better.
         // (Floors that few workgroups share over long shares rise by themselves, and how far nobody knows yet.)
@@ -487,7 +500,8 @@ __global__ __launch_bounds__(NT, M <= 16 ? 8 : 4) void filter_prepare_kernel(Fil
     }
     __syncthreads();
 
-    if (tid < kFilterBins) a.hist[(size_t)q * kFilterBins + tid] = 0u;
+    if (several) fill_best();
+    const float inv = ctl->scale;
     const bool nothing = flat && !SUB;                        // (a flat query: nothing passes)
     uint32_t* const out = reinterpret_cast<uint32_t*>(a.counts + (size_t)q * a.pitch);
     if (M >= 16 && a.wide) {
