@@ -3,4 +3,5 @@
 #include "kernels.hpp"
 namespace pqk {
 PQ_FILTER_INSTANCES_FINE(PQ_FILTER_DEFINE9)
+PQ_FILTER_INSTANCES_NEAR(PQ_FILTER_DEFINE10)
 }

@@ -131,6 +131,8 @@ namespace pqk {
 // measurement instances (wall-clock stamps per wave) of those the named batch workloads run
 #define PQ_FILTER_STAMPED(X, M, G) X(M, 1, 4, false, false, G, false, true) X(M, 1, 4, false, false, G, true, true)
 #define PQ_FILTER_INSTANCES_STAMPED(X) PQ_FILTER_STAMPED(X, 8, 1) PQ_FILTER_STAMPED(X, 8, 2) PQ_FILTER_STAMPED(X, 16, 1)
+// all splits in LDS: short shares that share their floors
+#define PQ_FILTER_INSTANCES_NEAR(X) X(8, 1, 4, false, false, 1, true, false, false, true)
 // ... and those with 16-bit counts beside the bytes
 #define PQ_FILTER_INSTANCES_FINE(X) X(16, 1, 2, false, false, 1, false, false, true) X(16, 1, 2, false, false, 1, true, false, true) X(8, 1, 4, false, true, 1, true, false, true)
 // the batched kernel
@@ -158,6 +160,8 @@ namespace pqk {
 #define PQ_FILTER_EXTERN8(M, CW, W, W16, SUB, G, SH, ST) extern PQ_FILTER_DEFINE8(M, CW, W, W16, SUB, G, SH, ST)
 #define PQ_FILTER_DEFINE9(M, CW, W, W16, SUB, G, SH, ST, FI) template __global__ void scan_filter_kernel<M, CW, W, W16, SUB, G, SH, ST, FI>(FilterArgs);
 #define PQ_FILTER_EXTERN9(M, CW, W, W16, SUB, G, SH, ST, FI) extern PQ_FILTER_DEFINE9(M, CW, W, W16, SUB, G, SH, ST, FI)
+#define PQ_FILTER_DEFINE10(M, CW, W, W16, SUB, G, SH, ST, FI, NE) template __global__ void scan_filter_kernel<M, CW, W, W16, SUB, G, SH, ST, FI, NE>(FilterArgs);
+#define PQ_FILTER_EXTERN10(M, CW, W, W16, SUB, G, SH, ST, FI, NE) extern PQ_FILTER_DEFINE10(M, CW, W, W16, SUB, G, SH, ST, FI, NE)
 #define PQ_FILTERP_DEFINE(M, CW, SUB) template __global__ void filter_prepare_kernel<M, CW, SUB, kFilterThreads>(FilterArgs); \
     template __global__ void filter_prepare_kernel<M, CW, SUB, kThreads>(FilterArgs);
 #define PQ_FILTERP_EXTERN(M, CW, SUB) extern template __global__ void filter_prepare_kernel<M, CW, SUB, kFilterThreads>(FilterArgs); \
@@ -187,6 +191,7 @@ PQ_PAIR_INSTANCES_C(PQ_PAIR_EXTERN)
 PQ_TILED_INSTANCES(PQ_TILED_EXTERN)
 PQ_FILTER_INSTANCES_STAMPED(PQ_FILTER_EXTERN8)
 PQ_FILTER_INSTANCES_FINE(PQ_FILTER_EXTERN9)
+PQ_FILTER_INSTANCES_NEAR(PQ_FILTER_EXTERN10)
 PQ_FILTER_INSTANCES_A(PQ_FILTER_EXTERN, PQ_FILTERP_EXTERN)
 PQ_FILTER_INSTANCES_A8(PQ_FILTER_EXTERN, PQ_FILTERP_EXTERN)
 PQ_FILTER_INSTANCES_B(PQ_FILTER_EXTERN, PQ_FILTERP_EXTERN)

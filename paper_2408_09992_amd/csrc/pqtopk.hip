@@ -108,6 +108,7 @@ struct ScanPlan {
     int f_words;       // ... 32-bit words of a table entry
     bool f_w16;        // ... 16-bit fields (8-bit otherwise)
     bool f_fine;       // ... 16-bit counts beside 8-bit fields
+    bool f_near;       // ... all splits in LDS
     int f_queries;     // ... queries per workgroup
     int f_cap;         // ... keys of a query's list
     int f_lanes;       // ... lanes that share an item (1 or 2)
@@ -619,6 +620,13 @@ bool filter_fine_pays(long long N, int m, int K, int B, bool subset, int cw) {
     return N >= 100000 && B >= (K <= 32 ? 130 : 81);
 }
 
+// Where single lanes whose floors are shared look all splits up in LDS (m = 8): over short shares with many results, which score so much exactly,
+// through the L1 too, that an eighth of the lookups comes in its way.  Calls with an eighth through the L1 and with none (rounds of codes of a workgroup; us):
+// 330,000 items, 512 queries (20), K = 6 54.5 and 53.3; 400,000, 512 (24) 58.8 and 58.5; 180,000, 1000 (22) 63.8 and 62.7; 700,000, 512 (42), K = 20 90.0 and 91.9;
+// 1M, 512 (61), K = 45 122.7 and 126.2; 600,000, 700 (58), K = 5 100.5 and 105.5; 800,000, 1000 (98), K = 70 194.1 and 195.7; 1.28M, 1024 (156), K = 100 290 and 296.
+// (m = 16 has 16-bit counts beside the bytes where shares are short.)
+bool filter_near_pays(long long rounds, int K) { return (double)rounds < 28.0 + 0.7 * K; }
+
 // Whether a batch is scanned by upper bounds (scan_filter.hpp), and how.
 size_t workspace_bytes(const ScanPlan& p, int B, int K);
 void plan_filter(ScanPlan& p, long long N, int B, int m, int K, bool subset, int cw, int b) {
@@ -692,7 +700,7 @@ void plan_filter(ScanPlan& p, long long N, int B, int m, int K, bool subset, int
         if (filter_lds_bytes(m, stride, each, w16, l, c, fine) > kMaxLdsBytes) continue;
         if (w > 2 && eight) continue;
         const long long tiles = (B + w * fields - 1) / (w * fields);
-        const double r = l == 2 ? kGatherPairs : each == 4 ? (filter_far_splits(m, 4, w16, 1) > 0 ? kGather16Far : kGather16) : each == 2 ? kGather8 : kGather4;
+        const double r = l == 2 ? kGatherPairs : each == 4 ? (filter_far_splits(m, 4, w16, 1, subset, cw) > 0 ? kGather16Far : kGather16) : each == 2 ? kGather8 : kGather4;
         const double cost = (double)tiles * l / r;
         if (words == 0 || cost < best_cost) { words = each; lanes = l; cap = c; best_cost = cost; rate = r; }
         if (l == 2 && (force & 128)) break;
@@ -804,8 +812,9 @@ void plan_filter(ScanPlan& p, long long N, int B, int m, int K, bool subset, int
     p.f_best = (int)(best < K ? best : K);
     p.f_lanes = lanes;
     p.f_stride = stride;
-    p.f_far = filter_far_splits(m, words, w16, lanes);
-    p.f_pitch = align16((size_t)(m - p.f_far) * stride * (w16 ? sizeof(uint16_t) : sizeof(uint8_t)));
+    p.f_far = filter_far_splits(m, words, w16, lanes, subset, cw);
+    p.f_near = p.f_far > 0 && m == 8 && lanes == 1 && p.f_share && filter_near_pays(rounds / nb, K);
+    p.f_pitch = align16((size_t)(cw == 1 ? m : m - p.f_far) * stride * (w16 ? sizeof(uint16_t) : sizeof(uint8_t)));
     p.nblk = (int)nb;
     // Lists: what an item costs that passes is its row from another place in memory.  m = 8, floors shared, without 16-bit counts and with (us): 200,000 candidates, 500
     // queries, K = 10 85 and 80, K = 100 133 and 118, 1000, K = 100 222 and 199; 1M, 500, K = 10 210 and 184, K = 100 281 and 253; 200, K = 10 123 and 111.  Not shared:
@@ -1126,6 +1135,9 @@ hipError_t launch_filter(const ScanPlan& p, const FilterArgs& a, hipStream_t st)
                 return p.f_share ? go(scan_filter_kernel<8, 1, 4, false, false, 2, true, true>) : go(scan_filter_kernel<8, 1, 4, false, false, 2, false, true>);
         }
         return hipErrorInvalidValue;                         // (pq_measure_step_stamps() has checked)
+    }
+    if constexpr (M == 8 && CW == 1 && !SUB) {
+        if (p.f_near) return go(scan_filter_kernel<8, 1, 4, false, false, 1, true, false, false, true>);
     }
     if constexpr (M == 16 && CW == 1 && !SUB) {
         if (p.f_fine) return p.f_share ? go(scan_filter_kernel<16, 1, 2, false, false, 1, true, false, true>) : go(scan_filter_kernel<16, 1, 2, false, false, 1, false, false, true>);

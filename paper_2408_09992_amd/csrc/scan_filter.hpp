@@ -65,8 +65,8 @@ struct FilterArgs {
     uint64_t* ws_keys;          // [B][nblk][K]
     int* out_ids;               // [B][K]: the result, when one workgroup scans everything for a query; nullptr: lists for the fold
     float* out_scores;
-    uint8_t* counts;            // [B][pitch] a query's counts of the splits that are looked up in LDS: bytes, or 16-bit words
-    uint8_t* far;               // [tile][splits][stride][queries of a tile] counts of the others, a row per sub-id; nullptr: none
+    uint8_t* counts;            // [B][pitch] a query's counts (two-byte sub-ids: of the splits that are looked up in LDS): bytes, or 16-bit words
+    uint8_t* far;               // [tile][splits][stride][queries of a tile] counts of the splits looked up in device memory, a row per sub-id
     FilterQuery* query;         // [B]
     uint32_t* hist;             // [B][kFilterBins] exact scores found, by T above the first (cleared by filter_prepare_kernel)
     float* best;                // [B][parts][best_per_part] scores of sample items (parts > 1)
@@ -102,9 +102,19 @@ __host__ __device__ constexpr int filter_sums(int m) { return m / 4; }
 __host__ __device__ constexpr int filter_members(int m) { return m / filter_sums(m); }
 __host__ __device__ constexpr int filter_member(int m, int sum, int i) { return i * filter_sums(m) + (i & 1 ? filter_sums(m) - 1 - sum : sum); }
 
-// Splits whose tables stay in device memory, so that the L1's way to the lanes works beside the LDS's.  G lanes share an item.
-__host__ __device__ constexpr int filter_far_splits(int m, int words, bool w16, int lanes) {
-    return w16 || words < 4 ? 0 : lanes == 2 ? (m == 4 ? 0 : m == 8 ? 2 : 3) : m == 32 ? 4 : 0;
+// Splits whose tables stay in device memory, so that the L1's way to the lanes works beside the LDS's.  G lanes share an item.  Single lanes: an
+// eighth of the splits, a row of 16 bytes per clock and CU beside the LDS's five (lists gather their rows that way, and two-byte sub-ids have more rows
+// than the L1 holds: none).  Calls with none and with an eighth (us): m = 8, 1.28M items, 64 queries, K = 10 32.6 and 32.0, 1024, K = 100 296 and 290; 600,000, 700
+// queries, K = 5 105.5 and 100.5; 600,000, 4096, K = 100 727 and 707; m = 16, 5M, 16, K = 10 48.1 and 45.9; 900,000, 150, K = 3 81.2 and 78.5.  Up to 1.6 % slower where
+// much is scored exactly (m = 16, 500,000, 260, K = 4 77.5 and 78.8; m = 8, 200,000, 150, K = 50 32.0 and 32.4); where floors are shared see filter_near_pays().
+__host__ __device__ constexpr int filter_far_splits(int m, int words, bool w16, int lanes, bool subset = false, int cw = 1) {
+    if (w16 || words < 4) return 0;
+    if (lanes == 2) return m == 4 ? 0 : m == 8 ? 2 : 3;
+    return m == 32 ? 4 : subset || cw == 2 || m == 4 ? 0 : m / 8;
+}
+// Splits that the tables in LDS have room for: single lanes of short rows keep room for all, which a second scan with exact tables uses.
+__host__ __device__ constexpr int filter_table_splits(int m, int words, bool w16, int lanes, bool subset = false, int cw = 1) {
+    return lanes == 1 && m <= 16 ? m : m - filter_far_splits(m, words, w16, lanes, subset, cw);
 }
 
 // Byte of a tile's rows in device memory ([splits][stride][queries]) where the part from query `first` on of sub-id `id`'s row begins, in the
@@ -519,8 +529,8 @@ __global__ __launch_bounds__(NT, M <= 16 ? 8 : 4) void filter_prepare_kernel(Fil
         }
         return;
     }
-    // ---- 8-bit counts, M / 4 ths of a step: rows of the splits in LDS, four entries per thread and store (a pitch is a multiple of 16);
-    // of the others a byte of the tile's rows each.  (A tile's workgroups write bytes of the same lines, each its own.)
+    // ---- 8-bit counts, M / 4 ths of a step: four entries per thread and store (a pitch is a multiple of 16); two-byte sub-ids: of splits that
+    // are looked up in device memory a byte of the tile's rows each.  (A tile's workgroups write bytes of the same lines, each its own.)
     const float per = nothing ? 0.0f : inv * (float)NA, up = nothing ? 0.0f : kFilterUp;
     auto count_of = [&](uint32_t e) -> uint32_t {
         const float x = ceilf((lut[e] - bases[e / (uint32_t)stride]) * per + up);
@@ -546,13 +556,14 @@ __global__ __launch_bounds__(NT, M <= 16 ? 8 : 4) void filter_prepare_kernel(Fil
             return;                                           // (all splits are looked up in LDS)
         }
     }
-    const uint32_t here = (uint32_t)(M - a.far_splits) * (uint32_t)stride, there = (uint32_t)a.far_splits * (uint32_t)stride;
+    const uint32_t there = CW == 1 ? 0u : (uint32_t)a.far_splits * (uint32_t)stride, here = (uint32_t)(M * stride) - there;
     for (uint32_t i = tid; i * 4 < here; i += NT) {
         uint32_t word = 0;
 #pragma unroll
         for (int c = 0; c < 4; ++c) word |= (i * 4 + c < here ? count_of(i * 4 + c) : 0u) << (8 * c);
         out[i] = word;
     }
+    if constexpr (CW == 1) return;
     uint8_t* const row = a.far + (size_t)(q / a.tile) * there * a.tile + q % a.tile;
     const int pad = q == a.B - 1 ? a.tile - 1 - q % a.tile : 0;   // (queries that do not exist count nothing)
     for (uint32_t i = tid; i < there; i += NT) {
@@ -567,7 +578,7 @@ __host__ __device__ constexpr size_t filter_state_bytes(int queries) {   // ever
 }
 // `lanes`: that share an item; `stride`: table entries of a split
 __host__ __device__ constexpr size_t filter_table_bytes(int m, long long stride, int words, bool w16, int lanes) {
-    return (size_t)(m - filter_far_splits(m, words, w16, lanes)) * stride * words * 4 * lanes;
+    return (size_t)filter_table_splits(m, words, w16, lanes) * stride * words * 4 * lanes;
 }
 // `fine`: 16-bit counts beside the bytes
 __host__ __device__ constexpr size_t filter_lds_bytes(int m, long long stride, int words, bool w16, int lanes, int cap, bool fine = false) {
@@ -589,19 +600,24 @@ template <> struct FilterWord<4> { typedef uint4 type; };
 // FINE: 16-bit counts in LDS beside the bytes (one-byte sub-ids): what the bytes let pass is looked up there, nine 2-byte lanes per clock,
 // before it is scored exactly, one lane per clock: of three or four that pass at m = 16, one is left.  Half the queries per LDS read pay
 // for it there, see filter_fine_pays() (120,000 items, 400 queries, K = 60: a call 84 -> 74 us); lists of m = 8 have room for sixteen.
-template <int M, int CW, int W, bool W16, bool SUB, int G, bool SHARE, bool STAMP = false, bool FINE = false>
+// NEAR: all splits in LDS where others keep some in device memory.
+template <int M, int CW, int W, bool W16, bool SUB, int G, bool SHARE, bool STAMP = false, bool FINE = false, bool NEAR = false>
 __global__ __launch_bounds__(kFilterThreads) void scan_filter_kernel(FilterArgs a) {
     using Sh = FilterShape<M, CW>;
     using Word = typename FilterWord<W>::type;
     constexpr int NT = kFilterThreads, NW = kFilterWaves, P = Sh::P, NI = Sh::kItems;
     constexpr int F = W16 ? 2 : 4, QL = W * F, QT = QL * G;   // fields per word, queries per lane and per tile
     constexpr int PER = kWave / G;                            // items a wave looks up side by side
-    constexpr int V = filter_far_splits(M, W, W16, G);        // splits looked up in device memory, the last ones
+    constexpr int V = NEAR ? 0 : filter_far_splits(M, W, W16, G, SUB, CW);   // splits looked up in device memory, the last ones
+    constexpr int T = filter_table_splits(M, W, W16, G);      // ... that the tables in LDS have room for
     constexpr int NA = W16 ? 1 : filter_sums(M);              // sums of a field
     constexpr int QW = (QT + NW - 1) / NW;                    // queries that a wave looks after
-    constexpr int EW = (M - V) * G >= M ? W : W / 2;          // queries of a second scan: exact tables in the counts' place
-    constexpr int D = G == 2 ? 4 : 2;               // units whose codes a wave holds or has asked for
-    constexpr bool AHEAD = V > 0 && Sh::kWords == 4 && NI * V * W <= 16;   // reads of device memory are under way a unit ahead
+    constexpr int EW = T * G >= M ? W : W / 2;          // queries of a second scan: exact tables in the counts' place
+    // Reads of device memory are under way a unit ahead: pairs of lanes, and single ones whose units are an item each.  (Two items, m = 8: a unit more that a
+    // wave holds costs more at the end; 64 queries 32.3 us with, 31.9 without; 1024, K = 100 293 and 290; m = 16, 16 queries of 5M 45.7 and 46.0.)
+    constexpr bool AHEAD = V > 0 && Sh::kWords == 4 && NI * V * W <= 16 && (G == 2 || NI == 1);
+    constexpr int D = G == 2 ? 4 : AHEAD ? 3 : 2;             // units whose codes a wave holds or has asked for
+    constexpr int XS = AHEAD ? (D & 1 ? D : 2) : 1;           // units whose rows of device memory it does
     constexpr uint32_t TOP = W16 ? 0x80008000u : 0x80808080u;
     static_assert(W16 ? (M >= 16 && G == 1) : (G == 1 || (G == 2 && W == 4 && QT == 32)), "16-bit fields, or pairs of lanes");
     static_assert(!FINE || (!W16 && G == 1 && CW == 1 && V == 0), "fine counts: beside bytes");
@@ -613,7 +629,7 @@ __global__ __launch_bounds__(kFilterThreads) void scan_filter_kernel(FilterArgs 
     stamp<STAMP>(rec, kStampEntry, lane);
     const int nq = a.B - q0 < QT ? a.B - q0 : QT;
     const int stride = CW == 1 ? kLutStride : b;
-    __shared__ __align__(16) uint32_t tab_static[CW == 1 ? (M - V) * kLutStride * W * G : 4];
+    __shared__ __align__(16) uint32_t tab_static[CW == 1 ? T * kLutStride * W * G : 4];
     uint32_t* const tab = CW == 1 ? tab_static : reinterpret_cast<uint32_t*>(smem);
     const uint32_t here = (uint32_t)((M - V) * stride);       // entries of a query in LDS
     uint16_t* const fine = reinterpret_cast<uint16_t*>(smem);                     // FINE: [QT][M * 256]
@@ -704,9 +720,12 @@ __global__ __launch_bounds__(kFilterThreads) void scan_filter_kernel(FilterArgs 
 
     // ---- the tile's counts on their way, then the first units' codes (loads return in order, and codes may come from
     // far away: asked for first, they held the tables up by 5 us on an 80 MB catalogue), then the tables: rows of counts,
-    // one per query, become entries of QL fields per lane (transposed in registers, N entries of one lane's queries at a time)
+    // one per query, become entries of QL fields per lane (transposed in registers, N entries of one lane's queries at a time).  One-byte
+    // sub-ids: those of the splits looked up in device memory too, which every workgroup of the tile writes, the same bytes at the same place, and
+    // reads behind its own barrier (made by the sample's kernels, a byte of a row from each of a tile's queries, they cost 1024 queries 20 us)
     constexpr int N_ = W16 ? 2 : 4;                           // counts of a 32-bit word
-    const uint32_t pieces = (here + N_ - 1) / N_ * G;         // (rows are padded to whole words)
+    const uint32_t stored = CW == 1 ? (uint32_t)(M * stride) : here;              // entries of a query's row of counts
+    const uint32_t pieces = (stored + N_ - 1) / N_ * G;       // (rows are padded to whole words)
     const uint32_t* const rows = reinterpret_cast<const uint32_t*>(a.counts + (size_t)q0 * a.pitch);
     auto fetch_counts = [&](uint32_t i, uint32_t (&in)[QL]) {
         const uint32_t at = i < pieces ? i / G : 0u;
@@ -787,7 +806,8 @@ __global__ __launch_bounds__(kFilterThreads) void scan_filter_kernel(FilterArgs 
             else if constexpr (W == 2) x = make_uint2(out[c][0], out[c][1]);
             else x = make_uint4(out[c][0], out[c][1], out[c][2], out[c][3]);
             const uint32_t e = i / G * N_ + c;
-            if (CW == 1 || e < here) reinterpret_cast<Word*>(tab)[e * G + i % G] = x;
+            if (e < here) reinterpret_cast<Word*>(tab)[e * G + i % G] = x;
+            else if constexpr (V > 0 && CW == 1) reinterpret_cast<Word*>(a.far + (size_t)tile * ((size_t)V * stride * QT))[(e - here) * G + i % G] = x;
         }
     }
     constexpr uint32_t kLost = 0x80000000u;                   // in passed[]
@@ -1191,7 +1211,8 @@ __global__ __launch_bounds__(kFilterThreads) void scan_filter_kernel(FilterArgs 
         uint32_t un = requested();
         request();
         fetch_ids(kShared, un, inext);
-        Word x[AHEAD ? 2 : 1][NI][V > 0 ? V : 1];
+        Word x[XS][NI][V > 0 ? V : 1];
+        static_assert(!AHEAD || D >= 3, "a unit's codes are here when its rows are asked for, a unit ahead");
         if constexpr (AHEAD) fetch_far(w[0], x[0]);
         while (unit[0] < units) {                             // (slot 0 holds the oldest; loads past the end are clamped and never count)
             look();
@@ -1200,8 +1221,7 @@ __global__ __launch_bounds__(kFilterThreads) void scan_filter_kernel(FilterArgs 
             bool some = false;
 #pragma unroll
             for (int i = 0; i < D; ++i) {
-                constexpr int kAt[2] = {0, AHEAD ? 1 : 0};
-                if constexpr (AHEAD) fetch_far(w[(i + 1) % D], x[kAt[(i + 1) & 1]]);
+                if constexpr (AHEAD) fetch_far(w[(i + 1) % D], x[(i + 1) % D % XS]);
                 else if constexpr (V > 0) fetch_far(w[i], x[0]);
                 const int into = (i + D - 1) % D;
                 unit[into] = un;
@@ -1211,7 +1231,7 @@ __global__ __launch_bounds__(kFilterThreads) void scan_filter_kernel(FilterArgs 
                 fetch_ids(kShared, un, inext);
                 in_group[i] = unit[i];
                 if (unit[i] < units) {
-                    some = scan_unit(unit[i], w[i], x[kAt[i & 1]], hits[i]) || some;
+                    some = scan_unit(unit[i], w[i], x[i % XS], hits[i]) || some;
                 } else {
 #pragma unroll
                     for (int e = 0; e < NI; ++e) hits[i][e] = 0;

@@ -560,7 +560,9 @@ SHARED_FLOORS = [("scan", 271_046, 1650, 4, 256, 10), ("scan", 137_321, 1650, 8,
                  ("scan", 97_743, 550, 16, 256, 40), ("scan", 220_001, 250, 16, 256, 270), ("scan", 97_742, 600, 32, 256, 10), ("scan", 97_742, 300, 64, 256, 10),
                  ("subset", 271_047, 1650, 4, 256, 10), ("subset", 137_321, 1650, 8, 256, 10), ("subset", 69_571, 700, 16, 256, 10),
                  ("subset", 97_743, 550, 16, 256, 50), ("scan16", 137_323, 1400, 4, 300, 10), ("scan16", 69_573, 1400, 8, 300, 10),
-                 ("scan16", 69_573, 700, 8, 1024, 10), ("scan16", 97_742, 550, 16, 300, 10), ("scan16", 69_570, 700, 16, 256, 10)]
+                 ("scan16", 69_573, 700, 8, 1024, 10), ("scan16", 97_742, 550, 16, 300, 10), ("scan16", 69_570, 700, 16, 256, 10),
+                 # (an eighth of the splits looked up in device memory; with K = 100 at m = 8, above, all of them in LDS)
+                 ("scan", 137_321, 1650, 8, 200, 5), ("scan", 220_001, 550, 16, 256, 3)]
 
 
 @pytest.mark.parametrize("tables", ["bell", "ties", "given_up"])
