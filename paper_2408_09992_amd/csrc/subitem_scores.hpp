@@ -240,19 +240,31 @@ __global__ __launch_bounds__(kSubMfmaThreads) void subitem_scores_mfma_kernel(co
     // slower: the extra registers cost more than the overlap gains; two or three workgroups per CU overlap instead.)
     for (int c = 0; c < s; c += CH) {
         if (c != 0) __syncthreads();                           // the previous chunk has been read
-        // sub-item embeddings j0 .. j0 + 63, elements c .. c + CH - 1 (rows past b repeat the last one)
+        // sub-item embeddings j0 .. j0 + 63, elements c .. c + CH - 1 (rows past b repeat the last one), and this wave's 32 query chunks: all asked for
+        // before the first store to LDS
+        constexpr int kPsi = 64 * C4 / kSubMfmaThreads, kPhi = 32 * C4 / kWave;
+        static_assert(64 * C4 % kSubMfmaThreads == 0 && 32 * C4 % kWave == 0, "whole pieces");
+        float4 x[kPsi], y[kPhi];
 #pragma unroll
-        for (int p = tid; p < 64 * C4; p += kSubMfmaThreads) {
-            const int row = p / C4, piece = p % C4, j = min(j0 + row, b - 1);
-            const float4 x = reinterpret_cast<const float4*>(centroids + ((size_t)k * b + j) * s + c)[piece];
-            *reinterpret_cast<float4*>(&psi[row * ROW + 4 * piece]) = x;
+        for (int i = 0; i < kPsi; ++i) {
+            const int p = tid + i * kSubMfmaThreads, row = p / C4, piece = p % C4, j = min(j0 + row, b - 1);
+            x[i] = reinterpret_cast<const float4*>(centroids + ((size_t)k * b + j) * s + c)[piece];
         }
-        // this wave's 32 query chunks
 #pragma unroll
-        for (int p = lane; active && p < 32 * C4; p += kWave) {
-            const int row = p / C4, piece = p % C4, q = min(q0 + row, B - 1);
-            const float4 x = reinterpret_cast<const float4*>(queries + (size_t)q * d + (size_t)k * s + c)[piece];
-            *reinterpret_cast<float4*>(&phi[wave][row * ROW + 4 * piece]) = x;
+        for (int i = 0; i < kPhi; ++i) {
+            const int p = lane + i * kWave, row = p / C4, piece = p % C4, q = min(q0 + row, B - 1);   // (a wave past the batch: its last query)
+            y[i] = reinterpret_cast<const float4*>(queries + (size_t)q * d + (size_t)k * s + c)[piece];
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < kPsi; ++i) {
+            const int p = tid + i * kSubMfmaThreads;
+            *reinterpret_cast<float4*>(&psi[p / C4 * ROW + 4 * (p % C4)]) = x[i];
+        }
+#pragma unroll
+        for (int i = 0; i < kPhi; ++i) {
+            const int p = lane + i * kWave;
+            *reinterpret_cast<float4*>(&phi[wave][p / C4 * ROW + 4 * (p % C4)]) = y[i];
         }
         __syncthreads();
         if (!active) continue;
