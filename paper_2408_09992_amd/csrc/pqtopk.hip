@@ -1399,7 +1399,7 @@ int enqueue_fold(const ScanPlan& p, int B, int K, void* workspace, int* out_ids,
 
 // Batch from which Eq. 4 runs on the matrix cores.  The scalar kernels are faster below: a wave's chain of d/m matrix
 // instructions takes as long for one tile of 32 queries as for a GPU full of them (measured at d = 512, m = 8, b = 256:
-// 5.8 us against 5.0 us at B = 256, 6.1 against 6.7 at B = 512, 6.7 against 10.8 at B = 1024, 21 against 35 at B = 4096).
+// 5.3 us at B = 448, the scalar kernels 5.2 at B = 400; 6.1 against 10.8 at B = 1024, 20 against 35 at B = 4096).
 constexpr int kSubMfmaMinBatch = 448;
 constexpr int kDefaultMfmaMinBatch = 3;    // default scoring: batch from which one matrix-core pass over W beats B mat-vec passes
 
