@@ -624,7 +624,9 @@ bool filter_fine_pays(long long N, int m, int K, int B, bool subset, int cw) {
 // through the L1 too, that an eighth of the lookups comes in its way.  Calls with an eighth through the L1 and with none (rounds of codes of a workgroup; us):
 // 330,000 items, 512 queries (20), K = 6 54.5 and 53.3; 400,000, 512 (24) 58.8 and 58.5; 180,000, 1000 (22) 63.8 and 62.7; 700,000, 512 (42), K = 20 90.0 and 91.9;
 // 1M, 512 (61), K = 45 122.7 and 126.2; 600,000, 700 (58), K = 5 100.5 and 105.5; 800,000, 1000 (98), K = 70 194.1 and 195.7; 1.28M, 1024 (156), K = 100 290 and 296.
-// (m = 16 has 16-bit counts beside the bytes where shares are short.)
+// m = 16, where such shares have 16-bit counts beside the bytes: many results of a query whose floors are not shared.  With and without, 800,000 items, 64
+// queries, K = 100 58.6 and 57.9, 300,000, 64, K = 20 30.9 and 30.5, 500,000, 60, K = 10 33.1 and 33.4, 5M, 16, K = 10 45.9 and 48.1; tables that let more pass
+// lose more (2M, 48, K = 100: heavy tails 145 and 131).
 bool filter_near_pays(long long rounds, int K) { return (double)rounds < 28.0 + 0.7 * K; }
 
 // Whether a batch is scanned by upper bounds (scan_filter.hpp), and how.
@@ -813,7 +815,7 @@ void plan_filter(ScanPlan& p, long long N, int B, int m, int K, bool subset, int
     p.f_lanes = lanes;
     p.f_stride = stride;
     p.f_far = filter_far_splits(m, words, w16, lanes, subset, cw);
-    p.f_near = p.f_far > 0 && m == 8 && lanes == 1 && p.f_share && filter_near_pays(rounds / nb, K);
+    p.f_near = p.f_far > 0 && lanes == 1 && (m == 8 ? p.f_share && filter_near_pays(rounds / nb, K) : m == 16 && !p.f_share && N < 30000LL * K);
     p.f_pitch = align16((size_t)(cw == 1 ? m : m - p.f_far) * stride * (w16 ? sizeof(uint16_t) : sizeof(uint8_t)));
     p.nblk = (int)nb;
     // Lists: what an item costs that passes is its row from another place in memory.  m = 8, floors shared, without 16-bit counts and with (us): 200,000 candidates, 500
@@ -1136,8 +1138,8 @@ hipError_t launch_filter(const ScanPlan& p, const FilterArgs& a, hipStream_t st)
         }
         return hipErrorInvalidValue;                         // (pq_measure_step_stamps() has checked)
     }
-    if constexpr (M == 8 && CW == 1 && !SUB) {
-        if (p.f_near) return go(scan_filter_kernel<8, 1, 4, false, false, 1, true, false, false, true>);
+    if constexpr ((M == 8 || M == 16) && CW == 1 && !SUB) {
+        if (p.f_near) return go(scan_filter_kernel<M, 1, 4, false, false, 1, M == 8, false, false, true>);
     }
     if constexpr (M == 16 && CW == 1 && !SUB) {
         if (p.f_fine) return p.f_share ? go(scan_filter_kernel<16, 1, 2, false, false, 1, true, false, true>) : go(scan_filter_kernel<16, 1, 2, false, false, 1, false, false, true>);
