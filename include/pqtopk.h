@@ -97,8 +97,8 @@ int pq_score_topk(const uint8_t* codes, const float* S, long long N, int B, int 
  * pq_score_topk() for callers that cannot allocate or pass device scratch: code under HIP graph capture, tight
  * serving loops, harnesses that forbid hipMalloc.  Same arguments (without the workspace), same kernels, same
  * result; the workgroups' partial top-K lists go to an array built into the library (PQ_STATIC_SCRATCH_BYTES = 8 MiB
- * of device memory per GPU the library runs on, held until the process ends) instead of a caller's workspace.  The
- * call allocates and frees nothing.
+ * of device memory, and a quarter as much again for table rows of large batches, per GPU the library runs on, held until the process ends)
+ * instead of a caller's workspace.  The call allocates and frees nothing.
  *   - A problem whose partial lists exceed PQ_STATIC_SCRATCH_BYTES, on a grid up to a quarter coarser than
  *     pq_score_topk() would take, is rejected with PQ_ERR_TOO_LARGE (nothing enqueued).  Where only a batch's tables of
  *     bounds do not fit, the batch is scanned without them.  Whatever pq_score_topk_workspace_bytes() puts at or below

@@ -114,11 +114,13 @@ int pq_measure_force_general(int mask);
 /*
  * How a call would be served: the scan kernel its shape (and the mask above) leads to, and how that is laid out.  Pure host
  * arithmetic.  kind: PQ_PLAN_BYTES for pq_score_topk(), PQ_PLAN_LIST for pq_score_topk_subset() (N: candidates), PQ_PLAN_WIDE for
- * pq_score_topk_u16().  `plan` (host) receives PQ_PLAN_FIELDS values.  Errors: PQ_ERR_NULL, PQ_ERR_SHAPE, PQ_ERR_UNSUPPORTED.
+ * pq_score_topk_u16(), PQ_PLAN_STATIC for pq_score_topk_static().  `plan` (host) receives PQ_PLAN_FIELDS values.  Errors: PQ_ERR_NULL,
+ * PQ_ERR_SHAPE, PQ_ERR_UNSUPPORTED, PQ_ERR_TOO_LARGE (PQ_PLAN_STATIC).
  */
 #define PQ_PLAN_BYTES  0
 #define PQ_PLAN_LIST   1
 #define PQ_PLAN_WIDE   2
+#define PQ_PLAN_STATIC 3
 #define PQ_PLAN_KERNEL      0   /* PQ_KERNEL_* */
 #define PQ_PLAN_GROUPS      1   /* workgroups that share a query */
 #define PQ_PLAN_QUERIES     2   /* queries of a workgroup */

@@ -455,7 +455,7 @@ def pq_measure_force_general(mask: int) -> int:
     return int(lib().pq_measure_force_general(int(mask)))
 
 
-PQ_PLAN_KINDS = {"scan": 0, "subset": 1, "scan16": 2}
+PQ_PLAN_KINDS = {"scan": 0, "subset": 1, "scan16": 2, "static": 3}
 PQ_PLAN_KERNELS = ("general", "batched", "short", "long", "short list", "bounds", "pairs", "list pairs")
 
 

@@ -43,8 +43,11 @@
 
 // Built-in scratch of pq_score_topk_static(): device memory, one copy per GPU, held until the process ends.  Host code
 // never uses this name as an address (it is a handle for hipGetSymbolAddress(), see static_scratch() below).
-constexpr size_t kStaticScratchBytes = PQ_STATIC_SCRATCH_BYTES;
-static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
+// Behind the bytes that decide what is taken there is room for the rows of counts that a batch's scan looks up in device memory: with these
+// among the 8 MiB, batches that otherwise fit were scanned without bounds (102,314 items, m = 8, 3141 queries, K = 2: 416 us instead of 97;
+// 699,551, 2485, K = 18 1427 and 321).  A query has at most 768 bytes of rows beside at least five times as many others.
+constexpr size_t kStaticScratchBytes = PQ_STATIC_SCRATCH_BYTES, kStaticRowsBytes = PQ_STATIC_SCRATCH_BYTES / 4;
+static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes + kStaticRowsBytes];
 
 namespace {
 
@@ -833,7 +836,7 @@ size_t keys_bytes(const ScanPlan& p, int B, int K) {
 }
 
 // workspace: [B][nblk][K] keys from the scan | filter scans, for the f_batch queries scanned together: tables of counts | FilterQuery
-// records | histograms | the rows that stay in device memory | 16-bit counts beside the bytes | the sample's best scores
+// records | histograms | 16-bit counts beside the bytes | the sample's best scores | the rows that stay in device memory
 size_t counts_bytes(const ScanPlan& p) { return p.filter ? ((size_t)p.f_batch * p.f_pitch + 255) & ~(size_t)255 : 0; }
 size_t far_bytes(const ScanPlan& p) {
     return p.filter ? ((size_t)((p.f_batch + p.f_queries - 1) / p.f_queries) * p.f_far * (size_t)p.f_stride * p.f_queries + 255) & ~(size_t)255 : 0;
@@ -841,9 +844,12 @@ size_t far_bytes(const ScanPlan& p) {
 size_t query_bytes(const ScanPlan& p) { return p.filter ? ((size_t)p.f_batch * sizeof(FilterQuery) + 255) & ~(size_t)255 : 0; }
 size_t hist_bytes(const ScanPlan& p) { return p.filter ? (size_t)p.f_batch * kFilterBins * sizeof(uint32_t) : 0; }
 size_t fine_bytes(const ScanPlan& p) { return p.filter && p.f_fine ? (size_t)p.f_batch * p.f_entries * sizeof(uint16_t) : 0; }
+size_t best_bytes(const ScanPlan& p) { return p.filter && p.f_parts > 1 ? ((size_t)p.f_batch * p.f_parts * p.f_best * sizeof(float) + 255) & ~(size_t)255 : 0; }
 size_t workspace_bytes(const ScanPlan& p, int B, int K) {
-    return keys_bytes(p, B, K) + counts_bytes(p) + query_bytes(p) + hist_bytes(p) + far_bytes(p) + fine_bytes(p) +
-           (p.filter && p.f_parts > 1 ? ((size_t)p.f_batch * p.f_parts * p.f_best * sizeof(float) + 255) & ~(size_t)255 : 0);
+    return keys_bytes(p, B, K) + counts_bytes(p) + query_bytes(p) + hist_bytes(p) + fine_bytes(p) + best_bytes(p) + far_bytes(p);
+}
+bool fits_static_scratch(const ScanPlan& p, int B, int K) {
+    return workspace_bytes(p, B, K) - far_bytes(p) <= kStaticScratchBytes && far_bytes(p) <= kStaticRowsBytes;   // (the rows come last)
 }
 
 // Lists that do not fit `bytes`: up to a quarter fewer item blocks per query, where the kernel takes any grid.  (The scan gets longer
@@ -855,6 +861,17 @@ void coarsen_to_fit(ScanPlan& p, int B, int K, size_t bytes) {
         p.nblk = (int)most;
         p.direct = p.nblk == 1;
     }
+}
+
+// pq_score_topk_static()'s plan: what does not fit its scratch is left out, first pairs of queries or bounds, then item blocks.
+ScanPlan make_static_plan(long long N, int B, int m, int K) {
+    ScanPlan p = make_plan(N, B, m, K);
+    for (int without = 0; (p.pair_scan || p.filter) && !fits_static_scratch(p, B, K);) {
+        without |= p.pair_scan ? kNoPair : kNoFilter;
+        p = make_plan(N, B, m, K, false, 1, kLutStride, without);
+    }
+    coarsen_to_fit(p, B, K, kStaticScratchBytes);
+    return p;
 }
 
 int check_topk_shape(long long N, int B, int m, int b, int K, int cw) {
@@ -1234,12 +1251,12 @@ int enqueue_scan(const ScanPlan& p, const uint8_t* codes, const float* S, long l
         f.entries = p.f_entries;
         f.hist = reinterpret_cast<uint32_t*>(ws + counts_bytes(p) + query_bytes(p));
         f.pitch = (uint32_t)p.f_pitch;
-        f.far = ws + counts_bytes(p) + query_bytes(p) + hist_bytes(p);
+        f.far = ws + counts_bytes(p) + query_bytes(p) + hist_bytes(p) + fine_bytes(p) + best_bytes(p);
         f.far_splits = p.f_far;
         f.tile = p.f_queries;
         f.wide = p.f_w16;
-        f.fine = p.f_fine ? reinterpret_cast<uint16_t*>(ws + counts_bytes(p) + query_bytes(p) + hist_bytes(p) + far_bytes(p)) : nullptr;
-        f.best = reinterpret_cast<float*>(ws + counts_bytes(p) + query_bytes(p) + hist_bytes(p) + far_bytes(p) + fine_bytes(p));
+        f.fine = p.f_fine ? reinterpret_cast<uint16_t*>(ws + counts_bytes(p) + query_bytes(p) + hist_bytes(p)) : nullptr;
+        f.best = reinterpret_cast<float*>(ws + counts_bytes(p) + query_bytes(p) + hist_bytes(p) + fine_bytes(p));
         f.sample = p.f_sample;
         f.rounds = p.f_rounds;
         f.parts = p.f_parts;
@@ -1526,16 +1543,11 @@ int pq_score_topk_static(const uint8_t* codes, const float* S, long long N, int 
     if (!codes || !S || !out_ids || !out_scores) return PQ_ERR_NULL;
     int rc = check_topk_shape(N, B, m, b, K, 1);
     if (rc != PQ_OK) return rc;
-    ScanPlan p = make_plan(N, B, m, K);
-    for (int without = 0; (p.pair_scan || p.filter) && workspace_bytes(p, B, K) > kStaticScratchBytes;) {
-        without |= p.pair_scan ? kNoPair : kNoFilter;
-        p = make_plan(N, B, m, K, false, 1, kLutStride, without);
-    }
-    coarsen_to_fit(p, B, K, kStaticScratchBytes);
+    const ScanPlan p = make_static_plan(N, B, m, K);
     if (p.scan_lds > kMaxLdsBytes || p.fold_lds > kMaxLdsBytes) return PQ_ERR_UNSUPPORTED;
     if (((uintptr_t)codes & 15) || ((uintptr_t)S & 3) || ((uintptr_t)out_ids & 3) || ((uintptr_t)out_scores & 3))
         return PQ_ERR_ALIGN;
-    if (workspace_bytes(p, B, K) > kStaticScratchBytes) return PQ_ERR_TOO_LARGE;
+    if (!fits_static_scratch(p, B, K)) return PQ_ERR_TOO_LARGE;
     void* ws = nullptr;
     rc = static_scratch(&ws);
     if (rc != PQ_OK) return rc;
@@ -1594,12 +1606,14 @@ int pq_measure_force_general(int mask) {
 
 int pq_measure_plan(long long N, int B, int m, int b, int K, int kind, int* plan) {
     if (!plan) return PQ_ERR_NULL;
-    if (kind < PQ_PLAN_BYTES || kind > PQ_PLAN_WIDE) return PQ_ERR_SHAPE;
+    if (kind < PQ_PLAN_BYTES || kind > PQ_PLAN_STATIC) return PQ_ERR_SHAPE;
     const int cw = kind == PQ_PLAN_WIDE ? 2 : 1;
     const int rc = check_topk_shape(N, B, m, b, K, cw);
     if (rc != PQ_OK) return rc;
-    const ScanPlan p = kind == PQ_PLAN_LIST ? make_plan(N, B, m, K, true) : kind == PQ_PLAN_WIDE ? make_plan(N, B, m, K, false, 2, b) : make_plan(N, B, m, K);
+    const ScanPlan p = kind == PQ_PLAN_LIST ? make_plan(N, B, m, K, true) : kind == PQ_PLAN_WIDE ? make_plan(N, B, m, K, false, 2, b)
+                       : kind == PQ_PLAN_STATIC ? make_static_plan(N, B, m, K) : make_plan(N, B, m, K);
     if (p.scan_lds > kMaxLdsBytes || p.fold_lds > kMaxLdsBytes) return PQ_ERR_UNSUPPORTED;
+    if (kind == PQ_PLAN_STATIC && !fits_static_scratch(p, B, K)) return PQ_ERR_TOO_LARGE;
     for (int i = 0; i < PQ_PLAN_FIELDS; ++i) plan[i] = 0;
     plan[PQ_PLAN_KERNEL] = p.filter ? PQ_KERNEL_BOUNDS : p.pair_scan ? PQ_KERNEL_PAIRS : p.tiled ? PQ_KERNEL_BATCHED : p.short_scan ? PQ_KERNEL_SHORT : p.long_scan ? PQ_KERNEL_LONG
                            : p.short_subset ? PQ_KERNEL_SHORT_LIST : p.subset_pair ? PQ_KERNEL_LIST_PAIRS : PQ_KERNEL_GENERAL;

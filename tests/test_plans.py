@@ -134,3 +134,17 @@ def test_queries_of_one_word_share_floors_where_that_pays(plan, kind, N, B, m, b
     # m = 64, 170 queries of 140,000 items, K = 120: 292 us without shared floors, 208 with; m = 4, b = 6000, 129 of 700,000, K = 4 59 and 75
     p = plan(kind, N, B, m, b, K)
     assert p["kernel"] == "bounds" and p["shared"] == shared
+
+
+@pytest.mark.parametrize("N,B,m,K", [(26_060, 3018, 8, 1), (102_314, 3141, 8, 2), (699_551, 2485, 8, 18), (3_670_000, 2800, 8, 1), (2_200_000, 2083, 8, 8), (298_538, 1563, 16, 2),
+                                     (401_145, 1691, 16, 4), (85_607, 884, 32, 1), (868_457, 828, 32, 6), (300_000, 800, 8, 100)])
+def test_static_scratch_holds_a_large_batchs_tables(plan, N, B, m, K):
+    # without bounds 102,314 items, m = 8, 3141 queries, K = 2 take 416 us, with them 97
+    assert plan("static", N, B, m, 256, K) == plan("scan", N, B, m, 256, K)
+    assert plan("static", N, B, m, 256, K)["kernel"] == "bounds"
+
+
+@pytest.mark.parametrize("N,B,m,K,instead", [(150_000, 8000, 8, 2, "pairs"), (400_000, 300, 64, 10, "pairs"), (1_000_000, 3000, 16, 100, "batched")])
+def test_static_scratch_leaves_out_bounds_that_do_not_fit(plan, N, B, m, K, instead):
+    assert plan("scan", N, B, m, 256, K)["kernel"] == "bounds"
+    assert plan("static", N, B, m, 256, K)["kernel"] == instead

@@ -85,3 +85,19 @@ def test_static_scratch_without_pairs_of_queries(pq, N, B, m, K):
     ids, sc = torch.empty_like(ref_ids), torch.empty_like(ref_sc)
     pq.pq_score_topk_static(G, S, K, ids, sc)
     assert torch.equal(ids, ref_ids) and torch.equal(sc.view(torch.int32), ref_sc.view(torch.int32))
+
+
+@pytest.mark.parametrize("N,B,m,K", [(26_060, 3018, 8, 1), (102_314, 3141, 8, 2), (341_385, 1908, 8, 101), (699_551, 2485, 8, 18), (298_538, 1563, 16, 2), (85_607, 884, 32, 1)])
+def test_static_scratch_with_a_large_batchs_rows_behind_it(pq, N, B, m, K):
+    # more than 8 MiB with the rows of counts that stay in device memory; by single lanes, by pairs of lanes, m = 32
+    import torch
+    from paper_2408_09992_amd import workloads as W
+    assert pq.pq_measure_plan("static", N, B, m, 256, K)["kernel"] == "bounds"
+    assert pq.pq_score_topk_workspace_bytes(N, B, m, 256, K) > pq.PQ_STATIC_SCRATCH_BYTES
+    G = W.codes_uniform_device(N, m, 256, 3)
+    S = torch.randn((B, m, 256), device="cuda", generator=torch.Generator(device="cuda").manual_seed(3))
+    ref_ids, ref_sc = pq.pq_score_topk(G, S, K)
+    ids, sc = torch.empty_like(ref_ids), torch.empty_like(ref_sc)
+    for _ in range(2):
+        pq.pq_score_topk_static(G, S, K, ids.fill_(-7), sc.fill_(0.0))
+        assert torch.equal(ids, ref_ids) and torch.equal(sc.view(torch.int32), ref_sc.view(torch.int32))
