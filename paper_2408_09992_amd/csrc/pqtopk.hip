@@ -552,9 +552,21 @@ constexpr size_t kFilterTableBytes = 64u << 20;
 
 // LDS reads a CU returns per clock when every lane reads at random: of 4-, 8- and 16-byte words.
 constexpr double kGather4 = 8.7, kGather8 = 8.5, kGather16 = 5.0;
-// ... and of 16-byte words with an eighth of the splits read from device memory, and by pairs of lanes that read a row of 32 bytes together,
-// a quarter of the splits from device memory.
+// ... and of 16-byte words with an eighth of the splits read from device memory (5 reads from LDS for seven splits of eight: 5.7; with its fixed costs a whole
+// call at m = 8, 50M items, 40 queries, comes to 5.4, at m = 16, 16M, to 5.1), and by pairs of lanes that read a row of 32 bytes together,
+// a quarter of the splits from device memory (7.0 and 6.1).  33 to 48 queries of long scans are two tiles of pairs or three of single lanes
+// (us): m = 8, K = 10, 10M 97.9 and 90.4, 50M 372 and 363; m = 16, 2.2M 69.5 and 58.2, 16M 272 and 246.
 constexpr double kGather16Far = 5.7, kGatherPairs = 7.4;
+
+// Eight queries to a workgroup instead of sixteen single lanes at m = 8 and 16, an eighth of whose splits comes from device memory: the reads alone
+// speak for sixteen, but a workgroup of eight has half to look after and to select for, which is 1 to 3 us of a call and decides where the last of the
+// sixteens is hardly half full: 17 to 24 queries, and 33 to 40 over shorter scans.  Calls with sixteen and eight (us): m = 8, 20 queries, 700,000 items, K = 10 22.4 and
+// 20.0, 1.3M 24.9 and 23.0, K = 128 36.6 and 34.2, 5M, K = 10 42.5 and 39.1, 7.5M, K = 200 77.9 and 73.9, 20M 145 and 158; 36 queries, 700,000 24.2 and 22.3, 1.3M 28.9 and 27.2, 3.5M 44.5
+// and 43.1, K = 40 50.5 and 50.6, 5.2M 64.6 and 67.0, K = 200 87.9 and 99.8; m = 16, 20 queries, 600,000, K = 10 26.2 and 24.5, 3.7M 57.6 and 52.9, 10M, K = 40 122 and 115;
+// 36, 250,000, K = 10 24.3 and 22.1, 2.6M, K = 50 71.8 and 71.2, 3.7M, K = 40 91.9 and 90.5, 5.8M, K = 200 (all splits in LDS) 167 and 178.  Long scans for more than 128 results fill
+// their lists, sixteen's most: 36, K = 200, m = 8, 14M 179 and 190, 20M 268 and 234, 50M 509 and 483; m = 16, 9M 285 and 229, 20M 464 and 436.
+// In costs as below, three eights for two sixteens are 1.01 of these, five for three 1.12, seven for four 1.17.
+double half_tiles_within(long long N, int m, int K) { return N <= 4000000 || (K > 128 && N * m >= 130000000) ? 1.15 : 1.02; }
 
 // Whether the workgroups of a query, `each` queries to one, share its floors: few of them, `least` rounds of codes each (see shares() below).
 bool few_share(long long N, int B, int row, int each, int least) {
@@ -707,7 +719,8 @@ void plan_filter(ScanPlan& p, long long N, int B, int m, int K, bool subset, int
         const long long tiles = (B + w * fields - 1) / (w * fields);
         const double r = l == 2 ? kGatherPairs : each == 4 ? (filter_far_splits(m, 4, w16, 1, subset, cw) > 0 ? kGather16Far : kGather16) : each == 2 ? kGather8 : kGather4;
         const double cost = (double)tiles * l / r;
-        if (words == 0 || cost < best_cost) { words = each; lanes = l; cap = c; best_cost = cost; rate = r; }
+        const double within = each == 2 && words == 4 && lanes == 1 && m <= 16 && filter_far_splits(m, 4, w16, 1, subset, cw) > 0 ? half_tiles_within(N, m, K) : 1.0;
+        if (words == 0 || cost < best_cost * within) { words = each; lanes = l; cap = c; best_cost = cost; rate = r; }
         if (l == 2 && (force & 128)) break;
     }
     if (words == 0) return;

@@ -148,3 +148,14 @@ def test_static_scratch_holds_a_large_batchs_tables(plan, N, B, m, K):
 def test_static_scratch_leaves_out_bounds_that_do_not_fit(plan, N, B, m, K, instead):
     assert plan("scan", N, B, m, 256, K)["kernel"] == "bounds"
     assert plan("static", N, B, m, 256, K)["kernel"] == instead
+
+
+@pytest.mark.parametrize("N,B,m,K,queries", [
+    (700_000, 17, 8, 10, 8), (5_000_000, 24, 8, 100, 8), (2_600_000, 20, 16, 128, 8), (10_000_000, 20, 16, 40, 8), (997_951, 17, 16, 128, 8), (443_030, 22, 16, 213, 8),
+    (700_000, 33, 8, 10, 8), (3_500_000, 36, 8, 10, 8), (2_600_000, 33, 16, 102, 8), (3_000_000, 40, 16, 10, 8), (20_000_000, 36, 8, 200, 8), (9_000_000, 36, 16, 200, 8),
+    (5_200_000, 36, 8, 200, 16), (9_000_000, 36, 8, 70, 16), (50_000_000, 40, 8, 10, 16), (10_000_000, 48, 8, 30, 16), (16_000_000, 33, 16, 10, 16),
+    (1_300_000, 16, 8, 10, 16), (1_300_000, 25, 8, 10, 16), (1_300_000, 41, 8, 10, 16), (1_280_000, 64, 8, 10, 16)])
+def test_eight_queries_per_workgroup_where_sixteen_leave_the_last_half_empty(plan, N, B, m, K, queries):
+    # m = 8, 20 queries of 700,000 items, K = 10: 22.4 us by sixteens, 20.0 by eights; 36 queries of 5.2M, K = 200 88 and 100; 33 to 48 of long scans by pairs of lanes 98, by sixteens 90
+    p = plan("scan", N, B, m, 256, K)
+    assert (p["kernel"], p["queries"]) == ("bounds", queries)
