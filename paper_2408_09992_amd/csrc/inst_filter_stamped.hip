@@ -3,4 +3,5 @@
 #include "kernels.hpp"
 namespace pqk {
 PQ_FILTER_INSTANCES_STAMPED(PQ_FILTER_DEFINE8)
+PQ_FILTER_INSTANCES_NEAR_STAMPED(PQ_FILTER_DEFINE10)
 }

@@ -133,6 +133,7 @@ namespace pqk {
 #define PQ_FILTER_INSTANCES_STAMPED(X) PQ_FILTER_STAMPED(X, 8, 1) PQ_FILTER_STAMPED(X, 8, 2) PQ_FILTER_STAMPED(X, 16, 1)
 // all splits in LDS: short shares that share their floors (m = 8), many results (m = 16)
 #define PQ_FILTER_INSTANCES_NEAR(X) X(8, 1, 4, false, false, 1, true, false, false, true) X(16, 1, 4, false, false, 1, false, false, false, true)
+#define PQ_FILTER_INSTANCES_NEAR_STAMPED(X) X(8, 1, 4, false, false, 1, true, true, false, true) X(16, 1, 4, false, false, 1, false, true, false, true)
 // ... and those with 16-bit counts beside the bytes
 #define PQ_FILTER_INSTANCES_FINE(X) X(16, 1, 2, false, false, 1, false, false, true) X(16, 1, 2, false, false, 1, true, false, true) X(8, 1, 4, false, true, 1, true, false, true)
 // the batched kernel
@@ -192,6 +193,7 @@ PQ_TILED_INSTANCES(PQ_TILED_EXTERN)
 PQ_FILTER_INSTANCES_STAMPED(PQ_FILTER_EXTERN8)
 PQ_FILTER_INSTANCES_FINE(PQ_FILTER_EXTERN9)
 PQ_FILTER_INSTANCES_NEAR(PQ_FILTER_EXTERN10)
+PQ_FILTER_INSTANCES_NEAR_STAMPED(PQ_FILTER_EXTERN10)
 PQ_FILTER_INSTANCES_A(PQ_FILTER_EXTERN, PQ_FILTERP_EXTERN)
 PQ_FILTER_INSTANCES_A8(PQ_FILTER_EXTERN, PQ_FILTERP_EXTERN)
 PQ_FILTER_INSTANCES_B(PQ_FILTER_EXTERN, PQ_FILTERP_EXTERN)

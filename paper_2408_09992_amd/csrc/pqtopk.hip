@@ -1159,6 +1159,7 @@ hipError_t launch_filter(const ScanPlan& p, const FilterArgs& a, hipStream_t st)
     };
     if (a.stamps != nullptr) {
         if constexpr ((M == 8 || M == 16) && CW == 1 && !SUB) {
+            if (p.f_near) return go(scan_filter_kernel<M, 1, 4, false, false, 1, M == 8, true, false, true>);
             if (p.f_words == 4 && p.f_lanes == 1 && !p.f_w16)
                 return p.f_share ? go(scan_filter_kernel<M, 1, 4, false, false, 1, true, true>) : go(scan_filter_kernel<M, 1, 4, false, false, 1, false, true>);
         }

@@ -612,6 +612,29 @@ def _large_batch_case(pq, oracle, kind, N, B, m, b, K, tables, mask=0):
     assert np.array_equal(ids[::9], rid) and np.array_equal(sc[::9].view(np.uint32), rsc.view(np.uint32))
 
 
+# The measurement call runs the instance that the plain call runs: plans that look all splits up in LDS leave the rows of counts, which come last in
+# the workspace, alone, others write them.  N, B, m, K, splits looked up in device memory
+@pytest.mark.parametrize("N,B,m,K,far", [(180_003, 1000, 8, 6, 0), (200_001, 64, 16, 20, 0), (300_001, 64, 8, 10, 1), (500_001, 48, 16, 3, 2)])
+def test_step_stamps_of_the_instance_that_runs(pq, N, B, m, K, far):
+    import torch
+    gen = torch.Generator(device="cuda").manual_seed(N)
+    codes = torch.randint(0, 256, (N, m), device="cuda", generator=gen, dtype=torch.uint8)
+    Q = torch.randn((B, 8 * m), device="cuda", generator=gen)
+    cent = torch.randn((m, 256, 8), device="cuda", generator=gen)
+    S = pq.pq_subitem_scores(Q, cent)
+    want_ids, want_sc = pq.pq_score_topk(codes, S, K)
+    plan = pq.pq_measure_plan("scan", N, B, m, 256, K)
+    assert (plan["kernel"], plan["queries"]) == ("bounds", 16)
+    size, rows = pq.pq_score_topk_workspace_bytes(N, B, m, 256, K), -(-B // 16) * 16 * 256 * (m // 8)
+    ws = torch.full((size,), 0xA5, dtype=torch.uint8, device="cuda")
+    ids, sc = torch.empty_like(want_ids), torch.empty_like(want_sc)
+    stamps = torch.zeros((3, pq.PQ_STAMP_RECORDS, pq.PQ_STAMP_SLOTS), dtype=torch.int64, device="cuda")
+    groups, waves = pq.pq_measure_step_stamps(Q, cent, codes, K, S, ids, sc, ws, stamps)
+    assert torch.equal(ids, want_ids) and torch.equal(sc.view(torch.int32), want_sc.view(torch.int32))
+    assert groups == plan["groups"] * -(-B // 16) and bool((stamps[1, :groups * waves, 0] > 0).all())
+    assert bool((ws[size - rows:] == 0xA5).all()) == (far == 0)
+
+
 # Every instance of the scan by bounds that batches reach beyond those above: how many queries a workgroup takes, the width of the fields, whether
 # workgroups share floors.  The mask keeps a shape on pairs of lanes (16 | 128), or on bounds (16).  kind, N, B, m, b, K, mask, queries, field bits, shared
 MORE_INSTANCES = [("scan", 116_559, 700, 4, 256, 150, 0, 8, 8, 1), ("scan", 102_643, 1639, 4, 256, 17, 144, 32, 8, 1), ("scan", 89_267, 530, 8, 256, 100, 0, 8, 8, 1),
