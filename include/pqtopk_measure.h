@@ -129,7 +129,8 @@ int pq_measure_force_general(int mask);
 #define PQ_PLAN_SHARED      5   /* ... a query's workgroups share their floors */
 #define PQ_PLAN_PARTS       6   /* ... parts of the sample ... */
 #define PQ_PLAN_ROUNDS      7   /* ... and the rounds of each */
-#define PQ_PLAN_FIELDS      8
+#define PQ_PLAN_FAR         8   /* ... splits looked up in device memory, beside those in LDS */
+#define PQ_PLAN_FIELDS      9
 #define PQ_KERNEL_GENERAL     0
 #define PQ_KERNEL_BATCHED     1
 #define PQ_KERNEL_SHORT       2

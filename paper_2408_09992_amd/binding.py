@@ -83,7 +83,7 @@ def lib() -> ctypes.CDLL:
         L.pq_measure_sync_variant.restype = I
         L.pq_measure_force_general.argtypes = [I]
         L.pq_measure_force_general.restype = I
-        L.pq_measure_plan.argtypes = [LL, I, I, I, I, I, ctypes.POINTER(I * 8)]
+        L.pq_measure_plan.argtypes = [LL, I, I, I, I, I, ctypes.POINTER(I * len(PQ_PLAN_NAMES))]
         L.pq_measure_plan.restype = I
         L.pq_measure_step_stamps.argtypes = [P, P, P, LL, I, I, I, I, I, P, P, P, P, SZ, P, SZ, ctypes.POINTER(I * 2), P]
         L.pq_measure_step_stamps.restype = I
@@ -456,17 +456,17 @@ def pq_measure_force_general(mask: int) -> int:
 
 
 PQ_PLAN_KINDS = {"scan": 0, "subset": 1, "scan16": 2, "static": 3}
+PQ_PLAN_NAMES = ("kernel", "groups", "queries", "field_bits", "fine", "shared", "parts", "rounds", "far")
 PQ_PLAN_KERNELS = ("general", "batched", "short", "long", "short list", "bounds", "pairs", "list pairs")
 
 
 def pq_measure_plan(kind: str, N: int, B: int, m: int, b: int, K: int) -> dict:
     """How a call of that shape is served (no GPU needed): the scan kernel and its layout, see pqtopk_measure.h."""
-    plan = (ctypes.c_int * 8)()
+    plan = (ctypes.c_int * len(PQ_PLAN_NAMES))()
     rc = lib().pq_measure_plan(N, B, m, b, K, PQ_PLAN_KINDS[kind], ctypes.byref(plan))
     if rc != PQ_OK:
         raise PQError(rc, "pq_measure_plan")
-    return dict(zip(("kernel", "groups", "queries", "field_bits", "fine", "shared", "parts", "rounds"),
-                    (PQ_PLAN_KERNELS[plan[0]], *plan[1:])))
+    return dict(zip(PQ_PLAN_NAMES, (PQ_PLAN_KERNELS[plan[0]], *plan[1:])))
 
 
 PQ_STAMP_SLOTS, PQ_STAMP_RECORDS = 16, 8192

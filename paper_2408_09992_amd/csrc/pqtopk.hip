@@ -116,7 +116,7 @@ struct ScanPlan {
     int f_cap;         // ... keys of a query's list
     int f_lanes;       // ... lanes that share an item (1 or 2)
     size_t f_pitch;    // ... bytes of a query's counts that go to LDS
-    int f_far;         // ... splits whose counts stay in device memory
+    int f_far;         // ... splits whose counts stay in device memory (f_near: none)
     int f_stride;      // ... table entries of a split
     bool f_share;      // ... the workgroups of a query share their floors
     bool f_patient;    // ... which rise so far that the sample gives no query up
@@ -832,6 +832,7 @@ void plan_filter(ScanPlan& p, long long N, int B, int m, int K, bool subset, int
     p.f_stride = stride;
     p.f_far = filter_far_splits(m, words, w16, lanes, subset, cw);
     p.f_near = p.f_far > 0 && lanes == 1 && (m == 8 ? p.f_share && filter_near_pays(rounds / nb, K) : m == 16 && !p.f_share && N < 30000LL * K);
+    if (p.f_near) p.f_far = 0;
     p.f_pitch = align16((size_t)(cw == 1 ? m : m - p.f_far) * stride * (w16 ? sizeof(uint16_t) : sizeof(uint8_t)));
     p.nblk = (int)nb;
     // Lists: what an item costs that passes is its row from another place in memory.  m = 8, floors shared, without 16-bit counts and with (us): 200,000 candidates, 500
@@ -1639,6 +1640,7 @@ int pq_measure_plan(long long N, int B, int m, int b, int K, int kind, int* plan
         plan[PQ_PLAN_SHARED] = p.f_share;
         plan[PQ_PLAN_PARTS] = p.f_parts;
         plan[PQ_PLAN_ROUNDS] = p.f_rounds;
+        plan[PQ_PLAN_FAR] = p.f_far;
     }
     return PQ_OK;
 }

@@ -374,6 +374,15 @@ def _bounds_case(pq, oracle, codes, S, K, subset=None, mask=16):
     assert np.array_equal(sc.cpu().numpy().view(np.uint32), rsc.view(np.uint32))
 
 
+def _planned(pq, N, B, m, K, mask=16, **fields):
+    prev = pq.pq_measure_force_general(mask)
+    try:
+        plan = pq.pq_measure_plan("scan", N, B, m, 256, K)
+    finally:
+        pq.pq_measure_force_general(prev)
+    assert plan["kernel"] == "bounds" and {k: plan[k] for k in fields} == fields
+
+
 @pytest.mark.parametrize("m", [4, 8, 16, 32, 64])
 @pytest.mark.parametrize("N,B,K,b", [(1_027, 1, 1, 256), (20_001, 2, 10, 256), (70_003, 5, 33, 7), (50_002, 17, 100, 256),
                                      (150_001, 16, 10, 200), (9_000, 3, 512, 256), (400_001, 4, 128, 256)])
@@ -518,25 +527,32 @@ def _odd_tables(kind, S):
                                   "high_and_masked", "heavy_tails", "far_offset"])
 def test_scan_by_upper_bounds_of_tables_that_are_not_bell_shaped(pq, oracle, kind):
     rng = np.random.default_rng(11)
-    for m, N, B, K in ((4, 30_003, 7, 10), (8, 60_001, 18, 100), (8, 400_001, 6, 10), (16, 90_001, 5, 10), (16, 50_000, 9, 40), (32, 150_001, 3, 10), (32, 60_001, 18, 3), (64, 40_001, 5, 3)):
+    for m, N, B, K in ((4, 30_003, 7, 10), (8, 60_001, 18, 100), (8, 400_001, 6, 10), (16, 90_001, 5, 10), (16, 50_000, 9, 40), (32, 150_001, 3, 10), (32, 60_001, 18, 3), (64, 40_001, 5, 3),
+                       (8, 60_001, 16, 10), (16, 60_001, 16, 1)):
         print(f"case {kind} m={m} N={N} B={B} K={K}", flush=True)
         codes = rng.integers(0, 256, (N, m), dtype=np.uint8)
         S = _odd_tables(kind, rng.standard_normal((B, m, 256), dtype=np.float32))
         _bounds_case(pq, oracle, codes, S, K)
-        if m == 8:
+        if B == 16:                                            # (an eighth of the splits in device memory, floors not shared)
+            _planned(pq, N, B, m, K, queries=16, shared=0, far=m // 8)
+        elif m == 8:
             _bounds_case(pq, oracle, codes, S, K, subset=rng.permutation(N)[: N // 2].astype(np.int32))
             wide = rng.integers(0, 700, (N, m), dtype=np.uint16)
             _bounds_case(pq, oracle, wide, _odd_tables(kind, rng.standard_normal((B, m, 700), dtype=np.float32)), K)
 
 
 @pytest.mark.parametrize("kind", ["rare_high", "denormal", "equal_rows", "mixed"])
-@pytest.mark.parametrize("m,K", [(4, 10), (8, 1), (8, 100), (8, 300), (16, 10), (16, 40), (32, 3), (32, 10), (64, 5)])
+@pytest.mark.parametrize("m,K", [(4, 10), (8, 1), (8, 100), (8, 300), (16, 1), (16, 10), (16, 40), (32, 3), (32, 10), (64, 5)])
 def test_queries_that_the_bounds_are_no_use_for(pq, oracle, m, K, kind):
     # a large entry that five items have, sums that hardly differ, a catalogue of seven rows: such queries are scanned a second
     # time, exactly; "mixed" has them beside ordinary ones in a tile (more of them than one pass takes)
-    # (m = 32: with three results in bytes, whose tables leave four splits in device memory, with ten in 16 bits)
+    # (m = 32: with three results in bytes, whose tables leave four splits in device memory, with ten in 16 bits; m = 8 and 16 with sixteen queries to
+    # a workgroup: an eighth of the splits there, but all in LDS for many results at m = 16)
     rng = np.random.default_rng(m + K)
     N, B = 60_003, 13
+    far = {(8, 1): 1, (8, 100): 1, (16, 1): 2, (16, 10): 0, (16, 40): 0, (32, 3): 4}
+    if (m, K) in far:
+        _planned(pq, N, B, m, K, queries=16, shared=0, far=far[m, K])
     codes = rng.integers(0, 256, (N, m), dtype=np.uint8)
     S = rng.standard_normal((B, m, 256), dtype=np.float32)
     which = slice(None) if kind != "mixed" else [0, 2, 3, 5, 8, 9, 12]
@@ -561,14 +577,16 @@ SHARED_FLOORS = [("scan", 271_046, 1650, 4, 256, 10), ("scan", 137_321, 1650, 8,
                  ("subset", 271_047, 1650, 4, 256, 10), ("subset", 137_321, 1650, 8, 256, 10), ("subset", 69_571, 700, 16, 256, 10),
                  ("subset", 97_743, 550, 16, 256, 50), ("scan16", 137_323, 1400, 4, 300, 10), ("scan16", 69_573, 1400, 8, 300, 10),
                  ("scan16", 69_573, 700, 8, 1024, 10), ("scan16", 97_742, 550, 16, 300, 10), ("scan16", 69_570, 700, 16, 256, 10),
-                 # (an eighth of the splits looked up in device memory; with K = 100 at m = 8, above, all of them in LDS)
                  ("scan", 137_321, 1650, 8, 200, 5), ("scan", 220_001, 550, 16, 256, 3)]
+# ... an eighth of the splits looked up in device memory, or all of them in LDS
+SPLITS_IN_DEVICE_MEMORY = {("scan", 137_321, 1650, 8, 200, 5): 1, ("scan", 220_001, 550, 16, 256, 3): 2, ("scan", 137_321, 1650, 8, 256, 100): 0}
 
 
 @pytest.mark.parametrize("tables", ["bell", "ties", "given_up"])
 @pytest.mark.parametrize("kind,N,B,m,b,K", SHARED_FLOORS)
 def test_floors_shared_between_workgroups(pq, oracle, kind, N, B, m, b, K, tables):
-    assert pq.pq_measure_plan(kind, N, B, m, b, K)["shared"] == 1
+    plan = pq.pq_measure_plan(kind, N, B, m, b, K)
+    assert plan["shared"] == 1 and plan["far"] == SPLITS_IN_DEVICE_MEMORY.get((kind, N, B, m, b, K), 0)
     _large_batch_case(pq, oracle, kind, N, B, m, b, K, tables)
 
 
@@ -612,8 +630,8 @@ def _large_batch_case(pq, oracle, kind, N, B, m, b, K, tables, mask=0):
     assert np.array_equal(ids[::9], rid) and np.array_equal(sc[::9].view(np.uint32), rsc.view(np.uint32))
 
 
-# The measurement call runs the instance that the plain call runs: plans that look all splits up in LDS leave the rows of counts, which come last in
-# the workspace, alone, others write them.  N, B, m, K, splits looked up in device memory
+# The measurement call runs the instance that the plain call runs: plans that look all splits up in LDS have no rows of counts in the workspace and
+# touch nothing behind it, others write these rows, which come last.  N, B, m, K, splits looked up in device memory
 @pytest.mark.parametrize("N,B,m,K,far", [(180_003, 1000, 8, 6, 0), (200_001, 64, 16, 20, 0), (300_001, 64, 8, 10, 1), (500_001, 48, 16, 3, 2)])
 def test_step_stamps_of_the_instance_that_runs(pq, N, B, m, K, far):
     import torch
@@ -624,15 +642,16 @@ def test_step_stamps_of_the_instance_that_runs(pq, N, B, m, K, far):
     S = pq.pq_subitem_scores(Q, cent)
     want_ids, want_sc = pq.pq_score_topk(codes, S, K)
     plan = pq.pq_measure_plan("scan", N, B, m, 256, K)
-    assert (plan["kernel"], plan["queries"]) == ("bounds", 16)
+    assert (plan["kernel"], plan["queries"], plan["far"]) == ("bounds", 16, far)
     size, rows = pq.pq_score_topk_workspace_bytes(N, B, m, 256, K), -(-B // 16) * 16 * 256 * (m // 8)
-    ws = torch.full((size,), 0xA5, dtype=torch.uint8, device="cuda")
+    end = size if far else size + rows
+    ws = torch.full((size + rows,), 0xA5, dtype=torch.uint8, device="cuda")
     ids, sc = torch.empty_like(want_ids), torch.empty_like(want_sc)
     stamps = torch.zeros((3, pq.PQ_STAMP_RECORDS, pq.PQ_STAMP_SLOTS), dtype=torch.int64, device="cuda")
-    groups, waves = pq.pq_measure_step_stamps(Q, cent, codes, K, S, ids, sc, ws, stamps)
+    groups, waves = pq.pq_measure_step_stamps(Q, cent, codes, K, S, ids, sc, ws[:size], stamps)
     assert torch.equal(ids, want_ids) and torch.equal(sc.view(torch.int32), want_sc.view(torch.int32))
     assert groups == plan["groups"] * -(-B // 16) and bool((stamps[1, :groups * waves, 0] > 0).all())
-    assert bool((ws[size - rows:] == 0xA5).all()) == (far == 0)
+    assert bool((ws[end - rows:end] == 0xA5).all()) == (far == 0)
 
 
 # Every instance of the scan by bounds that batches reach beyond those above: how many queries a workgroup takes, the width of the fields, whether

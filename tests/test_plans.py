@@ -159,3 +159,17 @@ def test_eight_queries_per_workgroup_where_sixteen_leave_the_last_half_empty(pla
     # m = 8, 20 queries of 700,000 items, K = 10: 22.4 us by sixteens, 20.0 by eights; 36 queries of 5.2M, K = 200 88 and 100; 33 to 48 of long scans by pairs of lanes 98, by sixteens 90
     p = plan("scan", N, B, m, 256, K)
     assert (p["kernel"], p["queries"]) == ("bounds", queries)
+
+
+@pytest.mark.parametrize("N,B,m,K,far", [
+    (1_280_000, 64, 8, 10, 1), (1_280_000, 1024, 8, 100, 1), (180_003, 1000, 8, 6, 0), (137_321, 1650, 8, 100, 0), (5_000_000, 16, 16, 10, 2), (300_000, 64, 16, 20, 0),
+    (400_000, 600, 32, 4, 4), (50_000_000, 32, 8, 10, 2), (20_000_000, 32, 16, 10, 3), (1_280_000, 64, 4, 10, 0), (1_000_000, 8, 64, 10, 0)])
+def test_splits_in_device_memory_and_the_room_for_their_rows(plan, N, B, m, K, far):
+    # m = 8, 400,000 items, 512 queries, K = 6: 58.8 us with an eighth of the splits in device memory, 58.5 without; 64 of 1.28M, K = 10 32.0 and 32.6
+    from paper_2408_09992_amd import binding
+    p = plan("scan", N, B, m, 256, K)
+    assert (p["kernel"], p["far"]) == ("bounds", far)
+    tables = binding.pq_score_topk_workspace_bytes(N, B, m, 256, K) - 8 * K * B * p["groups"]
+    a_query = 256 * m * (2 if p["field_bits"] == 16 else 1) + 512 + 16 + 256 * far
+    others = 4 * p["parts"] * (K + 4) if p["parts"] > 1 else 0
+    assert B * a_query <= tables <= -(-B // p["queries"]) * p["queries"] * (a_query + others) + 5 * 256

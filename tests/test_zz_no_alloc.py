@@ -87,7 +87,7 @@ def test_static_scratch_without_pairs_of_queries(pq, N, B, m, K):
     assert torch.equal(ids, ref_ids) and torch.equal(sc.view(torch.int32), ref_sc.view(torch.int32))
 
 
-@pytest.mark.parametrize("N,B,m,K", [(26_060, 3018, 8, 1), (102_314, 3141, 8, 2), (341_385, 1908, 8, 101), (699_551, 2485, 8, 18), (298_538, 1563, 16, 2), (85_607, 884, 32, 1)])
+@pytest.mark.parametrize("N,B,m,K", [(26_060, 3018, 8, 1), (102_314, 3141, 8, 2), (400_000, 1943, 8, 93), (699_551, 2485, 8, 18), (298_538, 1563, 16, 2), (85_607, 884, 32, 1)])
 def test_static_scratch_with_a_large_batchs_rows_behind_it(pq, N, B, m, K):
     # more than 8 MiB with the rows of counts that stay in device memory; by single lanes, by pairs of lanes, m = 32
     import torch
