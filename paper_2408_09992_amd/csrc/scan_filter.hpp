@@ -113,8 +113,8 @@ __host__ __device__ constexpr int filter_far_splits(int m, int words, bool w16, 
     return m == 32 ? 4 : subset || cw == 2 || m == 4 ? 0 : m / 8;
 }
 // Splits that the tables in LDS have room for: single lanes of short rows keep room for all, which a second scan with exact tables uses.
-__host__ __device__ constexpr int filter_table_splits(int m, int words, bool w16, int lanes, bool subset = false, int cw = 1) {
-    return lanes == 1 && m <= 16 ? m : m - filter_far_splits(m, words, w16, lanes, subset, cw);
+__host__ __device__ constexpr int filter_table_splits(int m, int words, bool w16, int lanes) {
+    return lanes == 1 && m <= 16 ? m : m - filter_far_splits(m, words, w16, lanes);
 }
 
 // Byte of a tile's rows in device memory ([splits][stride][queries]) where the part from query `first` on of sub-id `id`'s row begins, in the
@@ -610,6 +610,7 @@ __global__ __launch_bounds__(kFilterThreads) void scan_filter_kernel(FilterArgs 
     constexpr int PER = kWave / G;                            // items a wave looks up side by side
     constexpr int V = NEAR ? 0 : filter_far_splits(M, W, W16, G, SUB, CW);   // splits looked up in device memory, the last ones
     constexpr int T = filter_table_splits(M, W, W16, G);      // ... that the tables in LDS have room for
+    static_assert(T >= M - V, "room for the splits looked up in LDS");
     constexpr int NA = W16 ? 1 : filter_sums(M);              // sums of a field
     constexpr int QW = (QT + NW - 1) / NW;                    // queries that a wave looks after
     constexpr int EW = T * G >= M ? W : W / 2;          // queries of a second scan: exact tables in the counts' place

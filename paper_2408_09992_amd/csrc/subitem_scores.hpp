@@ -93,7 +93,6 @@ __global__ __launch_bounds__(kSubThreads) void subitem_scores_kernel(const float
 constexpr int kSubBatchWaves = 4;
 constexpr int kSubBatchThreads = kSubBatchWaves * kWave;
 constexpr int kSubInterleave = 4;                                     // I where there are queries enough
-constexpr int kSubBatchTile = kSubBatchWaves * kSubInterleave;        // queries per workgroup then
 
 template <int S_ELEMS, int I>   // d/m, a multiple of 4; rows of queries and centroids 16-byte aligned
 __global__ __launch_bounds__(kSubBatchThreads) void subitem_scores_batched_kernel(
