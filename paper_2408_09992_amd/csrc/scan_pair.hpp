@@ -55,40 +55,42 @@ __device__ __forceinline__ void pair_scores(const float2* lut, int stride, uint3
 }
 
 // The tables of queries q0 and q0 + 1 (`two`; else q0 once more) to LDS, interleaved: two entries of each at a time when size and address
-// allow.  `then`: more loads to ask for.  One-byte sub-ids: behind the first of the tables', since loads return in order and codes come from
-// further away (45,000 items, m = 8, 200 queries 16.7 us before, now 16.4; lists: 20,000 candidates, m = 16, 100 queries 16.0 and 15.2).  Two-byte
-// sub-ids, whose tables take several batches: before them (no faster the other way, 100,000 items, b = 500, 40 queries 12.4 us and 12.9).
-template <int M, int CW, int NT, typename Then>
+// allow.  `then`: more loads, asked for behind the tables' (FIRST) or by the caller before.  Behind tables that one batch of loads brings (one-byte sub-ids,
+// m <= 16), since loads return in order and codes come from further away (45,000 items, m = 8, 200 queries 16.7 us before, now 16.4; lists: 20,000
+// candidates, m = 16, 100 queries 16.0 and 15.2).  Before tables of several batches, which would wait for the codes between them (m = 64, 2109 items, 328
+// queries 13.2 us and, behind the first, 13.8, 7490, 710 62.3 and 63.8; two bytes, 100,000 items, b = 500, 40 queries 12.4 and 12.9).
+__host__ __device__ constexpr bool pair_tables_first(int m, int cw, int threads) { return cw == 1 && m * kLutStride / 2 <= 4 * threads; }
+template <int M, int CW, int NT, bool FIRST, typename Then>
 __device__ __forceinline__ void pair_tables(float2* lut, const float* S, int q0, bool two, int b, int tid, Then&& then) {
     const float* S0 = S + (size_t)q0 * M * b;
     const float* S1 = two ? S0 + (size_t)M * b : S0;
     const int total = M * b;
-    if constexpr (CW == 2) then();
+    static_assert(!FIRST || M * kLutStride / 2 >= NT, "every thread has a part of the one batch");
     if ((CW == 2 || b == kLutStride) && (total & 1) == 0 && ((uintptr_t)S & 7) == 0) {
         constexpr int kBatch = CW == 2 || M * kLutStride / 2 > 4 * NT ? 4 : (M * kLutStride / 2 + NT - 1) / NT;   // (requested together, before the first store)
         const float2* src0 = reinterpret_cast<const float2*>(S0);
         const float2* src1 = reinterpret_cast<const float2*>(S1);
         const int pieces = total >> 1;
-        auto batch = [&](int e0, auto&& between) {
+        for (int e0 = tid; FIRST || e0 < pieces; e0 += kBatch * NT) {
             float2 x[kBatch], y[kBatch];
 #pragma unroll
             for (int i = 0; i < kBatch; ++i) { const int e = min(e0 + i * NT, pieces - 1); x[i] = src0[e]; y[i] = src1[e]; }
             __builtin_amdgcn_sched_barrier(0);
-            between();
-            __builtin_amdgcn_sched_barrier(0);
+            if constexpr (FIRST) {
+                then();
+                __builtin_amdgcn_sched_barrier(0);
+            }
 #pragma unroll
             for (int i = 0; i < kBatch; ++i)
                 if (e0 + i * NT < pieces) reinterpret_cast<float4*>(lut)[e0 + i * NT] = make_float4(x[i].x, y[i].x, x[i].y, y[i].y);
-        };
-        auto nothing = []() {};
-        if constexpr (CW == 1) batch(tid, then);
-        for (int e0 = CW == 1 ? tid + kBatch * NT : tid; e0 < pieces; e0 += kBatch * NT) batch(e0, nothing);
+            if constexpr (FIRST) break;                       // (one batch, and every thread asks for its codes)
+        }
     } else if constexpr (CW == 2) {
 #pragma unroll 4
         for (int e = tid; e < total; e += NT) lut[e] = make_float2(S0[e], S1[e]);
     } else {
         // fewer than 256 sub-ids per split, or an odd address: element by element, rows padded with zeros
-        then();
+        if constexpr (FIRST) then();
 #pragma unroll 4
         for (int e = tid; e < M * kLutStride; e += NT) {
             const int k = e / kLutStride, j = e % kLutStride;
@@ -105,8 +107,11 @@ __device__ __forceinline__ void pair_tables(float2* lut, const float* S, int q0,
 // (14.9 and 16.0 us below).  Steps without Eq. 4, one query per workgroup and two (us): two-byte sub-ids, m = 8, b = 1024, 1.28M items,
 // four queries, K = 10: 17.3 and 14.9; m = 8, 65,603 items, 97 queries: 20.5 and 14.6; m = 16, 300,000, 12, K = 48: 20.0 and 16.6; m = 32,
 // 500,000, 8, K = 10: 29.5 and 21.5; m = 64, 30,000, 300: 141 and 81; m = 64, 51,826, 129, K = 20: 113 and 77.
+// (waves per SIMD: seven units of m = 4 need 129 registers when left to themselves, with 128 a compute unit holds two workgroups: 28,058 items, 496
+// queries 20.2 and 15.8 us)
+__host__ __device__ constexpr int pair_waves(int m, int u, int cw) { return m == 4 && cw == 1 && u == 7 ? 4 : 1; }
 template <int M, int U, int NT, int CW = 1>
-__global__ __launch_bounds__(NT, 1) void scan_pair_kernel(const uint8_t* codes, const float* S, void* out, float* out_scores, uint32_t N, int b, int B, int K) {
+__global__ __launch_bounds__(NT, pair_waves(M, U, CW)) void scan_pair_kernel(const uint8_t* codes, const float* S, void* out, float* out_scores, uint32_t N, int b, int B, int K) {
     ScanArgs a;                                               // (plain arguments: see scan_short_kernel)
     a.codes = codes; a.S = S; a.N = N; a.m = M; a.b = b; a.K = K;
     a.ws_keys = static_cast<uint64_t*>(out); a.out_ids = out_scores != nullptr ? static_cast<int*>(out) : nullptr;
@@ -142,10 +147,16 @@ __global__ __launch_bounds__(NT, 1) void scan_pair_kernel(const uint8_t* codes, 
             to[0] = x.x; to[1] = x.y; to[2] = x.z; to[3] = x.w;
         }
     };
-    pair_tables<M, CW, NT>(lut, a.S, q0, two, b, tid, [&]() {
+    if constexpr (pair_tables_first(M, CW, NT)) {
+        pair_tables<M, CW, NT, true>(lut, a.S, q0, two, b, tid, [&]() {
+#pragma unroll
+            for (int u = 0; u < kRing; ++u) fetch(u);
+        });
+    } else {
 #pragma unroll
         for (int u = 0; u < kRing; ++u) fetch(u);
-    });
+        pair_tables<M, CW, NT, false>(lut, a.S, q0, two, b, tid, []() {});
+    }
     auto& select = *reinterpret_cast<MidSelectLds<NT>(*)[2]>(sel);
     mid_select_clear<NT>(select[0], tid);
     mid_select_clear<NT>(select[1], tid);

@@ -118,6 +118,9 @@ __host__ __device__ constexpr bool subset_pair_has(int m, int u) { return u <= s
 // Candidate lists for several queries: as scan_subset_kernel, two queries per workgroup (grid.y = (B + 1) / 2), their tables' entries side
 // by side in LDS as in scan_pair_kernel.  What bounds a list is the gathering of its rows, about one per clock and CU, and then the
 // lookups: both are done once for two queries here.
+// Rows are asked for behind the tables (see pair_tables()) but where a thread holds sixteen vectors: at m = 16 tables and rows together then take 132
+// registers, and a compute unit has room for one workgroup instead of two (13,498 candidates, 899 queries 67.2 us, rows first 45.5; m = 8, 26,148, 491, K = 152 77.3
+// and 74.3).
 template <int M, int U, int NT>
 __global__ __launch_bounds__(NT, 1) void scan_subset_pair_kernel(const uint8_t* codes, const int* subset, const float* S, void* out, float* out_scores,
                                                                  uint32_t N, uint32_t n_items, int b, int B, int K) {
@@ -143,13 +146,16 @@ __global__ __launch_bounds__(NT, 1) void scan_subset_pair_kernel(const uint8_t* 
         const uint32_t pos = first + (uint32_t)s * stride;
         item[s] = (uint32_t)a.subset[pos < n ? pos : n - 1];  // (past the end: a re-read, never scored)
     }
-    pair_tables<M, 1, NT>(lut, a.S, q0, two, b, tid, [&]() {
+    auto fetch_rows = [&]() {
 #pragma unroll
         for (int s = 0; s < R; ++s) {
             item[s] = item[s] < a.n_items ? item[s] : a.n_items - 1;
             load_row_words<M>(a.codes, item[s], &w[s / IPV][s % IPV * (M / 4)]);
         }
-    });
+    };
+    constexpr bool kTablesFirst = U != 16;
+    if constexpr (!kTablesFirst) fetch_rows();
+    pair_tables<M, 1, NT, kTablesFirst>(lut, a.S, q0, two, b, tid, fetch_rows);
     mid_select_clear<NT>(select[0], tid);
     mid_select_clear<NT>(select[1], tid);
     __syncthreads();
