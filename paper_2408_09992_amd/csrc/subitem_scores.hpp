@@ -84,7 +84,7 @@ __global__ __launch_bounds__(kSubThreads) void subitem_scores_kernel(const float
 // Eq. 4 for batches.  A workgroup of four waves serves 64 sub-ids of ONE split and up to 4 * I queries, I of them per wave, whose
 // chains run side by side (independent chains hide the latency of each chain's dependent multiply-adds).  Per query the
 // arithmetic is the same left-to-right chain from +0 as above.
-// What bounds it is latency: one round trip to memory, then 64 multiply-adds per chain.  So everything is asked for at
+// What bounds it is latency: one round trip to memory, then d/m multiply-adds per chain.  So everything is asked for at
 // once, in whole cache lines, before the first store to LDS waits for any of it: the 64 sub-item embeddings (consecutive memory) and
 // the queries' chunks; a lane's row is read from LDS (rows padded by 16 bytes: conflict-free), a query's chunk by all lanes at once.
 // Read straight from memory, row by row, every load of a lane's row touched 64 cache lines, and the queries' chunks came four
@@ -109,23 +109,33 @@ __global__ __launch_bounds__(kSubBatchThreads) void subitem_scores_batched_kerne
     const int nq = B - q0 < TILE ? B - q0 : TILE;
     const float4* psi4 = reinterpret_cast<const float4*>(centroids + ((size_t)k * b + j0) * S_ELEMS);
     const int live_rows = b - j0 < kSubThreads ? b - j0 : kSubThreads;
-    float4 r[kRows], c[kPhi];
+    if constexpr (S_ELEMS < 128 || I < 4) {
+        float4 r[kRows], c[kPhi];
 #pragma unroll
-    for (int i = 0; i < kRows; ++i) r[i] = psi4[min(tid + i * NT, live_rows * PPR - 1)];   // (past the end: a repeat, not stored)
+        for (int i = 0; i < kRows; ++i) r[i] = psi4[min(tid + i * NT, live_rows * PPR - 1)];   // (past the end: a repeat, not stored)
 #pragma unroll
-    for (int i = 0; i < kPhi; ++i) {
-        const int p = min(tid + i * NT, nq * PPR - 1);
-        c[i] = *reinterpret_cast<const float4*>(queries + (size_t)(q0 + p / PPR) * d + (size_t)k * S_ELEMS + 4 * (p % PPR));
+        for (int i = 0; i < kPhi; ++i) {
+            const int p = min(tid + i * NT, nq * PPR - 1);
+            c[i] = *reinterpret_cast<const float4*>(queries + (size_t)(q0 + p / PPR) * d + (size_t)k * S_ELEMS + 4 * (p % PPR));
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < kRows; ++i) {
+            const int p = tid + i * NT;
+            if (p < live_rows * PPR) *reinterpret_cast<float4*>(&rows[(p / PPR) * kRow + 4 * (p % PPR)]) = r[i];
+        }
+#pragma unroll
+        for (int i = 0; i < kPhi; ++i)
+            if (tid + i * NT < nq * PPR) *reinterpret_cast<float4*>(&phi[4 * (tid + i * NT)]) = c[i];
+    } else {
+        // (128 elements, four chains to a wave: the rows are eight loads a thread, and two or three workgroups to a compute unit hide one's second round trip behind
+        // another's work.  64 queries, m = 4, b = 4000: 9.2 us this way, 10.6 the other; 200 queries, b = 1024 8.5 and 9.3)
+#pragma unroll 4
+        for (int p = tid; p < nq * PPR; p += NT)
+            *reinterpret_cast<float4*>(&phi[4 * p]) = *reinterpret_cast<const float4*>(queries + (size_t)(q0 + p / PPR) * d + (size_t)k * S_ELEMS + 4 * (p % PPR));
+#pragma unroll 8
+        for (int p = tid; p < live_rows * PPR; p += NT) *reinterpret_cast<float4*>(&rows[(p / PPR) * kRow + 4 * (p % PPR)]) = psi4[p];
     }
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int i = 0; i < kRows; ++i) {
-        const int p = tid + i * NT;
-        if (p < live_rows * PPR) *reinterpret_cast<float4*>(&rows[(p / PPR) * kRow + 4 * (p % PPR)]) = r[i];
-    }
-#pragma unroll
-    for (int i = 0; i < kPhi; ++i)
-        if (tid + i * NT < nq * PPR) *reinterpret_cast<float4*>(&phi[4 * (tid + i * NT)]) = c[i];
     __syncthreads();
     const int first = wave * I;
     if (first >= nq || lane >= live_rows) return;
@@ -233,7 +243,7 @@ __global__ __launch_bounds__(kSubMfmaThreads) void subitem_scores_mfma_kernel(co
     const int jtiles = (b + 63) / 64;
     const int k = blockIdx.x / jtiles, j0 = (blockIdx.x % jtiles) * 64;
     const int q0 = blockIdx.y * kSubMfmaQueries + wave * 32;
-    const bool active = q0 < B;                                // (a wave past the batch only helps staging the embeddings)
+    const bool active = q0 < B;                                // (a wave past the batch only helps staging)
     floatx32 acc;
 #pragma unroll
     for (int v = 0; v < 32; ++v) acc[v] = 0.0f;
@@ -241,31 +251,46 @@ __global__ __launch_bounds__(kSubMfmaThreads) void subitem_scores_mfma_kernel(co
     // slower: the extra registers cost more than the overlap gains; two or three workgroups per CU overlap instead.)
     for (int c = 0; c < s; c += CH) {
         if (c != 0) __syncthreads();                           // the previous chunk has been read
-        // sub-item embeddings j0 .. j0 + 63, elements c .. c + CH - 1 (rows past b repeat the last one), and this wave's 32 query chunks: all asked for
-        // before the first store to LDS
+        // sub-item embeddings j0 .. j0 + 63, elements c .. c + CH - 1, and this wave's 32 query chunks: all asked for before the first store to LDS.  (Chunks of
+        // 16 elements are three loads, and the results' stores bound the kernel: one after the other, 3000 queries, m = 8, b = 4000 85.5 us and 92)
         constexpr int kPsi = 64 * C4 / kSubMfmaThreads, kPhi = 32 * C4 / kWave;
         static_assert(64 * C4 % kSubMfmaThreads == 0 && 32 * C4 % kWave == 0, "whole pieces");
-        float4 x[kPsi], y[kPhi];
+        if constexpr (CH > 16) {
+            float4 x[kPsi], y[kPhi];
 #pragma unroll
-        for (int i = 0; i < kPsi; ++i) {
-            const int p = tid + i * kSubMfmaThreads, row = p / C4, piece = p % C4, j = min(j0 + row, b - 1);
-            x[i] = reinterpret_cast<const float4*>(centroids + ((size_t)k * b + j) * s + c)[piece];
-        }
+            for (int i = 0; i < kPsi; ++i) {
+                const int p = tid + i * kSubMfmaThreads, row = p / C4, piece = p % C4, j = min(j0 + row, b - 1);   // (rows past b repeat the last one)
+                x[i] = reinterpret_cast<const float4*>(centroids + ((size_t)k * b + j) * s + c)[piece];
+            }
 #pragma unroll
-        for (int i = 0; i < kPhi; ++i) {
-            const int p = lane + i * kWave, row = p / C4, piece = p % C4, q = min(q0 + row, B - 1);   // (a wave past the batch: its last query)
-            y[i] = reinterpret_cast<const float4*>(queries + (size_t)q * d + (size_t)k * s + c)[piece];
-        }
-        __builtin_amdgcn_sched_barrier(0);
+            for (int i = 0; i < kPhi; ++i) {
+                const int p = lane + i * kWave, row = p / C4, piece = p % C4, q = min(q0 + row, B - 1);   // (a wave past the batch: its last query's, which nobody reads)
+                y[i] = reinterpret_cast<const float4*>(queries + (size_t)q * d + (size_t)k * s + c)[piece];
+            }
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int i = 0; i < kPsi; ++i) {
-            const int p = tid + i * kSubMfmaThreads;
-            *reinterpret_cast<float4*>(&psi[p / C4 * ROW + 4 * (p % C4)]) = x[i];
-        }
+            for (int i = 0; i < kPsi; ++i) {
+                const int p = tid + i * kSubMfmaThreads;
+                *reinterpret_cast<float4*>(&psi[p / C4 * ROW + 4 * (p % C4)]) = x[i];
+            }
 #pragma unroll
-        for (int i = 0; i < kPhi; ++i) {
-            const int p = lane + i * kWave;
-            *reinterpret_cast<float4*>(&phi[wave][p / C4 * ROW + 4 * (p % C4)]) = y[i];
+            for (int i = 0; i < kPhi; ++i) {
+                const int p = lane + i * kWave;
+                *reinterpret_cast<float4*>(&phi[wave][p / C4 * ROW + 4 * (p % C4)]) = y[i];
+            }
+        } else {
+#pragma unroll
+            for (int p = tid; p < 64 * C4; p += kSubMfmaThreads) {
+                const int row = p / C4, piece = p % C4, j = min(j0 + row, b - 1);
+                const float4 x = reinterpret_cast<const float4*>(centroids + ((size_t)k * b + j) * s + c)[piece];
+                *reinterpret_cast<float4*>(&psi[row * ROW + 4 * piece]) = x;
+            }
+#pragma unroll
+            for (int p = lane; active && p < 32 * C4; p += kWave) {
+                const int row = p / C4, piece = p % C4, q = min(q0 + row, B - 1);
+                const float4 x = reinterpret_cast<const float4*>(queries + (size_t)q * d + (size_t)k * s + c)[piece];
+                *reinterpret_cast<float4*>(&phi[wave][row * ROW + 4 * piece]) = x;
+            }
         }
         __syncthreads();
         if (!active) continue;

@@ -59,10 +59,12 @@ def test_subitem_scores_bit_exact(pq, oracle, B, d, m, b):
 
 
 # one, two and four chains to a wave: batches at the edges of a workgroup's queries, where a workgroup per compute unit ends (32 and 33
-# queries, 64 and 65), ragged blocks of sub-ids, every row length with an instance
+# queries, 64 and 65), ragged blocks of sub-ids, every row length with an instance; rows of 128 elements and four chains to a wave, and the matrix cores' chunks of 16
+# elements, are staged in an order of their own
 @pytest.mark.gpu
 @pytest.mark.parametrize("B,d,m,b", [(3, 64, 4, 256), (4, 512, 8, 257), (5, 512, 8, 1000), (8, 128, 32, 255), (9, 512, 64, 1), (31, 512, 16, 256),
-                                     (32, 512, 8, 256), (33, 512, 8, 256), (64, 512, 8, 256), (65, 512, 8, 256), (67, 512, 4, 65), (127, 256, 8, 300)])
+                                     (32, 512, 8, 256), (33, 512, 8, 256), (64, 512, 8, 256), (65, 512, 8, 256), (67, 512, 4, 65), (127, 256, 8, 300),
+                                     (37, 512, 4, 1001), (447, 512, 4, 300), (449, 512, 32, 99)])
 def test_subitem_scores_of_small_batches(pq, oracle, B, d, m, b):
     print(f"case subitem small batch B={B} d={d} m={m} b={b}", flush=True)
     rng = np.random.default_rng(B * 1000 + m)
