@@ -639,10 +639,13 @@ bool filter_fine_pays(long long N, int m, int K, int B, bool subset, int cw) {
 // through the L1 too, that an eighth of the lookups comes in its way.  Calls with an eighth through the L1 and with none (rounds of codes of a workgroup; us):
 // 330,000 items, 512 queries (20), K = 6 54.5 and 53.3; 400,000, 512 (24) 58.8 and 58.5; 180,000, 1000 (22) 63.8 and 62.7; 700,000, 512 (42), K = 20 90.0 and 91.9;
 // 1M, 512 (61), K = 45 122.7 and 126.2; 600,000, 700 (58), K = 5 100.5 and 105.5; 800,000, 1000 (98), K = 70 194.1 and 195.7; 1.28M, 1024 (156), K = 100 290 and 296.
-// m = 16, where such shares have 16-bit counts beside the bytes: many results of a query whose floors are not shared.  With and without, 800,000 items, 64
-// queries, K = 100 58.6 and 57.9, 300,000, 64, K = 20 30.9 and 30.5, 500,000, 60, K = 10 33.1 and 33.4, 5M, 16, K = 10 45.9 and 48.1; tables that let more pass
-// lose more (2M, 48, K = 100: heavy tails 145 and 131).
 bool filter_near_pays(long long rounds, int K) { return (double)rounds < 28.0 + 0.7 * K; }
+// m = 16, where such shares have 16-bit counts beside the bytes: many results of a query whose floors are not shared, for the items that there are or for its
+// workgroups `nb`, each of which looks for as many.  With an eighth through the L1 and with none (us), 800,000 items, 64 queries, K = 100 58.6 and 57.9, 300,000, 64, K = 20 30.9
+// and 30.5, 500,000, 60, K = 10 33.1 and 33.4, 5M, 16, K = 10 45.9 and 48.1; tables that let more pass lose more (2M, 48, K = 100: heavy tails 145 and 131).
+// Long shares, as a ratio, 5M, 12M and 20M items: 256 workgroups K = 130 0.99 0.96 0.97, K = 256 1.01 0.98 1.04; 128 K = 130 0.97 0.96 1.00, K = 200 1.02 1.01 1.06; 85 K = 100
+// 1.01 1.00 1.01, K = 130 1.04 1.03 1.04, K = 200 1.08 1.10 1.09; 64 K = 100 1.00 0.97 0.97, K = 130 1.04 1.00 1.00, K = 200 1.07 1.06 1.04; 51 K = 64 1.00 0.98 0.96, K = 100 1.08 1.03 1.00.
+bool filter_near_pays16(long long N, int K, long long nb) { return N < 30000LL * K || (K >= (nb <= 56 ? 90 : 125) && 5LL * K >= 7 * nb); }
 
 // Whether a batch is scanned by upper bounds (scan_filter.hpp), and how.
 size_t workspace_bytes(const ScanPlan& p, int B, int K);
@@ -831,7 +834,7 @@ void plan_filter(ScanPlan& p, long long N, int B, int m, int K, bool subset, int
     p.f_lanes = lanes;
     p.f_stride = stride;
     p.f_far = filter_far_splits(m, words, w16, lanes, subset, cw);
-    p.f_near = p.f_far > 0 && lanes == 1 && (m == 8 ? p.f_share && filter_near_pays(rounds / nb, K) : m == 16 && !p.f_share && N < 30000LL * K);
+    p.f_near = p.f_far > 0 && lanes == 1 && (m == 8 ? p.f_share && filter_near_pays(rounds / nb, K) : m == 16 && !p.f_share && filter_near_pays16(N, K, nb));
     if (p.f_near) p.f_far = 0;
     p.f_pitch = align16((size_t)(cw == 1 ? m : m - p.f_far) * stride * (w16 ? sizeof(uint16_t) : sizeof(uint8_t)));
     p.nblk = (int)nb;
