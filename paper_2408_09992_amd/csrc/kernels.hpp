@@ -131,9 +131,9 @@ namespace pqk {
 // measurement instances (wall-clock stamps per wave) of those the named batch workloads run
 #define PQ_FILTER_STAMPED(X, M, G) X(M, 1, 4, false, false, G, false, true) X(M, 1, 4, false, false, G, true, true)
 #define PQ_FILTER_INSTANCES_STAMPED(X) PQ_FILTER_STAMPED(X, 8, 1) PQ_FILTER_STAMPED(X, 8, 2) PQ_FILTER_STAMPED(X, 16, 1)
-// all splits in LDS: short shares that share their floors (m = 8), many results (m = 16)
-#define PQ_FILTER_INSTANCES_NEAR(X) X(8, 1, 4, false, false, 1, true, false, false, true) X(16, 1, 4, false, false, 1, false, false, false, true)
-#define PQ_FILTER_INSTANCES_NEAR_STAMPED(X) X(8, 1, 4, false, false, 1, true, true, false, true) X(16, 1, 4, false, false, 1, false, true, false, true)
+// all splits in LDS: short shares (m = 8), many results (m = 16)
+#define PQ_FILTER_INSTANCES_NEAR(X) X(8, 1, 4, false, false, 1, false, false, false, true) X(8, 1, 4, false, false, 1, true, false, false, true) X(16, 1, 4, false, false, 1, false, false, false, true)
+#define PQ_FILTER_INSTANCES_NEAR_STAMPED(X) X(8, 1, 4, false, false, 1, false, true, false, true) X(8, 1, 4, false, false, 1, true, true, false, true) X(16, 1, 4, false, false, 1, false, true, false, true)
 // ... and those with 16-bit counts beside the bytes
 #define PQ_FILTER_INSTANCES_FINE(X) X(16, 1, 2, false, false, 1, false, false, true) X(16, 1, 2, false, false, 1, true, false, true) X(8, 1, 4, false, true, 1, true, false, true)
 // the batched kernel

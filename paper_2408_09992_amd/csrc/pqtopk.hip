@@ -635,11 +635,14 @@ bool filter_fine_pays(long long N, int m, int K, int B, bool subset, int cw) {
     return N >= 100000 && B >= (K <= 32 ? 130 : 81);
 }
 
-// Where single lanes whose floors are shared look all splits up in LDS (m = 8): over short shares with many results, which score so much exactly,
+// Where single lanes look all splits up in LDS.  m = 8, floors shared: over short shares with many results, which score so much exactly,
 // through the L1 too, that an eighth of the lookups comes in its way.  Calls with an eighth through the L1 and with none (rounds of codes of a workgroup; us):
 // 330,000 items, 512 queries (20), K = 6 54.5 and 53.3; 400,000, 512 (24) 58.8 and 58.5; 180,000, 1000 (22) 63.8 and 62.7; 700,000, 512 (42), K = 20 90.0 and 91.9;
 // 1M, 512 (61), K = 45 122.7 and 126.2; 600,000, 700 (58), K = 5 100.5 and 105.5; 800,000, 1000 (98), K = 70 194.1 and 195.7; 1.28M, 1024 (156), K = 100 290 and 296.
-bool filter_near_pays(long long rounds, int K) { return (double)rounds < 28.0 + 0.7 * K; }
+// Floors that are not shared: from 512 queries on (whose shares are short then, and whose samples are by half a workgroup) from 16 results on.  80,000 items, 512 queries, K = 10
+// 32.8 and 33.0, K = 16 35.2 and 34.4, K = 30 42.3 and 39.9, K = 100 73.6 and 67.9; 60,000, 2500, K = 30 109.5 and 104.0; 130,000, 4000, K = 100 318.9 and 308.6.  (100,000 items, 400
+// queries, K = 100 57.3 and 57.4; 120 queries 28.2 and 29.7.)
+bool filter_near_pays(long long rounds, int K, int queries, bool shared) { return (shared || (queries >= 2 * kAssumedCUs && K >= 16)) && (double)rounds < 28.0 + 0.7 * K; }
 // m = 16, where such shares have 16-bit counts beside the bytes: many results of a query whose floors are not shared, for the items that there are or for its
 // workgroups `nb`, each of which looks for as many.  With an eighth through the L1 and with none (us), 800,000 items, 64 queries, K = 100 58.6 and 57.9, 300,000, 64, K = 20 30.9
 // and 30.5, 500,000, 60, K = 10 33.1 and 33.4, 5M, 16, K = 10 45.9 and 48.1; tables that let more pass lose more (2M, 48, K = 100: heavy tails 145 and 131).
@@ -834,7 +837,7 @@ void plan_filter(ScanPlan& p, long long N, int B, int m, int K, bool subset, int
     p.f_lanes = lanes;
     p.f_stride = stride;
     p.f_far = filter_far_splits(m, words, w16, lanes, subset, cw);
-    p.f_near = p.f_far > 0 && lanes == 1 && (m == 8 ? p.f_share && filter_near_pays(rounds / nb, K) : m == 16 && !p.f_share && filter_near_pays16(N, K, nb));
+    p.f_near = p.f_far > 0 && lanes == 1 && (m == 8 ? filter_near_pays(rounds / nb, K, batch, p.f_share) : m == 16 && !p.f_share && filter_near_pays16(N, K, nb));
     if (p.f_near) p.f_far = 0;
     p.f_pitch = align16((size_t)(cw == 1 ? m : m - p.f_far) * stride * (w16 ? sizeof(uint16_t) : sizeof(uint8_t)));
     p.nblk = (int)nb;
@@ -1163,7 +1166,11 @@ hipError_t launch_filter(const ScanPlan& p, const FilterArgs& a, hipStream_t st)
     };
     if (a.stamps != nullptr) {
         if constexpr ((M == 8 || M == 16) && CW == 1 && !SUB) {
-            if (p.f_near) return go(scan_filter_kernel<M, 1, 4, false, false, 1, M == 8, true, false, true>);
+            if (p.f_near) {
+                if constexpr (M == 8)
+                    if (p.f_share) return go(scan_filter_kernel<8, 1, 4, false, false, 1, true, true, false, true>);
+                return go(scan_filter_kernel<M, 1, 4, false, false, 1, false, true, false, true>);
+            }
             if (p.f_words == 4 && p.f_lanes == 1 && !p.f_w16)
                 return p.f_share ? go(scan_filter_kernel<M, 1, 4, false, false, 1, true, true>) : go(scan_filter_kernel<M, 1, 4, false, false, 1, false, true>);
         }
@@ -1174,7 +1181,11 @@ hipError_t launch_filter(const ScanPlan& p, const FilterArgs& a, hipStream_t st)
         return hipErrorInvalidValue;                         // (pq_measure_step_stamps() has checked)
     }
     if constexpr ((M == 8 || M == 16) && CW == 1 && !SUB) {
-        if (p.f_near) return go(scan_filter_kernel<M, 1, 4, false, false, 1, M == 8, false, false, true>);
+        if (p.f_near) {
+            if constexpr (M == 8)
+                if (p.f_share) return go(scan_filter_kernel<8, 1, 4, false, false, 1, true, false, false, true>);
+            return go(scan_filter_kernel<M, 1, 4, false, false, 1, false, false, false, true>);
+        }
     }
     if constexpr (M == 16 && CW == 1 && !SUB) {
         if (p.f_fine) return p.f_share ? go(scan_filter_kernel<16, 1, 2, false, false, 1, true, false, true>) : go(scan_filter_kernel<16, 1, 2, false, false, 1, false, false, true>);
@@ -1435,8 +1446,10 @@ int enqueue_fold(const ScanPlan& p, int B, int K, void* workspace, int* out_ids,
 }
 
 // Batch from which Eq. 4 runs on the matrix cores.  The scalar kernels are faster below: a wave's chain of d/m matrix
-// instructions takes as long for one tile of 32 queries as for a GPU full of them (measured at d = 512, m = 8, b = 256:
-// 5.3 us at B = 448, the scalar kernels 5.2 at B = 400; 6.1 against 10.8 at B = 1024, 20 against 35 at B = 4096).
+// instructions takes as long for one tile of 32 queries as for a GPU full of them.  Scalar kernels and matrix cores (us): d = 512, m = 8, b = 256 256
+// queries 3.97 and 5.10, 400 5.21 and 5.20, 448 5.32 and 5.25, 640 6.25 and 5.47, 1024 8.69 and 5.98, 4096 27.7 and 19.9; m = 16 320 4.29 and 4.32, 448 5.20
+// and 4.62.  The line is one for all: with more sub-ids it could lie lower (b = 1024 200 7.59 and 5.71), with shorter chunks higher (d = 256 448 3.74 and 4.10, 640
+// 4.32 and 4.32; d = 128 448 2.88 and 3.63, 1024 4.30 and 4.26).
 constexpr int kSubMfmaMinBatch = 448;
 constexpr int kDefaultMfmaMinBatch = 3;    // default scoring: batch from which one matrix-core pass over W beats B mat-vec passes
 

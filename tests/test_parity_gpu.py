@@ -634,7 +634,7 @@ def _large_batch_case(pq, oracle, kind, N, B, m, b, K, tables, mask=0):
 
 # The measurement call runs the instance that the plain call runs: plans that look all splits up in LDS have no rows of counts in the workspace and
 # touch nothing behind it, others write these rows, which come last.  N, B, m, K, splits looked up in device memory
-@pytest.mark.parametrize("N,B,m,K,far", [(180_003, 1000, 8, 6, 0), (200_001, 64, 16, 20, 0), (300_001, 64, 8, 10, 1), (500_001, 48, 16, 3, 2)])
+@pytest.mark.parametrize("N,B,m,K,far", [(180_003, 1000, 8, 6, 0), (200_001, 64, 16, 20, 0), (80_003, 600, 8, 30, 0), (300_001, 64, 8, 10, 1), (500_001, 48, 16, 3, 2)])
 def test_step_stamps_of_the_instance_that_runs(pq, N, B, m, K, far):
     import torch
     gen = torch.Generator(device="cuda").manual_seed(N)
@@ -669,7 +669,9 @@ MORE_INSTANCES = [("scan", 116_559, 700, 4, 256, 150, 0, 8, 8, 1), ("scan", 102_
                   ("subset", 398_141, 257, 4, 256, 17, 0, 16, 8, 1), ("subset", 194_850, 137, 8, 256, 300, 0, 8, 8, 1), ("subset", 201_753, 273, 8, 256, 150, 0, 16, 8, 1),
                   ("subset", 212_279, 162, 16, 256, 10, 0, 16, 8, 1), ("scan16", 806_718, 20, 16, 1900, 400, 0, 2, 16, 0), ("scan16", 251_345, 66, 16, 1900, 100, 0, 2, 16, 1),
                   ("scan16", 389_382, 25, 16, 700, 131, 0, 4, 16, 0), ("scan16", 110_893, 101, 16, 700, 40, 0, 4, 16, 1), ("scan16", 392_274, 25, 16, 300, 131, 0, 8, 16, 0),
-                  ("scan16", 97_407, 225, 16, 300, 40, 0, 8, 16, 1)]
+                  ("scan16", 97_407, 225, 16, 300, 40, 0, 8, 16, 1),
+                  # (many queries, few items: all splits in LDS, floors not shared, sixteen queries to a workgroup and a last one of nine)
+                  ("scan", 60_001, 697, 8, 256, 30, 0, 16, 8, 0)]
 
 
 @pytest.mark.parametrize("kind,N,B,m,b,K,mask,queries,bits,shared", MORE_INSTANCES)

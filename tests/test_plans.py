@@ -163,6 +163,7 @@ def test_eight_queries_per_workgroup_where_sixteen_leave_the_last_half_empty(pla
 
 @pytest.mark.parametrize("N,B,m,K,far", [
     (1_280_000, 64, 8, 10, 1), (1_280_000, 1024, 8, 100, 1), (180_003, 1000, 8, 6, 0), (137_321, 1650, 8, 100, 0), (5_000_000, 16, 16, 10, 2), (300_000, 64, 16, 20, 0),
+    (80_000, 512, 8, 100, 0), (80_000, 1000, 8, 30, 0), (80_000, 512, 8, 10, 1), (100_000, 400, 8, 100, 1),
     (7_000_000, 48, 16, 200, 0), (12_000_000, 48, 16, 130, 0), (20_000_000, 80, 16, 100, 0), (12_000_000, 64, 16, 100, 2), (12_000_000, 32, 16, 130, 2), (12_000_000, 16, 16, 256, 2),
     (400_000, 600, 32, 4, 4), (50_000_000, 32, 8, 10, 2), (20_000_000, 32, 16, 10, 3), (1_280_000, 64, 4, 10, 0), (1_000_000, 8, 64, 10, 0)])
 def test_splits_in_device_memory_and_the_room_for_their_rows(plan, N, B, m, K, far):
