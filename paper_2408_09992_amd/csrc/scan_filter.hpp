@@ -104,9 +104,11 @@ __host__ __device__ constexpr int filter_member(int m, int sum, int i) { return 
 
 // Splits whose tables stay in device memory, so that the L1's way to the lanes works beside the LDS's.  G lanes share an item.  Single lanes: an
 // eighth of the splits, a row of 16 bytes per clock and CU beside the LDS's five (lists gather their rows that way, and two-byte sub-ids have more rows
-// than the L1 holds: none).  Calls with none and with an eighth (us): m = 8, 1.28M items, 64 queries, K = 10 32.6 and 32.0, 1024, K = 100 296 and 290; 600,000, 700
+// than the L1 holds: none).  Calls with none and with an eighth (us): m = 8, 1.28M items, 64 queries, K = 10 32.6 and 32.0, 1024, K = 100 296 and 290 (popular sub-ids,
+// and Eq. 4 between the calls: 257 and 252 a step, in other runs within 1 %: exact scores come through the L1 too); 600,000, 700
 // queries, K = 5 105.5 and 100.5; 600,000, 4096, K = 100 727 and 707; m = 16, 5M, 16, K = 10 48.1 and 45.9; 900,000, 150, K = 3 81.2 and 78.5.  Up to 1.6 % slower where
-// much is scored exactly (m = 16, 500,000, 260, K = 4 77.5 and 78.8; m = 8, 200,000, 150, K = 50 32.0 and 32.4); where floors are shared see filter_near_pays().
+// much is scored exactly (m = 16, 500,000, 260, K = 4 77.5 and 78.8; m = 8, 200,000, 150, K = 50 32.0 and 32.4); where floors are shared, and for many results at m = 16, see
+// filter_near_pays() and filter_near_pays16().
 __host__ __device__ constexpr int filter_far_splits(int m, int words, bool w16, int lanes, bool subset = false, int cw = 1) {
     if (w16 || words < 4) return 0;
     if (lanes == 2) return m == 4 ? 0 : m == 8 ? 2 : 3;
