@@ -104,9 +104,10 @@ int pq_measure_sync_variant(int variant, void* scratch, size_t scratch_bytes, vo
  * candidate list is never left to one workgroup per query but for want of more; bit 6: a single query over a catalogue too
  * long for the short kernel is always scanned in segments; bit 7: batches scanned by upper bounds are by pairs of lanes wherever
  * these fit (lists: m = 4); bit 8: a batch takes the short kernels for two queries per workgroup wherever they fit (bit 0 keeps
- * it off these too).
+ * it off these too); bit 9: a single query is never scanned by one-byte bounds; bit 10: it is wherever that fits (bit 0 keeps it off
+ * too).
  * 0 restores the library's own choice.
- * Process-wide, takes effect for calls made after it returns (workspace sizes depend on bits 0 and 3 to 8).  Returns the
+ * Process-wide, takes effect for calls made after it returns (workspace sizes depend on bits 0 and 3 to 10).  Returns the
  * previous mask.
  */
 int pq_measure_force_general(int mask);
@@ -124,7 +125,7 @@ int pq_measure_force_general(int mask);
 #define PQ_PLAN_KERNEL      0   /* PQ_KERNEL_* */
 #define PQ_PLAN_GROUPS      1   /* workgroups that share a query */
 #define PQ_PLAN_QUERIES     2   /* queries of a workgroup */
-#define PQ_PLAN_FIELD_BITS  3   /* scans by bounds: 8 or 16 */
+#define PQ_PLAN_FIELD_BITS  3   /* scans by bounds: 8 or 16 (PQ_KERNEL_GENERAL, a single query: 8 where one-byte bounds go first) */
 #define PQ_PLAN_FINE        4   /* ... 16-bit counts beside 8-bit fields */
 #define PQ_PLAN_SHARED      5   /* ... a query's workgroups share their floors */
 #define PQ_PLAN_PARTS       6   /* ... parts of the sample ... */

@@ -1,6 +1,6 @@
 // Constants, cross-lane helpers (DPP), wave-level reductions and the bitonic sort shared by every kernel.
 // Part of kernels.hpp, which includes these parts inside namespace pqk in this order:
-// common.hpp, subitem_scores.hpp, topk_parts.hpp, select_small.hpp, scan_single.hpp, scan_short.hpp, scan_pair.hpp, scan_long.hpp, scan_subset.hpp,
+// common.hpp, subitem_scores.hpp, topk_parts.hpp, select_small.hpp, scan_single.hpp, scan_bytes.hpp, scan_short.hpp, scan_pair.hpp, scan_long.hpp, scan_subset.hpp,
 // scan_batched.hpp, scan_filter.hpp, fold.hpp, comparison.hpp.
 #pragma once
 
@@ -103,6 +103,17 @@ __device__ __forceinline__ void wave_minmax(float& mn, float& mx) {
 }
 
 // min and max over the wave of unsigned values, in every lane
+__device__ __forceinline__ float wave_sum_f32(float v) {     // (for bounds and heuristics: any order will do)
+    v += dpp_f32<kDppQuadSwap1>(0.0f, v);
+    v += dpp_f32<kDppQuadSwap2>(0.0f, v);
+    v += dpp_f32<kDppRowHalfMirror>(0.0f, v);
+    v += dpp_f32<kDppRowMirror>(0.0f, v);
+    float sum = 0.0f;
+#pragma unroll
+    for (int row = 0; row < 4; ++row) sum += __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), row * 16));
+    return sum;
+}
+
 __device__ __forceinline__ void wave_minmax_u32(uint32_t& mn, uint32_t& mx) {
     mn = min(mn, dpp_u32<kDppQuadSwap1>(mn, mn));       mx = max(mx, dpp_u32<kDppQuadSwap1>(mx, mx));
     mn = min(mn, dpp_u32<kDppQuadSwap2>(mn, mn));       mx = max(mx, dpp_u32<kDppQuadSwap2>(mx, mx));

@@ -1,7 +1,7 @@
 // The last launch of every TopK call: the workgroups' lists -> the final sorted K per query (fold_lists_kernel,
 // fold_small_kernel).
 // Part of kernels.hpp, which includes these parts inside namespace pqk in this order:
-// common.hpp, subitem_scores.hpp, topk_parts.hpp, select_small.hpp, scan_single.hpp, scan_short.hpp, scan_pair.hpp, scan_long.hpp, scan_subset.hpp,
+// common.hpp, subitem_scores.hpp, topk_parts.hpp, select_small.hpp, scan_single.hpp, scan_bytes.hpp, scan_short.hpp, scan_pair.hpp, scan_long.hpp, scan_subset.hpp,
 // scan_batched.hpp, scan_filter.hpp, fold.hpp, comparison.hpp.
 #pragma once
 

@@ -61,7 +61,7 @@ thread_local char g_hip_error[256] = "no HIP error recorded";
 // pq_measure_force_general(): bit 0 keeps calls off the short and long scans and off those by pairs of queries, bit 1 off fold_small_kernel, bit 2
 // Eq. 4 off the matrix cores, bit 3 off the scans by upper bounds; bit 4 on them wherever they can; bit 5 spreads short candidate lists
 // over the chip; bit 6: longer single queries always in segments; bit 7: scans by upper bounds by pairs of lanes wherever these fit; bit 8: batches by
-// pairs of queries wherever these fit (0: the product's choice)
+// pairs of queries wherever these fit; bit 9 keeps single queries off the scan by one-byte bounds; bit 10: on it wherever it fits (0: the product's choice)
 std::atomic<int> g_force_general{0};
 
 int record_hip(hipError_t e) {
@@ -102,6 +102,7 @@ struct ScanPlan {
     bool glut;       // two-byte sub-ids: the m x b table does not fit LDS and is read from device memory
     bool short_scan; // scan_short_kernel: every workgroup's share fits its registers, K small
     int short_units; // ... units (code vectors, or items for m = 32, 64) a thread holds
+    bool bytes;      // scan_bytes_kernel: one query's long catalogue by one-byte upper bounds
     bool long_scan;  // scan_long_kernel: one query's catalogue in segments
     bool pair_scan;  // scan_pair_kernel: as the short scan, two queries per workgroup (short_units: what a thread holds)
     bool short_subset; // scan_subset_kernel: a candidate list whose share per thread fits its registers, K small
@@ -130,7 +131,7 @@ struct ScanPlan {
 };
 
 // What make_plan() may choose from.
-enum { kNoFilter = 1, kNoLong = 2, kNoPair = 4 };
+enum { kNoFilter = 1, kNoLong = 2, kNoPair = 4, kNoBytes = 8 };
 
 bool is_vec_m(int m) { return m == 1 || m == 2 || m == 4 || m == 8 || m == 16 || m == 32 || m == 64; }
 
@@ -190,6 +191,25 @@ constexpr long long kDirectUnits(int row) { return row <= 16 ? 8 : row == 32 ? 4
 bool subset_direct_pays(long long N, int m, int B) {
     if (N * m > kDirectUnits(16) * 16LL * kThreads) return false;
     return N * (m + 8) <= (112LL << 10) + 720LL * B;
+}
+
+// Bytes of codes from which one query's catalogue is scanned by one-byte bounds (scan_bytes_kernel): before that its sample, counts and lists per wave
+// weigh more than the lookups and the uneven rounds that it saves.  Calls without and with (us; codes that no cache holds), just below the lines and further on: m = 4:
+// 8M items, K = 10 16.2 and 17.3, 16M 23.1 and 21.5, 11M, K = 100 25.2 and 25.9, 24M 36.4 and 34.0; m = 8: 5M, K = 10 17.7 and 18.0, 8M 24.8 and 21.3, 40M 66.2 and 57.0,
+// 12M, K = 100 32.8 and 32.6, 24M 51.1 and 46.4, 12M, K = 256 37.5 and 38.6, 24M 59.0 and 54.1, K = 512 (codes partly held), 16M 52.9 and 55.1, 30M 78.8 and 74.1; m = 16: 4M, K = 10
+// 20.5 and 21.2, 7M 33.4 and 27.1, 24M 79.9 and 66.1, 5M, K = 100 28.0 and 30.4, 9M 43.9 and 39.3, 7M, K = 256 39.4 and 40.4, 14M 61.9 and 57.8; m = 32: 2M, K = 10 22.4 and
+// 22.0, 4M 33.9 and 30.9, K = 100 37.8 and 38.1, 6M 56.2 and 46.4, 4M, K = 256 40.6 and 43.8, 9M 75.1 and 68.1; m = 64: 4M, K = 10 55.4 and 57.3, 8M 102.0 and 97.3, 6M, K = 40
+// 82.8 and 82.9, 8M, K = 256 111.2 and 107.9.
+bool bytes_pay(long long N, int m, int K) {
+    const double bytes = (double)N * m;
+    switch (m) {
+        case 4: return bytes >= (K <= 16 ? 4.4e7 : K <= 256 ? 7.0e7 : 9.0e7);
+        case 8: return bytes >= (K <= 16 ? 5.2e7 : K <= 128 ? 1.1e8 : K <= 256 ? 1.4e8 : 1.8e8);
+        case 16: return bytes >= (K <= 16 ? 8.8e7 : K <= 128 ? 1.1e8 : 1.4e8);
+        case 32: return bytes >= (K <= 16 ? 8.0e7 : K <= 128 ? 1.5e8 : 1.9e8);
+        case 64: return bytes >= (K <= 16 ? 3.6e8 : 4.5e8);
+        default: return false;
+    }
 }
 
 // Where one query's catalogue is scanned in segments (scan_long_kernel) and not by the general kernel's per-wave lists: while the first
@@ -423,6 +443,21 @@ ScanPlan make_plan(long long N, int B, int m, int K, bool generic = false, int c
             p.big = true;
             p.scan_dyn_lds = sizeof(LongSelectLds<kLongThreads>) + table16;
             p.scan_lds = sizeof(LongSelectLds<kLongThreads>) + table;
+        }
+    }
+    // Long catalogues of a single query: one-byte bounds first.
+    p.bytes = false;
+    if (!(without & kNoBytes) && B == 1 && cw == 1 && p.vec && !generic && m >= 4 && !(g_force_general.load(std::memory_order_relaxed) & (1 | 512)) &&
+        (bytes_pay(N, m, K) || (g_force_general.load(std::memory_order_relaxed) & 1024))) {
+        const size_t dyn = scan_lds_bytes(0, p.cap, p.candmax, K, kMaxWaves), tables = (size_t)m * (kLutStride * (sizeof(float) + 1) + 2 * sizeof(float));
+        if (dyn + tables <= kMaxLdsBytes) {
+            p.bytes = true;
+            p.short_scan = p.long_scan = false;
+            p.nblk = kAssumedCUs;
+            p.copies = 1;
+            p.big = true;
+            p.scan_dyn_lds = dyn;
+            p.scan_lds = dyn + tables;
         }
     }
     // Candidate lists (the `generic` plans) of rows of 4, 8 or 16 bytes, short enough for a thread to
@@ -790,7 +825,7 @@ void plan_filter(ScanPlan& p, long long N, int B, int m, int K, bool subset, int
         if (fill == 1 || us < best_us) { best_us = us; nb = cand; }
     }
     p.filter = true;
-    p.tiled = p.short_scan = p.pair_scan = p.short_subset = p.subset_pair = p.long_scan = false;
+    p.tiled = p.short_scan = p.pair_scan = p.short_subset = p.subset_pair = p.long_scan = p.bytes = false;
     p.f_words = words;
     p.f_w16 = w16;
     p.f_queries = queries;
@@ -1324,6 +1359,14 @@ int enqueue_scan(const ScanPlan& p, const uint8_t* codes, const float* S, long l
         if (stamps != nullptr && m != 8) return PQ_ERR_UNSUPPORTED;
         return record_hip(launch_short(p, a, B, m, st));
     }
+    if (p.bytes) {
+        if (stamps != nullptr && m != 8) return PQ_ERR_UNSUPPORTED;
+        auto go = [&](auto kernel) {
+            hipError_t err = allow_lds(kernel, p.scan_dyn_lds);
+            return err != hipSuccess ? err : launch(kernel, dim3(p.nblk, B), kBytesThreads, p.scan_dyn_lds, st, a);
+        };
+        return record_hip(stamps != nullptr ? go(scan_bytes_kernel<8, true>) : m == 4 ? go(scan_bytes_kernel<4>) : m == 8 ? go(scan_bytes_kernel<8>) : m == 16 ? go(scan_bytes_kernel<16>) : m == 32 ? go(scan_bytes_kernel<32>) : go(scan_bytes_kernel<64>));
+    }
     if (p.pair_scan) {
         if (stamps != nullptr) return PQ_ERR_UNSUPPORTED;
         return record_hip(launch_pair(p, a, B, m, cw, st));
@@ -1632,7 +1675,7 @@ int pq_score_topk_profile(const uint8_t* codes, const float* S, long long N, int
 }
 
 int pq_measure_force_general(int mask) {
-    return g_force_general.exchange(mask & 511, std::memory_order_relaxed);
+    return g_force_general.exchange(mask & 2047, std::memory_order_relaxed);
 }
 
 int pq_measure_plan(long long N, int B, int m, int b, int K, int kind, int* plan) {
@@ -1650,6 +1693,7 @@ int pq_measure_plan(long long N, int B, int m, int b, int K, int kind, int* plan
                            : p.short_subset ? PQ_KERNEL_SHORT_LIST : p.subset_pair ? PQ_KERNEL_LIST_PAIRS : PQ_KERNEL_GENERAL;
     plan[PQ_PLAN_GROUPS] = p.nblk;
     plan[PQ_PLAN_QUERIES] = p.filter ? p.f_queries : p.tiled ? kQ : p.pair_scan || p.subset_pair ? 2 : 1;
+    if (p.bytes) plan[PQ_PLAN_FIELD_BITS] = 8;
     if (p.filter) {
         plan[PQ_PLAN_FIELD_BITS] = p.f_w16 ? 16 : 8;
         plan[PQ_PLAN_FINE] = p.f_fine;
@@ -1674,9 +1718,9 @@ int pq_measure_step_stamps(const float* queries, const float* centroids, const u
     static_assert(PQ_STAMP_SLOTS == kStampSlots, "header and kernels agree on the record size");
     // (the scan in segments has no measurement instance, that by upper bounds those of the named workloads: otherwise the kernels
     // that would run without them)
-    ScanPlan p = make_plan(N, B, m, K, false, 1, kLutStride, kNoLong | kNoPair);
+    ScanPlan p = make_plan(N, B, m, K, false, 1, kLutStride, kNoLong | kNoPair | (m == 8 ? 0 : kNoBytes));
     if (p.filter && (p.f_w16 || p.f_fine || p.f_words != 4 || !(m == 8 || (m == 16 && p.f_lanes == 1))))
-        p = make_plan(N, B, m, K, false, 1, kLutStride, kNoLong | kNoPair | kNoFilter);
+        p = make_plan(N, B, m, K, false, 1, kLutStride, kNoLong | kNoPair | kNoFilter | kNoBytes);
     if (workspace_bytes_given < workspace_bytes(p, B, K)) return PQ_ERR_WORKSPACE;
     if (!(p.filter || p.tiled || m == 8))
         return PQ_ERR_UNSUPPORTED;                             // (scan kernels with a measurement instance)

@@ -1,7 +1,7 @@
 // Eq. 5 + TopK for batches (filter_prepare_kernel, scan_filter_kernel): a scan of small-integer upper bounds finds the few
 // items that can matter, and only those are scored exactly.
 // Part of kernels.hpp, which includes these parts inside namespace pqk in this order:
-// common.hpp, subitem_scores.hpp, topk_parts.hpp, select_small.hpp, scan_single.hpp, scan_short.hpp, scan_pair.hpp, scan_long.hpp, scan_subset.hpp,
+// common.hpp, subitem_scores.hpp, topk_parts.hpp, select_small.hpp, scan_single.hpp, scan_bytes.hpp, scan_short.hpp, scan_pair.hpp, scan_long.hpp, scan_subset.hpp,
 // scan_batched.hpp, scan_filter.hpp, fold.hpp, comparison.hpp.
 //
 // What bounds a batch is the LDS: random 16-byte gathers return 5 lane reads per clock and CU whatever they hold.  With
@@ -132,17 +132,6 @@ __device__ __forceinline__ uint32_t filter_sub_id(const uint32_t* w, int item, i
     const int byte = item * P + k * CW;
     if constexpr (CW == 2) return (byte & 2) ? (w[byte >> 2] >> 16) : (w[byte >> 2] & 0xFFFFu);
     else return (w[byte >> 2] >> ((byte & 3) * 8)) & 0xFFu;
-}
-
-__device__ __forceinline__ float wave_sum_f32(float v) {     // (for bounds and heuristics: any order will do)
-    v += dpp_f32<kDppQuadSwap1>(0.0f, v);
-    v += dpp_f32<kDppQuadSwap2>(0.0f, v);
-    v += dpp_f32<kDppRowHalfMirror>(0.0f, v);
-    v += dpp_f32<kDppRowMirror>(0.0f, v);
-    float sum = 0.0f;
-#pragma unroll
-    for (int row = 0; row < 4; ++row) sum += __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), row * 16));
-    return sum;
 }
 
 __host__ __device__ inline size_t filter_prepare_lds_bytes(long long entries, int m) {

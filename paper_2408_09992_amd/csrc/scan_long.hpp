@@ -1,7 +1,7 @@
 // Eq. 5 + TopK for catalogues beyond what one set of registers holds (scan_long_kernel): the single query over tens of millions of
 // items, and queries side by side whose tables of two-byte sub-ids leave no room for lists per wave.
 // Part of kernels.hpp, which includes these parts inside namespace pqk in this order:
-// common.hpp, subitem_scores.hpp, topk_parts.hpp, select_small.hpp, scan_single.hpp, scan_short.hpp, scan_pair.hpp, scan_long.hpp, scan_subset.hpp,
+// common.hpp, subitem_scores.hpp, topk_parts.hpp, select_small.hpp, scan_single.hpp, scan_bytes.hpp, scan_short.hpp, scan_pair.hpp, scan_long.hpp, scan_subset.hpp,
 // scan_batched.hpp, scan_filter.hpp, fold.hpp, comparison.hpp.
 #pragma once
 

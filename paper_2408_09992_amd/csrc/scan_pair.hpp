@@ -1,7 +1,7 @@
 // Eq. 5 + TopK for a few queries over catalogues short enough that a workgroup's share fits its registers (scan_pair_kernel): as
 // scan_short_kernel, two queries per workgroup.
 // Part of kernels.hpp, which includes these parts inside namespace pqk in this order:
-// common.hpp, subitem_scores.hpp, topk_parts.hpp, select_small.hpp, scan_single.hpp, scan_short.hpp, scan_pair.hpp, scan_long.hpp, scan_subset.hpp,
+// common.hpp, subitem_scores.hpp, topk_parts.hpp, select_small.hpp, scan_single.hpp, scan_bytes.hpp, scan_short.hpp, scan_pair.hpp, scan_long.hpp, scan_subset.hpp,
 // scan_batched.hpp, scan_filter.hpp, fold.hpp, comparison.hpp.
 #pragma once
 

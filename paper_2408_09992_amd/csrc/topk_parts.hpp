@@ -1,6 +1,6 @@
 // What the TopK side of every kernel is made of: keys, histogram cuts, per-wave candidate lists, exact selection.
 // Part of kernels.hpp, which includes these parts inside namespace pqk in this order:
-// common.hpp, subitem_scores.hpp, topk_parts.hpp, select_small.hpp, scan_single.hpp, scan_short.hpp, scan_pair.hpp, scan_long.hpp, scan_subset.hpp,
+// common.hpp, subitem_scores.hpp, topk_parts.hpp, select_small.hpp, scan_single.hpp, scan_bytes.hpp, scan_short.hpp, scan_pair.hpp, scan_long.hpp, scan_subset.hpp,
 // scan_batched.hpp, scan_filter.hpp, fold.hpp, comparison.hpp.
 #pragma once
 

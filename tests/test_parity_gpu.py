@@ -317,6 +317,40 @@ def test_single_query_in_segments(pq, oracle, m, wide, N, K):
     check(pq, oracle, codes, S, K, "rising")
 
 
+# One query by one-byte bounds, on it by the mask: from a single code vector to several steps, with and without a tail after the last whole vector and
+# workgroups without a share; tables whose bounds are exact, loose, useless (ties, one far entry, scores that hardly differ in fp32) or masked.
+@pytest.mark.parametrize("m,b,K", [(4, 256, 10), (4, 5, 40), (8, 256, 1), (8, 256, 100), (8, 250, 512), (16, 256, 10), (16, 3, 17), (32, 256, 16), (32, 256, 100), (64, 256, 10), (64, 100, 17)])
+def test_single_query_by_one_byte_bounds(pq, oracle, m, b, K):
+    rng = np.random.default_rng(100 * m + K)
+    per_step = 256 * 1024 * max(1, 16 // m)
+    prev = pq.pq_measure_force_general(1024)
+    try:
+        for N in (max(K, 16 // m), 16 // min(m, 16) * 64 + K + 1, 70_001, per_step // 16 * 16 + 3, 2 * per_step + 64 * 17 + 1):
+            assert pq.pq_measure_plan("scan", N, 1, m, b, K)["field_bits"] == 8
+            codes = rng.integers(0, b, (N, m), dtype=np.uint8)
+            codes[N // 2:N // 2 + 40] = codes[:min(40, N - N // 2)]
+            S = rng.standard_normal((1, m, b), dtype=np.float32)
+            assert_same_topk(pq, oracle, codes, S, K, f"normal {N}")
+            if N < 60_000:
+                continue
+            small = codes[:150_001]
+            uneven = S * np.where(np.arange(m) == 1, np.float32(50.0), np.float32(0.02))[None, :, None]
+            masked, far, deep = S.copy(), S.copy(), S.copy()
+            masked[0, 1, :b // 3] = -1e9
+            masked[0, m - 1, b // 2] = -np.inf
+            far[0, 2, 1] = 1e4
+            deep[0, 0, :-1] = -1e9
+            for name, T in (("uneven", uneven), ("masked", masked), ("far entry", far), ("one entry of a split counts", deep), ("ties", np.round(S)), ("zeros", 0 * S), ("negative", S - 20),
+                            ("offset", S + np.float32(1e7)), ("denormal", (np.abs(S) * np.float32(1e-41)).astype(np.float32))):
+                assert_same_topk(pq, oracle, small, T.astype(np.float32), K, f"{name} {N}")
+            infinite = np.where(S > 2.5, np.float32(np.inf), S)   # (the bar above subtracts: the bits alone)
+            ids, sc = run_topk(pq, small, infinite, K)
+            rid, rsc = oracle.score_topk(small, infinite, K)
+            assert np.array_equal(ids, rid) and np.array_equal(sc.view(np.uint32), rsc.view(np.uint32)), N
+    finally:
+        pq.pq_measure_force_general(prev)
+
+
 # ... several of them, and any number of results, where two-byte sub-ids' tables leave no room for lists per wave: one to many
 # workgroups per query, tables up to the largest that fit
 @pytest.mark.parametrize("N,m,b,B,K", [(6_400_003, 4, 7297, 2, 421), (300_001, 8, 4096, 64, 250), (150_003, 4, 8300, 200, 120), (60_001, 16, 2048, 300, 512),
