@@ -13,7 +13,8 @@
 // floor; a wave with any other scores its vector exactly, by the same left-to-right fp32 chain as everywhere, and only exact scores enter lists, floors
 // and results: bit for bit the other kernels' results, whatever the tables are.
 // 50M items, m = 8, K = 10 and 100: calls 78.9 -> 68.6 and 88.4 -> 75.6 us (16 copies of the tables in LDS; 5.8 TB/s now); 20M, m = 16 68.6 -> 55.9; 6M, m = 32 45.8 -> 37.7.  A
-// unit's codes are asked for one unit ahead: every further one costs a microsecond, since the sample waits for all that was asked for before.
+// wave's second unit is asked for when the tables are there, and from then on one at a time: asked for before, every further unit costs a microsecond, since the
+// sample waits for all of them.
 #pragma once
 
 constexpr int kBytesThreads = kBigThreads;
@@ -82,7 +83,7 @@ __global__ __launch_bounds__(kBytesThreads) void scan_bytes_kernel(ScanArgs a) {
     uint32_t w[2][4 * VPI], unit[2] = {(uint32_t)wave, 0};
     fetch(unit[0], w[0]);
     for (int i = tid; i < kBins; i += NT) L.hist[i] = 0;
-    if (tid == 0) { ctl->shared_floor = -__builtin_inff(); ctl->ncand = 0; ctl->next_unit = NW; }
+    if (tid == 0) { ctl->shared_floor = -__builtin_inff(); ctl->ncand = 0; ctl->next_unit = 2 * NW; }
     stamp<STAMP>(rec, kStampRequested, lane);
     // a split's largest entry, and how far below it the best of the middle lane's entries lies: about a sixth of all lie less far.  (A mean would
     // be carried away by one masked entry.)
@@ -115,6 +116,8 @@ __global__ __launch_bounds__(kBytesThreads) void scan_bytes_kernel(ScanArgs a) {
     }
     __syncthreads();
     stamp<STAMP>(rec, kStampTables, lane);
+    unit[1] = (uint32_t)(NW + wave);
+    fetch(unit[1], w[1]);
 
     WaveTopK top{L.lists + (size_t)wave * a.cap, a.cap, K, 0, 0, 0ull, -__builtin_inff()};
     // ---- counts: 255 steps below every split's largest entry, what lies deeper counts as that
@@ -306,11 +309,11 @@ __global__ __launch_bounds__(kBytesThreads) void scan_bytes_kernel(ScanArgs a) {
         while (unit[0] < units && (!decltype(bounded)::value || in_a_row < kInARow)) {   // (slot 0 holds the older one)
 #pragma unroll
             for (int i = 0; i < 2; ++i) {
-                unit[i ^ 1] = (uint32_t)__builtin_amdgcn_readfirstlane(pending);
-                request();
-                fetch(unit[i ^ 1], w[i ^ 1]);
                 if (!seen && unit[i] < units) process(bounded, w[i], unit[i]);
                 seen = false;
+                unit[i] = (uint32_t)__builtin_amdgcn_readfirstlane(pending);
+                request();
+                fetch(unit[i], w[i]);
             }
         }
     };
