@@ -101,8 +101,8 @@ namespace pqk {
     PQ_SHORT16_U(X, 16, 8) PQ_SHORT16_U(X, 16, 12) PQ_SHORT16_U(X, 16, 16) PQ_SHORT16_U(X, 16, 24) PQ_SHORT16_U(X, 16, 32) \
     PQ_SHORT16_U(X, 16, 1) PQ_SHORT16_U(X, 16, 2) PQ_SHORT16_U(X, 16, 3) PQ_SHORT16_U(X, 16, 4) PQ_SHORT16_U(X, 16, 5) PQ_SHORT16_U(X, 16, 6)
 // scan_long_kernel<M, CW, C>
-// scan_bytes_kernel<M, STAMP> instances (measurement: m = 8)
-#define PQ_BYTES_INSTANCES(X) X(4, false) X(8, false) X(16, false) X(32, false) X(64, false) X(8, true)
+// scan_bytes_kernel<M, CW, STAMP> instances (measurement: m = 8)
+#define PQ_BYTES_INSTANCES(X) X(4, 1, false) X(8, 1, false) X(16, 1, false) X(32, 1, false) X(64, 1, false) X(8, 1, true) X(4, 2, false) X(8, 2, false) X(16, 2, false)
 #define PQ_LONG_INSTANCES(X) \
     X(4, 1, kTableCopies) X(8, 1, kTableCopies) X(16, 1, 1) X(32, 1, 1) X(64, 1, 1) X(4, 2, 1) X(8, 2, 1) X(16, 2, 1)
 // scan_subset_kernel<M, U, NT>: rows of 4, 8, 16 bytes, every number of vectors per thread
@@ -152,8 +152,8 @@ namespace pqk {
 #define PQ_PAIR_DEFINE(M, U, NT, CW) template __global__ void scan_pair_kernel<M, U, NT, CW>(const uint8_t*, const float*, void*, float*, uint32_t, int, int, int);
 #define PQ_PAIR_EXTERN(M, U, NT, CW) extern PQ_PAIR_DEFINE(M, U, NT, CW)
 #define PQ_SHORT16_EXTERN(M, U, NT, ST, CW) extern PQ_SHORT16_DEFINE(M, U, NT, ST, CW)
-#define PQ_BYTES_DEFINE(M, ST) template __global__ void scan_bytes_kernel<M, ST>(ScanArgs);
-#define PQ_BYTES_EXTERN(M, ST) extern PQ_BYTES_DEFINE(M, ST)
+#define PQ_BYTES_DEFINE(M, CW, ST) template __global__ void scan_bytes_kernel<M, CW, ST>(ScanArgs);
+#define PQ_BYTES_EXTERN(M, CW, ST) extern PQ_BYTES_DEFINE(M, CW, ST)
 #define PQ_LONG_DEFINE(M, CW, C) template __global__ void scan_long_kernel<M, CW, C>(const uint8_t*, const float*, void*, float*, uint32_t, int, int);
 #define PQ_LONG_EXTERN(M, CW, C) extern PQ_LONG_DEFINE(M, CW, C)
 #define PQ_SUBSET_DEFINE(M, U, NT) template __global__ void scan_subset_kernel<M, U, NT>(const uint8_t*, const int*, const float*, void*, float*, uint32_t, uint32_t, int, int);

@@ -200,8 +200,12 @@ bool subset_direct_pays(long long N, int m, int B) {
 // 20.5 and 21.2, 7M 33.4 and 27.1, 24M 79.9 and 66.1, 5M, K = 100 28.0 and 30.4, 9M 43.9 and 39.3, 7M, K = 256 39.4 and 40.4, 14M 61.9 and 57.8; m = 32: 2M, K = 10 22.4 and
 // 22.0, 4M 33.9 and 30.9, K = 100 37.8 and 38.1, 6M 56.2 and 46.4, 4M, K = 256 40.6 and 43.8, 9M 75.1 and 68.1; m = 64: 4M, K = 10 55.4 and 57.3, 8M 102.0 and 97.3, 6M, K = 40
 // 82.8 and 82.9, 8M, K = 256 111.2 and 107.9.
-bool bytes_pay(long long N, int m, int K) {
-    const double bytes = (double)N * m;
+// Two bytes: what they gain is the memory's rate (units of one vector, 6.3 TB/s instead of 5.9), the less the larger the tables that come first.  m = 4, b = 1500: 8M, K = 10 19.9 and 22.4, 14M
+// 29.1 and 28.5, 48M 74.6 and 69.2; b = 5000: 24M 42.0 and 42.6, 48M 74.6 and 72.2; m = 8, b = 1024: 8M 29.6 and 31.0, 14M 46.5 and 45.1, 45M 126.4 and 120.5, K = 100 133.3 and 123.9; b = 2500:
+// 14M, K = 10 47.3 and 47.4, 45M 127.9 and 122.9; m = 16, b = 300: 3M 24.6 and 25.7, 6M 42.6 and 39.8, 22M 124.4 and 121.3; b = 1000: 22M, K = 100 129.7 and 129.5.
+bool bytes_pay(long long N, int m, int b, int K, int cw) {
+    const double bytes = (double)N * m * cw;
+    if (cw == 2) return m * b <= 9000 ? bytes >= (m == 4 ? 1.1e8 : 2.0e8) : bytes >= 4.5e8 && (m < 16 || K <= 16);
     switch (m) {
         case 4: return bytes >= (K <= 16 ? 4.4e7 : K <= 256 ? 7.0e7 : 9.0e7);
         case 8: return bytes >= (K <= 16 ? 5.2e7 : K <= 128 ? 1.1e8 : K <= 256 ? 1.4e8 : 1.8e8);
@@ -447,17 +451,17 @@ ScanPlan make_plan(long long N, int B, int m, int K, bool generic = false, int c
     }
     // Long catalogues of a single query: one-byte bounds first.
     p.bytes = false;
-    if (!(without & kNoBytes) && B == 1 && cw == 1 && p.vec && !generic && m >= 4 && !(g_force_general.load(std::memory_order_relaxed) & (1 | 512)) &&
-        (bytes_pay(N, m, K) || (g_force_general.load(std::memory_order_relaxed) & 1024))) {
-        const size_t dyn = scan_lds_bytes(0, p.cap, p.candmax, K, kMaxWaves), tables = (size_t)m * (kLutStride * (sizeof(float) + 1) + 2 * sizeof(float));
-        if (dyn + tables <= kMaxLdsBytes) {
+    if (!(without & kNoBytes) && B == 1 && p.vec && !generic && m >= 4 && !(g_force_general.load(std::memory_order_relaxed) & (1 | 512)) &&
+        (bytes_pay(N, m, b, K, cw) || (g_force_general.load(std::memory_order_relaxed) & 1024))) {
+        const size_t dyn = scan_lds_bytes(0, p.cap, p.candmax, K, kMaxWaves), tables = bytes_table_bytes(m, b, cw), all = dyn + tables + 2 * kMaxWaves * sizeof(float) + (m > kMaxWaves ? 2 * (m - kMaxWaves) * sizeof(float) : 0);
+        if (all + 64 <= kMaxLdsBytes) {
             p.bytes = true;
-            p.short_scan = p.long_scan = false;
+            p.short_scan = p.long_scan = p.glut = false;
             p.nblk = kAssumedCUs;
             p.copies = 1;
             p.big = true;
-            p.scan_dyn_lds = dyn;
-            p.scan_lds = dyn + tables;
+            p.scan_dyn_lds = dyn + (cw == 2 ? tables : 0);
+            p.scan_lds = all;
         }
     }
     // Candidate lists (the `generic` plans) of rows of 4, 8 or 16 bytes, short enough for a thread to
@@ -1351,6 +1355,14 @@ int enqueue_scan(const ScanPlan& p, const uint8_t* codes, const float* S, long l
     a.ws_keys = static_cast<uint64_t*>(workspace);
     a.out_ids = p.direct ? out_ids : nullptr; a.out_scores = out_scores;
     hipError_t e;
+    if (p.bytes) {
+        if (stamps != nullptr && m != 8) return PQ_ERR_UNSUPPORTED;
+        auto go = [&](auto kernel) {
+            hipError_t err = allow_lds(kernel, p.scan_dyn_lds);
+            return err != hipSuccess ? err : launch(kernel, dim3(p.nblk, B), kBytesThreads, p.scan_dyn_lds, st, a);
+        };
+        return record_hip(stamps != nullptr ? go(scan_bytes_kernel<8, 1, true>) : cw == 2 ? (m == 4 ? go(scan_bytes_kernel<4, 2>) : m == 8 ? go(scan_bytes_kernel<8, 2>) : go(scan_bytes_kernel<16, 2>)) : m == 4 ? go(scan_bytes_kernel<4>) : m == 8 ? go(scan_bytes_kernel<8>) : m == 16 ? go(scan_bytes_kernel<16>) : m == 32 ? go(scan_bytes_kernel<32>) : go(scan_bytes_kernel<64>));
+    }
     if (p.short_scan && cw == 2) {
         if (stamps != nullptr) return PQ_ERR_UNSUPPORTED;
         return record_hip(m == 4 ? launch_short16_m<4>(p, a, B, st) : m == 8 ? launch_short16_m<8>(p, a, B, st) : launch_short16_m<16>(p, a, B, st));
@@ -1358,14 +1370,6 @@ int enqueue_scan(const ScanPlan& p, const uint8_t* codes, const float* S, long l
     if (p.short_scan) {
         if (stamps != nullptr && m != 8) return PQ_ERR_UNSUPPORTED;
         return record_hip(launch_short(p, a, B, m, st));
-    }
-    if (p.bytes) {
-        if (stamps != nullptr && m != 8) return PQ_ERR_UNSUPPORTED;
-        auto go = [&](auto kernel) {
-            hipError_t err = allow_lds(kernel, p.scan_dyn_lds);
-            return err != hipSuccess ? err : launch(kernel, dim3(p.nblk, B), kBytesThreads, p.scan_dyn_lds, st, a);
-        };
-        return record_hip(stamps != nullptr ? go(scan_bytes_kernel<8, true>) : m == 4 ? go(scan_bytes_kernel<4>) : m == 8 ? go(scan_bytes_kernel<8>) : m == 16 ? go(scan_bytes_kernel<16>) : m == 32 ? go(scan_bytes_kernel<32>) : go(scan_bytes_kernel<64>));
     }
     if (p.pair_scan) {
         if (stamps != nullptr) return PQ_ERR_UNSUPPORTED;

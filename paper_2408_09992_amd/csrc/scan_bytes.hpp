@@ -29,24 +29,36 @@ struct ByteBounds {
     }
 };
 
+// bytes of a split's counts (two-byte sub-ids: whole words)
+__host__ __device__ constexpr int bytes_stride(int b, int cw) { return cw == 1 ? kLutStride : (b + 3) & ~3; }
+__host__ __device__ constexpr size_t bytes_table_bytes(int m, int b, int cw) {
+    return align16((size_t)m * (cw == 1 ? kLutStride : b) * sizeof(float)) + align16((size_t)m * bytes_stride(b, cw));
+}
+
+// M, CW: splits, bytes per sub-id.  Two-byte sub-ids: tables in dynamic LDS, exact ones as they lie in memory.
 // STAMP: measurement instance that also records wall-clock stamps per wave.
-template <int M, bool STAMP = false>
+template <int M, int CW = 1, bool STAMP = false>
 __global__ __launch_bounds__(kBytesThreads) void scan_bytes_kernel(ScanArgs a) {
     constexpr int NT = kBytesThreads, NW = NT / kWave;
-    constexpr int VPI = M > 16 ? M / 16 : 1, IPV = M > 16 ? 1 : 16 / M;   // vectors of a piece, items of a piece
+    constexpr int P = M * CW;                                  // bytes of an item's row
+    constexpr int VPI = P > 16 ? P / 16 : 1, IPV = P > 16 ? 1 : 16 / P;   // vectors of a piece, items of a piece
     constexpr int kSplits = (M + NW - 1) / NW;                 // of a wave, while the tables are made
-    __shared__ __align__(16) float lut[M * kLutStride];
-    __shared__ __align__(16) uint8_t counts[M * kLutStride];
-    __shared__ float largest[M], spreads[M];
+    constexpr int kParts = CW == 1 ? 1 : NW / M;               // waves of a split, likewise
+    __shared__ __align__(16) float lut_static[CW == 1 ? M * kLutStride : 4];
+    __shared__ __align__(16) uint8_t counts_static[CW == 1 ? M * kLutStride : 4];
+    __shared__ float largest[M * kParts], spreads[M * kParts];
     extern __shared__ __align__(16) unsigned char smem[];
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid / kWave);
     const int q = blockIdx.y, nblk = gridDim.x, blk = blockIdx.x, K = a.K, b = a.b;
     uint64_t* const rec = STAMP ? a.stamps + (((size_t)q * nblk + blk) * NW + wave) * kStampSlots : nullptr;
     stamp<STAMP>(rec, kStampEntry, lane);
-    const ScanLds L = carve_scan(smem, 0, a.cap, a.candmax, NW);
+    const int stride = CW == 1 ? kLutStride : b, count_stride = bytes_stride(b, CW);
+    float* const lut = CW == 1 ? lut_static : reinterpret_cast<float*>(smem);
+    uint8_t* const counts = CW == 1 ? counts_static : smem + align16((size_t)M * b * sizeof(float));
+    const ScanLds L = carve_scan(smem + (CW == 1 ? 0 : bytes_table_bytes(M, b, CW)), 0, a.cap, a.candmax, NW);
     Ctl* const ctl = L.ctl;
     // pieces: code vectors that lie wholly inside the catalogue, or items whose rows take several (the host sees to it: one at least)
-    const uint32_t total = (uint32_t)(M <= 16 ? (a.N * M) / 16 : a.N), last = total - 1, n_scan = total * IPV;
+    const uint32_t total = (uint32_t)(P <= 16 ? (a.N * P) / 16 : a.N), last = total - 1, n_scan = total * IPV;
     // unit i: a piece per lane, what wave i % NW takes of step i / NW.  (Two pieces to a unit: 50M items, m = 8, 71.1 -> 74.1 us a call, four 100.)
     auto piece_of = [&](uint32_t i) -> uint32_t { return ((i / NW) * (uint32_t)nblk + (uint32_t)blk) * NT + (i % NW) * kWave + (uint32_t)lane; };
     // (loads past the end: a line of the wave's own, not one for thousands of waves that get there together)
@@ -60,59 +72,93 @@ __global__ __launch_bounds__(kBytesThreads) void scan_bytes_kernel(ScanArgs a) {
         }
     };
     // The sample: the first unit of the first `sampling` waves; of long rows, which take longer to score, fewer items.
-    const int sampling = K > 16 ? NW : M == 64 ? NW / 4 : M == 32 ? NW / 2 : NW;
-    // ---- the tables on their way, a wave per split, four entries per lane, then the first codes
+    const int sampling = K > 16 ? NW : P == 64 ? NW / 4 : P == 32 ? NW / 2 : NW;
     const float* const Sq = a.S + (size_t)q * M * b;
-    float v[kSplits][4];
-    if (b == kLutStride && ((uintptr_t)Sq & 15) == 0) {
-#pragma unroll
-        for (int i = 0; i < kSplits; ++i) {
-            const int k = wave + i * NW;
-            const float4 x = reinterpret_cast<const float4*>(Sq)[(k < M ? k : 0) * kWave + lane];
-            v[i][0] = x.x; v[i][1] = x.y; v[i][2] = x.z; v[i][3] = x.w;
-        }
-    } else {
-#pragma unroll
-        for (int i = 0; i < kSplits; ++i)
-#pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                const int k = wave + i * NW, j = lane * 4 + c;
-                v[i][c] = (k < M && j < b) ? Sq[k * b + j] : 0.0f;   // (sub-ids beyond the alphabet score 0)
-            }
-    }
     uint32_t w[2][4 * VPI], unit[2] = {(uint32_t)wave, 0};
-    fetch(unit[0], w[0]);
-    for (int i = tid; i < kBins; i += NT) L.hist[i] = 0;
-    if (tid == 0) { ctl->shared_floor = -__builtin_inff(); ctl->ncand = 0; ctl->next_unit = 2 * NW; }
-    stamp<STAMP>(rec, kStampRequested, lane);
-    // a split's largest entry, and how far below it the best of the middle lane's entries lies: about a sixth of all lie less far.  (A mean would
-    // be carried away by one masked entry.)
-    {
-        float mx[kSplits];
-        uint32_t image[kSplits], at[kSplits];
-        const int lanes = (b + 3) / 4, want = lanes / 2 > 0 ? lanes / 2 : 1;
+    // a split's largest entry, and how far below it the best of the middle lane's entries lies: about a sixth of all lie less far (a lane having four).  (A
+    // mean would be carried away by one masked entry.)
+    const auto clear = [&]() {
+        for (int i = tid; i < kBins; i += NT) L.hist[i] = 0;
+        if (tid == 0) { ctl->shared_floor = -__builtin_inff(); ctl->ncand = 0; ctl->next_unit = 2 * NW; }
+        stamp<STAMP>(rec, kStampRequested, lane);
+    };
+    auto middle = [&](const uint32_t image, int want) -> float {   // the want-th smallest image of a float >= 0, to an eighth of itself
+        uint32_t at = 0;
 #pragma unroll
-        for (int i = 0; i < kSplits; ++i) {
-            const int k = wave + i * NW;
-            if (k < M) reinterpret_cast<float4*>(lut)[k * kWave + lane] = make_float4(v[i][0], v[i][1], v[i][2], v[i][3]);
-            const float best = fmaxf(fmaxf(v[i][0], v[i][1]), fmaxf(v[i][2], v[i][3]));
-            float mn = best;
-            mx[i] = best;
-            wave_minmax(mn, mx[i]);
-            const float below = mx[i] - best;                  // (>= 0, or NaN)
-            image[i] = (lane < lanes && below >= 0.0f) ? __float_as_uint(below) : 0x7F800000u;
-            at[i] = 0;
-        }
+        for (uint32_t bit = 0x40000000u; bit >= 0x200000u; bit >>= 1)
+            if (__popcll(__ballot(image < (at | bit))) < want) at |= bit;
+        return __uint_as_float(at + 0x100000u);
+    };
+    if constexpr (CW == 1) {
+        // ---- the tables on their way, a wave per split, four entries per lane, then the first codes
+        float v[kSplits][4];
+        if (b == kLutStride && ((uintptr_t)Sq & 15) == 0) {
 #pragma unroll
-        for (uint32_t bit = 0x40000000u; bit >= 0x200000u; bit >>= 1)   // the want-th smallest, to an eighth of itself
+            for (int i = 0; i < kSplits; ++i) {
+                const int k = wave + i * NW;
+                const float4 x = reinterpret_cast<const float4*>(Sq)[(k < M ? k : 0) * kWave + lane];
+                v[i][0] = x.x; v[i][1] = x.y; v[i][2] = x.z; v[i][3] = x.w;
+            }
+        } else {
 #pragma unroll
             for (int i = 0; i < kSplits; ++i)
-                if (__popcll(__ballot(image[i] < (at[i] | bit))) < want) at[i] |= bit;
 #pragma unroll
-        for (int i = 0; i < kSplits; ++i) {
-            const int k = wave + i * NW;
-            if (lane == 0 && k < M) { largest[k] = mx[i]; spreads[k] = __uint_as_float(at[i] + 0x100000u); }
+                for (int c = 0; c < 4; ++c) {
+                    const int k = wave + i * NW, j = lane * 4 + c;
+                    v[i][c] = (k < M && j < b) ? Sq[k * b + j] : 0.0f;   // (sub-ids beyond the alphabet score 0)
+                }
         }
+        fetch(unit[0], w[0]);
+        clear();
+        {
+            float mx[kSplits];
+            uint32_t image[kSplits], at[kSplits];
+            const int lanes = (b + 3) / 4, want = lanes / 2 > 0 ? lanes / 2 : 1;
+#pragma unroll
+            for (int i = 0; i < kSplits; ++i) {
+                const int k = wave + i * NW;
+                if (k < M) reinterpret_cast<float4*>(lut)[k * kWave + lane] = make_float4(v[i][0], v[i][1], v[i][2], v[i][3]);
+                const float best = fmaxf(fmaxf(v[i][0], v[i][1]), fmaxf(v[i][2], v[i][3]));
+                float mn = best;
+                mx[i] = best;
+                wave_minmax(mn, mx[i]);
+                const float below = mx[i] - best;                  // (>= 0, or NaN)
+                image[i] = (lane < lanes && below >= 0.0f) ? __float_as_uint(below) : 0x7F800000u;
+                at[i] = 0;
+            }
+#pragma unroll
+            for (uint32_t bit = 0x40000000u; bit >= 0x200000u; bit >>= 1)   // the want-th smallest, to an eighth of itself
+#pragma unroll
+                for (int i = 0; i < kSplits; ++i)
+                    if (__popcll(__ballot(image[i] < (at[i] | bit))) < want) at[i] |= bit;
+#pragma unroll
+            for (int i = 0; i < kSplits; ++i) {
+                const int k = wave + i * NW;
+                if (lane == 0 && k < M) { largest[k] = mx[i]; spreads[k] = __uint_as_float(at[i] + 0x100000u); }
+            }
+        }
+    } else {
+        // ---- the query's m x b table as it lies in memory, behind the first codes; then a split's entries by kParts waves
+        const int entries = M * b;
+        fetch(unit[0], w[0]);
+        if ((entries & 3) == 0 && ((uintptr_t)Sq & 15) == 0) {
+#pragma unroll 4
+            for (int e = tid; e < entries >> 2; e += NT) reinterpret_cast<float4*>(lut)[e] = reinterpret_cast<const float4*>(Sq)[e];
+        } else {
+#pragma unroll 4
+            for (int e = tid; e < entries; e += NT) lut[e] = Sq[e];
+        }
+        clear();
+        __syncthreads();
+        const int k = wave / kParts, j0 = wave % kParts * kWave + lane;
+        float best = -__builtin_inff();
+        for (int j = j0; j < b; j += kParts * kWave) best = fmaxf(best, lut[k * b + j]);
+        float mn = best, mx = best;
+        wave_minmax(mn, mx);
+        const float below = mx - best;                         // (>= 0, or NaN)
+        const int lanes = b - wave % kParts * kWave < kWave ? b - wave % kParts * kWave : kWave;
+        const float spread = middle(j0 < b && below >= 0.0f ? __float_as_uint(below) : 0x7F800000u, lanes / 2 > 0 ? lanes / 2 : 1);
+        if (lane == 0) { largest[wave] = mx; spreads[wave] = spread; }
     }
     __syncthreads();
     stamp<STAMP>(rec, kStampTables, lane);
@@ -120,10 +166,22 @@ __global__ __launch_bounds__(kBytesThreads) void scan_bytes_kernel(ScanArgs a) {
     fetch(unit[1], w[1]);
 
     WaveTopK top{L.lists + (size_t)wave * a.cap, a.cap, K, 0, 0, 0ull, -__builtin_inff()};
+    auto largest_of = [&](int k) -> float {
+        float l = largest[k * kParts];
+#pragma unroll
+        for (int i = 1; i < kParts; ++i) l = fmaxf(l, largest[k * kParts + i]);
+        return l;
+    };
     // ---- counts: 255 steps below every split's largest entry, what lies deeper counts as that
     float step, inv, span;                                     // span: what the splits' spreads add up to
     {
-        const float l = lane < M ? largest[lane < M ? lane : 0] : 0.0f, s = lane < M ? spreads[lane < M ? lane : 0] : 0.0f;
+        const float l = lane < M ? largest_of(lane < M ? lane : 0) : 0.0f;
+        float s = 0.0f;
+        if (lane < M) {
+            s = l - largest[lane * kParts] + spreads[lane * kParts];
+#pragma unroll
+            for (int i = 1; i < kParts; ++i) s = fminf(s, l - largest[lane * kParts + i] + spreads[lane * kParts + i]);
+        }
         float none = 0.0f, widest = s;
         wave_minmax(none, widest);
         span = wave_sum_f32(s);
@@ -131,14 +189,30 @@ __global__ __launch_bounds__(kBytesThreads) void scan_bytes_kernel(ScanArgs a) {
         inv = 1.0f / step;
         if (!(inv < 1.0e30f) || !(step < 1.0e30f) || __ballot(!(fabsf(l) < 1.0e30f)) != 0) { inv = 0.0f; step = 0.0f; }   // degenerate: every item is scored
     }
-    for (int i = tid; i < M * kWave; i += NT) {
-        const float4 x = reinterpret_cast<const float4*>(lut)[i];
-        const float base = largest[i / kWave] - 255.0f * step, e[4] = {x.x, x.y, x.z, x.w};
+    const int words = count_stride / 4;                        // of a split's counts
+    for (int i = tid; i < M * words; i += NT) {
+        const int k = i / (CW == 1 ? kWave : words), j = (i - k * words) * 4;
+        const float base = largest_of(k) - 255.0f * step;
+        float e[4];
+        if constexpr (CW == 1) {
+            const float4 x = reinterpret_cast<const float4*>(lut)[i];
+            e[0] = x.x; e[1] = x.y; e[2] = x.z; e[3] = x.w;
+        } else {
+#pragma unroll
+            for (int c = 0; c < 4; ++c) e[c] = lut[k * b + (j + c < b ? j + c : b - 1)];
+        }
         uint32_t word = 0;
 #pragma unroll
         for (int c = 0; c < 4; ++c) word |= (uint32_t)fminf(fmaxf(ceilf((e[c] - base) * inv + 2.5e-4f), 0.0f), 255.0f) << (8 * c);
         reinterpret_cast<uint32_t*>(counts)[i] = word;
     }
+    // exact scores of a piece
+    auto score = [&](const uint32_t (&w)[4 * VPI], float (&sc)[IPV]) {
+        if constexpr (CW == 2 && P > 16) sc[0] = score_wide16<M>(lut, stride, w);
+        else if constexpr (CW == 2) score_vector16<M>(lut, stride, w, sc);
+        else if constexpr (M > 16) sc[0] = score_wide<M>(lut, w);
+        else score_vector<M>(lut, w, sc);
+    };
     float hlo, hscale;
     {
         // ---- the sample's items, exactly: a histogram over their range gives the first floor (it lives on: every score that enters
@@ -147,10 +221,7 @@ __global__ __launch_bounds__(kBytesThreads) void scan_bytes_kernel(ScanArgs a) {
         auto finite = [](float x) { return fminf(fmaxf(x, -1.0e30f), 1.0e30f); };   // (a range that buckets can divide)
         const uint32_t p = piece_of(unit[0]);
         const bool mine = wave < sampling && p <= last;
-        if (wave < sampling) {
-            if constexpr (M > 16) sc[0] = score_wide<M>(lut, w[0]);
-            else score_vector<M>(lut, w[0], sc);
-        }
+        if (wave < sampling) score(w[0], sc);
         if (mine) {
 #pragma unroll
             for (int e = 0; e < IPV; ++e) { mn = fminf(mn, finite(sc[e])); mx = fmaxf(mx, finite(sc[e])); }
@@ -234,7 +305,7 @@ __global__ __launch_bounds__(kBytesThreads) void scan_bytes_kernel(ScanArgs a) {
     // monotone in each term), so no entry that matters is larger than that.
     ByteBounds bounds;
     {
-        const float l = lane < M ? largest[lane < M ? lane : 0] : 0.0f, sum_max = wave_sum_f32(l), depth = sum_max - top.floor_ge;
+        const float l = lane < M ? largest_of(lane < M ? lane : 0) : 0.0f, sum_max = wave_sum_f32(l), depth = sum_max - top.floor_ge;
         // what fp32 chains of M additions (scores, sums of bases) can be off by
         const float slack = 4.0f * (float)(M + 1) * 5.9604645e-8f * wave_sum_f32(lane < M ? fmaxf(fabsf(l), fabsf(l - depth)) + 255.0f * step : 0.0f);
         bounds.off = sum_max - (float)M * 255.0f * step + slack;
@@ -265,13 +336,17 @@ __global__ __launch_bounds__(kBytesThreads) void scan_bytes_kernel(ScanArgs a) {
             any = 0;
 #pragma unroll
             for (int j = 0; j < VPI; ++j) {
-                uint32_t x[16];
+                constexpr int kIds = 16 / CW;                  // of a vector
+                uint32_t x[kIds];
 #pragma unroll
-                for (int c = 0; c < 16; ++c) x[c] = counts[(j * 16 + c) % M * kLutStride + ((w[4 * j + c / 4] >> (c % 4 * 8)) & 0xFFu)];
+                for (int c = 0; c < kIds; ++c) {
+                    const uint32_t word = w[4 * j + c * CW / 4], id = CW == 2 ? (c & 1 ? word >> 16 : word & 0xFFFFu) : (word >> (c % 4 * 8)) & 0xFFu;
+                    x[c] = counts[(j * kIds + c) % M * count_stride + id];
+                }
 #pragma unroll
-                for (int c = 0; c < 16; ++c) {
-                    const int e = M > 16 ? 0 : c / M;
-                    sum[e] = (M > 16 ? j == 0 && c == 0 : c % M == 0) ? x[c] : sum[e] + x[c];
+                for (int c = 0; c < kIds; ++c) {
+                    const int e = P > 16 ? 0 : c / M;
+                    sum[e] = (P > 16 ? j == 0 && c == 0 : c % M == 0) ? x[c] : sum[e] + x[c];
                 }
             }
 #pragma unroll
@@ -285,10 +360,7 @@ __global__ __launch_bounds__(kBytesThreads) void scan_bytes_kernel(ScanArgs a) {
         }
         ++in_a_row;
         float sc[IPV];
-        if (hit) {                                             // (the lookups of a few lanes collide less)
-            if constexpr (M > 16) sc[0] = score_wide<M>(lut, w);
-            else score_vector<M>(lut, w, sc);
-        }
+        if (hit) score(w, sc);                                 // (the lookups of a few lanes collide less)
 #pragma unroll
         for (int e = 0; e < IPV; ++e) {
             const bool take = hit && sc[e] >= top.floor_ge;
@@ -319,17 +391,18 @@ __global__ __launch_bounds__(kBytesThreads) void scan_bytes_kernel(ScanArgs a) {
     };
     stream(std::true_type());
     stream(std::false_type());
-    if constexpr (M <= 16) {
-        // the fewer than 16 / M items after the last whole code vector, one per lane of one wave
+    if constexpr (P <= 16) {
+        // the fewer than 16 / P items after the last whole code vector, one per lane of one wave
         if (blk == 0 && wave == 0) {
             const uint32_t item = n_scan + (uint32_t)lane;
             float sc = 0.0f;
             bool take = false;
             if (item < (uint32_t)a.N) {
-                const uint8_t* const row = a.codes + (size_t)item * M;
-                sc = lut[row[0]];
+                const uint8_t* const row = a.codes + (size_t)item * P;
+                auto id = [&](int k) -> uint32_t { return CW == 2 ? (uint32_t)reinterpret_cast<const uint16_t*>(row)[k] : (uint32_t)row[k]; };
+                sc = lut[id(0)];
 #pragma unroll
-                for (int k = 1; k < M; ++k) sc = sc + lut[k * kLutStride + row[k]];
+                for (int k = 1; k < M; ++k) sc = sc + lut[k * stride + id(k)];
                 take = sc >= top.floor_ge;
             }
             const uint64_t mask = __ballot(take);

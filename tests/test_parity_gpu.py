@@ -351,6 +351,29 @@ def test_single_query_by_one_byte_bounds(pq, oracle, m, b, K):
         pq.pq_measure_force_general(prev)
 
 
+@pytest.mark.parametrize("m,b,K", [(4, 5, 3), (4, 1501, 10), (4, 5000, 100), (8, 300, 17), (8, 1024, 10), (8, 70, 256), (16, 257, 10), (16, 1000, 40)])
+def test_single_query_of_two_byte_sub_ids_by_one_byte_bounds(pq, oracle, m, b, K):
+    rng = np.random.default_rng(100 * m + b)
+    prev = pq.pq_measure_force_general(1024)
+    try:
+        for N in (max(K, 4), 300 + K, 70_001, 256 * 1024 * 2 + 64 * 17 + 1):
+            assert pq.pq_measure_plan("scan16", N, 1, m, b, K)["field_bits"] == 8
+            codes = rng.integers(0, b, (N, m), dtype=np.uint16)
+            codes[N // 2:N // 2 + 40] = codes[:min(40, N - N // 2)]
+            S = rng.standard_normal((1, m, b), dtype=np.float32)
+            assert_same_topk_u16(pq, oracle, codes, S, K, f"normal {N}")
+            if N != 70_001:
+                continue
+            masked, far = S.copy(), S.copy()
+            masked[0, 1, :b // 3] = -1e9
+            masked[0, m - 1, b // 2] = -np.inf
+            far[0, 2, 1] = 1e4
+            for name, T in (("masked", masked), ("far entry", far), ("ties", np.round(S)), ("zeros", 0 * S), ("offset", S + np.float32(1e7))):
+                assert_same_topk_u16(pq, oracle, codes, T.astype(np.float32), K, f"{name} {N}")
+    finally:
+        pq.pq_measure_force_general(prev)
+
+
 # ... several of them, and any number of results, where two-byte sub-ids' tables leave no room for lists per wave: one to many
 # workgroups per query, tables up to the largest that fit
 @pytest.mark.parametrize("N,m,b,B,K", [(6_400_003, 4, 7297, 2, 421), (300_001, 8, 4096, 64, 250), (150_003, 4, 8300, 200, 120), (60_001, 16, 2048, 300, 512),
