@@ -213,9 +213,11 @@ __global__ __launch_bounds__(NT, M <= 16 ? 8 : 4) void filter_prepare_kernel(Fil
     float* piece = reinterpret_cast<float*>(n_found + 1);     // [pieces of the tables][3]: max, min, sum
     const float* Sq = a.S + (size_t)q * M * b;
 
-    // ---- the sample's rows: units spread evenly over the catalogue (or the list), the parts' and rounds' interleaved
+    // ---- the sample's rows: runs of units spread evenly over the catalogue (or the list), the parts' and rounds' interleaved.  (Runs of one, a line of memory
+    // for every lane: 1024 queries, m = 8, four rounds, 25.7 us, of four 19.0; 32 queries, eight parts of three rounds 13.0 and 10.1; 64, four parts 7.9 and 6.4.)
     constexpr bool kByItem = SUB || P > 16;
     constexpr int kLoads = SUB ? Sh::kSampleItems : Sh::kSampleUnits;
+    constexpr uint32_t kRun = SUB || P > 32 ? 1u : P == 32 ? 2u : 4u;   // units that follow each other in memory, 64 bytes: a line's neighbours come with it
     const uint32_t total = (uint32_t)(kByItem ? a.N : (a.N * P) / 16);
     const uint32_t n_sample = (uint32_t)a.sample < total ? (uint32_t)a.sample : total, every = total / n_sample;
     auto fetch = [&](int round, uint32_t (&w)[Sh::kSampleWords]) {
@@ -224,7 +226,8 @@ __global__ __launch_bounds__(NT, M <= 16 ? 8 : 4) void filter_prepare_kernel(Fil
 #pragma unroll
         for (int u = 0; u < kLoads; ++u) {
             uint32_t i = (uint32_t)(u * NT + tid);
-            i = (i < n_sample ? i : n_sample - 1) * every + shift;
+            i = i < n_sample ? i : n_sample - 1;
+            i = (i & ~(kRun - 1u)) * every + shift * kRun + (i & (kRun - 1u));   // (within the units: shift < every, or 0 where every is 1)
             if constexpr (SUB) {
                 uint32_t item = (uint32_t)a.subset[i];
                 item = item < a.n_items ? item : a.n_items - 1;
