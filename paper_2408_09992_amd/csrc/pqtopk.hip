@@ -842,14 +842,17 @@ void plan_filter(ScanPlan& p, long long N, int B, int m, int K, bool subset, int
     // The sample: n items cost n * m lookups of 4 bytes, and (K / n) of the catalogue then passes the first floor and is
     // scored from device memory, an eighth as fast: least together at about 5 sqrt(K N), for few results of many queries 8 (300 queries,
     // 200,000 items, m = 4, K = 12 41 and 29 us; 478, 115,861, m = 8, K = 11 48 and 42; 300, 300,000, K = 26 52 and 56).  Where the workgroups
-    // of a query share their floors those rise fast by themselves.
+    // of a query share their floors those rise fast by themselves.  Over many items 7, since the sample reads runs of memory (calls with 5 and 7, us: 50M, m = 8, 32, K = 10 204.6 and
+    // 200.6, 5M, 20 37.9 and 37.6, m = 16, 16 44.5 and 44.0; 1.28M, m = 8, 64 31.3 and 31.9; m = 64, 6M, 8 157.7 and 159.3).
     p.f_share = shares(nb);
     const long long items_per_round = (long long)p.f_sample * N / units;
-    long long want = (long long)((K <= 16 && B > 128 && !subset && !p.f_share ? 8.0 : 5.0) * sqrt((double)K * (double)N)) / items_per_round;
+    long long want = (long long)((K <= 16 && B > 128 && !subset && !p.f_share ? 8.0 : N >= 2500000 && m <= 16 && !subset ? 7.0 : 5.0) * sqrt((double)K * (double)N)) / items_per_round;
     // (... but at m = 32, where an exact score costs most, not within so short a time, if the catalogue is worth the sample: one round and four, 500,000 items, 480 queries,
     // K = 10 428 and 301, 800,000, 900, K = 20 1169 and 928, K = 30 (16-bit fields) 1139 and 1087; 200,000, 70, K = 100 66 and 80.  m = 16 with bytes alone, one and two: 900,
     // 500,000, K = 5 231 and 212)
-    const long long few_rounds = K <= 32 ? (m == 16 && !fine && !w16 && !subset ? 2 : 1) : m == 4 ? 4 : m == 8 ? 2 : 1;
+    // Many results with shared floors, rounds of 1024 threads: m = 4, four and six, 2M, 300, K = 100 97.4 and 96.3; m = 8, two and three, 1.28M, 1024, K = 100 266.2 and 263.9, 700,000, 512, K = 64
+    // 106.8 and 104.8 (four: 262.5 beside 261.3 with three); m = 16, one and three, 1M, 300, K = 100 190.6 and 181.9, 600,000, 600, K = 200 251.6 and 241.1.
+    const long long few_rounds = K <= 32 ? (m == 16 && !fine && !w16 && !subset ? 2 : 1) : m == 4 ? 6 : m == 8 || m == 16 ? 3 : 1;
     const long long most_rounds = (nb > 16 ? 4 : m == 32 ? std::min<long long>(4, 1 + N / 170000) : few_rounds) * (kFilterThreads / p.f_prepare);
     if (p.f_share && want > most_rounds) want = most_rounds;
     if (want > N / 8 / items_per_round) want = N / 8 / items_per_round;
