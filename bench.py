@@ -501,9 +501,9 @@ def rules_mode(args):
         us, same = _two_sides(torch, pq, _prepared(torch, pq, W, kind, N, B, m, b, K), masks)
         taken = pq.pq_measure_plan(kind, N, B, m, b, K)
         rows.append({"rule": rule, "kind": kind, "N": N, "B": B, "m": m, "b": b, "K": K, names[0]: us[0], names[1]: us[1],
-                     "taken": taken["kernel"], "groups": taken["groups"], "same": same})
+                     "taken": "bytes" if B == 1 and taken["kernel"] == "general" and taken["field_bits"] == 8 else taken["kernel"], "groups": taken["groups"], "same": same})
         print(f"{rule:10s} {kind:7s} N={N:9d} B={B:4d} m={m:2d} b={b:4d} K={K:3d}  {names[0]} {us[0]:8.1f}  {names[1]} {us[1]:8.1f}  "
-              f"takes {taken['kernel']} ({taken['groups']})  same {same}", file=sys.stderr, flush=True)
+              f"takes {rows[-1]['taken']} ({taken['groups']})  same {same}", file=sys.stderr, flush=True)
 
     # one query, scanned in segments (mask bit 6) or by the general kernel (bit 0): lines in N and K
     for kind, m, b, Ns, Ks in (("scan", 4, 256, (12_000_000, 16_000_000, 18_000_000, 40_000_000), (10, 256, 257)),
@@ -515,6 +515,13 @@ def rules_mode(args):
         for N in Ns:
             for K in Ks:
                 row("segments", kind, N, 1, m, b, K, (64, 1), ("segments", "general"))
+    # one query by one-byte bounds (mask bit 10) or without (bit 9): lines in bytes of codes
+    for kind, m, b, lines in (("scan", 4, 256, ((10, 4.4e7), (100, 7.0e7))), ("scan", 8, 256, ((10, 5.2e7), (100, 1.1e8), (256, 1.4e8), (512, 1.8e8))),
+                              ("scan", 16, 256, ((10, 8.8e7), (100, 1.1e8), (256, 1.4e8))), ("scan", 32, 256, ((10, 8.0e7), (100, 1.5e8))), ("scan", 64, 256, ((10, 3.6e8), (100, 4.5e8))),
+                              ("scan16", 4, 1500, ((10, 1.1e8),)), ("scan16", 8, 1024, ((10, 2.0e8), (100, 2.0e8))), ("scan16", 16, 300, ((10, 2.0e8),)), ("scan16", 8, 2500, ((10, 4.5e8),))):
+        for K, line in lines:
+            for f in (0.5, 0.8, 1.25, 2.0):
+                row("bytes", kind, int(f * line / (m * (2 if kind == "scan16" else 1))), 1, m, b, K, (1024, 512), ("bytes", "without"))
     # batches by bounds (mask bit 4) or with every score computed (bit 3): lines in lookups ...
     for kind, m, b, K, least, Bs in (("scan", 4, 256, 10, 6.0e7, (4, 64)), ("scan", 8, 256, 10, 6.5e7, (4, 64)), ("scan", 8, 256, 10, 9.75e7, (2,)),
                                      ("scan", 16, 256, 10, 1.0e8, (4, 64)), ("scan", 32, 256, 10, 1.6e8, (8, 64)), ("scan", 32, 256, 100, 2.1e8, (8,)),

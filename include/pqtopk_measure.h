@@ -104,8 +104,8 @@ int pq_measure_sync_variant(int variant, void* scratch, size_t scratch_bytes, vo
  * candidate list is never left to one workgroup per query but for want of more; bit 6: a single query over a catalogue too
  * long for the short kernel is always scanned in segments; bit 7: batches scanned by upper bounds are by pairs of lanes wherever
  * these fit (lists: m = 4); bit 8: a batch takes the short kernels for two queries per workgroup wherever they fit (bit 0 keeps
- * it off these too); bit 9: a single query is never scanned by one-byte bounds; bit 10: it is wherever that fits (bit 0 keeps it off
- * too).
+ * it off these too); bit 9: a single query is never scanned by one-byte bounds; bit 10: it is wherever that fits (bits 0 and 6 keep it
+ * off too).
  * 0 restores the library's own choice.
  * Process-wide, takes effect for calls made after it returns (workspace sizes depend on bits 0 and 3 to 10).  Returns the
  * previous mask.

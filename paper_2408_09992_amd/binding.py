@@ -451,7 +451,8 @@ def pq_measure_force_general(mask: int) -> int:
     """Bit 0: scans avoid the short kernel; bit 1: folds avoid the small-K fold; bit 2: Eq. 4 avoids the matrix cores;
     bit 3: batches are not scanned by upper bounds; bit 4: they are, whatever their size; bit 5: candidate lists are spread
     over workgroups; bit 6: longer single queries are scanned in segments (workspace sizes depend on these four); bit 7: scans by bounds run by pairs of lanes wherever these fit; bit 8: batches take two queries
-    per workgroup wherever that fits; 0: the library's choice.  Returns the previous mask."""
+    per workgroup wherever that fits; bit 9: a single query is never scanned by one-byte bounds; bit 10: it is wherever that fits; 0: the
+    library's choice.  Returns the previous mask."""
     return int(lib().pq_measure_force_general(int(mask)))
 
 

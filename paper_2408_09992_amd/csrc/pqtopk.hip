@@ -451,7 +451,7 @@ ScanPlan make_plan(long long N, int B, int m, int K, bool generic = false, int c
     }
     // Long catalogues of a single query: one-byte bounds first.
     p.bytes = false;
-    if (!(without & kNoBytes) && B == 1 && p.vec && !generic && m >= 4 && !(g_force_general.load(std::memory_order_relaxed) & (1 | 512)) &&
+    if (!(without & kNoBytes) && B == 1 && p.vec && !generic && m >= 4 && !(g_force_general.load(std::memory_order_relaxed) & (1 | 64 | 512)) &&
         (bytes_pay(N, m, b, K, cw) || (g_force_general.load(std::memory_order_relaxed) & 1024))) {
         const size_t dyn = scan_lds_bytes(0, p.cap, p.candmax, K, kMaxWaves), tables = bytes_table_bytes(m, b, cw), all = dyn + tables + 2 * kMaxWaves * sizeof(float) + (m > kMaxWaves ? 2 * (m - kMaxWaves) * sizeof(float) : 0);
         if (all + 64 <= kMaxLdsBytes) {
