@@ -47,6 +47,7 @@ __global__ __launch_bounds__(kBytesThreads) void scan_bytes_kernel(ScanArgs a) {
     __shared__ __align__(16) float lut_static[CW == 1 ? M * kLutStride : 4];
     __shared__ __align__(16) uint8_t counts_static[CW == 1 ? M * kLutStride : 4];
     __shared__ float largest[M * kParts], spreads[M * kParts];
+    __shared__ int crowd;                                      // scores in the bucket of the sample's K-th best, when it was found
     extern __shared__ __align__(16) unsigned char smem[];
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid / kWave);
     const int q = blockIdx.y, nblk = gridDim.x, blk = blockIdx.x, K = a.K, b = a.b;
@@ -235,7 +236,10 @@ __global__ __launch_bounds__(kBytesThreads) void scan_bytes_kernel(ScanArgs a) {
         __syncthreads();
         if (wave == 0) {
             find_cut(L.hist, K, ctl, lane);
-            if (lane == 0) ctl->shared_floor = next_up(ctl->cut);
+            if (lane == 0) {
+                ctl->shared_floor = next_up(ctl->cut);
+                crowd = (int)L.hist[ctl->bstar];
+            }
         }
         __syncthreads();
         // A score far from the others (an item with a masked sub-id, at -1e9) stretches the range until the buckets tell nothing apart: while the K-th
@@ -249,8 +253,9 @@ __global__ __launch_bounds__(kBytesThreads) void scan_bytes_kernel(ScanArgs a) {
         bool narrowed = hscale * span < 128.0f;                // (buckets too wide for floors to rise by)
 #pragma unroll 1
         for (int pass = 0; pass < 8; ++pass) {
+            // (one decision: waves that leave count into the histogram at once, so nobody looks there)
             const int bstar = ctl->bstar;
-            if (__builtin_expect((int)L.hist[bstar] <= 2 * left + kWave || !(per > 0.0f), 1)) break;
+            if (__builtin_expect(crowd <= 2 * left + kWave || !(per > 0.0f), 1)) break;
             narrowed = true;
             __syncthreads();
 #pragma unroll
@@ -274,7 +279,10 @@ __global__ __launch_bounds__(kBytesThreads) void scan_bytes_kernel(ScanArgs a) {
             for (int e = 0; e < IPV; ++e)
                 if (in[e]) atomicAdd(&L.hist[bucket_of(sc[e], lo, per)], 1u);
             __syncthreads();
-            if (wave == 0) find_cut(L.hist, left, ctl, lane);
+            if (wave == 0) {
+                find_cut(L.hist, left, ctl, lane);
+                if (lane == 0) crowd = (int)L.hist[ctl->bstar];
+            }
             __syncthreads();
         }
         const float cut = ctl->cut;                            // (K of the sample's scores exceed it)

@@ -1,0 +1,121 @@
+"""The scan by one-byte bounds on the CPU, one workgroup, waves far out of step (no GPU): what no barrier orders gives other results or waves that
+wait at different barriers."""
+import os
+import shutil
+import subprocess
+
+import numpy as np
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2408_09992_amd", "csrc")
+PARTS = ("common.hpp", "topk_parts.hpp", "scan_single.hpp", "scan_bytes.hpp")
+
+MAIN = r"""
+#include "workgroup_on_cpu.hpp"
+namespace pqk {
+#include "common.hpp"
+#include "topk_parts.hpp"
+#include "scan_single.hpp"
+#include "scan_bytes.hpp"
+}
+template <int M, int CW>
+bool go(const pqk::ScanArgs& a, const std::vector<int>& order) { return emu::run(pqk::kBytesThreads, order, [&]() { pqk::scan_bytes_kernel<M, CW>(a); }); }
+int main(int argc, char** argv) {   // file of codes, of scores, of keys; m, bytes of a sub-id, b, N, K, capacity of a list, of the candidates; waves in order
+    auto read = [](const char* name) {
+        FILE* f = fopen(name, "rb");
+        fseek(f, 0, SEEK_END);
+        std::vector<uint4> v(ftell(f) / 16 + 1);
+        rewind(f);
+        if (fread(v.data(), 1, v.size() * 16, f) == 0) abort();
+        fclose(f);
+        return v;
+    };
+    const std::vector<uint4> codes = read(argv[1]), scores = read(argv[2]);
+    pqk::ScanArgs a{};
+    a.codes = reinterpret_cast<const uint8_t*>(codes.data());
+    a.S = reinterpret_cast<const float*>(scores.data());
+    const int cw = atoi(argv[5]);
+    a.m = atoi(argv[4]); a.b = atoi(argv[6]); a.N = atoll(argv[7]); a.K = atoi(argv[8]); a.cap = atoi(argv[9]); a.candmax = atoi(argv[10]);
+    std::vector<uint64_t> keys(a.K);
+    a.ws_keys = keys.data();
+    a.n_items = (uint32_t)a.N;
+    std::vector<int> order;
+    for (int i = 11; i < argc; ++i) order.push_back(atoi(argv[i]));
+    const bool ok = cw == 2 ? go<8, 2>(a, order) : a.m == 8 ? go<8, 1>(a, order) : go<64, 1>(a, order);
+    FILE* f = fopen(argv[3], "wb");
+    fwrite(keys.data(), 8, keys.size(), f);
+    fclose(f);
+    return ok ? 0 : 1;
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def program(tmp_path_factory):
+    gxx = shutil.which("g++")
+    if gxx is None:
+        pytest.skip("needs g++")
+    at = tmp_path_factory.mktemp("waves")
+    for name in PARTS:
+        with open(os.path.join(CSRC, name)) as f:
+            text = f.read()
+        text = text.replace("extern __shared__ __align__(16) unsigned char smem[];", "unsigned char* const smem = emu::lds;")
+        (at / name).write_text(text)
+    (at / "main.cpp").write_text(MAIN)
+    build = subprocess.run([gxx, "-std=c++17", "-O1", "-fno-strict-aliasing", "-ffp-contract=off", "-w", "-I", str(at), "-I", os.path.join(ROOT, "tests"), str(at / "main.cpp"), "-o", str(at / "main")],
+                           capture_output=True, text=True)
+    assert build.returncode == 0, build.stderr[-4000:]
+    return at
+
+
+def scan(at, codes, S, K, order):
+    """the workgroup's K best: (ids, scores)"""
+    codes.tofile(at / "codes")
+    S.astype(np.float32).tofile(at / "scores")
+    cap = 1
+    while cap < K + 64:
+        cap *= 2
+    run = subprocess.run([str(at / "main"), str(at / "codes"), str(at / "scores"), str(at / "keys"), str(codes.shape[1]), str(codes.dtype.itemsize), str(S.shape[1]), str(codes.shape[0]), str(K),
+                          str(max(cap, 128)), "512"] + [str(w) for w in order], capture_output=True, text=True, timeout=300)
+    assert run.returncode == 0, (run.stdout + run.stderr)[-2000:]
+    keys = np.fromfile(at / "keys", dtype=np.uint64)
+    high, low = (keys >> np.uint64(32)).astype(np.uint32), (keys & np.uint64(0xFFFFFFFF)).astype(np.uint32)
+    return (~low).astype(np.int32), np.where(high >> 31, high ^ np.uint32(0x80000000), ~high).astype(np.uint32).view(np.float32)
+
+
+def expected(codes, S, K):
+    score = S[0, codes[:, 0]].astype(np.float32)
+    for k in range(1, codes.shape[1]):
+        score = score + S[k, codes[:, k]]
+    ids = np.argsort(-score, kind="stable")[:K]
+    return ids.astype(np.int32), score[ids]
+
+
+# a wave that is late everywhere, the first or the last, and waves front to back
+ORDERS = [list(range(16)), list(range(1, 16)) + [0], list(range(15, -1, -1)), [w for w in range(16) if w != 7] + [7]]
+
+
+def same(at, codes, S, K):
+    ids, sc = expected(codes, S, K)
+    for order in ORDERS:
+        got, got_sc = scan(at, codes, S, K, order)
+        assert np.array_equal(got, ids) and np.array_equal(got_sc, sc), order
+
+
+def near_limit(best, n, seed):
+    """m = 8: the first `best` of the sample's 2048 items and every item behind it share the largest score"""
+    rng = np.random.default_rng(seed)
+    codes = rng.integers(0, 255, (n, 8), dtype=np.uint8)
+    codes[rng.choice(2048, best, replace=False), 0] = 255
+    codes[2048:, 0] = 255
+    S = np.zeros((8, 256), np.float32)
+    S[0] = rng.uniform(0.0, 0.9, 256)
+    S[0, 255] = 1.0
+    return codes, S
+
+
+# the sample's bucket of the K-th best holds as many as are let be, one less and one more: waves that are ahead count into it while others still look at it
+@pytest.mark.parametrize("K,best", [(1, 65), (1, 66), (1, 67), (10, 84)])
+def test_whether_the_sample_is_taken_apart_is_one_decision(program, K, best):
+    same(program, *near_limit(best, 5001, K + best), K)
