@@ -523,6 +523,8 @@ __device__ __forceinline__ void workgroup_select(const ScanLds& L, Ctl* ctl, Wav
     }
     if (!ranked) {
         // too many keys for one ranking (long lists, large K): histogram over the listed keys' own range, or a sort
+        // (every wave has read the others' floors before set_range() writes over them: one that reads late would take what is no floor)
+        __syncthreads();
         float mn = __builtin_inff(), mx = -__builtin_inff();
         for (int t = lane; t < top.cnt; t += kWave) {
             const float v = score_of_key(top.buf[t]);

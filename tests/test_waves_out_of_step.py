@@ -119,3 +119,11 @@ def near_limit(best, n, seed):
 @pytest.mark.parametrize("K,best", [(1, 65), (1, 66), (1, 67), (10, 84)])
 def test_whether_the_sample_is_taken_apart_is_one_decision(program, K, best):
     same(program, *near_limit(best, 5001, K + best), K)
+
+
+# all scores alike: more keys than are ranked at once and no floor, so the lists' own range is taken; the words that gave the floor are written for it
+@pytest.mark.parametrize("m,K", [(8, 32), (8, 100)])
+def test_floor_of_the_waves_lists_is_read_before_it_is_written_over(program, m, K):
+    rng = np.random.default_rng(K)
+    codes = rng.integers(0, 256, (2500, m), dtype=np.uint8)
+    same(program, codes, np.ones((m, 256), np.float32), K)
