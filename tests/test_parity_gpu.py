@@ -331,9 +331,8 @@ def test_single_query_by_one_byte_bounds(pq, oracle, m, b, K):
             codes[N // 2:N // 2 + 40] = codes[:min(40, N - N // 2)]
             S = rng.standard_normal((1, m, b), dtype=np.float32)
             assert_same_topk(pq, oracle, codes, S, K, f"normal {N}")
-            if N < 60_000:
-                continue
-            small = codes[:150_001]
+            if N < 2 * per_step:
+                continue                                       # (shorter: every item is in the sample, and no bound is looked at)
             uneven = S * np.where(np.arange(m) == 1, np.float32(50.0), np.float32(0.02))[None, :, None]
             masked, far, deep = S.copy(), S.copy(), S.copy()
             masked[0, 1, :b // 3] = -1e9
@@ -342,11 +341,35 @@ def test_single_query_by_one_byte_bounds(pq, oracle, m, b, K):
             deep[0, 0, :-1] = -1e9
             for name, T in (("uneven", uneven), ("masked", masked), ("far entry", far), ("one entry of a split counts", deep), ("ties", np.round(S)), ("zeros", 0 * S), ("negative", S - 20),
                             ("offset", S + np.float32(1e7)), ("denormal", (np.abs(S) * np.float32(1e-41)).astype(np.float32))):
-                assert_same_topk(pq, oracle, small, T.astype(np.float32), K, f"{name} {N}")
+                assert_same_topk(pq, oracle, codes, T.astype(np.float32), K, f"{name} {N}")
             infinite = np.where(S > 2.5, np.float32(np.inf), S)   # (the bar above subtracts: the bits alone)
-            ids, sc = run_topk(pq, small, infinite, K)
-            rid, rsc = oracle.score_topk(small, infinite, K)
+            ids, sc = run_topk(pq, codes, infinite, K)
+            rid, rsc = oracle.score_topk(codes, infinite, K)
             assert np.array_equal(ids, rid) and np.array_equal(sc.view(np.uint32), rsc.view(np.uint32)), N
+    finally:
+        pq.pq_measure_force_general(prev)
+
+
+# ... over so many steps that waves which find nothing to dismiss go on without bounds (one far entry; scores that differ in their last bits; nearly all masked), and
+# that scores which rise along the catalogue fill the lists over and over
+@pytest.mark.parametrize("wide,m,b,K", [(False, 8, 256, 100), (False, 64, 256, 10), (True, 8, 300, 40)])
+def test_single_query_by_one_byte_bounds_that_dismiss_nothing(pq, oracle, wide, m, b, K):
+    rng = np.random.default_rng(m + K)
+    N = 42 * 256 * 1024 * (2 if m == 8 and not wide else 1) // (2 if m == 64 else 1) + 64 * 5 + 1
+    same = assert_same_topk_u16 if wide else assert_same_topk
+    codes = rng.integers(0, b, (N, m), dtype=np.uint16 if wide else np.uint8)
+    S = rng.standard_normal((1, m, b), dtype=np.float32)
+    far, deep, rising = S.copy(), S.copy(), S.copy()
+    far[0, 2, 1] = 1e4
+    deep[0, 0, :-1] = -1e9
+    rising[0, 0] = np.arange(b, dtype=np.float32) * 0.5
+    prev = pq.pq_measure_force_general(1024)
+    try:
+        assert pq.pq_measure_plan("scan16" if wide else "scan", N, 1, m, b, K)["field_bits"] == 8
+        for name, T in (("normal", S), ("far entry", far), ("offset", S + np.float32(1e7)), ("one entry of a split counts", deep)):
+            same(pq, oracle, codes, T, K, name)
+        codes[:, 0] = np.arange(N, dtype=np.int64) * b // N
+        same(pq, oracle, codes, rising, K, "rising")
     finally:
         pq.pq_measure_force_general(prev)
 
@@ -356,13 +379,13 @@ def test_single_query_of_two_byte_sub_ids_by_one_byte_bounds(pq, oracle, m, b, K
     rng = np.random.default_rng(100 * m + b)
     prev = pq.pq_measure_force_general(1024)
     try:
-        for N in (max(K, 4), 300 + K, 70_001, 256 * 1024 * 2 + 64 * 17 + 1):
+        for N in (max(K, 4), 300 + K, 70_001, 256 * 1024 * 2 * max(1, 8 // m) + 64 * 17 + 1):
             assert pq.pq_measure_plan("scan16", N, 1, m, b, K)["field_bits"] == 8
             codes = rng.integers(0, b, (N, m), dtype=np.uint16)
             codes[N // 2:N // 2 + 40] = codes[:min(40, N - N // 2)]
             S = rng.standard_normal((1, m, b), dtype=np.float32)
             assert_same_topk_u16(pq, oracle, codes, S, K, f"normal {N}")
-            if N != 70_001:
+            if N <= 70_001:
                 continue
             masked, far = S.copy(), S.copy()
             masked[0, 1, :b // 3] = -1e9

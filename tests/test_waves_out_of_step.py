@@ -127,3 +127,24 @@ def test_floor_of_the_waves_lists_is_read_before_it_is_written_over(program, m, 
     rng = np.random.default_rng(K)
     codes = rng.integers(0, 256, (2500, m), dtype=np.uint8)
     same(program, codes, np.ones((m, 256), np.float32), K)
+
+
+# bounds of every kind, in the stream (six units to a wave), lists that overflow among them
+@pytest.mark.parametrize("m,dtype,b,n,K", [(8, np.uint8, 256, 12_345, 10), (8, np.uint8, 250, 12_345, 512), (64, np.uint8, 256, 6_000, 17), (8, np.uint16, 300, 6_000, 100)])
+def test_bounds_that_are_exact_loose_or_useless(program, m, dtype, b, n, K):
+    rng = np.random.default_rng(m + b + K)
+    codes = rng.integers(0, b, (n, m)).astype(dtype)
+    S = rng.standard_normal((m, b)).astype(np.float32)
+    masked, far, deep = S.copy(), S.copy(), S.copy()
+    masked[1, :b // 3] = -1e9
+    far[2, 1] = 1e4
+    deep[0, :-1] = -1e9
+    for name, T in (("normal", S), ("uneven", S * np.where(np.arange(m) == 1, 50.0, 0.02)[:, None]), ("masked", masked), ("far entry", far), ("one entry of a split counts", deep), ("ties", np.round(S)),
+                    ("zeros", 0 * S), ("negative", S - 20), ("offset", S + np.float32(1e7)), ("heavy tails", np.tan(np.pi * (rng.random(S.shape) - 0.5)))):
+        ids, sc = expected(codes, T.astype(np.float32), K)
+        got, got_sc = scan(program, codes, T, K, rng.permutation(16))
+        assert np.array_equal(got, ids) and np.array_equal(got_sc, sc), name
+    rising = S.copy()
+    rising[0] = np.arange(b) * 0.5
+    codes[:, 0] = np.arange(n) * b // n
+    same(program, codes, rising, K)
