@@ -250,7 +250,8 @@ __global__ __launch_bounds__(kBytesThreads) void scan_bytes_kernel(ScanArgs a) {
         for (int e = 0; e < IPV; ++e) in[e] = mine;
         int left = K;                                          // the left-th best of what is `in` is sought
         float lo = hlo, per = hscale;
-        bool narrowed = hscale * span < 128.0f;                // (buckets too wide for floors to rise by)
+        float floor_ge = next_up(ctl->cut);                    // (K of the sample's scores reach it, and every later one)
+        bool narrowed = per * span < 128.0f;                   // (degenerate ranges among them)
 #pragma unroll 1
         for (int pass = 0; pass < 8; ++pass) {
             // (one decision: waves that leave count into the histogram at once, so nobody looks there)
@@ -275,6 +276,7 @@ __global__ __launch_bounds__(kBytesThreads) void scan_bytes_kernel(ScanArgs a) {
                 if (in[e]) { mn = fminf(mn, finite(sc[e])); mx = fmaxf(mx, finite(sc[e])); }
             __syncthreads();                                   // (set_range() clears the counter that was read)
             set_range<NW>(mn, mx, ctl, tid, lo, per);
+            if (lo > -1.0e30f) floor_ge = fmaxf(floor_ge, lo); // (the lowest of what is `in`: the best floor there is where all are alike)
 #pragma unroll
             for (int e = 0; e < IPV; ++e)
                 if (in[e]) atomicAdd(&L.hist[bucket_of(sc[e], lo, per)], 1u);
@@ -284,21 +286,21 @@ __global__ __launch_bounds__(kBytesThreads) void scan_bytes_kernel(ScanArgs a) {
                 if (lane == 0) crowd = (int)L.hist[ctl->bstar];
             }
             __syncthreads();
+            floor_ge = fmaxf(floor_ge, next_up(ctl->cut));
         }
-        const float cut = ctl->cut;                            // (K of the sample's scores exceed it)
-        if (__builtin_expect(narrowed, 0)) {                   // the histogram again, from the cut on
+        if (__builtin_expect(narrowed, 0)) {                   // the histogram again, from the floor on
             __syncthreads();
             for (int t = tid; t < kBins; t += NT) L.hist[t] = 0;
-            hlo = cut;
-            hscale = cut > -__builtin_inff() && span > 0.0f && (float)kBins / span < 3.0e38f ? (float)kBins / span : 0.0f;
+            hlo = floor_ge;
+            hscale = floor_ge > -__builtin_inff() && span > 0.0f && (float)kBins / span < 3.0e38f ? (float)kBins / span : 0.0f;
             __syncthreads();
 #pragma unroll
             for (int e = 0; e < IPV; ++e)
-                if (mine && sc[e] > cut) atomicAdd(&L.hist[bucket_of(sc[e], hlo, hscale)], 1u);
-            if (tid == 0) ctl->shared_floor = next_up(cut);
+                if (mine && sc[e] >= floor_ge) atomicAdd(&L.hist[bucket_of(sc[e], hlo, hscale)], 1u);
+            if (tid == 0) ctl->shared_floor = floor_ge;
             __syncthreads();
         }
-        top.floor_ge = next_up(cut);
+        top.floor_ge = floor_ge;
         if (wave < sampling) {
 #pragma unroll
             for (int e = 0; e < IPV; ++e) {

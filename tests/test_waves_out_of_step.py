@@ -46,6 +46,7 @@ int main(int argc, char** argv) {   // file of codes, of scores, of keys; m, byt
     FILE* f = fopen(argv[3], "wb");
     fwrite(keys.data(), 8, keys.size(), f);
     fclose(f);
+    printf("%lld %lld\n", emu::counted, emu::scored);
     return ok ? 0 : 1;
 }
 """
@@ -70,7 +71,7 @@ def program(tmp_path_factory):
 
 
 def scan(at, codes, S, K, order):
-    """the workgroup's K best: (ids, scores)"""
+    """the workgroup's K best: (ids, scores), additions to counters and how many pieces were scored exactly"""
     codes.tofile(at / "codes")
     S.astype(np.float32).tofile(at / "scores")
     cap = 1
@@ -81,7 +82,7 @@ def scan(at, codes, S, K, order):
     assert run.returncode == 0, (run.stdout + run.stderr)[-2000:]
     keys = np.fromfile(at / "keys", dtype=np.uint64)
     high, low = (keys >> np.uint64(32)).astype(np.uint32), (keys & np.uint64(0xFFFFFFFF)).astype(np.uint32)
-    return (~low).astype(np.int32), np.where(high >> 31, high ^ np.uint32(0x80000000), ~high).astype(np.uint32).view(np.float32)
+    return (~low).astype(np.int32), np.where(high >> 31, high ^ np.uint32(0x80000000), ~high).astype(np.uint32).view(np.float32), [int(x) for x in run.stdout.split()]
 
 
 def expected(codes, S, K):
@@ -99,7 +100,7 @@ ORDERS = [list(range(16)), list(range(1, 16)) + [0], list(range(15, -1, -1)), [w
 def same(at, codes, S, K):
     ids, sc = expected(codes, S, K)
     for order in ORDERS:
-        got, got_sc = scan(at, codes, S, K, order)
+        got, got_sc, _ = scan(at, codes, S, K, order)
         assert np.array_equal(got, ids) and np.array_equal(got_sc, sc), order
 
 
@@ -142,9 +143,21 @@ def test_bounds_that_are_exact_loose_or_useless(program, m, dtype, b, n, K):
     for name, T in (("normal", S), ("uneven", S * np.where(np.arange(m) == 1, 50.0, 0.02)[:, None]), ("masked", masked), ("far entry", far), ("one entry of a split counts", deep), ("ties", np.round(S)),
                     ("zeros", 0 * S), ("negative", S - 20), ("offset", S + np.float32(1e7)), ("heavy tails", np.tan(np.pi * (rng.random(S.shape) - 0.5)))):
         ids, sc = expected(codes, T.astype(np.float32), K)
-        got, got_sc = scan(program, codes, T, K, rng.permutation(16))
+        got, got_sc, _ = scan(program, codes, T, K, rng.permutation(16))
         assert np.array_equal(got, ids) and np.array_equal(got_sc, sc), name
     rising = S.copy()
     rising[0] = np.arange(b) * 0.5
     codes[:, 0] = np.arange(n) * b // n
     same(program, codes, rising, K)
+
+
+# of two scores the larger one is an eighth of the items': taking it apart leaves nothing to tell, and that score is the floor
+def test_taking_ties_apart_keeps_the_floor(program):
+    rng = np.random.default_rng(4)
+    codes = rng.integers(0, 256, (20_000, 64), dtype=np.uint8)
+    S = np.zeros((64, 256), np.float32)
+    S[0, :32] = 100.0
+    ids, sc = expected(codes, S, 20)
+    got, got_sc, (_, scored) = scan(program, codes, S, 20, [])
+    assert np.array_equal(got, ids) and np.array_equal(got_sc, sc)
+    assert scored <= 4 * (1024 + 20_000 // 4), scored          # (a row's four vectors; the sample, and who passes)

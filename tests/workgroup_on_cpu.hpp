@@ -27,6 +27,8 @@ inline std::vector<Lane> lanes;
 inline std::vector<uint64_t> seen;            // what the lanes brought to the wave's last cross-lane operation
 inline ucontext_t scheduler;
 inline int current;
+inline long long counted;                    // additions to counters in LDS
+inline long long scored;                     // pieces that a lane has scored exactly (a marker of the scoring functions; long rows: several to a piece)
 inline std::function<void()> body;
 alignas(16) inline unsigned char lds[160 * 1024];
 
@@ -46,7 +48,7 @@ inline void entry() {
     stop(kDone, {"the end", 0});
 }
 
-// Runs `kernel` by `threads` lanes; `order`: waves, the foremost that can go on does.  False, with a line on stdout, where waves part.
+// Runs `kernel` by `threads` lanes; `order`: waves, the foremost that can go on does (none: in turn, an operation each).  False, with a line on stdout, where waves part.
 inline bool run(int threads, const std::vector<int>& order, std::function<void()> kernel) {
     body = kernel;
     lanes.resize(threads);
@@ -67,10 +69,14 @@ inline bool run(int threads, const std::vector<int>& order, std::function<void()
     };
     std::vector<State> wave(threads / 64, kRunning);
     std::vector<bool> wave_free(threads / 64, true);           // (may leave the barrier that its lanes stand at)
-    for (;;) {
+    for (int last = -1;;) {
         int w = -1;
-        for (int o : order)
-            if (wave[o] == kRunning) { w = o; break; }
+        const int waves = (int)wave.size();
+        for (int i = 0; i < waves && w < 0; ++i) {
+            const int o = order.empty() ? (last + 1 + i) % waves : order[i];
+            if (wave[o] == kRunning) w = o;
+        }
+        last = w;
         if (w < 0) {                                           // every wave at a barrier, or at its end
             for (int i = 1; i < threads; ++i)
                 if (lanes[i].state != lanes[0].state || lanes[i].at.line != lanes[0].at.line || strcmp(lanes[i].at.file, lanes[0].at.file) != 0) {
@@ -147,7 +153,7 @@ inline int min(int a, int b) { return a < b ? a : b; }
 inline int max(int a, int b) { return a > b ? a : b; }
 inline uint32_t min(uint32_t a, uint32_t b) { return a < b ? a : b; }
 inline uint32_t max(uint32_t a, uint32_t b) { return a > b ? a : b; }
-template <typename T> inline T atomicAdd(T* p, T v) { const T old = *p; *p += v; return old; }
+template <typename T> inline T atomicAdd(T* p, T v) { ++emu::counted; const T old = *p; *p += v; return old; }
 inline uint64_t wall_clock64() { return 0; }
 
 #define __global__
@@ -169,7 +175,7 @@ inline uint64_t wall_clock64() { return 0; }
 #define __hip_atomic_store(p, v, order, scope) (*(p) = (v))
 #define __builtin_amdgcn_fence(...) ((void)0)
 #define __builtin_amdgcn_wave_barrier() ((void)emu::step(0, __LINE__))
-#define __builtin_amdgcn_sched_barrier(x) ((void)0)
+#define __builtin_amdgcn_sched_barrier(x) ((void)++emu::scored)
 #define __builtin_amdgcn_s_waitcnt(x) ((void)0)
 #define __builtin_amdgcn_readlane(v, l) emu::readlane(v, l, __LINE__)
 #define __builtin_amdgcn_readfirstlane(v) emu::readlane(v, 0, __LINE__)
