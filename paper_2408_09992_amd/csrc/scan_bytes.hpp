@@ -243,8 +243,9 @@ __global__ __launch_bounds__(kBytesThreads) void scan_bytes_kernel(ScanArgs a) {
         }
         __syncthreads();
         // A score far from the others (an item with a masked sub-id, at -1e9) stretches the range until the buckets tell nothing apart: while the K-th
-        // best shares its bucket with many that are no better, that bucket alone is taken apart again.  (An entry of every split at -1e9: 50M items, m = 8
-        // 146 us without this, 72 with, 4M, m = 64 98 and 53.)
+        // best shares its bucket with many that are no better, or buckets are too wide for floors to rise by, that bucket alone is taken apart again.  (An
+        // entry of every split at -1e9: 50M items, m = 8 146 us without this, 72 with, 4M, m = 64 98 and 53; buckets too wide, half a split at -1e9: 28M,
+        // m = 8, K = 512 451 and 76.)
         bool in[IPV];
 #pragma unroll
         for (int e = 0; e < IPV; ++e) in[e] = mine;
@@ -256,7 +257,7 @@ __global__ __launch_bounds__(kBytesThreads) void scan_bytes_kernel(ScanArgs a) {
         for (int pass = 0; pass < 8; ++pass) {
             // (one decision: waves that leave count into the histogram at once, so nobody looks there)
             const int bstar = ctl->bstar;
-            if (__builtin_expect(crowd <= 2 * left + kWave || !(per > 0.0f), 1)) break;
+            if (__builtin_expect((crowd <= 2 * left + kWave && !(per * span < 128.0f)) || !(per > 0.0f), 1)) break;
             narrowed = true;
             __syncthreads();
 #pragma unroll

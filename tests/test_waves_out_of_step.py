@@ -151,6 +151,18 @@ def test_bounds_that_are_exact_loose_or_useless(program, m, dtype, b, n, K):
     same(program, codes, rising, K)
 
 
+# most items far below the others, and of the sample fewer than twice K and 64 not among them: floors rise by what lies between the others all the same
+def test_far_scores_do_not_keep_floors_from_rising(program):
+    rng = np.random.default_rng(3)
+    codes = rng.integers(0, 256, (120_000, 8), dtype=np.uint8)
+    S = rng.standard_normal((8, 256)).astype(np.float32)
+    S[4:6, np.arange(256) % 4 != 0] = -1e9
+    ids, sc = expected(codes, S, 40)
+    got, got_sc, (counted, _) = scan(program, codes, S, 40, [])
+    assert np.array_equal(got, ids) and np.array_equal(got_sc, sc)
+    assert counted <= 2048 + 1000, counted                     # (the sample; 7500 items are not masked)
+
+
 # of two scores the larger one is an eighth of the items': taking it apart leaves nothing to tell, and that score is the floor
 def test_taking_ties_apart_keeps_the_floor(program):
     rng = np.random.default_rng(4)
