@@ -381,6 +381,13 @@ __global__ __launch_bounds__(kBytesThreads) void scan_bytes_kernel(ScanArgs a) {
                 top.append(mask, take, sc[e], p * IPV + (uint32_t)e, lane);
             }
         }
+        // A list that has been sorted: K of its keys are no worse than the K-th, and what this wave has yet to see has higher ids than all of them, so
+        // ties with the K-th come too late.  (All scores alike, 50M items, m = 8, K = 10: 1217 us without this, 139; m = 16, 20M, K = 100, all + 1e7 1011 and 502.)
+        if (__builtin_expect(top.thr != 0ull, 0)) {
+            const float kth = score_of_key(top.thr);
+            if (lane == 0 && kth > lds_peek(&ctl->shared_floor)) lds_poke(&ctl->shared_floor, kth);
+            top.floor_ge = fmaxf(top.floor_ge, next_up(kth));
+        }
     };
     // Units are handed out by a counter in LDS: waves that fall behind do not hold the others up.  (A request is answered a unit later.)
     int pending = 0;

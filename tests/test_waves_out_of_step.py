@@ -173,3 +173,16 @@ def test_taking_ties_apart_keeps_the_floor(program):
     got, got_sc, (_, scored) = scan(program, codes, S, 20, [])
     assert np.array_equal(got, ids) and np.array_equal(got_sc, sc)
     assert scored <= 4 * (1024 + 20_000 // 4), scored          # (a row's four vectors; the sample, and who passes)
+
+
+# all scores alike: a list that is full of them takes no more, whichever waves are ahead
+@pytest.mark.parametrize("K", [10, 100])
+def test_ties_beyond_a_full_list_are_not_taken(program, K):
+    rng = np.random.default_rng(5)
+    codes = rng.integers(0, 256, (40_000, 8), dtype=np.uint8)
+    S = np.ones((8, 256), np.float32)
+    ids, sc = expected(codes, S, K)
+    for order in ORDERS + [[]]:
+        got, got_sc, (counted, _) = scan(program, codes, S, K, order)
+        assert np.array_equal(got, ids) and np.array_equal(got_sc, sc), order
+        assert counted <= 20_000, counted                      # (the sample, a list of every wave, and the selection from these)
