@@ -169,20 +169,17 @@ __device__ __forceinline__ uint32_t wave_prefix_sum(uint32_t v) {
     return v;
 }
 
-// Bitonic sort of n (a power of two) keys in LDS, descending.  BLOCK: all threads of the workgroup take part and
-// stages are separated by workgroup barriers; otherwise one wave sorts its own array.
-template <bool BLOCK>
-__device__ void bitonic_sort_desc(uint64_t* a, int n, int tid, int nthr) {
+// Bitonic sort of n (a power of two) keys in LDS, descending, by one wave.
+__device__ inline void wave_sort_desc(uint64_t* a, int n, int lane) {
     for (int k = 2; k <= n; k <<= 1) {
         for (int j = k >> 1; j > 0; j >>= 1) {
-            for (int t = tid; t < (n >> 1); t += nthr) {
-                int i = ((t & ~(j - 1)) << 1) | (t & (j - 1));
-                int p = i | j;
-                bool desc = (i & k) == 0;
-                uint64_t x = a[i], y = a[p];
+            for (int t = lane; t < (n >> 1); t += kWave) {
+                const int i = ((t & ~(j - 1)) << 1) | (t & (j - 1)), p = i | j;
+                const bool desc = (i & k) == 0;
+                const uint64_t x = a[i], y = a[p];
                 if ((x < y) == desc) { a[i] = y; a[p] = x; }
             }
-            if (BLOCK) __syncthreads(); else wave_sync();
+            wave_sync();
         }
     }
 }

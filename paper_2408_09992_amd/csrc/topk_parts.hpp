@@ -106,7 +106,7 @@ __device__ void find_cut(const uint32_t* hist, int K, Ctl* ctl, int lane) {
 __device__ __noinline__ uint64_t sort_wave_list(uint64_t* buf, int cap, int cnt, int K, int lane) {
     for (int t = cnt + lane; t < cap; t += kWave) buf[t] = 0;
     wave_sync();
-    bitonic_sort_desc<false>(buf, cap, lane, kWave);
+    wave_sort_desc(buf, cap, lane);
     return cnt >= K ? buf[K - 1] : 0ull;
 }
 
@@ -403,12 +403,40 @@ __device__ void rank_select(uint64_t* cand, int C, int K, uint64_t* dst, int tid
     __syncthreads();
 }
 
+// One wave: the highest bucket b* such that buckets >= b* hold at least K entries (there are as many), and how many the buckets above it hold.  Same
+// values in all lanes; nothing is written.
+template <int BINS = kBins>
+__device__ __forceinline__ int highest_bucket(const uint32_t* hist, int K, int& above, int lane) {
+    constexpr int per = BINS / kWave;                        // buckets per lane; lane 0 owns the top ones
+    const int first = BINS - per * (lane + 1);
+    uint32_t c[per], mine = 0;
+#pragma unroll
+    for (int i = 0; i < per; i += 4) {
+        const uint4 v = *reinterpret_cast<const uint4*>(hist + first + i);
+        c[i] = v.x; c[i + 1] = v.y; c[i + 2] = v.z; c[i + 3] = v.w;
+        mine += v.x + v.y + v.z + v.w;
+    }
+    const uint32_t upto = wave_prefix_sum(mine);
+    const uint64_t has = __ballot(upto >= (uint32_t)K);
+    const int owner = has != 0 ? __builtin_ctzll(has) : kWave - 1;
+    uint32_t more = upto - mine, before = more;              // entries above bucket i, and above the one that is found
+    int found = -1;
+#pragma unroll
+    for (int i = per - 1; i >= 0; --i) {
+        if (found < 0 && more + c[i] >= (uint32_t)K) { found = i; before = more; }
+        more += c[i];
+    }
+    above = __builtin_amdgcn_readlane((int)before, owner);
+    return __builtin_amdgcn_readlane(first + (found < 0 ? 0 : found), owner);
+}
+
 // Exact selection of the K best among the nonzero keys of src[0..n) (LDS, zeros allowed anywhere), written sorted
 // to dst[0..K) (zero-filled if fewer than K exist).  All NT threads of the workgroup call it, ctl->lo / scale / ncand = 0 set.
-// `cand` holds candmax keys, `hist` kBins counters.  If the histogram cannot narrow the set to candmax keys (ties,
-// degenerate range), src is sorted in place instead, which needs n to be a power of two.
+// `cand` holds candmax keys, `hist` kBins counters.  If the histogram cannot narrow the set to candmax keys (ties, a far score that
+// stretches the range), the keys' own bits do, ten at a time from the top: two barriers and a pass over src a time, seven times at most.  (Sorting src instead:
+// 16,384 keys of sixteen waves, 28M items, m = 8, K = 512, an entry at +1e4 596 us.)
 template <int NT = kThreads>
-__device__ void block_select(uint64_t* src, int n, int K, uint64_t* dst, uint64_t* cand, int candmax, uint32_t* hist,
+__device__ void block_select(const uint64_t* src, int n, int K, uint64_t* dst, uint64_t* cand, int candmax, uint32_t* hist,
                              Ctl* ctl, int tid) {
     const int lane = tid & (kWave - 1);
     for (int i = tid; i < kBins; i += NT) hist[i] = 0;
@@ -431,14 +459,40 @@ __device__ void block_select(uint64_t* src, int n, int K, uint64_t* dst, uint64_
         }
     }
     __syncthreads();
-    const int C = ctl->ncand;
+    int C = ctl->ncand;
     if (C <= candmax) {
         rank_select<NT>(cand, C, K, dst, tid, hist, lo, scale);
-    } else {
-        bitonic_sort_desc<true>(src, n, tid, NT);
-        for (int i = tid; i < K; i += NT) dst[i] = src[i];
-        __syncthreads();
+        return;
     }
+    static_assert(kBins == 1 << 10, "ten bits of a key at a time");
+    uint64_t prefix = 0;                                     // the K-th best key's bits from `shift` on
+    int shift = 64, left = K;                                // the left-th best of the keys that share them is sought
+    do {
+        const int from = shift;
+        shift = from > 10 ? from - 10 : 0;
+        const uint32_t digits = (1u << (from - shift)) - 1u;
+        __syncthreads();                                     // (everyone has read the count, and the histogram)
+        for (int i = tid; i < kBins; i += NT) hist[i] = 0;
+        __syncthreads();
+        for (int i = tid; i < n; i += NT) {
+            const uint64_t key = src[i];
+            if (key && (from == 64 || key >> from == prefix)) atomicAdd(&hist[(uint32_t)(key >> shift) & digits], 1u);
+        }
+        __syncthreads();
+        int above;                                           // (every wave by itself)
+        const int digit = highest_bucket(hist, left, above, lane);
+        left -= above;
+        prefix = prefix << (from - shift) | (uint32_t)digit;
+        C = K - left + (int)hist[digit];                     // (K - left: better than all that share the prefix)
+    } while (C > candmax && shift > 0);                      // (no two keys are the same: in the end C is K)
+    if (tid == 0) ctl->ncand = 0;
+    __syncthreads();
+    for (int i = tid; i < n; i += NT) {
+        const uint64_t key = src[i];
+        if (key && key >> shift >= prefix) cand[atomicAdd(&ctl->ncand, 1)] = key;
+    }
+    __syncthreads();
+    rank_select<NT>(cand, C, K, dst, tid);
 }
 
 __host__ __device__ constexpr size_t align16(size_t x) { return (x + 15) & ~(size_t)15; }

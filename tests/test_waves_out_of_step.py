@@ -46,7 +46,7 @@ int main(int argc, char** argv) {   // file of codes, of scores, of keys; m, byt
     FILE* f = fopen(argv[3], "wb");
     fwrite(keys.data(), 8, keys.size(), f);
     fclose(f);
-    printf("%lld %lld\n", emu::counted, emu::scored);
+    printf("%lld %lld %lld\n", emu::counted, emu::scored, emu::barriers);
     return ok ? 0 : 1;
 }
 """
@@ -71,7 +71,7 @@ def program(tmp_path_factory):
 
 
 def scan(at, codes, S, K, order):
-    """the workgroup's K best: (ids, scores), additions to counters and how many pieces were scored exactly"""
+    """the workgroup's K best: (ids, scores), [additions to counters, pieces scored exactly, barriers]"""
     codes.tofile(at / "codes")
     S.astype(np.float32).tofile(at / "scores")
     cap = 1
@@ -158,7 +158,7 @@ def test_far_scores_do_not_keep_floors_from_rising(program):
     S = rng.standard_normal((8, 256)).astype(np.float32)
     S[4:6, np.arange(256) % 4 != 0] = -1e9
     ids, sc = expected(codes, S, 40)
-    got, got_sc, (counted, _) = scan(program, codes, S, 40, [])
+    got, got_sc, (counted, _, _) = scan(program, codes, S, 40, [])
     assert np.array_equal(got, ids) and np.array_equal(got_sc, sc)
     assert counted <= 2048 + 1000, counted                     # (the sample; 7500 items are not masked)
 
@@ -170,7 +170,7 @@ def test_taking_ties_apart_keeps_the_floor(program):
     S = np.zeros((64, 256), np.float32)
     S[0, :32] = 100.0
     ids, sc = expected(codes, S, 20)
-    got, got_sc, (_, scored) = scan(program, codes, S, 20, [])
+    got, got_sc, (_, scored, _) = scan(program, codes, S, 20, [])
     assert np.array_equal(got, ids) and np.array_equal(got_sc, sc)
     assert scored <= 4 * (1024 + 20_000 // 4), scored          # (a row's four vectors; the sample, and who passes)
 
@@ -179,10 +179,30 @@ def test_taking_ties_apart_keeps_the_floor(program):
 @pytest.mark.parametrize("K", [10, 100])
 def test_ties_beyond_a_full_list_are_not_taken(program, K):
     rng = np.random.default_rng(5)
-    codes = rng.integers(0, 256, (40_000, 8), dtype=np.uint8)
+    codes = rng.integers(0, 256, (100_000, 8), dtype=np.uint8)
     S = np.ones((8, 256), np.float32)
     ids, sc = expected(codes, S, K)
     for order in ORDERS + [[]]:
-        got, got_sc, (counted, _) = scan(program, codes, S, K, order)
+        got, got_sc, (counted, _, _) = scan(program, codes, S, K, order)
         assert np.array_equal(got, ids) and np.array_equal(got_sc, sc), order
-        assert counted <= 20_000, counted                      # (the sample, a list of every wave, and the selection from these)
+        assert counted <= 60_000, counted                      # (the sample, a list of every wave, and the selection from these)
+
+
+# more keys in the waves' lists than are ranked at once, and a range that tells them apart no further (a far score, ties): narrowed down by their bits, not sorted
+@pytest.mark.parametrize("K", [512])
+@pytest.mark.parametrize("name", ["one entry +1e4", "few values", "negative"])
+def test_many_keys_in_few_buckets_are_narrowed_down(program, name, K):
+    rng = np.random.default_rng(6)
+    codes = rng.integers(0, 256, (20_000, 8), dtype=np.uint8)
+    S = rng.standard_normal((8, 256)).astype(np.float32)
+    if name == "few values":
+        S = np.round(0.3 * S)
+    if name == "negative":
+        S -= 30.0
+        S[1:] *= np.float32(1e-7)
+    codes[7, 4] = 17
+    S[4, 17] += 1e4
+    ids, sc = expected(codes, S, K)
+    got, got_sc, (_, _, barriers) = scan(program, codes, S, K, [])
+    assert np.array_equal(got, ids) and np.array_equal(got_sc, sc)
+    assert barriers <= 90, barriers

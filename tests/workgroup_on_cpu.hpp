@@ -27,7 +27,7 @@ inline std::vector<Lane> lanes;
 inline std::vector<uint64_t> seen;            // what the lanes brought to the wave's last cross-lane operation
 inline ucontext_t scheduler;
 inline int current;
-inline long long counted;                    // additions to counters in LDS
+inline long long counted, barriers;          // additions to counters in LDS; barriers that all lanes have passed
 inline long long scored;                     // pieces that a lane has scored exactly (a marker of the scoring functions; long rows: several to a piece)
 inline std::function<void()> body;
 alignas(16) inline unsigned char lds[160 * 1024];
@@ -84,6 +84,7 @@ inline bool run(int threads, const std::vector<int>& order, std::function<void()
                     return false;
                 }
             if (wave[0] == kDone) return true;
+            ++barriers;
             wave.assign(wave.size(), kRunning);
             wave_free.assign(wave.size(), true);
             continue;
