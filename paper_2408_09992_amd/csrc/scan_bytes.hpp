@@ -327,10 +327,12 @@ __global__ __launch_bounds__(kBytesThreads) void scan_bytes_kernel(ScanArgs a) {
     stamp<STAMP>(rec, kStampOffered, lane);
     // ---- stream
     int turn = wave, gap = NW;                                 // units until this wave's next turn; grows by a quarter
-    // Tables whose bounds say little let every unit pass: after so many in a row a wave goes on without them.  (An entry that five items have, 50M items, m = 8:
-    // 160 us with the bounds to the end, 116.)
-    constexpr uint32_t kInARow = 32;
-    uint32_t in_a_row = 0;
+    // Tables whose bounds say little let many lanes of most units pass: after three such units in a row, or some among others, a wave goes on without bounds for
+    // a while, each time for longer, and looks again.  (Few lanes of every unit, as many results have until floors have risen, cost less than doing without.
+    // Bounds given up for good after 32 units of which any lane passes, which 30 units a wave never get to, and as it is: 8M items, m = 64, Cauchy 138 us and 115,
+    // +1e4 140 and 113, denormal 171 and 139, m = 32 +1e4 77 and 64; 50M, m = 8, K = 100, ordinary 75.7 and 76.2.)
+    constexpr int kManyLanes = 24, kMostCredit = 4, kMostRest = 64;
+    int credit = kMostCredit, rest = 16;
     auto process = [&](auto bounded, const uint32_t (&w)[4 * VPI], uint32_t i) {
         top.floor_ge = fmaxf(top.floor_ge, lds_peek(&ctl->shared_floor));
         if (--turn < 0) {
@@ -365,11 +367,13 @@ __global__ __launch_bounds__(kBytesThreads) void scan_bytes_kernel(ScanArgs a) {
         }
         const uint32_t p = piece_of(i);
         const bool hit = any >= t && p <= last;
-        if (__ballot(hit) == 0) {
-            in_a_row = 0;
-            return;
+        const uint64_t hits = __ballot(hit), before = top.thr;
+        if constexpr (decltype(bounded)::value) {
+            credit = __popcll(hits) >= kManyLanes ? credit - 2 : credit < kMostCredit ? credit + 1 : kMostCredit;
+            if (hits == 0) return;
+        } else {
+            --credit;
         }
-        ++in_a_row;
         float sc[IPV];
         if (hit) score(w, sc);                                 // (the lookups of a few lanes collide less)
 #pragma unroll
@@ -382,8 +386,8 @@ __global__ __launch_bounds__(kBytesThreads) void scan_bytes_kernel(ScanArgs a) {
             }
         }
         // A list that has been sorted: K of its keys are no worse than the K-th, and what this wave has yet to see has higher ids than all of them, so
-        // ties with the K-th come too late.  (All scores alike, 50M items, m = 8, K = 10: 1217 us without this, 139; m = 16, 20M, K = 100, all + 1e7 1011 and 502.)
-        if (__builtin_expect(top.thr != 0ull, 0)) {
+        // ties with the K-th come too late.  (All scores alike, 50M items, m = 8, K = 10: 1217 us without this, 115.)
+        if (__builtin_expect(top.thr != before, 0)) {
             const float kth = score_of_key(top.thr);
             if (lane == 0 && kth > lds_peek(&ctl->shared_floor)) lds_poke(&ctl->shared_floor, kth);
             top.floor_ge = fmaxf(top.floor_ge, next_up(kth));
@@ -396,7 +400,7 @@ __global__ __launch_bounds__(kBytesThreads) void scan_bytes_kernel(ScanArgs a) {
     request();
     bool seen = wave < sampling;
     auto stream = [&](auto bounded) {
-        while (unit[0] < units && (!decltype(bounded)::value || in_a_row < kInARow)) {   // (slot 0 holds the older one)
+        while (unit[0] < units && credit >= 0) {               // (slot 0 holds the older one)
 #pragma unroll
             for (int i = 0; i < 2; ++i) {
                 if (!seen && unit[i] < units) process(bounded, w[i], unit[i]);
@@ -407,8 +411,13 @@ __global__ __launch_bounds__(kBytesThreads) void scan_bytes_kernel(ScanArgs a) {
             }
         }
     };
-    stream(std::true_type());
-    stream(std::false_type());
+    while (unit[0] < units) {
+        stream(std::true_type());
+        credit = rest;
+        rest = rest < kMostRest ? 2 * rest : kMostRest;
+        stream(std::false_type());
+        credit = 0;
+    }
     if constexpr (P <= 16) {
         // the fewer than 16 / P items after the last whole code vector, one per lane of one wave
         if (blk == 0 && wave == 0) {

@@ -206,3 +206,17 @@ def test_many_keys_in_few_buckets_are_narrowed_down(program, name, K):
     got, got_sc, (_, _, barriers) = scan(program, codes, S, K, [])
     assert np.array_equal(got, ids) and np.array_equal(got_sc, sc)
     assert barriers <= 90, barriers
+
+
+# scores that rise along the first quarter of the catalogue, where bounds dismiss nothing, and are low in the rest: waves that went on without bounds come back
+def test_waves_come_back_to_their_bounds(program):
+    rng = np.random.default_rng(7)
+    codes = rng.integers(0, 256, (400_000, 8), dtype=np.uint8)
+    S = rng.standard_normal((8, 256)).astype(np.float32)
+    S[0] = np.arange(256)
+    codes[:100_000, 0] = 1 + np.arange(100_000) * 255 // 100_000
+    codes[100_000:, 0] = 0
+    ids, sc = expected(codes, S, 10)
+    got, got_sc, (_, scored, _) = scan(program, codes, S, 10, [])
+    assert np.array_equal(got, ids) and np.array_equal(got_sc, sc)
+    assert scored <= 120_000, scored                           # (of 200,000 code vectors)
