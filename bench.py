@@ -9,6 +9,7 @@ from __future__ import annotations
 
 import argparse
 import json
+import math
 import os
 import sys
 import time
@@ -490,6 +491,17 @@ def _prepared(torch, pq, W, kind, N, B, m, b, K, S=None, codes=None, seed=1):
     return lambda: pq.PreparedScoreTopK(codes, S, K)
 
 
+class _InTurn:
+    """Marshalled calls, each call the next of them; the results are the first one's."""
+
+    def __init__(self, calls):
+        self.calls, self.at, self.ids, self.scores = calls, 0, calls[0].ids, calls[0].scores
+
+    def __call__(self):
+        self.calls[self.at]()
+        self.at = (self.at + 1) % len(self.calls)
+
+
 def rules_mode(args):
     """Both sides of the rules that choose a scan, on either side of each of their lines: the whole call by the kernel the library
     takes and by the one it leaves (pq_measure_force_general), the same inputs, the same results."""
@@ -497,8 +509,10 @@ def rules_mode(args):
     from paper_2408_09992_amd import binding as pq, workloads as W
     rows = []
 
-    def row(rule, kind, N, B, m, b, K, masks, names):
-        us, same = _two_sides(torch, pq, _prepared(torch, pq, W, kind, N, B, m, b, K), masks)
+    def row(rule, kind, N, B, m, b, K, masks, names, in_turn=0.0):
+        copies = max(1, math.ceil(in_turn / (N * m * (2 if kind == "scan16" else 1))))
+        prepare = [_prepared(torch, pq, W, kind, N, B, m, b, K, seed=1 + i) for i in range(copies)]
+        us, same = _two_sides(torch, pq, (lambda: _InTurn([p() for p in prepare])) if copies > 1 else prepare[0], masks)
         taken = pq.pq_measure_plan(kind, N, B, m, b, K)
         rows.append({"rule": rule, "kind": kind, "N": N, "B": B, "m": m, "b": b, "K": K, names[0]: us[0], names[1]: us[1],
                      "taken": "bytes" if B == 1 and taken["kernel"] == "general" and taken["field_bits"] == 8 else taken["kernel"], "groups": taken["groups"], "same": same})
@@ -515,13 +529,13 @@ def rules_mode(args):
         for N in Ns:
             for K in Ks:
                 row("segments", kind, N, 1, m, b, K, (64, 1), ("segments", "general"))
-    # one query by one-byte bounds (mask bit 10) or without (bit 9): lines in bytes of codes
+    # one query by one-byte bounds (mask bit 10) or without (bit 9): lines in bytes of codes; several catalogues in turn, more than the caches hold
     for kind, m, b, lines in (("scan", 4, 256, ((10, 4.4e7), (100, 7.0e7))), ("scan", 8, 256, ((10, 5.2e7), (100, 1.1e8), (256, 1.4e8), (512, 1.8e8))),
-                              ("scan", 16, 256, ((10, 8.8e7), (100, 1.1e8), (256, 1.4e8))), ("scan", 32, 256, ((10, 8.0e7), (100, 1.5e8))), ("scan", 64, 256, ((10, 3.6e8), (100, 4.5e8))),
-                              ("scan16", 4, 1500, ((10, 1.1e8),)), ("scan16", 8, 1024, ((10, 2.0e8), (100, 2.0e8))), ("scan16", 16, 300, ((10, 2.0e8),)), ("scan16", 8, 2500, ((10, 4.5e8),))):
+                              ("scan", 16, 256, ((10, 8.8e7), (100, 1.1e8), (256, 1.4e8))), ("scan", 32, 256, ((10, 8.0e7), (100, 1.5e8))), ("scan", 64, 256, ((10, 2.7e8), (100, 2.7e8), (256, 4.0e8))),
+                              ("scan16", 4, 1500, ((10, 1.5e8),)), ("scan16", 8, 1024, ((10, 3.0e8), (100, 3.0e8))), ("scan16", 16, 300, ((10, 2.0e8), (100, 2.0e8))), ("scan16", 8, 2500, ((10, 4.5e8),))):
         for K, line in lines:
             for f in (0.5, 0.8, 1.25, 2.0):
-                row("bytes", kind, int(f * line / (m * (2 if kind == "scan16" else 1))), 1, m, b, K, (1024, 512), ("bytes", "without"))
+                row("bytes", kind, int(f * line / (m * (2 if kind == "scan16" else 1))), 1, m, b, K, (1024, 512), ("bytes", "without"), 9.0e8)
     # batches by bounds (mask bit 4) or with every score computed (bit 3): lines in lookups ...
     for kind, m, b, K, least, Bs in (("scan", 4, 256, 10, 6.0e7, (4, 64)), ("scan", 8, 256, 10, 6.5e7, (4, 64)), ("scan", 8, 256, 10, 9.75e7, (2,)),
                                      ("scan", 16, 256, 10, 1.0e8, (4, 64)), ("scan", 32, 256, 10, 1.6e8, (8, 64)), ("scan", 32, 256, 100, 2.1e8, (8,)),

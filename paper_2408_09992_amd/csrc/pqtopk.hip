@@ -194,24 +194,25 @@ bool subset_direct_pays(long long N, int m, int B) {
 }
 
 // Bytes of codes from which one query's catalogue is scanned by one-byte bounds (scan_bytes_kernel): before that its sample, counts and lists per wave
-// weigh more than the lookups and the uneven rounds that it saves.  Calls without and with (us; codes that no cache holds), just below the lines and further on: m = 4:
-// 8M items, K = 10 16.2 and 17.3, 16M 23.1 and 21.5, 11M, K = 100 25.2 and 25.9, 24M 36.4 and 34.0; m = 8: 5M, K = 10 17.7 and 18.0, 8M 24.8 and 21.3, 40M 66.2 and 57.0,
-// 12M, K = 100 32.8 and 32.6, 24M 51.1 and 46.4, 12M, K = 256 37.5 and 38.6, 24M 59.0 and 54.1, K = 512 (codes partly held), 16M 52.9 and 55.1, 30M 78.8 and 74.1; m = 16: 4M, K = 10
-// 20.5 and 21.2, 7M 33.4 and 27.1, 24M 79.9 and 66.1, 5M, K = 100 28.0 and 30.4, 9M 43.9 and 39.3, 7M, K = 256 39.4 and 40.4, 14M 61.9 and 57.8; m = 32: 2M, K = 10 22.4 and
-// 22.0, 4M 33.9 and 30.9, K = 100 37.8 and 38.1, 6M 56.2 and 46.4, 4M, K = 256 40.6 and 43.8, 9M 75.1 and 68.1; m = 64: 4M, K = 10 55.4 and 57.3, 8M 102.0 and 97.3, 6M, K = 40
-// 82.8 and 82.9, 8M, K = 256 111.2 and 107.9.
-// Two bytes: what they gain is the memory's rate (units of one vector, 6.3 TB/s instead of 5.9), the less the larger the tables that come first.  m = 4, b = 1500: 8M, K = 10 19.9 and 22.4, 14M
-// 29.1 and 28.5, 48M 74.6 and 69.2; b = 5000: 24M 42.0 and 42.6, 48M 74.6 and 72.2; m = 8, b = 1024: 8M 29.6 and 31.0, 14M 46.5 and 45.1, 45M 126.4 and 120.5, K = 100 133.3 and 123.9; b = 2500:
-// 14M, K = 10 47.3 and 47.4, 45M 127.9 and 122.9; m = 16, b = 300: 3M 24.6 and 25.7, 6M 42.6 and 39.8, 22M 124.4 and 121.3; b = 1000: 22M, K = 100 129.7 and 129.5.
+// weigh more than the lookups and the uneven rounds that it saves.  Calls without and with (us; several catalogues in turn, so that no cache holds the codes; in brackets where one
+// catalogue over and over says something else), just below the lines and further on: m = 4: 8M items, K = 10 16.4 and 17.2, 11M 19.5 and 18.8, K = 100 25.4 and 25.8, 17.5M 32.3 and 30.1,
+// K = 512 14M 39.1 and 45.0, 22M 56.3 and 52.3; m = 8: 5M, K = 10 17.7 and 18.0, 6.5M 22.7 and 19.8, K = 100 10M 31.1 and 31.2, 13.8M 36.7 and 35.4, K = 256 13.8M 41.6 and 41.9, 17.5M 48.5 and 46.8, K = 512
+// 13.8M 46.8 and 54.5, 22.5M 68.9 and 66.9; m = 16: 4M, K = 10 20.7 and 21.2, 5.5M 25.1 and 24.2, K = 100 5.5M 29.3 and 31.5, 7M 36.2 and 34.9, K = 256 7M 39.3 and 40.9, 9M 47.4 and 46.4; m = 32: 2M, K = 10
+// 22.5 and 22.1 (21.6 and 21.8), 2.5M 25.5 and 24.1, K = 100 3.2M 33.9 and 34.2, 4.7M 49.1 and 40.4, K = 256 3.2M 36.4 and 39.4, 6M 55.8 and 53.4; m = 64, from where the short kernel ends: 3.5M, K = 10 49.4 and
+// 51.3 (48.9 and 46.5), 4.2M 61.9 and 60.0 (61.2 and 52.8), K = 100 3.5M 54.0 and 56.9, 4.2M 66.5 and 63.5, K = 256 4.2M 70.6 and 71.4, 7M 100.4 and 98.1.
+// Two bytes: what they gain is the memory's rate (units of one vector, 6.3 TB/s instead of 5.9), the less the larger the tables that come first, and nothing while the last-level cache holds the
+// codes.  m = 4, b = 1500: 14M, K = 10 29.1 and 29.1, 18M 34.3 and 33.7 (32.4 and 32.6); b = 3500: 30M 50.3 and 49.1 (47.1 and 47.2), 56M 85.6 and 80.8; m = 8, b = 1024: 12.5M 40.8 and 41.4 (38.3 and 39.7), 16M 50.1 and
+// 50.3 (46.6 and 48.7), 45M 126.4 and 120.5; b = 1500: 20M 61.3 and 60.2 (60.1 and 59.8), 30M 88.5 and 85.0; m = 16, b = 300: 4M 29.2 and 31.5, 6.3M 43.6 and 42.0, K = 100 51.8 and 46.3; b = 800: 10M,
+// K = 10 62.9 and 63.5, 15M 88.7 and 89.6.
 bool bytes_pay(long long N, int m, int b, int K, int cw) {
     const double bytes = (double)N * m * cw;
-    if (cw == 2) return m * b <= 9000 ? bytes >= (m == 4 ? 1.1e8 : 2.0e8) : bytes >= 4.5e8 && (m < 16 || K <= 16);
+    if (cw == 2) return m * b <= 9000 ? bytes >= (m == 4 ? 1.5e8 : m == 8 ? 3.0e8 : 2.0e8) : m < 16 && bytes >= 4.5e8;
     switch (m) {
         case 4: return bytes >= (K <= 16 ? 4.4e7 : K <= 256 ? 7.0e7 : 9.0e7);
         case 8: return bytes >= (K <= 16 ? 5.2e7 : K <= 128 ? 1.1e8 : K <= 256 ? 1.4e8 : 1.8e8);
         case 16: return bytes >= (K <= 16 ? 8.8e7 : K <= 128 ? 1.1e8 : 1.4e8);
         case 32: return bytes >= (K <= 16 ? 8.0e7 : K <= 128 ? 1.5e8 : 1.9e8);
-        case 64: return bytes >= (K <= 16 ? 3.6e8 : 4.5e8);
+        case 64: return bytes >= (K <= 128 ? 2.7e8 : 4.0e8);
         default: return false;
     }
 }

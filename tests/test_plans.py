@@ -176,3 +176,14 @@ def test_splits_in_device_memory_and_the_room_for_their_rows(plan, N, B, m, K, f
     a_query = 256 * m * (2 if p["field_bits"] == 16 else 1) + 512 + 16 + 256 * far
     others = 4 * p["parts"] * (K + 4) if p["parts"] > 1 else 0
     assert B * a_query <= tables <= -(-B // p["queries"]) * p["queries"] * (a_query + others) + 5 * 256
+
+
+# One query by one-byte bounds or without: both sides measured over catalogues that no cache holds, and over one that it holds in part.  Two-byte sub-ids of one round of
+# tables (m * b to 9000) gain nothing while the last-level cache holds the codes (m = 8, b = 1024, 12.5M 38.3 us without and 39.7, 16M 46.6 and 48.7; m = 16, b = 800, 15M 88.7 and 89.6); rows of
+# 64 gain from where the short kernel ends (4.2M, K = 10 61.9 and 60.0, K = 100 66.5 and 63.5).
+@pytest.mark.parametrize("kind,m,b,K,N,by_bytes", [("scan16", 8, 1024, 10, 12_500_000, False), ("scan16", 8, 1024, 10, 16_000_000, False), ("scan16", 8, 1024, 10, 45_000_000, True),
+                                                   ("scan16", 4, 1500, 10, 14_000_000, False), ("scan16", 4, 1500, 10, 20_000_000, True), ("scan16", 16, 800, 10, 15_000_000, False),
+                                                   ("scan16", 16, 300, 100, 6_300_000, True), ("scan", 64, 256, 10, 4_000_000, False), ("scan", 64, 256, 10, 4_500_000, True),
+                                                   ("scan", 64, 256, 100, 5_600_000, True), ("scan", 64, 256, 256, 5_600_000, False)])
+def test_one_byte_bounds_where_they_pay(plan, kind, m, b, K, N, by_bytes):
+    assert (plan(kind, N, 1, m, b, K)["field_bits"] == 8) == by_bytes
