@@ -102,8 +102,8 @@ __device__ __forceinline__ void wave_minmax(float& mn, float& mx) {
     mx = fmaxf(fmaxf(x0, x1), fmaxf(x2, x3));
 }
 
-// min and max over the wave of unsigned values, in every lane
-__device__ __forceinline__ float wave_sum_f32(float v) {     // (for bounds and heuristics: any order will do)
+// sum over the wave, in every lane (for bounds and heuristics: any order will do)
+__device__ __forceinline__ float wave_sum_f32(float v) {
     v += dpp_f32<kDppQuadSwap1>(0.0f, v);
     v += dpp_f32<kDppQuadSwap2>(0.0f, v);
     v += dpp_f32<kDppRowHalfMirror>(0.0f, v);
@@ -114,6 +114,7 @@ __device__ __forceinline__ float wave_sum_f32(float v) {     // (for bounds and 
     return sum;
 }
 
+// min and max over the wave of unsigned values, in every lane
 __device__ __forceinline__ void wave_minmax_u32(uint32_t& mn, uint32_t& mx) {
     mn = min(mn, dpp_u32<kDppQuadSwap1>(mn, mn));       mx = max(mx, dpp_u32<kDppQuadSwap1>(mx, mx));
     mn = min(mn, dpp_u32<kDppQuadSwap2>(mn, mn));       mx = max(mx, dpp_u32<kDppQuadSwap2>(mx, mx));

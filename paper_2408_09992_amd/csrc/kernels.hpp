@@ -100,9 +100,10 @@ namespace pqk {
     PQ_SHORT16_U(X, 8, 16) PQ_SHORT16_U(X, 8, 24) PQ_SHORT16_U(X, 8, 32) PQ_SHORT16_U(X, 8, 48) \
     PQ_SHORT16_U(X, 16, 8) PQ_SHORT16_U(X, 16, 12) PQ_SHORT16_U(X, 16, 16) PQ_SHORT16_U(X, 16, 24) PQ_SHORT16_U(X, 16, 32) \
     PQ_SHORT16_U(X, 16, 1) PQ_SHORT16_U(X, 16, 2) PQ_SHORT16_U(X, 16, 3) PQ_SHORT16_U(X, 16, 4) PQ_SHORT16_U(X, 16, 5) PQ_SHORT16_U(X, 16, 6)
-// scan_long_kernel<M, CW, C>
 // scan_bytes_kernel<M, CW, STAMP> instances (measurement: m = 8)
-#define PQ_BYTES_INSTANCES(X) X(4, 1, false) X(8, 1, false) X(16, 1, false) X(32, 1, false) X(64, 1, false) X(8, 1, true) X(4, 2, false) X(8, 2, false) X(16, 2, false)
+#define PQ_BYTES_INSTANCES(X) \
+    X(4, 1, false) X(8, 1, false) X(16, 1, false) X(32, 1, false) X(64, 1, false) X(4, 2, false) X(8, 2, false) X(16, 2, false) X(8, 1, true)
+// scan_long_kernel<M, CW, C>
 #define PQ_LONG_INSTANCES(X) \
     X(4, 1, kTableCopies) X(8, 1, kTableCopies) X(16, 1, 1) X(32, 1, 1) X(64, 1, 1) X(4, 2, 1) X(8, 2, 1) X(16, 2, 1)
 // scan_subset_kernel<M, U, NT>: rows of 4, 8, 16 bytes, every number of vectors per thread

@@ -1365,7 +1365,15 @@ int enqueue_scan(const ScanPlan& p, const uint8_t* codes, const float* S, long l
             hipError_t err = allow_lds(kernel, p.scan_dyn_lds);
             return err != hipSuccess ? err : launch(kernel, dim3(p.nblk, B), kBytesThreads, p.scan_dyn_lds, st, a);
         };
-        return record_hip(stamps != nullptr ? go(scan_bytes_kernel<8, 1, true>) : cw == 2 ? (m == 4 ? go(scan_bytes_kernel<4, 2>) : m == 8 ? go(scan_bytes_kernel<8, 2>) : go(scan_bytes_kernel<16, 2>)) : m == 4 ? go(scan_bytes_kernel<4>) : m == 8 ? go(scan_bytes_kernel<8>) : m == 16 ? go(scan_bytes_kernel<16>) : m == 32 ? go(scan_bytes_kernel<32>) : go(scan_bytes_kernel<64>));
+        if (stamps != nullptr) return record_hip(go(scan_bytes_kernel<8, 1, true>));
+        if (cw == 2) return record_hip(m == 4 ? go(scan_bytes_kernel<4, 2>) : m == 8 ? go(scan_bytes_kernel<8, 2>) : go(scan_bytes_kernel<16, 2>));
+        switch (m) {
+            case 4: return record_hip(go(scan_bytes_kernel<4>));
+            case 8: return record_hip(go(scan_bytes_kernel<8>));
+            case 16: return record_hip(go(scan_bytes_kernel<16>));
+            case 32: return record_hip(go(scan_bytes_kernel<32>));
+            default: return record_hip(go(scan_bytes_kernel<64>));
+        }
     }
     if (p.short_scan && cw == 2) {
         if (stamps != nullptr) return PQ_ERR_UNSUPPORTED;

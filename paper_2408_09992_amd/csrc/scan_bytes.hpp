@@ -7,7 +7,8 @@
 // What bounds the exact scans is the LDS: random four-byte lookups in tables of 1 KB per split collide in its banks (9 to 10 return per clock and
 // CU, 14 from sixteen copies).  A table of 256 BYTES is 64 words, two to a bank of 32: lanes that look up the same word are served together, so a lookup
 // collides two ways at most: 15 return per clock and CU (48 % of the LDS's cycles are conflicts), as from sixteen copies of the exact tables, which only rows of eight
-// and fewer have room for and whose 128 KB take 5 us to write.  A scan of 400 MB of codes that only adds such bytes up takes 66.3 us at m = 8 (71.7 at 64), one that only reads them 65.0.
+// and fewer have room for and whose 128 KB take 5 us to write.  (This kernel without floors, lists and exact scores, which only adds such bytes up, took 66.3 us for 400 MB of codes at
+// m = 8 and 71.7 at 64, without the lookups too 65.0.)
 // A byte counts steps above a base of its split, rounded up: an item's sum of counts bounds its score from above.  One query's sums are added in
 // 32 bits, so the counts use all 256 values whatever the row length is.  Items whose sum is below T, the floor's image, cannot reach the
 // floor; a wave with any other scores its vector exactly, by the same left-to-right fp32 chain as everywhere, and only exact scores enter lists, floors

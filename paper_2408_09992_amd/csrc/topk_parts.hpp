@@ -382,7 +382,7 @@ __device__ void rank_select(uint64_t* cand, int C, int K, uint64_t* dst, int tid
                (p3.x > mine) + (p3.y > mine);
     };
     if (C8 * 4 <= NT) {
-        const int t = tid >> 2, part = tid & 3;              // (C8 is a multiple of 8: a wave is all in or all out)
+        const int t = tid >> 2, part = tid & 3;              // (four lanes that add up are all in or all out)
         if (t < C8) {
             const uint64_t mine = cand[t];
             uint32_t rank = 0;

@@ -27,7 +27,7 @@ def compiled(obj, tmp):
 def test_scans_by_bounds_and_by_pairs_keep_nothing_in_scratch_memory(pqlib_path, tmp_path):
     from paper_2408_09992_amd import build
     objects = sorted(glob.glob(os.path.join(build.OBJ, "inst_filter_*.o")) + glob.glob(os.path.join(build.OBJ, "inst_scan_pair_*.o")) +
-                     glob.glob(os.path.join(build.OBJ, "inst_scan_subset_pair.o")))
+                     glob.glob(os.path.join(build.OBJ, "inst_scan_subset_pair.o")) + glob.glob(os.path.join(build.OBJ, "inst_scan_bytes.o")))
     if not objects:
         pytest.skip("the library was built elsewhere")
     found = {}
