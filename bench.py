@@ -531,8 +531,8 @@ def rules_mode(args):
                 row("segments", kind, N, 1, m, b, K, (64, 1), ("segments", "general"))
     # one query by one-byte bounds (mask bit 10) or without (bit 9): lines in bytes of codes; several catalogues in turn, more than the caches hold
     for kind, m, b, lines in (("scan", 4, 256, ((10, 4.4e7), (100, 7.0e7))), ("scan", 8, 256, ((10, 5.2e7), (100, 1.1e8), (256, 1.4e8), (512, 1.8e8))),
-                              ("scan", 16, 256, ((10, 8.8e7), (100, 1.1e8), (256, 1.4e8))), ("scan", 32, 256, ((10, 8.0e7), (100, 1.5e8))), ("scan", 64, 256, ((10, 2.7e8), (100, 2.7e8), (256, 4.0e8))),
-                              ("scan16", 4, 1500, ((10, 1.5e8),)), ("scan16", 8, 1024, ((10, 3.0e8), (100, 3.0e8))), ("scan16", 16, 300, ((10, 2.0e8), (100, 2.0e8))), ("scan16", 8, 2500, ((10, 4.5e8),))):
+                              ("scan", 16, 256, ((10, 1.0e8), (100, 1.4e8), (256, 2.5e8))), ("scan", 32, 256, ((10, 1.35e8), (100, 1.5e8), (256, 3.2e8))), ("scan", 64, 256, ((10, 2.5e9),)),
+                              ("scan16", 4, 1500, ((10, 2.0e8),)), ("scan16", 8, 1024, ((10, 3.0e8), (100, 3.0e8))), ("scan16", 16, 300, ((10, 2.0e8), (100, 2.0e8))), ("scan16", 8, 2500, ((10, 4.5e8),))):
         for K, line in lines:
             for f in (0.5, 0.8, 1.25, 2.0):
                 row("bytes", kind, int(f * line / (m * (2 if kind == "scan16" else 1))), 1, m, b, K, (1024, 512), ("bytes", "without"), 9.0e8)
@@ -603,7 +603,7 @@ def tables_mode(args):
               ("scan", 5_000_000, 16, 16, 256, 10), ("scan", 2_000_000, 48, 16, 256, 100), ("scan", 50_000_000, 32, 8, 256, 10), ("scan", 1_000_000, 40, 64, 256, 10),
               ("subset", 400_000, 64, 8, 256, 10), ("scan16", 1_280_000, 32, 8, 1024, 10),
               ("scan", 40_000_000, 1, 4, 256, 10), ("scan", 50_000_000, 1, 8, 256, 10), ("scan", 50_000_000, 1, 8, 256, 100), ("scan", 28_000_000, 1, 8, 256, 512),
-              ("scan", 20_000_000, 1, 16, 256, 100), ("scan", 8_000_000, 1, 32, 256, 10), ("scan", 8_000_000, 1, 64, 256, 10), ("scan16", 45_000_000, 1, 8, 1024, 10)]
+              ("scan", 20_000_000, 1, 16, 256, 100), ("scan", 8_000_000, 1, 32, 256, 10), ("scan", 40_000_000, 1, 64, 256, 10), ("scan16", 45_000_000, 1, 8, 1024, 10)]
     kinds = ["normal", "a third of the queries zero", "one entry -1e4", "one entry per split -1e9", "one entry the lowest float", "half a split -1e9",
              "one entry +1e4", "... that five items have", "all entries + 1e4", "all entries + 1e7", "denormal", "Cauchy", "whole numbers", "seven rows", "rows sorted"]
     for kind, N, B, m, b, K in shapes:

@@ -194,25 +194,28 @@ bool subset_direct_pays(long long N, int m, int B) {
 }
 
 // Bytes of codes from which one query's catalogue is scanned by one-byte bounds (scan_bytes_kernel): before that its sample, counts and lists per wave
-// weigh more than the lookups and the uneven rounds that it saves.  Calls without and with (us; several catalogues in turn, so that no cache holds the codes; in brackets where one
-// catalogue over and over says something else), just below the lines and further on: m = 4: 8M items, K = 10 16.4 and 17.2, 11M 19.5 and 18.8, K = 100 25.4 and 25.8, 17.5M 32.3 and 30.1,
-// K = 512 14M 39.1 and 45.0, 22M 56.3 and 52.3; m = 8: 5M, K = 10 17.7 and 18.0, 6.5M 22.7 and 19.8, K = 100 10M 31.1 and 31.2, 13.8M 36.7 and 35.4, K = 256 13.8M 41.6 and 41.9, 17.5M 48.5 and 46.8, K = 512
-// 13.8M 46.8 and 54.5, 22.5M 68.9 and 66.9; m = 16: 4M, K = 10 20.7 and 21.2, 5.5M 25.1 and 24.2, K = 100 5.5M 29.3 and 31.5, 7M 36.2 and 34.9, K = 256 7M 39.3 and 40.9, 9M 47.4 and 46.4; m = 32: 2M, K = 10
-// 22.5 and 22.1 (21.6 and 21.8), 2.5M 25.5 and 24.1, K = 100 3.2M 33.9 and 34.2, 4.7M 49.1 and 40.4, K = 256 3.2M 36.4 and 39.4, 6M 55.8 and 53.4; m = 64, from where the short kernel ends: 3.5M, K = 10 49.4 and
-// 51.3 (48.9 and 46.5), 4.2M 61.9 and 60.0 (61.2 and 52.8), K = 100 3.5M 54.0 and 56.9, 4.2M 66.5 and 63.5, K = 256 4.2M 70.6 and 71.4, 7M 100.4 and 98.1.
+// weigh more than the lookups and the uneven rounds that it saves.  Popular sub-ids (codes by Zipf(1.1)) collide less in exact tables, so the lines of long rows and many results lie where these
+// gain too.  Calls without and with (us; uniform codes from several catalogues in turn, so that no cache holds them; Zipf: one catalogue), just below the lines and further on:
+// m = 4: 8M items, K = 10 16.4 and 17.2, 11M 19.5 and 18.8, Zipf 19.4 and 18.6, K = 100 25.4 and 25.8, 17.5M 32.3 and 30.1, K = 512 14M 39.1 and 45.0, 22M 56.3 and 52.3;
+// m = 8: 5M, K = 10 17.7 and 18.0, 6.5M 22.7 and 19.8, Zipf 20.2 and 19.2, K = 100 10M 31.1 and 31.2, 13.8M 36.7 and 35.4, Zipf 35.7 and 34.7, K = 256 13.8M 41.6 and 41.9, 17.5M 48.5 and 46.8, Zipf 47.5 and 46.2,
+// K = 512 13.8M 46.8 and 54.5, 22.5M 68.9 and 66.9, Zipf 67.1 and 65.4;
+// m = 16: Zipf, K = 10 6M 23.7 and 24.4, 6.5M (no longer the short kernel) 29.4 and 25.5, uniform 7M 33.6 and 27.3; K = 100 8M 35.3 and 35.8, 9M 39.9 and 38.4, uniform 43.9 and 39.6; K = 256 14M 56.2 and 56.8, 16M
+// 61.4 and 61.3, uniform 66.4 and 61.9;
+// m = 32: Zipf, K = 10 4M 29.1 and 29.2, 4.5M (likewise) 34.7 and 31.6, uniform 4.7M 39.5 and 34.1; K = 100 4.7M 44.8 and 39.1, uniform 3.2M 33.9 and 34.2; K = 256 8M 57.9 and 61.5, 10M 72.1 and 70.7, uniform 78.8 and 71.9;
+// m = 64: Zipf, K = 10 9M 104.0 and 107.8, 20M 219 and 222, 40M 429 and 424, uniform 9M 112.6 and 108.8, 40M 443 and 424; K = 100 and 256 alike.
 // Two bytes: what they gain is the memory's rate (units of one vector, 6.3 TB/s instead of 5.9), the less the larger the tables that come first, and nothing while the last-level cache holds the
-// codes.  m = 4, b = 1500: 14M, K = 10 29.1 and 29.1, 18M 34.3 and 33.7 (32.4 and 32.6); b = 3500: 30M 50.3 and 49.1 (47.1 and 47.2), 56M 85.6 and 80.8; m = 8, b = 1024: 12.5M 40.8 and 41.4 (38.3 and 39.7), 16M 50.1 and
-// 50.3 (46.6 and 48.7), 45M 126.4 and 120.5; b = 1500: 20M 61.3 and 60.2 (60.1 and 59.8), 30M 88.5 and 85.0; m = 16, b = 300: 4M 29.2 and 31.5, 6.3M 43.6 and 42.0, K = 100 51.8 and 46.3; b = 800: 10M,
-// K = 10 62.9 and 63.5, 15M 88.7 and 89.6.
+// codes (in brackets: one catalogue over and over).  m = 4, b = 1500: 14M, K = 10 29.1 and 29.1, 19M (33.4 and 33.9), 30M (46.9 and 45.1); b = 3500: 30M 50.3 and 49.1 (47.1 and 47.2), 60M 89.8 and 85.4; m = 8, b = 1024:
+// 12.5M 40.8 and 41.4 (38.3 and 39.7), 16M 50.1 and 50.3 (46.6 and 48.7), 19M 56.2 and 55.2, 45M 126.4 and 120.5; b = 1500: 20M 61.3 and 60.2 (60.1 and 59.8), 30M 88.5 and 85.0; m = 16, b = 300: 4M 29.2 and 31.5, 6.3M
+// 43.6 and 42.0, K = 100 51.8 and 46.3; b = 800: 10M, K = 10 62.9 and 63.5, 15M 88.7 and 89.6.  Zipf codes give the same there.
 bool bytes_pay(long long N, int m, int b, int K, int cw) {
     const double bytes = (double)N * m * cw;
-    if (cw == 2) return m * b <= 9000 ? bytes >= (m == 4 ? 1.5e8 : m == 8 ? 3.0e8 : 2.0e8) : m < 16 && bytes >= 4.5e8;
+    if (cw == 2) return m * b <= 9000 ? bytes >= (m == 8 ? 3.0e8 : 2.0e8) : m < 16 && bytes >= 4.5e8;
     switch (m) {
         case 4: return bytes >= (K <= 16 ? 4.4e7 : K <= 256 ? 7.0e7 : 9.0e7);
         case 8: return bytes >= (K <= 16 ? 5.2e7 : K <= 128 ? 1.1e8 : K <= 256 ? 1.4e8 : 1.8e8);
-        case 16: return bytes >= (K <= 16 ? 8.8e7 : K <= 128 ? 1.1e8 : 1.4e8);
-        case 32: return bytes >= (K <= 16 ? 8.0e7 : K <= 128 ? 1.5e8 : 1.9e8);
-        case 64: return bytes >= (K <= 128 ? 2.7e8 : 4.0e8);
+        case 16: return bytes >= (K <= 16 ? 1.0e8 : K <= 128 ? 1.4e8 : 2.5e8);
+        case 32: return bytes >= (K <= 16 ? 1.35e8 : K <= 128 ? 1.5e8 : 3.2e8);
+        case 64: return bytes >= 2.5e9;
         default: return false;
     }
 }
