@@ -460,7 +460,7 @@ __device__ void block_select(const uint64_t* src, int n, int K, uint64_t* dst, u
     }
     __syncthreads();
     int C = ctl->ncand;
-    if (C <= candmax) {
+    if (n <= candmax || C <= candmax) {                      // (a caller whose src is no longer has none of what follows)
         rank_select<NT>(cand, C, K, dst, tid, hist, lo, scale);
         return;
     }
