@@ -848,14 +848,14 @@ void plan_filter(ScanPlan& p, long long N, int B, int m, int K, bool subset, int
     // 200,000 items, m = 4, K = 12 41 and 29 us; 478, 115,861, m = 8, K = 11 48 and 42; 300, 300,000, K = 26 52 and 56).  Where the workgroups
     // of a query share their floors those rise fast by themselves.  Over many items 7, since the sample reads runs of memory (calls with 5 and 7, us: 50M, m = 8, 32, K = 10 204.6 and
     // 200.6, 5M, 20 37.9 and 37.6, m = 16, 16 44.5 and 44.0, 13M, m = 4, 24, K = 39 51.8 and 50.6; 1.28M, m = 8, 64 31.3 and 31.9; m = 64, 6M, 8 157.7 and 159.3), but not for up to sixteen queries, whose sixteen parts have a
-    // compute unit each, by more rounds of these (8.5M, m = 8, 3, K = 39 30.4 and 31.6, K = 217 41.7 and 43.4; m = 16, 13M, 2, K = 39 56.9 and 59.9), nor for many results at m = 16 (2.6M, 40, K = 39 67.4 and 69.0,
+    // compute unit each, by more rounds of these (8.5M, m = 8, 3, K = 39 30.4 and 31.6, K = 217 41.7 and 43.4; m = 16, 13M, 2, K = 39 56.9 and 59.9, from nine queries on K = 10 8.5M, 16 61.2 and 60.2), nor for many results at m = 16 (2.6M, 40, K = 39 67.4 and 69.0,
     // 8.5M, 24 101.2 and 103.5).
     p.f_share = shares(nb);
     const long long items_per_round = (long long)p.f_sample * N / units;
     const bool few_of_many = K <= 16 && B > 128 && !subset && !p.f_share;
     auto rounds_of = [&](double times) -> long long { return (long long)(times * sqrt((double)K * (double)N)) / items_per_round; };
     long long want = rounds_of(few_of_many ? 8.0 : 5.0);
-    if (!few_of_many && !subset && N >= 2500000 && (m < 16 || (m == 16 && K <= 16))) want = B > 16 ? rounds_of(7.0) : std::max(want, std::min<long long>(rounds_of(7.0), 16));
+    if (!few_of_many && !subset && N >= 2500000 && (m < 16 || (m == 16 && K <= 16))) want = B > (m == 16 ? 8 : 16) ? rounds_of(7.0) : std::max(want, std::min<long long>(rounds_of(7.0), 16));
     // (... but at m = 32, where an exact score costs most, not within so short a time, if the catalogue is worth the sample: one round and four, 500,000 items, 480 queries,
     // K = 10 428 and 301, 800,000, 900, K = 20 1169 and 928, K = 30 (16-bit fields) 1139 and 1087; 200,000, 70, K = 100 66 and 80.  m = 16 with bytes alone, one and two: 900,
     // 500,000, K = 5 231 and 212)

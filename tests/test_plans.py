@@ -190,7 +190,7 @@ def test_one_byte_bounds_where_they_pay(plan, kind, m, b, K, N, by_bytes):
     assert (plan(kind, N, 1, m, b, K)["field_bits"] == 8) == by_bytes
 
 
-@pytest.mark.parametrize("N,B,m,K,rounds", [(8_500_000, 3, 8, 39, 1), (8_500_000, 3, 8, 217, 3), (4_400_000, 6, 8, 217, 2), (13_000_000, 2, 16, 39, 3), (24_000_000, 4, 4, 10, 1), (4_500_000, 40, 4, 217, 8), (24_000_000, 24, 4, 39, 5)])
+@pytest.mark.parametrize("N,B,m,K,rounds", [(8_500_000, 3, 8, 39, 1), (8_500_000, 3, 8, 217, 3), (4_400_000, 6, 8, 217, 2), (13_000_000, 2, 16, 39, 3), (8_500_000, 8, 16, 10, 1), (8_500_000, 16, 16, 10, 2), (24_000_000, 4, 4, 10, 1), (4_500_000, 40, 4, 217, 8), (24_000_000, 24, 4, 39, 5)])
 def test_a_few_queries_samples_grow_by_parts_not_by_rounds(plan, N, B, m, K, rounds):
     # up to sixteen queries have sixteen parts with a compute unit each: 8.5M items, m = 8, 3 queries, K = 39 30.4 us with one round of these, 31.6 with two; more queries gain by larger
     # samples (24M, m = 4, 24, K = 39 80.1 with four, 75.4 with five)
