@@ -532,7 +532,7 @@ def rules_mode(args):
     # one query by one-byte bounds (mask bit 10) or without (bit 9): lines in bytes of codes; several catalogues in turn, more than the caches hold
     for kind, m, b, lines in (("scan", 4, 256, ((10, 4.4e7), (100, 7.0e7))), ("scan", 8, 256, ((10, 5.2e7), (100, 1.1e8), (256, 1.4e8), (512, 1.8e8))),
                               ("scan", 16, 256, ((10, 1.0e8), (100, 1.4e8), (256, 2.5e8))), ("scan", 32, 256, ((10, 1.35e8), (100, 1.5e8), (256, 3.2e8))), ("scan", 64, 256, ((10, 2.5e9),)),
-                              ("scan16", 4, 1500, ((10, 2.0e8),)), ("scan16", 8, 1024, ((10, 3.0e8), (100, 3.0e8))), ("scan16", 16, 300, ((10, 2.0e8), (100, 2.0e8))), ("scan16", 8, 2500, ((10, 4.5e8),))):
+                              ("scan16", 4, 1500, ((10, 2.0e8),)), ("scan16", 8, 1024, ((10, 3.0e8), (100, 3.0e8))), ("scan16", 16, 300, ((10, 1.5e8), (100, 1.5e8))), ("scan16", 8, 2500, ((10, 4.5e8),))):
         for K, line in lines:
             for f in (0.5, 0.8, 1.25, 2.0):
                 row("bytes", kind, int(f * line / (m * (2 if kind == "scan16" else 1))), 1, m, b, K, (1024, 512), ("bytes", "without"), 9.0e8)

@@ -205,11 +205,11 @@ bool subset_direct_pays(long long N, int m, int B) {
 // m = 64: Zipf, K = 10 9M 104.0 and 107.8, 20M 219 and 222, 40M 429 and 424, uniform 9M 112.6 and 108.8, 40M 443 and 424; K = 100 and 256 alike.
 // Two bytes: what they gain is the memory's rate (units of one vector, 6.3 TB/s instead of 5.9), the less the larger the tables that come first, and nothing while the last-level cache holds the
 // codes (in brackets: one catalogue over and over).  m = 4, b = 1500: 14M, K = 10 29.1 and 29.1, 19M (33.4 and 33.9), 30M (46.9 and 45.1); b = 3500: 30M 50.3 and 49.1 (47.1 and 47.2), 60M 89.8 and 85.4; m = 8, b = 1024:
-// 12.5M 40.8 and 41.4 (38.3 and 39.7), 16M 50.1 and 50.3 (46.6 and 48.7), 19M 56.2 and 55.2, 45M 126.4 and 120.5; b = 1500: 20M 61.3 and 60.2 (60.1 and 59.8), 30M 88.5 and 85.0; m = 16, b = 300: 4M 29.2 and 31.5, 6.3M
-// 43.6 and 42.0, K = 100 51.8 and 46.3; b = 800: 10M, K = 10 62.9 and 63.5, 15M 88.7 and 89.6.  Zipf codes give the same there.
+// 12.5M 40.8 and 41.4 (38.3 and 39.7), 16M 50.1 and 50.3 (46.6 and 48.7), 19M 56.2 and 55.2, 45M 126.4 and 120.5; b = 1500: 20M 61.3 and 60.2 (60.1 and 59.8), 30M 88.5 and 85.0; m = 16, b = 300: 4M 29.2 and 31.5, 5M (no
+// longer the short kernel) 37.4 and 36.6, K = 100 46.0 and 41.0; b = 800: 10M, K = 10 62.9 and 63.5, 15M 88.7 and 89.6.  Zipf codes give the same there.
 bool bytes_pay(long long N, int m, int b, int K, int cw) {
     const double bytes = (double)N * m * cw;
-    if (cw == 2) return m * b <= 9000 ? bytes >= (m == 8 ? 3.0e8 : 2.0e8) : m < 16 && bytes >= 4.5e8;
+    if (cw == 2) return m * b <= 9000 ? bytes >= (m == 4 ? 2.0e8 : m == 8 ? 3.0e8 : 1.5e8) : m < 16 && bytes >= 4.5e8;
     switch (m) {
         case 4: return bytes >= (K <= 16 ? 4.4e7 : K <= 256 ? 7.0e7 : 9.0e7);
         case 8: return bytes >= (K <= 16 ? 5.2e7 : K <= 128 ? 1.1e8 : K <= 256 ? 1.4e8 : 1.8e8);

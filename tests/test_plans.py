@@ -185,7 +185,7 @@ def test_splits_in_device_memory_and_the_room_for_their_rows(plan, N, B, m, K, f
                                                    ("scan", 32, 256, 10, 3_000_000, False), ("scan", 32, 256, 10, 4_500_000, True), ("scan", 32, 256, 256, 8_000_000, False), ("scan", 32, 256, 256, 10_100_000, True),
                                                    ("scan", 64, 256, 10, 9_000_000, False), ("scan", 64, 256, 100, 40_000_000, True), ("scan16", 8, 1024, 10, 12_500_000, False), ("scan16", 8, 1024, 10, 16_000_000, False),
                                                    ("scan16", 8, 1024, 10, 45_000_000, True), ("scan16", 4, 1500, 10, 14_000_000, False), ("scan16", 4, 1500, 10, 30_000_000, True), ("scan16", 16, 800, 10, 15_000_000, False),
-                                                   ("scan16", 16, 300, 100, 6_300_000, True)])
+                                                   ("scan16", 16, 300, 100, 4_000_000, False), ("scan16", 16, 300, 100, 5_000_000, True)])
 def test_one_byte_bounds_where_they_pay(plan, kind, m, b, K, N, by_bytes):
     assert (plan(kind, N, 1, m, b, K)["field_bits"] == 8) == by_bytes
 
