@@ -331,8 +331,9 @@ def test_single_query_by_one_byte_bounds(pq, oracle, m, b, K):
             codes[N // 2:N // 2 + 40] = codes[:min(40, N - N // 2)]
             S = rng.standard_normal((1, m, b), dtype=np.float32)
             assert_same_topk(pq, oracle, codes, S, K, f"normal {N}")
-            if N < 2 * per_step:
-                continue                                       # (shorter: every item is in the sample, and no bound is looked at)
+            if N < 60_000:
+                continue
+            small = codes[:150_001]
             uneven = S * np.where(np.arange(m) == 1, np.float32(50.0), np.float32(0.02))[None, :, None]
             masked, far, deep = S.copy(), S.copy(), S.copy()
             masked[0, 1, :b // 3] = -1e9
@@ -341,11 +342,64 @@ def test_single_query_by_one_byte_bounds(pq, oracle, m, b, K):
             deep[0, 0, :-1] = -1e9
             for name, T in (("uneven", uneven), ("masked", masked), ("far entry", far), ("one entry of a split counts", deep), ("ties", np.round(S)), ("zeros", 0 * S), ("negative", S - 20),
                             ("offset", S + np.float32(1e7)), ("denormal", (np.abs(S) * np.float32(1e-41)).astype(np.float32))):
-                assert_same_topk(pq, oracle, codes, T.astype(np.float32), K, f"{name} {N}")
+                assert_same_topk(pq, oracle, small, T.astype(np.float32), K, f"{name} {N}")
+            infinite = np.where(S > 2.5, np.float32(np.inf), S)   # (the bar above subtracts: the bits alone)
+            ids, sc = run_topk(pq, small, infinite, K)
+            rid, rsc = oracle.score_topk(small, infinite, K)
+            assert np.array_equal(ids, rid) and np.array_equal(sc.view(np.uint32), rsc.view(np.uint32)), N
+    finally:
+        pq.pq_measure_force_general(prev)
+
+
+@pytest.mark.parametrize("m,b,K", [(4, 5, 3), (4, 1501, 10), (4, 5000, 100), (8, 300, 17), (8, 1024, 10), (8, 70, 256), (16, 257, 10), (16, 1000, 40)])
+def test_single_query_of_two_byte_sub_ids_by_one_byte_bounds(pq, oracle, m, b, K):
+    rng = np.random.default_rng(100 * m + b)
+    prev = pq.pq_measure_force_general(1024)
+    try:
+        for N in (max(K, 4), 300 + K, 70_001, 256 * 1024 * 2 + 64 * 17 + 1):
+            assert pq.pq_measure_plan("scan16", N, 1, m, b, K)["field_bits"] == 8
+            codes = rng.integers(0, b, (N, m), dtype=np.uint16)
+            codes[N // 2:N // 2 + 40] = codes[:min(40, N - N // 2)]
+            S = rng.standard_normal((1, m, b), dtype=np.float32)
+            assert_same_topk_u16(pq, oracle, codes, S, K, f"normal {N}")
+            if N != 70_001:
+                continue
+            masked, far = S.copy(), S.copy()
+            masked[0, 1, :b // 3] = -1e9
+            masked[0, m - 1, b // 2] = -np.inf
+            far[0, 2, 1] = 1e4
+            for name, T in (("masked", masked), ("far entry", far), ("ties", np.round(S)), ("zeros", 0 * S), ("offset", S + np.float32(1e7))):
+                assert_same_topk_u16(pq, oracle, codes, T.astype(np.float32), K, f"{name} {N}")
+    finally:
+        pq.pq_measure_force_general(prev)
+
+
+# ... over two steps and a tail, so that bounds are looked at (shorter: every item is in the sample, which is scored exactly)
+@pytest.mark.parametrize("wide,m,b,K", [(False, 4, 256, 10), (False, 4, 5, 40), (False, 8, 256, 1), (False, 8, 256, 100), (False, 8, 250, 512), (False, 16, 256, 10), (False, 16, 3, 17), (False, 32, 256, 16), (False, 64, 256, 10),
+                                        (True, 4, 5, 3), (True, 4, 1501, 10), (True, 4, 5000, 100), (True, 8, 300, 17), (True, 8, 70, 256), (True, 16, 257, 10), (True, 16, 1000, 40)])
+def test_single_query_by_one_byte_bounds_of_odd_tables_in_the_stream(pq, oracle, wide, m, b, K):
+    rng = np.random.default_rng(1000 * m + b + K)
+    N = 2 * 256 * 1024 * max(1, (8 if wide else 16) // m) + 64 * 17 + 1
+    same = assert_same_topk_u16 if wide else assert_same_topk
+    codes = rng.integers(0, b, (N, m), dtype=np.uint16 if wide else np.uint8)
+    codes[N // 2:N // 2 + 40] = codes[:40]
+    S = rng.standard_normal((1, m, b), dtype=np.float32)
+    masked, far, deep = S.copy(), S.copy(), S.copy()
+    masked[0, 1, :b // 3] = -1e9
+    masked[0, m - 1, b // 2] = -np.inf
+    far[0, 2, 1] = 1e4
+    deep[0, 0, :-1] = -1e9
+    prev = pq.pq_measure_force_general(1024)
+    try:
+        assert pq.pq_measure_plan("scan16" if wide else "scan", N, 1, m, b, K)["field_bits"] == 8
+        for name, T in (("normal", S), ("uneven", S * np.where(np.arange(m) == 1, np.float32(50.0), np.float32(0.02))[None, :, None]), ("masked", masked), ("far entry", far), ("one entry of a split counts", deep),
+                        ("ties", np.round(S)), ("zeros", 0 * S), ("negative", S - 20), ("offset", S + np.float32(1e7)), ("denormal", (np.abs(S) * np.float32(1e-41)).astype(np.float32))):
+            same(pq, oracle, codes, T.astype(np.float32), K, name)
+        if not wide:
             infinite = np.where(S > 2.5, np.float32(np.inf), S)   # (the bar above subtracts: the bits alone)
             ids, sc = run_topk(pq, codes, infinite, K)
             rid, rsc = oracle.score_topk(codes, infinite, K)
-            assert np.array_equal(ids, rid) and np.array_equal(sc.view(np.uint32), rsc.view(np.uint32)), N
+            assert np.array_equal(ids, rid) and np.array_equal(sc.view(np.uint32), rsc.view(np.uint32))
     finally:
         pq.pq_measure_force_general(prev)
 
@@ -370,29 +424,6 @@ def test_single_query_by_one_byte_bounds_that_dismiss_nothing(pq, oracle, wide, 
             same(pq, oracle, codes, T, K, name)
         codes[:, 0] = np.arange(N, dtype=np.int64) * b // N
         same(pq, oracle, codes, rising, K, "rising")
-    finally:
-        pq.pq_measure_force_general(prev)
-
-
-@pytest.mark.parametrize("m,b,K", [(4, 5, 3), (4, 1501, 10), (4, 5000, 100), (8, 300, 17), (8, 1024, 10), (8, 70, 256), (16, 257, 10), (16, 1000, 40)])
-def test_single_query_of_two_byte_sub_ids_by_one_byte_bounds(pq, oracle, m, b, K):
-    rng = np.random.default_rng(100 * m + b)
-    prev = pq.pq_measure_force_general(1024)
-    try:
-        for N in (max(K, 4), 300 + K, 70_001, 256 * 1024 * 2 * max(1, 8 // m) + 64 * 17 + 1):
-            assert pq.pq_measure_plan("scan16", N, 1, m, b, K)["field_bits"] == 8
-            codes = rng.integers(0, b, (N, m), dtype=np.uint16)
-            codes[N // 2:N // 2 + 40] = codes[:min(40, N - N // 2)]
-            S = rng.standard_normal((1, m, b), dtype=np.float32)
-            assert_same_topk_u16(pq, oracle, codes, S, K, f"normal {N}")
-            if N <= 70_001:
-                continue
-            masked, far = S.copy(), S.copy()
-            masked[0, 1, :b // 3] = -1e9
-            masked[0, m - 1, b // 2] = -np.inf
-            far[0, 2, 1] = 1e4
-            for name, T in (("masked", masked), ("far entry", far), ("ties", np.round(S)), ("zeros", 0 * S), ("offset", S + np.float32(1e7))):
-                assert_same_topk_u16(pq, oracle, codes, T.astype(np.float32), K, f"{name} {N}")
     finally:
         pq.pq_measure_force_general(prev)
 
