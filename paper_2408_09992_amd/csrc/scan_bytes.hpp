@@ -328,12 +328,17 @@ __global__ __launch_bounds__(kBytesThreads) void scan_bytes_kernel(ScanArgs a) {
     stamp<STAMP>(rec, kStampOffered, lane);
     // ---- stream
     int turn = wave, gap = NW;                                 // units until this wave's next turn; grows by a quarter
-    // Tables whose bounds say little let many lanes of most units pass: after three such units in a row, or some among others, a wave goes on without bounds for
-    // a while, each time for longer, and looks again.  (Few lanes of every unit, as many results have until floors have risen, cost less than doing without.
+    // Tables whose bounds say little let many lanes of most units pass: after three such units in a row a wave goes on without bounds for a while, each time for
+    // longer, and looks again (after the first such unit from then on).  (Few lanes of every unit, as many results have until floors have risen, cost less than doing without.
     // Bounds given up for good after 32 units of which any lane passes, which 30 units a wave never get to, and as it is: 8M items, m = 64, Cauchy 138 us and 115,
     // +1e4 140 and 113, denormal 171 and 139, m = 32 +1e4 77 and 64; 50M, m = 8, K = 100, ordinary 75.7 and 76.2.)
     constexpr int kManyLanes = 24, kMostCredit = 4, kMostRest = 64;
+    // (A wave has two units on its way, so whatever a unit does besides is waited for: one without hits sets the credit, one with few lanes too, and the loop has one bound.  A
+    // credit that every unit counts up or down and the loop asks for, and a K-th key compared with every unit's before: 40M, m = 8, K = 100 64.9 us, and 64.5 now; 28M, K = 512 74.4 and 73.7; 40M, m = 4, K = 100
+    // 42.9 and 42.6; tables whose bounds say little the same.)
+    const uint32_t per_step = (uint32_t)NT * (uint32_t)nblk, units = (total + per_step - 1) / per_step * NW;
     int credit = kMostCredit, rest = 16;
+    uint32_t until = units;                                    // 0: the loop at hand ends
     auto process = [&](auto bounded, const uint32_t (&w)[4 * VPI], uint32_t i) {
         top.floor_ge = fmaxf(top.floor_ge, lds_peek(&ctl->shared_floor));
         if (--turn < 0) {
@@ -368,12 +373,17 @@ __global__ __launch_bounds__(kBytesThreads) void scan_bytes_kernel(ScanArgs a) {
         }
         const uint32_t p = piece_of(i);
         const bool hit = any >= t && p <= last;
-        const uint64_t hits = __ballot(hit), before = top.thr;
+        const uint64_t hits = __builtin_amdgcn_ballot_w64(hit);
         if constexpr (decltype(bounded)::value) {
-            credit = __popcll(hits) >= kManyLanes ? credit - 2 : credit < kMostCredit ? credit + 1 : kMostCredit;
-            if (hits == 0) return;
-        } else {
-            --credit;
+            if (hits == 0) { credit = kMostCredit; return; }
+            if (__builtin_expect(__popcll(hits) >= kManyLanes, 0)) {
+                credit -= 2;
+                if (credit < 0) until = 0;
+            } else {
+                credit = kMostCredit;
+            }
+        } else if (--credit < 0) {
+            until = 0;
         }
         float sc[IPV];
         if (hit) score(w, sc);                                 // (the lookups of a few lanes collide less)
@@ -388,7 +398,8 @@ __global__ __launch_bounds__(kBytesThreads) void scan_bytes_kernel(ScanArgs a) {
         }
         // A list that has been sorted: K of its keys are no worse than the K-th, and what this wave has yet to see has higher ids than all of them, so
         // ties with the K-th come too late.  (All scores alike, 50M items, m = 8, K = 10: 1217 us without this, 115.)
-        if (__builtin_expect(top.thr != before, 0)) {
+        if (__builtin_expect(top.sorted, 0)) {
+            top.sorted = false;
             const float kth = score_of_key(top.thr);
             if (lane == 0 && kth > lds_peek(&ctl->shared_floor)) lds_poke(&ctl->shared_floor, kth);
             top.floor_ge = fmaxf(top.floor_ge, next_up(kth));
@@ -397,11 +408,10 @@ __global__ __launch_bounds__(kBytesThreads) void scan_bytes_kernel(ScanArgs a) {
     // Units are handed out by a counter in LDS: waves that fall behind do not hold the others up.  (A request is answered a unit later.)
     int pending = 0;
     auto request = [&]() { if (lane == 0) pending = (int)__builtin_amdgcn_atomic_inc32(reinterpret_cast<uint32_t*>(&ctl->next_unit), ~0u, __ATOMIC_RELAXED, "workgroup"); };
-    const uint32_t per_step = (uint32_t)NT * (uint32_t)nblk, units = (total + per_step - 1) / per_step * NW;
     request();
     bool seen = wave < sampling;
     auto stream = [&](auto bounded) {
-        while (unit[0] < units && credit >= 0) {               // (slot 0 holds the older one)
+        while (unit[0] < until) {                              // (slot 0 holds the older one)
 #pragma unroll
             for (int i = 0; i < 2; ++i) {
                 if (!seen && unit[i] < units) process(bounded, w[i], unit[i]);
@@ -415,9 +425,11 @@ __global__ __launch_bounds__(kBytesThreads) void scan_bytes_kernel(ScanArgs a) {
     while (unit[0] < units) {
         stream(std::true_type());
         credit = rest;
+        until = units;
         rest = rest < kMostRest ? 2 * rest : kMostRest;
         stream(std::false_type());
         credit = 0;
+        until = units;
     }
     if constexpr (P <= 16) {
         // the fewer than 16 / P items after the last whole code vector, one per lane of one wave

@@ -173,6 +173,7 @@ struct WaveTopK {
     int cnt;             // keys in the list (wave-uniform)
     uint64_t thr;        // K-th best key of the list once known, else 0
     float floor_ge;      // a score must be >= this to be worth appending
+    bool sorted = false; // append() has sorted the list (for those who ask: they clear it)
 
     // lanes in `mask` (non-empty, = ballot(take)) append the key of (score, id)
     __device__ __forceinline__ void append(uint64_t mask, bool take, float score, uint32_t id, int lane) {
@@ -181,6 +182,7 @@ struct WaveTopK {
         if (cnt + n > cap) {                                  // rare: make room by sorting and keeping the K best
             const uint64_t kth = sort_wave_list(buf, cap, cnt, K, lane);
             if (cnt >= K) { cnt = K; thr = kth; floor_ge = fmaxf(floor_ge, score_of_key(thr)); }
+            sorted = true;
             take = take && key > thr;
             mask = __ballot(take);
             if (mask == 0) return;

@@ -170,6 +170,7 @@ inline uint64_t wall_clock64() { return 0; }
 #define gridDim emu::grid
 #define __syncthreads() emu::stop(emu::kAtBarrier, {__FILE__, __LINE__})
 #define __ballot(p) emu::ballot(p, __LINE__)
+#define __builtin_amdgcn_ballot_w64(p) emu::ballot(p, __LINE__)
 #define __popcll(x) __builtin_popcountll(x)
 #define __HIP_MEMORY_SCOPE_WORKGROUP 0
 #define __hip_atomic_load(p, order, scope) (*(p))
